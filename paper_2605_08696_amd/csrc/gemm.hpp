@@ -6,7 +6,8 @@
 //     (v_mfma_f32_32x32x16_bf16, fp32 accumulate); tiles go global -> LDS with
 //     buffer_load ... lds into a 16-byte XOR-swizzled layout, two LDS stages,
 //     operands read from LDS two k-substeps ahead of the MFMAs that use them.
-//   gemm_f32_kernel: plain fp32 FMA tiles for the fp32 configurations.
+//   gemm_f32_kernel: plain fp32 FMA tiles of fp32 operands of any size and alignment
+//     (gemm_f32.hpp holds the matrix-core kernels that the fp32 models run).
 //
 // Epilogues are fused: bias, exact GELU, residual add into the fp32 stream,
 // and for the LM head a per-tile (max, index) partial so that logits need not

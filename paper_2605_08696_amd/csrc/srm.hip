@@ -14,6 +14,7 @@
 
 #include "srm.h"
 #include "gemm.hpp"
+#include "gemm_f32.hpp"
 #include "gemm_persist.hpp"
 #include "mega.hpp"
 #include "mixer.hpp"
@@ -599,6 +600,50 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     }
 }
 
+template <int EPI, int T, int NS>
+static int launch_f32_slices(const float *A, const float *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
+{
+    constexpr int smem = 4 * NS * 2 * T * f32gemm::BK * (int)sizeof(float);
+    auto kern = gemm_f32_slices_kernel<EPI, T, NS>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(cdiv(M, T) * cdiv(N, T))), dim3(256), smem, st, A, W, M, N, K, ep);
+    HIP_TRY(hipGetLastError());
+    return SRM_OK;
+}
+// The fp32 matrix-core kernels: which tile.  A launch of few tiles takes as long as one tile's trip through K, so
+// the tile shrinks until the launch covers the chip; the 64x64 tile needs about a tile per CU.  Measured (graph of
+// launches back to back; M x N x K: gemm_f32_kernel | 16 | 32 | 64, microseconds): 128 x 256 x 256: 28 | 3.1 | 4.5 |
+// 9.3; 128 x 256 x 1024: 98 | 4.4 | 8.1 | 25; 512 x 256 x 1024 (512 tiles of 16): 98 | 5.9 | 8.2 | 25; 1024 x 256 x
+// 1024 (1024 tiles of 16): 98 | 11 | 8.9 | 25; 1024 x 1024 x 256 (256 tiles of 64): 30 | 19 | 10.5 | 10.1;
+// 2048 x 256 x 1024 (128 tiles of 64): 124 | 20 | 14.9 | 25; 4096 x 4096 x 256: 134 | 293 | 134 | 99 (87 TFLOP/s of
+// the 157 the matrix cores peak at in fp32).  All tiles give the same bits (see gemm_f32.hpp).
+// LM head: always 64 columns per tile, which its partial winners are counted in.
+template <int EPI>
+static int launch_f32_tiles(const float *A, const float *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
+{
+    const int64_t t64 = cdiv(M, 64) * cdiv(N, 64), t32 = cdiv(M, 32) * cdiv(N, 32), t16 = cdiv(M, 16) * cdiv(N, 16);
+    if constexpr (EPI != EPI_ARGMAX) {
+        if (t16 <= 640) return launch_f32_slices<EPI, 16, 4>(A, W, M, N, K, ep, st);
+        if (t64 < 200) {
+            // one work-group per CU: a deeper ring; else two fit a CU
+            if (t32 <= 256) return launch_f32_slices<EPI, 32, 4>(A, W, M, N, K, ep, st);
+            return launch_f32_slices<EPI, 32, 2>(A, W, M, N, K, ep, st);
+        }
+    }
+    hipLaunchKernelGGL(gemm_f32_tile_kernel<EPI>, dim3((unsigned)t64), dim3(256), 0, st, A, W, M, N, K, ep);
+    HIP_TRY(hipGetLastError());
+    return SRM_OK;
+}
+// whole 16-byte vectors along K (and of the outputs' rows where N % 4 == 0), byte offsets within a descriptor
+static bool f32_tiles_ok(const float *A, const float *W, int K, const GemmEpi &ep)
+{
+    return K % 4 == 0 && K <= (1 << 20) && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)ep.out | (uintptr_t)ep.state) & 15) == 0;
+}
+
 template <int EPI>
 static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, GemmEpi ep, hipStream_t st,
                       int *nparts_out, int ksplit = 1)
@@ -613,6 +658,8 @@ static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, G
         // LM head are counted per 64 columns, or where 16 would make too many blocks)
         if (EPI == EPI_ARGMAX || N >= 16384) return launch_gemv_rows<float, float, EPI, 4>(A, W, (int)M, N, K, ep, st, ksplit, nparts_out);
         return launch_gemv_rows<float, float, EPI, 1>(A, W, (int)M, N, K, ep, st, ksplit, nparts_out);
+    } else if (f32_tiles_ok(A, W, K, ep)) {
+        return launch_f32_tiles<EPI>(A, W, (int)M, N, K, ep, st);
     } else {
         const int64_t nb = cdiv(M, 64) * cdiv(N, 64);
         hipLaunchKernelGGL(gemm_f32_kernel<EPI>, dim3((unsigned)nb), dim3(256), 0, st, A, W, (int)M, N, K, ep);

@@ -88,6 +88,16 @@ def test_linear_fp32(srm, shape, epi):
     _linear_case(srm, srm.SRM_FP32, M, N, K, epi, None, seed=M * 7 + epi)
 
 
+@pytest.mark.parametrize("shape", [(33, 16, 4), (49, 37, 36), (640, 256, 252), (641, 260, 1028), (300, 1500, 96),
+                                   (897, 899, 68), (1030, 832, 256)])
+@pytest.mark.parametrize("epi", [0, 1, 2, 3, 4])
+def test_linear_fp32_matrix_cores(srm, shape, epi):
+    """The fp32 MFMA kernels at the edges of their tiles: fewer k tiles than wavefronts, K and N that end inside a
+    tile, the last shape of the 16-wide tile and the first of the 32-wide one, its two ring depths, the 64-wide tile."""
+    M, N, K = shape
+    _linear_case(srm, srm.SRM_FP32, M, N, K, epi, None, seed=M * 3 + epi)
+
+
 @pytest.mark.parametrize("dtype_name", ["fp32", "bf16"])
 def test_argmax_ties_go_to_the_lowest_index(srm, dtype_name):
     dtype = srm.SRM_BF16 if dtype_name == "bf16" else srm.SRM_FP32
