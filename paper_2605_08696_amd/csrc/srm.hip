@@ -1783,7 +1783,7 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
         auto mix = [&](int l) {
             const LayerDev &y = m->layers[l];
             const dim3 grid((unsigned)cdiv(T_, 64), (unsigned)(m->Hs * cdiv(dh, 64)), (unsigned)nc);
-            hipLaunchKernelGGL((mixer_parallel_kernel<T>), grid, dim3(256), (size_t)T_ * sizeof(float), st,
+            hipLaunchKernelGGL((mixer_parallel_kernel<T>), grid, dim3(256), (size_t)(T_ + 1) * sizeof(float), st,
                                static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam,
                                m->cfg.n_ctx, m->Hs, m->hrow, dm, T_);
             HIP_TRY(hipGetLastError());

@@ -552,3 +552,19 @@ def test_extreme_shapes_match_oracle(srm, orc_mod, dtype_name, d, H, V, e):
     for b in range(B):
         tok, mg, mm = orc_mod.pick_topp(lg[b].cpu().numpy(), 0.9, 0.8, 4, 2, b, want_margins=True)
         assert int(tkn[b]) == tok or mm < 1e-5 or mg < 1e-5
+
+
+@pytest.mark.parametrize("T", [1, 5, 64, 65, 131, 257])
+def test_parallel_form_at_the_edges_of_its_blocks(srm, orc_mod, T):
+    """The block-wise triangular product: a block's own square, one and several blocks in front of it, positions that
+    end inside a group of four, and heads that are no multiple of 64 channels wide (104 = 64 + 40)."""
+    cfg = srm_synth.tiny_config(vocab=64, d_model=208, n_layers=2, n_heads=2, n_ctx=260, mlp_expansion=1)
+    w = srm_synth.make_weights(cfg, stress=True)
+    toks = srm_synth.make_prompts(cfg, batch=2, length=T, seed=T)
+    ref = orc_mod.Oracle(cfg, w, "f64").parallel_forward(toks)
+    model = srm.Model(cfg, w)
+    hid = torch.zeros((2, T, cfg.d_model), dtype=torch.float32, device="cuda")
+    print(f"parallel form T={T}", flush=True)
+    model.parallel_forward(to_dev(toks), hid, workspace=model.new_workspace(2 * T))
+    torch.cuda.synchronize()
+    assert np.abs(hid.cpu().numpy() - ref["hidden"]).max() <= 1e-4 * np.abs(ref["hidden"]).max()
