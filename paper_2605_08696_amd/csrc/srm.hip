@@ -16,6 +16,7 @@
 #include "gemm.hpp"
 #include "gemm_f32.hpp"
 #include "gemm_persist.hpp"
+#include "gemm_slices.hpp"
 #include "mega.hpp"
 #include "mixer.hpp"
 #include "norm.hpp"
@@ -348,15 +349,14 @@ struct Workspace {
     int *ctr;          // [2] position and step counters of srm_generate
     int *slow;         // [64 + rows] nucleus pass: count, then (from slow + 64) the rows that need the search
     unsigned char *mega;  // [kMegaScratch] one-kernel small-batch path: partial winners and the barrier words
-    float *part;       // [slices][rows][d] split-K slabs of a residual projection (rows <= kSplitMaxRows), else null
+    float *part;       // [slices][rows][d] slabs of a residual projection (rows <= kSplitMaxRows), else null
     size_t bytes;
 };
 
-// Split-K of the MLP down projection for small batches: with few token rows the
-// GEMM has too few tiles to fill the chip and a long serial k loop, so K is cut
-// into kSplitK slices whose fp32 slabs the following LayerNorm kernel adds to the
-// residual stream (in slab order: deterministic).
-constexpr int kSplitK = 4;
+// Slabs of a residual projection that the following LayerNorm kernel adds to the residual stream, in slab order
+// (deterministic).  One-kernel token mixing (at most kSplitMaxRows rows): d / 128 <= 4 slabs of the out-projection;
+// room for kSlabs.
+constexpr int kSlabs = 8;
 constexpr int64_t kSplitMaxRows = 2048;
 // fp32 models with at most kGemvRows rows run their projections as GEMVs, whose grid is only
 // N / 64 blocks: the two residual projections are cut into up to kGemvSplitMax K slices the same way.
@@ -388,8 +388,7 @@ static Workspace carve(const srm_model *m, void *base, int64_t rows)
     w.pi = reinterpret_cast<int32_t *>(take(r * nparts * 4));
     w.slow = reinterpret_cast<int *>(take(256 + r * 4));
     // sized so that the workspace grows monotonically with the row count
-    // (twice kSplitK slabs: the one-kernel token mixing writes its out-projection slabs behind the MLP's)
-    const size_t part_rows = std::max<size_t>((size_t)2 * kSplitK * std::min<int64_t>(rows, kSplitMaxRows),
+    const size_t part_rows = std::max<size_t>((size_t)kSlabs * std::min<int64_t>(rows, kSplitMaxRows),
                                               (size_t)kGemvSplitMax * std::min<int64_t>(rows, kGemvRows));
     float *part = reinterpret_cast<float *>(take(part_rows * d * 4));
     w.part = rows <= kSplitMaxRows ? part : nullptr;
@@ -407,8 +406,7 @@ extern "C" size_t srm_workspace_bytes(const srm_model *m, int64_t rows)
 
 // ------------------------------------------------------------------ launchers
 template <int BM, int BN, int WM, int WN, int EPI, typename TAct, int NS = 2>
-static int launch_bf16_tile(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st,
-                            int ksplit = 1)
+static int launch_bf16_tile(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
     constexpr size_t smem = (size_t)NS * (BM + BN) * 64 * sizeof(bf16);
     auto kern = gemm_bf16_kernel<BM, BN, WM, WN, EPI, TAct, NS>;
@@ -419,7 +417,7 @@ static int launch_bf16_tile(const bf16 *A, const bf16 *W, int M, int N, int K, c
         attr_set = true;
     }
     const int64_t nb = cdiv(M, BM) * cdiv(N, BN);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nb, (unsigned)ksplit), dim3(WM * WN * 64), smem, st, A, W, M, N, K, ep);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(WM * WN * 64), smem, st, A, W, M, N, K, ep);
     HIP_TRY(hipGetLastError());
     return SRM_OK;
 }
@@ -464,26 +462,6 @@ static int launch_bf16_persist(const bf16 *A, const bf16 *W, int M, int N, int K
     return SRM_OK;
 }
 
-// A handful of rows, LayerNorm made by the GEMM itself (see the LNA note in gemm.hpp): one row tile of 64x64
-// blocks, the normalised rows as a [K / 64][32][64] bf16 panel in LDS next to an eight-tile ring for W.
-template <int EPI>
-static int launch_bf16_lna(const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
-{
-    constexpr int NS = 8;
-    const size_t smem = (size_t)K * 64 + (size_t)NS * 64 * 64 * sizeof(bf16);
-    auto kern = gemm_bf16_kernel<64, 64, 2, 2, EPI, bf16, NS, true>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    1024 * 64 + NS * 64 * 64 * (int)sizeof(bf16)));
-        attr_set = true;
-    }
-    hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(N, 64), 1), dim3(256), smem, st, W /*A: unused*/, W, M, N, K, ep);
-    HIP_TRY(hipGetLastError());
-    return SRM_OK;
-}
-static bool lna_ok(int64_t M, int K) { return M <= kLnaRows && K <= 1024 && K % 64 == 0; }
-
 // Few rows: the streaming GEMV (gemv_rows_kernel), 16 * CPG columns per block.
 constexpr int kGemvMB = 8;                 // rows per pass over W
 constexpr size_t kGemvMaxLds = 128 * 1024;
@@ -513,28 +491,72 @@ static bool gemv_rows_ok(int64_t M, int K, int ksplit, int64_t max_rows)
     return M <= max_rows && K % (vw * ksplit) == 0 && (size_t)kGemvMB * (K / ksplit) * sizeof(float) <= kGemvMaxLds;
 }
 
+// The slice form (gemm_slices.hpp) with a tile of 16 RT x 16 CT and a ring of NS line steps per wavefront.
+template <int EPI, int RT, int CT, int NS, bool LNA = false>
+static int launch_slices_tile(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
+{
+    constexpr int rings = kSliceWaves * slices_wave_lds<RT, CT, NS, LNA>();
+    const int smem = rings + (LNA ? K / 64 * 2048 : 0);
+    auto kern = gemm_bf16_slices_kernel<EPI, RT, CT, NS, LNA>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    rings + (LNA ? 1024 / 64 * 2048 : 0)));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(cdiv(M, 16 * RT) * cdiv(N, 16 * CT))), dim3(kSliceWaves * 64), smem, st, A, W,
+                       M, N, K, ep);
+    HIP_TRY(hipGetLastError());
+    return SRM_OK;
+}
+// Whether a GEMM takes the slice form: while its 64x64 tiles number at most one per CU.  Measured (us, 64x64 or
+// 128x128 tile | slices): 256 x 4096 x 1024, 256 tiles: 8.4 | 6.9; 1024 x 1024 x 1024, 256: 8.5 | 7.0; 1024 x 1024 x
+// 4096, 256: 19.1 | 15.8; 1900 x 512 x 2048, 240: 12.2 | 9.7; 300 x 4096 x 1024, 320 tiles: 9.4 | 11.4; 3000 x 512 x
+// 512, 376: 7.5 | 9.7 (rows x columns x K).  M is the row count of the whole call: its sums run in another order than
+// those of the other tiles, and a call that the workspace cuts into passes should not change with the cut.
+static bool slices_ok(int64_t M, int N, int K)
+{
+    return N % 4 == 0 && K % 64 == 0 && cdiv(M, 64) * cdiv(N, 64) <= device_cus();
+}
+// ... and with which tile: the smallest whose tiles still fit the chip in one round, since the time of a work-group
+// is proportional to the cache lines it loads (us with tiles of 16x16 | 32x16 | 32x32 | 64x32 | 64x64: 64 x 1024 x
+// 4096: 5.2 | 6.5 | 7.6 | 10.5 | 14; 128 x 1024 x 4096 (512 tiles of 16x16): 8.6 | 6.6 | 7.5 | 10 | 14; 300 x 1024 x
+// 1024: 7.5 | 7.6 | 6.6 | 5.0 | 6.5; 1024 x 1024 x 1024: 18 | 18 | 12 | 8.7 | 7.0).  Every tile gives the same bits.
+template <int EPI>
+static int launch_slices(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
+{
+    const int cus = device_cus();
+    auto fits = [&](int rt, int ct) { return cdiv(M, 16 * rt) * cdiv(N, 16 * ct) <= cus; };
+    if (fits(1, 1)) return launch_slices_tile<EPI, 1, 1, 4>(A, W, M, N, K, ep, st);
+    if (fits(2, 1)) return launch_slices_tile<EPI, 2, 1, 2>(A, W, M, N, K, ep, st);
+    if (fits(2, 2)) return launch_slices_tile<EPI, 2, 2, 2>(A, W, M, N, K, ep, st);
+    if (fits(4, 2)) return launch_slices_tile<EPI, 4, 2, 1>(A, W, M, N, K, ep, st);
+    return launch_slices_tile<EPI, 4, 4, 1>(A, W, M, N, K, ep, st);
+}
+static bool lna_ok(int64_t M, int N, int K) { return M <= kLnaRows && K <= 1024 && K % 64 == 0 && N % 4 == 0; }
+
 // The 64x64 tile with few blocks on the chip: its k loop is bound by the latency of the tile loads, so
 // the LDS ring is deepened as far as the blocks per CU allow (8 stages = 128 KB: one block per CU;
 // 4 stages = 64 KB: two).
 template <int EPI, typename TAct>
-static int launch_bf16_small(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st,
-                             int ksplit)
+static int launch_bf16_small(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
-    const int64_t blocks = cdiv(M, 64) * cdiv(N, 64) * ksplit;
-    const int kt = K / ksplit / 64;
-    if (blocks <= 256 && kt > 4) return launch_bf16_tile<64, 64, 2, 2, EPI, TAct, 8>(A, W, M, N, K, ep, st, ksplit);
-    if (blocks <= 512 && kt > 2) return launch_bf16_tile<64, 64, 2, 2, EPI, TAct, 4>(A, W, M, N, K, ep, st, ksplit);
-    return launch_bf16_tile<64, 64, 2, 2, EPI, TAct>(A, W, M, N, K, ep, st, ksplit);
+    const int64_t blocks = cdiv(M, 64) * cdiv(N, 64);
+    const int kt = K / 64;
+    if (blocks <= 256 && kt > 4) return launch_bf16_tile<64, 64, 2, 2, EPI, TAct, 8>(A, W, M, N, K, ep, st);
+    if (blocks <= 512 && kt > 2) return launch_bf16_tile<64, 64, 2, 2, EPI, TAct, 4>(A, W, M, N, K, ep, st);
+    return launch_bf16_tile<64, 64, 2, 2, EPI, TAct>(A, W, M, N, K, ep, st);
 }
 
 // Tile codes of the bf16 GEMM: 0 = 256x256 (8 waves), 1 = 128x128 (4 waves),
 // 2 = 64x64 (4 waves), 3 = 128x128 (8 waves), 4 = 256x128 (8 waves); 5 .. 8 pin the
-// ring depth of a tile for sweeps, 9 / 10 pin the persistent / one-tile-per-work-group form of 256x256.  min_bn > 64 rules out the 64-wide tile (the LM
+// ring depth of a tile for sweeps, 9 / 10 pin the persistent / one-tile-per-work-group form of 256x256, 11 .. 15 the
+// slice form with tiles of 16x16, 32x16, 32x32, 64x32 and 64x64.  min_bn > 64 rules out the 64-wide tile (the LM
 // head's partial buffers are sized for column tiles >= 128).  Measured on C4's
 // shapes over 512 .. 16384 rows: the big tile wins once it fills most of the chip in
 // whole rounds (one block per CU: 384 tiles are two rounds at 75 %, and lose to 1536
 // tiles of 128x128); 128x128 wins over 64x64 from about 144 blocks on.
-constexpr int kNumTiles = 11;
+constexpr int kNumTiles = 16;
 static int choose_tile(int64_t M, int N, int K, int min_bn)
 {
     const int64_t t256 = cdiv(M, 256) * cdiv(N, 256), t128 = cdiv(M, 128) * cdiv(N, 128);
@@ -555,22 +577,17 @@ static thread_local int64_t g_clock_blocks = 0;
 
 template <int EPI, typename TAct>
 static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, GemmEpi ep, hipStream_t st,
-                       int min_bn, int *nparts_out, int ksplit = 1)
+                       int min_bn, int *nparts_out, int64_t call_rows)
 {
     if (K % 64) return fail(SRM_EINVAL, "bf16 GEMM needs K %% 64 == 0 (K = %d)", K);
-    if (ksplit > 1) {
-        // slices of whole 64-wide k tiles, fp32 slabs, small tiles (the point is to fill the chip)
-        if (EPI != EPI_F32 || K % (64 * ksplit)) return fail(SRM_EINVAL, "bf16 GEMM: bad split of K = %d", K);
-        if (M <= 0 || M >= (1 << 30) || N <= 0) return fail(SRM_EINVAL, "GEMM shape out of range");
-        ep.nparts = 0;
-        return launch_bf16_small<EPI, TAct>(A, W, (int)M, N, K, ep, st, ksplit);
-    }
     if (M <= 0 || M >= (1 << 30) || N <= 0) return fail(SRM_EINVAL, "GEMM shape out of range");
     if ((int64_t)K * 256 * 2 >= (1LL << 31)) return fail(SRM_EINVAL, "bf16 GEMM: K = %d too large", K);
+    const int m = (int)M;
+    if constexpr (EPI != EPI_ARGMAX)                 // (whose partial winners are counted per 128 columns or more)
+        if (g_force_tile < 0 && slices_ok(std::max(M, call_rows), N, K)) return launch_slices<EPI>(A, W, m, N, K, ep, st);
     const int tile = g_force_tile >= 0 ? g_force_tile : choose_tile(M, N, K, min_bn);
     ep.nparts = (int)cdiv(N, tile_bn(tile));
     if (nparts_out) *nparts_out = ep.nparts;
-    const int m = (int)M;
     switch (tile) {
     case 0:
         // more tiles than CUs: the persistent form, whose tiles after a CU's first start without a launch and
@@ -584,7 +601,7 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
         if (cdiv(M, 128) * cdiv(N, 128) <= 256 && K / 64 > 4)
             return launch_bf16_tile<128, 128, 2, 2, EPI, TAct, 4>(A, W, m, N, K, ep, st);
         return launch_bf16_tile<128, 128, 2, 2, EPI, TAct>(A, W, m, N, K, ep, st);
-    case 2: return launch_bf16_small<EPI, TAct>(A, W, m, N, K, ep, st, 1);
+    case 2: return launch_bf16_small<EPI, TAct>(A, W, m, N, K, ep, st);
     case 3: return launch_bf16_tile<128, 128, 2, 4, EPI, TAct>(A, W, m, N, K, ep, st);
     case 4: return launch_bf16_tile<256, 128, 4, 2, EPI, TAct>(A, W, m, N, K, ep, st);
     // sweeps only: a fixed ring depth
@@ -596,8 +613,20 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
         if (!persist_ok(M, N, K)) return fail(SRM_EINVAL, "the persistent GEMM does not take this shape");
         return launch_bf16_persist<EPI, TAct>(A, W, m, N, K, ep, st);
     case 10: return launch_bf16_tile<256, 256, 2, 4, EPI, TAct>(A, W, m, N, K, ep, st);
-    default: return fail(SRM_EINVAL, "unknown GEMM tile code %d", tile);
+    default: break;
     }
+    if constexpr (EPI != EPI_ARGMAX) {
+        if (N % 4) return fail(SRM_EINVAL, "the slice form needs N %% 4 == 0 (N = %d)", N);
+        switch (tile) {
+        case 11: return launch_slices_tile<EPI, 1, 1, 4>(A, W, m, N, K, ep, st);
+        case 12: return launch_slices_tile<EPI, 2, 1, 2>(A, W, m, N, K, ep, st);
+        case 13: return launch_slices_tile<EPI, 2, 2, 2>(A, W, m, N, K, ep, st);
+        case 14: return launch_slices_tile<EPI, 4, 2, 1>(A, W, m, N, K, ep, st);
+        case 15: return launch_slices_tile<EPI, 4, 4, 1>(A, W, m, N, K, ep, st);
+        default: break;
+        }
+    }
+    return fail(SRM_EINVAL, "GEMM tile code %d does not exist for this epilogue", tile);
 }
 
 template <int EPI, int T, int NS>
@@ -711,43 +740,37 @@ struct MixArgs {           // EPI_MIX: state slab of the layer and its coefficie
     int n_ctx = 0, hrow = 0, dh = 0, state_half = 0;
 };
 
-struct SlabArgs {          // slabs of a K-sliced projection that no kernel has added to the residual stream yet
-    const float *part = nullptr;
-    int nsplit = 0;
-    int64_t stride = 0;
-};
-struct LnArgs {            // A = LayerNorm(x [+ slabs]) made by the GEMM itself (bf16, a handful of rows)
+struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (bf16, a handful of rows)
     const float *x = nullptr, *g = nullptr, *b = nullptr;
-    SlabArgs slabs;
     float eps = 0.0f;
 };
 
-// out = epilogue(A W^T + bias) with operands of type T (float or bf16)
+// out = epilogue(A W^T + bias) with operands of type T (float or bf16).  call_rows: the rows of the whole call where
+// M is one of its passes (see slices_ok).
 template <int EPI, typename T>
 static int linear(const void *A, const void *W, const float *bias, int64_t M, int N, int K, void *out,
                   hipStream_t st, float *pv = nullptr, int32_t *pi = nullptr, int min_bn = 64,
                   int *nparts_out = nullptr, Sampling sm = Sampling(), int ksplit = 1, MixArgs mx = MixArgs(),
-                  SlabArgs add = SlabArgs(), LnArgs ln = LnArgs())
+                  int64_t call_rows = 0, LnArgs ln = LnArgs())
 {
     GemmEpi ep{bias, out, (int64_t)N, pv, pi, 0, sm.temp, sm.seed, sm.pos, sm.pos_dev, sm.pos_rows, sm.row_base,
                mx.state, mx.alpha, mx.beta, mx.lam, mx.n_ctx, mx.hrow, mx.dh, mx.state_half};
-    ep.add_part = add.part; ep.add_nsplit = add.part ? add.nsplit : 0; ep.add_stride = add.stride;
     ep.clk = g_clock_probe; ep.clk_blocks = g_clock_blocks;
-    if (add.part && EPI != EPI_RESID) return fail(SRM_EINVAL, "linear: pending slabs need the residual epilogue");
     if (ln.x) {
         if constexpr (sizeof(T) == 2 && (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_MIX)) {
-            if (!lna_ok(M, K) || ksplit != 1) return fail(SRM_EINVAL, "linear: LayerNorm-on-load needs M <= %d, K <= 1024", kLnaRows);
+            if (M <= 0 || N <= 0 || !lna_ok(M, N, K))
+                return fail(SRM_EINVAL, "linear: LayerNorm-on-load needs at most %d rows, K <= 1024, N %% 4 == 0", kLnaRows);
             ep.ln_x = ln.x; ep.ln_g = ln.g; ep.ln_b = ln.b; ep.ln_eps = ln.eps;
-            ep.ln_part = ln.slabs.part; ep.ln_nsplit = ln.slabs.part ? ln.slabs.nsplit : 0; ep.ln_stride = ln.slabs.stride;
-            ep.nparts = 0;
-            return launch_bf16_lna<EPI>(static_cast<const bf16 *>(W), (int)M, N, K, ep, st);
+            // (the ring holds W only: four line steps of it are 64 KB)
+            return launch_slices_tile<EPI, 1, 1, 4, true>(static_cast<const bf16 *>(W), static_cast<const bf16 *>(W), (int)M, N,
+                                                          K, ep, st);
         } else {
             return fail(SRM_EINVAL, "linear: LayerNorm-on-load exists for bf16 store / GELU / mixer epilogues only");
         }
     }
     if constexpr (sizeof(T) == 2)
         return launch_bf16<EPI, bf16>(static_cast<const bf16 *>(A), static_cast<const bf16 *>(W), M, N, K, ep,
-                                      st, min_bn, nparts_out, ksplit);
+                                      st, min_bn, nparts_out, call_rows);
     else
         return launch_f32<EPI>(static_cast<const float *>(A), static_cast<const float *>(W), M, N, K, ep, st,
                                nparts_out, ksplit);
@@ -860,28 +883,28 @@ static bool fuse_mixer(const srm_model *m, int64_t rows)
 }
 
 // A handful of samples of a bf16 model: every LayerNorm between two GEMMs of the step is made by the GEMM
-// that consumes it (gemm_bf16_kernel's LNA form) instead of a launch of its own - with one row the
-// LayerNorm launches are a quarter of the step's time.  SRM_LN_ON_LOAD=0 in the environment keeps the
-// separate kernels.
+// that consumes it (gemm_bf16_slices_kernel's LNA form) instead of a launch of its own.  Where the token mixing of a
+// layer can be one kernel, that is the shorter step from kTokMixMinRows rows on.  SRM_LN_ON_LOAD=0 in the environment
+// keeps the separate kernels.
+constexpr int64_t kTokMixMinRows = 9;
+static bool token_mix_shape_ok(const srm_model *m)
+{
+    return m->wsize == 2 && !m->noproj && m->dm == m->d && (m->d == 256 || m->d == 512);
+}
 static bool ln_on_load(const srm_model *m, int64_t rows)
 {
-    if (m->wsize != 2 || m->noproj || !lna_ok(rows, m->d)) return false;
+    if (m->wsize != 2 || m->noproj || !lna_ok(rows, m->dm, m->d)) return false;
+    if (token_mix_shape_ok(m) && rows >= kTokMixMinRows) return false;
     const char *e = getenv("SRM_LN_ON_LOAD");
     return !(e && e[0] == '0');
 }
 
 // A dozen to about a thousand rows of a bf16 model with head projections: LayerNorm1, in-projection, state
 // update and out-projection of a layer are one kernel (tokmix.hpp), which leaves the out-projection as d / 128
-// slabs behind the slabs that the previous layer's K-sliced MLP-down projection may have left; the LayerNorm2
-// kernel adds all of them to x.  Taken while its work-groups (16 rows x 128 columns each) fit the chip in one
+// slabs; the LayerNorm2 kernel adds them to x.  Taken while its work-groups (16 rows x 128 columns each) fit the chip in one
 // round: measured on C3's model (d 512, L 8) per step 0.280 -> 0.248 ms at 16 rows, 0.298 -> 0.260 at 64,
 // 0.318 -> 0.285 at 256, 0.353 -> 0.310 at 512, 0.378 -> 0.361 at 1024, and 0.473 -> 0.512 at 2048 (two rounds).
 // SRM_TOKEN_MIX=0 in the environment keeps the separate kernels, =1 takes the one kernel wherever it can run.
-constexpr int64_t kTokMixMinRows = 9;
-static bool token_mix_shape_ok(const srm_model *m)
-{
-    return m->wsize == 2 && !m->noproj && m->dm == m->d && (m->d == 256 || m->d == 512);
-}
 static bool token_mix_one_kernel(const srm_model *m, int64_t rows)
 {
     if (!token_mix_shape_ok(m) || ln_on_load(m, rows) || rows > kSplitMaxRows) return false;   // (w.part: see carve)
@@ -893,7 +916,6 @@ static bool token_mix_one_kernel(const srm_model *m, int64_t rows)
 }
 struct TokMixCall {
     const float *x;
-    SlabArgs pending;
     void *state;
     Sampling where;
     float *slabs;          // [d / 128][rows][d]
@@ -903,9 +925,6 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
     const LayerDev &y = m->layers[l];
     TokMixArgs a{};
     a.x = c.x;
-    a.pend = c.pending.nsplit > 0 ? c.pending.part : nullptr;
-    a.npend = c.pending.nsplit > 0 ? c.pending.nsplit : 0;
-    a.pend_stride = c.pending.stride;
     a.ln1_g = y.ln1_g; a.ln1_b = y.ln1_b;
     a.eps = m->cfg.ln_eps;
     a.w_in = static_cast<const bf16 *>(y.w_in); a.w_out = static_cast<const bf16 *>(y.w_out);
@@ -942,63 +961,38 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
 // w.a holds LayerNorm1(x) of this layer; mix(l) turns w.u into w.mx.  With
 // norm_next, w.a leaves holding the next layer's LayerNorm1(x), or the final
 // LayerNorm after the last layer.
-// With pend (decode of a handful of rows, see ln_on_load): no LayerNorm kernels between the GEMMs.  From
-// layer 1 on w.a is not used: the in- and up-projection normalise the rows of w.x themselves, *pend says how
-// many slabs of the previous layer's K-sliced MLP-down projection still wait in w.part (the in-projection
-// adds them for its LayerNorm, the out-projection's residual epilogue adds them to w.x), and on return it
-// holds this layer's count.  Layer 0 enters with w.a from the embedding kernel as usual.
+// With lnf (decode of a handful of rows, see ln_on_load): no LayerNorm kernels between the GEMMs.  From layer 1 on w.a
+// is not used: the in- and up-projection normalise the rows of w.x themselves.  Layer 0 enters with w.a from the
+// embedding kernel as usual.  With one_mix (see token_mix_one_kernel) w.a on entry is not used either.
+// call_rows: the rows of the whole call (rows are one of its passes; see slices_ok).
 template <typename T, typename MIX>
-static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, hipStream_t st, MIX &&mix,
+static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, int64_t call_rows, hipStream_t st, MIX &&mix,
                  bool norm_next, bool allow_split = false, void *fuse_state = nullptr, Sampling fuse_pos = Sampling(),
-                 void *np_state = nullptr, int *pend = nullptr, int *tm_pend = nullptr)
+                 void *np_state = nullptr, bool lnf = false, bool one_mix = false)
 {
     const LayerDev &y = m->layers[l];
     const int d = m->d, dm = m->dm, ff = m->ff;
-    const bool lnf = pend != nullptr;
-    const SlabArgs waiting = lnf && *pend > 0 ? SlabArgs{w.part, *pend, (int64_t)rows * d} : SlabArgs();
-    const LnArgs ln1 = lnf && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, waiting, m->cfg.ln_eps} : LnArgs();
-    const LnArgs ln2 = lnf ? LnArgs{w.x, y.ln2_g, y.ln2_b, SlabArgs(), m->cfg.ln_eps} : LnArgs();
-    // K slices of a residual projection (decode with few rows; see kSplitK).  bf16: the MLP down projection in
-    // kSplitK slices while the 64x64 tiles number at most 192 (measured: more slices, or slicing the
-    // out-projection too, costs more in the LayerNorm that adds the slabs than the shorter k loops save;
-    // since the unsplit tile runs on a deep LDS ring the two arrangements time the same at 192 tiles and
-    // the unsplit one is 5 % faster per step at 256, for d = 512 and for d = 1024).
-    // fp32 with at most kGemvRows rows (GEMVs): both projections, slices of at least 64 k.
-    auto resid_split = [&](int K, bool down) {
-        if (!allow_split || !w.part) return 1;
-        if (sizeof(T) == 4) {
-            if (rows > kGemvRows) return 1;
-            int sp = kGemvSplitMax;
-            while (sp > 1 && (K % (16 * sp) || K / sp < 64)) sp >>= 1;
-            return sp;
-        }
-        return down && K >= 1024 && K % (64 * kSplitK) == 0 && cdiv(rows, 64) * cdiv(d, 64) <= 192 ? kSplitK : 1;
+    const LnArgs ln1 = lnf && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
+    const LnArgs ln2 = lnf ? LnArgs{w.x, y.ln2_g, y.ln2_b, m->cfg.ln_eps} : LnArgs();
+    // K slices of the residual projections of an fp32 model with at most kGemvRows rows (decode; the GEMVs' grid is
+    // only N / 16 work-groups): slices of at least 64 k, whose slabs the following LayerNorm adds.
+    auto resid_split = [&](int K) {
+        if (sizeof(T) != 4 || !allow_split || !w.part || rows > kGemvRows) return 1;
+        int sp = kGemvSplitMax;
+        while (sp > 1 && (K % (16 * sp) || K / sp < 64)) sp >>= 1;
+        return sp;
     };
     if constexpr (sizeof(T) == 2) {
-        if (tm_pend) {
-            // Token mixing in one kernel (see token_mix_one_kernel).  w.part holds 2 * kSplitK slabs: the first
-            // kSplitK are the MLP-down projection's (*tm_pend of them wait from the previous layer), the rest
-            // take this layer's out-projection.  w.a on entry is not used (the kernel normalises w.x + waiting
-            // slabs itself); LayerNorm2 adds everything to w.x.  On return *tm_pend is this layer's count.
-            const int64_t stride = (int64_t)rows * d;
-            const int nq = d / kTokMixCols;
-            float *mine = w.part + (size_t)*tm_pend * stride;      // directly behind the waiting slabs
-            const SlabArgs waiting_tm = *tm_pend > 0 ? SlabArgs{w.part, *tm_pend, stride} : SlabArgs();
-            SRM_TRY(token_mix(m, l, TokMixCall{w.x, waiting_tm, np_state, fuse_pos, mine}, rows, st));
+        if (one_mix) {
+            // token mixing in one kernel, which normalises w.x itself; LayerNorm2 adds its slabs to w.x
+            SRM_TRY(token_mix(m, l, TokMixCall{w.x, np_state, fuse_pos, w.part}, rows, st));
             SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, w.part,
-                                         *tm_pend + nq)));
-            SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st)));
-            const int spd = resid_split(ff, true);
-            if (spd > 1)
-                SRM_TRY((linear<EPI_F32, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.part, st, nullptr, nullptr, 64,
-                                            nullptr, Sampling(), spd)));
-            else
-                SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st)));
-            *tm_pend = spd > 1 ? spd : 0;
-            if (l + 1 < m->L) return SRM_OK;                       // the next layer's kernels add the slabs
-            if (spd > 1)
-                return layernorm<T, false>(m, w.x, d, nullptr, w.x, m->lnf_g, m->lnf_b, w.a, rows, st, nullptr, 0, 0,
-                                           w.part, spd);
+                                         d / kTokMixCols)));
+            SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(),
+                                         1, MixArgs(), call_rows)));
+            SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr,
+                                          Sampling(), 1, MixArgs(), call_rows)));
+            if (l + 1 < m->L) return SRM_OK;
             return layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, rows, st);
         }
     }
@@ -1032,14 +1026,14 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, hi
         // few rows: the state update rides in the in-projection's epilogue (one kernel less per layer)
         const MixArgs mx{fuse_state, y.alpha, y.beta, y.lam, m->cfg.n_ctx, m->hrow, dm / m->Hs, m->shalf ? 1 : 0};
         SRM_TRY((linear<EPI_MIX, T>(w.a, y.w_in, y.b_in, rows, dm, d, w.mx, st, nullptr, nullptr, 64, nullptr, fuse_pos,
-                                    1, mx, SlabArgs(), ln1)));
+                                    1, mx, call_rows, ln1)));
     } else {
         SRM_TRY((linear<EPI_STORE, T>(w.a, y.w_in, y.b_in, rows, dm, d, w.u, st, nullptr, nullptr, 64, nullptr, Sampling(),
-                                      1, MixArgs(), SlabArgs(), ln1)));
+                                      1, MixArgs(), call_rows, ln1)));
         SRM_TRY(mix(l));
     }
     if (!m->noproj) {
-        const int sp = resid_split(dm, false);
+        const int sp = resid_split(dm);
         if (sp > 1) {
             SRM_TRY((linear<EPI_F32, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.part, st, nullptr, nullptr, 64, nullptr,
                                         Sampling(), sp)));
@@ -1047,20 +1041,20 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, hi
                                          sp)));
         } else {
             SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr,
-                                          Sampling(), 1, MixArgs(), l > 0 ? waiting : SlabArgs())));
+                                          Sampling(), 1, MixArgs(), call_rows)));
             if (!lnf) SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, y.ln2_g, y.ln2_b, w.a, rows, st)));
         }
     }
     SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(), 1,
-                                 MixArgs(), SlabArgs(), ln2)));
+                                 MixArgs(), call_rows, ln2)));
     // (not with the fused non-projected layer: no LayerNorm kernel follows there to add the slabs)
-    const int spd = (norm_next && !(m->noproj && np_state)) ? resid_split(ff, true) : 1;
+    const int spd = (norm_next && !(m->noproj && np_state)) ? resid_split(ff) : 1;
     if (spd > 1)
         SRM_TRY((linear<EPI_F32, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.part, st, nullptr, nullptr, 64, nullptr,
                                     Sampling(), spd)));
     else
-        SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st)));
-    if (lnf) *pend = spd > 1 ? spd : 0;
+        SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr,
+                                      Sampling(), 1, MixArgs(), call_rows)));
     if (lnf && l + 1 < m->L) return SRM_OK;                        // the next layer's in-projection normalises
     if (norm_next && !(m->noproj && np_state && l + 1 < m->L)) {   // the fused kernel does its own LayerNorm1
         const float *g = l + 1 < m->L ? m->layers[l + 1].ln1_g : m->lnf_g;
@@ -1136,12 +1130,10 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     };
     const bool fuse = fuse_mixer(m, nb);
     const Sampling where{0.0f, 0, a.pos, a.pos_dev, pos_rows, 1.0f, 0};
-    int pend = 0, tm_pend = 0;
     const bool lnf = ln_on_load(m, nb);
     const bool tm = token_mix_one_kernel(m, nb);
     for (int l = 0; l < m->L; ++l)
-        SRM_TRY((block<T>(m, l, w, nb, st, mix, true, true, fuse ? slab(l) : nullptr, where, slab(l),
-                          lnf ? &pend : nullptr, tm ? &tm_pend : nullptr)));
+        SRM_TRY((block<T>(m, l, w, nb, a.B, st, mix, true, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
     if (a.hidden)
         HIP_TRY(hipMemcpyAsync(a.hidden + (size_t)b0 * d, w.x, (size_t)nb * d * 4, hipMemcpyDeviceToDevice, st));
     const Sampling sm{a.temperature, a.seed, a.pos, a.pos_dev, pos_rows, a.top_p, (uint32_t)b0, a.eos_plus1};
@@ -1235,49 +1227,6 @@ extern "C" int srm_decode_step_topp(srm_model *m, int64_t B, int32_t pos, const 
 }
 
 // ------------------------------------------------------------------ decode, one position per sample
-template <typename T>
-static int decode_ragged_impl(srm_model *m, int64_t B, int32_t *pos_rows, int advance, const int32_t *tok_in,
-                              void *state, int32_t *tok_out, float *logits, void *ws, hipStream_t st,
-                              float temperature, uint32_t seed, float top_p)
-{
-    const Workspace w = carve(m, ws, B);
-    const int dm = m->dm;
-    SRM_TRY((layernorm<T, true>(m, nullptr, 0, tok_in, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a, B, st)));
-    auto mix = [&](int l) {
-        const LayerDev &y = m->layers[l];
-        const int64_t nvec = B * (dm / 4);
-        if (m->shalf)
-            hipLaunchKernelGGL((state_update_ragged_kernel<T, f16>), dim3((unsigned)cdiv(nvec, 256)), dim3(256), 0, st,
-                               static_cast<const T *>(w.u), static_cast<f16 *>(layer_state(m, state, l, B)),
-                               static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, pos_rows, m->cfg.n_ctx, m->Hs, m->hrow, dm, nvec);
-        else
-            hipLaunchKernelGGL((state_update_ragged_kernel<T>), dim3((unsigned)cdiv(nvec, 256)), dim3(256), 0, st,
-                               static_cast<const T *>(w.u), static_cast<float *>(layer_state(m, state, l, B)),
-                               static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, pos_rows, m->cfg.n_ctx, m->Hs, m->hrow, dm, nvec);
-        HIP_TRY(hipGetLastError());
-        return (int)SRM_OK;
-    };
-    const bool fuse = fuse_mixer(m, B);
-    const Sampling where{0.0f, 0, 0, nullptr, pos_rows, 1.0f};
-    int pend = 0, tm_pend = 0;
-    const bool lnf = ln_on_load(m, B);
-    const bool tm = token_mix_one_kernel(m, B);
-    for (int l = 0; l < m->L; ++l)
-        SRM_TRY((block<T>(m, l, w, B, st, mix, true, true, fuse ? layer_state(m, state, l, B) : nullptr, where,
-                          layer_state(m, state, l, B), lnf ? &pend : nullptr, tm ? &tm_pend : nullptr)));
-    const bool topp = temperature > 0.0f && top_p < 1.0f;
-    FinalizeRagged rg{};
-    rg.pos_rows = pos_rows;
-    rg.advance = advance && !topp;        // with a nucleus pass the positions move after it
-    rg.n_ctx = m->cfg.n_ctx;
-    if (topp) rg.zero_counter = w.slow;
-    const Sampling sm{temperature, seed, 0, nullptr, pos_rows, top_p};
-    SRM_TRY((head_argmax<T>(m, w, w.a, B, logits, tok_out, 0, 1, st, TokenStore(), sm, rg)));
-    if (topp)
-        SRM_TRY(nucleus(logits, B, m->V, sm, tok_out, nullptr, nullptr, 0, advance ? pos_rows : nullptr, w.slow, st));
-    return SRM_OK;
-}
-
 extern "C" int srm_decode_step_ragged(srm_model *m, int64_t B, int32_t *d_pos, int32_t advance,
                                       const int32_t *d_tok_in, void *d_state, int32_t *d_tok_out,
                                       float temperature, float top_p, uint32_t seed, float *d_logits,
@@ -1607,7 +1556,7 @@ static int prefill_impl(srm_model *m, const int32_t *prompts, int N, int P, int 
             return prefill_mixer<T>(m, l, w, layer_state(m, state, l, Btot), (int)nc, P, chunk, nchunks, nullptr, 0, rows,
                                     n0, k, nullptr, 0, st);
         };
-        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, st, mix, l + 1 < m->L)));
+        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, (int64_t)N * P, st, mix, l + 1 < m->L)));
         // final LayerNorm of each prompt's last position only, packed [nc][d] into w.a
         SRM_TRY((layernorm<T, false>(m, w.x + (size_t)(P - 1) * d, (int64_t)P * d, nullptr, nullptr, m->lnf_g,
                                      m->lnf_b, w.a, nc, st)));
@@ -1667,7 +1616,7 @@ static int prefill_ragged_impl(srm_model *m, const int32_t *tokens, const int32_
             return prefill_mixer<T>(m, l, w, layer_state(m, state, l, state_batch), nc, chunk ? pmax_call : pmax, chunk,
                                     nchunks, d_off, base, rows, (int64_t)n0, k, slot, state_batch, st);
         };
-        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, st, mix, l + 1 < m->L)));
+        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, h_off[N] - h_off[0], st, mix, l + 1 < m->L)));
         // final LayerNorm of each prompt's last row, packed [nc][d] into w.a
         SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, nc, st, d_off + n0, base,
                                      rows)));
@@ -1789,10 +1738,11 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
             HIP_TRY(hipGetLastError());
             return (int)SRM_OK;
         };
-        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, st, mix, true)));
+        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, (int64_t)B * T_, st, mix, true)));
         HIP_TRY(hipMemcpyAsync(hidden + (size_t)b0 * T_ * d, w.x, (size_t)rows * d * 4, hipMemcpyDeviceToDevice, st));
         if (logits)
-            SRM_TRY((linear<EPI_F32, T>(w.a, m->head, nullptr, rows, m->V, d, logits + (size_t)b0 * T_ * m->V, st)));
+            SRM_TRY((linear<EPI_F32, T>(w.a, m->head, nullptr, rows, m->V, d, logits + (size_t)b0 * T_ * m->V, st, nullptr, nullptr, 64,
+                                        nullptr, Sampling(), 1, MixArgs(), (int64_t)B * T_)));
     }
     return SRM_OK;
 }
@@ -1868,7 +1818,7 @@ extern "C" int srm_mixer_block(srm_model *m, int32_t layer, int32_t pos, const i
     Sampling where;
     where.pos = pos;
     where.pos_rows = d_pos_rows;
-    SRM_TRY(token_mix(m, layer, TokMixCall{d_x, SlabArgs(), d_state_layer, where, d_slabs}, B, st));
+    SRM_TRY(token_mix(m, layer, TokMixCall{d_x, d_state_layer, where, d_slabs}, B, st));
     const LayerDev &y = m->layers[layer];
     return layernorm<bf16, false>(m, d_x, m->d, nullptr, d_x, y.ln2_g, y.ln2_b, d_norm_out, B, st, nullptr, 0, 0, d_slabs,
                                   m->d / kTokMixCols);

@@ -1,7 +1,7 @@
 // Token mixing of an SRM block for decode steps of a dozen to about a thousand rows of a bf16 model
 // (Eq. 2 / Eq. 3 with the head projections of Eq. 10, behind the block's first LayerNorm), as ONE kernel:
 //
-//   a = LN1(x + pending slabs);  u = a W_in^T + b_in;  S, m = state update(S, u);  slab_q = m_q W_out[:, q]^T
+//   a = LN1(x);  u = a W_in^T + b_in;  S, m = state update(S, u);  slab_q = m_q W_out[:, q]^T
 //
 // followed by the LayerNorm kernel that adds the slabs to x and normalises (ln_kernel).  As separate launches
 // (LayerNorm, in-projection + update, out-projection) these are three dependent kernels of 5 - 8 us each at such
@@ -31,9 +31,6 @@
 
 struct TokMixArgs {
     const float *x;            // [rows][d] residual stream
-    const float *pend;         // npend slabs [rows][d] (slab stride pend_stride floats) that a K-sliced projection
-    int32_t npend;             // left to be added to x: LN1 sees x + slabs (summed in slab order); or nullptr
-    int64_t pend_stride;
     const float *ln1_g, *ln1_b;
     float eps;
     const bf16 *w_in, *w_out;  // [d][d]
@@ -170,29 +167,6 @@ token_mix_kernel(TokMixArgs a)
         const int c = ucol0 + t * 16 + 4 * g;
         sv[t] = load_state4(sp, (rl * D + c) >> 2);
         bi[t] = load4(a.b_in + c);
-    }
-    // the slabs still to be added to x, four requested at a time (one at a time would serialise their latencies),
-    // summed in slab order
-    for (int s0 = 0; s0 < a.npend; s0 += 4) {
-        float4 p[4][RPW][VPL];
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int r = 0; r < RPW; ++r)
-#pragma unroll
-                for (int i = 0; i < VPL; ++i)
-                    p[s][r][i] = load4(a.pend + (int64_t)min(s0 + s, a.npend - 1) * a.pend_stride + xrow[r] * D + i * 256 + lane * 4);
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (s0 + s < a.npend) {
-#pragma unroll
-                for (int r = 0; r < RPW; ++r)
-#pragma unroll
-                    for (int i = 0; i < VPL; ++i) {
-                        xr[r][i].x += p[s][r][i].x; xr[r][i].y += p[s][r][i].y;
-                        xr[r][i].z += p[s][r][i].z; xr[r][i].w += p[s][r][i].w;
-                    }
-            }
     }
     const int ps = a.pos_rows ? p_row : a.pos_dev ? __builtin_amdgcn_readfirstlane(p_dev) : a.pos;
     const bool act = ps >= 0 && ps < a.n_ctx;

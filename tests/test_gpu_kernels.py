@@ -80,6 +80,17 @@ def test_linear_bf16_auto_tile_shapes(srm, shape):
         _linear_case(srm, srm.SRM_BF16, M, N, K, epi, None, seed=M + N)
 
 
+@pytest.mark.parametrize("shape", [(1, 64, 64), (16, 4096, 1024), (17, 68, 320), (37, 4096, 192), (130, 1024, 576),
+                                   (300, 1000, 512), (1000, 1000, 1088), (1024, 1024, 2048)])
+@pytest.mark.parametrize("tile", [None, 11, 12, 13, 14, 15])
+def test_linear_bf16_slices(srm, shape, tile):
+    """The GEMM whose wavefronts cut K between them: every tile over the same shapes (ragged edges, fewer k tiles than
+    wavefronts, slices of unequal length, rings that never fill and that wrap), alone and as the launcher chooses."""
+    M, N, K = shape
+    for epi in (0, 1, 2, 4):
+        _linear_case(srm, srm.SRM_BF16, M, N, K, epi, tile, seed=M + N + K + epi)
+
+
 @pytest.mark.parametrize("shape", [(1, 5, 3), (8, 256, 256), (70, 130, 37), (128, 64, 100), (5, 130, 64), (17, 70, 128),
                                    (32, 4096, 256), (33, 64, 64)])
 @pytest.mark.parametrize("epi", [0, 1, 2, 3, 4])

@@ -237,6 +237,12 @@ def test_layernorm_made_by_the_consuming_gemm_equals_the_separate_kernel(srm, or
     assert torch.equal(res[0][1], res[1][1])
 
 
+@pytest.mark.parametrize("d,B", [(1024, 16), (320, 11)])
+def test_layernorm_made_by_the_gemm_up_to_its_last_row_count(srm, orc_mod, d, B, monkeypatch):
+    """The same comparison up to the sixteen rows of the panel."""
+    test_layernorm_made_by_the_consuming_gemm_equals_the_separate_kernel(srm, orc_mod, d, B, True, monkeypatch)
+
+
 @pytest.mark.parametrize("d,B,layers", [(256, 9, 3), (256, 100, 3), (512, 33, 2), (512, 700, 2)])
 @pytest.mark.parametrize("half_state", [False, True])
 def test_token_mixing_in_one_kernel_matches_the_separate_kernels(srm, orc_mod, d, B, layers, half_state, monkeypatch):
