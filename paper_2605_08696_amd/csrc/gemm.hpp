@@ -251,6 +251,66 @@ __device__ __forceinline__ void epi_store4(const GemmEpi &ep, int64_t row, int c
     }
 }
 
+// The same for kernels that know their output quads before their products: what the epilogue reads from memory is
+// requested early (epi_quad_request) and the four columns stored at the end (epi_quad_store; v with bias).
+struct EpiQuad {
+    float4 bias, old;                // old: the residual stream or the recurrent state
+    float al, be, la;
+    int head;                        // EPI_MIX: -1 for a row that is inactive
+};
+template <int EPI>
+__device__ __forceinline__ EpiQuad epi_quad_request(const GemmEpi &ep, int64_t row, int col)
+{
+    EpiQuad q;
+    q.bias = q.old = make_float4(0.f, 0.f, 0.f, 0.f);
+    q.al = q.be = q.la = 0.0f;
+    q.head = -1;
+    if (ep.bias) q.bias = load4(ep.bias + col);
+    const int64_t at = row * ep.ldo + col;
+    if constexpr (EPI == EPI_RESID) {
+        q.old = load4(reinterpret_cast<const float *>(ep.out) + at);
+    } else if constexpr (EPI == EPI_MIX) {
+        const int p = (int)(ep.pos_rows ? (uint32_t)ep.pos_rows[row] : epi_shared_pos(ep));
+        if (p >= 0 && p < ep.n_ctx) {
+            q.head = col / ep.dh;
+            q.al = ep.alpha[(size_t)q.head * ep.n_ctx + p];
+            q.be = ep.beta[(size_t)q.head * ep.n_ctx + p];
+            q.la = ep.lam[q.head];
+            q.old = ep.state_half ? load_state4(static_cast<const f16 *>(ep.state), at >> 2)
+                                  : load_state4(static_cast<const float *>(ep.state), at >> 2);
+        }
+    }
+    return q;
+}
+template <int EPI, typename TAct>
+__device__ __forceinline__ void epi_quad_store(const GemmEpi &ep, int64_t row, int col, const EpiQuad &q, float4 v)
+{
+    const int64_t at = row * ep.ldo + col;
+    if constexpr (EPI == EPI_RESID) {
+        store4(reinterpret_cast<float *>(ep.out) + at, make_float4(q.old.x + v.x, q.old.y + v.y, q.old.z + v.z, q.old.w + v.w));
+    } else if constexpr (EPI == EPI_MIX) {
+        TAct *o = reinterpret_cast<TAct *>(ep.out) + at;
+        if (q.head < 0) { store4(o, make_float4(0.f, 0.f, 0.f, 0.f)); return; }
+        const bool row_repeat = q.head < ep.hrow;
+        const float p = row_repeat ? q.al : 1.0f, c = row_repeat ? 1.0f : q.al;
+        float4 n;
+        n.x = fmaf(q.la, q.old.x, p * (float)(TAct)v.x);
+        n.y = fmaf(q.la, q.old.y, p * (float)(TAct)v.y);
+        n.z = fmaf(q.la, q.old.z, p * (float)(TAct)v.z);
+        n.w = fmaf(q.la, q.old.w, p * (float)(TAct)v.w);
+        if (ep.state_half) {
+            f16 *sp = static_cast<f16 *>(ep.state);
+            n = make_float4(to_state(n.x, sp), to_state(n.y, sp), to_state(n.z, sp), to_state(n.w, sp));
+            store_state4(sp, at >> 2, n);
+        } else {
+            store_state4(static_cast<float *>(ep.state), at >> 2, n);
+        }
+        store4(o, make_float4(fmaf(c, n.x, q.be), fmaf(c, n.y, q.be), fmaf(c, n.z, q.be), fmaf(c, n.w, q.be)));
+    } else {
+        epi_store4<EPI, TAct>(ep, row, col, v);
+    }
+}
+
 template <int EPI, typename TAct>
 __device__ __forceinline__ void epi_store1p(const GemmEpi &ep, int64_t row, int col, float v)
 {
@@ -476,6 +536,66 @@ __device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[BM / WM / 32][BN /
             ep.part_idx[(int64_t)bn * M + row] = bi;
         }
     }
+}
+
+// LayerNorm of the rows ep.ln_x [M][d], M <= kLnaRows and d <= 1024, by a work-group of NW wavefronts in the arithmetic
+// of ln_kernel: put(row, column, four values) for every quad, then a barrier.
+constexpr int kLnaRows = 16;
+template <int NW, typename F>
+__device__ __forceinline__ void layernorm_panel(const GemmEpi &ep, int M, int d, int wave, int lane, F &&put)
+{
+    constexpr int RW = kLnaRows / NW, VPL = 4;              // d <= 256 * VPL
+    float4 v[RW][VPL], pg[VPL], pb[VPL];
+    float sum[RW], sq[RW], mean[RW], rstd[RW];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        const int c = (i * 64 + lane) * 4;
+        pg[i] = pb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c < d) { pg[i] = load4(ep.ln_g + c); pb[i] = load4(ep.ln_b + c); }
+#pragma unroll
+        for (int j = 0; j < RW; ++j) {
+            v[j][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j * NW + wave < M && c < d) v[j][i] = load4(ep.ln_x + (int64_t)(j * NW + wave) * d + c);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+        sum[j] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+            if ((i * 64 + lane) * 4 < d) sum[j] += (v[j][i].x + v[j][i].y) + (v[j][i].z + v[j][i].w);
+    }
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+        mean[j] = wave_sum(sum[j]) / (float)d;
+        sq[j] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+            if ((i * 64 + lane) * 4 < d) {
+                const float a = v[j][i].x - mean[j], b = v[j][i].y - mean[j], c = v[j][i].z - mean[j], e = v[j][i].w - mean[j];
+                sq[j] += (a * a + b * b) + (c * c + e * e);
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < RW; ++j) rstd[j] = 1.0f / sqrtf(wave_sum(sq[j]) / (float)d + ep.ln_eps);
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+        const int r = j * NW + wave;
+        if (r >= M) continue;                        // wave-uniform
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            const int c = (i * 64 + lane) * 4;
+            if (c < d) {
+                float4 o;
+                o.x = (v[j][i].x - mean[j]) * rstd[j] * pg[i].x + pb[i].x;
+                o.y = (v[j][i].y - mean[j]) * rstd[j] * pg[i].y + pb[i].y;
+                o.z = (v[j][i].z - mean[j]) * rstd[j] * pg[i].z + pb[i].z;
+                o.w = (v[j][i].w - mean[j]) * rstd[j] * pg[i].w + pb[i].w;
+                put(r, c, o);
+            }
+        }
+    }
+    __syncthreads();
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, typename TAct, int NS = 2>
@@ -772,17 +892,16 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, int M,
 }
 
 // ------------------------------------------------------------------ few rows: streaming GEMV
-// out = epilogue(A W^T + bias) for at most a few dozen rows (fp32 models; with bf16 weights the 64x64
-// MFMA tile is faster even for one row: measured 2.7 us + 3.4 us per 1024 k against 5.5 + 6.9 for this
-// kernel reading bf16, whose eight rows of activations per weight vector make it LDS-bound).  The
+// out = epilogue(A W^T + bias) for at most a few dozen rows of fp32 operands: the LM head, whose partial winners
+// are counted per 64 columns, and operands that the matrix-core kernels do not take (which are faster for all other
+// shapes: 8 x 1024 x 256: 4.9 us here, 3.7 there; 32 x 512 x 2048: 37 and 7.1).  The
 // product is bound by streaming W once, so the grid is made of
 // many small column slices (16 * CPG columns per block) and the loads are coalesced: 16 lanes
 // share CPG columns (4 such groups per wavefront), lane l16 reading every 16th 16-byte vector of
 // a weight row; MB rows of A sit in LDS as fp32 and are read by every column; after the 16-lane
 // reduction lane l16 == b owns row b of the group's columns.  Weight vectors are requested one
 // batch ahead, the first batch before A is staged.  Rows are processed MB at a time (W is streamed
-// again per group of MB rows).  Split K as in gemm_bf16_kernel (gridDim.y slabs, EPI_F32 only).
-// Dynamic LDS: MB * (K / gridDim.y) floats.
+// again per group of MB rows).  Dynamic LDS: MB * K floats.
 template <typename TW> struct GemvVec;
 template <> struct GemvVec<float> {
     static constexpr int VW = 4;
@@ -796,27 +915,22 @@ template <typename TW, typename TAct, int EPI, int MB, int CPG>
 __global__ void __launch_bounds__(256)
 gemv_rows_kernel(const TAct *__restrict__ A, const TW *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
-    extern __shared__ __align__(16) float gr_sm[];      // [MB][Kp]
+    extern __shared__ __align__(16) float gr_sm[];      // [MB][K]
     __shared__ float red_v[16][MB];
     __shared__ int red_i[16][MB];
     constexpr int VW = GemvVec<TW>::VW;
     constexpr int JB = 8 / CPG;                          // 16-byte vectors per lane, column and batch
     static_assert(MB <= 16 && CPG * JB == 8, "one owner lane per row; eight vectors per lane and batch");
-    const int Kp = K / (int)gridDim.y, kb = blockIdx.y * Kp;
-    if (gridDim.y > 1) {
-        ep.out = reinterpret_cast<float *>(ep.out) + (int64_t)blockIdx.y * M * ep.ldo;
-        if (blockIdx.y) ep.bias = nullptr;
-    }
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15;
     const int grp = (tid >> 6) * 4 + (lane >> 4);        // 0..15
-    const int KV = Kp / VW;                              // 16-byte vectors per row slice
+    const int KV = K / VW;                               // 16-byte vectors per row
     const int nbatch = (KV + 16 * JB - 1) / (16 * JB);
     int n[CPG];
     const u32x4_t *wr[CPG];
 #pragma unroll
     for (int c = 0; c < CPG; ++c) {
         n[c] = (blockIdx.x * 16 + grp) * CPG + c;
-        wr[c] = reinterpret_cast<const u32x4_t *>(W + (size_t)min(n[c], N - 1) * K + kb);
+        wr[c] = reinterpret_cast<const u32x4_t *>(W + (size_t)min(n[c], N - 1) * K);
     }
     auto load_batch = [&](u32x4_t (&w)[CPG][JB], int jb) {
 #pragma unroll
@@ -839,15 +953,15 @@ gemv_rows_kernel(const TAct *__restrict__ A, const TW *__restrict__ W, int M, in
         __syncthreads();                                 // the previous group's products are done with the stage
         // stage the group's rows as fp32: a thread takes the same four k of every row, all MB loads in flight
         const int rows_here = min(MB, M - mg);
-        for (int k = tid * 4; k < Kp; k += 256 * 4) {
+        for (int k = tid * 4; k < K; k += 256 * 4) {
             float4 v[MB];
 #pragma unroll
             for (int m = 0; m < MB; ++m) {
-                v[m] = load4(A + (size_t)(mg + min(m, rows_here - 1)) * K + kb + k);
+                v[m] = load4(A + (size_t)(mg + min(m, rows_here - 1)) * K + k);
                 if (m >= rows_here) v[m] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
 #pragma unroll
-            for (int m = 0; m < MB; ++m) *reinterpret_cast<float4 *>(gr_sm + m * Kp + k) = v[m];
+            for (int m = 0; m < MB; ++m) *reinterpret_cast<float4 *>(gr_sm + m * K + k) = v[m];
         }
         __syncthreads();
         if (mg > 0) load_batch(w, 0);
@@ -872,7 +986,7 @@ gemv_rows_kernel(const TAct *__restrict__ A, const TW *__restrict__ W, int M, in
                 for (int b = 0; b < MB; ++b)
 #pragma unroll
                     for (int q = 0; q < VW / 4; ++q)
-                        av[b][q] = *reinterpret_cast<const float4 *>(gr_sm + b * Kp + kv * VW + q * 4);
+                        av[b][q] = *reinterpret_cast<const float4 *>(gr_sm + b * K + kv * VW + q * 4);
 #pragma unroll
                 for (int b = 0; b < MB; ++b)
 #pragma unroll

@@ -90,16 +90,20 @@ __device__ __forceinline__ void store_quad(const GemmEpi &ep, int row, int col, 
 }
 }  // namespace f32gemm
 
-template <int EPI, int T, int NS>
-__global__ void __launch_bounds__(256)
+// LNA (T = 16, M <= kLnaRows, K <= 1024, K % 32 == 0): as in gemm_bf16_slices_kernel, the A operand is LayerNorm(ep.ln_x
+// rows), made by the work-group: a panel [K / 32][16 rows][32] behind the rings, which then hold W only.
+template <int EPI, int T, int NS, bool LNA = false>
+__global__ void __launch_bounds__(f32gemm::kSlices * 64)
 gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
     using namespace f32gemm;
     static_assert(T == 16 || T == 32, "the tile of one MFMA");
     static_assert(EPI != EPI_ARGMAX, "partial winners are counted per 64 columns");
     constexpr int NW = kSlices;
-    constexpr int STAGE = 2 * T * BK;                    // floats: T rows of A, T rows of W
-    constexpr int LD = 2 * T / 8;                        // tile loads (8 rows each) per k tile
+    static_assert(!LNA || T == kLnaRows, "the panel holds one row tile");
+    constexpr int AR = LNA ? 0 : T;                      // rows of A in a stage
+    constexpr int STAGE = (AR + T) * BK;                 // floats: rows of A, T rows of W
+    constexpr int LD = (AR + T) / 8;                     // tile loads (8 rows each) per k tile
     constexpr int RS = T + 4;                            // row stride of the reduction area in floats
     static_assert(NW * T * RS <= NW * NS * STAGE, "the reduction area exceeds the rings");
     extern __shared__ __align__(16) float f32_sm[];
@@ -122,8 +126,8 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
         for (int i = 0; i < LD; ++i) {
             const int op_i = i % (T / 8);                // eight of rows within its operand
             const int k = kt * BK + (chunk ^ ((op_i & 1) << 4));
-            const int voff = kt < kt1 && k < K ? ((op_i * 8 + ld_r) * K + k) * 4 : kOutside;
-            dma(i < T / 8 ? rs_a : rs_w, ring_lds + (slot * STAGE + i * 8 * BK) * 4, voff);
+            const int voff = k < K ? ((op_i * 8 + ld_r) * K + k) * 4 : kOutside;
+            dma(i < AR / 8 ? rs_a : rs_w, ring_lds + (slot * STAGE + i * 8 * BK) * 4, voff);
         }
     };
     const int li = lane % T, lh = lane / T;              // operand row, k group of this lane
@@ -133,11 +137,25 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
 #pragma unroll
     for (int r = 0; r < T * T / 64; ++r) acc[r] = 0.0f;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) issue(kt0 + s, s);
+    for (int s = 0; s < NS; ++s)
+        if (kt0 + s < kt1) issue(kt0 + s, s);
+    // this thread's quad of the output: what its epilogue reads from memory is requested behind the first tiles
+    const int er = m0 + tid / (T / 4), ec = n0 + tid % (T / 4) * 4;
+    const bool owner = tid < T * T / 4 && er < M && ec < N, whole = (N & 3) == 0;
+    EpiQuad eq;
+    if (owner && whole) eq = epi_quad_request<EPI>(ep, er, ec);
+    float *panel = f32_sm + NW * NS * STAGE;
+    if constexpr (LNA)
+        layernorm_panel<NW>(ep, M, K, wave, lane, [&](int r, int c, float4 o) {
+            *reinterpret_cast<float4 *>(panel + (c >> 5) * T * BK + r * BK + ((((c & 31) >> 2) ^ swz_of_row(r)) << 2)) = o;
+        });
     int slot = 0;
     for (int kt = kt0; kt < kt1; ++kt) {
-        wait_loads<(NS - 1) * LD>();                     // k tile kt has landed, younger ones may be on their way
-        const float *as = ring + slot * STAGE + li * BK, *ws = as + T * BK;
+        // k tile kt has landed, younger ones may be on their way (behind the last one issued: none)
+        if (kt + NS <= kt1) wait_loads<(NS - 1) * LD>();
+        else wait_loads<0>();
+        const float *ws = ring + slot * STAGE + (AR + li) * BK;
+        const float *as = LNA ? panel + kt * T * BK + li * BK : ring + slot * STAGE + li * BK;
         constexpr int G = 64 / T, NR = 8 / G;            // 16-byte chunks per LDS read of a row, reads per k tile
         f32x4_t fa[NR], fw[NR];
 #pragma unroll
@@ -147,7 +165,7 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
             fw[s] = *reinterpret_cast<const f32x4_t *>(ws + ch);
         }
         wait_lds();
-        issue(kt + NS, slot);                            // the slot is free again
+        if (kt + NS < kt1) issue(kt + NS, slot);         // the slot is free again
         if constexpr (T == 32) {
             mfma_k32(fw, fa, acc);
         } else {
@@ -158,7 +176,6 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
         }
         slot = slot + 1 == NS ? 0 : slot + 1;
     }
-    wait_loads<0>();                                     // (of the loads behind the slice: they write zeros)
     __syncthreads();
     float *red = f32_sm + wave * T * RS;
 #pragma unroll
@@ -166,15 +183,20 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
         *reinterpret_cast<float4 *>(red + li * RS + (T == 32 ? 8 * g : 0) + 4 * lh) =
             make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
     __syncthreads();
-    if (tid < T * T / 4) {
-        const int r = tid / (T / 4), c = tid % (T / 4) * 4;
-        float4 v = *reinterpret_cast<const float4 *>(f32_sm + r * RS + c);
+    if (owner) {
+        const float *p = f32_sm + (er - m0) * RS + ec - n0;
+        float4 v = *reinterpret_cast<const float4 *>(p);
 #pragma unroll
         for (int w = 1; w < NW; ++w) {
-            const float4 t = *reinterpret_cast<const float4 *>(f32_sm + (w * T + r) * RS + c);
+            const float4 t = *reinterpret_cast<const float4 *>(p + w * T * RS);
             v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
         }
-        if (m0 + r < M && n0 + c < N) store_quad<EPI>(ep, m0 + r, n0 + c, N, v);
+        if (whole) {
+            v.x += eq.bias.x; v.y += eq.bias.y; v.z += eq.bias.z; v.w += eq.bias.w;
+            epi_quad_store<EPI, float>(ep, er, ec, eq, v);
+        } else {
+            store_quad<EPI>(ep, er, ec, N, v);
+        }
     }
 }
 

@@ -24,69 +24,11 @@ constexpr int slices_wave_lds()
     return ring > part ? ring : part;
 }
 
-// LayerNorm of the rows ep.ln_x [M][K] into the panel described below: two rows per wavefront.
-__device__ __forceinline__ void slices_layernorm_panel(unsigned char *panel, const GemmEpi &ep, int M, int d, int wave, int lane)
-{
-    constexpr int RW = 2, VPL = 4;                   // d <= 256 * VPL
-    float4 v[RW][VPL], pg[VPL], pb[VPL];
-    float sum[RW], sq[RW], mean[RW], rstd[RW];
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-        const int c = (i * 64 + lane) * 4;
-        pg[i] = pb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c < d) { pg[i] = load4(ep.ln_g + c); pb[i] = load4(ep.ln_b + c); }
-#pragma unroll
-        for (int j = 0; j < RW; ++j) {
-            v[j][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (wave * RW + j < M && c < d) v[j][i] = load4(ep.ln_x + (int64_t)(wave * RW + j) * d + c);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        sum[j] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < VPL; ++i)
-            if ((i * 64 + lane) * 4 < d) sum[j] += (v[j][i].x + v[j][i].y) + (v[j][i].z + v[j][i].w);
-    }
-#pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        mean[j] = wave_sum(sum[j]) / (float)d;
-        sq[j] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < VPL; ++i)
-            if ((i * 64 + lane) * 4 < d) {
-                const float a = v[j][i].x - mean[j], b = v[j][i].y - mean[j], c = v[j][i].z - mean[j], e = v[j][i].w - mean[j];
-                sq[j] += (a * a + b * b) + (c * c + e * e);
-            }
-    }
-#pragma unroll
-    for (int j = 0; j < RW; ++j) rstd[j] = 1.0f / sqrtf(wave_sum(sq[j]) / (float)d + ep.ln_eps);
-#pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        const int r = wave * RW + j;
-        if (r >= M) continue;                        // wave-uniform
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const int c = (i * 64 + lane) * 4;
-            if (c < d) {
-                float4 o;
-                o.x = (v[j][i].x - mean[j]) * rstd[j] * pg[i].x + pb[i].x;
-                o.y = (v[j][i].y - mean[j]) * rstd[j] * pg[i].y + pb[i].y;
-                o.z = (v[j][i].z - mean[j]) * rstd[j] * pg[i].z + pb[i].z;
-                o.w = (v[j][i].w - mean[j]) * rstd[j] * pg[i].w + pb[i].w;
-                store4(reinterpret_cast<bf16 *>(panel + (c >> 6) * 2048 + r * 128 + ((((c & 63) >> 3) ^ swz_of_row(r)) << 4)) + (c & 7), o);
-            }
-        }
-    }
-    __syncthreads();
-}
-
 // LNA (M <= kLnaRows, one row tile, K <= 1024): the A operand is not read from memory but made by the work-group itself,
 // A = LayerNorm(ep.ln_x rows) in the arithmetic of ln_kernel, written once as a panel [K / 64][16 rows][64] behind the
 // rings, in the layout of a ring's A tile, while the first W loads travel.  Every column block normalises the few rows
 // again, which is cheaper than the LayerNorm launch it replaces.  Panel rows >= M feed accumulator rows that no
 // epilogue stores.
-constexpr int kLnaRows = 16;
 constexpr int kSliceWaves = 8;
 template <int EPI, int RT, int CT, int NS, bool LNA = false>
 __global__ void __launch_bounds__(kSliceWaves * 64)
@@ -160,38 +102,20 @@ gemm_bf16_slices_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, 
     // what the epilogue needs from memory, requested behind the first operands
     int row[NQ], col[NQ];
     bool in[NQ];
-    float4 bias[NQ], old[NQ];
-    float al[NQ], be[NQ], la[NQ];
-    int ps[NQ];
+    EpiQuad eq[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int g = tid + q * NTHR;
         row[q] = m0 + g / GPR;
         col[q] = n0 + g % GPR * 4;
         in[q] = g < G && row[q] < M && col[q] < N;   // N is a multiple of 4 (the launcher checks)
-        bias[q] = old[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        al[q] = be[q] = la[q] = 0.0f;
-        ps[q] = -1;
-        if (!in[q]) continue;
-        if (ep.bias) bias[q] = load4(ep.bias + col[q]);
-        const int64_t at = (int64_t)row[q] * ep.ldo + col[q];
-        if constexpr (EPI == EPI_RESID) {
-            old[q] = load4(reinterpret_cast<const float *>(ep.out) + at);
-        } else if constexpr (EPI == EPI_MIX) {
-            const int p = (int)(ep.pos_rows ? (uint32_t)ep.pos_rows[row[q]] : epi_shared_pos(ep));
-            if (p >= 0 && p < ep.n_ctx) {
-                const int h = col[q] / ep.dh;
-                ps[q] = h;
-                al[q] = ep.alpha[(size_t)h * ep.n_ctx + p];
-                be[q] = ep.beta[(size_t)h * ep.n_ctx + p];
-                la[q] = ep.lam[h];
-                old[q] = ep.state_half ? load_state4(static_cast<const f16 *>(ep.state), at >> 2)
-                                       : load_state4(static_cast<const float *>(ep.state), at >> 2);
-            }
-        }
+        if (in[q]) eq[q] = epi_quad_request<EPI>(ep, row[q], col[q]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (LNA) slices_layernorm_panel(smem_raw + NW * WAVE_LDS, ep, M, K, wave, lane);
+    if constexpr (LNA) layernorm_panel<NW>(ep, M, K, wave, lane, [&](int r, int c, float4 o) {
+        store4(reinterpret_cast<bf16 *>(smem_raw + NW * WAVE_LDS + (c >> 6) * 2048 + r * 128 +
+                                        ((((c & 63) >> 3) ^ swz_of_row(r)) << 4)) + (c & 7), o);
+    });
 
     f32x4_t acc[RT][CT];
 #pragma unroll
@@ -254,37 +178,13 @@ gemm_bf16_slices_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, 
     for (int q = 0; q < NQ; ++q) {
         if (!in[q]) continue;
         const float *p = part + (row[q] - m0) * RS + col[q] - n0;
-        float4 v = bias[q];
+        float4 v = eq[q].bias;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float4 t = *reinterpret_cast<const float4 *>(p + w * (WAVE_LDS / 4));
             v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
         }
-        const int64_t at = (int64_t)row[q] * ep.ldo + col[q];
-        if constexpr (EPI == EPI_RESID) {
-            store4(reinterpret_cast<float *>(ep.out) + at,
-                   make_float4(old[q].x + v.x, old[q].y + v.y, old[q].z + v.z, old[q].w + v.w));
-        } else if constexpr (EPI == EPI_MIX) {
-            bf16 *o = reinterpret_cast<bf16 *>(ep.out) + at;
-            if (ps[q] < 0) { store4(o, make_float4(0.f, 0.f, 0.f, 0.f)); continue; }
-            const bool row_repeat = ps[q] < ep.hrow;
-            const float l = la[q], pp = row_repeat ? al[q] : 1.0f, qq = row_repeat ? 1.0f : al[q];
-            float4 n;
-            n.x = fmaf(l, old[q].x, pp * (float)(bf16)v.x);
-            n.y = fmaf(l, old[q].y, pp * (float)(bf16)v.y);
-            n.z = fmaf(l, old[q].z, pp * (float)(bf16)v.z);
-            n.w = fmaf(l, old[q].w, pp * (float)(bf16)v.w);
-            if (ep.state_half) {
-                f16 *sp = static_cast<f16 *>(ep.state);
-                n = make_float4(to_state(n.x, sp), to_state(n.y, sp), to_state(n.z, sp), to_state(n.w, sp));
-                store_state4(sp, at >> 2, n);
-            } else {
-                store_state4(static_cast<float *>(ep.state), at >> 2, n);
-            }
-            store4(o, make_float4(fmaf(qq, n.x, be[q]), fmaf(qq, n.y, be[q]), fmaf(qq, n.z, be[q]), fmaf(qq, n.w, be[q])));
-        } else {
-            epi_store4<EPI, bf16>(ep, row[q], col[q], v);
-        }
+        epi_quad_store<EPI, bf16>(ep, row[q], col[q], eq[q], v);
     }
     if (probe) {
         __builtin_amdgcn_s_waitcnt(0);                // this wave's stores have completed

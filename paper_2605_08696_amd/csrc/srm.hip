@@ -358,9 +358,7 @@ struct Workspace {
 // room for kSlabs.
 constexpr int kSlabs = 8;
 constexpr int64_t kSplitMaxRows = 2048;
-// fp32 models with at most kGemvRows rows run their projections as GEMVs, whose grid is only
-// N / 64 blocks: the two residual projections are cut into up to kGemvSplitMax K slices the same way.
-constexpr int kGemvSplitMax = 8;
+// fp32 LM heads of at most kGemvRows rows run as GEMVs.
 constexpr int64_t kGemvRows = 32;
 
 // Scratch of the one-kernel path: [kMegaMaxBlocks][kMegaMaxB] floats, the same of ints, then the barrier's
@@ -389,7 +387,7 @@ static Workspace carve(const srm_model *m, void *base, int64_t rows)
     w.slow = reinterpret_cast<int *>(take(256 + r * 4));
     // sized so that the workspace grows monotonically with the row count
     const size_t part_rows = std::max<size_t>((size_t)kSlabs * std::min<int64_t>(rows, kSplitMaxRows),
-                                              (size_t)kGemvSplitMax * std::min<int64_t>(rows, kGemvRows));
+                                              (size_t)kSlabs * std::min<int64_t>(rows, kGemvRows));
     float *part = reinterpret_cast<float *>(take(part_rows * d * 4));
     w.part = rows <= kSplitMaxRows ? part : nullptr;
     w.mega = take(kMegaScratch);
@@ -466,10 +464,10 @@ static int launch_bf16_persist(const bf16 *A, const bf16 *W, int M, int N, int K
 constexpr int kGemvMB = 8;                 // rows per pass over W
 constexpr size_t kGemvMaxLds = 128 * 1024;
 template <typename TW, typename TAct, int EPI, int CPG>
-static int launch_gemv_rows(const TAct *A, const TW *W, int M, int N, int K, GemmEpi ep, hipStream_t st, int ksplit,
+static int launch_gemv_rows(const TAct *A, const TW *W, int M, int N, int K, GemmEpi ep, hipStream_t st,
                             int *nparts_out)
 {
-    const size_t lds = (size_t)kGemvMB * (K / ksplit) * sizeof(float);
+    const size_t lds = (size_t)kGemvMB * K * sizeof(float);
     auto kern = gemv_rows_kernel<TW, TAct, EPI, kGemvMB, CPG>;
     static bool attr_set = false;
     if (!attr_set) {
@@ -479,16 +477,16 @@ static int launch_gemv_rows(const TAct *A, const TW *W, int M, int N, int K, Gem
     }
     ep.nparts = (int)cdiv(N, 16 * CPG);
     if (nparts_out) *nparts_out = ep.nparts;
-    hipLaunchKernelGGL(kern, dim3((unsigned)ep.nparts, (unsigned)ksplit), dim3(256), lds, st, A, W, M, N, K, ep);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ep.nparts), dim3(256), lds, st, A, W, M, N, K, ep);
     HIP_TRY(hipGetLastError());
     return SRM_OK;
 }
-// whether the streaming GEMV applies: few rows, whole 16-byte weight vectors per K slice, the rows' stage within LDS
+// whether the streaming GEMV applies: few rows, whole 16-byte weight vectors, the rows' stage within LDS
 template <typename TW>
-static bool gemv_rows_ok(int64_t M, int K, int ksplit, int64_t max_rows)
+static bool gemv_rows_ok(int64_t M, int K)
 {
     const int vw = 16 / (int)sizeof(TW);
-    return M <= max_rows && K % (vw * ksplit) == 0 && (size_t)kGemvMB * (K / ksplit) * sizeof(float) <= kGemvMaxLds;
+    return M <= kGemvRows && K % vw == 0 && (size_t)kGemvMB * K * sizeof(float) <= kGemvMaxLds;
 }
 
 // The slice form (gemm_slices.hpp) with a tile of 16 RT x 16 CT and a ring of NS line steps per wavefront.
@@ -533,7 +531,9 @@ static int launch_slices(const bf16 *A, const bf16 *W, int M, int N, int K, cons
     if (fits(4, 2)) return launch_slices_tile<EPI, 4, 2, 1>(A, W, M, N, K, ep, st);
     return launch_slices_tile<EPI, 4, 4, 1>(A, W, M, N, K, ep, st);
 }
-static bool lna_ok(int64_t M, int N, int K) { return M <= kLnaRows && K <= 1024 && K % 64 == 0 && N % 4 == 0; }
+// whether the work-groups of a GEMM can make the LayerNorm of their rows themselves (whole k tiles of 128 bytes)
+template <typename T>
+static bool lna_ok(int64_t M, int N, int K) { return M <= kLnaRows && K <= 1024 && K % (128 / (int)sizeof(T)) == 0 && N % 4 == 0; }
 
 // The 64x64 tile with few blocks on the chip: its k loop is bound by the latency of the tile loads, so
 // the LDS ring is deepened as far as the blocks per CU allow (8 stages = 128 KB: one block per CU;
@@ -629,17 +629,20 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     return fail(SRM_EINVAL, "GEMM tile code %d does not exist for this epilogue", tile);
 }
 
-template <int EPI, int T, int NS>
+template <int EPI, int T, int NS, bool LNA = false>
 static int launch_f32_slices(const float *A, const float *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
-    constexpr int smem = 4 * NS * 2 * T * f32gemm::BK * (int)sizeof(float);
-    auto kern = gemm_f32_slices_kernel<EPI, T, NS>;
+    constexpr int rings = f32gemm::kSlices * NS * (LNA ? 1 : 2) * T * f32gemm::BK * (int)sizeof(float);
+    const int smem = rings + (LNA ? K * T * (int)sizeof(float) : 0);
+    auto kern = gemm_f32_slices_kernel<EPI, T, NS, LNA>;
     static bool attr_set = false;
     if (!attr_set) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    rings + (LNA ? 1024 * T * (int)sizeof(float) : 0)));
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(cdiv(M, T) * cdiv(N, T))), dim3(256), smem, st, A, W, M, N, K, ep);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(cdiv(M, T) * cdiv(N, T))), dim3(f32gemm::kSlices * 64), smem, st, A, W, M, N,
+                       K, ep);
     HIP_TRY(hipGetLastError());
     return SRM_OK;
 }
@@ -656,9 +659,9 @@ static int launch_f32_tiles(const float *A, const float *W, int M, int N, int K,
 {
     const int64_t t64 = cdiv(M, 64) * cdiv(N, 64), t32 = cdiv(M, 32) * cdiv(N, 32), t16 = cdiv(M, 16) * cdiv(N, 16);
     if constexpr (EPI != EPI_ARGMAX) {
+        // one work-group per CU: a deeper ring; else two fit a CU
         if (t16 <= 640) return launch_f32_slices<EPI, 16, 4>(A, W, M, N, K, ep, st);
         if (t64 < 200) {
-            // one work-group per CU: a deeper ring; else two fit a CU
             if (t32 <= 256) return launch_f32_slices<EPI, 32, 4>(A, W, M, N, K, ep, st);
             return launch_f32_slices<EPI, 32, 2>(A, W, M, N, K, ep, st);
         }
@@ -675,18 +678,17 @@ static bool f32_tiles_ok(const float *A, const float *W, int K, const GemmEpi &e
 
 template <int EPI>
 static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, GemmEpi ep, hipStream_t st,
-                      int *nparts_out, int ksplit = 1)
+                      int *nparts_out)
 {
     if (M <= 0 || M >= (1 << 30) || N <= 0 || K <= 0) return fail(SRM_EINVAL, "GEMM shape out of range");
     ep.nparts = (int)cdiv(N, 64);
     if (nparts_out) *nparts_out = ep.nparts;
-    const bool rows_ok = gemv_rows_ok<float>(M, K, ksplit, 32);
-    if (ksplit > 1 && !(EPI == EPI_F32 && rows_ok)) return fail(SRM_EINVAL, "fp32 GEMM: bad split of K = %d", K);
-    if (rows_ok) {
-        // few rows: stream W once per group of kGemvMB rows (64 columns per block where the partial winners of the
-        // LM head are counted per 64 columns, or where 16 would make too many blocks)
-        if (EPI == EPI_ARGMAX || N >= 16384) return launch_gemv_rows<float, float, EPI, 4>(A, W, (int)M, N, K, ep, st, ksplit, nparts_out);
-        return launch_gemv_rows<float, float, EPI, 1>(A, W, (int)M, N, K, ep, st, ksplit, nparts_out);
+    if (gemv_rows_ok<float>(M, K) && (EPI == EPI_ARGMAX || !f32_tiles_ok(A, W, K, ep))) {
+        // LM head of few rows (and operands the tiles do not take): stream W once per group of kGemvMB rows (64 columns
+        // per block where the partial winners of the LM head are counted per 64 columns, or where 16 would make too
+        // many blocks)
+        if (EPI == EPI_ARGMAX || N >= 16384) return launch_gemv_rows<float, float, EPI, 4>(A, W, (int)M, N, K, ep, st, nparts_out);
+        return launch_gemv_rows<float, float, EPI, 1>(A, W, (int)M, N, K, ep, st, nparts_out);
     } else if (f32_tiles_ok(A, W, K, ep)) {
         return launch_f32_tiles<EPI>(A, W, (int)M, N, K, ep, st);
     } else {
@@ -750,22 +752,22 @@ struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (bf16, a 
 template <int EPI, typename T>
 static int linear(const void *A, const void *W, const float *bias, int64_t M, int N, int K, void *out,
                   hipStream_t st, float *pv = nullptr, int32_t *pi = nullptr, int min_bn = 64,
-                  int *nparts_out = nullptr, Sampling sm = Sampling(), int ksplit = 1, MixArgs mx = MixArgs(),
+                  int *nparts_out = nullptr, Sampling sm = Sampling(), MixArgs mx = MixArgs(),
                   int64_t call_rows = 0, LnArgs ln = LnArgs())
 {
     GemmEpi ep{bias, out, (int64_t)N, pv, pi, 0, sm.temp, sm.seed, sm.pos, sm.pos_dev, sm.pos_rows, sm.row_base,
                mx.state, mx.alpha, mx.beta, mx.lam, mx.n_ctx, mx.hrow, mx.dh, mx.state_half};
     ep.clk = g_clock_probe; ep.clk_blocks = g_clock_blocks;
     if (ln.x) {
-        if constexpr (sizeof(T) == 2 && (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_MIX)) {
-            if (M <= 0 || N <= 0 || !lna_ok(M, N, K))
+        if constexpr (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_MIX) {
+            if (M <= 0 || N <= 0 || !lna_ok<T>(M, N, K))
                 return fail(SRM_EINVAL, "linear: LayerNorm-on-load needs at most %d rows, K <= 1024, N %% 4 == 0", kLnaRows);
             ep.ln_x = ln.x; ep.ln_g = ln.g; ep.ln_b = ln.b; ep.ln_eps = ln.eps;
-            // (the ring holds W only: four line steps of it are 64 KB)
-            return launch_slices_tile<EPI, 1, 1, 4, true>(static_cast<const bf16 *>(W), static_cast<const bf16 *>(W), (int)M, N,
-                                                          K, ep, st);
+            const T *w = static_cast<const T *>(W);  // (in A's place: not read)
+            if constexpr (sizeof(T) == 2) return launch_slices_tile<EPI, 1, 1, 4, true>(w, w, (int)M, N, K, ep, st);
+            else return launch_f32_slices<EPI, 16, 4, true>(w, w, (int)M, N, K, ep, st);
         } else {
-            return fail(SRM_EINVAL, "linear: LayerNorm-on-load exists for bf16 store / GELU / mixer epilogues only");
+            return fail(SRM_EINVAL, "linear: LayerNorm-on-load exists for store / GELU / mixer epilogues only");
         }
     }
     if constexpr (sizeof(T) == 2)
@@ -773,7 +775,7 @@ static int linear(const void *A, const void *W, const float *bias, int64_t M, in
                                       st, min_bn, nparts_out, call_rows);
     else
         return launch_f32<EPI>(static_cast<const float *>(A), static_cast<const float *>(W), M, N, K, ep, st,
-                               nparts_out, ksplit);
+                               nparts_out);
 }
 
 struct TokenStore {        // optional second destination of the greedy tokens (srm_generate)
@@ -882,8 +884,8 @@ static bool fuse_mixer(const srm_model *m, int64_t rows)
     return m->wsize == 2 || rows * m->dm <= (1 << 20);
 }
 
-// A handful of samples of a bf16 model: every LayerNorm between two GEMMs of the step is made by the GEMM
-// that consumes it (gemm_bf16_slices_kernel's LNA form) instead of a launch of its own.  Where the token mixing of a
+// A handful of samples: every LayerNorm between two GEMMs of the step is made by the GEMM that consumes it (the
+// LNA form of the slice kernels) instead of a launch of its own.  Where the token mixing of a
 // layer can be one kernel, that is the shorter step from kTokMixMinRows rows on.  SRM_LN_ON_LOAD=0 in the environment
 // keeps the separate kernels.
 constexpr int64_t kTokMixMinRows = 9;
@@ -893,7 +895,7 @@ static bool token_mix_shape_ok(const srm_model *m)
 }
 static bool ln_on_load(const srm_model *m, int64_t rows)
 {
-    if (m->wsize != 2 || m->noproj || !lna_ok(rows, m->dm, m->d)) return false;
+    if (m->noproj || !(m->wsize == 2 ? lna_ok<bf16>(rows, m->dm, m->d) : lna_ok<float>(rows, m->dm, m->d))) return false;
     if (token_mix_shape_ok(m) && rows >= kTokMixMinRows) return false;
     const char *e = getenv("SRM_LN_ON_LOAD");
     return !(e && e[0] == '0');
@@ -967,21 +969,13 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
 // call_rows: the rows of the whole call (rows are one of its passes; see slices_ok).
 template <typename T, typename MIX>
 static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, int64_t call_rows, hipStream_t st, MIX &&mix,
-                 bool norm_next, bool allow_split = false, void *fuse_state = nullptr, Sampling fuse_pos = Sampling(),
+                 bool norm_next, void *fuse_state = nullptr, Sampling fuse_pos = Sampling(),
                  void *np_state = nullptr, bool lnf = false, bool one_mix = false)
 {
     const LayerDev &y = m->layers[l];
     const int d = m->d, dm = m->dm, ff = m->ff;
     const LnArgs ln1 = lnf && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
     const LnArgs ln2 = lnf ? LnArgs{w.x, y.ln2_g, y.ln2_b, m->cfg.ln_eps} : LnArgs();
-    // K slices of the residual projections of an fp32 model with at most kGemvRows rows (decode; the GEMVs' grid is
-    // only N / 16 work-groups): slices of at least 64 k, whose slabs the following LayerNorm adds.
-    auto resid_split = [&](int K) {
-        if (sizeof(T) != 4 || !allow_split || !w.part || rows > kGemvRows) return 1;
-        int sp = kGemvSplitMax;
-        while (sp > 1 && (K % (16 * sp) || K / sp < 64)) sp >>= 1;
-        return sp;
-    };
     if constexpr (sizeof(T) == 2) {
         if (one_mix) {
             // token mixing in one kernel, which normalises w.x itself; LayerNorm2 adds its slabs to w.x
@@ -989,9 +983,9 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
             SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, w.part,
                                          d / kTokMixCols)));
             SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(),
-                                         1, MixArgs(), call_rows)));
+                                         MixArgs(), call_rows)));
             SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr,
-                                          Sampling(), 1, MixArgs(), call_rows)));
+                                          Sampling(), MixArgs(), call_rows)));
             if (l + 1 < m->L) return SRM_OK;
             return layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, rows, st);
         }
@@ -1026,43 +1020,26 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
         // few rows: the state update rides in the in-projection's epilogue (one kernel less per layer)
         const MixArgs mx{fuse_state, y.alpha, y.beta, y.lam, m->cfg.n_ctx, m->hrow, dm / m->Hs, m->shalf ? 1 : 0};
         SRM_TRY((linear<EPI_MIX, T>(w.a, y.w_in, y.b_in, rows, dm, d, w.mx, st, nullptr, nullptr, 64, nullptr, fuse_pos,
-                                    1, mx, call_rows, ln1)));
+                                    mx, call_rows, ln1)));
     } else {
         SRM_TRY((linear<EPI_STORE, T>(w.a, y.w_in, y.b_in, rows, dm, d, w.u, st, nullptr, nullptr, 64, nullptr, Sampling(),
-                                      1, MixArgs(), call_rows, ln1)));
+                                      MixArgs(), call_rows, ln1)));
         SRM_TRY(mix(l));
     }
     if (!m->noproj) {
-        const int sp = resid_split(dm);
-        if (sp > 1) {
-            SRM_TRY((linear<EPI_F32, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.part, st, nullptr, nullptr, 64, nullptr,
-                                        Sampling(), sp)));
-            SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, w.part,
-                                         sp)));
-        } else {
-            SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr,
-                                          Sampling(), 1, MixArgs(), call_rows)));
-            if (!lnf) SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, y.ln2_g, y.ln2_b, w.a, rows, st)));
-        }
+        SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
+                                      MixArgs(), call_rows)));
+        if (!lnf) SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, y.ln2_g, y.ln2_b, w.a, rows, st)));
     }
-    SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(), 1,
+    SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                  MixArgs(), call_rows, ln2)));
-    // (not with the fused non-projected layer: no LayerNorm kernel follows there to add the slabs)
-    const int spd = (norm_next && !(m->noproj && np_state)) ? resid_split(ff) : 1;
-    if (spd > 1)
-        SRM_TRY((linear<EPI_F32, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.part, st, nullptr, nullptr, 64, nullptr,
-                                    Sampling(), spd)));
-    else
-        SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr,
-                                      Sampling(), 1, MixArgs(), call_rows)));
+    SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
+                                  MixArgs(), call_rows)));
     if (lnf && l + 1 < m->L) return SRM_OK;                        // the next layer's in-projection normalises
     if (norm_next && !(m->noproj && np_state && l + 1 < m->L)) {   // the fused kernel does its own LayerNorm1
         const float *g = l + 1 < m->L ? m->layers[l + 1].ln1_g : m->lnf_g;
         const float *b = l + 1 < m->L ? m->layers[l + 1].ln1_b : m->lnf_b;
-        if (spd > 1)               // x += slabs, then normalise
-            SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, g, b, w.a, rows, st, nullptr, 0, 0, w.part, spd)));
-        else
-            SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, g, b, w.a, rows, st)));
+        SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, g, b, w.a, rows, st)));
     }
     return SRM_OK;
 }
@@ -1133,7 +1110,7 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     const bool lnf = ln_on_load(m, nb);
     const bool tm = token_mix_one_kernel(m, nb);
     for (int l = 0; l < m->L; ++l)
-        SRM_TRY((block<T>(m, l, w, nb, a.B, st, mix, true, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
+        SRM_TRY((block<T>(m, l, w, nb, a.B, st, mix, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
     if (a.hidden)
         HIP_TRY(hipMemcpyAsync(a.hidden + (size_t)b0 * d, w.x, (size_t)nb * d * 4, hipMemcpyDeviceToDevice, st));
     const Sampling sm{a.temperature, a.seed, a.pos, a.pos_dev, pos_rows, a.top_p, (uint32_t)b0, a.eos_plus1};
@@ -1742,7 +1719,7 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
         HIP_TRY(hipMemcpyAsync(hidden + (size_t)b0 * T_ * d, w.x, (size_t)rows * d * 4, hipMemcpyDeviceToDevice, st));
         if (logits)
             SRM_TRY((linear<EPI_F32, T>(w.a, m->head, nullptr, rows, m->V, d, logits + (size_t)b0 * T_ * m->V, st, nullptr, nullptr, 64,
-                                        nullptr, Sampling(), 1, MixArgs(), (int64_t)B * T_)));
+                                        nullptr, Sampling(), MixArgs(), (int64_t)B * T_)));
     }
     return SRM_OK;
 }
@@ -1798,9 +1775,9 @@ extern "C" int srm_mixer_project_update(srm_model *m, int32_t layer, int32_t pos
     Sampling where;
     where.pos = pos;
     return m->wsize == 2 ? linear<EPI_MIX, bf16>(d_a, y.w_in, y.b_in, B, m->dm, m->d, d_m, st, nullptr, nullptr, 64,
-                                                 nullptr, where, 1, mx)
+                                                 nullptr, where, mx)
                          : linear<EPI_MIX, float>(d_a, y.w_in, y.b_in, B, m->dm, m->d, d_m, st, nullptr, nullptr, 64,
-                                                  nullptr, where, 1, mx);
+                                                  nullptr, where, mx);
 }
 
 extern "C" int srm_mixer_block(srm_model *m, int32_t layer, int32_t pos, const int32_t *d_pos_rows, int64_t B,
