@@ -73,13 +73,6 @@ __device__ __forceinline__ float to_state(float v, const f16 *)
 }
 
 // ---- wavefront reductions ------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
-
 // Sum over each group of 16 consecutive lanes (a DPP row), result in every lane of the group.
 __device__ __forceinline__ float row16_sum(float v)
 {
@@ -88,6 +81,17 @@ __device__ __forceinline__ float row16_sum(float v)
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));  // row_half_mirror
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));  // row_mirror
     return v;
+}
+// Sum over the wavefront, in every lane: the four row sums are read into scalar registers.  (Six exchanges through the
+// LDS crossbar instead are a chain of some hundred clocks each, twice per LayerNorm.)  All lanes must be active.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    const int r = __builtin_bit_cast(int, row16_sum(v));
+    const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(r, 0));
+    const float b = __builtin_bit_cast(float, __builtin_amdgcn_readlane(r, 16));
+    const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane(r, 32));
+    const float d = __builtin_bit_cast(float, __builtin_amdgcn_readlane(r, 48));
+    return (a + b) + (c + d);
 }
 
 // (value, index) pair ordered by larger value, then smaller index.
