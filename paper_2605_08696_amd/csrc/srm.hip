@@ -1433,6 +1433,16 @@ static int scan_chunk_len(const srm_model *m, int64_t nseq, int P)
     return 0;
 }
 
+// Where the chunked scan would run, mixer_parallel_kernel (one launch, every block reads the positions in front of it
+// itself) is faster until those reads count: their bytes grow with sequences x channels x P^2.  Measured (us per layer,
+// chunked - block form, d = 1024): 1 x 509 positions +4.4, 8 x 320 +4.8, 64 x 128 (2^30) +4.3, 32 x 200 (1.2 x 2^30)
+// +0.9, 8 x 509 (2 x 2^30) +0.7, 64 x 200 -3.5, 32 x 509 -18; d = 512: 32 x 320 +5.3, 64 x 200 (1.2 x 2^30) +0.8, 120 x
+// 200 -4.  A property of the whole call, like the chunk length.
+static bool scan_in_blocks(const srm_model *m, int chunk, int64_t nseq, int P)
+{
+    return chunk > 0 && P < 8192 && nseq * m->dm * (int64_t)P * P <= (1 << 30);
+}
+
 // The chunked scan keeps its per-chunk partial states F [nc][nchunks][dm] fp32 in the pass's MLP buffer
 // w.g ([rows][ff] activation elements, free until the layer's MLP): whether they fit there.
 static bool scan_scratch_fits(const srm_model *m, int64_t nc, int nchunks, int64_t rows)
@@ -1478,11 +1488,20 @@ static RaggedPlan plan_ragged(const srm_model *m, const int32_t *h_off, int N, i
 // The mixer of one prefill pass: nc sequences in rows of w.u -> w.mx, final states to S_layer.
 template <typename T>
 static int prefill_mixer(const srm_model *m, int l, const Workspace &w, void *S_layer, int nc, int P, int chunk,
-                         int nchunks, const int32_t *offsets, int64_t base, int64_t rows, int64_t seq0, int rep,
+                         int nchunks, bool in_blocks, const int32_t *offsets, int64_t base, int64_t rows, int64_t seq0, int rep,
                          const int32_t *slot, int64_t nslots, hipStream_t st)
 {
     const LayerDev &y = m->layers[l];
     const int d = m->dm;           // the mixer's row width
+    if (in_blocks) {
+        const dim3 grid((unsigned)cdiv(P, 64), (unsigned)(m->Hs * cdiv(d / m->Hs, 64)), (unsigned)nc);
+        hipLaunchKernelGGL((mixer_parallel_kernel<T, true>), grid, dim3(256), (size_t)(P + 1) * sizeof(float), st,
+                           static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, m->cfg.n_ctx,
+                           m->Hs, m->hrow, d, P,
+                           PrefillSeqs{static_cast<float *>(S_layer), offsets, base, rows, seq0, rep, slot, nslots});
+        HIP_TRY(hipGetLastError());
+        return SRM_OK;
+    }
     if (chunk > 0) {
         float *F = static_cast<float *>(w.g);       // free until the MLP of this layer
         const unsigned nb = (unsigned)cdiv((int64_t)nc * nchunks * (d / 4), 256);
@@ -1523,6 +1542,7 @@ static int prefill_impl(srm_model *m, const int32_t *prompts, int N, int P, int 
     const int d = m->d;
     const int64_t Btot = (int64_t)N * k;
     const int nchunks = chunk ? (int)cdiv(P, chunk) : 1;
+    const bool in_blocks = scan_in_blocks(m, chunk, N, P);
     for (int64_t n0 = 0; n0 < N; n0 += per_pass) {
         const int64_t nc = std::min<int64_t>(per_pass, N - n0);
         const int64_t rows = nc * P;
@@ -1530,7 +1550,7 @@ static int prefill_impl(srm_model *m, const int32_t *prompts, int N, int P, int 
         SRM_TRY((layernorm<T, true>(m, nullptr, 0, prompts + n0 * P, w.x, m->layers[0].ln1_g,
                                     m->layers[0].ln1_b, w.a, rows, st)));
         auto mix = [&](int l) {
-            return prefill_mixer<T>(m, l, w, layer_state(m, state, l, Btot), (int)nc, P, chunk, nchunks, nullptr, 0, rows,
+            return prefill_mixer<T>(m, l, w, layer_state(m, state, l, Btot), (int)nc, P, chunk, nchunks, in_blocks, nullptr, 0, rows,
                                     n0, k, nullptr, 0, st);
         };
         for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, (int64_t)N * P, st, mix, l + 1 < m->L)));
@@ -1579,6 +1599,7 @@ static int prefill_ragged_impl(srm_model *m, const int32_t *tokens, const int32_
 {
     const int d = m->d;
     const int chunk = plan.chunk, nchunks = plan.nchunks;
+    const bool in_blocks = scan_in_blocks(m, chunk, N, pmax_call);
     for (size_t pass = 0; pass + 1 < plan.first.size(); ++pass) {
         // as many whole prompts as the workspace holds
         const int n0 = plan.first[pass], n1 = plan.first[pass + 1];
@@ -1591,7 +1612,7 @@ static int prefill_ragged_impl(srm_model *m, const int32_t *tokens, const int32_
                                     rows, st)));
         auto mix = [&](int l) {
             return prefill_mixer<T>(m, l, w, layer_state(m, state, l, state_batch), nc, chunk ? pmax_call : pmax, chunk,
-                                    nchunks, d_off, base, rows, (int64_t)n0, k, slot, state_batch, st);
+                                    nchunks, in_blocks, d_off, base, rows, (int64_t)n0, k, slot, state_batch, st);
         };
         for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, h_off[N] - h_off[0], st, mix, l + 1 < m->L)));
         // final LayerNorm of each prompt's last row, packed [nc][d] into w.a
@@ -1711,7 +1732,7 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
             const dim3 grid((unsigned)cdiv(T_, 64), (unsigned)(m->Hs * cdiv(dh, 64)), (unsigned)nc);
             hipLaunchKernelGGL((mixer_parallel_kernel<T>), grid, dim3(256), (size_t)(T_ + 1) * sizeof(float), st,
                                static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam,
-                               m->cfg.n_ctx, m->Hs, m->hrow, dm, T_);
+                               m->cfg.n_ctx, m->Hs, m->hrow, dm, T_, PrefillSeqs{});
             HIP_TRY(hipGetLastError());
             return (int)SRM_OK;
         };

@@ -404,6 +404,29 @@ def test_chunked_scan_prefill_matches_oracle_and_decode_steps(c1, N, P):
     assert torch.equal(st, st_c) and torch.equal(tk, tk_c)
 
 
+@pytest.mark.parametrize("N,P,k", [(1, 64, 3), (2, 127, 1), (2, 129, 20), (64, 256, 1), (65, 256, 2)])
+def test_prefill_scan_forms_match_decode_steps(c1, N, P, k):
+    """Both forms of the scan of few sequences, on each side of the rule that chooses (64 x 256 positions of 256
+    channels is the largest call for blocks) and at the ends of their blocks, with the state written to k samples:
+    against P single decode steps, to fp32 rounding."""
+    cfg, w, model, orc = c1
+    prompts = np.random.default_rng(N + P).integers(0, cfg.vocab, (N, P)).astype(np.int32)
+    print(f"prefill scan forms N={N} P={P} k={k}", flush=True)
+    ws = model.new_workspace(N * P)
+    st, tk = model.new_state(N * k), torch.empty(N * k, dtype=torch.int32, device="cuda")
+    st.fill_(float("nan"))
+    model.prefill(to_dev(prompts), k, st, tk, workspace=ws)
+    st_b, tk_b = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+    st_b.zero_()
+    pc = to_dev(prompts).t().contiguous()
+    for t in range(P):
+        model.decode_step(N, t, pc[t], st_b, tk_b, workspace=ws)
+    torch.cuda.synchronize()
+    got = st.view(cfg.n_layers, N, k, cfg.d_model)
+    want = st_b.view(cfg.n_layers, N, 1, cfg.d_model)
+    assert (got - want).abs().max() <= 1e-5 * want.abs().max()
+
+
 def test_chunked_scan_ragged_prompts(c1):
     cfg, w, model, orc = c1
     lens = [200, 77, 1, 130, 16]
