@@ -715,7 +715,7 @@ struct Sampling {          // temp == 0: greedy
 static int nucleus(const float *logits, int64_t rows, int V, const Sampling &sm, int32_t *tok, int32_t *store,
                    const int *step_dev, int64_t store_stride, int32_t *pos_advance, int *slow, hipStream_t st)
 {
-    constexpr int NT = 512, EPT = 64;
+    constexpr int NT = 1024, EPT = 32;
     if (V > NT * EPT) {
         // vocabulary too large for the register-resident search: one kernel, searching from memory
         hipLaunchKernelGGL((nucleus_kernel<256, false, false>), dim3((unsigned)rows), dim3(256), 0, st, logits,

@@ -179,3 +179,27 @@ def test_topp_step_bf16_rows_against_oracle_rule(srm, orc_mod):
     assert int(posr[5]) == -1 and (posr[live] == pos + 1).all()
     with pytest.raises(srm.SrmError):                           # the truncation needs the logits buffer
         model.decode_step(B, pos, tok, st, out, workspace=ws, temperature=T, seed=seed, top_p=top_p)
+
+
+@pytest.mark.parametrize("V,groups", [(1501, 0), (32000, 0), (5001, 5), (5000, 8), (32000, 40)])
+def test_topp_search_against_oracle_rule(srm, orc_mod, V, groups):
+    """The nucleus search of the decode step: distinct logits (the cut lies in a step of few elements) and logits that
+    take `groups` values only, each in more elements than a step may gather; vocabularies that are read by fours and
+    that are not.  Every row's token equals the oracle's choice from the GPU's own logits."""
+    cfg = srm_synth.tiny_config(vocab=V, d_model=64, n_layers=1, n_heads=4, n_ctx=16, seed=5)
+    w = srm_synth.make_weights(cfg, stress=True)
+    w["head"] = w["head"] * 20.0
+    if groups:
+        w["head"] = w["head"][np.arange(V) % groups].copy()
+    model = srm.Model(cfg, w)
+    B, T, top_p, seed, pos = 40, 0.8, 0.7, 12, 3
+    print(f"top-p search V={V} groups={groups}", flush=True)
+    tok = to_dev(np.arange(B, dtype=np.int32) * 7 % V)
+    st = torch.randn(cfg.n_layers * B * cfg.d_model, device="cuda") * 0.1
+    lg = torch.empty((B, V), dtype=torch.float32, device="cuda")
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    model.decode_step(B, pos, tok, st, out, logits=lg, workspace=model.new_workspace(B), temperature=T, seed=seed,
+                      top_p=top_p)
+    torch.cuda.synchronize()
+    tolerated, changed = _check_rows(orc_mod, out.cpu().numpy(), lg.cpu().numpy(), T, top_p, seed, lambda r: pos)
+    assert tolerated <= 2 and changed > 0
