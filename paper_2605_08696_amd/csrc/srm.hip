@@ -551,12 +551,13 @@ static int launch_bf16_small(const bf16 *A, const bf16 *W, int M, int N, int K, 
 // Tile codes of the bf16 GEMM: 0 = 256x256 (8 waves), 1 = 128x128 (4 waves),
 // 2 = 64x64 (4 waves), 3 = 128x128 (8 waves), 4 = 256x128 (8 waves); 5 .. 8 pin the
 // ring depth of a tile for sweeps, 9 / 10 pin the persistent / one-tile-per-work-group form of 256x256, 11 .. 15 the
-// slice form with tiles of 16x16, 32x16, 32x32, 64x32 and 64x64.  min_bn > 64 rules out the 64-wide tile (the LM
+// slice form with tiles of 16x16, 32x16, 32x32, 64x32 and 64x64; 16 = 192x256 (8 waves), 17 = 96x128, 18 = 128x64 (4
+// waves, ring of four).  min_bn > 64 rules out the 64-wide tile (the LM
 // head's partial buffers are sized for column tiles >= 128).  Measured on C4's
 // shapes over 512 .. 16384 rows: the big tile wins once it fills most of the chip in
 // whole rounds (one block per CU: 384 tiles are two rounds at 75 %, and lose to 1536
 // tiles of 128x128); 128x128 wins over 64x64 from about 144 blocks on.
-constexpr int kNumTiles = 16;
+constexpr int kNumTiles = 19;
 static int choose_tile(int64_t M, int N, int K, int min_bn)
 {
     const int64_t t256 = cdiv(M, 256) * cdiv(N, 256), t128 = cdiv(M, 128) * cdiv(N, 128);
@@ -568,6 +569,24 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
     else tile = 2;
     if (tile == 2 && min_bn > 64) tile = 1;
     return tile;
+}
+// Launches whose 256x256 tiles do not fill the chip and whose 128x128 tiles leave the last round part empty: the tile
+// that makes one round of it (-1: none does, choose_tile decides).  Measured (us, choose_tile's tile | this; rows x
+// columns x K): 128x64 up to 256 tiles: 1300 x 1024 x 4096: 27.7 | 23.4, 2048 x 1024 x 1024: 11.8 | 11.3, 700 x 2048 x
+// 1024: 10.2 | 8.9 (320 tiles: 14.9 | 18.0).  96x128 up to 256: 2500 x 1024 x 4096: 34.1 | 30.2, 3000 x 1024 x 1024:
+// 15.4 | 13.6, 700 x 4096 x 1024: 14.1 | 12.4 (296: 16.3 | 21.6).  192x256 from 188 to 256: 2500 x 4096 x 1024: 33.4 |
+// 28.1, 9000 x 1024 x 4096: 103 | 79 (176: 23.7 | 26.2; 304: 34.9 | 49.4), and two or three rounds of it that are full
+// where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8.  Every tile gives the same bits.
+static int choose_one_round_tile(int64_t M, int N, int K)
+{
+    if (K < 512) return -1;                          // (rings of four k tiles)
+    if (cdiv(M, 128) * cdiv(N, 64) <= 256) return 18;
+    if (cdiv(M, 96) * cdiv(N, 128) <= 256) return 17;
+    const int64_t t192 = cdiv(M, 192) * cdiv(N, 256), t256 = cdiv(M, 256) * cdiv(N, 256);
+    if (t192 >= 188 && t192 <= 256) return 16;
+    const int64_t r192 = cdiv(t192, 256) * 256, r256 = cdiv(t256, 256) * 256;
+    if (t192 > 256 && t192 <= 768 && t192 * 20 >= r192 * 19 && t256 * 5 < r256 * 4) return 16;
+    return -1;
 }
 static int tile_bn(int tile) { return tile == 0 || tile >= 9 ? 256 : (tile == 2 || tile >= 6) ? 64 : 128; }
 
@@ -585,7 +604,10 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     const int m = (int)M;
     if constexpr (EPI != EPI_ARGMAX)                 // (whose partial winners are counted per 128 columns or more)
         if (g_force_tile < 0 && slices_ok(std::max(M, call_rows), N, K)) return launch_slices<EPI>(A, W, m, N, K, ep, st);
-    const int tile = g_force_tile >= 0 ? g_force_tile : choose_tile(M, N, K, min_bn);
+    int tile = g_force_tile;
+    if constexpr (EPI != EPI_ARGMAX)
+        if (tile < 0) tile = choose_one_round_tile(M, N, K);
+    if (tile < 0) tile = choose_tile(M, N, K, min_bn);
     ep.nparts = (int)cdiv(N, tile_bn(tile));
     if (nparts_out) *nparts_out = ep.nparts;
     switch (tile) {
@@ -616,6 +638,9 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     default: break;
     }
     if constexpr (EPI != EPI_ARGMAX) {
+        if (tile == 16) return launch_bf16_tile<192, 256, 2, 4, EPI, TAct>(A, W, m, N, K, ep, st);
+        if (tile == 17) return launch_bf16_tile<96, 128, 1, 4, EPI, TAct, 4>(A, W, m, N, K, ep, st);
+        if (tile == 18) return launch_bf16_tile<128, 64, 2, 2, EPI, TAct, 4>(A, W, m, N, K, ep, st);
         if (N % 4) return fail(SRM_EINVAL, "the slice form needs N %% 4 == 0 (N = %d)", N);
         switch (tile) {
         case 11: return launch_slices_tile<EPI, 1, 1, 4>(A, W, m, N, K, ep, st);

@@ -91,6 +91,15 @@ def test_linear_bf16_slices(srm, shape, tile):
         _linear_case(srm, srm.SRM_BF16, M, N, K, epi, tile, seed=M + N + K + epi)
 
 
+@pytest.mark.parametrize("shape,tile", [((300, 328, 192), 16), ((300, 328, 192), 17), ((300, 328, 192), 18),
+                                        ((1300, 1022, 512), None), ((2500, 1000, 512), None), ((2450, 4094, 512), None)])
+def test_linear_bf16_one_round_tiles(srm, shape, tile):
+    """The tiles for launches that make one round of the chip, pinned over ragged edges and as the launcher chooses."""
+    M, N, K = shape
+    for epi in (0, 1, 2, 4):
+        _linear_case(srm, srm.SRM_BF16, M, N, K, epi, tile, seed=M + N + K + epi)
+
+
 @pytest.mark.parametrize("shape", [(1, 5, 3), (8, 256, 256), (70, 130, 37), (128, 64, 100), (5, 130, 64), (17, 70, 128),
                                    (32, 4096, 256), (33, 64, 64)])
 @pytest.mark.parametrize("epi", [0, 1, 2, 3, 4])
