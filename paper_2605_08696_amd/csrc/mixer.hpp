@@ -502,7 +502,7 @@ scan_chunk_apply_kernel(const TAct *__restrict__ u, TAct *__restrict__ m, float 
 // PREFILL: sequence b of the launch lies where PrefillSeqs says, T is the longest one, and the block that holds a
 // sequence's last position writes the state behind it: lam^(T-j0) C + sum_{i>=j0} lam^(T-1-i) p_i U[i].  One launch in
 // the place of the chunked scan's two, whose threads are few and wait for memory in a row: one sequence of 509
-// positions of 1024 channels 14.0 -> 9.6 us per layer, 24 prompts of up to 150 tokens of 512 channels 13.5 -> 7.
+// positions of 1024 channels 14.0 -> 8.6 us per layer, 24 prompts of up to 150 tokens of 512 channels 13.5 -> 7.
 // Dynamic LDS: T + 1 floats (the power table).
 struct PrefillSeqs {
     float *S;                        // [nslots or all samples][d] of this layer
@@ -550,6 +550,19 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
         av[r] = al[j];
         bv[r] = bl[j];
     }
+    // rows g, g + 16, ... of the prefix (j0 is a multiple of 64), PRE of them in one request, the first under the table
+    constexpr int PRE = 16;
+    raw_t u[PRE];
+    float a[PRE];
+    auto request = [&](int i0) {
+#pragma unroll
+        for (int k = 0; k < PRE; ++k) {
+            const int i = min(i0 + 16 * k, j0 - 1);
+            u[k] = *reinterpret_cast<const raw_t *>(Ub + (int64_t)i * d);
+            a[k] = al[i];
+        }
+    };
+    if (g < j0) request(g);
     for (int k = tid; k <= min(T, j0 + 64); k += 256) {
         double sq = (double)lam[h], v = 1.0;
         for (int e = k; e; e >>= 1, sq *= sq)
@@ -560,19 +573,12 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
     auto axpy = [](float w, float4 x, float4 &s) {
         s.x = fmaf(w, x.x, s.x); s.y = fmaf(w, x.y, s.y); s.z = fmaf(w, x.z, s.z); s.w = fmaf(w, x.w, s.w);
     };
-    // C: rows g, g + 16, ... of the prefix (j0 is a multiple of 64)
+    // C, this group's share
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i0 = g; i0 < j0; i0 += 128) {
-        raw_t u[8];
-        float a[8];
+    for (int i0 = g; i0 < j0; i0 += 16 * PRE) {
+        if (i0 > g) request(i0);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int i = min(i0 + 16 * k, j0 - 1);
-            u[k] = *reinterpret_cast<const raw_t *>(Ub + (int64_t)i * d);
-            a[k] = al[i];
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < PRE; ++k) {
             const int i = i0 + 16 * k;
             if (i < j0) axpy(pw[j0 - 1 - i] * (row_repeat ? a[k] : 1.0f), widen4(u[k]), s);
         }
