@@ -33,7 +33,7 @@ __device__ __forceinline__ float4 widen4(const TRaw &r) { return make_float4((fl
 // f(t, u_t) for the positions t0 .. t1-1 of a sequence, u_t = four channels of row t (row stride d), in order.  The
 // rows travel in blocks of kScanAhead, the next block requested before the current one is used: a scan keeps one
 // row per thread in flight otherwise, and every position then costs a trip to memory.
-constexpr int kScanAhead = 8;
+constexpr int kScanAhead = 16;
 template <typename TAct, typename F>
 __device__ __forceinline__ void scan_rows(const TAct *__restrict__ u, int64_t d, int t0, int t1, F &&f)
 {
