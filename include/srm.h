@@ -357,7 +357,8 @@ int srm_prefill_ragged(srm_model *m, const int32_t *d_tokens, const int32_t *h_o
  * Host-only planning query (no GPU call, no model): how srm_prefill_ragged would
  * take the packed prompts h_offsets[N + 1] of a model with configuration cfg
  * through a workspace of workspace_bytes.  The mixer of a prefill pass is either
- * one sequential scan per prompt or a chunked scan ("MAX model details" names a
+ * one sequential scan per prompt or a chunked scan (or, for the smallest calls
+ * that would take it, the same sums in blocks of 64 positions; "MAX model details" names a
  * parallel scan for recurrent prefill as unexplored; the recurrence of Eq. 2 /
  * Eq. 3 is linear, so the state entering chunk j is lambda^c times the state
  * entering chunk j-1 plus what chunk j-1 reaches from zero).  The chunked scan
@@ -460,8 +461,10 @@ int srm_mixer_block(srm_model *m, int32_t layer, int32_t pos, const int32_t *d_p
  * ring of 2 / 4 / 8 stages, 9 / 10 = 256x256 as a persistent kernel (one work-group
  * per compute unit walks several tiles; needs K % 128 == 0, K >= 256, N % 4 == 0) /
  * as one work-group per tile (tile 0 takes the first form when there are more tiles
- * than compute units and the shape allows it).  Same values for every tile up to the fp32 summation
- * order inside a k tile (none: all tiles accumulate k in the same order).
+ * than compute units and the shape allows it), 11 .. 15 = 16x16, 32x16, 32x32, 64x32, 64x64
+ * with K cut over the wavefronts (not epilogue 3; N % 4 == 0), 16 / 17 / 18 = 192x256 (8),
+ * 96x128 and 128x64 (4, four-stage ring; not epilogue 3).  Tiles 11 .. 15 add the slices of K
+ * in slice order, all other tiles accumulate k in one order: two sets of equal values.
  * Errors: SRM_EINVAL (null operand or output, sizes <= 0, K % 64 with SRM_BF16,
  * unknown dtype, epilogue or tile code).
  */
