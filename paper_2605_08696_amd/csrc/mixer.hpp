@@ -494,8 +494,9 @@ scan_chunk_apply_kernel(const TAct *__restrict__ u, TAct *__restrict__ m, float 
 // (lam^(j0-1-i) p_i), so the block forms C[c] = sum_{i<j0} lam^(j0-1-i) p_i U[i][c] once (sixteen row groups side by
 // side, added in LDS) instead of 64 x j0 products per channel, and the square itself in two levels: sixteen groups of
 // four positions, whose sums F reach the later groups through LDS, and the 4 x 4 triangles written out.
-// lam^k comes from a per-block table of powers formed by squaring in double (every entry within a few units of 2^-53
-// before it is rounded), not from running products in fp32, so this path shares no rounding with the recurrence.
+// lam^k comes from a per-block table of powers formed by squaring in double (squaring doubles a relative error, so
+// entry k is within about k units of 2^-53 before it is rounded: 1e-12 at the longest table that fits), not from running
+// products in fp32, so this path shares no rounding with the recurrence.
 // Bound: reading U (and its prefix, out of the L2) with a few loads per thread in flight.  Measured for 6 x 500
 // positions of a 1024-wide layer: 12.8 us, against 102 for the explicit product in 64 x 64 x 64 tiles on the vector
 // units, whose time was T^2 d multiply-adds.
@@ -503,7 +504,11 @@ scan_chunk_apply_kernel(const TAct *__restrict__ u, TAct *__restrict__ m, float 
 // sequence's last position writes the state behind it: lam^(T-j0) C + sum_{i>=j0} lam^(T-1-i) p_i U[i].  One launch in
 // the place of the chunked scan's two, whose threads are few and wait for memory in a row: one sequence of 509
 // positions of 1024 channels 14.0 -> 8.6 us per layer, 24 prompts of up to 150 tokens of 512 channels 13.5 -> 7.
-// Dynamic LDS: T + 1 floats (the power table).
+// Dynamic LDS: parallel_table_floats(T) floats, the powers 0 .. T.  The exchange between the sixteen groups reads up to
+// power 60 whatever T is (groups behind the end of a sequence form sums that nobody stores), so the table always holds
+// the powers of one whole square.
+constexpr int kParSquare = 64;           // output positions of a block: sixteen groups of four
+__host__ __device__ constexpr int parallel_table_floats(int T) { return T + 1 > kParSquare ? T + 1 : kParSquare; }
 struct PrefillSeqs {
     float *S;                        // [nslots or all samples][d] of this layer
     const int32_t *offsets;          // ragged: sequence boundaries, else null: T rows each
@@ -519,7 +524,7 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
                       const float *__restrict__ lam, int n_ctx, int H, int hrow, int d, int T, PrefillSeqs ps)
 {
     typedef typename Raw4<TAct>::type raw_t;
-    extern __shared__ float pw[];            // [T + 1]
+    extern __shared__ float pw[];            // [parallel_table_floats(T of the launch)]
     __shared__ float4 part[16][16];          // [row group][four channels]
     const int dh = d / H;
     const int ctiles = (dh + 63) / 64;
@@ -563,7 +568,7 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
         }
     };
     if (g < j0) request(g);
-    for (int k = tid; k <= min(T, j0 + 64); k += 256) {
+    for (int k = tid; k < parallel_table_floats(min(T, j0 + kParSquare)); k += 256) {
         double sq = (double)lam[h], v = 1.0;
         for (int e = k; e; e >>= 1, sq *= sq)
             if (e & 1) v *= sq;

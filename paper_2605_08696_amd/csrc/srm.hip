@@ -1520,7 +1520,8 @@ static int prefill_mixer(const srm_model *m, int l, const Workspace &w, void *S_
     const int d = m->dm;           // the mixer's row width
     if (in_blocks) {
         const dim3 grid((unsigned)cdiv(P, 64), (unsigned)(m->Hs * cdiv(d / m->Hs, 64)), (unsigned)nc);
-        hipLaunchKernelGGL((mixer_parallel_kernel<T, true>), grid, dim3(256), (size_t)(P + 1) * sizeof(float), st,
+        hipLaunchKernelGGL((mixer_parallel_kernel<T, true>), grid, dim3(256),
+                           (size_t)parallel_table_floats(P) * sizeof(float), st,
                            static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, m->cfg.n_ctx,
                            m->Hs, m->hrow, d, P,
                            PrefillSeqs{static_cast<float *>(S_layer), offsets, base, rows, seq0, rep, slot, nslots});
@@ -1755,7 +1756,8 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
         auto mix = [&](int l) {
             const LayerDev &y = m->layers[l];
             const dim3 grid((unsigned)cdiv(T_, 64), (unsigned)(m->Hs * cdiv(dh, 64)), (unsigned)nc);
-            hipLaunchKernelGGL((mixer_parallel_kernel<T>), grid, dim3(256), (size_t)(T_ + 1) * sizeof(float), st,
+            hipLaunchKernelGGL((mixer_parallel_kernel<T>), grid, dim3(256),
+                               (size_t)parallel_table_floats(T_) * sizeof(float), st,
                                static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam,
                                m->cfg.n_ctx, m->Hs, m->hrow, dm, T_, PrefillSeqs{});
             HIP_TRY(hipGetLastError());

@@ -450,6 +450,35 @@ def test_chunked_scan_ragged_prompts(c1):
         assert int(tk[b]) == int(ref["tokens"][0, 0])
 
 
+@pytest.mark.parametrize("lens", [[1, 2, 3, 5, 59, 60, 61, 66], [64, 1], [63, 65, 4]])
+def test_block_scan_of_sequences_shorter_than_a_block(c1, lens):
+    """Short prompts next to one that puts the call on the block form: their groups behind the last position read the
+    power table past the sequence's own powers (the table holds a whole block's whatever the length).  The same
+    sequences alone through the parallel form, whose table is the shortest there.  Against the oracle."""
+    cfg, w, model, orc = c1
+    rng = np.random.default_rng(sum(lens))
+    prompts = rng.integers(0, cfg.vocab, (len(lens), max(lens))).astype(np.int32)
+    toks, off = _pack(prompts, lens)
+    N = len(lens)
+    ws = model.new_workspace(int(off[-1]))
+    st, tk = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+    st.fill_(float("nan"))
+    lg = torch.empty((N, cfg.vocab), dtype=torch.float32, device="cuda")
+    print(f"block scan lens={lens}", flush=True)
+    keep = model.prefill_ragged(to_dev(toks), off, st, tk, logits=lg, workspace=ws)
+    torch.cuda.synchronize()
+    del keep
+    sv = st.view(cfg.n_layers, N, cfg.d_model)
+    for b, n in enumerate(lens):
+        ref = orc.greedy(prompts[b:b + 1, :n], 1, want_logits=True)
+        assert rel_err_rows(lg[b:b + 1].cpu().numpy(), ref["logits"][:, 0]) <= 1e-4
+        assert np.abs(sv[:, b].cpu().numpy() - ref["state"][0]).max() <= 1e-4 * np.abs(ref["state"][0]).max()
+        hid = torch.empty((1, n, cfg.d_model), dtype=torch.float32, device="cuda")
+        model.parallel_forward(to_dev(prompts[b:b + 1, :n].copy()), hid, workspace=ws)
+        want = orc.parallel_forward(prompts[b:b + 1, :n])["hidden"]
+        assert np.abs(hid.cpu().numpy() - want).max() <= 1e-4 * np.abs(want).max()
+
+
 def test_skewed_lengths_fall_back_to_the_sequential_scan(c1, srm):
     """Many one-token prompts next to a long one: the chunk count of the chunked scan follows the long prompt,
     its scratch the few rows of the pass, so the call must take the sequential scan (and stay inside the
