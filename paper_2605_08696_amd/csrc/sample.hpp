@@ -343,12 +343,15 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
             z += e[k];
         }
         atomicAdd(&sum_s, z);
-        // the step of a logit above w0: never smaller for a larger logit
+        // the step of a logit above w0, never smaller for a larger logit: 0 where M - xw overflows (scale 0, and 0 times
+        // infinity), the last one where it is so small that scale is infinite
         const float scale = (float)kSteps / (M - xw);
-        auto place = [](float v, float xw_, float scale_) { return (v - xw_) * scale_; };
+        auto step_of = [](float v, float xw_, float scale_) {
+            return (int)fminf(fmaxf((v - xw_) * scale_, 0.0f), (float)(kSteps - 1));
+        };
 #pragma unroll
         for (int k = 0; k < EPT; ++k) {
-            if (x[k] > xw) atomicAdd(&hist[min(max((int)place(x[k], xw, scale), 0), kSteps - 1)], (u64)e[k]);
+            if (x[k] > xw) atomicAdd(&hist[step_of(x[k], xw, scale)], (u64)e[k]);
         }
         __syncthreads();
         const u64 target = (u64)ceil((double)top_p * (double)sum_s);
@@ -386,11 +389,9 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
             // places and comparisons in registers)
             float xw2 = xw, scale2 = scale;
             asm volatile("" : "+v"(xw2), "+v"(scale2));
-            const float from_u = cut > 0 ? (float)cut : -INFINITY, to_u = cut < kSteps - 1 ? (float)(cut + 1) : INFINITY;
 #pragma unroll
             for (int k = 0; k < EPT; ++k) {
-                const float u = place(x[k], xw2, scale2);
-                if (x[k] > xw2 && !(u < from_u) && !(u >= to_u)) {
+                if (x[k] > xw2 && step_of(x[k], xw2, scale2) == cut) {
                     const int at = atomicAdd(&count_s, 1);
                     if (at < kCand) cand[at] = make_uint2(order_key(x[k]), e[k]);
                 }

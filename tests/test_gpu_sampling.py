@@ -203,3 +203,35 @@ def test_topp_search_against_oracle_rule(srm, orc_mod, V, groups):
     torch.cuda.synchronize()
     tolerated, changed = _check_rows(orc_mod, out.cpu().numpy(), lg.cpu().numpy(), T, top_p, seed, lambda r: pos)
     assert tolerated <= 2 and changed > 0
+
+
+@pytest.mark.parametrize("V", [333, 1501])
+@pytest.mark.parametrize("kind", ["close", "far"])
+def test_topp_search_at_the_ends_of_the_float_range(srm, orc_mod, V, kind):
+    """Logits so close together that the search's steps per unit of logit are beyond the float range (all elements in
+    the last step: few enough to be gathered, and too many), and so far apart that the difference between the largest
+    and w0 is (all in the first step).  Both distributions put w0 outside the nucleus in a good part of the rows."""
+    cfg = srm_synth.tiny_config(vocab=V, d_model=64, n_layers=1, n_heads=4, n_ctx=16, seed=6)
+    w = srm_synth.make_weights(cfg, stress=True)
+    rng = np.random.default_rng(V)
+    if kind == "close":                              # equally likely within the precision of the noise
+        x, T, top_p = rng.standard_normal(V).clip(-3.2, 3.2) * 2e-37, 0.8, 0.7
+    else:                                            # one logit 3.6e38 above the others, at a temperature of that order
+        x, T, top_p = rng.uniform(-3.2e38, -3.1e38, V), 0.8e38, 0.05
+        x[V // 3] = 0.5e38
+    w["lnf_g"], w["lnf_b"] = np.zeros_like(w["lnf_g"]), np.eye(1, cfg.d_model, dtype=np.float32)[0]
+    w["head"] = np.zeros_like(w["head"])
+    w["head"][:, 0] = x                              # the logits of every row
+    B, seed, pos = 40, 12, 3
+    print(f"top-p search V={V} {kind}", flush=True)
+    model = srm.Model(cfg, w)
+    st = torch.zeros(cfg.n_layers * B * cfg.d_model, device="cuda")
+    lg = torch.empty((B, V), dtype=torch.float32, device="cuda")
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    model.decode_step(B, pos, to_dev(np.zeros(B, np.int32)), st, out, logits=lg, workspace=model.new_workspace(B),
+                      temperature=T, seed=seed, top_p=top_p)
+    torch.cuda.synchronize()
+    logits = lg.cpu().numpy()
+    assert np.array_equal(logits[0], w["head"][:, 0])
+    tolerated, changed = _check_rows(orc_mod, out.cpu().numpy(), logits, T, top_p, seed, lambda r: pos)
+    assert tolerated == 0 and changed > 3
