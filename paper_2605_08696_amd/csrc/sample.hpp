@@ -265,8 +265,10 @@ nucleus_kernel(const float *__restrict__ logits, int64_t ld, int V, float temp, 
 }
 
 // The rows nucleus_kernel<.., DEFER> listed, each held in registers for the whole search: a thread keeps the logits and
-// the probabilities of its EPT elements (V <= NT * EPT), these as integers, round(2^31 p / p_max), so that sums over
-// them are exact and do not depend on their order.  The elements above w0 go into a histogram of masses over equal
+// the probabilities p / p_max of its EPT elements (V <= NT * EPT).  Sums are taken over their images in units of 2^-47
+// (nucleus_mass), so they are exact, do not depend on their order, and a long tail counts: with V <= 2^15 elements the
+// total is short of the probabilities' by less than 2^-32 p_max, where a float sum rounds by 2^-24 of itself.
+// The elements above w0 go into a histogram of masses over equal
 // steps of logit value (LDS atomics); the step that the cut lies in holds a few dozen elements of most rows, which are
 // gathered, and each of them is asked whether the mass from it upwards reaches the target.  A step of more than kCand
 // elements (ties, extreme ranges) is left to a bisection over all elements.
@@ -275,6 +277,15 @@ nucleus_kernel(const float *__restrict__ logits, int64_t ld, int V, float temp, 
 // Persistent: block i takes list entries i, i + gridDim, ...  Arguments as
 // nucleus_kernel; tok[row] holds the unrestricted winner on entry.
 __device__ __forceinline__ float key_value(uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k); }
+
+// floor(2^47 e) for 0 <= e <= 1: the upper 23 bits, then the rest (both differences are exact); 0 for a NaN
+__device__ __forceinline__ unsigned long long nucleus_mass(float e)
+{
+    const float t = fmaxf(e, 0.0f) * 8388608.0f;                       // 2^23
+    const uint32_t hi = (uint32_t)t;
+    const uint32_t lo = (uint32_t)((t - (float)hi) * 16777216.0f);     // 2^24
+    return (unsigned long long)hi << 24 | lo;
+}
 
 constexpr int kCand = 512, kSteps = 1024;
 template <int NT, int EPT>
@@ -292,7 +303,8 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
     __shared__ float red[NW];
     __shared__ int redi[NW];
     __shared__ u64 hist[kSteps];
-    __shared__ uint2 cand[kCand];                    // key, mass
+    __shared__ u64 cand_mass[kCand];
+    __shared__ uint32_t cand_key[kCand];
     __shared__ u64 group_s[kSteps / 64];
     __shared__ u64 sum_s, above_s;                   // a block sum; the mass above the cut's step
     __shared__ int step_s, count_s;
@@ -307,7 +319,7 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
         // element k of this thread has index first + 4 NT (k / 4) + (k % 4) next; absent ones are -inf
         const int first = vec ? 4 * tid : tid, next = vec ? 1 : NT;
         float x[EPT];
-        uint32_t e[EPT];
+        float e[EPT];
         float mt = -INFINITY;
         if (vec) {
             const f32x4_t *L4 = reinterpret_cast<const f32x4_t *>(L);
@@ -336,23 +348,21 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
         for (int b = tid; b < kSteps; b += NT) hist[b] = 0;
         if (tid == 0) { sum_s = 0; count_s = 0; hi_s = 0; step_s = -1; }
         const float M = block_max<NW>(mt, red);      // (its barriers also order the stores above)
-        u64 z = 0;
-#pragma unroll
-        for (int k = 0; k < EPT; ++k) {
-            e[k] = (uint32_t)rintf(__builtin_amdgcn_exp2f((x[k] - M) * inv) * 2147483648.0f);    // absent: exp2(-inf) = 0
-            z += e[k];
-        }
-        atomicAdd(&sum_s, z);
         // the step of a logit above w0, never smaller for a larger logit: 0 where M - xw overflows (scale 0, and 0 times
         // infinity), the last one where it is so small that scale is infinite
         const float scale = (float)kSteps / (M - xw);
         auto step_of = [](float v, float xw_, float scale_) {
             return (int)fminf(fmaxf((v - xw_) * scale_, 0.0f), (float)(kSteps - 1));
         };
+        u64 z = 0;
 #pragma unroll
         for (int k = 0; k < EPT; ++k) {
-            if (x[k] > xw) atomicAdd(&hist[step_of(x[k], xw, scale)], (u64)e[k]);
+            e[k] = __builtin_amdgcn_exp2f((x[k] - M) * inv);           // absent: exp2(-inf) = 0
+            const u64 mass = nucleus_mass(e[k]);
+            z += mass;
+            if (x[k] > xw) atomicAdd(&hist[step_of(x[k], xw, scale)], mass);
         }
+        atomicAdd(&sum_s, z);
         __syncthreads();
         const u64 target = (u64)ceil((double)top_p * (double)sum_s);
         // suffix sums over groups of 64 steps, one group per wavefront at a time; then the step whose own mass takes the
@@ -393,7 +403,7 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
             for (int k = 0; k < EPT; ++k) {
                 if (x[k] > xw2 && step_of(x[k], xw2, scale2) == cut) {
                     const int at = atomicAdd(&count_s, 1);
-                    if (at < kCand) cand[at] = make_uint2(order_key(x[k]), e[k]);
+                    if (at < kCand) { cand_key[at] = order_key(x[k]); cand_mass[at] = nucleus_mass(e[k]); }
                 }
             }
             __syncthreads();
@@ -401,10 +411,10 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
             uint32_t hi;
             if (nc <= kCand) {
                 if (tid < nc) {
-                    const uint32_t key = cand[tid].x;
+                    const uint32_t key = cand_key[tid];
                     u64 f = above;
 #pragma unroll 4
-                    for (int j = 0; j < nc; ++j) f += cand[j].x >= key ? cand[j].y : 0u;
+                    for (int j = 0; j < nc; ++j) f += cand_key[j] >= key ? cand_mass[j] : 0;
                     if (f >= target) atomicMax(&hi_s, key);
                 }
                 __syncthreads();
@@ -421,7 +431,7 @@ nucleus_slow_kernel(const float *__restrict__ logits, int64_t ld, int V, float t
                     __syncthreads();
                     const float above_v = key_value(mid);              // (as floats: 64 keys would be kept over the loop)
 #pragma unroll
-                    for (int k = 0; k < EPT; ++k) f += x[k] > above_v ? e[k] : 0u;
+                    for (int k = 0; k < EPT; ++k) f += x[k] > above_v ? nucleus_mass(e[k]) : 0;
                     atomicAdd(&sum_s, f);
                     __syncthreads();
                     if (sum_s < target) hi = mid; else lo = mid;

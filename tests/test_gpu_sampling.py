@@ -235,3 +235,34 @@ def test_topp_search_at_the_ends_of_the_float_range(srm, orc_mod, V, kind):
     assert np.array_equal(logits[0], w["head"][:, 0])
     tolerated, changed = _check_rows(orc_mod, out.cpu().numpy(), logits, T, top_p, seed, lambda r: pos)
     assert tolerated == 0 and changed > 3
+
+
+@pytest.mark.parametrize("seed", [96672, 140406, 213598, 422384, 756542, 1199177])
+def test_topp_search_counts_a_long_flat_tail(srm, orc_mod, seed):
+    """One dominant token, 256 of probability 1.4e-6 and 31 743 of 2.4e-10 each, 7.5e-6 together.  The seeds (found with
+    the oracle's generator) draw one of the 256 whose mass from above exceeds the cut by 2e-6 .. 5e-6: outside the
+    nucleus, but inside for a search that loses or rounds up the tail.  At fp32 the streaming pass that lists the row
+    rounds by 2^-24 of a mass of 1, a thirtieth of that distance."""
+    V, pos = 32000, 3
+    x = np.full(V, np.log(0.51 * 2.0 ** -31))
+    x[0] = 0.0
+    mid = 1 + 120 * np.arange(256)
+    x[mid] = np.log(1.4e-6) - 1e-4 * np.arange(256)
+    top_p = float(np.float32(0.99981743))
+    cfg = srm_synth.tiny_config(vocab=V, d_model=64, n_layers=1, n_heads=4, n_ctx=16, seed=6)
+    w = srm_synth.make_weights(cfg, stress=True)
+    w["lnf_g"], w["lnf_b"] = np.zeros_like(w["lnf_g"]), np.eye(1, cfg.d_model, dtype=np.float32)[0]
+    w["head"] = np.zeros_like(w["head"])
+    w["head"][:, 0] = x                              # the logits, whatever the token
+    print(f"top-p search with a flat tail, seed={seed}", flush=True)
+    model = srm.Model(cfg, w)
+    lg = torch.empty((1, V), dtype=torch.float32, device="cuda")
+    out = torch.empty(1, dtype=torch.int32, device="cuda")
+    model.decode_step(1, pos, to_dev(np.zeros(1, np.int32)), torch.zeros(cfg.n_layers * cfg.d_model, device="cuda"), out,
+                      logits=lg, workspace=model.new_workspace(1), temperature=1.0, seed=seed, top_p=top_p)
+    torch.cuda.synchronize()
+    logits = lg.cpu().numpy()[0]
+    assert np.array_equal(logits, w["head"][:, 0])
+    drawn = orc_mod.pick(logits, 1.0, seed, pos, 0)
+    assert drawn in mid[130:133]
+    assert int(out[0]) == orc_mod.pick_topp(logits, 1.0, top_p, seed, pos, 0) != drawn
