@@ -703,12 +703,13 @@ static bool f32_tiles_ok(const float *A, const float *W, int K, const GemmEpi &e
 
 template <int EPI>
 static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, GemmEpi ep, hipStream_t st,
-                      int *nparts_out)
+                      int *nparts_out, int64_t call_rows)
 {
     if (M <= 0 || M >= (1 << 30) || N <= 0 || K <= 0) return fail(SRM_EINVAL, "GEMM shape out of range");
     ep.nparts = (int)cdiv(N, 64);
     if (nparts_out) *nparts_out = ep.nparts;
-    if (gemv_rows_ok<float>(M, K) && (EPI == EPI_ARGMAX || !f32_tiles_ok(A, W, K, ep))) {
+    // (by the rows of the call: the GEMV sums in an order of its own, see slices_ok)
+    if (gemv_rows_ok<float>(std::max(M, call_rows), K) && (EPI == EPI_ARGMAX || !f32_tiles_ok(A, W, K, ep))) {
         // LM head of few rows (and operands the tiles do not take): stream W once per group of kGemvMB rows (64 columns
         // per block where the partial winners of the LM head are counted per 64 columns, or where 16 would make too
         // many blocks)
@@ -800,7 +801,7 @@ static int linear(const void *A, const void *W, const float *bias, int64_t M, in
                                       st, min_bn, nparts_out, call_rows);
     else
         return launch_f32<EPI>(static_cast<const float *>(A), static_cast<const float *>(W), M, N, K, ep, st,
-                               nparts_out);
+                               nparts_out, call_rows);
 }
 
 struct TokenStore {        // optional second destination of the greedy tokens (srm_generate)
@@ -1069,16 +1070,16 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     return SRM_OK;
 }
 
-// LM head on M normalised rows `a`: optional fp32 logits, greedy token written
+// LM head on M normalised rows `a` (of call_rows in the whole call): optional fp32 logits, greedy token written
 // `rep` times at d_tok[(row0 + row) * rep + r].
 template <typename T>
-static int head_argmax(const srm_model *m, const Workspace &w, const void *a, int64_t M, float *logits,
+static int head_argmax(const srm_model *m, const Workspace &w, const void *a, int64_t M, int64_t call_rows, float *logits,
                        int32_t *d_tok, int64_t row0, int rep, hipStream_t st, TokenStore ts = TokenStore(),
                        Sampling sm = Sampling(), FinalizeRagged rg = FinalizeRagged{})
 {
     int nparts = 0;
     SRM_TRY((linear<EPI_ARGMAX, T>(a, m->head, nullptr, M, m->V, m->d, logits, st, w.pv, w.pi, head_min_bn(m),
-                                   &nparts, sm)));
+                                   &nparts, sm, MixArgs(), call_rows)));
     return argmax_finalize(w.pv, w.pi, M, nparts, d_tok, row0, rep, m->V, st, ts, rg);
 }
 
@@ -1150,7 +1151,7 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     }
     if (topp) rg.zero_counter = w.slow;
     float *lg = a.logits ? a.logits + (size_t)b0 * m->V : nullptr;
-    SRM_TRY((head_argmax<T>(m, w, w.a, nb, lg, a.tok_out, b0, 1, st, a.ts, sm, rg)));
+    SRM_TRY((head_argmax<T>(m, w, w.a, nb, a.B, lg, a.tok_out, b0, 1, st, a.ts, sm, rg)));
     if (topp)
         SRM_TRY(nucleus(lg, nb, m->V, sm, a.tok_out + b0, a.ts.store ? a.ts.store + b0 : nullptr, a.ts.step_dev,
                         a.ts.stride, (pos_rows && a.advance) ? pos_rows : nullptr, w.slow, st));
@@ -1584,7 +1585,7 @@ static int prefill_impl(srm_model *m, const int32_t *prompts, int N, int P, int 
         // final LayerNorm of each prompt's last position only, packed [nc][d] into w.a
         SRM_TRY((layernorm<T, false>(m, w.x + (size_t)(P - 1) * d, (int64_t)P * d, nullptr, nullptr, m->lnf_g,
                                      m->lnf_b, w.a, nc, st)));
-        SRM_TRY((head_argmax<T>(m, w, w.a, nc, logits ? logits + (size_t)n0 * m->V : nullptr, next_tok, n0, k, st)));
+        SRM_TRY((head_argmax<T>(m, w, w.a, nc, N, logits ? logits + (size_t)n0 * m->V : nullptr, next_tok, n0, k, st)));
     }
     return SRM_OK;
 }
@@ -1650,7 +1651,7 @@ static int prefill_ragged_impl(srm_model *m, const int32_t *tokens, const int32_
         rg.nslots = state_batch;
         rg.offsets = d_off;
         rg.pos_set = pos_out;
-        SRM_TRY((head_argmax<T>(m, w, w.a, nc, logits ? logits + (size_t)n0 * m->V : nullptr, next_tok, n0, k, st,
+        SRM_TRY((head_argmax<T>(m, w, w.a, nc, N, logits ? logits + (size_t)n0 * m->V : nullptr, next_tok, n0, k, st,
                                 TokenStore(), Sampling(), rg)));
     }
     return SRM_OK;

@@ -525,6 +525,29 @@ def test_bf16_decode_does_not_depend_on_its_slices(srm, d, B, rows):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("B", [257, 272, 288, 530])
+def test_fp32_calls_with_a_short_last_pass(srm, B):
+    """Last passes of 1, 16, 32 and 18 rows, for which the LM head of a call that small runs as a GEMV: logits, tokens
+    and states of a decode step and of a prefill of as many prompts equal the one-pass call bit for bit."""
+    cfg = srm_synth.tiny_config(vocab=300, d_model=64, n_layers=1, n_heads=4, n_ctx=16, seed=84)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    prompts = to_dev(np.random.default_rng(B).integers(0, cfg.vocab, (B, 2)).astype(np.int32))
+    tok0 = prompts[:, 0].contiguous()
+    print(f"short last pass B={B}", flush=True)
+    got = []
+    for rows in (B, 256):
+        lg, lgp = (torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda") for _ in range(2))
+        tk, tkp = (torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2))
+        st, stp = model.new_state(B), model.new_state(B)
+        st.zero_()
+        model.decode_step(B, 0, tok0, st, tk, logits=lg, workspace=model.new_workspace(rows))
+        model.prefill(prompts, 1, stp, tkp, logits=lgp, workspace=model.new_workspace(2 * rows))
+        torch.cuda.synchronize()
+        got.append((lg, tk, st, lgp, tkp, stp))
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("dtype_name", ["fp32", "bf16"])
 def test_workspace_bytes_grows_monotonically(srm, dtype_name):
     """The calls find the rows a workspace holds by bisection over srm_workspace_bytes."""
