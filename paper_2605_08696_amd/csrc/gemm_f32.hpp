@@ -21,7 +21,8 @@
 // sees every k once, in another order than the memory's.  The product is formed transposed (W first), so a lane
 // holds four consecutive output columns of one row per register quad.
 // LDS rows are 128 bytes (32 k), 16-byte chunk c of row r at c ^ ((r >> 1) & 7), as in gemm_bf16_kernel.
-// Needs K % 4 == 0 and 16-byte aligned operands and outputs (launch_f32 falls back to gemm_f32_kernel otherwise).
+// Needs K % 4 == 0, 16-byte aligned operands, and outputs aligned so where N % 4 == 0 (launch_f32 falls back to
+// gemm_f32_kernel otherwise).
 #pragma once
 #include "gemm.hpp"
 

@@ -695,10 +695,13 @@ static int launch_f32_tiles(const float *A, const float *W, int M, int N, int K,
     HIP_TRY(hipGetLastError());
     return SRM_OK;
 }
-// whole 16-byte vectors along K (and of the outputs' rows where N % 4 == 0), byte offsets within a descriptor
-static bool f32_tiles_ok(const float *A, const float *W, int K, const GemmEpi &ep)
+// Whole 16-byte vectors along K, and of the outputs' rows where the tiles store them as vectors (N % 4 == 0; elements
+// otherwise, so that a pass of a call with odd rows takes the kernel of its other passes wherever its output starts);
+// byte offsets within a descriptor.
+static bool f32_tiles_ok(const float *A, const float *W, int N, int K, const GemmEpi &ep)
 {
-    return K % 4 == 0 && K <= (1 << 20) && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)ep.out | (uintptr_t)ep.state) & 15) == 0;
+    const uintptr_t outputs = N % 4 ? 0 : (uintptr_t)ep.out | (uintptr_t)ep.state;
+    return K % 4 == 0 && K <= (1 << 20) && (((uintptr_t)A | (uintptr_t)W | outputs) & 15) == 0;
 }
 
 template <int EPI>
@@ -709,13 +712,13 @@ static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, G
     ep.nparts = (int)cdiv(N, 64);
     if (nparts_out) *nparts_out = ep.nparts;
     // (by the rows of the call: the GEMV sums in an order of its own, see slices_ok)
-    if (gemv_rows_ok<float>(std::max(M, call_rows), K) && (EPI == EPI_ARGMAX || !f32_tiles_ok(A, W, K, ep))) {
+    if (gemv_rows_ok<float>(std::max(M, call_rows), K) && (EPI == EPI_ARGMAX || !f32_tiles_ok(A, W, N, K, ep))) {
         // LM head of few rows (and operands the tiles do not take): stream W once per group of kGemvMB rows (64 columns
         // per block where the partial winners of the LM head are counted per 64 columns, or where 16 would make too
         // many blocks)
         if (EPI == EPI_ARGMAX || N >= 16384) return launch_gemv_rows<float, float, EPI, 4>(A, W, (int)M, N, K, ep, st, nparts_out);
         return launch_gemv_rows<float, float, EPI, 1>(A, W, (int)M, N, K, ep, st, nparts_out);
-    } else if (f32_tiles_ok(A, W, K, ep)) {
+    } else if (f32_tiles_ok(A, W, N, K, ep)) {
         return launch_f32_tiles<EPI>(A, W, (int)M, N, K, ep, st);
     } else {
         const int64_t nb = cdiv(M, 64) * cdiv(N, 64);
