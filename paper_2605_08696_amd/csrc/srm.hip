@@ -711,11 +711,18 @@ static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, G
     if (M <= 0 || M >= (1 << 30) || N <= 0 || K <= 0) return fail(SRM_EINVAL, "GEMM shape out of range");
     ep.nparts = (int)cdiv(N, 64);
     if (nparts_out) *nparts_out = ep.nparts;
-    // (by the rows of the call: the GEMV sums in an order of its own, see slices_ok)
-    if (gemv_rows_ok<float>(std::max(M, call_rows), K) && (EPI == EPI_ARGMAX || !f32_tiles_ok(A, W, N, K, ep))) {
-        // LM head of few rows (and operands the tiles do not take): stream W once per group of kGemvMB rows (64 columns
-        // per block where the partial winners of the LM head are counted per 64 columns, or where 16 would make too
-        // many blocks)
+    // The streaming GEMV: the LM head of few rows, operands the tiles do not take, and at most one of its passes
+    // (kGemvMB rows) over a weight matrix so wide that launch_f32_tiles would take the 64x64 tile, most of whose rows are
+    // padding then: bound by reading W (us, tile | GEMV: 8 x 32000 x 1024: 45.6 | 31, 1 x 24000 x 1024: 41 | 24.4, 8 x
+    // 32000 x 256: 15.3 | 10.9, 4 x 16384 x 256: 9.2 | 7.8, 8 x 12800 x 1024: 25.5 | 23.0; with fewer columns or more rows
+    // the tiles win: 8 x 14000 x 256: 9.2 | 10.8, 4 x
+    // 16384 x 64: 4.9 | 5.2, 9 x 16384 x 256: 9.3 | 11.3; rows x columns x K).  By the rows of the
+    // call: the GEMV sums in an order of its own, see slices_ok.
+    const int64_t call = std::max(M, call_rows);
+    const bool wide = call <= kGemvMB && cdiv(N, 64) >= 200 && (N >= (K >= 256 ? 16384 : 20000) || K >= 1024);
+    if (gemv_rows_ok<float>(call, K) && (EPI == EPI_ARGMAX || wide || !f32_tiles_ok(A, W, N, K, ep))) {
+        // (64 columns per block where the partial winners of the LM head are counted per 64 columns, or where 16 would
+        // make too many blocks)
         if (EPI == EPI_ARGMAX || N >= 16384) return launch_gemv_rows<float, float, EPI, 4>(A, W, (int)M, N, K, ep, st, nparts_out);
         return launch_gemv_rows<float, float, EPI, 1>(A, W, (int)M, N, K, ep, st, nparts_out);
     } else if (f32_tiles_ok(A, W, N, K, ep)) {

@@ -118,6 +118,14 @@ def test_linear_fp32_matrix_cores(srm, shape, epi):
     _linear_case(srm, srm.SRM_FP32, M, N, K, epi, None, seed=M * 3 + epi)
 
 
+@pytest.mark.parametrize("shape", [(8, 16384, 256), (9, 16384, 256), (1, 20001, 64), (8, 12800, 1024), (8, 12796, 1024)])
+@pytest.mark.parametrize("epi", [0, 2, 4])
+def test_linear_fp32_few_rows_of_a_wide_matrix(srm, shape, epi):
+    """Both sides of the rule that sends at most eight rows over a wide weight matrix to the streaming GEMV."""
+    M, N, K = shape
+    _linear_case(srm, srm.SRM_FP32, M, N, K, epi, None, seed=M + N + epi)
+
+
 @pytest.mark.parametrize("dtype_name", ["fp32", "bf16"])
 def test_argmax_ties_go_to_the_lowest_index(srm, dtype_name):
     dtype = srm.SRM_BF16 if dtype_name == "bf16" else srm.SRM_FP32

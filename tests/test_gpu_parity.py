@@ -617,17 +617,13 @@ def test_parallel_form_at_the_edges_of_its_blocks(srm, orc_mod, T):
     assert np.abs(hid.cpu().numpy() - ref["hidden"]).max() <= 1e-4 * np.abs(ref["hidden"]).max()
 
 
-@pytest.mark.parametrize("vocab", [301, 1002, 4096])
-def test_parallel_form_does_not_depend_on_its_passes(srm, vocab):
-    """Logits rows of a vocabulary that is no multiple of four start at every alignment: each pass of the call takes the
-    same GEMM kernel, so hidden states and logits equal the one-pass call bit for bit."""
-    cfg = srm_synth.tiny_config(vocab=vocab, d_model=64, n_layers=1, n_heads=4, n_ctx=16, seed=85)
+def _parallel_in_passes(srm, vocab, B, T, d, per_pass):
+    cfg = srm_synth.tiny_config(vocab=vocab, d_model=d, n_layers=1, n_heads=4, n_ctx=16, seed=85)
     model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
-    B, T = 14, 7
     toks = to_dev(srm_synth.make_prompts(cfg, batch=B, length=T, seed=vocab))
-    print(f"parallel form in passes vocab={vocab}", flush=True)
+    print(f"parallel form in passes vocab={vocab} B={B} T={T}", flush=True)
     got = []
-    for seqs in (B, 1, 3):
+    for seqs in (B, *per_pass):
         hid = torch.empty((B, T, cfg.d_model), dtype=torch.float32, device="cuda")
         lg = torch.empty((B, T, vocab), dtype=torch.float32, device="cuda")
         model.parallel_forward(toks, hid, logits=lg, workspace=model.new_workspace(seqs * T))
@@ -635,3 +631,16 @@ def test_parallel_form_does_not_depend_on_its_passes(srm, vocab):
         got.append((hid, lg))
     for hid, lg in got[1:]:
         assert torch.equal(hid, got[0][0]) and torch.equal(lg, got[0][1])
+
+
+@pytest.mark.parametrize("vocab", [301, 1002, 4096])
+def test_parallel_form_does_not_depend_on_its_passes(srm, vocab):
+    """Logits rows of a vocabulary that is no multiple of four start at every alignment: each pass of the call takes the
+    same GEMM kernel, so hidden states and logits equal the one-pass call bit for bit."""
+    _parallel_in_passes(srm, vocab, 14, 7, 64, (1, 3))
+
+
+@pytest.mark.parametrize("B,T", [(2, 4), (3, 3)])
+def test_parallel_form_of_few_rows_over_a_wide_head(srm, B, T):
+    """Eight rows of a call take the GEMV for such logits in every pass, nine rows the tiles in every pass."""
+    _parallel_in_passes(srm, 20004, B, T, 64, (1,))
