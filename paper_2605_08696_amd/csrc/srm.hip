@@ -577,9 +577,15 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 // 15.4 | 13.6, 700 x 4096 x 1024: 14.1 | 12.4 (296: 16.3 | 21.6).  192x256 from 188 to 256: 2500 x 4096 x 1024: 33.4 |
 // 28.1, 9000 x 1024 x 4096: 103 | 79 (176: 23.7 | 26.2; 304: 34.9 | 49.4), and two or three rounds of it that are full
 // where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8.  Every tile gives the same bits.
-static int choose_one_round_tile(int64_t M, int N, int K)
+// Rows of odd width (N % 4) are stored by element, which the small tiles spread over more wavefronts: where choose_tile
+// takes the 64x64 tile, that stays up to about one tile per CU (300 x 1022 x 1024: 9.0 | 9.7, with the residual epilogue
+// 12.2 | 16.0; 1800 x 514 x 4096, 261 tiles: 20.1 | 22.7; 297: 26.0 | 21.8), and, unless the epilogue is a plain store, for
+// short k loops beyond (residual: 2100 x 1022 x 512: 14.8 | 20.4, x 1024: 19.0 | 22.4, x 4096: 41.9 | 38.0; store, x 512:
+// 11.5 | 10.7).
+static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store)
 {
     if (K < 512) return -1;                          // (rings of four k tiles)
+    if (N % 4 && choose_tile(M, N, K, 64) == 2 && (cdiv(M, 64) * cdiv(N, 64) <= 288 || (!plain_store && K < 4096))) return -1;
     if (cdiv(M, 128) * cdiv(N, 64) <= 256) return 18;
     if (cdiv(M, 96) * cdiv(N, 128) <= 256) return 17;
     const int64_t t192 = cdiv(M, 192) * cdiv(N, 256), t256 = cdiv(M, 256) * cdiv(N, 256);
@@ -606,7 +612,7 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
         if (g_force_tile < 0 && slices_ok(std::max(M, call_rows), N, K)) return launch_slices<EPI>(A, W, m, N, K, ep, st);
     int tile = g_force_tile;
     if constexpr (EPI != EPI_ARGMAX)
-        if (tile < 0) tile = choose_one_round_tile(M, N, K);
+        if (tile < 0) tile = choose_one_round_tile(M, N, K, EPI == EPI_STORE || EPI == EPI_F32);
     if (tile < 0) tile = choose_tile(M, N, K, min_bn);
     ep.nparts = (int)cdiv(N, tile_bn(tile));
     if (nparts_out) *nparts_out = ep.nparts;
