@@ -575,8 +575,9 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 // columns x K): 128x64 up to 256 tiles: 1300 x 1024 x 4096: 27.7 | 23.4, 2048 x 1024 x 1024: 11.8 | 11.3, 700 x 2048 x
 // 1024: 10.2 | 8.9 (320 tiles: 14.9 | 18.0).  96x128 up to 256: 2500 x 1024 x 4096: 34.1 | 30.2, 3000 x 1024 x 1024:
 // 15.4 | 13.6, 700 x 4096 x 1024: 14.1 | 12.4 (296: 16.3 | 21.6).  192x256 from 188 to 256: 2500 x 4096 x 1024: 33.4 |
-// 28.1, 9000 x 1024 x 4096: 103 | 79 (176: 23.7 | 26.2; 304: 34.9 | 49.4), and two or three rounds of it that are full
-// where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8.  Every tile gives the same bits.
+// 28.1, 9000 x 1024 x 4096: 103 | 79 (176: 23.7 | 26.2; 304: 34.9 | 49.4; not while the 128x128 tiles fit two per CU,
+// where its rows are padding: 1000 x 8192 x 2048: 40.1 | 45.3, 200 x 32000 x 1024: 28.1 | 31.0), and two or three rounds of
+// it that are full where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8.  Every tile gives the same bits.
 // Rows of odd width (N % 4) are stored by element, which the small tiles spread over more wavefronts: where choose_tile
 // takes the 64x64 tile, that stays up to about one tile per CU (300 x 1022 x 1024: 9.0 | 9.7, with the residual epilogue
 // 12.2 | 16.0; 1800 x 514 x 4096, 261 tiles: 20.1 | 22.7; 297: 26.0 | 21.8), and, unless the epilogue is a plain store, for
@@ -589,7 +590,7 @@ static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store)
     if (cdiv(M, 128) * cdiv(N, 64) <= 256) return 18;
     if (cdiv(M, 96) * cdiv(N, 128) <= 256) return 17;
     const int64_t t192 = cdiv(M, 192) * cdiv(N, 256), t256 = cdiv(M, 256) * cdiv(N, 256);
-    if (t192 >= 188 && t192 <= 256) return 16;
+    if (t192 >= 188 && t192 <= 256 && cdiv(M, 128) * cdiv(N, 128) > 512) return 16;
     const int64_t r192 = cdiv(t192, 256) * 256, r256 = cdiv(t256, 256) * 256;
     if (t192 > 256 && t192 <= 768 && t192 * 20 >= r192 * 19 && t256 * 5 < r256 * 4) return 16;
     return -1;
