@@ -512,9 +512,11 @@ static int launch_slices_tile(const bf16 *A, const bf16 *W, int M, int N, int K,
 // 4096, 256: 19.1 | 15.8; 1900 x 512 x 2048, 240: 12.2 | 9.7; 300 x 4096 x 1024, 320 tiles: 9.4 | 11.4; 3000 x 512 x
 // 512, 376: 7.5 | 9.7 (rows x columns x K).  M is the row count of the whole call: its sums run in another order than
 // those of the other tiles, and a call that the workspace cuts into passes should not change with the cut.
+// With fewer than five k tiles half of the wavefronts have no slice; there the form ends with its 64x32 tile (2500 x 256 x
+// 64: 3.5 | 4.3, x 256: 4.2 | 4.7, 1024 x 1024 x 128: 3.9 | 4.6; with five k tiles it is the faster one again).
 static bool slices_ok(int64_t M, int N, int K)
 {
-    return N % 4 == 0 && K % 64 == 0 && cdiv(M, 64) * cdiv(N, 64) <= device_cus();
+    return N % 4 == 0 && K % 64 == 0 && cdiv(M, 64) * cdiv(N, K > 32 * kSliceWaves ? 64 : 32) <= device_cus();
 }
 // ... and with which tile: the smallest whose tiles still fit the chip in one round, since the time of a work-group
 // is proportional to the cache lines it loads (us with tiles of 16x16 | 32x16 | 32x32 | 64x32 | 64x64: 64 x 1024 x
