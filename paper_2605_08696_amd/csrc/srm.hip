@@ -349,15 +349,18 @@ struct Workspace {
     int *ctr;          // [2] position and step counters of srm_generate
     int *slow;         // [64 + rows] nucleus pass: count, then (from slow + 64) the rows that need the search
     unsigned char *mega;  // [kMegaScratch] one-kernel small-batch path: partial winners and the barrier words
-    float *part;       // [slices][rows][d] slabs of a residual projection (rows <= kSplitMaxRows), else null
+    float *part;       // [d / 128][rows][d] slabs of the one-kernel token mixing where it can run (rows <= kSplitMaxRows), else null
     size_t bytes;
 };
 
-// Slabs of a residual projection that the following LayerNorm kernel adds to the residual stream, in slab order
-// (deterministic).  One-kernel token mixing (at most kSplitMaxRows rows): d / 128 <= 4 slabs of the out-projection;
-// room for kSlabs.
-constexpr int kSlabs = 8;
+// Slabs of the out-projection that the one-kernel token mixing leaves and the following LayerNorm kernel adds to the
+// residual stream, in slab order (deterministic): d / 128 of them, for calls of at most kSplitMaxRows rows of a model
+// whose token mixing can be one kernel.
 constexpr int64_t kSplitMaxRows = 2048;
+static bool token_mix_shape_ok(const srm_model *m)
+{
+    return m->wsize == 2 && !m->noproj && m->dm == m->d && (m->d == 256 || m->d == 512);
+}
 // fp32 LM heads of at most kGemvRows rows run as GEMVs.
 constexpr int64_t kGemvRows = 32;
 
@@ -386,10 +389,9 @@ static Workspace carve(const srm_model *m, void *base, int64_t rows)
     w.pi = reinterpret_cast<int32_t *>(take(r * nparts * 4));
     w.slow = reinterpret_cast<int *>(take(256 + r * 4));
     // sized so that the workspace grows monotonically with the row count
-    const size_t part_rows = std::max<size_t>((size_t)kSlabs * std::min<int64_t>(rows, kSplitMaxRows),
-                                              (size_t)kSlabs * std::min<int64_t>(rows, kGemvRows));
-    float *part = reinterpret_cast<float *>(take(part_rows * d * 4));
-    w.part = rows <= kSplitMaxRows ? part : nullptr;
+    const size_t slabs = token_mix_shape_ok(m) ? d / kTokMixCols : 0;
+    float *part = reinterpret_cast<float *>(take(slabs * std::min<int64_t>(rows, kSplitMaxRows) * d * 4));
+    w.part = slabs && rows <= kSplitMaxRows ? part : nullptr;
     w.mega = take(kMegaScratch);
     w.ctr = reinterpret_cast<int *>(take(256));
     w.bytes = off;
@@ -934,10 +936,6 @@ static bool fuse_mixer(const srm_model *m, int64_t rows)
 // layer can be one kernel, that is the shorter step from kTokMixMinRows rows on.  SRM_LN_ON_LOAD=0 in the environment
 // keeps the separate kernels.
 constexpr int64_t kTokMixMinRows = 9;
-static bool token_mix_shape_ok(const srm_model *m)
-{
-    return m->wsize == 2 && !m->noproj && m->dm == m->d && (m->d == 256 || m->d == 512);
-}
 static bool ln_on_load(const srm_model *m, int64_t rows)
 {
     if (m->noproj || !(m->wsize == 2 ? lna_ok<bf16>(rows, m->dm, m->d) : lna_ok<float>(rows, m->dm, m->d))) return false;

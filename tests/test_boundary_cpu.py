@@ -166,6 +166,15 @@ def test_plan_rejects_what_the_prefill_rejects(srm):
         srm.prefill_ragged_plan(cfg, [0, 20], srm.workspace_bytes_config(cfg, 8))   # workspace below one prompt
 
 
+@pytest.mark.parametrize("dtype,d,slabs", [("fp32", 256, 0), ("bf16", 1024, 0), ("bf16", 256, 2), ("bf16", 512, 4)])
+def test_workspace_holds_token_mixing_slabs_only_where_they_are_used(srm, dtype, d, slabs):
+    """Up to 2048 rows a workspace holds d / 128 fp32 slabs for the models whose token mixing can be one kernel, and
+    none for the others."""
+    cfg = srm_synth.tiny_config(vocab=64, d_model=d, n_layers=1, n_heads=4, n_ctx=16, weight_dtype=dtype)
+    size = {r: srm.workspace_bytes_config(cfg, r) for r in (1024, 2048, 4096, 8192)}
+    assert size[2048] - size[1024] == (size[8192] - size[4096]) // 4 + 1024 * slabs * d * 4
+
+
 def test_binding_shape_checks(srm):
     cfg = srm_synth.tiny_config(vocab=32, d_model=16, n_layers=1, n_heads=2, n_ctx=16)
     w = srm_synth.make_weights(cfg)
