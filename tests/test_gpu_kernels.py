@@ -100,6 +100,39 @@ def test_linear_bf16_one_round_tiles(srm, shape, tile):
         _linear_case(srm, srm.SRM_BF16, M, N, K, epi, tile, seed=M + N + K + epi)
 
 
+def _linear_f32_out(srm, dtype, A, W, bias, tile=None):
+    out = torch.full((A.shape[0], W.shape[0]), 7.0, dtype=torch.float32, device="cuda")
+    srm.linear(dtype, 4, A, W, bias, out=out, tile=tile)
+    return out
+
+
+@pytest.mark.parametrize("shape", [(300, 332, 320), (130, 1000, 1088), (520, 516, 2048)])
+def test_linear_bf16_tiles_give_the_same_bits(srm, shape):
+    """The two sets of equal values that the choice among tiles relies on: the slice tiles (11 .. 15), and the tiles that
+    accumulate k in one order (0 .. 8, 10, 16 .. 18, and the persistent form where it takes the shape)."""
+    M, N, K = shape
+    rng = np.random.default_rng(M)
+    A, W = (to_dev(srm_synth.round_to_bf16(rng.standard_normal(s).astype(np.float32)), torch.bfloat16)
+            for s in ((M, K), (N, K)))
+    bias = to_dev(rng.standard_normal(N).astype(np.float32))
+    print(f"equal bits M={M} N={N} K={K}", flush=True)
+    for tiles in ((11, 12, 13, 14, 15), (0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 16, 17, 18) + ((9,) if K % 128 == 0 else ())):
+        outs = [_linear_f32_out(srm, srm.SRM_BF16, A, W, bias, t) for t in tiles]
+        for t, o in zip(tiles, outs):
+            assert torch.equal(o, outs[0]), f"tile {t} differs from tile {tiles[0]}"
+
+
+@pytest.mark.parametrize("N,K", [(832, 256), (832, 1028), (260, 36)])
+def test_linear_fp32_rows_do_not_depend_on_the_launch(srm, N, K):
+    """The fp32 matrix-core tiles (16, 32 with either ring, 64) give a row the same bits: 40, 200, 500 and 1030 rows."""
+    rng = np.random.default_rng(N + K)
+    A, W, bias = (to_dev(rng.standard_normal(s).astype(np.float32)) for s in ((1030, K), (N, K), (N,)))
+    print(f"fp32 rows N={N} K={K}", flush=True)
+    whole = _linear_f32_out(srm, srm.SRM_FP32, A, W, bias)
+    for M in (1, 40, 200, 500):
+        assert torch.equal(_linear_f32_out(srm, srm.SRM_FP32, A[:M].contiguous(), W, bias), whole[:M])
+
+
 @pytest.mark.parametrize("shape", [(1, 5, 3), (8, 256, 256), (70, 130, 37), (128, 64, 100), (5, 130, 64), (17, 70, 128),
                                    (32, 4096, 256), (33, 64, 64)])
 @pytest.mark.parametrize("epi", [0, 1, 2, 3, 4])
