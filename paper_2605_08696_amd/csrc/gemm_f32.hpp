@@ -20,6 +20,11 @@
 // j = 0 .. 3 of the s-th group of 8 (16x16: k = 16 s + 4 q + j), the same mapping for A and W, so the contraction
 // sees every k once, in another order than the memory's.  The product is formed transposed (W first), so a lane
 // holds four consecutive output columns of one row per register quad.
+// NA: how many sums a slice of K is kept in, 1 or kFine = 8 (by j and by the half of a 32-wide k tile), added in pairs at
+// the end of the slice.  Eight for calls of at most 32 rows: against 64-bit arithmetic the logits of a 256-wide, 4-layer
+// model are off by 5.0e-7 of their norm with one sum, by 2.9e-7 with the GEMV that these kernels replaced there (16 lanes
+// per dot product) and by 2.8e-7 with eight; up to 0.1 us per launch.  One for larger calls, where gemm_f32_kernel was off
+// by 9.7e-7 and one sum is by 5.0e-7 (four: 3.1e-7, but 4096 x 4096 x 256 takes 106 us instead of 99).
 // LDS rows are 128 bytes (32 k), 16-byte chunk c of row r at c ^ ((r >> 1) & 7), as in gemm_bf16_kernel.
 // Needs K % 4 == 0, 16-byte aligned operands, and outputs aligned so where N % 4 == 0 (launch_f32 falls back to
 // gemm_f32_kernel otherwise).
@@ -29,6 +34,7 @@
 namespace f32gemm {
 constexpr int BK = 32;
 constexpr int kSlices = 4;                 // slices of K, whose sums are added in order
+constexpr int kFine = 8;
 
 __device__ __forceinline__ u32x4_t descriptor(const void *base, int bytes)
 {
@@ -61,15 +67,33 @@ constexpr int kOutside = 0x7ffffff0;       // a byte offset past every descripto
 
 // The products of one 32-wide k tile on a 32x32 tile, operands as four 16-byte reads per lane (read s holds k = 8 s +
 // 4 (lane / 32) + j): two 32x32x2 products for each 16x16x4 one of the 16-wide tile, over the same four k.
-__device__ __forceinline__ void mfma_k32(const f32x4_t (&fw)[4], const f32x4_t (&fa)[4], f32x16_t &acc)
+template <int NA>
+__device__ __forceinline__ void mfma_k32(const f32x4_t (&fw)[4], const f32x4_t (&fa)[4], f32x16_t (&acc)[NA])
 {
 #pragma unroll
     for (int s = 0; s < 4; s += 2)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s][j], fa[s][j], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s + 1][j], fa[s + 1][j], acc, 0, 0, 0);
+            f32x16_t &a = acc[(2 * s + j) % NA];
+            a = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s][j], fa[s][j], a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s + 1][j], fa[s + 1][j], a, 0, 0, 0);
         }
+}
+// element r of a slice's sum
+template <int NA, typename ACC>
+__device__ __forceinline__ float slice_sum(const ACC (&acc)[NA], int r)
+{
+    static_assert(NA == 1 || NA == 8, "one sum or eight");
+    if constexpr (NA == 1) return acc[0][r];
+    else return ((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r])) + ((acc[4][r] + acc[5][r]) + (acc[6][r] + acc[7][r]));
+}
+template <int NA, int R, typename ACC>
+__device__ __forceinline__ void clear_sums(ACC (&acc)[NA])
+{
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[a][r] = 0.0f;
 }
 
 // Four consecutive columns of one output row, column tests where the row ends.
@@ -93,8 +117,10 @@ __device__ __forceinline__ void store_quad(const GemmEpi &ep, int row, int col, 
 
 // LNA (T = 16, M <= kLnaRows, K <= 1024, K % 32 == 0): as in gemm_bf16_slices_kernel, the A operand is LayerNorm(ep.ln_x
 // rows), made by the work-group: a panel [K / 32][16 rows][32] behind the rings, which then hold W only.
-template <int EPI, int T, int NS, bool LNA = false>
-__global__ void __launch_bounds__(f32gemm::kSlices * 64)
+// (launch bounds of two wavefronts per SIMD: the sums then live in VGPRs; as AGPRs, four of the thirty-two were copied
+// back and forth around every k tile)
+template <int EPI, int T, int NS, int NA, bool LNA = false>
+__global__ void __launch_bounds__(f32gemm::kSlices * 64, NA > 1 ? 2 : 1)
 gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
     using namespace f32gemm;
@@ -134,9 +160,8 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
     const int li = lane % T, lh = lane / T;              // operand row, k group of this lane
     const int sw = swz_of_row(li);
     typedef typename std::conditional<T == 32, f32x16_t, f32x4_t>::type acc_t;
-    acc_t acc;
-#pragma unroll
-    for (int r = 0; r < T * T / 64; ++r) acc[r] = 0.0f;
+    acc_t acc[NA];
+    clear_sums<NA, T * T / 64>(acc);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
         if (kt0 + s < kt1) issue(kt0 + s, s);
@@ -173,7 +198,10 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
 #pragma unroll
             for (int s = 0; s < NR; ++s)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[s][j], fa[s][j], acc, 0, 0, 0);
+                for (int j = 0; j < 4; ++j) {
+                    acc_t &a = acc[(4 * s + j) % NA];
+                    a = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[s][j], fa[s][j], a, 0, 0, 0);
+                }
         }
         slot = slot + 1 == NS ? 0 : slot + 1;
     }
@@ -182,7 +210,7 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
 #pragma unroll
     for (int g = 0; g < T * T / 256; ++g)
         *reinterpret_cast<float4 *>(red + li * RS + (T == 32 ? 8 * g : 0) + 4 * lh) =
-            make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+            make_float4(slice_sum(acc, 4 * g), slice_sum(acc, 4 * g + 1), slice_sum(acc, 4 * g + 2), slice_sum(acc, 4 * g + 3));
     __syncthreads();
     if (owner) {
         const float *p = f32_sm + (er - m0) * RS + ec - n0;
@@ -201,8 +229,8 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
     }
 }
 
-template <int EPI>
-__global__ void __launch_bounds__(256)
+template <int EPI, int NA>
+__global__ void __launch_bounds__(256, NA > 1 ? 2 : 1)
 gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
     using namespace f32gemm;
@@ -237,9 +265,10 @@ gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, i
     const int lr = lane & 31, lk = lane >> 5, sw = swz_of_row(lr);
     // K in the slices of gemm_f32_slices_kernel, one after the other, and their sums in the same order: the two
     // kernels give the same bits, so a row's result does not depend on how many rows the launch has.
-    f32x16_t acc, sum;
+    f32x16_t acc[NA], sum;
+    clear_sums<NA, 16>(acc);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = sum[r] = 0.0f;
+    for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
     int slice = 0, slice_end = 0;
     auto next_slice = [&](int done) {                    // the first slice that ends behind k tile `done`
         while (slice < kSlices && slice_end <= done) slice_end = kt_all * ++slice / kSlices;
@@ -264,7 +293,8 @@ gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, i
         mfma_k32(fw, fa, acc);
         if (kt + 1 == slice_end) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) { sum[r] += acc[r]; acc[r] = 0.0f; }
+            for (int r = 0; r < 16; ++r) sum[r] += slice_sum(acc, r);
+            clear_sums<NA, 16>(acc);
             next_slice(kt + 1);
         }
     }

@@ -361,7 +361,7 @@ static bool token_mix_shape_ok(const srm_model *m)
 {
     return m->wsize == 2 && !m->noproj && m->dm == m->d && (m->d == 256 || m->d == 512);
 }
-// fp32 LM heads of at most kGemvRows rows run as GEMVs.
+// fp32 calls of at most kGemvRows rows: the LM head runs as a GEMV, the other GEMMs with finer sums (see gemm_f32.hpp).
 constexpr int64_t kGemvRows = 32;
 
 // Scratch of the one-kernel path: [kMegaMaxBlocks][kMegaMaxB] floats, the same of ints, then the barrier's
@@ -665,12 +665,12 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     return fail(SRM_EINVAL, "GEMM tile code %d does not exist for this epilogue", tile);
 }
 
-template <int EPI, int T, int NS, bool LNA = false>
+template <int EPI, int T, int NS, int NA, bool LNA = false>
 static int launch_f32_slices(const float *A, const float *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
     constexpr int rings = f32gemm::kSlices * NS * (LNA ? 1 : 2) * T * f32gemm::BK * (int)sizeof(float);
     const int smem = rings + (LNA ? K * T * (int)sizeof(float) : 0);
-    auto kern = gemm_f32_slices_kernel<EPI, T, NS, LNA>;
+    auto kern = gemm_f32_slices_kernel<EPI, T, NS, NA, LNA>;
     static bool attr_set = false;
     if (!attr_set) {
         HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -688,21 +688,22 @@ static int launch_f32_slices(const float *A, const float *W, int M, int N, int K
 // 9.3; 128 x 256 x 1024: 98 | 4.4 | 8.1 | 25; 512 x 256 x 1024 (512 tiles of 16): 98 | 5.9 | 8.2 | 25; 1024 x 256 x
 // 1024 (1024 tiles of 16): 98 | 11 | 8.9 | 25; 1024 x 1024 x 256 (256 tiles of 64): 30 | 19 | 10.5 | 10.1;
 // 2048 x 256 x 1024 (128 tiles of 64): 124 | 20 | 14.9 | 25; 4096 x 4096 x 256: 134 | 293 | 134 | 99 (87 TFLOP/s of
-// the 157 the matrix cores peak at in fp32).  All tiles give the same bits (see gemm_f32.hpp).
+// the 157 the matrix cores peak at in fp32).  All tiles give the same bits for one NA
+// (see gemm_f32.hpp), which follows the rows of the call.
 // LM head: always 64 columns per tile, which its partial winners are counted in.
-template <int EPI>
+template <int EPI, int NA>
 static int launch_f32_tiles(const float *A, const float *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
     const int64_t t64 = cdiv(M, 64) * cdiv(N, 64), t32 = cdiv(M, 32) * cdiv(N, 32), t16 = cdiv(M, 16) * cdiv(N, 16);
     if constexpr (EPI != EPI_ARGMAX) {
         // one work-group per CU: a deeper ring; else two fit a CU
-        if (t16 <= 640) return launch_f32_slices<EPI, 16, 4>(A, W, M, N, K, ep, st);
+        if (t16 <= 640) return launch_f32_slices<EPI, 16, 4, NA>(A, W, M, N, K, ep, st);
         if (t64 < 200) {
-            if (t32 <= 256) return launch_f32_slices<EPI, 32, 4>(A, W, M, N, K, ep, st);
-            return launch_f32_slices<EPI, 32, 2>(A, W, M, N, K, ep, st);
+            if (t32 <= 256) return launch_f32_slices<EPI, 32, 4, NA>(A, W, M, N, K, ep, st);
+            return launch_f32_slices<EPI, 32, 2, NA>(A, W, M, N, K, ep, st);
         }
     }
-    hipLaunchKernelGGL(gemm_f32_tile_kernel<EPI>, dim3((unsigned)t64), dim3(256), 0, st, A, W, M, N, K, ep);
+    hipLaunchKernelGGL((gemm_f32_tile_kernel<EPI, NA>), dim3((unsigned)t64), dim3(256), 0, st, A, W, M, N, K, ep);
     HIP_TRY(hipGetLastError());
     return SRM_OK;
 }
@@ -737,7 +738,9 @@ static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, G
         if (EPI == EPI_ARGMAX || N >= 16384) return launch_gemv_rows<float, float, EPI, 4>(A, W, (int)M, N, K, ep, st, nparts_out);
         return launch_gemv_rows<float, float, EPI, 1>(A, W, (int)M, N, K, ep, st, nparts_out);
     } else if (f32_tiles_ok(A, W, N, K, ep)) {
-        return launch_f32_tiles<EPI>(A, W, (int)M, N, K, ep, st);
+        if constexpr (EPI != EPI_ARGMAX)
+            if (call <= kGemvRows) return launch_f32_tiles<EPI, f32gemm::kFine>(A, W, (int)M, N, K, ep, st);
+        return launch_f32_tiles<EPI, 1>(A, W, (int)M, N, K, ep, st);
     } else {
         const int64_t nb = cdiv(M, 64) * cdiv(N, 64);
         hipLaunchKernelGGL(gemm_f32_kernel<EPI>, dim3((unsigned)nb), dim3(256), 0, st, A, W, (int)M, N, K, ep);
@@ -812,7 +815,7 @@ static int linear(const void *A, const void *W, const float *bias, int64_t M, in
             ep.ln_x = ln.x; ep.ln_g = ln.g; ep.ln_b = ln.b; ep.ln_eps = ln.eps;
             const T *w = static_cast<const T *>(W);  // (in A's place: not read)
             if constexpr (sizeof(T) == 2) return launch_slices_tile<EPI, 1, 1, 4, true>(w, w, (int)M, N, K, ep, st);
-            else return launch_f32_slices<EPI, 16, 4, true>(w, w, (int)M, N, K, ep, st);
+            else return launch_f32_slices<EPI, 16, 4, f32gemm::kFine, true>(w, w, (int)M, N, K, ep, st);
         } else {
             return fail(SRM_EINVAL, "linear: LayerNorm-on-load exists for store / GELU / mixer epilogues only");
         }

@@ -124,13 +124,37 @@ def test_linear_bf16_tiles_give_the_same_bits(srm, shape):
 
 @pytest.mark.parametrize("N,K", [(832, 256), (832, 1028), (260, 36)])
 def test_linear_fp32_rows_do_not_depend_on_the_launch(srm, N, K):
-    """The fp32 matrix-core tiles (16, 32 with either ring, 64) give a row the same bits: 40, 200, 500 and 1030 rows."""
+    """The fp32 matrix-core tiles (16, 32 with either ring, 64) give a row the same bits: 40, 200, 500 and 1030 rows, and
+    1, 8 and 32, whose sums are finer."""
     rng = np.random.default_rng(N + K)
     A, W, bias = (to_dev(rng.standard_normal(s).astype(np.float32)) for s in ((1030, K), (N, K), (N,)))
     print(f"fp32 rows N={N} K={K}", flush=True)
     whole = _linear_f32_out(srm, srm.SRM_FP32, A, W, bias)
-    for M in (1, 40, 200, 500):
-        assert torch.equal(_linear_f32_out(srm, srm.SRM_FP32, A[:M].contiguous(), W, bias), whole[:M])
+    few = _linear_f32_out(srm, srm.SRM_FP32, A[:32].contiguous(), W, bias)
+    for M in (1, 8, 40, 200, 500):
+        assert torch.equal(_linear_f32_out(srm, srm.SRM_FP32, A[:M].contiguous(), W, bias), (few if M <= 32 else whole)[:M])
+
+
+@pytest.mark.parametrize("N", [256, 8192, 12000, 13000])
+def test_linear_fp32_few_rows_are_summed_finely(srm, N):
+    """At most 32 rows, whichever tile takes them (16, 32 with either ring, 64 columns): the result is no further from
+    64-bit sums than sixteen fp32 partial sums of K / 16 products, added in pairs, are (their error over the same operands
+    varies by a few percent with the order of k: a tenth is added)."""
+    M, K = 32, 1024
+    rng = np.random.default_rng(N)
+    A, W = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K)))
+    print(f"fp32 fine sums N={N}", flush=True)
+    got = _linear_f32_out(srm, srm.SRM_FP32, to_dev(A), to_dev(W), to_dev(np.zeros(N, np.float32))).cpu().numpy()
+    ref = A.astype(np.float64) @ W.astype(np.float64).T
+    cols = rng.permutation(N)[:256]
+    prod = A[:, None, :].astype(np.float64) * W[None, cols].astype(np.float64)
+    part = np.zeros((M, cols.size, 16), np.float32)
+    for k in range(0, K, 16):                       # one rounding per product, as a fused multiply-add
+        part = (part + prod[..., k:k + 16]).astype(np.float32)
+    while part.shape[-1] > 1:
+        part = part[..., ::2] + part[..., 1::2]
+    lanes = np.sqrt(np.mean((part[..., 0] - ref[:, cols]) ** 2))
+    assert np.sqrt(np.mean((got - ref) ** 2)) <= 1.1 * lanes
 
 
 @pytest.mark.parametrize("shape", [(1, 5, 3), (8, 256, 256), (70, 130, 37), (128, 64, 100), (5, 130, 64), (17, 70, 128),
