@@ -40,9 +40,14 @@
  *     of the same arithmetic and exist for tests and measurements):
  *     SRM_FUSE_MIXER=0   the recurrent state update as a kernel of its own instead
  *                        of inside the in-projection's epilogue (same bits);
- *     SRM_LN_ON_LOAD=0   bf16 models, at most 8 samples: LayerNorm launches
- *                        between the GEMMs instead of LayerNorm made by the
- *                        consuming GEMM (same bits);
+ *     SRM_LN_ON_LOAD=0   steps of at most 16 samples (8 where token mixing can
+ *                        be one kernel): LayerNorm launches between the GEMMs
+ *                        instead of LayerNorm made by the consuming GEMM (same
+ *                        bits);
+ *     SRM_TOKEN_MIX=0    bf16 models of d_model 256 or 512, steps of 9 to about
+ *                        1000 samples: the token mixing of a layer as separate
+ *                        kernels instead of one (sums in another order); =1 as
+ *                        one kernel up to 2048 samples;
  *     SRM_MEGAKERNEL, SRM_MEGA_BLOCKS   see srm_generate_one_kernel_blocks.
  */
 #ifndef SRM_H

@@ -3,7 +3,7 @@
 // The residual stream is fp32; the normalised row is written in the type the
 // next GEMM consumes (bf16 or fp32).  Statistics are two-pass (mean, then the
 // biased variance of the centred values) over values held in registers, summed
-// with wavefront shuffles.
+// by DPP within rows of 16 lanes and by scalar reads across them (wave_sum).
 #pragma once
 #include "common.hpp"
 #include <type_traits>

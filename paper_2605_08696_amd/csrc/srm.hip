@@ -792,7 +792,7 @@ struct MixArgs {           // EPI_MIX: state slab of the layer and its coefficie
     int n_ctx = 0, hrow = 0, dh = 0, state_half = 0;
 };
 
-struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (bf16, a handful of rows)
+struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (at most kLnaRows rows)
     const float *x = nullptr, *g = nullptr, *b = nullptr;
     float eps = 0.0f;
 };
@@ -1285,9 +1285,11 @@ static int mega_blocks(const srm_model *m, int64_t B)
     if (!m->mega_layers || m->shalf || B > kMegaMaxB || m->L > kMegaMaxLayers) return 0;
     const int widest = std::max(std::max(m->d, m->dm), m->ff);
     if (m->d > 1024 || m->d % 4 || m->dm % 4 || m->ff % 4 || (size_t)mega_rows(B) * widest * 4 > 128 * 1024) return 0;
-    // The small grid has a fraction of the chip's arithmetic and cache bandwidth: measured against the step
-    // kernels, the path wins while rows x matrix elements stay below about 16 M (C1's model: 93 against 132 us
-    // per step at B = 1, 112 against 132 at B = 4, 130 against 126 at B = 8; a 25 M-element model loses at B = 1).
+    // The small grid has a fraction of the chip's arithmetic and cache bandwidth, so the path is for few rows of small
+    // models: rows x matrix elements up to 16 M.  That limit was measured against step kernels of 132 us per step of C1's
+    // model.  Against the present ones (us per step, one kernel | step kernels): C1's model 91 | 83 at B = 1, 100 | 83 at
+    // 2, 112 | 84 at 4, 131 | 85 at 8; 128 wide, 2 layers, 1024 tokens 44 | 46, 47 | 47, 52 | 47, 58 | 48; 64 wide, 2
+    // layers, 256 tokens 42 | 43, 44 | 43, 47 | 44, 53 | 44.
     const char *sw = getenv("SRM_MEGAKERNEL");
     if (sw && sw[0] == '0') return 0;
     const double elems = (double)m->L * ((double)2 * m->d * m->dm + (double)2 * m->d * m->ff) + (double)m->V * m->d;
@@ -1481,10 +1483,12 @@ static int scan_chunk_len(const srm_model *m, int64_t nseq, int P)
 }
 
 // Where the chunked scan would run, mixer_parallel_kernel (one launch, every block reads the positions in front of it
-// itself) is faster until those reads count: their bytes grow with sequences x channels x P^2.  Measured (us per layer,
-// chunked - block form, d = 1024): 1 x 509 positions +4.4, 8 x 320 +4.8, 64 x 128 (2^30) +4.3, 32 x 200 (1.2 x 2^30)
-// +0.9, 8 x 509 (2 x 2^30) +0.7, 64 x 200 -3.5, 32 x 509 -18; d = 512: 32 x 320 +5.3, 64 x 200 (1.2 x 2^30) +0.8, 120 x
-// 200 -4.  A property of the whole call, like the chunk length.
+// itself) is faster until those reads count: their bytes grow with sequences x channels x P^2.  Measured (chunked - block
+// form, us per layer; in brackets the product in units of 2^30), d = 1024: 1 x 509 positions (0.25) +4.4, 8 x 320 (0.8)
+// +4.8, 64 x 128 (1) +4.3, 32 x 200 (1.2) +0.9, 8 x 509 (2) +0.7, 64 x 200 (2.4) -3.5, 32 x 509 (8) -18; d = 512: 32 x 320
+// (1.6) +5.3, 64 x 200 (1.2) +0.8, 120 x 200 (2.3) -4.  The limit keeps to the side where every call measured gains
+// clearly; the calls between it and the crossover at about 2 take the chunked scan.  A property of the whole call, like
+// the chunk length.
 static bool scan_in_blocks(const srm_model *m, int chunk, int64_t nseq, int P)
 {
     return chunk > 0 && P < 8192 && nseq * m->dm * (int64_t)P * P <= (1 << 30);
