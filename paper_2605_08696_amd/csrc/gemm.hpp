@@ -893,8 +893,9 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, int M,
 
 // ------------------------------------------------------------------ few rows: streaming GEMV
 // out = epilogue(A W^T + bias) for at most a few dozen rows of fp32 operands: the LM head, whose partial winners
-// are counted per 64 columns, and operands that the matrix-core kernels do not take (which are faster for all other
-// shapes: 8 x 1024 x 256: 4.9 us here, 3.7 there; 32 x 512 x 2048: 37 and 7.1).  The
+// are counted per 64 columns, at most MB rows over a matrix of 24 000 columns and more (see launch_f32), and operands that
+// the matrix-core kernels do not take (which are faster for the other shapes: 8 x 1024 x 256: 4.9 us here, 3.1 there; 32 x
+// 512 x 2048: 37 and 7.1).  The
 // product is bound by streaming W once, so the grid is made of
 // many small column slices (16 * CPG columns per block) and the loads are coalesced: 16 lanes
 // share CPG columns (4 such groups per wavefront), lane l16 reading every 16th 16-byte vector of

@@ -229,8 +229,8 @@ gemm_f32_slices_kernel(const float *__restrict__ A, const float *__restrict__ W,
     }
 }
 
-template <int EPI, int NA>
-__global__ void __launch_bounds__(256, NA > 1 ? 2 : 1)
+template <int EPI>
+__global__ void __launch_bounds__(256)
 gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
     using namespace f32gemm;
@@ -263,10 +263,10 @@ gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, i
     };
     const int wm = wave >> 1, wn = wave & 1;
     const int lr = lane & 31, lk = lane >> 5, sw = swz_of_row(lr);
-    // K in the slices of gemm_f32_slices_kernel, one after the other, and their sums in the same order: the two
+    // K in the slices of gemm_f32_slices_kernel (with one sum each), one after the other, added in the same order: the two
     // kernels give the same bits, so a row's result does not depend on how many rows the launch has.
-    f32x16_t acc[NA], sum;
-    clear_sums<NA, 16>(acc);
+    f32x16_t acc[1], sum;
+    clear_sums<1, 16>(acc);
 #pragma unroll
     for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
     int slice = 0, slice_end = 0;
@@ -294,7 +294,7 @@ gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, i
         if (kt + 1 == slice_end) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) sum[r] += slice_sum(acc, r);
-            clear_sums<NA, 16>(acc);
+            clear_sums<1, 16>(acc);
             next_slice(kt + 1);
         }
     }

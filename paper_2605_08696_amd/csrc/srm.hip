@@ -688,23 +688,28 @@ static int launch_f32_slices(const float *A, const float *W, int M, int N, int K
 // 9.3; 128 x 256 x 1024: 98 | 4.4 | 8.1 | 25; 512 x 256 x 1024 (512 tiles of 16): 98 | 5.9 | 8.2 | 25; 1024 x 256 x
 // 1024 (1024 tiles of 16): 98 | 11 | 8.9 | 25; 1024 x 1024 x 256 (256 tiles of 64): 30 | 19 | 10.5 | 10.1;
 // 2048 x 256 x 1024 (128 tiles of 64): 124 | 20 | 14.9 | 25; 4096 x 4096 x 256: 134 | 293 | 134 | 99 (87 TFLOP/s of
-// the 157 the matrix cores peak at in fp32).  All tiles give the same bits for one NA
+// the 157 the matrix cores peak at in fp32).  With eight sums per slice, i.e. at most 32 rows, the 32-wide tile also where
+// the 64-wide one would be taken, half of whose rows or more do not exist (64 with one sum | 32 with eight: 16 x 16384 x
+// 256: 9.3 | 6.7, 16 x 32000 x 256: 14.8 | 11.8, 32 x 32000 x 1024: 42.2 | 30.3).  All tiles give the same bits for one NA
 // (see gemm_f32.hpp), which follows the rows of the call.
 // LM head: always 64 columns per tile, which its partial winners are counted in.
 template <int EPI, int NA>
 static int launch_f32_tiles(const float *A, const float *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
+    static_assert(NA == 1 || EPI != EPI_ARGMAX, "the LM head of so few rows is a GEMV");
     const int64_t t64 = cdiv(M, 64) * cdiv(N, 64), t32 = cdiv(M, 32) * cdiv(N, 32), t16 = cdiv(M, 16) * cdiv(N, 16);
     if constexpr (EPI != EPI_ARGMAX) {
         // one work-group per CU: a deeper ring; else two fit a CU
         if (t16 <= 640) return launch_f32_slices<EPI, 16, 4, NA>(A, W, M, N, K, ep, st);
-        if (t64 < 200) {
+        if (NA > 1 || t64 < 200) {
             if (t32 <= 256) return launch_f32_slices<EPI, 32, 4, NA>(A, W, M, N, K, ep, st);
             return launch_f32_slices<EPI, 32, 2, NA>(A, W, M, N, K, ep, st);
         }
     }
-    hipLaunchKernelGGL((gemm_f32_tile_kernel<EPI, NA>), dim3((unsigned)t64), dim3(256), 0, st, A, W, M, N, K, ep);
-    HIP_TRY(hipGetLastError());
+    if constexpr (NA == 1) {
+        hipLaunchKernelGGL(gemm_f32_tile_kernel<EPI>, dim3((unsigned)t64), dim3(256), 0, st, A, W, M, N, K, ep);
+        HIP_TRY(hipGetLastError());
+    }
     return SRM_OK;
 }
 // Whole 16-byte vectors along K, and of the outputs' rows where the tiles store them as vectors (N % 4 == 0; elements
@@ -724,14 +729,12 @@ static int launch_f32(const float *A, const float *W, int64_t M, int N, int K, G
     ep.nparts = (int)cdiv(N, 64);
     if (nparts_out) *nparts_out = ep.nparts;
     // The streaming GEMV: the LM head of few rows, operands the tiles do not take, and at most one of its passes
-    // (kGemvMB rows) over a weight matrix so wide that launch_f32_tiles would take the 64x64 tile, most of whose rows are
-    // padding then: bound by reading W (us, tile | GEMV: 8 x 32000 x 1024: 45.6 | 31, 1 x 24000 x 1024: 41 | 24.4, 8 x
-    // 32000 x 256: 15.3 | 10.9, 4 x 16384 x 256: 9.2 | 7.8, 8 x 12800 x 1024: 25.5 | 23.0; with fewer columns or more rows
-    // the tiles win: 8 x 14000 x 256: 9.2 | 10.8, 4 x
-    // 16384 x 64: 4.9 | 5.2, 9 x 16384 x 256: 9.3 | 11.3; rows x columns x K).  By the rows of the
-    // call: the GEMV sums in an order of its own, see slices_ok.
+    // (kGemvMB rows) over the widest matrices, where both are bound by reading W and it has less to do beside (us, 32-wide
+    // slices | GEMV: 4 x 50000 x 256: 17.2 | 16.6, 4 x 32000 x 256: 11.6 | 10.7, x 64: 6.6 | 6.1; 4 x 24000 x 256: 9.6 |
+    // 9.7; 4 x 16384 x 256: 6.6 | 7.7, 4 x 13000 x 1024: 15.4 | 22.1; rows x columns x K).  By the rows of the call: the
+    // GEMV sums in an order of its own, see slices_ok.
     const int64_t call = std::max(M, call_rows);
-    const bool wide = call <= kGemvMB && cdiv(N, 64) >= 200 && (N >= (K >= 256 ? 16384 : 20000) || K >= 1024);
+    const bool wide = call <= kGemvMB && N >= 24000;
     if (gemv_rows_ok<float>(call, K) && (EPI == EPI_ARGMAX || wide || !f32_tiles_ok(A, W, N, K, ep))) {
         // (64 columns per block where the partial winners of the LM head are counted per 64 columns, or where 16 would
         // make too many blocks)

@@ -175,10 +175,11 @@ def test_linear_fp32_matrix_cores(srm, shape, epi):
     _linear_case(srm, srm.SRM_FP32, M, N, K, epi, None, seed=M * 3 + epi)
 
 
-@pytest.mark.parametrize("shape", [(8, 16384, 256), (9, 16384, 256), (1, 20001, 64), (8, 12800, 1024), (8, 12796, 1024)])
+@pytest.mark.parametrize("shape", [(8, 24000, 256), (9, 24000, 256), (8, 23996, 256), (1, 24001, 64), (32, 12800, 1024), (17, 16384, 68)])
 @pytest.mark.parametrize("epi", [0, 2, 4])
 def test_linear_fp32_few_rows_of_a_wide_matrix(srm, shape, epi):
-    """Both sides of the rule that sends at most eight rows over a wide weight matrix to the streaming GEMV."""
+    """Both sides of the rule that sends at most eight rows over a wide weight matrix to the streaming GEMV, and the
+    32-wide tile over matrices beside it."""
     M, N, K = shape
     _linear_case(srm, srm.SRM_FP32, M, N, K, epi, None, seed=M + N + epi)
 

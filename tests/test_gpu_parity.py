@@ -643,4 +643,4 @@ def test_parallel_form_does_not_depend_on_its_passes(srm, vocab):
 @pytest.mark.parametrize("B,T", [(2, 4), (3, 3)])
 def test_parallel_form_of_few_rows_over_a_wide_head(srm, B, T):
     """Eight rows of a call take the GEMV for such logits in every pass, nine rows the tiles in every pass."""
-    _parallel_in_passes(srm, 20004, B, T, 64, (1,))
+    _parallel_in_passes(srm, 24004, B, T, 64, (1,))
