@@ -587,11 +587,15 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 // 12.2 | 16.0; 1800 x 514 x 4096, 261 tiles: 20.1 | 22.7; 297: 26.0 | 21.8), and, unless the epilogue is a plain store, for
 // short k loops beyond (residual: 2100 x 1022 x 512: 14.8 | 20.4, x 1024: 19.0 | 22.4, x 4096: 41.9 | 38.0; store, x 512:
 // 11.5 | 10.7).
-static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store)
+// slow_update: a state update in the epilogue with a short k loop in front of it or a state in 16 bits, whose rows the
+// 64x64 tile takes with twice the wavefronts: 2300 x 512 x 512: 9.6 | 11.0, state in 16 bits 10.6 | 13.4, 2049 x 1024 x
+// 1024 so: 15.3 | 19.3; with K = 1024 and a state in 32 bits: 15.6 | 15.0.  (Larger launches than one round of 128x64 take
+// the 96x128 tile all the same: 2300 x 1024 x 1024, 16 bits: 23.0 | 20.2.)
+static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store, bool slow_update)
 {
     if (K < 512) return -1;                          // (rings of four k tiles)
     if (N % 4 && choose_tile(M, N, K, 64) == 2 && (cdiv(M, 64) * cdiv(N, 64) <= 288 || (!plain_store && K < 4096))) return -1;
-    if (cdiv(M, 128) * cdiv(N, 64) <= 256) return 18;
+    if (cdiv(M, 128) * cdiv(N, 64) <= 256) return slow_update ? -1 : 18;
     if (cdiv(M, 96) * cdiv(N, 128) <= 256) return 17;
     const int64_t t192 = cdiv(M, 192) * cdiv(N, 256), t256 = cdiv(M, 256) * cdiv(N, 256);
     if (t192 >= 188 && t192 <= 256 && cdiv(M, 128) * cdiv(N, 128) > 512) return 16;
@@ -617,7 +621,8 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
         if (g_force_tile < 0 && slices_ok(std::max(M, call_rows), N, K)) return launch_slices<EPI>(A, W, m, N, K, ep, st);
     int tile = g_force_tile;
     if constexpr (EPI != EPI_ARGMAX)
-        if (tile < 0) tile = choose_one_round_tile(M, N, K, EPI == EPI_STORE || EPI == EPI_F32);
+        if (tile < 0) tile = choose_one_round_tile(M, N, K, EPI == EPI_STORE || EPI == EPI_F32,
+                                                   EPI == EPI_MIX && (K < 1024 || ep.state_half));
     if (tile < 0) tile = choose_tile(M, N, K, min_bn);
     ep.nparts = (int)cdiv(N, tile_bn(tile));
     if (nparts_out) *nparts_out = ep.nparts;
