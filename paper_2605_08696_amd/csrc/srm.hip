@@ -581,7 +581,9 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 // 15.4 | 13.6, 700 x 4096 x 1024: 14.1 | 12.4 (296: 16.3 | 21.6).  192x256 from 188 to 256: 2500 x 4096 x 1024: 33.4 |
 // 28.1, 9000 x 1024 x 4096: 103 | 79 (176: 23.7 | 26.2; 304: 34.9 | 49.4; not while the 128x128 tiles fit two per CU,
 // where its rows are padding: 1000 x 8192 x 2048: 40.1 | 45.3, 200 x 32000 x 1024: 28.1 | 31.0), and two or three rounds of
-// it that are full where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8.  Every tile gives the same bits.
+// it that are full where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8 (with K = 512 not with
+// vectors of fp32 to store: residual 9000 x 4096: 68.1 | 71.4, fp32 rows of odd width 88.9 | 93.5; GELU 57.1 | 54.9).  Every
+// tile gives the same bits.
 // Rows of odd width (N % 4) are stored by element, which the small tiles spread over more wavefronts: where choose_tile
 // takes the 64x64 tile, that stays up to about one tile per CU (300 x 1022 x 1024: 9.0 | 9.7, with the residual epilogue
 // 12.2 | 16.0; 1800 x 514 x 4096, 261 tiles: 20.1 | 22.7; 297: 26.0 | 21.8), and, unless the epilogue is a plain store, for
@@ -591,7 +593,7 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 // 64x64 tile takes with twice the wavefronts: 2300 x 512 x 512: 9.6 | 11.0, state in 16 bits 10.6 | 13.4, 2049 x 1024 x
 // 1024 so: 15.3 | 19.3; with K = 1024 and a state in 32 bits: 15.6 | 15.0.  (Larger launches than one round of 128x64 take
 // the 96x128 tile all the same: 2300 x 1024 x 1024, 16 bits: 23.0 | 20.2.)
-static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store, bool slow_update)
+static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store, bool slow_update, bool fp32_store)
 {
     if (K < 512) return -1;                          // (rings of four k tiles)
     if (N % 4 && choose_tile(M, N, K, 64) == 2 && (cdiv(M, 64) * cdiv(N, 64) <= 288 || (!plain_store && K < 4096))) return -1;
@@ -600,7 +602,7 @@ static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store, bool
     const int64_t t192 = cdiv(M, 192) * cdiv(N, 256), t256 = cdiv(M, 256) * cdiv(N, 256);
     if (t192 >= 188 && t192 <= 256 && cdiv(M, 128) * cdiv(N, 128) > 512) return 16;
     const int64_t r192 = cdiv(t192, 256) * 256, r256 = cdiv(t256, 256) * 256;
-    if (t192 > 256 && t192 <= 768 && t192 * 20 >= r192 * 19 && t256 * 5 < r256 * 4) return 16;
+    if ((K >= 1024 || !fp32_store) && t192 > 256 && t192 <= 768 && t192 * 20 >= r192 * 19 && t256 * 5 < r256 * 4) return 16;
     return -1;
 }
 static int tile_bn(int tile) { return tile == 0 || tile >= 9 ? 256 : (tile == 2 || tile >= 6) ? 64 : 128; }
@@ -622,7 +624,8 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     int tile = g_force_tile;
     if constexpr (EPI != EPI_ARGMAX)
         if (tile < 0) tile = choose_one_round_tile(M, N, K, EPI == EPI_STORE || EPI == EPI_F32,
-                                                   EPI == EPI_MIX && (K < 1024 || ep.state_half));
+                                                   EPI == EPI_MIX && (K < 1024 || ep.state_half),
+                                                   EPI == EPI_F32 || (EPI == EPI_RESID && N % 4 == 0));
     if (tile < 0) tile = choose_tile(M, N, K, min_bn);
     ep.nparts = (int)cdiv(N, tile_bn(tile));
     if (nparts_out) *nparts_out = ep.nparts;
