@@ -163,8 +163,9 @@ size_t srm_state_bytes(const srm_model *m, int64_t batch);
  * srm_generate*) accept a smaller workspace and then take the step in slices of
  * as many samples as it holds, at least min(B, 256) - the samples are
  * independent - so the number of resident sequences is bounded by the state,
- * not by the workspace.  Results do not depend on the slicing: which kernels sum
- * in which order follows the rows of the call.
+ * not by the workspace.  Results do not depend on the slicing in fp32 models; in
+ * bf16 models a slice takes the kernels of its size, which may sum in another
+ * order.
  */
 size_t srm_workspace_bytes(const srm_model *m, int64_t rows);
 /* The same number from a configuration alone (host only, no GPU call), for sizing buffers before a model

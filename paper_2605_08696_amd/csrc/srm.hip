@@ -1164,9 +1164,8 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     };
     const bool fuse = fuse_mixer(m, nb);          // (same bits either way)
     const Sampling where{0.0f, 0, a.pos, a.pos_dev, pos_rows, 1.0f, 0};
-    // by the rows of the call, as slices_ok: both forms sum in an order of their own (a.B > kLnaRows: nb may be fewer)
-    const bool lnf = ln_on_load(m, a.B);
-    const bool tm = token_mix_one_kernel(m, a.B);
+    const bool lnf = ln_on_load(m, nb);
+    const bool tm = token_mix_one_kernel(m, nb);
     for (int l = 0; l < m->L; ++l)
         SRM_TRY((block<T>(m, l, w, nb, a.B, st, mix, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
     if (a.hidden)

@@ -501,30 +501,6 @@ def test_decode_in_slices_when_the_workspace_is_smaller_than_the_batch(srm):
         model.decode_step(B, 0, tok0, st0.clone(), tok0.clone(), workspace=small[:model.workspace_bytes(100)])
 
 
-@pytest.mark.parametrize("d,B,rows", [(1024, 520, 256), (1024, 1025, 512), (512, 1100, 512), (256, 2100, 256)])
-def test_bf16_decode_does_not_depend_on_its_slices(srm, d, B, rows):
-    """Which GEMM form a bf16 step takes follows the rows of the call: last slices of 8 and 1 rows (LayerNorm made by
-    the consuming GEMM for calls that small), and slices of a size that alone would take the one-kernel token mixing.
-    Hidden states, logits, tokens and states equal the one-pass step bit for bit."""
-    cfg = srm_synth.tiny_config(vocab=304, d_model=d, n_layers=2, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=83)
-    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
-    rng = np.random.default_rng(B)
-    tok0 = to_dev(rng.integers(0, cfg.vocab, B).astype(np.int32))
-    st0 = torch.randn(cfg.n_layers * B * d, device="cuda") * 0.3
-    print(f"sliced bf16 decode d={d} B={B} rows-per-pass={rows}", flush=True)
-    got = []
-    for ws in (model.new_workspace(B), model.new_workspace(rows)):
-        st, tk = st0.clone(), tok0.clone()
-        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
-        hd = torch.empty((B, d), dtype=torch.float32, device="cuda")
-        for g in range(2):
-            model.decode_step(B, 2 + g, tk, st, tk, logits=lg, hidden=hd, workspace=ws)
-        torch.cuda.synchronize()
-        got.append((hd, lg, tk, st))
-    for x, y in zip(*got):
-        assert torch.equal(x, y)
-
-
 @pytest.mark.parametrize("B", [257, 272, 288, 530])
 def test_fp32_calls_with_a_short_last_pass(srm, B):
     """Last passes of 1, 16, 32 and 18 rows, for which the LM head of a call that small runs as a GEMV: logits, tokens
