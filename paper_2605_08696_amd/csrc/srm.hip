@@ -513,7 +513,8 @@ static int launch_slices_tile(const bf16 *A, const bf16 *W, int M, int N, int K,
 // 128x128 tile | slices): 256 x 4096 x 1024, 256 tiles: 8.4 | 6.9; 1024 x 1024 x 1024, 256: 8.5 | 7.0; 1024 x 1024 x
 // 4096, 256: 19.1 | 15.8; 1900 x 512 x 2048, 240: 12.2 | 9.7; 300 x 4096 x 1024, 320 tiles: 9.4 | 11.4; 3000 x 512 x
 // 512, 376: 7.5 | 9.7 (rows x columns x K).  M is the row count of the whole call: its sums run in another order than
-// those of the other tiles, and a call that the workspace cuts into passes should not change with the cut.
+// those of the other tiles, and a prefill or sequence-form call that the workspace cuts into passes does not change with
+// the cut (nor does an fp32 step; a bf16 step does, see decode_rows).
 // With fewer than five k tiles half of the wavefronts have no slice; there the form ends with its 64x32 tile (2500 x 256 x
 // 64: 3.5 | 4.3, x 256: 4.2 | 4.7, 1024 x 1024 x 128: 3.9 | 4.6; with five k tiles it is the faster one again).
 static bool slices_ok(int64_t M, int N, int K)
@@ -1164,10 +1165,14 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     };
     const bool fuse = fuse_mixer(m, nb);          // (same bits either way)
     const Sampling where{0.0f, 0, a.pos, a.pos_dev, pos_rows, 1.0f, 0};
-    const bool lnf = ln_on_load(m, nb);
-    const bool tm = token_mix_one_kernel(m, nb);
+    // A slice of a bf16 step takes the kernels of its own rows; fp32 results do not depend on the slicing, so whatever sums
+    // in an order of its own follows the call there.  (4096 rows through a 512-row workspace, d = 1024: 6272 us by the
+    // slice's rows, 9478 with the slice form of the GEMMs by the call's.)
+    const int64_t call_rows = sizeof(T) == 4 ? a.B : nb;
+    const bool lnf = ln_on_load(m, call_rows);
+    const bool tm = token_mix_one_kernel(m, call_rows);
     for (int l = 0; l < m->L; ++l)
-        SRM_TRY((block<T>(m, l, w, nb, a.B, st, mix, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
+        SRM_TRY((block<T>(m, l, w, nb, call_rows, st, mix, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
     if (a.hidden)
         HIP_TRY(hipMemcpyAsync(a.hidden + (size_t)b0 * d, w.x, (size_t)nb * d * 4, hipMemcpyDeviceToDevice, st));
     const Sampling sm{a.temperature, a.seed, a.pos, a.pos_dev, pos_rows, a.top_p, (uint32_t)b0, a.eos_plus1};
@@ -1181,7 +1186,7 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     }
     if (topp) rg.zero_counter = w.slow;
     float *lg = a.logits ? a.logits + (size_t)b0 * m->V : nullptr;
-    SRM_TRY((head_argmax<T>(m, w, w.a, nb, a.B, lg, a.tok_out, b0, 1, st, a.ts, sm, rg)));
+    SRM_TRY((head_argmax<T>(m, w, w.a, nb, call_rows, lg, a.tok_out, b0, 1, st, a.ts, sm, rg)));
     if (topp)
         SRM_TRY(nucleus(lg, nb, m->V, sm, a.tok_out + b0, a.ts.store ? a.ts.store + b0 : nullptr, a.ts.step_dev,
                         a.ts.stride, (pos_rows && a.advance) ? pos_rows : nullptr, w.slow, st));
