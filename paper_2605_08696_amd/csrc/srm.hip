@@ -585,6 +585,8 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 // it that are full where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8 (with K = 512 not with
 // vectors of fp32 to store: residual 9000 x 4096: 68.1 | 71.4, fp32 rows of odd width 88.9 | 93.5; GELU 57.1 | 54.9).  Every
 // tile gives the same bits.
+// At most one 64x64 tile per CU (one pass of a larger call; calls that small take the slice form): that tile on its deep
+// ring (us, 64x64 | 128x64: 200 x 1024 x 1024: 7.5 | 8.4, 1000 x 512 x 2048: 11.7 | 13.3, 512 x 1024 x 4096: 18.8 | 20.2).
 // Rows of odd width (N % 4) are stored by element, which the small tiles spread over more wavefronts: where choose_tile
 // takes the 64x64 tile, that stays up to about one tile per CU (300 x 1022 x 1024: 9.0 | 9.7, with the residual epilogue
 // 12.2 | 16.0; 1800 x 514 x 4096, 261 tiles: 20.1 | 22.7; 297: 26.0 | 21.8), and, unless the epilogue is a plain store, for
@@ -597,7 +599,8 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store, bool slow_update, bool fp32_store)
 {
     if (K < 512) return -1;                          // (rings of four k tiles)
-    if (N % 4 && choose_tile(M, N, K, 64) == 2 && (cdiv(M, 64) * cdiv(N, 64) <= 288 || (!plain_store && K < 4096))) return -1;
+    const int64_t t64 = cdiv(M, 64) * cdiv(N, 64);
+    if (choose_tile(M, N, K, 64) == 2 && (t64 <= 256 || (N % 4 && (t64 <= 288 || (!plain_store && K < 4096))))) return -1;
     if (cdiv(M, 128) * cdiv(N, 64) <= 256) return slow_update ? -1 : 18;
     if (cdiv(M, 96) * cdiv(N, 128) <= 256) return 17;
     const int64_t t192 = cdiv(M, 192) * cdiv(N, 256), t256 = cdiv(M, 256) * cdiv(N, 256);
