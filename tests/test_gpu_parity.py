@@ -593,11 +593,11 @@ def test_parallel_form_at_the_edges_of_its_blocks(srm, orc_mod, T):
     assert np.abs(hid.cpu().numpy() - ref["hidden"]).max() <= 1e-4 * np.abs(ref["hidden"]).max()
 
 
-def _parallel_in_passes(srm, vocab, B, T, d, per_pass):
-    cfg = srm_synth.tiny_config(vocab=vocab, d_model=d, n_layers=1, n_heads=4, n_ctx=16, seed=85)
+def _parallel_in_passes(srm, vocab, B, T, d, per_pass, dtype="fp32"):
+    cfg = srm_synth.tiny_config(vocab=vocab, d_model=d, n_layers=1, n_heads=4, n_ctx=16, weight_dtype=dtype, seed=85)
     model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
     toks = to_dev(srm_synth.make_prompts(cfg, batch=B, length=T, seed=vocab))
-    print(f"parallel form in passes vocab={vocab} B={B} T={T}", flush=True)
+    print(f"parallel form in passes {dtype} vocab={vocab} B={B} T={T} d={d}", flush=True)
     got = []
     for seqs in (B, *per_pass):
         hid = torch.empty((B, T, cfg.d_model), dtype=torch.float32, device="cuda")
@@ -614,6 +614,13 @@ def test_parallel_form_does_not_depend_on_its_passes(srm, vocab):
     """Logits rows of a vocabulary that is no multiple of four start at every alignment: each pass of the call takes the
     same GEMM kernel, so hidden states and logits equal the one-pass call bit for bit."""
     _parallel_in_passes(srm, vocab, 14, 7, 64, (1, 3))
+
+
+@pytest.mark.parametrize("vocab,B,T,d", [(301, 14, 7, 64), (1000, 14, 7, 512), (1000, 200, 13, 512)])
+def test_bf16_parallel_form_does_not_depend_on_its_passes(srm, vocab, B, T, d):
+    """The same for bf16 models, whose slice GEMMs follow the rows of the call: a call that takes them, and one of too
+    many rows, of which a pass alone would take them."""
+    _parallel_in_passes(srm, vocab, B, T, d, (1, B // 5), "bf16")
 
 
 @pytest.mark.parametrize("B,T", [(2, 4), (3, 3)])
