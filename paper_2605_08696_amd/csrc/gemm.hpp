@@ -3,9 +3,9 @@
 // MLP and the LM head.
 //
 //   gemm_bf16_kernel: bf16 operands on the gfx950 matrix cores
-//     (v_mfma_f32_32x32x16_bf16, fp32 accumulate); tiles go global -> LDS with
+//     (v_mfma_f32_16x16x32_bf16, fp32 accumulate); tiles go global -> LDS with
 //     buffer_load ... lds into a 16-byte XOR-swizzled layout, two LDS stages,
-//     operands read from LDS two k-substeps ahead of the MFMAs that use them.
+//     operands read from LDS half a k tile ahead of the MFMAs that use them.
 //   gemm_f32_kernel: plain fp32 FMA tiles of fp32 operands of any size and alignment
 //     (gemm_f32.hpp holds the matrix-core kernels that the fp32 models run).
 //
@@ -131,18 +131,20 @@ __device__ __forceinline__ void epi_store(const GemmEpi &ep, int64_t row, int co
 
 // ------------------------------------------------------------------ bf16 MFMA
 // Block tile BM x BN x 64 split over WM x WN waves, each wave holding a
-// (BM/WM) x (BN/WN) accumulator tile of 32x32x16 MFMAs.  Built to keep the matrix
-// pipe fed:
-//  (1) the MFMA operands of k-substep kk+1 are read from LDS before the MFMAs of
-//      kk issue (two register sets, order pinned with scheduling barriers);
+// (BM/WM) x (BN/WN) accumulator tile of 16x16x32 MFMAs.  (The chip's power sets the
+// clock of these loops, and 16x16x32 products need less of it than 32x32x16 ones:
+// bare products on random operands run at 2.15 PFLOP/s and 2.1 GHz against 1.91 and
+// 1.87.)  Built to keep the matrix pipe fed:
+//  (1) the MFMA operands of one half of a k tile are read from LDS behind the MFMAs of
+//      the other half (two register sets, order pinned with scheduling barriers);
 //  (2) tiles travel global -> LDS directly (buffer_load ... lds), two tiles ahead
-//      of the MFMAs, and the barrier sits one substep before the end of a tile
+//      of the MFMAs, and the barrier sits in the middle of a tile
 //      (see the pipeline table in the kernel); writing the tiles with ds_write
 //      from registers instead cost ~30% of the main loop;
 //  (3) the product is formed transposed (W fragment as the first MFMA operand),
 //      so a lane holds four consecutive output columns of ONE row per register
-//      quad: the LM-head argmax reduces in-lane and needs a single cross-lane
-//      exchange, and the epilogue passes 32-row slices through a wave-private
+//      quad: the LM-head argmax reduces in-lane and needs two cross-lane
+//      exchanges, and the epilogue passes 32-row slices through a wave-private
 //      LDS stage with 16-byte writes and reads, so that global stores and the
 //      residual read-modify-write are 16-byte vectors over whole cache lines.
 // LDS chunk swizzle: 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7);
@@ -282,6 +284,29 @@ __device__ __forceinline__ EpiQuad epi_quad_request(const GemmEpi &ep, int64_t r
     }
     return q;
 }
+// The state update of a quad: active: the row's position lies inside the context; else the state stays and zeros go out.
+template <typename TAct>
+__device__ __forceinline__ void epi_mix_store(const GemmEpi &ep, int64_t row, int col, const EpiQuad &q, bool active, bool row_repeat,
+                                              float4 v)
+{
+    const int64_t at = row * ep.ldo + col;
+    TAct *o = reinterpret_cast<TAct *>(ep.out) + at;
+    if (!active) { store4(o, make_float4(0.f, 0.f, 0.f, 0.f)); return; }
+    const float p = row_repeat ? q.al : 1.0f, c = row_repeat ? 1.0f : q.al;
+    float4 n;
+    n.x = fmaf(q.la, q.old.x, p * (float)(TAct)v.x);
+    n.y = fmaf(q.la, q.old.y, p * (float)(TAct)v.y);
+    n.z = fmaf(q.la, q.old.z, p * (float)(TAct)v.z);
+    n.w = fmaf(q.la, q.old.w, p * (float)(TAct)v.w);
+    if (ep.state_half) {
+        f16 *sp = static_cast<f16 *>(ep.state);
+        n = make_float4(to_state(n.x, sp), to_state(n.y, sp), to_state(n.z, sp), to_state(n.w, sp));
+        store_state4(sp, at >> 2, n);
+    } else {
+        store_state4(static_cast<float *>(ep.state), at >> 2, n);
+    }
+    store4(o, make_float4(fmaf(c, n.x, q.be), fmaf(c, n.y, q.be), fmaf(c, n.z, q.be), fmaf(c, n.w, q.be)));
+}
 template <int EPI, typename TAct>
 __device__ __forceinline__ void epi_quad_store(const GemmEpi &ep, int64_t row, int col, const EpiQuad &q, float4 v)
 {
@@ -289,23 +314,7 @@ __device__ __forceinline__ void epi_quad_store(const GemmEpi &ep, int64_t row, i
     if constexpr (EPI == EPI_RESID) {
         store4(reinterpret_cast<float *>(ep.out) + at, make_float4(q.old.x + v.x, q.old.y + v.y, q.old.z + v.z, q.old.w + v.w));
     } else if constexpr (EPI == EPI_MIX) {
-        TAct *o = reinterpret_cast<TAct *>(ep.out) + at;
-        if (q.head < 0) { store4(o, make_float4(0.f, 0.f, 0.f, 0.f)); return; }
-        const bool row_repeat = q.head < ep.hrow;
-        const float p = row_repeat ? q.al : 1.0f, c = row_repeat ? 1.0f : q.al;
-        float4 n;
-        n.x = fmaf(q.la, q.old.x, p * (float)(TAct)v.x);
-        n.y = fmaf(q.la, q.old.y, p * (float)(TAct)v.y);
-        n.z = fmaf(q.la, q.old.z, p * (float)(TAct)v.z);
-        n.w = fmaf(q.la, q.old.w, p * (float)(TAct)v.w);
-        if (ep.state_half) {
-            f16 *sp = static_cast<f16 *>(ep.state);
-            n = make_float4(to_state(n.x, sp), to_state(n.y, sp), to_state(n.z, sp), to_state(n.w, sp));
-            store_state4(sp, at >> 2, n);
-        } else {
-            store_state4(static_cast<float *>(ep.state), at >> 2, n);
-        }
-        store4(o, make_float4(fmaf(c, n.x, q.be), fmaf(c, n.y, q.be), fmaf(c, n.z, q.be), fmaf(c, n.w, q.be)));
+        epi_mix_store<TAct>(ep, row, col, q, q.head >= 0, q.head < ep.hrow, v);
     } else {
         epi_store4<EPI, TAct>(ep, row, col, v);
     }
@@ -322,22 +331,21 @@ __device__ __forceinline__ void epi_store1p(const GemmEpi &ep, int64_t row, int 
     }
 }
 
-// Epilogue shared by the bf16 kernels.  Accumulator register r of lane (lk, lr)
-// of tile (i, j) is output row i*32 + lr, column j*32 + 8*(r/4) + 4*lk + r%4 of
-// the wave tile.  smem_raw: the block's LDS, free for reuse (all tile reads and
+// Epilogue shared by the bf16 kernels.  Accumulator register r of lane (lq, lr)
+// of tile (i, j) is output row i*16 + lr, column j*16 + 4*lq + r of the wave tile.  smem_raw: the block's LDS, free for reuse (all tile reads and
 // loads have completed and a barrier has been passed); lds_bytes its size.
 template <int BM, int BN, int WM, int WN, int EPI, typename TAct>
-__device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[BM / WM / 32][BN / WN / 32], unsigned char *smem_raw,
+__device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / WN / 16], unsigned char *smem_raw,
                                               const GemmEpi &ep, int M, int N, int m0, int n0, int bn,
                                               const int tid = threadIdx.x)
 {
     constexpr int NW = WM * WN, NTHR = NW * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
+    constexpr int TN = WTN / 16, SL = WTM / 32;       // column tiles; slices of 32 rows that pass through the stage
     constexpr int STG = WTN + 4;                     // stage row stride in floats: 16 B * odd
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
-    const int lr = lane & 31, lk = lane >> 5;
+    const int lr = lane & 15, lq = lane >> 4;
     float *stage = reinterpret_cast<float *>(smem_raw) + wave * 32 * STG;        // wave-private [32][STG]
     float *red_val = reinterpret_cast<float *>(smem_raw) + NW * 32 * STG;        // [BM][WN]
     int *red_idx = reinterpret_cast<int *>(red_val + BM * WN);                   // [BM][WN]
@@ -352,64 +360,63 @@ __device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[BM / WM / 32][BN /
     const bool cols_inside = vec_ok && n0 + BN <= N;                   // block-uniform
     const bool rows_inside = m0 + BM <= M;                             // block-uniform
 
+    if constexpr (EPI == EPI_ARGMAX) {
+        // in-lane over this lane's TN*4 columns of a row in ascending order (strict > keeps the lowest
+        // index), then two exchanges with the lanes holding the row's other columns, all rows' at once
+        // (row by row their round trips add up)
+        float bv[2 * SL];
+        int bi[2 * SL];
+        auto rows_best = [&](auto &&row_key, auto &&score, auto edge_c) {
+            static_for<0, 2 * SL>([&](auto t_) {
+                constexpr int t = decltype(t_)::value;
+                const uint32_t key = row_key(m0 + wm * WTM + t * 16 + lr);
+                float best = -INFINITY;
+                int brel = 0;
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int col = wcol0 + 4 * lq + j * 16 + r;
+                        const float v = score(acc[t][j][r], key, col);
+                        if ((!decltype(edge_c)::value || col < N) && v > best) { best = v; brel = j * 16 + r; }
+                    }
+                bv[t] = best;
+                bi[t] = best == -INFINITY ? 0x7fffffff : wcol0 + 4 * lq + brel;
+            });
+        };
+        if (ep.temp > 0.0f)
+            rows_best([&](int row) { return srm_rowkey(ep.seed, epi_pos(ep, row, M), (uint32_t)row + ep.row_base); },
+                      [&](float v, uint32_t key, int col) { return v + ep.temp * srm_gumbel(key, (uint32_t)col); }, std::true_type{});
+        else if (n_edge)
+            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::true_type{});
+        else
+            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::false_type{});
+        static_for<0, 2>([&](auto x_) {
+            static_for<0, 2 * SL>([&](auto t_) {
+                constexpr int t = decltype(t_)::value;
+                const float ov = __shfl_xor(bv[t], 16 << decltype(x_)::value, kWave);
+                const int oi = __shfl_xor(bi[t], 16 << decltype(x_)::value, kWave);
+                if (arg_better(ov, oi, bv[t], bi[t])) { bv[t] = ov; bi[t] = oi; }
+            });
+        });
+        static_for<0, 2 * SL>([&](auto t_) {
+            constexpr int t = decltype(t_)::value;
+            if (lq == 0) {
+                red_val[(wm * WTM + t * 16 + lr) * WN + wn] = bv[t];
+                red_idx[(wm * WTM + t * 16 + lr) * WN + wn] = bi[t];
+            }
+        });
+    }
     // (a compile-time loop: with the largest epilogue the compiler kept `#pragma unroll` rolled, which indexes
     // the accumulators with a variable and so moves all of them, main loop included, to scratch memory)
-    static_for<0, TM>([&](auto ic_) {
+    static_for<0, SL>([&](auto ic_) {
         constexpr int i = decltype(ic_)::value;
-        if constexpr (EPI == EPI_ARGMAX) {
-            // in-lane over this lane's TN*16 columns in ascending order (strict >
-            // keeps the lowest index), then one exchange with the lane holding
-            // the other half of the row's columns
-            float bv = -INFINITY;
-            int brel = 0;
-            if (ep.temp > 0.0f) {
-                const int srow = m0 + wm * WTM + i * 32 + lr;
-                const uint32_t rk = srm_rowkey(ep.seed, epi_pos(ep, srow, M), (uint32_t)srow + ep.row_base);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int rel = j * 32 + 8 * (r >> 2) + (r & 3);
-                        const int col = wcol0 + 4 * lk + rel;
-                        const float v = acc[i][j][r] + ep.temp * srm_gumbel(rk, (uint32_t)col);
-                        if (col < N && v > bv) { bv = v; brel = rel; }
-                    }
-            } else if (!n_edge) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float v = acc[i][j][r];
-                        if (v > bv) { bv = v; brel = j * 32 + 8 * (r >> 2) + (r & 3); }
-                    }
-            } else {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int rel = j * 32 + 8 * (r >> 2) + (r & 3);
-                        const int col = wcol0 + 4 * lk + rel;
-                        const float v = acc[i][j][r];
-                        if (col < N && v > bv) { bv = v; brel = rel; }
-                    }
-            }
-            int bi = bv == -INFINITY ? 0x7fffffff : wcol0 + 4 * lk + brel;
-            const float ov = __shfl_xor(bv, 32, kWave);
-            const int oi = __shfl_xor(bi, 32, kWave);
-            if (arg_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-            if (lk == 0) {
-                const int lrow = wm * WTM + i * 32 + lr;
-                red_val[lrow * WN + wn] = bv;
-                red_idx[lrow * WN + wn] = bi;
-            }
-        }
         if (want_store) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<float4 *>(stage + lr * STG + j * 32 + 8 * g + 4 * lk) =
-                        make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+                for (int j = 0; j < TN; ++j)
+                    *reinterpret_cast<f32x4_t *>(stage + (h * 16 + lr) * STG + j * 16 + 4 * lq) = acc[2 * i + h][j];
             // All columns of the tile inside the matrix: no column tests, all staged reads (and, for the
             // residual add and the state update, all loads of the old values) issued before the first use,
             // so their latencies overlap instead of adding up once per 128-byte row segment.  Compiled
@@ -606,7 +613,7 @@ gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, 
     static_assert(NS >= 2 && (NS & (NS - 1)) == 0, "the LDS ring holds a power-of-two number of k tiles");
     constexpr int NW = WM * WN, NTHR = NW * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
+    constexpr int TM = WTM / 16, TN = WTN / 16;
     constexpr int A_IT = BM * BK / 8 / NTHR, B_IT = BN * BK / 8 / NTHR;
     constexpr int STG = WTN + 4;                     // stage row stride in floats: 16 B * odd
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32x32");
@@ -629,7 +636,7 @@ gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: LDS targets of the tile loads
     const int wm = wave / WN, wn = wave % WN;
-    const int lr = lane & 31, lk = lane >> 5;
+    const int lr = lane & 15, lq = lane >> 4;
 
     // global -> LDS: buffer loads that write LDS directly (no VGPR staging, no
     // ds_write).  One wave instruction moves 8 rows x 128 bytes; the hardware puts
@@ -660,77 +667,58 @@ gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, 
     // s_waitcnt immediate: vmcnt = n, expcnt and lgkmcnt unconstrained
 #define SRM_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-    // The accumulators start at the bias of their column (bias + sum: the epilogues add nothing).  Register
-    // quad g of tile (i, j) holds columns j*32 + 8g + 4lk .. +3 of the wave tile (see gemm_epilogue).  The
+    // The accumulators start at the bias of their column (bias + sum: the epilogues add nothing).  Tile (i, j) of a
+    // lane holds columns j*16 + 4lq .. +3 of the wave tile (see gemm_epilogue).  The
     // bias is requested here, in front of the first tile loads, and moved into the accumulators once the
     // first tile has landed (loads return in order): its latency hides under the first tile's.
-    float4 bq[TN][4];
+    float4 bq[TN];
     if (ep.bias && (N & 3) == 0 && n0 + BN <= N) {       // block-uniform: all of the tile's columns exist
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) bq[j][g] = load4(ep.bias + n0 + wn * WTN + j * 32 + 8 * g + 4 * lk);
+        for (int j = 0; j < TN; ++j) bq[j] = load4(ep.bias + n0 + wn * WTN + j * 16 + 4 * lq);
     } else {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int col = n0 + wn * WTN + j * 32 + 8 * g + 4 * lk;
-                bq[j][g] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (ep.bias) {
-                    bq[j][g].x = col < N ? ep.bias[col] : 0.f;
-                    bq[j][g].y = col + 1 < N ? ep.bias[col + 1] : 0.f;
-                    bq[j][g].z = col + 2 < N ? ep.bias[col + 2] : 0.f;
-                    bq[j][g].w = col + 3 < N ? ep.bias[col + 3] : 0.f;
-                }
+        for (int j = 0; j < TN; ++j) {
+            const int col = n0 + wn * WTN + j * 16 + 4 * lq;
+            bq[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ep.bias) {
+                bq[j].x = col < N ? ep.bias[col] : 0.f;
+                bq[j].y = col + 1 < N ? ep.bias[col + 1] : 0.f;
+                bq[j].z = col + 2 < N ? ep.bias[col + 2] : 0.f;
+                bq[j].w = col + 3 < N ? ep.bias[col + 3] : 0.f;
             }
+        }
     }
-    f32x16_t acc[TM][TN];
+    f32x4_t acc[TM][TN];
 
     const int sw = swz_of_row(lr);                   // wave-tile rows are multiples of 32 apart
     const int a_row_off = (wm * WTM + lr) * BK;
     const int b_row_off = (wn * WTN + lr) * BK;
-    bf16x8_t fa[4][TM], fb[4][TN];                   // one operand set per k-substep
-#define SRM_READ_FRAGS(buf, kk, set)                                                             \
+    bf16x8_t fa[2][TM], fb[2][TN];                   // one operand set per half of a k tile
+    // operand number r of half h of the k tile in `buf`: the first TM are of A, the rest of W
+#define SRM_READ_ONE(r, buf, h)                                                                  \
     {                                                                                            \
-        const int ch_ = ((((kk) * 2 + lk) ^ sw) << 3);                                           \
-        const bf16 *as_ = As + (buf) * BM * BK + a_row_off + ch_;                                \
-        const bf16 *bs_ = Bs + (buf) * BN * BK + b_row_off + ch_;                               \
-        _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-            fa[set][i] = *reinterpret_cast<const bf16x8_t *>(as_ + i * 32 * BK);                 \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                           \
-            fb[set][j] = *reinterpret_cast<const bf16x8_t *>(bs_ + j * 32 * BK);                 \
+        const int ch_ = ((((h) * 4 + lq) ^ sw) << 3);                                            \
+        if ((r) < TM)                                                                            \
+            fa[h][r] = *reinterpret_cast<const bf16x8_t *>(As + (buf) * BM * BK + a_row_off + ch_ + (r) * 16 * BK);        \
+        else                                                                                     \
+            fb[h][(r) - TM] = *reinterpret_cast<const bf16x8_t *>(Bs + (buf) * BN * BK + b_row_off + ch_ + ((r) - TM) * 16 * BK); \
     }
+#define SRM_READ_FRAGS(buf, h)                                                                   \
+    _Pragma("unroll") for (int r_ = 0; r_ < TM + TN; ++r_) { SRM_READ_ONE(r_, buf, h) }
 
-#define SRM_MFMA_STEP(set)                                                                       \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i)                                               \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j) /* transposed: MFMA rows run over N */    \
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
-    // Issue order inside the k-substeps that only read operands (0, 1 and 3): one LDS read behind
-    // each MFMA, so that the reads issue while the matrix pipe works instead of in a burst in front
-    // of it.  (Substep 2, which also issues the tile loads, is written out in issue order below.)
-#define SRM_INTERLEAVE()                                                                         \
-    _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) {                                        \
-        constexpr int S_ = TM * TN;                                                              \
-        constexpr int R_ = (TM + TN + S_ - 1) / S_;                                              \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
-        if (q * R_ < TM + TN) __builtin_amdgcn_sched_group_barrier(0x100, R_, 0);                \
-    }                                                                                            \
-    __builtin_amdgcn_sched_barrier(0);
-
-    // Software pipeline over K tiles (four k-substeps of 16 each), a ring of NS LDS
+    // Software pipeline over K tiles (two halves of 32 each), a ring of NS LDS
     // buffers (NS = 2 below; with few blocks on the chip a k loop is bound by the
     // latency of its tile loads, and a deeper ring keeps NS - 1 tiles in flight),
-    // MFMA operands read two substeps ahead (four register sets):
-    //   substep 0: read operands of substep 2                  | MFMAs of substep 0
-    //   substep 1: read operands of substep 3                  | MFMAs of substep 1
-    //              wait for tile kt+1's loads, barrier: buffer `cur` is now free
-    //   substep 2: read substep-0 operands of tile kt+1,       | MFMAs of substep 2
-    //              start tile kt+2's loads into `cur`
-    //   substep 3: read substep-1 operands of tile kt+1        | MFMAs of substep 3
+    // MFMA operands read one half ahead (two register sets):
+    //   half 0: read operands of half 1                        | MFMAs of half 0
+    //           wait for tile kt+1's loads, barrier: buffer `cur` is now free
+    //   half 1: read half-0 operands of tile kt+1,             | MFMAs of half 1
+    //           start tile kt+2's loads into `cur`
     // A tile's loads have a full tile period to land and every operand read has
-    // two substeps, which absorbs the queueing of reads behind the tile writes in
-    // the LDS pipe.  Loads for tiles past the end are issued like any other
+    // half a tile, which absorbs the queueing of reads behind the tile writes in
+    // the LDS pipe.  The reads and loads are spread over the MFMAs by hand, pinned
+    // (left to the scheduler they go in front of the second MFMA in one burst).
+    // Loads for tiles past the end are issued like any other
     // (range check: zeros nobody reads), which keeps the loop branch-free.
     const int KT = K / BK;
     static_assert((NS - 1) * (A_IT + B_IT) <= 63, "more tile loads in flight than the counter holds");
@@ -739,66 +727,52 @@ gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, 
     for (int stage = 0; stage < NS; ++stage) { SRM_DMA_TILE(stage * BK, stage) }       // (the macro's own loops use `i`)
     SRM_WAIT_VM((NS - 1) * LD_IT);
     __syncthreads();
-    SRM_READ_FRAGS(0, 0, 0)
-    SRM_READ_FRAGS(0, 1, 1)
+    SRM_READ_FRAGS(0, 0)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                acc[i][j][4 * g] = bq[j][g].x; acc[i][j][4 * g + 1] = bq[j][g].y;
-                acc[i][j][4 * g + 2] = bq[j][g].z; acc[i][j][4 * g + 3] = bq[j][g].w;
-            }
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{bq[j].x, bq[j].y, bq[j].z, bq[j].w};
     __builtin_amdgcn_sched_barrier(0);
     if (probe) { clk_c1 = clock64(); clk_t1 = wall_clock64(); }
 
+    constexpr int S_ = TM * TN;                      // MFMAs per half
+    // ... and those that the tile loads are spread over: all, as a burst makes the MFMAs wait for their turn to issue
+    // (3001 x 1024 x 4096: 30.6 us over half of them, 29.2 over all), but with four MFMAs only the loop is bound by the
+    // latency of the loads (64x64 tile, ring of eight, 512 x 1024 x 4096: 19.2 us over all, 15.8 behind the first)
+    constexpr int LSPAN = S_ <= 4 ? 1 : S_;
     for (int kt = 0; kt < KT; ++kt) {
         const int cur = kt & (NS - 1), nxt = (kt + 1) & (NS - 1);
-        SRM_READ_FRAGS(cur, 2, 2)
-        SRM_MFMA_STEP(0)
-        SRM_INTERLEAVE()
-        SRM_READ_FRAGS(cur, 3, 3)
-        SRM_MFMA_STEP(1)
-        SRM_INTERLEAVE()
+        // one operand read behind each of the MFMAs spread over the first three quarters of a half
+#pragma unroll
+        for (int q = 0; q < S_; ++q) {               // transposed: MFMA rows run over N
+            acc[q / TN][q % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][q % TN], fa[0][q / TN], acc[q / TN][q % TN], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < TM + TN; ++r)
+                if (r * (S_ * 3 / 4) / (TM + TN) == q) { SRM_READ_ONE(r, cur, 1) }
+            __builtin_amdgcn_sched_barrier(0);
+        }
         SRM_WAIT_VM((NS - 2) * LD_IT);                   // tile kt+1 has landed; later tiles may still be in flight
         __syncthreads();
-        // substep 2 in issue order, pinned: behind each MFMA its share of the operand reads of the next
-        // tile's substep 0 and of the tile loads (left to the scheduler, the reads and loads all went in
-        // front of the second MFMA in one burst)
-        {
-            const int ch_ = ((lk ^ sw) << 3);
-            const bf16 *as_ = As + nxt * BM * BK + a_row_off + ch_;
-            const bf16 *bs_ = Bs + nxt * BN * BK + b_row_off + ch_;
-            constexpr int S_ = TM * TN;
-            constexpr int RPM = (TM + TN + S_ - 1) / S_, LPM = (LD_IT + S_ - 1) / S_;
 #pragma unroll
-            for (int q = 0; q < S_; ++q) {
-                acc[q / TN][q % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[2][q % TN], fa[2][q / TN],
-                                                                              acc[q / TN][q % TN], 0, 0, 0);
+        for (int q = 0; q < S_; ++q) {
+            acc[q / TN][q % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[1][q % TN], fa[1][q / TN], acc[q / TN][q % TN], 0, 0, 0);
 #pragma unroll
-                for (int r = q * RPM; r < (q + 1) * RPM && r < TM + TN; ++r) {
-                    if (r < TM) fa[0][r] = *reinterpret_cast<const bf16x8_t *>(as_ + r * 32 * BK);
-                    else fb[0][r - TM] = *reinterpret_cast<const bf16x8_t *>(bs_ + (r - TM) * 32 * BK);
-                }
+            for (int r = 0; r < TM + TN; ++r)
+                if (r * (S_ * 3 / 4) / (TM + TN) == q) { SRM_READ_ONE(r, nxt, 0) }
 #pragma unroll
-                for (int l = q * LPM; l < (q + 1) * LPM && l < LD_IT; ++l) { SRM_DMA_ONE(l, (kt + NS) * BK, cur) }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int l = 0; l < LD_IT; ++l)
+                if (l * LSPAN / LD_IT == q) { SRM_DMA_ONE(l, (kt + NS) * BK, cur) }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        SRM_READ_FRAGS(nxt, 1, 1)
-        SRM_MFMA_STEP(3)
-        SRM_INTERLEAVE()
     }
     SRM_WAIT_VM(0);
     __syncthreads();                                  // LDS is reused by the epilogue
     if (probe) { clk_c2 = clock64(); clk_t2 = wall_clock64(); }
-#undef SRM_MFMA_STEP
-#undef SRM_INTERLEAVE
 #undef SRM_DMA_TILE
 #undef SRM_DMA_ONE
 #undef SRM_WAIT_VM
 #undef SRM_READ_FRAGS
+#undef SRM_READ_ONE
 
     gemm_epilogue<BM, BN, WM, WN, EPI, TAct>(acc, smem_raw, ep, M, N, m0, n0, bn);
     if (probe) {

@@ -1,51 +1,188 @@
-// Persistent form of the 256x256 bf16 MFMA GEMM (same contract and epilogues as gemm_bf16_kernel in
-// gemm.hpp: out = epilogue(A W^T + bias)), for launches with more output tiles than CUs.
+// The 256x256 bf16 MFMA GEMM (same contract and epilogues as gemm_bf16_kernel in gemm.hpp: out = epilogue(A W^T + bias)),
+// as a persistent kernel: one work-group per CU walks its output tiles v = blockIdx.x, blockIdx.x + gridDim.x, ... and the
+// LDS ring runs from one output tile into the next, so that a tile that is not a CU's first starts its MFMAs at once
+// instead of after a work-group launch and a cold round trip to memory.
 //
-// One work-group per CU walks its tiles v = blockIdx.x, blockIdx.x + gridDim.x, ... and keeps the LDS ring
-// running from one output tile into the next: the first k tile of the next output tile (and its 256 bias
-// values) is requested two k tiles before the current k loop ends, so it has landed before the epilogue
-// starts.  A tile that is not a CU's first therefore starts its MFMAs at once instead of after a work-group
-// launch and a cold round trip to memory.
-//
-// LDS (160 KB): ring slot 0 | ring slot 1 | 32 KB; a slot holds a 256x64 A tile, then a 256x64 W tile, in
-// the swizzled layout of gemm_bf16_kernel; the last 1 KB holds the tile's bias.
-//   RING = false: the epilogue stages its stores through slot 1 and the 32 KB behind it (78 KB), so only
-//     slot 0 is filled under it, and the next tile's second k tile is requested right after the epilogue.
-//   RING = true (the LM head's argmax without stored logits, whose epilogue needs 8 KB only, which lie behind
-//     the ring): both slots keep filling, the k loop of the next tile continues as if it were the same one.
+// LDS (160 KB) is a ring of five units of 32 KB, each an A tile or a W tile of 256 rows x 64 k in the swizzled layout of
+// gemm_bf16_kernel.  k tile T (counted on through all output tiles) has A in unit 2T mod 5 and W in unit 2T + 1 mod 5:
+//     half 0 of T: MFMAs of its first 32 k | operands of its second half | loads of A of T+2 (unit 2T+4: W of T-1 is done)
+//     barrier: T+1 has landed, T has been read by all
+//     half 1 of T: MFMAs of the other 32 k | operands of T+1's first half | loads of W of T+2 (unit 2T: A of T is done)
+// With two and a half tiles instead of two, loads are issued in both halves: a CU takes a load of 1 KB in about 16
+// clocks, 1024 per k tile of 2048 clocks of MFMAs, and all in one half they make the wavefronts wait for their turn to
+// issue (16384 x 1024 x 4096: 2555 clocks per k tile with the loads in one half, 2217 without any).
+// The epilogue stages its stores through the unit of the last k tile's W (32 KB, free since that k tile's barrier),
+// sixteen rows at a time; everything else keeps filling under it.
 #pragma once
 #include "gemm.hpp"
 
 constexpr int kPersistLds = 160 * 1024;
 
-template <int EPI, typename TAct, bool RING = false>
+// The epilogue: acc[t][j] of lane (lq, lr) is row t*16 + lr, columns j*16 + 4lq .. +3 of the wave tile (128 x 64; 2 x 4
+// wave tiles).  Sixteen rows at a time pass through a wave-private stage [16][64] in `stage` (16-byte chunk c of row r at
+// chunk c ^ r: writes and reads free of bank conflicts), so that global accesses are 16-byte vectors over 256 bytes of a
+// row.  Old values (residual stream, recurrent state) are requested for 32 rows at a time, in front of the stage.
+template <int EPI, typename TAct, typename BARRIER>
+__device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned char *stage_base, const GemmEpi &ep, int M, int N,
+                                                 int m0, int n0, int bn, const int tid, BARRIER &&lds_barrier)
+{
+    constexpr int TM = 8, TN = 4, WTM = 128, WTN = 64, WN = 4;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int lr = lane & 15, lq = lane >> 4;
+    const int wcol0 = n0 + wn * WTN, wrow0 = m0 + wm * WTM;
+    const bool inside = n0 + 256 <= N && m0 + 256 <= M;                // block-uniform
+    if (EPI != EPI_ARGMAX || ep.out != nullptr) {
+        f32x4_t *stage = reinterpret_cast<f32x4_t *>(stage_base) + wave * (16 * 16);   // [16 rows][16 chunks]
+        const int s_row = lane >> 4, s_chunk = lane & 15;
+        const int gcol = wcol0 + s_chunk * 4;
+        const unsigned lane_at = (unsigned)s_row * (unsigned)ep.ldo + s_chunk * 4;    // (the rest of an offset is uniform)
+        auto slices = [&](auto inside_c) {
+            constexpr bool IN = decltype(inside_c)::value;
+            auto row_of = [&](int t, int it) { return (int64_t)wrow0 + t * 16 + it * 4 + s_row; };
+            auto exists = [&](int t, int it) { return IN || (row_of(t, it) < M && gcol < N); };
+            // where the old values of a quad are read: one that exists
+            auto at = [&](int t, int it) {
+                if constexpr (IN) return (wrow0 + t * 16 + it * 4) * ep.ldo + wcol0 + (int64_t)lane_at;
+                else return min(row_of(t, it), (int64_t)M - 1) * ep.ldo + min(gcol, N - 4);
+            };
+            static_for<0, TM / 2>([&](auto p_) {
+                constexpr int t0 = 2 * decltype(p_)::value;
+                [[maybe_unused]] float4 old[2][4];
+                if constexpr (EPI == EPI_RESID || EPI == EPI_MIX) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int it = 0; it < 4; ++it) {
+                            if constexpr (EPI == EPI_RESID) old[h][it] = load4(static_cast<const float *>(ep.out) + at(t0 + h, it));
+                            else if (ep.state_half) old[h][it] = load_state4(static_cast<const f16 *>(ep.state), at(t0 + h, it) >> 2);
+                            else old[h][it] = load_state4(static_cast<const float *>(ep.state), at(t0 + h, it) >> 2);
+                        }
+                }
+                static_for<0, 2>([&](auto h_) {
+                    constexpr int h = decltype(h_)::value, t = t0 + h;
+                    [[maybe_unused]] float al[4], be[4], la = 0.0f;
+                    [[maybe_unused]] int ps[4];
+                    [[maybe_unused]] bool row_repeat = false;
+                    if constexpr (EPI == EPI_MIX) {
+                        const int hd = min(gcol, N - 4) / ep.dh;       // four consecutive channels lie in one head
+                        row_repeat = hd < ep.hrow;
+                        la = ep.lam[hd];
+#pragma unroll
+                        for (int it = 0; it < 4; ++it)
+                            ps[it] = (int)(ep.pos_rows ? (uint32_t)ep.pos_rows[IN ? row_of(t, it) : min(row_of(t, it), (int64_t)M - 1)]
+                                                       : epi_shared_pos(ep));
+#pragma unroll
+                        for (int it = 0; it < 4; ++it) {
+                            const int pc = ps[it] >= 0 && ps[it] < ep.n_ctx ? ps[it] : 0;
+                            al[it] = ep.alpha[(size_t)hd * ep.n_ctx + pc];
+                            be[it] = ep.beta[(size_t)hd * ep.n_ctx + pc];
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) stage[lr * 16 + ((4 * j + lq) ^ lr)] = acc[t][j];
+                    f32x4_t v[4];
+#pragma unroll
+                    for (int it = 0; it < 4; ++it) v[it] = stage[(it * 4 + s_row) * 16 + (s_chunk ^ (it * 4 + s_row))];
+#pragma unroll
+                    for (int it = 0; it < 4; ++it) {
+                        if (!exists(t, it)) continue;
+                        const int64_t row = row_of(t, it);
+                        const float4 w = make_float4(v[it][0], v[it][1], v[it][2], v[it][3]);
+                        if constexpr (EPI == EPI_RESID) {
+                            const float4 o = old[h][it];
+                            store4(static_cast<float *>(ep.out) + row * ep.ldo + gcol,
+                                   make_float4(o.x + w.x, o.y + w.y, o.z + w.z, o.w + w.w));
+                        } else if constexpr (EPI == EPI_MIX) {
+                            EpiQuad q;
+                            q.old = old[h][it];
+                            q.al = al[it]; q.be = be[it]; q.la = la;
+                            epi_mix_store<TAct>(ep, row, gcol, q, ps[it] >= 0 && ps[it] < ep.n_ctx, row_repeat, w);
+                        } else {
+                            epi_store4<EPI, TAct>(ep, row, gcol, w);
+                        }
+                    }
+                });
+            });
+        };
+        if (inside) slices(std::true_type{});
+        else slices(std::false_type{});
+    }
+    if constexpr (EPI == EPI_ARGMAX) {
+        // Every lane leaves the best of its sixteen columns of a row in the stage, entry wn*4 + lq of [256 rows][16] (at
+        // entry ^ row: no bank conflicts); two lanes per row then take the best of the sixteen.  (Exchanged between lanes
+        // row by row instead, the round trips through the LDS crossbar add up: 8.7 us per tile.)
+        uint2 *red = reinterpret_cast<uint2 *>(stage_base);
+        if (ep.out) lds_barrier();                   // the stages have been read back
+        // score(t, j, r, column): what is compared; strict > in ascending order keeps the lowest index
+        auto rows_best = [&](auto &&row_key, auto &&score, auto edge_c) {
+            static_for<0, TM>([&](auto t_) {
+                constexpr int t = decltype(t_)::value;
+                const uint32_t key = row_key(wrow0 + t * 16 + lr);
+                float bv = -INFINITY;
+                int brel = 0;
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int col = wcol0 + 4 * lq + j * 16 + r;
+                        const float v = score(acc[t][j][r], key, col);
+                        if ((!decltype(edge_c)::value || col < N) && v > bv) { bv = v; brel = j * 16 + r; }
+                    }
+                const int bi = bv == -INFINITY ? 0x7fffffff : wcol0 + 4 * lq + brel;
+                red[(wm * WTM + t * 16 + lr) * 16 + ((wn * 4 + lq) ^ lr)] = make_uint2(__float_as_uint(bv), (unsigned)bi);
+            });
+        };
+        if (ep.temp > 0.0f)
+            rows_best([&](int row) { return srm_rowkey(ep.seed, epi_pos(ep, row, M), (uint32_t)row + ep.row_base); },
+                      [&](float v, uint32_t key, int col) { return v + ep.temp * srm_gumbel(key, (uint32_t)col); }, std::true_type{});
+        else if (wcol0 + WTN > N)                    // wave-uniform
+            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::true_type{});
+        else
+            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::false_type{});
+        lds_barrier();
+        const int row = m0 + (tid >> 1);
+        const uint4 *mine = reinterpret_cast<const uint4 *>(red + tid * 8);
+        float bv = -INFINITY;
+        int bi = 0x7fffffff;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint4 x = mine[e];
+            if (arg_better(__uint_as_float(x.x), (int)x.y, bv, bi)) { bv = __uint_as_float(x.x); bi = (int)x.y; }
+            if (arg_better(__uint_as_float(x.z), (int)x.w, bv, bi)) { bv = __uint_as_float(x.z); bi = (int)x.w; }
+        }
+        const float ov = __shfl_xor(bv, 1, kWave);
+        const int oi = __shfl_xor(bi, 1, kWave);
+        if (arg_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        if ((tid & 1) == 0 && row < M) {
+            ep.part_val[(int64_t)bn * M + row] = bv;
+            ep.part_idx[(int64_t)bn * M + row] = bi;
+        }
+    }
+}
+
+template <int EPI, typename TAct>
 __global__ void __launch_bounds__(512)
 gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
     constexpr int BM = 256, BN = 256, WM = 2, WN = 4, BK = 64;
-    constexpr int NW = WM * WN, NTHR = NW * 64;
+    constexpr int NTHR = WM * WN * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
-    constexpr int A_IT = BM * BK / 8 / NTHR, B_IT = BN * BK / 8 / NTHR, LD_IT = A_IT + B_IT;
-    constexpr int SLOT = (BM + BN) * BK;             // elements per ring slot
-    constexpr int STG = WTN + 4;
-    static_assert(!RING || EPI == EPI_ARGMAX, "only the argmax epilogue can do without a stage");
-    // bytes: the epilogue's stage starts at slot 1; RING: placed so that the argmax partials lie behind the ring
-    constexpr int kStageOff = RING ? 2 * SLOT * 2 - NW * 32 * STG * 4 : SLOT * 2;
-    constexpr int kBiasOff = kPersistLds - BN * 4;
-    static_assert(kStageOff + NW * 32 * STG * 4 + BM * WN * 8 <= kBiasOff, "epilogue stage runs into the bias");
+    constexpr int TM = WTM / 16, TN = WTN / 16;
+    constexpr int UNITS = 5, UNIT = 256 * BK * 2;    // bytes
+    constexpr int LD_IT = UNIT / 16 / NTHR;          // loads per wavefront and unit
+    static_assert(UNITS * UNIT <= kPersistLds, "the ring is the LDS");
+    static_assert(WM * WN * 16 * WTN * 4 <= UNIT && BM * 16 * 8 <= UNIT, "the epilogue's stage fits a unit");
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    bf16 *ring = reinterpret_cast<bf16 *>(smem_raw);
-    const float *bias_lds = reinterpret_cast<const float *>(smem_raw + kBiasOff);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int lr = lane & 31, lk = lane >> 5;
+    const int lr = lane & 15, lq = lane >> 4;
 
     const int nbm = (M + BM - 1) / BM, nbn = (N + BN - 1) / BN, nblk = nbm * nbn;
-    const int KT = K / BK;                           // even and >= 4 (the launcher checks)
+    const int KT = K / BK;                           // >= 2 (the launcher checks)
 
     // Tile loads: buffer_load ... lds, one wave instruction = 8 rows x 128 bytes, lane (r = l >> 3, slot = l & 7)
     // fetches chunk slot ^ swz(r) of its row.  A descriptor covers exactly one tile's rows of A or W (rows past
@@ -67,31 +204,20 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         rs[3] = 0x00020000u;
         return rs;
     };
-    auto dma = [&](const u32x4_t &rs, unsigned lds_dst, int voff, int soff) {
+    // load number i of the unit at ring offset `unit`, from k tile kq
+    auto dma_one = [&](int i, const u32x4_t &rs, int kq, unsigned unit) {
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                      :
-                     : "s"(lds_dst), "v"(voff), "s"(rs), "s"(soff)
+                     : "s"(ring_lds + unit + (i * ROWS_PER_IT + wave * 8) * (BK * 2)), "v"(ld_voff), "s"(rs),
+                       "s"((i * ROWS_PER_IT * K + kq * BK) * 2)
                      : "memory");
     };
-    // tile load number i of k tile kq (the first A_IT fetch A, the rest W) into ring slot `slot`
-    auto dma_one = [&](int i, const u32x4_t &ra, const u32x4_t &rw, int kq, int slot) {
-        if (i < A_IT)
-            dma(ra, ring_lds + (slot * SLOT + (i * ROWS_PER_IT + wave * 8) * BK) * 2, ld_voff,
-                (i * ROWS_PER_IT * K + kq * BK) * 2);
-        else
-            dma(rw, ring_lds + (slot * SLOT + BM * BK + ((i - A_IT) * ROWS_PER_IT + wave * 8) * BK) * 2, ld_voff,
-                ((i - A_IT) * ROWS_PER_IT * K + kq * BK) * 2);
-    };
-    auto dma_tile = [&](const u32x4_t &ra, const u32x4_t &rw, int kq, int slot) {
-        static_for<0, LD_IT>([&](auto i_) { dma_one(decltype(i_)::value, ra, rw, kq, slot); });
-    };
-    // the 256 bias values of a tile: one instruction of wavefront 0 (zeros for columns past N)
-    auto dma_bias = [&](const u32x4_t &rb) {
-        if (ep.bias && wave == 0) dma(rb, ring_lds + kBiasOff, lane * 16, 0);
+    auto dma_unit = [&](const u32x4_t &rs, int kq, unsigned unit) {
+        static_for<0, LD_IT>([&](auto i_) { dma_one(decltype(i_)::value, rs, kq, unit); });
     };
     struct Tile {
         int m0, n0, bn;
-        u32x4_t ra, rw, rb;
+        u32x4_t ra, rw;
     };
     auto tile_at = [&](int v) {
         Tile t;
@@ -102,136 +228,106 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         t.n0 = t.bn * BN;
         t.ra = descriptor(A + (size_t)t.m0 * K, exists ? min(BM, M - t.m0) * K * 2 : 0);
         t.rw = descriptor(W + (size_t)t.n0 * K, exists ? min(BN, N - t.n0) * K * 2 : 0);
-        t.rb = descriptor(ep.bias ? ep.bias + t.n0 : nullptr, exists && ep.bias ? min(BN, N - t.n0) * 4 : 0);
         return t;
     };
+    // the bias of this lane's columns n0 + wn*64 + j*16 + 4lq .. +3 (zeros past N, which is a multiple of 4)
+    f32x4_t bq[TN];
+    auto bias_request = [&](int n0) {
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(ep.bias ? ep.bias + n0 : nullptr), 0, ep.bias ? max(min(BN, N - n0), 0) * 4 : 0, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            bq[j] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rb, (wn * WTN + j * 16 + 4 * lq) * 4, 0, 0));
+    };
 #define SRM_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+    // a barrier that orders LDS accesses only
+    auto lds_barrier = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
 
-    const int sw = swz_of_row(lr);
-    const int a_row_off = (wm * WTM + lr) * BK;
-    const int b_row_off = BM * BK + (wn * WTN + lr) * BK;
-    bf16x8_t fa[4][TM], fb[4][TN];                   // one operand set per k-substep
-    f32x16_t acc[TM][TN];
-#define SRM_READ_FRAGS(slot, kk, set)                                                            \
-    {                                                                                            \
-        const int ch_ = ((((kk) * 2 + lk) ^ sw) << 3);                                           \
-        const bf16 *as_ = ring + (slot) * SLOT + a_row_off + ch_;                                \
-        const bf16 *bs_ = ring + (slot) * SLOT + b_row_off + ch_;                                \
-        _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-            fa[set][i] = *reinterpret_cast<const bf16x8_t *>(as_ + i * 32 * BK);                 \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                           \
-            fb[set][j] = *reinterpret_cast<const bf16x8_t *>(bs_ + j * 32 * BK);                 \
-    }
-#define SRM_MFMA_STEP(set)                                                                       \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i)                                               \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j) /* transposed: MFMA rows run over N */    \
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
-    // one LDS read behind each MFMA (see gemm_bf16_kernel)
-#define SRM_INTERLEAVE()                                                                         \
-    _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) {                                        \
-        constexpr int S_ = TM * TN;                                                              \
-        constexpr int R_ = (TM + TN + S_ - 1) / S_;                                              \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
-        if (q * R_ < TM + TN) __builtin_amdgcn_sched_group_barrier(0x100, R_, 0);                \
-    }                                                                                            \
-    __builtin_amdgcn_sched_barrier(0);
+    // LDS byte offsets of this lane's first operands of half 0 in a unit; those of half 1 lie 64 bytes across
+    typedef const __attribute__((address_space(3))) bf16x8_t lds_frag;
+    const unsigned a_lds = ring_lds + (wm * WTM + lr) * (BK * 2) + ((lq ^ swz_of_row(lr)) << 4);
+    const unsigned b_lds = ring_lds + (wn * WTN + lr) * (BK * 2) + ((lq ^ swz_of_row(lr)) << 4);
+    bf16x8_t fa[2][TM], fb[2][TN];                   // one operand set per half of a k tile
+    f32x4_t acc[TM][TN];
+    // operand number r of half h of the k tile in units ua, ub: the first TM are of A, the rest of W
+    auto read_one = [&](auto r_, auto h_, unsigned ua, unsigned ub) {
+        constexpr int r = decltype(r_)::value, h = decltype(h_)::value;
+        if constexpr (r < TM) fa[h][r] = *(lds_frag *)((a_lds ^ (h * 64)) + ua + r * (16 * BK * 2));
+        else fb[h][r - TM] = *(lds_frag *)((b_lds ^ (h * 64)) + ub + (r - TM) * (16 * BK * 2));
+    };
+    constexpr std::integral_constant<int, 0> h0{};
+    constexpr std::integral_constant<int, 1> h1{};
+    // MFMAs of half h, transposed (MFMA rows run over N); pinned behind the q-th of them its share of the operand reads
+    // of the other half, over the first three quarters, and of the loads of a unit, over the first quarter
+    auto half = [&](auto h_, unsigned ua, unsigned ub, const u32x4_t &rs, int kq, unsigned unit) {
+        constexpr int S_ = TM * TN, h = decltype(h_)::value;
+        static_for<0, S_>([&](auto q_) {
+            constexpr int q = decltype(q_)::value;
+            acc[q / TN][q % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[h][q % TN], fa[h][q / TN], acc[q / TN][q % TN], 0, 0, 0);
+            static_for<0, TM + TN>([&](auto r_) {
+                if constexpr (decltype(r_)::value * (S_ * 3 / 4) / (TM + TN) == q)
+                    read_one(r_, std::integral_constant<int, 1 - h>{}, ua, ub);
+            });
+            static_for<0, LD_IT>([&](auto l_) {
+                if constexpr (decltype(l_)::value * (S_ / 4) / LD_IT == q) dma_one(decltype(l_)::value, rs, kq, unit);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    // the epilogues that hold old values leave no registers for the operands that the last k tile has read ahead
+    constexpr bool REREAD = EPI == EPI_RESID || EPI == EPI_MIX;
 
     int v = blockIdx.x;                              // gridDim.x <= nblk: every work-group has a first tile
     Tile cur = tile_at(v);
     unsigned long long clk_c0 = 0, clk_t0 = 0, clk_c1 = 0, clk_t1 = 0, clk_c2 = 0, clk_t2 = 0;
     if (ep.clk) { clk_c0 = clock64(); clk_t0 = wall_clock64(); }
-    dma_bias(cur.rb);
-    dma_tile(cur.ra, cur.rw, 0, 0);
-    dma_tile(cur.ra, cur.rw, 1, 1);
-    SRM_WAIT_VM(LD_IT);                              // loads return in order: the bias and k tile 0 are there
-    __syncthreads();
-    SRM_READ_FRAGS(0, 0, 0)
-    SRM_READ_FRAGS(0, 1, 1)
+    bias_request(cur.n0);
+    __builtin_amdgcn_sched_barrier(0);
+    dma_unit(cur.ra, 0, 0);
+    dma_unit(cur.rw, 0, UNIT);
+    dma_unit(cur.ra, 1, 2 * UNIT);
+    dma_unit(cur.rw, 1, 3 * UNIT);
+    SRM_WAIT_VM(2 * LD_IT);                          // loads return in order: the bias and k tile 0 are there
+    lds_barrier();
+    static_for<0, TM + TN>([&](auto r_) { read_one(r_, h0, 0, UNIT); });
 
+    unsigned u = 0;                                  // unit of A of this k tile; the five units from there on:
+    auto at = [&](unsigned k) { const unsigned x = u + k; return (x >= UNITS ? x - UNITS : x) * UNIT; };
     for (;;) {
         const bool probe = ep.clk != nullptr && v < ep.clk_blocks;
         const int vn = v + (int)gridDim.x;
         const Tile nxt = tile_at(vn);                // of zero size behind the last tile
-        // the accumulators start at the bias of their column: register quad g of tile (i, j) holds columns
-        // j*32 + 8g + 4lk .. +3 of the wave tile
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)                 // the accumulators start at the bias of their column
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (ep.bias) b = *reinterpret_cast<const float4 *>(bias_lds + wn * WTN + j * 32 + 8 * g + 4 * lk);
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    acc[i][j][4 * g] = b.x; acc[i][j][4 * g + 1] = b.y;
-                    acc[i][j][4 * g + 2] = b.z; acc[i][j][4 * g + 3] = b.w;
-                }
-            }
+            for (int i = 0; i < TM; ++i) acc[i][j] = bq[j];
         __builtin_amdgcn_sched_barrier(0);
         if (probe) { clk_c1 = clock64(); clk_t1 = wall_clock64(); }
 
-        // The schedule of gemm_bf16_kernel.  The loads issued in k tile kt fill the slot it frees with k tile
-        // kt+2 of this output tile or, from k tile KT-2 on, with k tile kt+2-KT of the next one; the operands
-        // it reads ahead in its second half are those of k tile kt+1, in k tile KT-1 (RING only) the next
-        // output tile's first.
-        const int kt_end = RING ? KT : KT - 1;
-        for (int kt = 0; kt < kt_end; ++kt) {
-            const int s_cur = kt & 1, s_nxt = s_cur ^ 1;
+        for (int kt = 0; kt < KT; ++kt) {
             const bool ahead = kt + 2 >= KT;
             const u32x4_t ra = ahead ? nxt.ra : cur.ra, rw = ahead ? nxt.rw : cur.rw;
             const int kq = ahead ? kt + 2 - KT : kt + 2;
-            SRM_READ_FRAGS(s_cur, 2, 2)
-            SRM_MFMA_STEP(0)
-            SRM_INTERLEAVE()
-            SRM_READ_FRAGS(s_cur, 3, 3)
-            SRM_MFMA_STEP(1)
-            SRM_INTERLEAVE()
-            SRM_WAIT_VM(0);                          // k tile kt+1 has landed
-            __syncthreads();                         // ... for everyone, and slot s_cur is free
-            {
-                const int ch_ = ((lk ^ sw) << 3);
-                const bf16 *as_ = ring + s_nxt * SLOT + a_row_off + ch_;
-                const bf16 *bs_ = ring + s_nxt * SLOT + b_row_off + ch_;
-                constexpr int S_ = TM * TN;
-                constexpr int RPM = (TM + TN + S_ - 1) / S_, LPM = (LD_IT + S_ - 1) / S_;
-#pragma unroll
-                for (int q = 0; q < S_; ++q) {
-                    acc[q / TN][q % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[2][q % TN], fa[2][q / TN],
-                                                                                  acc[q / TN][q % TN], 0, 0, 0);
-#pragma unroll
-                    for (int r = q * RPM; r < (q + 1) * RPM && r < TM + TN; ++r) {
-                        if (r < TM) fa[0][r] = *reinterpret_cast<const bf16x8_t *>(as_ + r * 32 * BK);
-                        else fb[0][r - TM] = *reinterpret_cast<const bf16x8_t *>(bs_ + (r - TM) * 32 * BK);
-                    }
-#pragma unroll
-                    for (int l = q * LPM; l < (q + 1) * LPM && l < LD_IT; ++l) dma_one(l, ra, rw, kq, s_cur);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (kt == KT - 2) dma_bias(nxt.rb);      // (read by nobody before the next output tile starts)
-            SRM_READ_FRAGS(s_nxt, 1, 1)
-            SRM_MFMA_STEP(3)
-            SRM_INTERLEAVE()
-        }
-        if constexpr (!RING) {
-            // k tile KT-1, from slot 1: nothing to read ahead, nothing to load (slot 1 becomes the epilogue's stage)
-            SRM_READ_FRAGS(1, 2, 2)
-            SRM_MFMA_STEP(0)
-            SRM_INTERLEAVE()
-            SRM_READ_FRAGS(1, 3, 3)
-            SRM_MFMA_STEP(1)
-            SRM_INTERLEAVE()
-            SRM_MFMA_STEP(2)
-            SRM_MFMA_STEP(3)
-            SRM_WAIT_VM(0);                          // the next output tile's k tile 0 and bias have landed
-            __syncthreads();                         // ... for everyone, and slot 1 is free
+            half(h0, at(0), at(1), ra, kq, at(4));
+            SRM_WAIT_VM(LD_IT);                      // k tile T+1 has landed
+            lds_barrier();                           // ... for everyone, and T's units are free
+            half(h1, at(2), at(3), rw, kq, at(0));
+            u = u + 2 >= UNITS ? u + 2 - UNITS : u + 2;
         }
         if (probe) { clk_c2 = clock64(); clk_t2 = wall_clock64(); }
 
+        if constexpr (EPI != EPI_MIX) bias_request(nxt.n0);
+        __builtin_amdgcn_sched_barrier(0);
         // (the thread index through an opaque copy: what the epilogue derives from it is computed here, per
         // tile, and not once in front of the tile loop, where it would be held in registers across every k loop)
         int tid_e = threadIdx.x;
         asm volatile("" : "+v"(tid_e));
-        gemm_epilogue<BM, BN, WM, WN, EPI, TAct>(acc, smem_raw + kStageOff, ep, M, N, cur.m0, cur.n0, cur.bn, tid_e);
+        persist_epilogue<EPI, TAct>(acc, smem_raw + at(4), ep, M, N, cur.m0, cur.n0, cur.bn, tid_e, lds_barrier);
         if (probe) {
             __builtin_amdgcn_s_waitcnt(0);           // this wave's stores have completed
             if (tid == 0) {
@@ -247,20 +343,10 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         if (vn >= nblk) break;                       // (block-uniform)
         v = vn;
         cur = nxt;
-        if constexpr (!RING) {
-            // every wave has read its stage back (the stores themselves may still be on their way): slot 1 can
-            // take the new output tile's k tile 1
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            dma_tile(cur.ra, cur.rw, 1, 1);
-            SRM_READ_FRAGS(0, 0, 0)
-            SRM_READ_FRAGS(0, 1, 1)
-        }
+        if constexpr (EPI == EPI_MIX) bias_request(cur.n0);            // (no registers for it before)
+        lds_barrier();                               // every wave has read its stage back: the unit can be filled
+        if constexpr (REREAD) static_for<0, TM + TN>([&](auto r_) { read_one(r_, h0, at(0), at(1)); });
     }
-    SRM_WAIT_VM(0);                                  // (RING: the loads behind the last tile, of zero size)
-#undef SRM_MFMA_STEP
-#undef SRM_INTERLEAVE
+    SRM_WAIT_VM(0);                                  // (the loads behind the last tile, of zero size)
 #undef SRM_WAIT_VM
-#undef SRM_READ_FRAGS
 }

@@ -422,11 +422,11 @@ static int launch_bf16_tile(const bf16 *A, const bf16 *W, int M, int N, int K, c
     return SRM_OK;
 }
 
-// The 256x256 tile as a persistent kernel (gemm_persist.hpp): one work-group per CU, for launches of more
-// tiles than CUs.  It needs an even number >= 4 of k tiles and whole float4 groups of bias per column tile.
+// The 256x256 tile as a persistent kernel (gemm_persist.hpp), one work-group per CU.  It needs two k tiles or more and
+// whole quads of columns.
 static bool persist_ok(int64_t M, int N, int K)
 {
-    return K % 128 == 0 && K >= 256 && (N & 3) == 0 && cdiv(M, 256) * cdiv(N, 256) < (1 << 30);
+    return K % 64 == 0 && K >= 128 && (N & 3) == 0 && cdiv(M, 256) * cdiv(N, 256) < (1 << 30);
 }
 static int device_cus()
 {
@@ -441,13 +441,10 @@ static int device_cus()
     }
     return cus_of;
 }
-template <int EPI, typename TAct, bool RING = false>
+template <int EPI, typename TAct>
 static int launch_bf16_persist(const bf16 *A, const bf16 *W, int M, int N, int K, const GemmEpi &ep, hipStream_t st)
 {
-    // (the argmax epilogue that stores no logits needs no stage in LDS: the ring runs through)
-    if constexpr (EPI == EPI_ARGMAX && !RING)
-        if (!ep.out) return launch_bf16_persist<EPI, TAct, true>(A, W, M, N, K, ep, st);
-    auto kern = gemm_bf16_persist_kernel<EPI, TAct, RING>;
+    auto kern = gemm_bf16_persist_kernel<EPI, TAct>;
     static bool attr_set = false;
     if (!attr_set) {
         HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -635,10 +632,7 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     if (nparts_out) *nparts_out = ep.nparts;
     switch (tile) {
     case 0:
-        // more tiles than CUs: the persistent form, whose tiles after a CU's first start without a launch and
-        // a cold first load (measured on C4's shapes: MLP-up -1 .. -4 %, LM head -2 %)
-        if (persist_ok(M, N, K) && cdiv(M, 256) * cdiv(N, 256) > device_cus())
-            return launch_bf16_persist<EPI, TAct>(A, W, m, N, K, ep, st);
+        if (persist_ok(M, N, K)) return launch_bf16_persist<EPI, TAct>(A, W, m, N, K, ep, st);
         return launch_bf16_tile<256, 256, 2, 4, EPI, TAct>(A, W, m, N, K, ep, st);
     case 1:
         // at most one block per CU: the k loop is bound by the latency of its tile loads (a 128x128x64 tile is
@@ -655,7 +649,8 @@ static int launch_bf16(const bf16 *A, const bf16 *W, int64_t M, int N, int K, Ge
     case 7: return launch_bf16_tile<64, 64, 2, 2, EPI, TAct, 4>(A, W, m, N, K, ep, st);
     case 8: return launch_bf16_tile<64, 64, 2, 2, EPI, TAct, 8>(A, W, m, N, K, ep, st);
     case 9:
-        if (!persist_ok(M, N, K)) return fail(SRM_EINVAL, "the persistent GEMM does not take this shape");
+        // (the pin keeps to an even number >= 4 of k tiles)
+        if (!persist_ok(M, N, K) || K % 128 || K < 256) return fail(SRM_EINVAL, "the persistent GEMM does not take this shape");
         return launch_bf16_persist<EPI, TAct>(A, W, m, N, K, ep, st);
     case 10: return launch_bf16_tile<256, 256, 2, 4, EPI, TAct>(A, W, m, N, K, ep, st);
     default: break;

@@ -378,6 +378,15 @@ def test_linear_bf16_persistent_kernel(srm, shape, epi):
     _linear_case(srm, srm.SRM_BF16, M, N, K, epi, 9, seed=900 + epi)
 
 
+@pytest.mark.parametrize("shape", [(51100, 256, 128), (51200, 256, 192), (64005, 516, 192), (64005, 516, 320)])
+@pytest.mark.parametrize("epi", [0, 1, 2, 4])
+def test_linear_bf16_persistent_ring_of_five_units(srm, shape, epi):
+    """k tile counts that end the ring in each of its places: two (the fewest), three and five, with one output tile per
+    work-group and with three, the last row and column tiles ragged."""
+    M, N, K = shape
+    _linear_case(srm, srm.SRM_BF16, M, N, K, epi, None, seed=950 + epi)
+
+
 def test_linear_bf16_persistent_kernel_rejects_odd_k_tile_counts(srm):
     A = torch.zeros((512, 192), dtype=torch.bfloat16, device="cuda")
     W = torch.zeros((512, 192), dtype=torch.bfloat16, device="cuda")
