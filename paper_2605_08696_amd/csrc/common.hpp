@@ -134,3 +134,35 @@ __device__ __forceinline__ float srm_gumbel(uint32_t rowkey, uint32_t v)
     const float e = w < (1.0f / 64.0f) ? e_small : e_big;
     return -0.69314718055994530942f * __builtin_amdgcn_logf(e);
 }
+
+// ---- matrices of the launches that follow, brought into the caches by work-groups that would be idle ----------
+// A GEMM reads its weights cold: from HBM, a trip to memory of about 2 us in launches of 3 to 60 us, while HBM is idle most
+// of the step.  The LayerNorm launches in front of them leave CUs free or are bound by other traffic; they carry extra
+// work-groups that read the matrices coming up, so that the GEMMs find them in L2 (us with the weights in HBM | L2; rows x
+// columns x K: 37 x 4096 x 1024: 5.0 | 3.7, 300 x 1024 x 4096: 13.3 | 9.2).  Each XCD has an L2 of its own and work-groups
+// are dealt to the XCDs in turn: those on XCD x read the eighth of a matrix's rows that tile_of_pid gives to the tiles on
+// XCD x (all they need while at most eight row tiles; the last-level cache has the rest).
+constexpr int kPrefetchMats = 4;
+struct Prefetch {
+    const void *mat[kPrefetchMats];          // null: none
+    uint32_t bytes[kPrefetchMats];           // a multiple of 128 is read
+    int blocks;                              // extra work-groups behind the launch's own: a multiple of 8
+};
+__device__ __forceinline__ void prefetch_matrices(const Prefetch &pf, int first_block)
+{
+    const int per_xcd = pf.blocks >> 3, at = ((int)blockIdx.x - first_block) >> 3, xcd = (int)blockIdx.x & 7;
+    const uint32_t step = (uint32_t)per_xcd * blockDim.x;
+#pragma unroll
+    for (int i = 0; i < kPrefetchMats; ++i) {
+        if (!pf.mat[i]) continue;
+        const uint32_t n = pf.bytes[i] >> 7;                           // vectors per XCD
+        const u32x4_t *p = static_cast<const u32x4_t *>(pf.mat[i]) + (size_t)xcd * n;
+        for (uint32_t l = (uint32_t)at * blockDim.x + threadIdx.x; l < n; l += 4 * step) {
+            u32x4_t v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = p[min(l + j * step, n - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm volatile("" : : "v"(v[j]));
+        }
+    }
+}

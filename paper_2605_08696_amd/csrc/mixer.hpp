@@ -182,8 +182,13 @@ np_token_mix_kernel(float *x, TState *__restrict__ S, TAct *__restrict__ out, co
                     const float *__restrict__ b1, const float *__restrict__ g2, const float *__restrict__ b2,
                     const float *__restrict__ alpha, const float *__restrict__ beta,
                     const float *__restrict__ lam, int pos, const int *__restrict__ pos_dev,
-                    const int *__restrict__ pos_rows, int n_ctx, int H, int hrow, int d, int64_t rows, float eps)
+                    const int *__restrict__ pos_rows, int n_ctx, int H, int hrow, int d, int64_t rows, float eps,
+                    Prefetch pf = Prefetch{})
 {
+    if ((int64_t)blockIdx.x * 4 >= rows) {           // an extra work-group
+        prefetch_matrices(pf, (int)((rows + 3) / 4));
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;

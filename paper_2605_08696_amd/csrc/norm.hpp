@@ -29,8 +29,12 @@ ln_kernel(const float *x_in, int64_t in_stride, const int32_t *__restrict__ tok,
           const float *__restrict__ g, const float *__restrict__ b, TAct *__restrict__ out,
           int64_t rows, int d, float eps, const int32_t *__restrict__ seq_end = nullptr, int64_t base = 0,
           int64_t src_rows = 0, const float *__restrict__ part = nullptr, int nsplit = 0, int64_t part_stride = 0,
-          const TAct *__restrict__ add_act = nullptr, int *advance_ctr = nullptr)
+          const TAct *__restrict__ add_act = nullptr, int *advance_ctr = nullptr, Prefetch pf = Prefetch{})
 {
+    if ((int64_t)blockIdx.x * 4 >= rows) {           // an extra work-group
+        prefetch_matrices(pf, (int)((rows + 3) / 4));
+        return;
+    }
     if (GATHER && advance_ctr && blockIdx.x == 0 && threadIdx.x == 0) {
         advance_ctr[0] += 1;
         advance_ctr[1] += 1;
@@ -155,8 +159,12 @@ ln_kernel(const float *x_in, int64_t in_stride, const int32_t *__restrict__ tok,
 template <typename TAct, int VPL, int RPW>
 __global__ void __launch_bounds__(256)
 ln_rows_kernel(const float *__restrict__ x, const float *__restrict__ g, const float *__restrict__ b,
-               TAct *__restrict__ out, int64_t rows, int d, float eps)
+               TAct *__restrict__ out, int64_t rows, int d, float eps, Prefetch pf = Prefetch{})
 {
+    if ((int64_t)blockIdx.x * (4 * RPW) >= rows) {   // an extra work-group
+        prefetch_matrices(pf, (int)((rows + 4 * RPW - 1) / (4 * RPW)));
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW;
     if (row0 >= rows) return;

@@ -854,12 +854,46 @@ static int argmax_finalize(const float *pv, const int32_t *pi, int64_t rows, int
     return SRM_OK;
 }
 
+// The matrices that a launch's extra work-groups touch (see Prefetch): the projections of layer l, its MLP.  (None that
+// would take the larger part of the L2s, eight of 4 MB.)
+static void prefetch_add(Prefetch &pf, int at, const void *mat, size_t bytes)
+{
+    if (bytes > (size_t)20 << 20) return;
+    pf.mat[at] = mat;
+    pf.bytes[at] = (uint32_t)bytes;
+}
+static void prefetch_mix(const srm_model *m, int l, Prefetch &pf, int at)
+{
+    if (l >= m->L || m->noproj) return;
+    prefetch_add(pf, at, m->layers[l].w_in, (size_t)m->d * m->dm * m->wsize);
+    prefetch_add(pf, at + 1, m->layers[l].w_out, (size_t)m->d * m->dm * m->wsize);
+}
+static void prefetch_mlp(const srm_model *m, int l, Prefetch &pf, int at)
+{
+    prefetch_add(pf, at, m->layers[l].w_up, (size_t)m->d * m->ff * m->wsize);
+    prefetch_add(pf, at + 1, m->layers[l].w_down, (size_t)m->d * m->ff * m->wsize);
+}
+// Extra work-groups of a LayerNorm launch (256 threads each).  For bf16 models whose matrices exceed the 256 MB of the
+// last-level cache, so that a step finds them in HBM (the mid model's 74 MB: no gain, up to 2 % slower), and up to 12 288
+// rows.  Measured per decode step of the large model (us, without | with): base 24 rows 445 | 436, 200: 605 | 574, 1000:
+// 1081 | 1025, 3001: 1957 | 1890, 4000: 2208 | 2206, 8192: 4065 | 3804, 12000: 5582 | 5324, 14000: 6437 | 6441, 16384:
+// 6846 | 6985; 17 rows 425 | 432; non-projected layers, whose token mixing is one such launch, 1 row: 322 | 314, 8: 325 |
+// 306, 200: 466 | 430, 6000: 2646 | 2490, 16384: 5430 | 5540.  96 work-groups are too few for the time of the launch (30
+// rows: 511, 192: 445, 384: 437), 768 no better.  The extra work-groups as part of the GEMM launches cost as much as they
+// gave (1 row: 357 | 355).
+static int prefetch_blocks(const srm_model *m, int64_t rows, int64_t least, const Prefetch &pf)
+{
+    const size_t elems = (size_t)m->L * ((m->noproj ? 0 : (size_t)2 * m->d * m->dm) + (size_t)2 * m->d * m->ff) + (size_t)m->V * m->d;
+    if (!pf.mat[0] || m->wsize != 2 || elems * m->wsize <= (size_t)256 << 20) return 0;
+    return rows >= least && rows <= 12288 ? 256 : 0;
+}
+
 template <typename T, bool GATHER>
 static int layernorm(const srm_model *m, const float *x_in, int64_t in_stride, const int32_t *tok,
                      float *x_out, const float *g, const float *b, void *out, int64_t rows, hipStream_t st,
                      const int32_t *seq_end = nullptr, int64_t base = 0, int64_t src_rows = 0,
                      const float *part = nullptr, int nsplit = 0, const void *add_act = nullptr,
-                     int *advance_ctr = nullptr)
+                     int *advance_ctr = nullptr, Prefetch pf = Prefetch{})
 {
     const int d = m->d;
     T *o = static_cast<T *>(out);
@@ -867,19 +901,22 @@ static int layernorm(const srm_model *m, const float *x_in, int64_t in_stride, c
         // plain, many rows: several rows per wavefront
         constexpr int RPW = 2;
         const unsigned nb2 = (unsigned)cdiv(rows, 4 * RPW);
-        if (d == 256) hipLaunchKernelGGL((ln_rows_kernel<T, 1, RPW>), dim3(nb2), dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps);
-        else if (d == 512) hipLaunchKernelGGL((ln_rows_kernel<T, 2, RPW>), dim3(nb2), dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps);
-        else if (d == 768) hipLaunchKernelGGL((ln_rows_kernel<T, 3, RPW>), dim3(nb2), dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps);
-        else hipLaunchKernelGGL((ln_rows_kernel<T, 4, RPW>), dim3(nb2), dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps);
+        pf.blocks = prefetch_blocks(m, rows, 24, pf);
+        const dim3 grid(nb2 + pf.blocks);
+        if (d == 256) hipLaunchKernelGGL((ln_rows_kernel<T, 1, RPW>), grid, dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps, pf);
+        else if (d == 512) hipLaunchKernelGGL((ln_rows_kernel<T, 2, RPW>), grid, dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps, pf);
+        else if (d == 768) hipLaunchKernelGGL((ln_rows_kernel<T, 3, RPW>), grid, dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps, pf);
+        else hipLaunchKernelGGL((ln_rows_kernel<T, 4, RPW>), grid, dim3(256), 0, st, x_in, g, b, o, rows, d, m->cfg.ln_eps, pf);
         HIP_TRY(hipGetLastError());
         return SRM_OK;
     }
     const unsigned nb = (unsigned)cdiv(rows, 4);
+    pf.blocks = prefetch_blocks(m, rows, 24, pf);
     const T *emb = static_cast<const T *>(m->embed);
 #define LN_CASE(VPL)                                                                                     \
-    hipLaunchKernelGGL((ln_kernel<T, T, VPL, GATHER>), dim3(nb), dim3(256), 0, st, x_in, in_stride, tok, \
+    hipLaunchKernelGGL((ln_kernel<T, T, VPL, GATHER>), dim3(nb + pf.blocks), dim3(256), 0, st, x_in, in_stride, tok, \
                        emb, m->V, x_out, g, b, o, rows, d, m->cfg.ln_eps, seq_end, base, src_rows, part, nsplit,       \
-                       (int64_t)rows * d, static_cast<const T *>(add_act), advance_ctr)
+                       (int64_t)rows * d, static_cast<const T *>(add_act), advance_ctr, pf)
     if (d <= 256) LN_CASE(1);
     else if (d <= 512) LN_CASE(2);
     else if (d <= 1024) LN_CASE(4);
@@ -1032,12 +1069,16 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     const int d = m->d, dm = m->dm, ff = m->ff;
     const LnArgs ln1 = lnf && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
     const LnArgs ln2 = lnf ? LnArgs{w.x, y.ln2_g, y.ln2_b, m->cfg.ln_eps} : LnArgs();
+    Prefetch pf_mlp{}, pf_next{};            // this layer's MLP, the next layer's projections
+    prefetch_mlp(m, l, pf_mlp, 0);
+    prefetch_mix(m, l + 1, pf_next, 0);
     if constexpr (sizeof(T) == 2) {
         if (one_mix) {
+            prefetch_mix(m, l + 1, pf_mlp, 2);
             // token mixing in one kernel, which normalises w.x itself; LayerNorm2 adds its slabs to w.x
             SRM_TRY(token_mix(m, l, TokMixCall{w.x, np_state, fuse_pos, w.part}, rows, st));
             SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, w.part,
-                                         d / kTokMixCols)));
+                                         d / kTokMixCols, nullptr, nullptr, pf_mlp)));
             SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                          MixArgs(), call_rows)));
             SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr,
@@ -1049,11 +1090,12 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     if (m->noproj && np_state) {
         // non-projected layer, decode: LayerNorm1, state update, residual add and LayerNorm2 in one kernel
         const unsigned nb = (unsigned)cdiv(rows, 4);
+        pf_mlp.blocks = prefetch_blocks(m, rows, 1, pf_mlp);
 #define NP_LAUNCH(VPL, TS)                                                                                    \
-    hipLaunchKernelGGL((np_token_mix_kernel<T, VPL, TS>), dim3(nb), dim3(256), 0, st, w.x,                     \
+    hipLaunchKernelGGL((np_token_mix_kernel<T, VPL, TS>), dim3(nb + pf_mlp.blocks), dim3(256), 0, st, w.x,                     \
                        static_cast<TS *>(np_state), static_cast<T *>(w.a), y.ln1_g, y.ln1_b, y.ln2_g, y.ln2_b, \
                        y.alpha, y.beta, y.lam, fuse_pos.pos, fuse_pos.pos_dev, fuse_pos.pos_rows, m->cfg.n_ctx, \
-                       m->Hs, m->hrow, d, rows, m->cfg.ln_eps)
+                       m->Hs, m->hrow, d, rows, m->cfg.ln_eps, pf_mlp)
 #define NP_CASE(VPL)                                                                                          \
     do {                                                                                                      \
         if (m->shalf) NP_LAUNCH(VPL, f16);                                                                    \
@@ -1071,7 +1113,7 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
         // non-projected layer: mixer on the LayerNorm output, its result added to x by the LayerNorm kernel
         SRM_TRY(mix(l));
         SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, nullptr,
-                                     0, w.mx)));
+                                     0, w.mx, nullptr, pf_mlp)));
     } else if (fuse_state) {
         // few rows: the state update rides in the in-projection's epilogue (one kernel less per layer)
         const MixArgs mx{fuse_state, y.alpha, y.beta, y.lam, m->cfg.n_ctx, m->hrow, dm / m->Hs, m->shalf ? 1 : 0};
@@ -1085,7 +1127,8 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     if (!m->noproj) {
         SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                       MixArgs(), call_rows)));
-        if (!lnf) SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, y.ln2_g, y.ln2_b, w.a, rows, st)));
+        if (!lnf) SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0,
+                                               nullptr, 0, nullptr, nullptr, pf_mlp)));
     }
     SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                  MixArgs(), call_rows, ln2)));
@@ -1095,7 +1138,8 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     if (norm_next && !(m->noproj && np_state && l + 1 < m->L)) {   // the fused kernel does its own LayerNorm1
         const float *g = l + 1 < m->L ? m->layers[l + 1].ln1_g : m->lnf_g;
         const float *b = l + 1 < m->L ? m->layers[l + 1].ln1_b : m->lnf_b;
-        SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, g, b, w.a, rows, st)));
+        SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, g, b, w.a, rows, st, nullptr, 0, 0, nullptr, 0, nullptr,
+                                     nullptr, pf_next)));
     }
     return SRM_OK;
 }
@@ -1144,8 +1188,10 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
         return static_cast<void *>(static_cast<unsigned char *>(layer_state(m, a.state, l, a.B)) +
                                    (size_t)b0 * dm * m->ssize);
     };
+    Prefetch pf{};
+    prefetch_mix(m, 0, pf, 0);
     SRM_TRY((layernorm<T, true>(m, nullptr, 0, a.tok_in + b0, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a, nb,
-                                st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr)));
+                                st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr, pf)));
     auto mix = [&](int l) {
         if (!pos_rows) return state_update<T>(m, l, a.pos, nb, w.u, slab(l), w.mx, st, a.pos_dev);
         const LayerDev &y = m->layers[l];

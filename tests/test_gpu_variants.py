@@ -552,3 +552,30 @@ def test_variants_at_the_large_configuration_shape(srm, orc_mod, variant):
     s_got = st[:, rows].permute(1, 0, 2).cpu().numpy()
     assert np.abs(s_got - ref["state"]).max() <= 2e-2 * np.abs(ref["state"]).max()
     assert bool(torch.isfinite(st).all()) and bool(((out >= 0) & (out < cfg.vocab)).all())
+
+
+@pytest.mark.parametrize("use_projections", [True, False])
+def test_matrices_read_ahead_change_no_bits(srm, use_projections, monkeypatch):
+    """A bf16 model whose matrices exceed the last-level cache (its head alone): LayerNorm launches carry extra
+    work-groups that read the matrices of the next launches, from 24 rows on where the layers have projections.  The rows
+    of a step are those of the same step over 16 rows (the GEMMs of both sum alike)."""
+    cfg = srm_synth.tiny_config(vocab=530000, d_model=256, n_layers=2, n_heads=4, n_ctx=16, weight_dtype="bf16",
+                                use_projections=use_projections, seed=17)
+    rng = np.random.default_rng(5)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    monkeypatch.setenv("SRM_TOKEN_MIX", "0")
+    monkeypatch.setenv("SRM_LN_ON_LOAD", "0")
+    n = 16
+    for B in (23, 24, 130):
+        print(f"read ahead: projections {use_projections}, {B} rows", flush=True)
+        tok = to_dev(rng.integers(0, cfg.vocab, B).astype(np.int32))
+        state = to_dev(rng.standard_normal((cfg.n_layers, B, cfg.d_model)).astype(np.float32))
+        out, hidden = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, cfg.d_model), device="cuda")
+        st = state.clone()
+        model.decode_step(B, 7, tok, st, out, hidden=hidden, workspace=model.new_workspace(B))
+        out2, hidden2 = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty((n, cfg.d_model), device="cuda")
+        for b0 in (0, B - n):
+            st2 = state[:, b0:b0 + n].contiguous()
+            model.decode_step(n, 7, tok[b0:b0 + n].contiguous(), st2, out2, hidden=hidden2, workspace=model.new_workspace(n))
+            assert torch.equal(hidden[b0:b0 + n], hidden2) and torch.equal(st[:, b0:b0 + n], st2)
+            assert torch.equal(out[b0:b0 + n], out2)
