@@ -462,12 +462,12 @@ static int launch_bf16_persist(const bf16 *A, const bf16 *W, int M, int N, int K
 // Few rows: the streaming GEMV (gemv_rows_kernel), 16 * CPG columns per block.
 constexpr int kGemvMB = 8;                 // rows per pass over W
 constexpr size_t kGemvMaxLds = 128 * 1024;
-template <typename TW, typename TAct, int EPI, int CPG>
+template <typename TW, typename TAct, int EPI, int CPG, bool LNA = false>
 static int launch_gemv_rows(const TAct *A, const TW *W, int M, int N, int K, GemmEpi ep, hipStream_t st,
                             int *nparts_out)
 {
     const size_t lds = (size_t)kGemvMB * K * sizeof(float);
-    auto kern = gemv_rows_kernel<TW, TAct, EPI, kGemvMB, CPG>;
+    auto kern = gemv_rows_kernel<TW, TAct, EPI, kGemvMB, CPG, LNA>;
     static bool attr_set = false;
     if (!attr_set) {
         HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -802,7 +802,7 @@ struct MixArgs {           // EPI_MIX: state slab of the layer and its coefficie
     int n_ctx = 0, hrow = 0, dh = 0, state_half = 0;
 };
 
-struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (at most kLnaRows rows)
+struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (see lna_ok)
     const float *x = nullptr, *g = nullptr, *b = nullptr;
     float eps = 0.0f;
 };
@@ -821,13 +821,19 @@ static int linear(const void *A, const void *W, const float *bias, int64_t M, in
     if (ln.x) {
         if constexpr (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_MIX) {
             if (M <= 0 || N <= 0 || !lna_ok<T>(M, N, K))
-                return fail(SRM_EINVAL, "linear: LayerNorm-on-load needs at most %d rows, K <= 1024, N %% 4 == 0", kLnaRows);
+                return fail(SRM_EINVAL, "linear: LayerNorm-on-load does not take %lld x %d x %d", (long long)M, N, K);
             ep.ln_x = ln.x; ep.ln_g = ln.g; ep.ln_b = ln.b; ep.ln_eps = ln.eps;
             const T *w = static_cast<const T *>(W);  // (in A's place: not read)
             if constexpr (sizeof(T) == 2) return launch_slices_tile<EPI, 1, 1, 4, true>(w, w, (int)M, N, K, ep, st);
             else return launch_f32_slices<EPI, 16, 4, f32gemm::kFine, true>(w, w, (int)M, N, K, ep, st);
+        } else if constexpr (EPI == EPI_ARGMAX && sizeof(T) == 4) {
+            if (M <= 0 || N <= 0 || M > kLnaRows || K > 1024 || !gemv_rows_ok<T>(M, K))
+                return fail(SRM_EINVAL, "linear: LayerNorm-on-load needs at most %d rows, K <= 1024", kLnaRows);
+            ep.ln_x = ln.x; ep.ln_g = ln.g; ep.ln_b = ln.b; ep.ln_eps = ln.eps;
+            const T *w = static_cast<const T *>(W);  // (in A's place: not read)
+            return launch_gemv_rows<T, T, EPI, 4, true>(w, w, (int)M, N, K, ep, st, nparts_out);
         } else {
-            return fail(SRM_EINVAL, "linear: LayerNorm-on-load exists for store / GELU / mixer epilogues only");
+            return fail(SRM_EINVAL, "linear: this epilogue has no LayerNorm-on-load");
         }
     }
     if constexpr (sizeof(T) == 2)
@@ -1057,7 +1063,7 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
 // norm_next, w.a leaves holding the next layer's LayerNorm1(x), or the final
 // LayerNorm after the last layer.
 // With lnf (decode of a handful of rows, see ln_on_load): no LayerNorm kernels between the GEMMs.  From layer 1 on w.a
-// is not used: the in- and up-projection normalise the rows of w.x themselves.  Layer 0 enters with w.a from the
+// is not used: the in- and up-projection (and the fp32 LM head) normalise the rows of w.x themselves.  Layer 0 enters with w.a from the
 // embedding kernel as usual.  With one_mix (see token_mix_one_kernel) w.a on entry is not used either.
 // call_rows: the rows of the whole call (rows are one of its passes; see slices_ok).
 template <typename T, typename MIX>
@@ -1149,11 +1155,11 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
 template <typename T>
 static int head_argmax(const srm_model *m, const Workspace &w, const void *a, int64_t M, int64_t call_rows, float *logits,
                        int32_t *d_tok, int64_t row0, int rep, hipStream_t st, TokenStore ts = TokenStore(),
-                       Sampling sm = Sampling(), FinalizeRagged rg = FinalizeRagged{})
+                       Sampling sm = Sampling(), FinalizeRagged rg = FinalizeRagged{}, LnArgs ln = LnArgs())
 {
     int nparts = 0;
     SRM_TRY((linear<EPI_ARGMAX, T>(a, m->head, nullptr, M, m->V, m->d, logits, st, w.pv, w.pi, head_min_bn(m),
-                                   &nparts, sm, MixArgs(), call_rows)));
+                                   &nparts, sm, MixArgs(), call_rows, ln)));
     return argmax_finalize(w.pv, w.pi, M, nparts, d_tok, row0, rep, m->V, st, ts, rg);
 }
 
@@ -1215,8 +1221,10 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     const int64_t call_rows = sizeof(T) == 4 ? a.B : nb;
     const bool lnf = ln_on_load(m, call_rows);
     const bool tm = token_mix_one_kernel(m, call_rows);
+    // ... and the LM head the last one, where it is the fp32 GEMV (bf16: one launch of many, for 64 rows of a tile)
+    const bool head_norm = lnf && sizeof(T) == 4;
     for (int l = 0; l < m->L; ++l)
-        SRM_TRY((block<T>(m, l, w, nb, call_rows, st, mix, true, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
+        SRM_TRY((block<T>(m, l, w, nb, call_rows, st, mix, !head_norm, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
     if (a.hidden)
         HIP_TRY(hipMemcpyAsync(a.hidden + (size_t)b0 * d, w.x, (size_t)nb * d * 4, hipMemcpyDeviceToDevice, st));
     const Sampling sm{a.temperature, a.seed, a.pos, a.pos_dev, pos_rows, a.top_p, (uint32_t)b0, a.eos_plus1};
@@ -1230,7 +1238,8 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     }
     if (topp) rg.zero_counter = w.slow;
     float *lg = a.logits ? a.logits + (size_t)b0 * m->V : nullptr;
-    SRM_TRY((head_argmax<T>(m, w, w.a, nb, call_rows, lg, a.tok_out, b0, 1, st, a.ts, sm, rg)));
+    SRM_TRY((head_argmax<T>(m, w, w.a, nb, call_rows, lg, a.tok_out, b0, 1, st, a.ts, sm, rg,
+                            head_norm ? LnArgs{w.x, m->lnf_g, m->lnf_b, m->cfg.ln_eps} : LnArgs())));
     if (topp)
         SRM_TRY(nucleus(lg, nb, m->V, sm, a.tok_out + b0, a.ts.store ? a.ts.store + b0 : nullptr, a.ts.step_dev,
                         a.ts.stride, (pos_rows && a.advance) ? pos_rows : nullptr, w.slow, st));
