@@ -24,7 +24,7 @@ constexpr int slices_wave_lds()
     return ring > part ? ring : part;
 }
 
-// LNA (M <= kLnaRows, one row tile, K <= 1024): the A operand is not read from memory but made by the work-group itself,
+// LNA (tiles of 16 rows, K <= 1024): the A operand is not read from memory but made by the work-group itself,
 // A = LayerNorm(ep.ln_x rows) in the arithmetic of ln_kernel, written once as a panel [K / 64][16 rows][64] behind the
 // rings, in the layout of a ring's A tile, while the first W loads travel.  Every column block normalises the few rows
 // again, which is cheaper than the LayerNorm launch it replaces.  Panel rows >= M feed accumulator rows that no
@@ -112,10 +112,10 @@ gemm_bf16_slices_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, 
         if (in[q]) eq[q] = epi_quad_request<EPI>(ep, row[q], col[q]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (LNA) layernorm_panel<NW>(ep, M, K, wave, lane, [&](int r, int c, float4 o) {
+    if constexpr (LNA) layernorm_panel<NW>(ep, min(BM, M - m0), K, wave, lane, [&](int r, int c, float4 o) {
         store4(reinterpret_cast<bf16 *>(smem_raw + NW * WAVE_LDS + (c >> 6) * 2048 + r * 128 +
                                         ((((c & 63) >> 3) ^ swz_of_row(r)) << 4)) + (c & 7), o);
-    });
+    }, m0);
 
     f32x4_t acc[RT][CT];
 #pragma unroll

@@ -536,6 +536,11 @@ static int launch_slices(const bf16 *A, const bf16 *W, int M, int N, int K, cons
 // whether the work-groups of a GEMM can make the LayerNorm of their rows themselves (whole k tiles of 128 bytes)
 template <typename T>
 static bool lna_ok(int64_t M, int N, int K) { return M <= kLnaRows && K <= 1024 && K % (128 / (int)sizeof(T)) == 0 && N % 4 == 0; }
+// ... or, bf16, those of several row tiles of 16 that are one round of the chip with the columns
+static bool lna_tiles_ok(int64_t M, int N, int K)
+{
+    return lna_ok<bf16>(1, N, K) && cdiv(M, kLnaRows) * cdiv(N, 16) <= device_cus();
+}
 
 // The 64x64 tile with few blocks on the chip: its k loop is bound by the latency of the tile loads, so
 // the LDS ring is deepened as far as the blocks per CU allow (8 stages = 128 KB: one block per CU;
@@ -802,7 +807,7 @@ struct MixArgs {           // EPI_MIX: state slab of the layer and its coefficie
     int n_ctx = 0, hrow = 0, dh = 0, state_half = 0;
 };
 
-struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (see lna_ok)
+struct LnArgs {            // A = LayerNorm(x) made by the GEMM itself (see lna_ok, lna_tiles_ok)
     const float *x = nullptr, *g = nullptr, *b = nullptr;
     float eps = 0.0f;
 };
@@ -820,7 +825,7 @@ static int linear(const void *A, const void *W, const float *bias, int64_t M, in
     ep.clk = g_clock_probe; ep.clk_blocks = g_clock_blocks;
     if (ln.x) {
         if constexpr (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_MIX) {
-            if (M <= 0 || N <= 0 || !lna_ok<T>(M, N, K))
+            if (M <= 0 || N <= 0 || !(lna_ok<T>(M, N, K) || (sizeof(T) == 2 && lna_tiles_ok(M, N, K))))
                 return fail(SRM_EINVAL, "linear: LayerNorm-on-load does not take %lld x %d x %d", (long long)M, N, K);
             ep.ln_x = ln.x; ep.ln_g = ln.g; ep.ln_b = ln.b; ep.ln_eps = ln.eps;
             const T *w = static_cast<const T *>(W);  // (in A's place: not read)
@@ -1015,6 +1020,16 @@ static bool token_mix_one_kernel(const srm_model *m, int64_t rows)
     if (e && e[0] == '1') return true;
     return rows >= kTokMixMinRows && cdiv(rows, 16) * (m->d / kTokMixCols) <= device_cus();
 }
+// Some dozens of rows of a bf16 model above that: the in-projection still normalises its rows, while tiles of 16 x 16 are one
+// round of the chip (the up-projection has more of them and leaves that to a LayerNorm launch).  Decode steps of the large
+// model (us, without | with): 17 rows 422 | 407, 24 with combined heads 443 | 440, 37: 445 | 443, 50: 446 | 443, 64 with a
+// state in 16 bits 452 | 446.
+static bool in_projection_normalises(const srm_model *m, int64_t rows)
+{
+    if (m->noproj || m->wsize != 2 || !lna_tiles_ok(rows, m->dm, m->d)) return false;
+    const char *e = getenv("SRM_LN_ON_LOAD");
+    return !(e && e[0] == '0');
+}
 struct TokMixCall {
     const float *x;
     void *state;
@@ -1064,20 +1079,21 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
 // LayerNorm after the last layer.
 // With lnf (decode of a handful of rows, see ln_on_load): no LayerNorm kernels between the GEMMs.  From layer 1 on w.a
 // is not used: the in- and up-projection (and the fp32 LM head) normalise the rows of w.x themselves.  Layer 0 enters with w.a from the
-// embedding kernel as usual.  With one_mix (see token_mix_one_kernel) w.a on entry is not used either.
+// embedding kernel as usual.  With ln1f (see in_projection_normalises) that holds for the in-projection alone.  With one_mix (see token_mix_one_kernel) w.a on entry is not used either.
 // call_rows: the rows of the whole call (rows are one of its passes; see slices_ok).
 template <typename T, typename MIX>
 static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, int64_t call_rows, hipStream_t st, MIX &&mix,
                  bool norm_next, void *fuse_state = nullptr, Sampling fuse_pos = Sampling(),
-                 void *np_state = nullptr, bool lnf = false, bool one_mix = false)
+                 void *np_state = nullptr, bool lnf = false, bool one_mix = false, bool ln1f = false)
 {
     const LayerDev &y = m->layers[l];
     const int d = m->d, dm = m->dm, ff = m->ff;
-    const LnArgs ln1 = lnf && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
+    const LnArgs ln1 = (lnf || ln1f) && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
     const LnArgs ln2 = lnf ? LnArgs{w.x, y.ln2_g, y.ln2_b, m->cfg.ln_eps} : LnArgs();
     Prefetch pf_mlp{}, pf_next{};            // this layer's MLP, the next layer's projections
     prefetch_mlp(m, l, pf_mlp, 0);
     prefetch_mix(m, l + 1, pf_next, 0);
+    if (ln1f) prefetch_mix(m, l + 1, pf_mlp, 2);
     if constexpr (sizeof(T) == 2) {
         if (one_mix) {
             prefetch_mix(m, l + 1, pf_mlp, 2);
@@ -1140,7 +1156,7 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
                                  MixArgs(), call_rows, ln2)));
     SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                   MixArgs(), call_rows)));
-    if (lnf && l + 1 < m->L) return SRM_OK;                        // the next layer's in-projection normalises
+    if ((lnf || ln1f) && l + 1 < m->L) return SRM_OK;              // the next layer's in-projection normalises
     if (norm_next && !(m->noproj && np_state && l + 1 < m->L)) {   // the fused kernel does its own LayerNorm1
         const float *g = l + 1 < m->L ? m->layers[l + 1].ln1_g : m->lnf_g;
         const float *b = l + 1 < m->L ? m->layers[l + 1].ln1_b : m->lnf_b;
@@ -1221,10 +1237,12 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     const int64_t call_rows = sizeof(T) == 4 ? a.B : nb;
     const bool lnf = ln_on_load(m, call_rows);
     const bool tm = token_mix_one_kernel(m, call_rows);
+    const bool ln1f = !lnf && !tm && in_projection_normalises(m, call_rows);
     // ... and the LM head the last one, where it is the fp32 GEMV (bf16: one launch of many, for 64 rows of a tile)
     const bool head_norm = lnf && sizeof(T) == 4;
     for (int l = 0; l < m->L; ++l)
-        SRM_TRY((block<T>(m, l, w, nb, call_rows, st, mix, !head_norm, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm)));
+        SRM_TRY((block<T>(m, l, w, nb, call_rows, st, mix, !head_norm, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm,
+                          ln1f)));
     if (a.hidden)
         HIP_TRY(hipMemcpyAsync(a.hidden + (size_t)b0 * d, w.x, (size_t)nb * d * 4, hipMemcpyDeviceToDevice, st));
     const Sampling sm{a.temperature, a.seed, a.pos, a.pos_dev, pos_rows, a.top_p, (uint32_t)b0, a.eos_plus1};

@@ -254,6 +254,13 @@ def test_layernorm_made_by_the_gemm_up_to_its_last_row_count(srm, orc_mod, d, B,
     test_layernorm_made_by_the_consuming_gemm_equals_the_separate_kernel(srm, orc_mod, d, B, True, monkeypatch)
 
 
+@pytest.mark.parametrize("d,B", [(1024, 17), (1024, 64), (1024, 65), (768, 50), (320, 33)])
+def test_layernorm_made_by_the_in_projection_of_dozens_of_rows(srm, orc_mod, d, B, monkeypatch):
+    """The same comparison where only the in-projection normalises, in several row tiles: from seventeen rows to the
+    last that fit one round of the chip (64 of 1024 columns), and the first that do not."""
+    _ln_on_load_case(srm, orc_mod, d, B, True, monkeypatch)
+
+
 @pytest.mark.parametrize("d,B,layers", [(256, 9, 3), (256, 100, 3), (512, 33, 2), (512, 700, 2)])
 @pytest.mark.parametrize("half_state", [False, True])
 def test_token_mixing_in_one_kernel_matches_the_separate_kernels(srm, orc_mod, d, B, layers, half_state, monkeypatch):
