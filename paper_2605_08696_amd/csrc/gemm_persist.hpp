@@ -121,15 +121,19 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                 const uint32_t key = row_key(wrow0 + t * 16 + lr);
                 float bv = -INFINITY;
                 int brel = 0;
+                // (opaque: what is derived from the columns is formed for each row, not held in registers across all rows,
+                // of which the noise had none left: 300 x 32000 x 512 with a temperature 2.7 us shorter)
+                int col0 = wcol0 + 4 * lq;
+                asm volatile("" : "+v"(col0));
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int col = wcol0 + 4 * lq + j * 16 + r;
+                        const int col = col0 + j * 16 + r;
                         const float v = score(acc[t][j][r], key, col);
                         if ((!decltype(edge_c)::value || col < N) && v > bv) { bv = v; brel = j * 16 + r; }
                     }
-                const int bi = bv == -INFINITY ? 0x7fffffff : wcol0 + 4 * lq + brel;
+                const int bi = bv == -INFINITY ? 0x7fffffff : col0 + brel;
                 red[(wm * WTM + t * 16 + lr) * 16 + ((wn * 4 + lq) ^ lr)] = make_uint2(__float_as_uint(bv), (unsigned)bi);
             });
         };
