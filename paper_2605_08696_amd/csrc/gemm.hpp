@@ -143,8 +143,8 @@ __device__ __forceinline__ void epi_store(const GemmEpi &ep, int64_t row, int co
 //      from registers instead cost ~30% of the main loop;
 //  (3) the product is formed transposed (W fragment as the first MFMA operand),
 //      so a lane holds four consecutive output columns of ONE row per register
-//      quad: the LM-head argmax reduces in-lane and needs two cross-lane
-//      exchanges, and the epilogue passes 32-row slices through a wave-private
+//      quad: the LM-head argmax reduces in-lane and then over a few entries per
+//      row in LDS, and the epilogue passes 32-row slices through a wave-private
 //      LDS stage with 16-byte writes and reads, so that global stores and the
 //      residual read-modify-write are 16-byte vectors over whole cache lines.
 // LDS chunk swizzle: 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7);
@@ -331,9 +331,89 @@ __device__ __forceinline__ void epi_store1p(const GemmEpi &ep, int64_t row, int 
     }
 }
 
+// The LM head's choice, one row at a time: the best of the columns col0 + j*16 + r that this lane holds of row `row`
+// (a[j][r]; strict > in ascending order keeps the lowest column), as its value and the code 4j + r.  -inf: none.
+struct RowBest {
+    float val;
+    int code;
+};
+// What is compared: the logits of a tile whose columns all exist, of one at the edge of the matrix, or with noise.  Chosen
+// once in front of all rows (with_choice): one row's code behind the other's, no jumps over the forms not taken.
+enum Choice { CHOICE_PLAIN, CHOICE_EDGE, CHOICE_NOISE };
+template <typename F>
+__device__ __forceinline__ void with_choice(const GemmEpi &ep, bool edge, F &&f)
+{
+    if (ep.temp > 0.0f) f(std::integral_constant<int, CHOICE_NOISE>{});
+    else if (edge) f(std::integral_constant<int, CHOICE_EDGE>{});
+    else f(std::integral_constant<int, CHOICE_PLAIN>{});
+}
+template <int CHOICE, int TN>
+__device__ __forceinline__ RowBest row_best(const GemmEpi &ep, const f32x4_t (&a)[TN], uint32_t key, int N, int col0)
+{
+    RowBest b{-INFINITY, 0};
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int col = col0 + j * 16 + r;
+            float v = a[j][r];
+            if constexpr (CHOICE == CHOICE_NOISE) v += ep.temp * srm_gumbel(key, (uint32_t)col);
+            if ((CHOICE == CHOICE_PLAIN || col < N) && v > b.val) { b.val = v; b.code = 4 * j + r; }
+        }
+    return b;
+}
+// The keys of the noise of rows row + 16 t, all their positions requested together.
+template <int T>
+__device__ __forceinline__ void noise_keys(const GemmEpi &ep, int row, int M, uint32_t (&key)[T])
+{
+    uint32_t pos[T];
+    if (ep.pos_rows) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) pos[t] = (uint32_t)ep.pos_rows[min(row + 16 * t, M - 1)];
+    } else {
+        const uint32_t p = epi_shared_pos(ep);
+#pragma unroll
+        for (int t = 0; t < T; ++t) pos[t] = p;
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) key[t] = srm_rowkey(ep.seed, pos[t], (uint32_t)(row + 16 * t) + ep.row_base);
+}
+// ... and as a partial winner: value and column, which the lanes of a row exchange through LDS.  (Exchanged between lanes
+// instead, the round trips through the LDS crossbar add up: 8.7 us per 256x256 tile.)
+__device__ __forceinline__ uint2 row_best_entry(RowBest b, int col0)
+{
+    return make_uint2(__float_as_uint(b.val), b.val == -INFINITY ? 0x7fffffffu : (unsigned)(col0 + (b.code >> 2) * 16 + (b.code & 3)));
+}
+// The best of `n` entries (even) at p, 16-byte aligned, joined to bv, bi.
+template <int n>
+__device__ __forceinline__ void best_entry(const uint2 *p, float &bv, int &bi)
+{
+#pragma unroll
+    for (int e = 0; e < n / 2; ++e) {
+        const uint4 x = reinterpret_cast<const uint4 *>(p)[e];
+        if (arg_better(__uint_as_float(x.x), (int)x.y, bv, bi)) { bv = __uint_as_float(x.x); bi = (int)x.y; }
+        if (arg_better(__uint_as_float(x.z), (int)x.w, bv, bi)) { bv = __uint_as_float(x.z); bi = (int)x.w; }
+    }
+}
+// ... over the `lanes` lanes (a power of two) that share a row
+template <int lanes>
+__device__ __forceinline__ void best_of_lanes(float &bv, int &bi)
+{
+#pragma unroll
+    for (int x = 1; x < lanes; x *= 2) {
+        const float ov = __shfl_xor(bv, x, kWave);
+        const int oi = __shfl_xor(bi, x, kWave);
+        if (arg_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    }
+}
+
 // Epilogue shared by the bf16 kernels.  Accumulator register r of lane (lq, lr)
-// of tile (i, j) is output row i*16 + lr, column j*16 + 4*lq + r of the wave tile.  smem_raw: the block's LDS, free for reuse (all tile reads and
-// loads have completed and a barrier has been passed); lds_bytes its size.
+// of tile (i, j) is output row i*16 + lr, column j*16 + 4*lq + r of the wave tile.
+// smem_raw: the block's LDS, free for reuse (all tile reads and loads have
+// completed and a barrier has been passed).  The argmax's winners go to LDS row by
+// row, in front of the row's stores: held in registers for all rows and exchanged
+// between lanes, they sent 80 registers to scratch memory (16384 x 32001 x 512:
+// 599 us | 456, with the logits 1447 | 1283; 300 x 32000 x 64: 16.0 | 10.2).
 template <int BM, int BN, int WM, int WN, int EPI, typename TAct>
 __device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / WN / 16], unsigned char *smem_raw,
                                               const GemmEpi &ep, int M, int N, int m0, int n0, int bn,
@@ -347,8 +427,8 @@ __device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / 
     const int wm = wave / WN, wn = wave % WN;
     const int lr = lane & 15, lq = lane >> 4;
     float *stage = reinterpret_cast<float *>(smem_raw) + wave * 32 * STG;        // wave-private [32][STG]
-    float *red_val = reinterpret_cast<float *>(smem_raw) + NW * 32 * STG;        // [BM][WN]
-    int *red_idx = reinterpret_cast<int *>(red_val + BM * WN);                   // [BM][WN]
+    constexpr int ENT = WN * 4;                      // partial winners of a row, entry e of row r at e ^ r
+    uint2 *red = reinterpret_cast<uint2 *>(smem_raw + NW * 32 * STG * 4);        // [BM][ENT]
     const bool vec_ok = (N & 3) == 0;
     constexpr int LPR = WTN / 4;                      // lanes per staged row
     constexpr int RPI = 64 / LPR;                     // rows per read instruction
@@ -360,57 +440,21 @@ __device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / 
     const bool cols_inside = vec_ok && n0 + BN <= N;                   // block-uniform
     const bool rows_inside = m0 + BM <= M;                             // block-uniform
 
-    if constexpr (EPI == EPI_ARGMAX) {
-        // in-lane over this lane's TN*4 columns of a row in ascending order (strict > keeps the lowest
-        // index), then two exchanges with the lanes holding the row's other columns, all rows' at once
-        // (row by row their round trips add up)
-        float bv[2 * SL];
-        int bi[2 * SL];
-        auto rows_best = [&](auto &&row_key, auto &&score, auto edge_c) {
-            static_for<0, 2 * SL>([&](auto t_) {
-                constexpr int t = decltype(t_)::value;
-                const uint32_t key = row_key(m0 + wm * WTM + t * 16 + lr);
-                float best = -INFINITY;
-                int brel = 0;
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int col = wcol0 + 4 * lq + j * 16 + r;
-                        const float v = score(acc[t][j][r], key, col);
-                        if ((!decltype(edge_c)::value || col < N) && v > best) { best = v; brel = j * 16 + r; }
-                    }
-                bv[t] = best;
-                bi[t] = best == -INFINITY ? 0x7fffffff : wcol0 + 4 * lq + brel;
-            });
-        };
-        if (ep.temp > 0.0f)
-            rows_best([&](int row) { return srm_rowkey(ep.seed, epi_pos(ep, row, M), (uint32_t)row + ep.row_base); },
-                      [&](float v, uint32_t key, int col) { return v + ep.temp * srm_gumbel(key, (uint32_t)col); }, std::true_type{});
-        else if (n_edge)
-            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::true_type{});
-        else
-            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::false_type{});
-        static_for<0, 2>([&](auto x_) {
-            static_for<0, 2 * SL>([&](auto t_) {
-                constexpr int t = decltype(t_)::value;
-                const float ov = __shfl_xor(bv[t], 16 << decltype(x_)::value, kWave);
-                const int oi = __shfl_xor(bi[t], 16 << decltype(x_)::value, kWave);
-                if (arg_better(ov, oi, bv[t], bi[t])) { bv[t] = ov; bi[t] = oi; }
-            });
-        });
-        static_for<0, 2 * SL>([&](auto t_) {
-            constexpr int t = decltype(t_)::value;
-            if (lq == 0) {
-                red_val[(wm * WTM + t * 16 + lr) * WN + wn] = bv[t];
-                red_idx[(wm * WTM + t * 16 + lr) * WN + wn] = bi[t];
-            }
-        });
-    }
     // (a compile-time loop: with the largest epilogue the compiler kept `#pragma unroll` rolled, which indexes
     // the accumulators with a variable and so moves all of them, main loop included, to scratch memory)
-    static_for<0, SL>([&](auto ic_) {
+    auto slices = [&](auto choice_c) { static_for<0, SL>([&](auto ic_) {
         constexpr int i = decltype(ic_)::value;
+        if constexpr (EPI == EPI_ARGMAX) {
+            // (the winners in front of the slice's stores, which travel meanwhile)
+            uint32_t key[2] = {0, 0};
+            if constexpr (decltype(choice_c)::value == CHOICE_NOISE) noise_keys(ep, m0 + wm * WTM + i * 32 + lr, M, key);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int wrow = wm * WTM + i * 32 + h * 16;
+                const RowBest b = row_best<decltype(choice_c)::value>(ep, acc[2 * i + h], key[h], N, wcol0 + 4 * lq);
+                red[(wrow + lr) * ENT + ((wn * 4 + lq) ^ (lr & (ENT - 1)))] = row_best_entry(b, wcol0 + 4 * lq);
+            }
+        }
         if (want_store) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -525,22 +569,21 @@ __device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / 
                 }
             }
         }
-    });
+    }); };
+    if constexpr (EPI == EPI_ARGMAX) with_choice(ep, n_edge, slices);
+    else slices(std::integral_constant<int, CHOICE_PLAIN>{});
     if constexpr (EPI == EPI_ARGMAX) {
         __syncthreads();
-        for (int lrow = tid; lrow < BM; lrow += NTHR) {
-            const int row = m0 + lrow;
-            if (row >= M) continue;
-            float bv = red_val[lrow * WN];
-            int bi = red_idx[lrow * WN];
-#pragma unroll
-            for (int w = 1; w < WN; ++w) {
-                const float ov = red_val[lrow * WN + w];
-                const int oi = red_idx[lrow * WN + w];
-                if (arg_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-            }
-            ep.part_val[(int64_t)bn * M + row] = bv;
-            ep.part_idx[(int64_t)bn * M + row] = bi;
+        constexpr int TPR = NTHR / BM;               // threads per row
+        static_assert(TPR >= 1 && ENT % (2 * TPR) == 0, "whole pairs of entries per thread");
+        const int lrow = tid / TPR;
+        float bv = -INFINITY;
+        int bi = 0x7fffffff;
+        best_entry<ENT / TPR>(red + tid * (ENT / TPR), bv, bi);
+        best_of_lanes<TPR>(bv, bi);
+        if (tid % TPR == 0 && m0 + lrow < M) {
+            ep.part_val[(int64_t)bn * M + m0 + lrow] = bv;
+            ep.part_idx[(int64_t)bn * M + m0 + lrow] = bi;
         }
     }
 }
@@ -606,8 +649,10 @@ __device__ __forceinline__ void layernorm_panel(const GemmEpi &ep, int M, int d,
     __syncthreads();
 }
 
+// (Two wavefronts per SIMD: 256 registers are enough for every tile.  Left more, the compiler keeps operands of the
+// four-wavefront tiles in accumulation registers and copies them inside the k loop: 13000 x 4096 x 1024 argmax 121 us | 104.)
 template <int BM, int BN, int WM, int WN, int EPI, typename TAct, int NS = 2>
-__global__ void __launch_bounds__(WM *WN * 64)
+__global__ void __launch_bounds__(WM *WN * 64, 2)
 gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, int N, int K, GemmEpi ep)
 {
     constexpr int BK = 64;
@@ -619,7 +664,7 @@ gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, 
     constexpr int STG = WTN + 4;                     // stage row stride in floats: 16 B * odd
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32x32");
     static_assert((BM * BK / 8) % NTHR == 0 && (BN * BK / 8) % NTHR == 0, "tile/threads mismatch");
-    static_assert(NW * 32 * STG * 4 + BM * WN * 8 <= NS * (BM + BN) * BK * 2, "epilogue stage exceeds the tile LDS");
+    static_assert(NW * 32 * STG * 4 + (EPI == EPI_ARGMAX ? BM * WN * 32 : 0) <= NS * (BM + BN) * BK * 2, "epilogue stage exceeds the tile LDS");
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int64_t probe_id = blockIdx.x;
@@ -722,6 +767,7 @@ gemm_bf16_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M, 
     // Loads for tiles past the end are issued like any other
     // (range check: zeros nobody reads), which keeps the loop branch-free.
     const int KT = K / BK;
+    __builtin_assume(KT > 0);                        // (a path without a k tile costs the 256x256 argmax 48 spilled registers)
     static_assert((NS - 1) * (A_IT + B_IT) <= 63, "more tile loads in flight than the counter holds");
     constexpr int LD_IT = A_IT + B_IT;
 #pragma unroll

@@ -1,0 +1,59 @@
+"""What the compiler made of the kernels: read from the metadata and the instructions of the built library's own code
+object (no GPU).  Registers in scratch memory, accumulators copied between register files inside a loop and loads that
+became loops over the lanes all give right results, only slowly, so no other test sees them."""
+import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+import paper_2605_08696_amd as srm
+
+msgpack = pytest.importorskip("msgpack")
+
+
+@pytest.fixture(scope="module")
+def code_object():
+    """The gfx950 ELF inside the offload bundle of libsrm.so."""
+    path = os.path.join(os.path.dirname(srm.__file__), "libsrm.so")
+    data = open(path, "rb").read()
+    base = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    (n,) = struct.unpack_from("<Q", data, base + 24)
+    at = base + 32
+    for _ in range(n):
+        off, size, length = struct.unpack_from("<QQQ", data, at)
+        triple = data[at + 24:at + 24 + length]
+        at += 24 + length
+        if b"gfx950" in triple:
+            return data[base + off:base + off + size]
+    raise AssertionError("no gfx950 code object in the library")
+
+
+@pytest.fixture(scope="module")
+def kernels(code_object):
+    (table,) = struct.unpack_from("<Q", code_object, 40)
+    entry, count = struct.unpack_from("<HH", code_object, 58)
+    for k in range(count):
+        (kind,) = struct.unpack_from("<I", code_object, table + k * entry + 4)
+        if kind != 7:                                            # SHT_NOTE
+            continue
+        (off,) = struct.unpack_from("<Q", code_object, table + k * entry + 24)
+        name_len, desc_len, _ = struct.unpack_from("<III", code_object, off)
+        desc = off + 12 + ((name_len + 3) & ~3)
+        return {q[".name"]: q for q in msgpack.unpackb(code_object[desc:desc + desc_len])["amdhsa.kernels"]}
+    raise AssertionError("no metadata note")
+
+
+def test_no_kernel_spills_vector_registers(kernels):
+    """nucleus_slow_kernel apart, whose 1024 threads hold 32 logits each within 128 registers."""
+    spilled = {n: q[".vgpr_spill_count"] for n, q in kernels.items() if q[".vgpr_spill_count"] and "nucleus_slow" not in n}
+    assert len(kernels) > 200 and not spilled
+
+
+def test_bf16_gemms_keep_their_accumulators_in_one_register_file(kernels):
+    """Two wavefronts per SIMD leave 256 registers, enough for every tile: with a larger budget the compiler keeps operands
+    in accumulation registers and copies them back and forth inside the k loop."""
+    gemms = {n: q for n, q in kernels.items() if "gemm_bf16_kernel" in n or "gemm_bf16_persist_kernel" in n}
+    assert len(gemms) > 40 and not {n: q[".agpr_count"] for n, q in gemms.items() if q[".agpr_count"]}
