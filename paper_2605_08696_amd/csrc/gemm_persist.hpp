@@ -237,8 +237,10 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
     // the bias of this lane's columns n0 + wn*64 + j*16 + 4lq .. +3 (zeros past N, which is a multiple of 4)
     f32x4_t bq[TN];
     auto bias_request = [&](int n0) {
+        // (n0 < N always.  A size clamped at zero as well is formed in a vector register, by v_med3, and each load becomes
+        // a loop over lanes with a wait for everything in flight, k tiles on their way included)
         const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(ep.bias ? ep.bias + n0 : nullptr), 0, ep.bias ? max(min(BN, N - n0), 0) * 4 : 0, 0x00020000);
+            const_cast<float *>(ep.bias ? ep.bias + n0 : nullptr), 0, ep.bias ? min(BN, N - n0) * 4 : 0, 0x00020000);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
             bq[j] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rb, (wn * WTN + j * 16 + 4 * lq) * 4, 0, 0));

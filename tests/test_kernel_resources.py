@@ -57,3 +57,21 @@ def test_bf16_gemms_keep_their_accumulators_in_one_register_file(kernels):
     in accumulation registers and copies them back and forth inside the k loop."""
     gemms = {n: q for n, q in kernels.items() if "gemm_bf16_kernel" in n or "gemm_bf16_persist_kernel" in n}
     assert len(gemms) > 40 and not {n: q[".agpr_count"] for n, q in gemms.items() if q[".agpr_count"]}
+
+
+def test_persistent_gemm_loads_its_bias_without_loops_over_lanes(code_object, kernels, tmp_path):
+    """A buffer descriptor that the compiler does not know to be uniform turns each of its loads into a loop."""
+    objdump = next((p for p in ("/opt/rocm/llvm/bin/llvm-objdump", shutil.which("llvm-objdump")) if p and os.path.exists(p)), None)
+    if objdump is None:
+        pytest.skip("no llvm-objdump")
+    elf = tmp_path / "gfx950.elf"
+    elf.write_bytes(code_object)
+    names = [n for n in kernels if "gemm_bf16_persist_kernel" in n]
+    assert len(names) >= 6
+    for name in names:
+        text = subprocess.run([objdump, "-d", f"--disassemble-symbols={name}", str(elf)], capture_output=True, text=True, check=True).stdout
+        lines = text.splitlines()
+        assert sum("v_mfma" in x for x in lines) >= 64
+        for i, line in enumerate(lines):
+            if re.search(r"buffer_load_dwordx4 v\[", line):
+                assert not any("s_cbranch_execnz" in x for x in lines[i + 1:i + 6]), name
