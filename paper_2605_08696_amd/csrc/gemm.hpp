@@ -337,13 +337,15 @@ struct RowBest {
     float val;
     int code;
 };
-// What is compared: the logits of a tile whose columns all exist, of one at the edge of the matrix, or with noise.  Chosen
-// once in front of all rows (with_choice): one row's code behind the other's, no jumps over the forms not taken.
-enum Choice { CHOICE_PLAIN, CHOICE_EDGE, CHOICE_NOISE };
+// What is compared: the logits or the logits with noise, of a tile whose columns all exist or of one at the edge of the
+// matrix.  Chosen once in front of all rows (with_choice): one row's code behind the other's, no jumps over the forms not
+// taken.
+enum Choice { CHOICE_PLAIN = 0, CHOICE_EDGE = 1, CHOICE_NOISE = 2 };
 template <typename F>
 __device__ __forceinline__ void with_choice(const GemmEpi &ep, bool edge, F &&f)
 {
-    if (ep.temp > 0.0f) f(std::integral_constant<int, CHOICE_NOISE>{});
+    if (ep.temp > 0.0f && edge) f(std::integral_constant<int, CHOICE_NOISE | CHOICE_EDGE>{});
+    else if (ep.temp > 0.0f) f(std::integral_constant<int, CHOICE_NOISE>{});
     else if (edge) f(std::integral_constant<int, CHOICE_EDGE>{});
     else f(std::integral_constant<int, CHOICE_PLAIN>{});
 }
@@ -357,8 +359,8 @@ __device__ __forceinline__ RowBest row_best(const GemmEpi &ep, const f32x4_t (&a
         for (int r = 0; r < 4; ++r) {
             const int col = col0 + j * 16 + r;
             float v = a[j][r];
-            if constexpr (CHOICE == CHOICE_NOISE) v += ep.temp * srm_gumbel(key, (uint32_t)col);
-            if ((CHOICE == CHOICE_PLAIN || col < N) && v > b.val) { b.val = v; b.code = 4 * j + r; }
+            if constexpr (CHOICE & CHOICE_NOISE) v += ep.temp * srm_gumbel(key, (uint32_t)col);
+            if ((!(CHOICE & CHOICE_EDGE) || col < N) && v > b.val) { b.val = v; b.code = 4 * j + r; }
         }
     return b;
 }
@@ -447,10 +449,11 @@ __device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / 
         if constexpr (EPI == EPI_ARGMAX) {
             // (the winners in front of the slice's stores, which travel meanwhile)
             uint32_t key[2] = {0, 0};
-            if constexpr (decltype(choice_c)::value == CHOICE_NOISE) noise_keys(ep, m0 + wm * WTM + i * 32 + lr, M, key);
+            if constexpr (decltype(choice_c)::value & CHOICE_NOISE) noise_keys(ep, m0 + wm * WTM + i * 32 + lr, M, key);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int wrow = wm * WTM + i * 32 + h * 16;
+                if ((decltype(choice_c)::value & CHOICE_NOISE) && m0 + wrow >= M) continue;     // rows that nobody keeps
                 const RowBest b = row_best<decltype(choice_c)::value>(ep, acc[2 * i + h], key[h], N, wcol0 + 4 * lq);
                 red[(wrow + lr) * ENT + ((wn * 4 + lq) ^ (lr & (ENT - 1)))] = row_best_entry(b, wcol0 + 4 * lq);
             }
@@ -575,7 +578,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4_t (&acc)[BM / WM / 16][BN / 
     if constexpr (EPI == EPI_ARGMAX) {
         __syncthreads();
         constexpr int TPR = NTHR / BM;               // threads per row
-        static_assert(TPR >= 1 && ENT % (2 * TPR) == 0, "whole pairs of entries per thread");
+        static_assert(NTHR % BM == 0 && ENT % (2 * TPR) == 0, "whole rows and pairs of entries per thread");
         const int lrow = tid / TPR;
         float bv = -INFINITY;
         int bi = 0x7fffffff;

@@ -22,7 +22,7 @@ constexpr int kPersistLds = 160 * 1024;
 // wave tiles).  Sixteen rows at a time pass through a wave-private stage [16][64] in `stage` (16-byte chunk c of row r at
 // chunk c ^ r: writes and reads free of bank conflicts), so that global accesses are 16-byte vectors over 256 bytes of a
 // row.  Old values (residual stream, recurrent state) are requested for 32 rows at a time, in front of the stage.
-template <int EPI, typename TAct, typename BARRIER>
+template <int EPI, typename TAct, bool STORE, typename BARRIER>
 __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned char *stage_base, const GemmEpi &ep, int M, int N,
                                                  int m0, int n0, int bn, const int tid, BARRIER &&lds_barrier)
 {
@@ -32,12 +32,42 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
     const int lr = lane & 15, lq = lane >> 4;
     const int wcol0 = n0 + wn * WTN, wrow0 = m0 + wm * WTM;
     const bool inside = n0 + 256 <= N && m0 + 256 <= M;                // block-uniform
-    if (EPI != EPI_ARGMAX || ep.out != nullptr) {
+    // EPI_ARGMAX: every lane leaves the best of its sixteen columns of a row in the stage, entry wn*4 + lq of [256 rows][16]
+    // (at entry ^ row: no bank conflicts); two lanes per row then take the best of the sixteen.  With logits to store the
+    // stage is in use until all rows are through: the winners wait in registers, their codes in four bits each.
+    [[maybe_unused]] uint2 *red = reinterpret_cast<uint2 *>(stage_base);
+    [[maybe_unused]] float best_val[TM];
+    [[maybe_unused]] unsigned best_code = 0;
+    [[maybe_unused]] uint32_t key[TM] = {};
+    [[maybe_unused]] auto leave = [&](int t, RowBest b, int col0) {
+        red[(wm * WTM + t * 16 + lr) * 16 + ((wn * 4 + lq) ^ lr)] = row_best_entry(b, col0);
+    };
+    [[maybe_unused]] auto choose = [&](auto choice_c, auto t_) {
+        constexpr int C = decltype(choice_c)::value, t = decltype(t_)::value;
+        best_val[t] = -INFINITY;
+        // (no noise for rows past M, whose entries nobody keeps)
+        if ((C & CHOICE_NOISE) && wrow0 + t * 16 >= M) return;         // wave-uniform
+        // (opaque: what is derived from the columns is formed for each row, not held in registers across all rows,
+        // of which the noise had none left: 300 x 32000 x 512 with a temperature 2.7 us shorter)
+        int col0 = wcol0 + 4 * lq;
+        asm volatile("" : "+v"(col0));
+        const RowBest b = row_best<C>(ep, acc[t], key[t], N, col0);
+        if constexpr (STORE) {
+            best_val[t] = b.val;
+            best_code |= (unsigned)b.code << (4 * t);
+        } else {
+            leave(t, b, col0);
+        }
+    };
+    [[maybe_unused]] auto keys = [&](auto choice_c) {
+        if constexpr (decltype(choice_c)::value & CHOICE_NOISE) noise_keys(ep, wrow0 + lr, M, key);
+    };
+    if constexpr (STORE) {
         f32x4_t *stage = reinterpret_cast<f32x4_t *>(stage_base) + wave * (16 * 16);   // [16 rows][16 chunks]
         const int s_row = lane >> 4, s_chunk = lane & 15;
         const int gcol = wcol0 + s_chunk * 4;
         const unsigned lane_at = (unsigned)s_row * (unsigned)ep.ldo + s_chunk * 4;    // (the rest of an offset is uniform)
-        auto slices = [&](auto inside_c) {
+        auto slices = [&](auto inside_c, auto choice_c) {
             constexpr bool IN = decltype(inside_c)::value;
             auto row_of = [&](int t, int it) { return (int64_t)wrow0 + t * 16 + it * 4 + s_row; };
             auto exists = [&](int t, int it) { return IN || (row_of(t, it) < M && gcol < N); };
@@ -79,6 +109,9 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                             be[it] = ep.beta[(size_t)hd * ep.n_ctx + pc];
                         }
                     }
+                    // (the choice in front of each sixteen rows' stores, which travel under the next rows' noise: a step of 300
+                    // rows of a mid-sized model with temperature and logits 251.8 us | 247.1, of 900 for top-p 402.4 | 393.9)
+                    if constexpr (EPI == EPI_ARGMAX) choose(choice_c, std::integral_constant<int, t>{});
 #pragma unroll
                     for (int j = 0; j < TN; ++j) stage[lr * 16 + ((4 * j + lq) ^ lr)] = acc[t][j];
                     f32x4_t v[4];
@@ -105,59 +138,35 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                 });
             });
         };
-        if (inside) slices(std::true_type{});
-        else slices(std::false_type{});
+        if constexpr (EPI == EPI_ARGMAX) {
+            with_choice(ep, !inside, [&](auto choice_c) {
+                keys(choice_c);
+                slices(std::integral_constant<bool, !(decltype(choice_c)::value & CHOICE_EDGE)>{}, choice_c);
+            });
+        } else if (inside) {
+            slices(std::true_type{}, std::integral_constant<int, CHOICE_PLAIN>{});
+        } else {
+            slices(std::false_type{}, std::integral_constant<int, CHOICE_EDGE>{});
+        }
+    } else if constexpr (EPI == EPI_ARGMAX) {
+        with_choice(ep, wcol0 + WTN > N, [&](auto choice_c) {
+            keys(choice_c);
+            static_for<0, TM>([&](auto t_) { choose(choice_c, t_); });
+        });
     }
     if constexpr (EPI == EPI_ARGMAX) {
-        // Every lane leaves the best of its sixteen columns of a row in the stage, entry wn*4 + lq of [256 rows][16] (at
-        // entry ^ row: no bank conflicts); two lanes per row then take the best of the sixteen.  (Exchanged between lanes
-        // row by row instead, the round trips through the LDS crossbar add up: 8.7 us per tile.)
-        uint2 *red = reinterpret_cast<uint2 *>(stage_base);
-        if (ep.out) lds_barrier();                   // the stages have been read back
-        // score(t, j, r, column): what is compared; strict > in ascending order keeps the lowest index
-        auto rows_best = [&](auto &&row_key, auto &&score, auto edge_c) {
-            static_for<0, TM>([&](auto t_) {
-                constexpr int t = decltype(t_)::value;
-                const uint32_t key = row_key(wrow0 + t * 16 + lr);
-                float bv = -INFINITY;
-                int brel = 0;
-                // (opaque: what is derived from the columns is formed for each row, not held in registers across all rows,
-                // of which the noise had none left: 300 x 32000 x 512 with a temperature 2.7 us shorter)
-                int col0 = wcol0 + 4 * lq;
-                asm volatile("" : "+v"(col0));
+        if constexpr (STORE) {
+            lds_barrier();                           // the stages have been read back
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int col = col0 + j * 16 + r;
-                        const float v = score(acc[t][j][r], key, col);
-                        if ((!decltype(edge_c)::value || col < N) && v > bv) { bv = v; brel = j * 16 + r; }
-                    }
-                const int bi = bv == -INFINITY ? 0x7fffffff : col0 + brel;
-                red[(wm * WTM + t * 16 + lr) * 16 + ((wn * 4 + lq) ^ lr)] = make_uint2(__float_as_uint(bv), (unsigned)bi);
-            });
-        };
-        if (ep.temp > 0.0f)
-            rows_best([&](int row) { return srm_rowkey(ep.seed, epi_pos(ep, row, M), (uint32_t)row + ep.row_base); },
-                      [&](float v, uint32_t key, int col) { return v + ep.temp * srm_gumbel(key, (uint32_t)col); }, std::true_type{});
-        else if (wcol0 + WTN > N)                    // wave-uniform
-            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::true_type{});
-        else
-            rows_best([](int) { return 0u; }, [](float v, uint32_t, int) { return v; }, std::false_type{});
+            for (int t = 0; t < TM; ++t)
+                leave(t, RowBest{best_val[t], (int)(best_code >> (4 * t) & 15)}, wcol0 + 4 * lq);
+        }
         lds_barrier();
         const int row = m0 + (tid >> 1);
-        const uint4 *mine = reinterpret_cast<const uint4 *>(red + tid * 8);
         float bv = -INFINITY;
         int bi = 0x7fffffff;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint4 x = mine[e];
-            if (arg_better(__uint_as_float(x.x), (int)x.y, bv, bi)) { bv = __uint_as_float(x.x); bi = (int)x.y; }
-            if (arg_better(__uint_as_float(x.z), (int)x.w, bv, bi)) { bv = __uint_as_float(x.z); bi = (int)x.w; }
-        }
-        const float ov = __shfl_xor(bv, 1, kWave);
-        const int oi = __shfl_xor(bi, 1, kWave);
-        if (arg_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        best_entry<8>(red + tid * 8, bv, bi);
+        best_of_lanes<2>(bv, bi);
         if ((tid & 1) == 0 && row < M) {
             ep.part_val[(int64_t)bn * M + row] = bv;
             ep.part_idx[(int64_t)bn * M + row] = bi;
@@ -327,13 +336,23 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         }
         if (probe) { clk_c2 = clock64(); clk_t2 = wall_clock64(); }
 
-        if constexpr (EPI != EPI_MIX) bias_request(nxt.n0);
-        __builtin_amdgcn_sched_barrier(0);
         // (the thread index through an opaque copy: what the epilogue derives from it is computed here, per
         // tile, and not once in front of the tile loop, where it would be held in registers across every k loop)
         int tid_e = threadIdx.x;
         asm volatile("" : "+v"(tid_e));
-        persist_epilogue<EPI, TAct>(acc, smem_raw + at(4), ep, M, N, cur.m0, cur.n0, cur.bn, tid_e, lds_barrier);
+        auto epilogue = [&](auto store_c) {
+            persist_epilogue<EPI, TAct, decltype(store_c)::value>(acc, smem_raw + at(4), ep, M, N, cur.m0, cur.n0, cur.bn, tid_e,
+                                                                  lds_barrier);
+        };
+        // The next bias is requested in front of the epilogue, unless that leaves no registers for it.
+        if (EPI == EPI_ARGMAX && ep.out) {
+            epilogue(std::true_type{});
+            bias_request(nxt.n0);
+        } else {
+            if constexpr (EPI != EPI_MIX) bias_request(nxt.n0);
+            __builtin_amdgcn_sched_barrier(0);
+            epilogue(std::integral_constant<bool, EPI != EPI_ARGMAX>{});
+        }
         if (probe) {
             __builtin_amdgcn_s_waitcnt(0);           // this wave's stores have completed
             if (tid == 0) {
@@ -349,7 +368,7 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         if (vn >= nblk) break;                       // (block-uniform)
         v = vn;
         cur = nxt;
-        if constexpr (EPI == EPI_MIX) bias_request(cur.n0);            // (no registers for it before)
+        if constexpr (EPI == EPI_MIX) bias_request(cur.n0);
         lds_barrier();                               // every wave has read its stage back: the unit can be filled
         if constexpr (REREAD) static_for<0, TM + TN>([&](auto r_) { read_one(r_, h0, at(0), at(1)); });
     }

@@ -266,3 +266,41 @@ def test_topp_search_counts_a_long_flat_tail(srm, orc_mod, seed):
     drawn = orc_mod.pick(logits, 1.0, seed, pos, 0)
     assert drawn in mid[130:133]
     assert int(out[0]) == orc_mod.pick_topp(logits, 1.0, top_p, seed, pos, 0) != drawn
+
+
+@pytest.mark.parametrize("B,V", [(257, 31004), (300, 31004), (300, 31002), (300, 2001)])
+def test_noise_in_the_head_of_large_tiles(srm, orc_mod, B, V):
+    """Plain sampling inside the bf16 LM head: the persistent 256x256 tile (31 004 columns, the row tile's groups of
+    sixteen rows whole, ragged and empty), the 256x256 tile of odd vocabularies and the 128x128 one.  Every row's token
+    is the oracle's choice from the GPU's own logits, the same without a logits buffer, at one position and at positions
+    of each row's own, idle rows among them."""
+    cfg = srm_synth.tiny_config(vocab=V, d_model=128, n_layers=1, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=33)
+    w = srm_synth.make_weights(cfg, stress=True)
+    w["head"] = srm_synth.round_to_bf16(w["head"] * 30.0)
+    model = srm.Model(cfg, w)
+    T, seed, pos = 0.8, 13, 3
+    rng = np.random.default_rng(4)
+    tok = to_dev(rng.integers(0, V, B).astype(np.int32))
+    st0 = torch.randn(cfg.n_layers * B * cfg.d_model, device="cuda") * 0.1
+    posr0 = rng.integers(0, cfg.n_ctx - 1, B).astype(np.int32)
+    posr0[[0, B // 2, B - 1]] = -1
+    ws = model.new_workspace(B)
+    lg = torch.empty((B, V), dtype=torch.float32, device="cuda")
+    for ragged in (False, True):
+        print(f"sampled head B={B} V={V} ragged={ragged}", flush=True)
+        res = []
+        for logits in (lg, None):
+            st, out = st0.clone(), torch.full((B,), -7, dtype=torch.int32, device="cuda")
+            if ragged:
+                model.decode_step_ragged(B, to_dev(posr0), tok, st, out, advance=False, temperature=T, seed=seed,
+                                         logits=logits, workspace=ws)
+            else:
+                model.decode_step(B, pos, tok, st, out, logits=logits, workspace=ws, temperature=T, seed=seed)
+            res.append(out.cpu().numpy())
+        np.testing.assert_array_equal(res[0], res[1])
+        live = np.flatnonzero(posr0 >= 0) if ragged else np.arange(B)
+        if ragged:
+            assert (res[0][posr0 < 0] == -1).all()
+        tolerated, _ = _check_rows(orc_mod, res[0][live], lg.cpu().numpy()[live], T, 1.0, seed,
+                                   lambda r: int(posr0[live[r]]) if ragged else pos, b_of=live)
+        assert tolerated <= 2
