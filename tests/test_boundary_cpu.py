@@ -23,6 +23,20 @@ def srm():
     return pkg
 
 
+def test_library_is_stale_after_any_change_of_what_makes_it(monkeypatch):
+    """A newer source, header or compile command (build.py itself holds the flags) means a new build."""
+    from paper_2605_08696_amd import build as b
+    times = {}
+    monkeypatch.setattr(b.os.path, "exists", lambda p: True)
+    monkeypatch.setattr(b.os.path, "getmtime", lambda p: times.get(os.path.basename(p), 1.0))
+    times["libsrm.so"] = 2.0
+    assert not b.is_stale()
+    for name in ("srm.hip", "gemm.hpp", "srm.h", "build.py"):
+        times[name] = 3.0
+        assert b.is_stale(), name
+        times[name] = 1.0
+
+
 def declared_functions():
     text = open(os.path.join(ROOT, "include", "srm.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
