@@ -48,6 +48,8 @@
  *                        1000 samples: the token mixing of a layer as separate
  *                        kernels instead of one (sums in another order); =1 as
  *                        one kernel up to 2048 samples;
+ *     SRM_READ_AHEAD=0   LayerNorm launches without the work-groups that read the
+ *                        matrices of the next launches (same bits);
  *     SRM_MEGAKERNEL, SRM_MEGA_BLOCKS   see srm_generate_one_kernel_blocks.
  */
 #ifndef SRM_H

@@ -140,8 +140,9 @@ __device__ __forceinline__ float srm_gumbel(uint32_t rowkey, uint32_t v)
 // of the step.  The LayerNorm launches in front of them leave CUs free or are bound by other traffic; they carry extra
 // work-groups that read the matrices coming up, so that the GEMMs find them in L2 (us with the weights in HBM | L2; rows x
 // columns x K: 37 x 4096 x 1024: 5.0 | 3.7, 300 x 1024 x 4096: 13.3 | 9.2).  Each XCD has an L2 of its own and work-groups
-// are dealt to the XCDs in turn: those on XCD x read the eighth of a matrix's rows that tile_of_pid gives to the tiles on
-// XCD x (all they need while at most eight row tiles; the last-level cache has the rest).
+// are dealt to the XCDs in turn: those on XCD x read an eighth of a matrix's rows, the columns of the tiles that tile_of_pid
+// gives to XCD x where the tiles are a multiple of eight, in at most eight rows and at least eight columns of them.
+// Elsewhere an XCD needs other rows too, which it finds in the last-level cache.
 constexpr int kPrefetchMats = 4;
 struct Prefetch {
     const void *mat[kPrefetchMats];          // null: none

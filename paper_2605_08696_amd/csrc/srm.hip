@@ -865,24 +865,34 @@ static int argmax_finalize(const float *pv, const int32_t *pi, int64_t rows, int
     return SRM_OK;
 }
 
-// The matrices that a launch's extra work-groups touch (see Prefetch): the projections of layer l, its MLP.  (None that
-// would take the larger part of the L2s, eight of 4 MB.)
-static void prefetch_add(Prefetch &pf, int at, const void *mat, size_t bytes)
+// What a launch's extra work-groups read (see Prefetch), in the order of use: the MLP of layer `mlp`, the projections of layer
+// `mix` (-1: none), up to the first matrix above kPrefetchMatrix.  Their sum may exceed the 32 MB of the L2s: what the L2s give
+// up the last-level cache still holds.  Decode steps of eight layers of 1536 and 1280 channels (MLP matrices of 18.9 and 13.1
+// MB; us, none | the first one | both): 1536 channels, 40 rows 359 | 333 | 347, 300: 556 | 523 | 519, 3001: 2105 | 2028 | 1998,
+// without projections 1 row 245 | 252 | 242, 300: 439 | 438 | 411; 1280 channels, 40 rows 300 | 279 | 283, 300: 471 | 450 | 443,
+// 3001: 1388 | 1341 | 1288.
+constexpr size_t kPrefetchMatrix = (size_t)20 << 20;
+static Prefetch prefetch_of(const srm_model *m, int mlp, int mix)
 {
-    if (bytes > (size_t)20 << 20) return;
-    pf.mat[at] = mat;
-    pf.bytes[at] = (uint32_t)bytes;
-}
-static void prefetch_mix(const srm_model *m, int l, Prefetch &pf, int at)
-{
-    if (l >= m->L || m->noproj) return;
-    prefetch_add(pf, at, m->layers[l].w_in, (size_t)m->d * m->dm * m->wsize);
-    prefetch_add(pf, at + 1, m->layers[l].w_out, (size_t)m->d * m->dm * m->wsize);
-}
-static void prefetch_mlp(const srm_model *m, int l, Prefetch &pf, int at)
-{
-    prefetch_add(pf, at, m->layers[l].w_up, (size_t)m->d * m->ff * m->wsize);
-    prefetch_add(pf, at + 1, m->layers[l].w_down, (size_t)m->d * m->ff * m->wsize);
+    Prefetch pf{};
+    int n = 0;
+    bool more = true;
+    auto add = [&](const void *mat, size_t elems) {
+        const size_t bytes = elems * m->wsize;
+        more = more && bytes <= kPrefetchMatrix;
+        if (!more) return;
+        pf.mat[n] = mat;
+        pf.bytes[n++] = (uint32_t)bytes;
+    };
+    if (mlp >= 0) {
+        add(m->layers[mlp].w_up, (size_t)m->d * m->ff);
+        add(m->layers[mlp].w_down, (size_t)m->d * m->ff);
+    }
+    if (mix >= 0 && mix < m->L && !m->noproj) {
+        add(m->layers[mix].w_in, (size_t)m->d * m->dm);
+        add(m->layers[mix].w_out, (size_t)m->d * m->dm);
+    }
+    return pf;
 }
 // Extra work-groups of a LayerNorm launch (256 threads each).  For bf16 models whose matrices exceed the 256 MB of the
 // last-level cache, so that a step finds them in HBM (the mid model's 74 MB: no gain, up to 2 % slower), and up to 12 288
@@ -896,6 +906,8 @@ static int prefetch_blocks(const srm_model *m, int64_t rows, int64_t least, cons
 {
     const size_t elems = (size_t)m->L * ((m->noproj ? 0 : (size_t)2 * m->d * m->dm) + (size_t)2 * m->d * m->ff) + (size_t)m->V * m->d;
     if (!pf.mat[0] || m->wsize != 2 || elems * m->wsize <= (size_t)256 << 20) return 0;
+    const char *e = getenv("SRM_READ_AHEAD");
+    if (e && e[0] == '0') return 0;
     return rows >= least && rows <= 12288 ? 256 : 0;
 }
 
@@ -1090,13 +1102,10 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     const int d = m->d, dm = m->dm, ff = m->ff;
     const LnArgs ln1 = (lnf || ln1f) && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
     const LnArgs ln2 = lnf ? LnArgs{w.x, y.ln2_g, y.ln2_b, m->cfg.ln_eps} : LnArgs();
-    Prefetch pf_mlp{}, pf_next{};            // this layer's MLP, the next layer's projections
-    prefetch_mlp(m, l, pf_mlp, 0);
-    prefetch_mix(m, l + 1, pf_next, 0);
-    if (ln1f) prefetch_mix(m, l + 1, pf_mlp, 2);
+    // read ahead: this layer's MLP (and the next layer's projections, if no launch stands in front of them), those projections
+    Prefetch pf_mlp = prefetch_of(m, l, ln1f || one_mix ? l + 1 : -1), pf_next = prefetch_of(m, -1, l + 1);
     if constexpr (sizeof(T) == 2) {
         if (one_mix) {
-            prefetch_mix(m, l + 1, pf_mlp, 2);
             // token mixing in one kernel, which normalises w.x itself; LayerNorm2 adds its slabs to w.x
             SRM_TRY(token_mix(m, l, TokMixCall{w.x, np_state, fuse_pos, w.part}, rows, st));
             SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, w.part,
@@ -1210,10 +1219,9 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
         return static_cast<void *>(static_cast<unsigned char *>(layer_state(m, a.state, l, a.B)) +
                                    (size_t)b0 * dm * m->ssize);
     };
-    Prefetch pf{};
-    prefetch_mix(m, 0, pf, 0);
     SRM_TRY((layernorm<T, true>(m, nullptr, 0, a.tok_in + b0, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a, nb,
-                                st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr, pf)));
+                                st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr,
+                                prefetch_of(m, -1, 0))));
     auto mix = [&](int l) {
         if (!pos_rows) return state_update<T>(m, l, a.pos, nb, w.u, slab(l), w.mx, st, a.pos_dev);
         const LayerDev &y = m->layers[l];

@@ -586,3 +586,30 @@ def test_matrices_read_ahead_change_no_bits(srm, use_projections, monkeypatch):
             model.decode_step(n, 7, tok[b0:b0 + n].contiguous(), st2, out2, hidden=hidden2, workspace=model.new_workspace(n))
             assert torch.equal(hidden[b0:b0 + n], hidden2) and torch.equal(st[:, b0:b0 + n], st2)
             assert torch.equal(out[b0:b0 + n], out2)
+
+
+@pytest.mark.parametrize("use_projections", [True, False])
+@pytest.mark.parametrize("switches", [{}, {"SRM_TOKEN_MIX": "0"}, {"SRM_TOKEN_MIX": "0", "SRM_LN_ON_LOAD": "0"}])
+def test_a_step_with_and_without_read_ahead_gives_the_same_bits(srm, use_projections, switches, monkeypatch):
+    """The same call with the extra work-groups and without them, in each arrangement of a layer: token mixing in one kernel
+    and the in-projection that normalises its rows (LayerNorm2 then names four matrices), separate launches, and from 4096
+    rows on the LayerNorm of several rows per wavefront (5003: neither kernel's rows fill its last work-group)."""
+    cfg = srm_synth.tiny_config(vocab=530000, d_model=256, n_layers=2, n_heads=4, n_ctx=16, weight_dtype="bf16",
+                                use_projections=use_projections, seed=19)
+    rng = np.random.default_rng(6)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    for name, value in switches.items():
+        monkeypatch.setenv(name, value)
+    for B in (1, 40, 130, 5003):
+        print(f"read ahead on and off: projections {use_projections}, {switches}, {B} rows", flush=True)
+        tok = to_dev(rng.integers(0, cfg.vocab, B).astype(np.int32))
+        state = to_dev(rng.standard_normal((cfg.n_layers, B, cfg.d_model)).astype(np.float32))
+        ws, got = model.new_workspace(B), []
+        for switch in ("1", "0"):
+            monkeypatch.setenv("SRM_READ_AHEAD", switch)
+            out, hidden = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, cfg.d_model), device="cuda")
+            st = state.clone()
+            model.decode_step(B, 7, tok, st, out, hidden=hidden, workspace=ws)
+            got.append((out, hidden, st))
+        assert all(torch.equal(a, b) for a, b in zip(*got))
+        assert bool(torch.isfinite(got[0][1]).all())
