@@ -387,6 +387,13 @@ def test_linear_bf16_persistent_ring_of_five_units(srm, shape, epi):
     _linear_case(srm, srm.SRM_BF16, M, N, K, epi, None, seed=950 + epi)
 
 
+@pytest.mark.parametrize("shape", [(51100, 256, 128), (64005, 516, 192), (64005, 516, 320)])
+def test_linear_bf16_persistent_ring_of_five_units_argmax(srm, shape):
+    """The same ring under the LM head's choice, with the logits and without."""
+    M, N, K = shape
+    _linear_case(srm, srm.SRM_BF16, M, N, K, 3, None, seed=953)
+
+
 def test_linear_bf16_persistent_kernel_rejects_odd_k_tile_counts(srm):
     A = torch.zeros((512, 192), dtype=torch.bfloat16, device="cuda")
     W = torch.zeros((512, 192), dtype=torch.bfloat16, device="cuda")

@@ -246,8 +246,8 @@ def test_ragged_bf16_logits_against_oracle(srm, orc_mod):
 
 @pytest.mark.parametrize("B", [13000, 66000])
 def test_ragged_decode_large_batch_fused_equals_separate(srm, B, monkeypatch):
-    """13 000 samples of width 1024 (the in-projection takes the 256x256 tile, the state update rides in its
-    epilogue) and 66 000 (more tiles than compute units: the persistent form of that tile) at per-sample
+    """13 000 samples of width 1024 (the in-projection takes the 256x256 tile, one per work-group, the state update rides
+    in its epilogue) and 66 000 (more tiles than compute units: several per work-group) at per-sample
     positions, idle slots (-1) included: the same states, tokens and positions as with the separate ragged
     state-update kernel, and idle samples untouched."""
     cfg = srm_synth.tiny_config(vocab=300, d_model=1024, n_layers=1, n_heads=4, n_ctx=8, weight_dtype="bf16", seed=9)
@@ -277,6 +277,38 @@ def test_ragged_decode_large_batch_fused_equals_separate(srm, B, monkeypatch):
     np.testing.assert_array_equal(pos[idle], pos0[idle])
     np.testing.assert_array_equal(pos[~idle], pos0[~idle] + 2)
     assert not np.array_equal(st[:, ~idle], S0[:, ~idle])
+
+
+@pytest.mark.parametrize("layout,d,B", [("mixed", 320, 40), ("combined", 320, 33), ("combined", 1024, 24), ("mixed", 768, 50)])
+@pytest.mark.parametrize("fuse", [True, False])
+def test_ragged_decode_of_dozens_of_rows_normalised_by_the_in_projection(srm, layout, d, B, fuse, monkeypatch):
+    """Some dozens of slots at their own positions, idle ones included: the step whose in-projection normalises its rows (in
+    several row tiles, with the state update in its epilogue or behind it, into heads of one and of two matrices) against
+    the step with LayerNorm launches: the same bits."""
+    cfg = srm_synth.tiny_config(vocab=200, d_model=d, n_layers=3, n_heads=4, n_ctx=12, weight_dtype="bf16", seed=18,
+                                head_layout=layout)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    rng = np.random.default_rng(19 + B)
+    pos0 = rng.integers(-1, cfg.n_ctx - 3, B).astype(np.int32)
+    tok0 = rng.integers(0, cfg.vocab, B).astype(np.int32)
+    S0 = rng.standard_normal((cfg.n_layers, B, cfg.state_width)).astype(np.float32)
+    ws = model.new_workspace(B)
+    if not fuse:
+        monkeypatch.setenv("SRM_FUSE_MIXER", "0")
+    res = []
+    for on_load in ("1", "0"):
+        monkeypatch.setenv("SRM_LN_ON_LOAD", on_load)
+        st, tk, pos = to_dev(S0), to_dev(tok0), to_dev(pos0)
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        print(f"ragged dozens {layout} d={d} B={B} fuse={fuse} SRM_LN_ON_LOAD={on_load}", flush=True)
+        for _ in range(2):
+            model.decode_step_ragged(B, pos, tk, st, tk, advance=True, logits=lg, workspace=ws)
+        torch.cuda.synchronize()
+        res.append((st, tk, pos, lg))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+    idle = pos0 < 0
+    assert idle.any() and np.array_equal(res[0][0].cpu().numpy()[:, idle], S0[:, idle])
+    assert bool(torch.isfinite(res[0][3]).all())
 
 
 @pytest.mark.parametrize("d,B", [(256, 40), (512, 300)])

@@ -613,3 +613,27 @@ def test_a_step_with_and_without_read_ahead_gives_the_same_bits(srm, use_project
             got.append((out, hidden, st))
         assert all(torch.equal(a, b) for a, b in zip(*got))
         assert bool(torch.isfinite(got[0][1]).all())
+
+
+@pytest.mark.parametrize("d,B", [(128, 51201), (192, 51201), (320, 79005)])
+def test_state_update_behind_few_k_tiles_of_the_largest_tile(srm, orc_mod, d, B, monkeypatch):
+    """The state update in the epilogue of 256x256 tiles behind two, three and five k tiles, one output tile per work-group
+    and several, against the update as a kernel of its own (same bits) and the oracle on the first and the last row."""
+    cfg = srm_synth.tiny_config(vocab=64, d_model=d, n_layers=1, n_heads=4, n_ctx=8, weight_dtype="bf16", seed=21)
+    w = srm_synth.make_weights(cfg, stress=True)
+    model, T = srm.Model(cfg, w), 2
+    toks = srm_synth.make_prompts(cfg, batch=B, length=T)
+    rows, tc = [0, B - 1], to_dev(toks).t().contiguous()
+    ref = orc_mod.Oracle(cfg, w, "f64").recurrent_forward(toks[rows])
+    ws, res = model.new_workspace(B), []
+    for fuse in ("1", "0"):
+        monkeypatch.setenv("SRM_FUSE_MIXER", fuse)
+        print(f"state update in the largest tile d={d} B={B} SRM_FUSE_MIXER={fuse}", flush=True)
+        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        hidden = torch.empty((B, d), dtype=torch.float32, device="cuda")
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        for t in range(T):
+            model.decode_step(B, t, tc[t], st, out, logits=lg, hidden=hidden, workspace=ws)
+            assert rel_err_rows(lg[rows].cpu().numpy(), ref["logits"][:, t]) <= 2e-2
+        res.append((st, out, hidden))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
