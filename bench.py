@@ -181,8 +181,8 @@ def gemm_timeline(torch, srm, launch, M, N, K):
                          "turnaround_us": float(np.mean(gaps)) if gaps else 0.0,
                          "launch_span_us": float((t3.max() - t0.min()) * us),
                          "k_loop_tflops_all_cus": flop_per_wg / (loop_us * 1e-6) * len(per_cu) * 1e-12,
-                         # cycles the four matrix pipes of a CU need for the work-group's flops (a 32x32x16 bf16
-                         # product, 32768 flop, occupies a SIMD's pipe for 32 cycles) over the cycles the loop took
+                         # cycles the four matrix pipes of a CU need for the work-group's flops (a 16x16x32 bf16
+                         # product, 16384 flop, occupies a SIMD's pipe for 16 cycles) over the cycles the loop took
                          "k_loop_mfma_busy_frac": float(flop_per_wg / 4096.0 / (c2 - c1).mean())}}
 
 
@@ -215,8 +215,8 @@ def achievable_rates(torch, srm):
     assert bool(torch.isfinite(out).all())
     return {"copy_gbs": max(rates.values()), **rates, "copy_bytes": 2 << 30,
             "mfma_bf16_tflops": flop[0] / t * 1e-12, "mfma_bf16_tflops_random_operands": flop[0] / t_rand * 1e-12,
-            "mfma_probe": f"{blocks} work-groups x 4 wavefronts x {iters} x 4 "
-            "independent 32x32x16 bf16 products, operands in registers (all ones; and pseudo-random in (-1, 1))"}
+            "mfma_probe": f"{blocks} work-groups x 4 wavefronts x {iters} x 8 "
+            "independent 16x16x32 bf16 products, operands in registers (all ones; and pseudo-random in (-1, 1))"}
 
 
 def cpu_baseline(cfg, w, rows, T):
@@ -490,9 +490,9 @@ def main():
         out["achievable"] = ach
         if esz == 2:
             up = legs["gemm_up"]
-            # (the library runs the 256x256 tile as a persistent kernel once there are more tiles than CUs)
-            persistent = B >= 4096 and -(-B // 256) * -(-ff // 256) > torch.cuda.get_device_properties(0).multi_processor_count
-            up_kernel = "gemm_bf16_persist_kernel<EPI=GELU>" if persistent else "gemm_bf16_kernel<256,256,2,4,EPI=GELU>"
+            # (the library runs the 256x256 tile as a persistent kernel; smaller batches take other tiles)
+            large = B >= 4096 and -(-B // 256) * -(-ff // 256) > torch.cuda.get_device_properties(0).multi_processor_count
+            up_kernel = "gemm_bf16_persist_kernel<EPI=GELU>" if large else "gemm_bf16_kernel<EPI=GELU>"
             out["roofline"] = {"kernel": up_kernel + " (MLP up, GELU epilogue)", "bound": "mfma",
                                "achieved": up["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                                "frac": up["tflops"] / PEAK_BF16_TFLOPS,
@@ -523,9 +523,9 @@ def main():
             # algorithmic bytes (state read + written, A read, W read, m written) over the launch time against
             # 8 TB/s; the launch also carries 2*B*d*d flop on the matrix cores, which run first (k loop), then
             # the epilogue streams the state - the two phases do not overlap inside one launch.
-            tr = measured_traffic("gemm_bf16_kernel<256,256,2,4,EPI=MIX>") if cfg.name == "C4" and B == 16384 else None
+            tr = measured_traffic("gemm_bf16_persist_kernel<EPI=MIX>") if cfg.name == "C4" and B == 16384 else None
             out["roofline_state_update_fused"] = {
-                "kernel": "gemm_bf16_kernel<EPI=MIX> (in-projection + state update, the launch the step runs)",
+                "kernel": "gemm_bf16_persist_kernel<EPI=MIX> (in-projection + state update, the launch the step runs)",
                 "bound": "hbm", "achieved": fu["gbs"], "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": fu["gbs"] / PEAK_HBM_GBS, "traffic": tr, "frac_of_achievable": fu["gbs"] / ach["copy_gbs"],
                 "avg_launch_ms": fu["ms"], "bytes_per_launch": fu["bytes"],

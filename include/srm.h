@@ -529,7 +529,7 @@ int32_t srm_generate_one_kernel_blocks(const srm_model *m, int64_t B);
  * non-temporal loads and stores.  HBM traffic = 2 * bytes.
  *
  * srm_probe_mfma: `blocks` work-groups of four wavefronts each issue `iters`
- * rounds of four independent 32x32x16 bf16 matrix-core products on register
+ * rounds of eight independent 16x16x32 bf16 matrix-core products on register
  * operands and write one fp32 sum per lane to d_out[blocks * 256].
  * random_operands == 0: A = B = 1, every sum is 1024 * iters (checkable).
  * random_operands != 0: operand elements pseudo-random in (-1, 1), which costs

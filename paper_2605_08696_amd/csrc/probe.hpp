@@ -28,14 +28,15 @@ __global__ __launch_bounds__(256) void probe_copy_kernel(const u32x4_t *__restri
     }
 }
 
-// Every wavefront issues `iters` rounds of four independent 32x32x16 bf16 products into four fp32
-// accumulator tiles held in registers (no memory traffic inside the loop), then writes one sum per
-// lane.  With A = 1 and B = 1 every accumulator element ends at 16 * iters, so the written value is
-// 4 * 16 * 16 * iters per lane (16 accumulator registers per tile): checkable on the host.  With
-// random_operands the operand elements are pseudo-random values in (-1, 1), different per lane and
-// element: the matrix cores draw more power on such data than on constants, and the clock the chip
-// holds (hence the rate) is lower; the sums are then only finite, not predictable.
-__global__ __launch_bounds__(256) void probe_mfma_kernel(float *__restrict__ out, int iters, float a_val,
+// Every wavefront issues `iters` rounds of eight independent 16x16x32 bf16 products, the ones that the
+// GEMMs are made of, into eight fp32 accumulator tiles held in registers (no memory traffic inside the
+// loop), then writes one sum per lane.  With A = 1 and B = 1 every accumulator element ends at
+// 32 * iters, so the written value is 8 * 4 * 32 * iters per lane (4 accumulator registers per tile):
+// checkable on the host.  With random_operands the operand elements are pseudo-random values in
+// (-1, 1), different per lane and element: the matrix cores draw more power on such data than on
+// constants, and the clock the chip holds (hence the rate) is lower; the sums are then only finite,
+// not predictable.
+__global__ __launch_bounds__(256, 2) void probe_mfma_kernel(float *__restrict__ out, int iters, float a_val,
                                                          int random_operands)
 {
     bf16x8_t a, b;
@@ -51,15 +52,20 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(float *__restrict__ out
             b[i] = (bf16)((float)(int32_t)h * (1.0f / 2147483648.0f));
         }
     }
-    f32x16_t c0 = {}, c1 = {}, c2 = {}, c3 = {};
-    for (int it = 0; it < iters; ++it) {
-        c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c0, 0, 0, 0);
-        c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c1, 0, 0, 0);
-        c2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c2, 0, 0, 0);
-        c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c3, 0, 0, 0);
-    }
+    f32x4_t c[8] = {};
+    // (Room for 256 registers: with more the compiler copies each product from and to accumulation registers.  The empty
+    // statement keeps a tile where it is, which else wanders through overlapping registers: 1.33 PFLOP/s on random operands so, 2.22 now.)
+#pragma clang loop unroll(disable)
+    for (int it = 0; it < iters; ++it)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c[t], 0, 0, 0);
+            asm volatile("" : "+v"(c[t]));
+        }
     float s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s += c0[i] + c1[i] + c2[i] + c3[i];
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s += c[t][i];
     out[(int64_t)blockIdx.x * 256 + threadIdx.x] = s;
 }

@@ -2011,7 +2011,7 @@ extern "C" int srm_probe_mfma(float *d_out, int32_t blocks, int32_t iters, int32
     hipLaunchKernelGGL(probe_mfma_kernel, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), d_out, iters, 1.0f,
                        random_operands ? 1 : 0);
     HIP_TRY(hipGetLastError());
-    if (flop) *flop = (double)blocks * 4 /*wavefronts*/ * iters * 4 /*tiles*/ * (2.0 * 32 * 32 * 16);
+    if (flop) *flop = (double)blocks * 4 /*wavefronts*/ * iters * 8 /*tiles*/ * (2.0 * 16 * 16 * 32);
     return SRM_OK;
 }
 
