@@ -54,7 +54,8 @@ __global__ __launch_bounds__(256, 2) void probe_mfma_kernel(float *__restrict__ 
     }
     f32x4_t c[8] = {};
     // (Room for 256 registers: with more the compiler copies each product from and to accumulation registers.  The empty
-    // statement keeps a tile where it is, which else wanders through overlapping registers: 1.33 PFLOP/s on random operands so, 2.22 now.)
+    // statement keeps a tile where it is, which else wanders through overlapping registers.  Random operands: 1.33 | 2.22
+    // PFLOP/s.)
 #pragma clang loop unroll(disable)
     for (int it = 0; it < iters; ++it)
 #pragma unroll

@@ -560,10 +560,10 @@ static int launch_bf16_small(const bf16 *A, const bf16 *W, int M, int N, int K, 
 // ring depth of a tile for sweeps, 9 / 10 pin the persistent / one-tile-per-work-group form of 256x256, 11 .. 15 the
 // slice form with tiles of 16x16, 32x16, 32x32, 64x32 and 64x64; 16 = 192x256 (8 waves), 17 = 96x128, 18 = 128x64 (4
 // waves, ring of four).  min_bn > 64 rules out the 64-wide tile (the LM
-// head's partial buffers are sized for column tiles >= 128).  Measured on C4's
-// shapes over 512 .. 16384 rows: the big tile wins once it fills most of the chip in
-// whole rounds (one block per CU: 384 tiles are two rounds at 75 %, and lose to 1536
-// tiles of 128x128); 128x128 wins over 64x64 from about 144 blocks on.
+// head's partial buffers are sized for column tiles >= 128).  The big tile wins once it fills most of the chip in
+// whole rounds (one block per CU; us, 128x128 | 256x256, rows x columns x K: 12544 x 1024 x 1024, 196 tiles: 31.9 | 28.1, 5120
+// x 4096 x 1024, 320: 43.6 | 46.1, 6144, 384: 48.2 | 47.2, 6700, 432: 58.3 | 48.4, 13000, 816: 104.3 | 94.2); 128x128 wins
+// over 64x64 from about 144 blocks on (700 x 4096 x 1024, 192: 10.2 | 11.4; 2048 x 1024 x 1024, 128: 9.9 | 8.7).
 constexpr int kNumTiles = 19;
 static int choose_tile(int64_t M, int N, int K, int min_bn)
 {
@@ -579,25 +579,26 @@ static int choose_tile(int64_t M, int N, int K, int min_bn)
 }
 // Launches whose 256x256 tiles do not fill the chip and whose 128x128 tiles leave the last round part empty: the tile
 // that makes one round of it (-1: none does, choose_tile decides).  Measured (us, choose_tile's tile | this; rows x
-// columns x K): 128x64 up to 256 tiles: 1300 x 1024 x 4096: 27.7 | 23.4, 2048 x 1024 x 1024: 11.8 | 11.3, 700 x 2048 x
-// 1024: 10.2 | 8.9 (320 tiles: 14.9 | 18.0).  96x128 up to 256: 2500 x 1024 x 4096: 34.1 | 30.2, 3000 x 1024 x 1024:
-// 15.4 | 13.6, 700 x 4096 x 1024: 14.1 | 12.4 (296: 16.3 | 21.6).  192x256 from 188 to 256: 2500 x 4096 x 1024: 33.4 |
-// 28.1, 9000 x 1024 x 4096: 103 | 79 (176: 23.7 | 26.2; 304: 34.9 | 49.4; not while the 128x128 tiles fit two per CU,
-// where its rows are padding: 1000 x 8192 x 2048: 40.1 | 45.3, 200 x 32000 x 1024: 28.1 | 31.0), and two or three rounds of
-// it that are full where the 256x256 tile's are not: 9000 x 4096 x 1024, 752 of 768: 89.9 | 81.8 (with K = 512 not with
-// vectors of fp32 to store: residual 9000 x 4096: 68.1 | 71.4, fp32 rows of odd width 88.9 | 93.5; GELU 57.1 | 54.9).  Every
-// tile gives the same bits.
+// columns x K): 128x64 up to 256 tiles: 1300 x 1024 x 4096: 24.6 | 20.3, 2048 x 1024 x 1024: 8.7 | 8.1, 700 x 2048 x
+// 1024: 8.4 | 8.0 (384 tiles: 10.2 | 12.9).  96x128 up to 256: 2500 x 1024 x 4096: 27.6 | 25.1, 3000 x 1024 x 1024:
+// 10.6 | 9.5, 700 x 4096 x 1024: 10.2 | 9.2 (296: 10.6 | 16.4).  192x256 from 188 to 256: 2500 x 4096 x 1024: 27.9 |
+// 22.3 (the 256x256 tile 24.7), 9000 x 1024 x 4096: 91.9 | 65.4 (77.7), 10240 x 1024 x 4096: 82.5 | 69.3 (176 tiles: 27.3 |
+// 21.2, 304: 27.7 | 41.2; not while the 128x128 tiles fit two per CU, where its rows are padding: 1000 x 8192 x 2048: 30.8 |
+// 34.4, 200 x 32000 x 1024: 23.7 | 27.7), and two or three rounds of it that are full where the 256x256 tile's are not:
+// 9000 x 4096 x 1024, 752 of 768: 73.2 | 67.6 (256x256: 70.8), GELU 80.4 | 76.5, residual 6000 x 4096 x 1024: 63.8 | 64.6
+// (with K = 512 not with vectors of fp32 to store: residual 9000 x 4096: 64.3 | 68.9, fp32 rows of odd width 81.3 | 85.8;
+// GELU 51.3 | 52.5).  Every tile gives the same bits.
 // At most one 64x64 tile per CU (one pass of a larger call; calls that small take the slice form): that tile on its deep
-// ring (us, 64x64 | 128x64: 200 x 1024 x 1024: 7.5 | 8.4, 1000 x 512 x 2048: 11.7 | 13.3, 512 x 1024 x 4096: 18.8 | 20.2).
+// ring (us, 64x64 | 128x64: 200 x 1024 x 1024: 8.2 | 8.1, 1000 x 512 x 2048: 9.1 | 11.6, 512 x 1024 x 4096: 15.4 | 18.9).
 // Rows of odd width (N % 4) are stored by element, which the small tiles spread over more wavefronts: where choose_tile
-// takes the 64x64 tile, that stays up to about one tile per CU (300 x 1022 x 1024: 9.0 | 9.7, with the residual epilogue
-// 12.2 | 16.0; 1800 x 514 x 4096, 261 tiles: 20.1 | 22.7; 297: 26.0 | 21.8), and, unless the epilogue is a plain store, for
-// short k loops beyond (residual: 2100 x 1022 x 512: 14.8 | 20.4, x 1024: 19.0 | 22.4, x 4096: 41.9 | 38.0; store, x 512:
-// 11.5 | 10.7).
+// takes the 64x64 tile, that stays up to about one tile per CU (300 x 1022 x 1024: 8.5 | 8.9, with the residual epilogue
+// 10.4 | 15.0; 1800 x 514 x 4096, 261 tiles: 20.7 | 22.5; 297: 25.3 | 21.6), and, unless the epilogue is a plain store, for
+// short k loops beyond (us, 64x64 | 96x128, residual: 2100 x 1022 x 512: 13.8 | 19.1, x 1024: 18.0 | 22.2, x 4096: 40.7 |
+// 38.5; store, x 512: 10.0 | 9.2).
 // slow_update: a state update in the epilogue with a short k loop in front of it or a state in 16 bits, whose rows the
 // 64x64 tile takes with twice the wavefronts: 2300 x 512 x 512: 9.6 | 11.0, state in 16 bits 10.6 | 13.4, 2049 x 1024 x
 // 1024 so: 15.3 | 19.3; with K = 1024 and a state in 32 bits: 15.6 | 15.0.  (Larger launches than one round of 128x64 take
-// the 96x128 tile all the same: 2300 x 1024 x 1024, 16 bits: 23.0 | 20.2.)
+// the 96x128 tile all the same: 2300 x 1024 x 1024, 16 bits: 23.0 | 20.2.  These with 32x32x16 products.)
 static int choose_one_round_tile(int64_t M, int N, int K, bool plain_store, bool slow_update, bool fp32_store)
 {
     if (K < 512) return -1;                          // (rings of four k tiles)
