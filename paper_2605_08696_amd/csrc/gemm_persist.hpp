@@ -10,7 +10,8 @@
 //     half 1 of T: MFMAs of the other 32 k | operands of T+1's first half | loads of W of T+2 (unit 2T: A of T is done)
 // With two and a half tiles instead of two, loads are issued in both halves: a CU takes a load of 1 KB in about 16
 // clocks, 1024 per k tile of 2048 clocks of MFMAs, and all in one half they make the wavefronts wait for their turn to
-// issue (16384 x 1024 x 4096: 2555 clocks per k tile with the loads in one half, 2217 without any).
+// issue (16384 x 1024 x 4096: 2555 clocks per k tile with the loads in one half, 2405 in both, 2217
+// without any).
 // The epilogue stages its stores through the unit of the last k tile's W (32 KB, free since that k tile's barrier),
 // sixteen rows at a time; everything else keeps filling under it.
 #pragma once

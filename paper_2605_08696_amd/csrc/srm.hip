@@ -1036,7 +1036,8 @@ static bool token_mix_one_kernel(const srm_model *m, int64_t rows)
 // Some dozens of rows of a bf16 model above that: the in-projection still normalises its rows, while tiles of 16 x 16 are one
 // round of the chip (the up-projection has more of them and leaves that to a LayerNorm launch).  Decode steps of the large
 // model (us, without | with): 17 rows 422 | 407, 24 with combined heads 443 | 440, 37: 445 | 443, 50: 446 | 443, 64 with a
-// state in 16 bits 452 | 446.
+// state in 16 bits 452 | 446.  Of eight layers at other widths: d = 64, 17 rows 135 | 132, 1000: 154 | 147; 128, 17: 140 | 133,
+// 500: 152 | 146; 320, 40: 166 | 160; 768, 17: 184 | 179, 80: 203 | 198; 1024, 64: 212 | 205.
 static bool in_projection_normalises(const srm_model *m, int64_t rows)
 {
     if (m->noproj || m->wsize != 2 || !lna_tiles_ok(rows, m->dm, m->d)) return false;

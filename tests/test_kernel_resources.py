@@ -9,7 +9,7 @@ import subprocess
 
 import pytest
 
-import paper_2605_08696_amd as srm
+from paper_2605_08696_amd import build
 
 msgpack = pytest.importorskip("msgpack")
 
@@ -17,8 +17,9 @@ msgpack = pytest.importorskip("msgpack")
 @pytest.fixture(scope="module")
 def code_object():
     """The gfx950 ELF inside the offload bundle of libsrm.so."""
-    path = os.path.join(os.path.dirname(srm.__file__), "libsrm.so")
-    data = open(path, "rb").read()
+    if not os.path.exists(build.LIB):
+        build.build_lib()
+    data = open(build.LIB, "rb").read()
     base = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
     (n,) = struct.unpack_from("<Q", data, base + 24)
     at = base + 32
