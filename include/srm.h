@@ -51,6 +51,20 @@
  *     SRM_READ_AHEAD=0   LayerNorm launches without the work-groups that read the
  *                        matrices of the next launches (same bits);
  *     SRM_MEGAKERNEL, SRM_MEGA_BLOCKS   see srm_generate_one_kernel_blocks.
+ *     SRM_ONE_KERNEL_STEP=0  steps of a handful of samples by the step kernels
+ *                        (sums in another order).  Otherwise srm_decode_step and
+ *                        its sampled forms run as one kernel for up to 4 samples
+ *                        of a bf16 model of d_model 512 or 1024 and up to 8 of an
+ *                        fp32 one of 256, mlp_expansion 4, one matrix per head,
+ *                        at least six layers, and so do all steps of
+ *                        srm_generate for those with projections and at least
+ *                        six layers times steps (SRM_MEGAKERNEL unset); not on a
+ *                        stream that is being captured.  Such kernels run one at
+ *                        a time on a device, in the order of the calls, whatever
+ *                        their streams.  Their waits are bounded like those of
+ *                        the one-kernel path of srm_generate (see there): should
+ *                        one give up, the tokens of the call are -1 and its state
+ *                        is undefined.
  */
 #ifndef SRM_H
 #define SRM_H
@@ -224,8 +238,9 @@ int srm_decode_step_sampled(srm_model *m, int64_t B, int32_t pos, const int32_t 
  * captured, the steps are launched one by one instead.  temperature = 0 is
  * greedy; temperature > 0 samples as srm_decode_step_sampled does.  Results are
  * identical to G srm_decode_step(_sampled) calls, except that a call which
- * qualifies for the one-kernel path (see srm_generate_one_kernel_blocks) runs
- * all G steps in one cooperative launch, with fp32 sums in another order: equal
+ * qualifies for a one-kernel path (see SRM_ONE_KERNEL_STEP above and
+ * srm_generate_one_kernel_blocks) runs
+ * all G steps in one launch, with fp32 sums in another order: equal
  * to the step calls up to fp32 rounding, token-exact unless two scores tie
  * within that rounding.  Such a call must not be made under stream capture.
  * The one-kernel path synchronises its work-groups with bounded waits; should a
@@ -516,7 +531,9 @@ size_t srm_linear_argmax_noalloc_max_bytes(void);
  * costs 4L + 1 barriers instead of 6L + 7 kernel launches.  Same results up to
  * the fp32 summation order.  Environment: SRM_MEGAKERNEL=0 switches it off,
  * SRM_MEGAKERNEL=2 takes it whatever the model's size, SRM_MEGA_BLOCKS=n sets
- * the grid (default 16, at most 64).
+ * the grid (default 16, at most 64).  (Calls that the steps of
+ * SRM_ONE_KERNEL_STEP cover take those, with a grid of their own that this
+ * function does not report, unless SRM_MEGAKERNEL is set.)
  */
 int32_t srm_generate_one_kernel_blocks(const srm_model *m, int64_t B);
 

@@ -1,5 +1,6 @@
 // libsrm: C ABI and step scheduler for SRM generation on gfx950.
 // The exported calls are declared and documented in include/srm.h.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -61,6 +62,11 @@ struct LayerDev {
     const void *w_in, *w_out, *w_up, *w_down;
 };
 
+struct FewLayer;              // (few.hpp)
+typedef unsigned long long few_word;
+constexpr int kFewDevices = 64;                      // devices that few_launch keeps an event for
+constexpr int kFewMaxLayers = 64;                    // their pointers are kept in LDS
+
 struct srm_model {
     srm_config cfg;
     int device;
@@ -79,6 +85,9 @@ struct srm_model {
     size_t wsize;          // bytes per matrix element
     void *slab;
     MegaLayer *mega_layers;   // device copy of the layers' pointers for the one-kernel small-batch path, or null
+    FewLayer *few_layers;     // ... and for the steps of few.hpp, or null,
+    void *few_slab;           // which read matrices packed for them
+    const void *few_head;
     const void *embed, *head;
     const float *lnf_g, *lnf_b;
     std::vector<LayerDev> layers;
@@ -162,10 +171,37 @@ static int model_geometry(const char *who, const srm_config *cfg, srm_model *m)
     m->wsize = cfg->weight_dtype == SRM_BF16 ? 2 : 4;
     m->slab = nullptr;
     m->mega_layers = nullptr;
+    m->few_layers = nullptr;
+    m->few_slab = nullptr;
+    m->few_head = nullptr;
     m->gexec = nullptr;
     m->gkey = {0, nullptr, nullptr, nullptr, nullptr, 0.0f, 0, 1.0f, nullptr, 0, nullptr, 0};
     return SRM_OK;
 }
+
+// Models whose steps of a few rows can be one kernel (few.hpp), the rows that are, and the columns (and computing wavefronts)
+// of a work-group.  Measured per step (us, step kernels | one kernel): d = 1024, 16 layers, 32000 tokens: 1 row 349 | 196, 2:
+// 355 | 234, 4: 360 | 288; without projections 299 | 148, 302 | 170, 305 | 202; d = 512, 8 layers: 1 row 136 | 73, 2: 137 | 82, 4:
+// 138 | 98, without projections 124 | 54, 4: 131 | 69; fp32, d = 256, 4 layers, 4096 tokens, steps of one launch: 1 row 80 | 32, 8:
+// 84 | 52.  (Eight rows of d = 512 with projections: 141 | 143.)  Eight columns instead of four: d = 1024, 1 row 231 | 213, 4 rows
+// 333 | 323; fp32, 1 row 31 | 29, 8 rows 52 | 55.
+static int few_max_rows(const srm_model *m)
+{
+    if (m->dm != m->d || m->ff != 4 * m->d || m->L > kFewMaxLayers || m->V < 4) return 0;
+    if (m->wsize == 2) return m->d == 512 || m->d == 1024 ? 4 : 0;
+    return m->d == 256 && !m->noproj ? 8 : 0;
+}
+static bool few_shape_ok(const srm_model *m) { return few_max_rows(m) > 0; }
+static int few_columns(const srm_model *m) { return m->wsize == 2 ? 8 : 4; }
+static int few_bucket(int64_t B) { return B <= 1 ? 1 : B <= 2 ? 2 : B <= 4 ? 4 : 8; }         // rows the kernel is unrolled for
+// Bytes of its words in the workspace (rows: the rows that the kernel is unrolled for).
+static size_t few_bytes(const srm_model *m, int64_t rows)
+{
+    const size_t gw = m->wsize == 2 ? m->ff / 2 : m->ff;
+    return (size_t)rows * ((size_t)2 * m->d + gw + 2 * (m->d / few_columns(m))) * sizeof(few_word) + 256;
+}
+
+static int few_pack(srm_model *m);
 
 extern "C" int srm_init_weights(const srm_config *cfg, const srm_host_weights *w, srm_model **out)
 {
@@ -310,6 +346,10 @@ extern "C" int srm_init_weights(const srm_config *cfg, const srm_host_weights *w
             return fail(SRM_EHIP, "srm_init_weights: layer table: %s", hipGetErrorString(e));
         }
     }
+    if (few_shape_ok(m)) {
+        const int rc = few_pack(m);
+        if (rc != SRM_OK) { srm_free(m); return rc; }
+    }
     *out = m;
     return SRM_OK;
 }
@@ -319,6 +359,8 @@ extern "C" void srm_free(srm_model *m)
     if (!m) return;
     if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
     if (m->mega_layers) (void)hipFree(m->mega_layers);
+    if (m->few_layers) (void)hipFree(m->few_layers);
+    if (m->few_slab) (void)hipFree(m->few_slab);
     if (m->slab) (void)hipFree(m->slab);
     delete m;
 }
@@ -401,7 +443,8 @@ static Workspace carve(const srm_model *m, void *base, int64_t rows)
 extern "C" size_t srm_workspace_bytes(const srm_model *m, int64_t rows)
 {
     if (!m || rows <= 0) return 0;
-    return carve(m, nullptr, rows).bytes;
+    const int few = few_max_rows(m);                 // the words of few.hpp lie behind the row arrays
+    return carve(m, nullptr, rows).bytes + (few ? few_bytes(m, few_bucket(std::min<int64_t>(rows, few))) : 0);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1303,6 +1346,10 @@ static int decode_batch(srm_model *m, const DecodeArgs &a, void *ws, size_t work
     return SRM_OK;
 }
 
+static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st);
+static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
+                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st);
+
 static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t pos, const int32_t *d_tok_in,
                               void *d_state, int32_t *d_tok_out, float *d_logits, float *d_hidden,
                               void *d_workspace, size_t workspace_bytes, void *hip_stream, float temperature,
@@ -1316,9 +1363,17 @@ static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t 
     if (temperature > 0.0f && top_p < 1.0f && !d_logits)
         return fail(SRM_EINVAL, "%s: top_p < 1 needs a logits buffer", who);
     SRM_TRY(check_device(m));
+    hipStream_t st = as_stream(hip_stream);
+    if (few_ok(m, B, 1, workspace_bytes, st)) {
+        SRM_TRY(few_run(m, B, pos, 1, d_tok_in, d_tok_out, nullptr, d_state, temperature, seed, d_logits, d_hidden,
+                        d_workspace, st));
+        if (!(temperature > 0.0f && top_p < 1.0f)) return SRM_OK;
+        return nucleus(d_logits, B, m->V, Sampling{temperature, seed, pos, nullptr, nullptr, top_p}, d_tok_out, nullptr, nullptr,
+                       0, nullptr, carve(m, d_workspace, B).slow, st);
+    }
     const DecodeArgs a{B, pos, nullptr, nullptr, 0, d_tok_in, d_state, d_tok_out, d_logits, d_hidden, TokenStore(),
                        temperature, seed, top_p};
-    return decode_batch(m, a, d_workspace, workspace_bytes, as_stream(hip_stream));
+    return decode_batch(m, a, d_workspace, workspace_bytes, st);
 }
 
 extern "C" int srm_decode_step(srm_model *m, int64_t B, int32_t pos, const int32_t *d_tok_in, void *d_state,
@@ -1364,6 +1419,24 @@ extern "C" int srm_decode_step_ragged(srm_model *m, int64_t B, int32_t *d_pos, i
     const DecodeArgs a{B, 0, nullptr, d_pos, advance != 0, d_tok_in, d_state, d_tok_out, d_logits, nullptr, TokenStore(),
                        temperature, seed, top_p};
     return decode_batch(m, a, d_workspace, workspace_bytes, as_stream(hip_stream));
+}
+
+// ------------------------------------------------------------------ few samples: steps as one kernel (few.hpp)
+// Whether G steps of B samples run as one kernel: the shapes of few_max_rows, a stream that is not being captured, and at least
+// six layers or layers times steps.  That is faster from there on at every size (us, step kernels | one kernel, d = 1024 with
+// projections, 4 rows | 1 row: 6 layers 137 | 118, 134 | 79; 8: 168 | 146, 163 | 98; 24: 521 | 417, 507 | 281; d = 512: 6 layers
+// 117 | 77, 114 | 59; fp32, d = 256: 8 rows 84 | 52, 1 row 80 | 32).  Shallower models have little to gain and keep a step
+// whose sums are, bit for bit, those of the ragged step and of larger batches.
+// SRM_ONE_KERNEL_STEP=0 in the environment keeps the step kernels.
+static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
+{
+    if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || m->device >= kFewDevices) return false;
+    if (G * m->L < 6) return false;
+    const char *e = getenv("SRM_ONE_KERNEL_STEP");
+    if (e && e[0] == '0') return false;
+    if (srm_workspace_bytes(m, B) > workspace_bytes || m->d / few_columns(m) > device_cus()) return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
 }
 
 // ------------------------------------------------------------------ generate, few samples: one persistent kernel
@@ -1477,6 +1550,8 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
                     (long long)std::min<int64_t>(B, 256));
     SRM_TRY(check_device(m));
     hipStream_t st = as_stream(hip_stream);
+    if (!topp && !d_pos && !eos_plus1 && !getenv("SRM_MEGAKERNEL") && few_ok(m, B, G, ws_bytes, st))
+        return few_run(m, B, pos0, G, d_tok, d_tok, d_tokens_out, d_state, temperature, seed, nullptr, nullptr, d_workspace, st);
     if (!topp && !d_pos && !eos_plus1 && srm_workspace_bytes(m, B) <= ws_bytes) {
         const int nblk = mega_blocks(m, B);
         if (nblk > 0)
@@ -1839,7 +1914,7 @@ extern "C" size_t srm_workspace_bytes_config(const srm_config *cfg, int64_t rows
     if (!cfg || rows <= 0) return 0;
     srm_model m;
     if (model_geometry("srm_workspace_bytes_config", cfg, &m) != SRM_OK) return 0;
-    return carve(&m, nullptr, rows).bytes;
+    return srm_workspace_bytes(&m, rows);
 }
 
 extern "C" int srm_prefill_ragged_plan(const srm_config *cfg, const int32_t *h_offsets, int32_t N,
@@ -2120,4 +2195,110 @@ extern "C" int srm_linear(int32_t dtype, int32_t epilogue, const void *d_A, cons
     else rc = fail(SRM_EINVAL, "srm_linear: unknown dtype %d", dtype);
     g_force_tile = -1;
     return rc;
+}
+
+// ------------------------------------------------------------------ few samples: steps as one kernel
+// (Included here so that its kernels come last in the code object: with 0.3 MB of them in front, the chains of short launches
+// of the others were up to 1 % slower, by where their own code then lies: sequence form 4 x 256 of the fp32 model 191.8 | 193.5 us.)
+#include "few.hpp"
+
+// The packed copies of a model's matrices and its table of layers.
+static int few_pack(srm_model *m)
+{
+    const size_t d = m->d, ff = m->ff, s = m->wsize, proj = m->noproj ? 0 : d * d * s, mlp = d * ff * s;
+    const size_t head = align_up((size_t)m->V, 4) * d * s, total = m->L * (2 * proj + 2 * mlp) + head;
+    hipError_t e = hipMalloc(&m->few_slab, total);
+    if (e != hipSuccess)
+        return fail(e == hipErrorOutOfMemory ? SRM_ENOMEM : SRM_EHIP, "srm_init_weights: hipMalloc(%zu): %s", total, hipGetErrorString(e));
+    unsigned char *at = static_cast<unsigned char *>(m->few_slab);
+    auto pack = [&](const void *W, size_t N, size_t K) {
+        const int64_t n = (int64_t)(align_up(N, 4) * K * s / 16);
+        hipLaunchKernelGGL(few_pack_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, nullptr, static_cast<const u32x4_t *>(W),
+                           reinterpret_cast<u32x4_t *>(at), (int)N, (int)(K * s / 16));
+        const void *p = at;
+        at += n * 16;
+        return p;
+    };
+    std::vector<FewLayer> fl(m->L);
+    for (int l = 0; l < m->L; ++l) {
+        const LayerDev &y = m->layers[l];
+        fl[l] = FewLayer{{y.ln1_g, y.ln1_b, y.ln2_g, y.ln2_b}, y.b_in, y.alpha, y.beta, y.lam, y.b_out, y.b_up, y.b_down,
+                         nullptr, nullptr, pack(y.w_up, ff, d), pack(y.w_down, d, ff)};
+        if (!m->noproj) {
+            fl[l].w_in = pack(y.w_in, d, d);
+            fl[l].w_out = pack(y.w_out, d, d);
+        }
+    }
+    m->few_head = pack(m->head, m->V, d);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&m->few_layers), sizeof(FewLayer) * m->L);
+    if (e == hipSuccess) e = hipMemcpy(m->few_layers, fl.data(), sizeof(FewLayer) * m->L, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    return e == hipSuccess ? SRM_OK : fail(SRM_EHIP, "srm_init_weights: packed matrices: %s", hipGetErrorString(e));
+}
+
+// The launch.  Its work-groups wait for each other, so all of them must become resident: they are at most one per CU (few_ok),
+// other kernels end by themselves (and mega.hpp's few work-groups leave room), and kernels of this kind run one at a time on
+// a device, in the order of their launches, whatever their streams: each launch waits for the event of the one before.  A
+// cooperative launch does as much by a queue of its own, which costs 20 us per launch instead of 5 (a step of 16 layers, d =
+// 1024: 211 | 195 us) and, once used, makes the later launches of the process slower (36 launches, 315 us: by 1 to 2 %).
+static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st)
+{
+    static std::mutex lock;
+    static hipEvent_t last[kFewDevices];             // kept until the process ends
+    const std::lock_guard<std::mutex> hold(lock);
+    hipEvent_t &ev = last[device];
+    if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    else HIP_TRY(hipStreamWaitEvent(st, ev, 0));
+    HIP_TRY(hipExtLaunchKernel(kern, dim3((unsigned)blocks), dim3((unsigned)threads), args, (size_t)lds, st, nullptr, ev, 0));
+    return SRM_OK;
+}
+
+template <typename TW, int D, int NWC, bool PROJ>
+static const void *few_kernel(int mb)
+{
+    switch (mb) {
+    case 1: return reinterpret_cast<const void *>(few_rows_kernel<TW, D, NWC, 1, PROJ>);
+    case 2: return reinterpret_cast<const void *>(few_rows_kernel<TW, D, NWC, 2, PROJ>);
+    case 4: return reinterpret_cast<const void *>(few_rows_kernel<TW, D, NWC, 4, PROJ>);
+    }
+    if constexpr (sizeof(TW) == 4) return reinterpret_cast<const void *>(few_rows_kernel<TW, D, NWC, 8, PROJ>);
+    else return nullptr;
+}
+
+static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
+                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st)
+{
+    const int mb = few_bucket(B), D = m->d, nwc = few_columns(m), nb = D / nwc;
+    const Workspace w = carve(m, ws, B);
+    const void *kern = m->wsize == 4 ? few_kernel<float, 256, 4, true>(mb)
+                       : m->noproj ? (D == 512 ? few_kernel<bf16, 512, 8, false>(mb) : few_kernel<bf16, 1024, 8, false>(mb))
+                                   : (D == 512 ? few_kernel<bf16, 512, 8, true>(mb) : few_kernel<bf16, 1024, 8, true>(mb));
+    if (!kern) return fail(SRM_EINVAL, "few_run: no kernel for %lld rows", (long long)B);
+    FewArgs a{};
+    a.layers = m->few_layers;
+    a.embed = m->embed; a.head = m->few_head;
+    a.lnf_g = m->lnf_g; a.lnf_b = m->lnf_b;
+    a.V = m->V; a.L = m->L; a.dh = m->dm / m->Hs; a.hrow = m->hrow; a.n_ctx = m->cfg.n_ctx;
+    a.eps = m->cfg.ln_eps;
+    a.B = (int)B; a.pos0 = pos0; a.G = G;
+    a.tok_in = tok_in; a.tok_out = tok_out; a.store = store;
+    a.state = state; a.state_half = m->shalf ? 1 : 0;
+    a.logits = logits; a.hidden = hidden;
+    a.temp = temperature; a.seed = seed;
+    unsigned char *base = static_cast<unsigned char *>(ws) + w.bytes;
+    a.xw = reinterpret_cast<few_word *>(base);
+    a.mw = a.xw + (size_t)mb * D;
+    a.gw = a.mw + (size_t)mb * D;
+    a.pw = a.gw + (size_t)mb * (m->wsize == 2 ? m->ff / 2 : m->ff);
+    a.flag = reinterpret_cast<unsigned *>(a.pw + (size_t)mb * nb * 2);
+    a.max_polls = 1u << 21;                          // a second or two
+    const int n = (int)(few_bytes(m, mb) / 16), n_store = store ? (int)B * G : 0;
+    hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
+                       reinterpret_cast<u32x4_t *>(base), n, w.slow, store, n_store);
+    HIP_TRY(hipGetLastError());
+    const int lds = few_lds_bytes((int)m->wsize, D, nwc, mb);
+    HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    void *args[] = {&a};
+    return few_launch(m->device, kern, nb, (kFewGather + nwc) * 64, lds, args, st);
 }

@@ -1,0 +1,219 @@
+"""Decode steps of a handful of samples as one kernel (a bf16 model of 512 or 1024 channels, an fp32 one of 256) against the
+oracle and against the step kernels (the library's switch)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import srm_synth
+from gpu_util import to_dev, rel_err_rows, check_tokens
+
+pytestmark = pytest.mark.gpu
+SWITCH = "SRM_ONE_KERNEL_STEP"
+
+
+@pytest.fixture(scope="module")
+def srm():
+    import paper_2605_08696_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+@pytest.fixture(scope="module")
+def orc_mod(oracle_mod):
+    return oracle_mod
+
+
+def _launches(fn):
+    """How often the kernels of few.hpp run in fn()."""
+    from torch.profiler import profile, ProfilerActivity
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    return sum("few_rows_kernel" in e.name for e in prof.events())
+
+
+def _steps(model, cfg, B, T, toks, garbage=None, **how):
+    """T steps on given tokens in a workspace full of `garbage`, with a guard behind it."""
+    n = model.workspace_bytes(B)
+    buf = torch.empty(n + 4096, dtype=torch.uint8, device="cuda")
+    buf.random_(0, 256) if garbage is None else buf.fill_(garbage)
+    guard = buf[n:].clone()
+    st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+    lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+    hd = torch.empty((B, cfg.d_model), dtype=torch.float32, device="cuda")
+    tc = to_dev(toks).t().contiguous()
+    res = []
+    for t in range(T):
+        model.decode_step(B, t, tc[t], st, out, logits=lg, hidden=hd, workspace=buf[:n], **how)
+        res.append((lg.clone(), hd.clone(), out.clone()))
+    torch.cuda.synchronize()
+    assert torch.equal(buf[n:], guard)
+    return res, st
+
+
+CASES = [("bf16", 1024, 1, {}), ("bf16", 1024, 3, dict(state_dtype="fp16")), ("bf16", 1024, 4, dict(head_layout="row", n_heads=1)),
+         ("bf16", 512, 1, dict(state_dtype="fp16")), ("bf16", 512, 2, dict(head_layout="column")), ("bf16", 512, 4, {}),
+         ("bf16", 1024, 2, dict(use_projections=False)), ("bf16", 512, 3, dict(use_projections=False, state_dtype="fp16")),
+         ("fp32", 256, 1, {}), ("fp32", 256, 5, dict(state_dtype="fp16")), ("fp32", 256, 8, {})]
+
+
+@pytest.mark.parametrize("dtype,d,B,variant", CASES)
+@pytest.mark.parametrize("vocab", [333, 1400])
+def test_one_kernel_step_matches_oracle_and_step_kernels(srm, orc_mod, dtype, d, B, variant, vocab, monkeypatch):
+    """Rows below, at and above the ones that the kernel is unrolled for; vocabularies that are no multiple of four and leave
+    work-groups without columns, or with several groups of them; garbage of two kinds in the workspace."""
+    kw = dict(vocab=vocab, d_model=d, n_layers=6, n_heads=4, n_ctx=12, weight_dtype=dtype, seed=53)
+    kw.update(variant)
+    cfg = srm_synth.tiny_config(**kw)
+    w = srm_synth.make_weights(cfg, stress=True)
+    model = srm.Model(cfg, w)
+    T = 4
+    toks = srm_synth.make_prompts(cfg, batch=B, length=T)
+    ref = orc_mod.Oracle(cfg, w, "f64").recurrent_forward(toks)
+    print(f"one-kernel step {dtype} d={d} B={B} V={vocab} {variant}", flush=True)
+    one, st = _steps(model, cfg, B, T, toks)
+    again, st2 = _steps(model, cfg, B, T, toks, garbage=0)
+    monkeypatch.setenv(SWITCH, "0")
+    many, st3 = _steps(model, cfg, B, T, toks)
+    half = cfg.state_dtype == "fp16"
+    tol = (4e-2 if half else 2e-2) if dtype == "bf16" else (1e-3 if half else 1e-4)
+    for t in range(T):
+        assert all(torch.equal(a, b) for a, b in zip(one[t], again[t]))         # a fixed order of sums: the same bits
+        assert rel_err_rows(one[t][0].cpu().numpy(), ref["logits"][:, t]) <= tol
+        assert rel_err_rows(one[t][1].cpu().numpy(), ref["hidden"][:, t]) <= tol
+        assert rel_err_rows(one[t][0].cpu().numpy(), many[t][0].cpu().numpy()) <= tol
+        assert torch.equal(one[t][2].long(), one[t][0].argmax(dim=1))
+    assert torch.equal(st, st2)
+    assert (st.float() - st3.float()).abs().max() <= tol * st3.float().abs().max()
+    s_got = st.float().view(cfg.n_layers, B, cfg.d_model).permute(1, 0, 2).cpu().numpy()
+    s_ref = orc_mod.Oracle(cfg, w, "f64").greedy(toks, 1)["state"]
+    assert np.abs(s_got - s_ref).max() <= tol * np.abs(s_ref).max()
+    model.close()
+
+
+@pytest.mark.parametrize("B,half", [(1, False), (3, False), (8, False), (8, True)])
+def test_generation_in_one_kernel_matches_oracle(srm, orc_mod, B, half):
+    """Many steps of one launch, greedy and sampled, tokens exact, twice in the same workspace."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], state_dtype="fp16" if half else "fp32")
+    w = srm_synth.make_weights(cfg)
+    w["head"] = w["head"] * 25.0
+    prompts = srm_synth.make_prompts(cfg)[:B]
+    P, G = prompts.shape[1], 30
+    model = srm.Model(cfg, w)
+    orc = orc_mod.Oracle(cfg, w, "f64")
+    ws = model.new_workspace(B * P)
+    for temperature in (0.0, 0.7):
+        kw = {"temperature": temperature, "seed": 7} if temperature else {}
+        ref = orc.greedy(prompts, G, want_logits=True, **kw)
+        dp = to_dev(prompts)
+        for _ in range(2):
+            st, tk = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+            model.prefill(dp[:, :P - 1].contiguous(), 1, st, tk, workspace=ws)
+            tk.copy_(dp[:, P - 1])
+            out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+            print(f"generation in one kernel B={B} half={half} T={temperature}", flush=True)
+            model.generate(B, P - 1, G, tk, st, out, workspace=ws, **kw)
+            torch.cuda.synchronize()
+            got = out.cpu().numpy().T
+            ties = check_tokens(got, ref["tokens"], ref["margin"], np.abs(ref["logits"]).max(axis=2), rtol=1e-3 if half else 1e-4)
+            assert (tk.cpu().numpy() == got[:, -1]).all()
+            if not half:
+                assert ties == 0
+                s_got = st.view(cfg.n_layers, B, cfg.d_model).permute(1, 0, 2).cpu().numpy()
+                assert np.abs(s_got - ref["state"]).max() <= 1e-4 * np.abs(ref["state"]).max()
+
+
+def test_sampled_and_nucleus_steps_choose_from_their_own_logits(srm, orc_mod):
+    cfg = srm_synth.tiny_config(vocab=1001, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=31)
+    w = srm_synth.make_weights(cfg, stress=True)
+    w["head"] = srm_synth.round_to_bf16(w["head"] * 30.0)
+    model = srm.Model(cfg, w)
+    B, T, seed, pos = 4, 0.8, 5, 3
+    tok = to_dev(np.arange(B, dtype=np.int32) * 7)
+    st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+    lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+    ws = model.new_workspace(B)
+    for top_p in (None, 0.5):
+        for s in range(seed, seed + 6):
+            model.decode_step(B, pos, tok, st, out, logits=lg, workspace=ws, temperature=T, seed=s, top_p=top_p)
+            got, L = out.cpu().numpy(), lg.cpu().numpy().astype(np.float64)
+            for b in range(B):
+                want = (orc_mod.pick(L[b], T, s, pos, b) if top_p is None else orc_mod.pick_topp(L[b], T, top_p, s, pos, b))
+                assert got[b] == want
+
+
+def test_which_calls_run_as_one_kernel(srm, monkeypatch):
+    """By rows, layers and the switch, and never into a graph that is being captured."""
+    cfg = srm_synth.tiny_config(vocab=300, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    tok, out = torch.zeros(5, dtype=torch.int32, device="cuda"), torch.empty(5, dtype=torch.int32, device="cuda")
+
+    def step(B, ws=None, m=model):
+        st = m.new_state(B)
+        ws = m.new_workspace(B) if ws is None else ws
+        return lambda: m.decode_step(B, 0, tok[:B], st, out[:B], workspace=ws)
+
+    step(1)(), step(5)()
+    assert _launches(step(4)) == 1 and _launches(step(3)) == 1 and _launches(step(5)) == 0
+    side, st, ws = torch.cuda.Stream(), model.new_state(2), model.new_workspace(2)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        model.decode_step(2, 0, tok[:2], st, out[:2], workspace=ws)
+    assert _launches(graph.replay) == 0
+    monkeypatch.setenv(SWITCH, "0")
+    assert _launches(step(4)) == 0
+    monkeypatch.delenv(SWITCH)
+    shallow = dataclasses.replace(cfg, n_layers=3)
+    other = srm.Model(shallow, srm_synth.make_weights(shallow))
+    assert _launches(step(1, m=other)) == 0
+
+
+def test_calls_on_several_streams_and_threads(srm):
+    """Kernels whose work-groups wait for each other, launched from four threads on four streams into workspaces of their own,
+    with two models and other work in between: each stream's results are those of the same calls alone."""
+    import threading
+    models = []
+    for dtype, d in (("bf16", 1024), ("fp32", 256)):
+        cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=64, weight_dtype=dtype, seed=23)
+        models.append((cfg, srm.Model(cfg, srm_synth.make_weights(cfg))))
+
+    def job(k):
+        cfg, model = models[k % 2]
+        B = 1 + k
+        tok = to_dev((np.arange(B) * 11 + k).astype(np.int32))
+        st, ws = model.new_state(B), model.new_workspace(B)
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        busy = torch.zeros(1 << 20, device="cuda")
+        for t in range(40):
+            model.decode_step(B, t, tok, st, tok, logits=lg, workspace=ws)
+            busy += 1.0
+        return lg, st, tok
+
+    alone = [job(k) for k in range(4)]
+    torch.cuda.synchronize()
+    got, streams = [None] * 4, [torch.cuda.Stream() for _ in range(4)]
+
+    def run(k):
+        with torch.cuda.stream(streams[k]):
+            got[k] = job(k)
+
+    print("one-kernel steps from four threads", flush=True)
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for a, b in zip(alone, got):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_workspace_size_without_a_model(srm):
+    """The size computed from a configuration alone covers the words of the one-kernel steps too."""
+    for dtype, d in (("bf16", 1024), ("bf16", 512), ("fp32", 256), ("bf16", 256)):
+        cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=64, weight_dtype=dtype, seed=23)
+        model = srm.Model(cfg, srm_synth.make_weights(cfg))
+        for rows in (1, 2, 3, 4, 5, 8, 9, 300):
+            assert srm.workspace_bytes_config(cfg, rows) == model.workspace_bytes(rows), (dtype, d, rows)
