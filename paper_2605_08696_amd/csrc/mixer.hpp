@@ -657,3 +657,20 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
 // captured step needs no host-side update: ctr[0] = position, ctr[1] = step.  (Every step after the
 // first advances them in its first kernel, the embedding LayerNorm.)
 __global__ void counters_set_kernel(int *ctr, int pos, int step) { ctr[0] = pos; ctr[1] = step; }
+
+// Row b of x' and y': the last row of sequence b, source row seq_end[b + 1] - 1 - base (or (b + 1) len - 1 without seq_end),
+// clamped to [0, src_rows).  d and dm are multiples of 4.  One work-group per row: a trip to memory for the boundary, one for
+// the row, 3 us in all for one row or 256.
+template <typename T>
+__global__ void __launch_bounds__(256)
+last_rows_kernel(const float *__restrict__ x, const T *__restrict__ y, float *__restrict__ x_out, T *__restrict__ y_out, int d,
+                 int dm, int64_t len, const int32_t *__restrict__ seq_end, int64_t base, int64_t src_rows)
+{
+    typedef typename Raw4<T>::type raw_t;
+    const int64_t b = blockIdx.x;
+    const int64_t src = min(max(seq_end ? (int64_t)seq_end[b + 1] - 1 - base : (b + 1) * len - 1, (int64_t)0), src_rows - 1);
+    for (int c = threadIdx.x * 4; c < max(d, dm); c += 1024) {
+        if (c < d) *reinterpret_cast<f32x4_t *>(x_out + b * d + c) = *reinterpret_cast<const f32x4_t *>(x + src * d + c);
+        if (c < dm) *reinterpret_cast<raw_t *>(y_out + b * dm + c) = *reinterpret_cast<const raw_t *>(y + src * dm + c);
+    }
+}

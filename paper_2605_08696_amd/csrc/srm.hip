@@ -1130,6 +1130,29 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
     return SRM_OK;
 }
 
+// The rows of a prefill pass that matter behind the last layer's mixer, each sequence's last one: the state is written, and
+// the head reads nothing else.  n rows of the pass, n_call of the call; row b ends at seq_end[b + 1] - base (packed
+// sequences) or (b + 1) len.  n = 0: all rows.
+struct LastRows {
+    int64_t n = 0, n_call = 0, len = 0;
+    const int32_t *seq_end = nullptr;
+    int64_t base = 0;
+};
+// Whether a call of N sequences, `rows` rows, the shortest of `shortest`, continues on them.  The gathered rows lie in front of
+// the last MLP's activations in w.g, where N sequences of that length leave room.  Behind the gather the last layer's
+// out-projection, LayerNorm2 and MLP (3 / 4 of its products or more) run on N rows instead of all; what that saves grows with
+// the rows times the width, what it costs is the gather's launch, 3 to 5 us (us per call, all rows | last rows; N x positions:
+// d = 1024, 24 layers 1 x 64: 527 | 530, 64 x 3: 619 | 617, 8 x 32: 658 | 655, 256 x 16: 2026 | 1958, 256 x 128: 11833 | 11250; d = 512, 8
+// layers 1 x 64: 205 | 208, 8 x 32: 241 | 236, 64 x 64: 503 | 476; fp32, d = 256, 4 layers 32 x 16: 165 | 169, 256 x 3: 176 | 174,
+// 1024 x 8: 610 | 523).  A property of the whole call, so that results do not depend on its passes.
+static bool last_rows_ok(const srm_model *m, int64_t N, int64_t rows, int64_t shortest)
+{
+    return (rows - N) * m->d >= (1 << 17) &&
+           (size_t)(m->ff + m->dm) * m->wsize + (size_t)m->d * 4 + 512 <= (size_t)shortest * m->ff * m->wsize;
+}
+template <typename T>
+static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr, int64_t rows, hipStream_t st);
+
 // One block (token mixing + channel mixing) on `rows` token rows.  On entry
 // w.a holds LayerNorm1(x) of this layer; mix(l) turns w.u into w.mx.  With
 // norm_next, w.a leaves holding the next layer's LayerNorm1(x), or the final
@@ -1137,12 +1160,21 @@ static int token_mix(const srm_model *m, int l, const TokMixCall &c, int64_t row
 // With lnf (decode of a handful of rows, see ln_on_load): no LayerNorm kernels between the GEMMs.  From layer 1 on w.a
 // is not used: the in- and up-projection (and the fp32 LM head) normalise the rows of w.x themselves.  Layer 0 enters with w.a from the
 // embedding kernel as usual.  With ln1f (see in_projection_normalises) that holds for the in-projection alone.  With one_mix (see token_mix_one_kernel) w.a on entry is not used either.
-// call_rows: the rows of the whole call (rows are one of its passes; see slices_ok).
+// call_rows: the rows of the whole call (rows are one of its passes; see slices_ok).  With last rows, what follows the mixer
+// is done on those alone, and w.x leaves as them.
 template <typename T, typename MIX>
-static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, int64_t call_rows, hipStream_t st, MIX &&mix,
+static int block(const srm_model *m, int l, Workspace &w, int64_t rows, int64_t call_rows, hipStream_t st, MIX &&mix,
                  bool norm_next, void *fuse_state = nullptr, Sampling fuse_pos = Sampling(),
-                 void *np_state = nullptr, bool lnf = false, bool one_mix = false, bool ln1f = false)
+                 void *np_state = nullptr, bool lnf = false, bool one_mix = false, bool ln1f = false,
+                 const LastRows &last = LastRows())
 {
+    auto keep_last = [&] {
+        if (!last.n) return (int)SRM_OK;
+        SRM_TRY((gather_last_rows<T>(m, w, last, rows, st)));
+        rows = last.n;
+        call_rows = last.n_call;
+        return (int)SRM_OK;
+    };
     const LayerDev &y = m->layers[l];
     const int d = m->d, dm = m->dm, ff = m->ff;
     const LnArgs ln1 = (lnf || ln1f) && l > 0 ? LnArgs{w.x, y.ln1_g, y.ln1_b, m->cfg.ln_eps} : LnArgs();
@@ -1188,6 +1220,7 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
     } else if (m->noproj) {
         // non-projected layer: mixer on the LayerNorm output, its result added to x by the LayerNorm kernel
         SRM_TRY(mix(l));
+        SRM_TRY(keep_last());
         SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, w.x, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0, nullptr,
                                      0, w.mx, nullptr, pf_mlp)));
     } else if (fuse_state) {
@@ -1199,6 +1232,7 @@ static int block(const srm_model *m, int l, const Workspace &w, int64_t rows, in
         SRM_TRY((linear<EPI_STORE, T>(w.a, y.w_in, y.b_in, rows, dm, d, w.u, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                       MixArgs(), call_rows, ln1)));
         SRM_TRY(mix(l));
+        SRM_TRY(keep_last());
     }
     if (!m->noproj) {
         SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
@@ -1257,7 +1291,7 @@ struct DecodeArgs {
 template <typename T>
 static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb, void *ws, hipStream_t st)
 {
-    const Workspace w = carve(m, ws, nb);
+    Workspace w = carve(m, ws, nb);
     const int d = m->d, dm = m->dm;
     int32_t *pos_rows = a.pos_rows ? a.pos_rows + b0 : nullptr;
     auto slab = [&](int l) {       // rows b0.. of layer l's state
@@ -1769,17 +1803,24 @@ static int prefill_impl(srm_model *m, const int32_t *prompts, int N, int P, int 
     for (int64_t n0 = 0; n0 < N; n0 += per_pass) {
         const int64_t nc = std::min<int64_t>(per_pass, N - n0);
         const int64_t rows = nc * P;
-        const Workspace w = carve(m, ws, rows);
+        Workspace w = carve(m, ws, rows);
+        LastRows last;
+        if (last_rows_ok(m, N, (int64_t)N * P, P)) last = {nc, N, P, nullptr, 0};
         SRM_TRY((layernorm<T, true>(m, nullptr, 0, prompts + n0 * P, w.x, m->layers[0].ln1_g,
                                     m->layers[0].ln1_b, w.a, rows, st)));
         auto mix = [&](int l) {
             return prefill_mixer<T>(m, l, w, layer_state(m, state, l, Btot), (int)nc, P, chunk, nchunks, in_blocks, nullptr, 0, rows,
                                     n0, k, nullptr, 0, st);
         };
-        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, (int64_t)N * P, st, mix, l + 1 < m->L)));
+        for (int l = 0; l < m->L; ++l)
+            SRM_TRY((block<T>(m, l, w, rows, (int64_t)N * P, st, mix, l + 1 < m->L, nullptr, Sampling(), nullptr, false, false, false,
+                              l + 1 < m->L ? LastRows() : last)));
         // final LayerNorm of each prompt's last position only, packed [nc][d] into w.a
-        SRM_TRY((layernorm<T, false>(m, w.x + (size_t)(P - 1) * d, (int64_t)P * d, nullptr, nullptr, m->lnf_g,
-                                     m->lnf_b, w.a, nc, st)));
+        if (last.n)
+            SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, nc, st)));
+        else
+            SRM_TRY((layernorm<T, false>(m, w.x + (size_t)(P - 1) * d, (int64_t)P * d, nullptr, nullptr, m->lnf_g,
+                                         m->lnf_b, w.a, nc, st)));
         SRM_TRY((head_argmax<T>(m, w, w.a, nc, N, logits ? logits + (size_t)n0 * m->V : nullptr, next_tok, n0, k, st)));
     }
     return SRM_OK;
@@ -1823,6 +1864,8 @@ static int prefill_ragged_impl(srm_model *m, const int32_t *tokens, const int32_
     const int d = m->d;
     const int chunk = plan.chunk, nchunks = plan.nchunks;
     const bool in_blocks = scan_in_blocks(m, chunk, N, pmax_call);
+    int shortest = pmax_call;
+    for (int n = 0; n < N; ++n) shortest = std::min(shortest, h_off[n + 1] - h_off[n]);
     for (size_t pass = 0; pass + 1 < plan.first.size(); ++pass) {
         // as many whole prompts as the workspace holds
         const int n0 = plan.first[pass], n1 = plan.first[pass + 1];
@@ -1830,17 +1873,24 @@ static int prefill_ragged_impl(srm_model *m, const int32_t *tokens, const int32_
         for (int n = n0; n < n1; ++n) pmax = std::max(pmax, h_off[n + 1] - h_off[n]);
         const int nc = n1 - n0;
         const int64_t base = h_off[n0], rows = (int64_t)h_off[n1] - base;
-        const Workspace w = carve(m, ws, rows);
+        Workspace w = carve(m, ws, rows);
+        LastRows last;
+        if (last_rows_ok(m, N, h_off[N] - h_off[0], shortest)) last = {nc, N, 0, d_off + n0, base};
         SRM_TRY((layernorm<T, true>(m, nullptr, 0, tokens + base, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a,
                                     rows, st)));
         auto mix = [&](int l) {
             return prefill_mixer<T>(m, l, w, layer_state(m, state, l, state_batch), nc, chunk ? pmax_call : pmax, chunk,
                                     nchunks, in_blocks, d_off, base, rows, (int64_t)n0, k, slot, state_batch, st);
         };
-        for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, h_off[N] - h_off[0], st, mix, l + 1 < m->L)));
+        for (int l = 0; l < m->L; ++l)
+            SRM_TRY((block<T>(m, l, w, rows, h_off[N] - h_off[0], st, mix, l + 1 < m->L, nullptr, Sampling(), nullptr, false, false,
+                              false, l + 1 < m->L ? LastRows() : last)));
         // final LayerNorm of each prompt's last row, packed [nc][d] into w.a
-        SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, nc, st, d_off + n0, base,
-                                     rows)));
+        if (last.n)
+            SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, nc, st)));
+        else
+            SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, m->lnf_g, m->lnf_b, w.a, nc, st, d_off + n0, base,
+                                         rows)));
         FinalizeRagged rg{};
         rg.slot = slot;
         rg.nslots = state_batch;
@@ -1947,7 +1997,7 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
     for (int64_t b0 = 0; b0 < B; b0 += per_pass) {
         const int64_t nc = std::min<int64_t>(per_pass, B - b0);
         const int64_t rows = nc * T_;
-        const Workspace w = carve(m, ws, rows);
+        Workspace w = carve(m, ws, rows);
         SRM_TRY((layernorm<T, true>(m, nullptr, 0, tok + b0 * T_, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b,
                                     w.a, rows, st)));
         auto mix = [&](int l) {
@@ -2235,6 +2285,25 @@ static int few_pack(srm_model *m)
     if (e == hipSuccess) e = hipMemcpy(m->few_layers, fl.data(), sizeof(FewLayer) * m->L, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     return e == hipSuccess ? SRM_OK : fail(SRM_EHIP, "srm_init_weights: packed matrices: %s", hipGetErrorString(e));
+}
+
+// x and mx of a pass's last rows (LastRows) into w.g, in front of the MLP's activations; w becomes the workspace of those rows.
+template <typename T>
+static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr, int64_t rows, hipStream_t st)
+{
+    unsigned char *p = static_cast<unsigned char *>(w.g);
+    const size_t xb = align_up((size_t)lr.n * m->d * 4, 256), mb = align_up((size_t)lr.n * m->dm * sizeof(T), 256);
+    if (xb + mb + (size_t)lr.n * m->ff * sizeof(T) > (size_t)rows * m->ff * sizeof(T))
+        return fail(SRM_EINVAL, "gather_last_rows: no room");
+    float *x = reinterpret_cast<float *>(p);
+    T *mx = reinterpret_cast<T *>(p + xb);
+    hipLaunchKernelGGL((last_rows_kernel<T>), dim3((unsigned)lr.n), dim3(256), 0, st, w.x, static_cast<const T *>(w.mx), x, mx,
+                       m->d, m->dm, lr.len, lr.seq_end, lr.base, rows);
+    HIP_TRY(hipGetLastError());
+    w.x = x;
+    w.mx = mx;
+    w.g = p + xb + mb;
+    return SRM_OK;
 }
 
 // The launch.  Its work-groups wait for each other, so all of them must become resident: they are at most one per CU (few_ok),

@@ -1,0 +1,65 @@
+"""Prefill whose last layer continues on each prompt's last row alone: on both sides of the rules for the shortest prompt and
+for the rows (512 beyond the last ones, at this width), one pass or several, against the oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import srm_synth
+from gpu_util import to_dev, rel_err_rows
+
+pytestmark = pytest.mark.gpu
+
+MODELS = {"tiny": {}, "narrow mlp": dict(mlp_expansion=1), "bare": dict(use_projections=False),
+          "combined": dict(head_layout="combined"), "one layer": dict(n_layers=1)}
+
+
+@pytest.fixture(scope="module")
+def srm():
+    import paper_2605_08696_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+@pytest.mark.parametrize("lens", [[1, 600], [2, 520, 2], [3, 3, 530, 4], [4, 256, 258], [171] * 3, [513], [512]], ids=str)
+@pytest.mark.parametrize("name", list(MODELS))
+def test_prefill_of_the_last_rows_matches_oracle(srm, oracle_mod, name, lens):
+    cfg = srm_synth.tiny_config(vocab=301, d_model=256, n_layers=2, n_heads=4, n_ctx=600, weight_dtype="fp32", seed=31)
+    cfg = dataclasses.replace(cfg, **MODELS[name])
+    w = srm_synth.make_weights(cfg)
+    model, orc = srm.Model(cfg, w), oracle_mod.Oracle(cfg, w, "f64")
+    N, rows = len(lens), sum(lens)
+    rng = np.random.default_rng(rows)
+    prompts = rng.integers(0, cfg.vocab, (N, max(lens))).astype(np.int32)
+    toks = to_dev(np.concatenate([prompts[i, :n] for i, n in enumerate(lens)]))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    uniform = len(set(lens)) == 1
+    print(f"prefill of last rows {name} lens={lens}", flush=True)
+    got = []
+    for how in ["packed", "passes"] + ["uniform"] * uniform:
+        room = max(lens) + 1 if how == "passes" else rows
+        n = model.workspace_bytes(room)
+        if srm.prefill_ragged_plan(cfg, off, n)["chunk_len"] != srm.prefill_ragged_plan(cfg, off, 1 << 40)["chunk_len"]:
+            continue                                   # passes too small for the chunked scan's sums: another mixer's rounding
+        buf = torch.randint(0, 256, (n + 4096,), dtype=torch.uint8, device="cuda")
+        guard = buf[n:].clone()
+        st, tk = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+        lg = torch.empty((N, cfg.vocab), dtype=torch.float32, device="cuda")
+        if how == "uniform":
+            keep = model.prefill(toks.view(N, -1), 1, st, tk, logits=lg, workspace=buf[:n])
+        else:
+            keep = model.prefill_ragged(toks, off, st, tk, logits=lg, workspace=buf[:n])
+        torch.cuda.synchronize()
+        del keep
+        assert torch.equal(buf[n:], guard)
+        got.append((lg, st, tk))
+    sv = got[0][1].view(cfg.n_layers, N, -1)
+    for b, n in enumerate(lens):
+        ref = orc.greedy(prompts[b:b + 1, :n], 1, want_logits=True)
+        # fp32 sums of at most 1024 products against double ones: the repository's bound for fp32 models
+        assert rel_err_rows(got[0][0][b:b + 1].cpu().numpy(), ref["logits"][:, 0]) <= 1e-4
+        assert np.abs(sv[:, b].cpu().numpy() - ref["state"][0]).max() <= 1e-4 * np.abs(ref["state"][0]).max()
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            assert torch.equal(x, y)
