@@ -491,7 +491,7 @@ scan_chunk_apply_kernel(const TAct *__restrict__ u, TAct *__restrict__ m, float 
     }
 }
 
-// Parallel form and prefill of few sequences.  U, Y: [B][T][d].  grid = (ceil(T/64), H * ceil(d_h/64), B);
+// Parallel form and prefill of few sequences.  U, Y: [B][T][d].  One block per ceil(T/64), H * ceil(d_h/64), B;
 // a block owns 64 output positions j0 .. j0+63 x up to 64 channels c of one head:
 //   Y[j][c] = sum_i U[i][c] * M[i][j] + beta_j,
 //   M[i][j] = lam^(j-i) * alpha_i (row-repeat) | lam^(j-i) * alpha_j (column-repeat), 0 for i > j.
@@ -522,7 +522,12 @@ struct PrefillSeqs {
     const int32_t *slot;             // ragged: destination sample, or null
     int64_t nslots;
 };
-template <typename TAct, bool PREFILL = false>
+// FEW (at most a block per CU): grid = (tiles of positions, head tiles, B) and the rows of a 512-position prefix in one request.
+// Otherwise grid = (head tiles, B, tiles of positions), the last positions first: with eight tiles of positions in x each of
+// them went to an XCD of its own, the one with the longest prefixes ended last, and every XCD read all channels (6 x 500
+// positions, 768 blocks: 13.4 -> 10.3 us).  The wider request costs registers that many blocks need (14.5 us there; 64 prompts
+// x 128, 16 layers: 3127 -> 3279 us) and is worth 0.7 us per layer to few (one sequence of 509: 802 -> 793 us).
+template <typename TAct, bool PREFILL, bool FEW>
 __global__ void __launch_bounds__(256)
 mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
                       const float *__restrict__ alpha, const float *__restrict__ beta,
@@ -533,8 +538,9 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
     __shared__ float4 part[16][16];          // [row group][four channels]
     const int dh = d / H;
     const int ctiles = (dh + 63) / 64;
-    const int h = blockIdx.y / ctiles, ct = blockIdx.y % ctiles;
-    const int j0 = blockIdx.x * 64, b = blockIdx.z;
+    const int ht = FEW ? blockIdx.y : blockIdx.x;
+    const int h = ht / ctiles, ct = ht % ctiles;
+    const int j0 = (FEW ? (int)blockIdx.x : (int)(gridDim.z - 1 - blockIdx.z)) * kParSquare, b = FEW ? blockIdx.z : blockIdx.y;
     const int tid = threadIdx.x, c4 = tid & 15, g = tid >> 4;
     const bool row_repeat = h < hrow;
     const float *al = alpha + (size_t)h * n_ctx, *bl = beta + (size_t)h * n_ctx;
@@ -560,13 +566,15 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
         av[r] = al[j];
         bv[r] = bl[j];
     }
-    // rows g, g + 16, ... of the prefix (j0 is a multiple of 64), PRE of them in one request, the first under the table
-    constexpr int PRE = 16;
+    // rows g, g + 16, ... of the prefix (j0 is a multiple of 64), PRE of them in one request (half of them where that is the whole
+    // prefix), the first under the table
+    constexpr int PRE = FEW && sizeof(TAct) == 2 ? 32 : 16;
     raw_t u[PRE];
     float a[PRE];
     auto request = [&](int i0) {
 #pragma unroll
         for (int k = 0; k < PRE; ++k) {
+            if (k == 16 && i0 - g + 256 >= j0) return;               // (the whole block)
             const int i = min(i0 + 16 * k, j0 - 1);
             u[k] = *reinterpret_cast<const raw_t *>(Ub + (int64_t)i * d);
             a[k] = al[i];
@@ -613,6 +621,7 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
     __syncthreads();
     float4 in = make_float4(0.f, 0.f, 0.f, 0.f);
     axpy(pw[4 * g], C, in);
+    // (fifteen requests at once instead of this loop: 0.9 us more per layer, every group then reads all the sums)
     for (int q = 0; q < g; ++q) axpy(pw[4 * (g - 1 - q)], part[q][c4], in);
     if constexpr (PREFILL) {
         if (j0 + 64 >= T) {                                       // the block of the last position: the state behind it

@@ -1741,6 +1741,24 @@ static RaggedPlan plan_ragged(const srm_model *m, const int32_t *h_off, int N, i
     return pl;
 }
 
+// mixer_parallel_kernel on nseq sequences of up to P positions, w.u -> w.mx.
+template <typename T, bool PREFILL>
+static int mixer_parallel(const srm_model *m, const LayerDev &y, const Workspace &w, int P, int64_t nseq, const PrefillSeqs &ps,
+                          hipStream_t st)
+{
+    const unsigned tiles = (unsigned)cdiv(P, kParSquare), heads = (unsigned)(m->Hs * cdiv(m->dm / m->Hs, 64));
+    const size_t lds = (size_t)parallel_table_floats(P) * sizeof(float);
+#define PARALLEL_LAUNCH(FEW, ...)                                                                               \
+    hipLaunchKernelGGL((mixer_parallel_kernel<T, PREFILL, FEW>), dim3(__VA_ARGS__), dim3(256), lds, st,           \
+                       static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, m->cfg.n_ctx, m->Hs, \
+                       m->hrow, m->dm, P, ps)
+    if ((int64_t)tiles * heads * nseq <= device_cus()) PARALLEL_LAUNCH(true, tiles, heads, (unsigned)nseq);
+    else PARALLEL_LAUNCH(false, heads, (unsigned)nseq, tiles);
+#undef PARALLEL_LAUNCH
+    HIP_TRY(hipGetLastError());
+    return SRM_OK;
+}
+
 // The mixer of one prefill pass: nc sequences in rows of w.u -> w.mx, final states to S_layer.
 template <typename T>
 static int prefill_mixer(const srm_model *m, int l, const Workspace &w, void *S_layer, int nc, int P, int chunk,
@@ -1750,14 +1768,7 @@ static int prefill_mixer(const srm_model *m, int l, const Workspace &w, void *S_
     const LayerDev &y = m->layers[l];
     const int d = m->dm;           // the mixer's row width
     if (in_blocks) {
-        const dim3 grid((unsigned)cdiv(P, 64), (unsigned)(m->Hs * cdiv(d / m->Hs, 64)), (unsigned)nc);
-        hipLaunchKernelGGL((mixer_parallel_kernel<T, true>), grid, dim3(256),
-                           (size_t)parallel_table_floats(P) * sizeof(float), st,
-                           static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, m->cfg.n_ctx,
-                           m->Hs, m->hrow, d, P,
-                           PrefillSeqs{static_cast<float *>(S_layer), offsets, base, rows, seq0, rep, slot, nslots});
-        HIP_TRY(hipGetLastError());
-        return SRM_OK;
+        return mixer_parallel<T, true>(m, y, w, P, nc, PrefillSeqs{static_cast<float *>(S_layer), offsets, base, rows, seq0, rep, slot, nslots}, st);
     }
     if (chunk > 0) {
         float *F = static_cast<float *>(w.g);       // free until the MLP of this layer
@@ -1993,7 +2004,7 @@ template <typename T>
 static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float *hidden, float *logits, void *ws,
                          int64_t per_pass, hipStream_t st)
 {
-    const int d = m->d, dm = m->dm, dh = dm / m->Hs;
+    const int d = m->d;
     for (int64_t b0 = 0; b0 < B; b0 += per_pass) {
         const int64_t nc = std::min<int64_t>(per_pass, B - b0);
         const int64_t rows = nc * T_;
@@ -2001,14 +2012,7 @@ static int parallel_impl(srm_model *m, const int32_t *tok, int B, int T_, float 
         SRM_TRY((layernorm<T, true>(m, nullptr, 0, tok + b0 * T_, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b,
                                     w.a, rows, st)));
         auto mix = [&](int l) {
-            const LayerDev &y = m->layers[l];
-            const dim3 grid((unsigned)cdiv(T_, 64), (unsigned)(m->Hs * cdiv(dh, 64)), (unsigned)nc);
-            hipLaunchKernelGGL((mixer_parallel_kernel<T>), grid, dim3(256),
-                               (size_t)parallel_table_floats(T_) * sizeof(float), st,
-                               static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam,
-                               m->cfg.n_ctx, m->Hs, m->hrow, dm, T_, PrefillSeqs{});
-            HIP_TRY(hipGetLastError());
-            return (int)SRM_OK;
+            return mixer_parallel<T, false>(m, m->layers[l], w, T_, nc, PrefillSeqs{}, st);
         };
         for (int l = 0; l < m->L; ++l) SRM_TRY((block<T>(m, l, w, rows, (int64_t)B * T_, st, mix, true)));
         HIP_TRY(hipMemcpyAsync(hidden + (size_t)b0 * T_ * d, w.x, (size_t)rows * d * 4, hipMemcpyDeviceToDevice, st));

@@ -63,3 +63,27 @@ def test_prefill_of_the_last_rows_matches_oracle(srm, oracle_mod, name, lens):
     for other in got[1:]:
         for x, y in zip(got[0], other):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("N,P", [(1, 64), (1, 65), (1, 257), (2, 320), (1, 512), (1, 513), (1, 580), (20, 64), (40, 321)])
+def test_block_scan_bf16_of_few_and_many_blocks(srm, oracle_mod, N, P):
+    """The block form of the mixer on both sides of one block per CU (20 x 64 positions: 80 blocks here, 40 x 321: 960) and at the
+    ends of its requests of 256 and 512 rows: prefill and sequence form of a bf16 model against the oracle (the repository's
+    bound for bf16 models)."""
+    cfg = srm_synth.tiny_config(vocab=300, d_model=128, n_layers=2, n_heads=4, n_ctx=600, weight_dtype="bf16", seed=13)
+    w = srm_synth.make_weights(cfg)
+    model, orc = srm.Model(cfg, w), oracle_mod.Oracle(cfg, w, "f64")
+    prompts = np.random.default_rng(P).integers(0, cfg.vocab, (N, P)).astype(np.int32)
+    ws = model.new_workspace(N * P)
+    st, tk = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+    hid = torch.empty((N, P, cfg.d_model), dtype=torch.float32, device="cuda")
+    print(f"block scan bf16 N={N} P={P}", flush=True)
+    model.prefill(to_dev(prompts), 1, st, tk, workspace=ws)
+    model.parallel_forward(to_dev(prompts), hid, workspace=ws)
+    torch.cuda.synchronize()
+    sv = st.view(cfg.n_layers, N, cfg.d_model).cpu().numpy()
+    for b in sorted({0, N // 2, N - 1}):
+        ref = orc.greedy(prompts[b:b + 1], 1, want_logits=True)
+        assert np.abs(sv[:, b] - ref["state"][0]).max() <= 2e-2 * np.abs(ref["state"][0]).max()
+        want = orc.parallel_forward(prompts[b:b + 1])["hidden"]
+        assert np.abs(hid[b:b + 1].cpu().numpy() - want).max() <= 2e-2 * np.abs(want).max()
