@@ -359,7 +359,6 @@ extern "C" void srm_free(srm_model *m)
     if (!m) return;
     if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
     if (m->mega_layers) (void)hipFree(m->mega_layers);
-    if (m->few_layers) (void)hipFree(m->few_layers);
     if (m->few_slab) (void)hipFree(m->few_slab);
     if (m->slab) (void)hipFree(m->slab);
     delete m;
@@ -2256,15 +2255,19 @@ extern "C" int srm_linear(int32_t dtype, int32_t epilogue, const void *d_A, cons
 // of the others were up to 1 % slower, by where their own code then lies: sequence form 4 x 256 of the fp32 model 191.8 | 193.5 us.)
 #include "few.hpp"
 
-// The packed copies of a model's matrices and its table of layers.
+// The packed copies of a model's matrices and, in front of them, its table of layers: one allocation of whole 2 MB pages (a table
+// of its own and the odd size went with decode steps of 65536 samples up to 1 % slower, 27119 against 26849 us before there were
+// copies; 26735 against 26723 this way).
 static int few_pack(srm_model *m)
 {
     const size_t d = m->d, ff = m->ff, s = m->wsize, proj = m->noproj ? 0 : d * d * s, mlp = d * ff * s;
-    const size_t head = align_up((size_t)m->V, 4) * d * s, total = m->L * (2 * proj + 2 * mlp) + head;
+    const size_t head = align_up((size_t)m->V, 4) * d * s, table = align_up(sizeof(FewLayer) * m->L, 256);
+    const size_t total = align_up(table + m->L * (2 * proj + 2 * mlp) + head, (size_t)2 << 20);
     hipError_t e = hipMalloc(&m->few_slab, total);
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? SRM_ENOMEM : SRM_EHIP, "srm_init_weights: hipMalloc(%zu): %s", total, hipGetErrorString(e));
-    unsigned char *at = static_cast<unsigned char *>(m->few_slab);
+    m->few_layers = static_cast<FewLayer *>(m->few_slab);
+    unsigned char *at = static_cast<unsigned char *>(m->few_slab) + table;
     auto pack = [&](const void *W, size_t N, size_t K) {
         const int64_t n = (int64_t)(align_up(N, 4) * K * s / 16);
         hipLaunchKernelGGL(few_pack_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, nullptr, static_cast<const u32x4_t *>(W),
@@ -2285,7 +2288,6 @@ static int few_pack(srm_model *m)
     }
     m->few_head = pack(m->head, m->V, d);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&m->few_layers), sizeof(FewLayer) * m->L);
     if (e == hipSuccess) e = hipMemcpy(m->few_layers, fl.data(), sizeof(FewLayer) * m->L, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     return e == hipSuccess ? SRM_OK : fail(SRM_EHIP, "srm_init_weights: packed matrices: %s", hipGetErrorString(e));
