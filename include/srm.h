@@ -59,7 +59,8 @@
  *                        at least six layers, and so do all steps of
  *                        srm_generate for those with projections and at least
  *                        six layers times steps (SRM_MEGAKERNEL unset); not on a
- *                        stream that is being captured.  Such kernels run one at
+ *                        stream that is being captured or whose CU mask leaves
+ *                        out some CUs.  Such kernels run one at
  *                        a time on a device, in the order of the calls, whatever
  *                        their streams.  Their waits are bounded like those of
  *                        the one-kernel path of srm_generate (see there): should

@@ -1455,8 +1455,8 @@ extern "C" int srm_decode_step_ragged(srm_model *m, int64_t B, int32_t *d_pos, i
 }
 
 // ------------------------------------------------------------------ few samples: steps as one kernel (few.hpp)
-// Whether G steps of B samples run as one kernel: the shapes of few_max_rows, a stream that is not being captured, and at least
-// six layers or layers times steps.  That is faster from there on at every size (us, step kernels | one kernel, d = 1024 with
+// Whether G steps of B samples run as one kernel: the shapes of few_max_rows, a stream that is not being captured and may use
+// every CU, and at least six layers or layers times steps.  That is faster from there on at every size (us, step kernels | one kernel, d = 1024 with
 // projections, 4 rows | 1 row: 6 layers 137 | 118, 134 | 79; 8: 168 | 146, 163 | 98; 24: 521 | 417, 507 | 281; d = 512: 6 layers
 // 117 | 77, 114 | 59; fp32, d = 256: 8 rows 84 | 52, 1 row 80 | 32).  Shallower models have little to gain and keep a step
 // whose sums are, bit for bit, those of the ragged step and of larger batches.
@@ -1469,7 +1469,13 @@ static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_by
     if (e && e[0] == '0') return false;
     if (srm_workspace_bytes(m, B) > workspace_bytes || m->d / few_columns(m) > device_cus()) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
+    // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) return false;
+    int cus = 0;
+    for (const uint32_t bits : mask) cus += __builtin_popcount(bits);
+    return cus >= device_cus();
 }
 
 // ------------------------------------------------------------------ generate, few samples: one persistent kernel

@@ -170,6 +170,38 @@ def test_which_calls_run_as_one_kernel(srm, monkeypatch):
     assert _launches(step(1, m=other)) == 0
 
 
+def test_stream_that_keeps_off_some_cus_takes_the_step_kernels(srm, orc_mod, monkeypatch):
+    """The work-groups wait for each other, and a stream with a CU mask need not have room for all of them: 32 of its CUs hold
+    no more than half of 64 work-groups.  The step kernels' results there, bit for bit."""
+    import ctypes
+    cfg = srm_synth.tiny_config(vocab=300, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    B = 3
+    tok = to_dev(np.arange(B, dtype=np.int32) * 5)
+    ws = model.new_workspace(B)
+
+    def step(stream=None):
+        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        model.decode_step(B, 0, tok, st, out, logits=lg, workspace=ws, stream=stream)
+        torch.cuda.synchronize()
+        return lg, out, st
+
+    step()
+    assert _launches(step) == 1
+    hip = ctypes.CDLL("libamdhip64.so")
+    handle, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(0xffffffff)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+    masked = torch.cuda.ExternalStream(handle.value)
+    print("step on a stream of 32 CUs", flush=True)
+    assert _launches(lambda: step(masked)) == 0
+    got = step(masked)
+    monkeypatch.setenv(SWITCH, "0")
+    assert all(torch.equal(a, b) for a, b in zip(got, step()))
+    assert hip.hipStreamDestroy(handle) == 0
+
+
 def test_calls_on_several_streams_and_threads(srm):
     """Kernels whose work-groups wait for each other, launched from four threads on four streams into workspaces of their own,
     with two models and other work in between: each stream's results are those of the same calls alone."""
