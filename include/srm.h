@@ -61,11 +61,22 @@
  *                        six layers times steps (SRM_MEGAKERNEL unset); not on a
  *                        stream that is being captured or whose CU mask leaves
  *                        out some CUs.  Such kernels run one at
- *                        a time on a device, in the order of the calls, whatever
- *                        their streams.  Their waits are bounded like those of
- *                        the one-kernel path of srm_generate (see there): should
- *                        one give up, the tokens of the call are -1 and its state
- *                        is undefined.
+ *                        a time per process and device, in the order of the calls,
+ *                        whatever their streams.  Their work-groups, half the
+ *                        device's CUs or fewer, start their work only once all of
+ *                        them have started.  Where that does not come about within
+ *                        some 8 ms (kernels of other processes that wait for each
+ *                        other too, cooperative kernels that fill the device), one
+ *                        of them does the call's work alone: same bits, some
+ *                        milliseconds per step.  Where several processes share
+ *                        a device, =0 is therefore the better setting.  =2 and =3
+ *                        (for tests): as if they had not all started, or with that
+ *                        wait as short as it can be.
+ *                        The waits behind that are bounded like those of the
+ *                        one-kernel path of srm_generate (see there): should one
+ *                        give up, the tokens of the call are -1 and its state is
+ *                        undefined (SRM_ONE_KERNEL_POLLS=n, for tests: that bound
+ *                        in polls).
  */
 #ifndef SRM_H
 #define SRM_H

@@ -30,8 +30,12 @@
 // exchanges 5.4, two LayerNorms 1.4, products, epilogues and waiting for weights 3.4, and 16 for the head, which reads at 4.5
 // TB/s.  Extra work-groups that read the next layer ahead into L2 made it 3 % slower at one row and 5 % faster at two and four.
 //
-// All work-groups must be resident at once (few_launch in srm.hip sees to it).  Every wait is bounded: a work-group that gives up raises a
-// flag that ends all other waits, and the tokens are -1.
+// All work-groups must be resident at once, which an ordinary launch cannot promise: other processes, or kernels that wait for
+// each other themselves, can hold the CUs.  So the first exchange is an arrival, before anything but scratch is written
+// (few_arrived): either every work-group sees that all have started, and then all stay until they end, or every one leaves, and
+// the last to leave does all the work alone (few_alone), slowly and with the same bits.
+// The waits behind the arrival are bounded all the same: a work-group that gives up raises a flag that ends all other waits, and
+// the tokens are -1.
 #pragma once
 #include "common.hpp"
 #include "gemm.hpp"
@@ -58,8 +62,8 @@ struct FewArgs {
     float temp;                                      // > 0: Gumbel-max sampling
     uint32_t seed;
     few_word *xw, *mw, *gw, *pw;                     // words of x [MB][D], m [MB][D], g [MB][FF words], winners [MB][NB][2]
-    unsigned *flag;                                  // a wait has given up
-    unsigned max_polls;
+    unsigned *flag;                                  // a wait has given up; [1]: work-groups that have left without arriving all
+    unsigned max_polls, arrive_polls;                // bounds of the waits
 };
 
 __device__ __forceinline__ void few_put(few_word *p, unsigned payload, unsigned tag)
@@ -83,6 +87,47 @@ __device__ __forceinline__ bool few_gather(few_word (&v)[N], AT &&at, unsigned t
             return false;
         }
     }
+}
+
+// The arrival of the NB work-groups: word b (`stride` words apart, zero at the launch) becomes 1 when work-group b starts, or
+// 2 when another one, tired of waiting, has withdrawn it first.  Each is set once, so all work-groups come to the same answer:
+// true where every word is 1.  One wavefront per work-group.
+constexpr few_word kFewHere = 1, kFewWithdrawn = 2;
+__device__ __forceinline__ void few_set(few_word *p, few_word value, few_word &found)
+{
+    found = 0;
+    __hip_atomic_compare_exchange_strong(p, &found, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (found == 0) found = value;
+}
+template <int NB>
+__device__ __forceinline__ bool few_arrived(few_word *words, int stride, int lane, unsigned max_polls)
+{
+    static_assert(NB % 64 == 0, "as many words for each lane");
+    constexpr int N = NB / 64;
+    few_word v[N];
+    bool here, withdrawn;
+    auto look = [&] {
+        here = true;
+        withdrawn = false;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            here = here && v[i] == kFewHere;
+            withdrawn = withdrawn || v[i] == kFewWithdrawn;
+        }
+    };
+    for (unsigned polls = 0;; ++polls) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            v[i] = __hip_atomic_load(words + (i * 64 + lane) * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        look();
+        if (__any(withdrawn)) return false;
+        if (__all(here)) return true;
+        if (polls >= max_polls) break;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) few_set(words + (i * 64 + lane) * stride, kFewWithdrawn, v[i]);
+    look();
+    return __all(here);
 }
 
 // A load through a pointer that came from LDS: global memory, which the compiler cannot know (a flat load would count as an
@@ -165,10 +210,319 @@ __device__ __forceinline__ void few_products(const u32x4_t (&w)[N], const unsign
     }
 }
 
+// Pieces that the exchanging wavefronts and few_alone share.  Element 128 i + 2 lane of a row and the one behind it:
+__device__ __forceinline__ int few_elem(int i, int lane) { return 128 * i + 2 * lane; }
+template <typename TW, int D, int MB>
+__device__ __forceinline__ void few_embed(const TW *embed, const int *tokb, float *xs, int from, int step)      // rows of the tokens
+{
+    constexpr int V = 16 / (int)sizeof(TW);
+    for (int i = from; i < MB * D / V; i += step) {
+        const int r = i / (D / V), c = i % (D / V) * V;
+        const u32x4_t t = *reinterpret_cast<const u32x4_t *>(embed + (size_t)tokb[r] * D + c);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (sizeof(TW) == 2) {
+                xs[r * D + c + 2 * k] = __uint_as_float(t[k] << 16);
+                xs[r * D + c + 2 * k + 1] = __uint_as_float(t[k] & 0xffff0000u);
+            } else {
+                xs[r * D + c + k] = __uint_as_float(t[k]);
+            }
+        }
+    }
+}
+template <int XL>
+__device__ __forceinline__ void few_row(const float *row, int lane, float (&v)[XL])
+{
+#pragma unroll
+    for (int i = 0; i < XL / 2; ++i) {
+        const float2 t = *reinterpret_cast<const float2 *>(row + few_elem(i, lane));
+        v[2 * i] = t.x;
+        v[2 * i + 1] = t.y;
+    }
+}
+// LayerNorm of a row in registers, two-pass statistics; t: gain and bias in LDS
+template <int D, int XL>
+__device__ __forceinline__ void few_normalise(const float (&v)[XL], const float *t, float eps, int lane, float (&o)[XL])
+{
+    float s = 0.0f, sq = 0.0f;
+#pragma unroll
+    for (int i = 0; i < XL; i += 2) s += v[i] + v[i + 1];
+    const float mean = wave_sum(s) / (float)D;
+#pragma unroll
+    for (int i = 0; i < XL; i += 2) {
+        const float a = v[i] - mean, c = v[i + 1] - mean;
+        sq += a * a + c * c;
+    }
+    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)D + eps);
+#pragma unroll
+    for (int i = 0; i < XL / 2; ++i) {
+        const float2 g = *reinterpret_cast<const float2 *>(t + few_elem(i, lane)), b = *reinterpret_cast<const float2 *>(t + D + few_elem(i, lane));
+        o[2 * i] = (v[2 * i] - mean) * rstd * g.x + b.x;
+        o[2 * i + 1] = (v[2 * i + 1] - mean) * rstd * g.y + b.y;
+    }
+}
+template <typename TW, int XL>
+__device__ __forceinline__ void few_leave(unsigned char *row, int lane, const float (&o)[XL])
+{
+#pragma unroll
+    for (int i = 0; i < XL / 2; ++i) {
+        TW *q = reinterpret_cast<TW *>(row) + few_elem(i, lane);
+        if constexpr (sizeof(TW) == 2) *reinterpret_cast<bf16x2_t *>(q) = __builtin_convertvector(f32x2_t{o[2 * i], o[2 * i + 1]}, bf16x2_t);
+        else *reinterpret_cast<float2 *>(q) = make_float2(o[2 * i], o[2 * i + 1]);
+    }
+}
+// State and mixer output of a channel: t, the in-projection without its bias
+template <typename TW>
+__device__ __forceinline__ TW few_mix(float t, float b_in, float s0, float al, float be, float la, bool row_repeat, int half, float &sn)
+{
+    const float u = (float)(TW)(t + b_in);           // u in the activation type
+    const float pp = row_repeat ? al : 1.0f, qq = row_repeat ? 1.0f : al;
+    sn = fmaf(la, s0, pp * u);
+    if (half) sn = to_state(sn, static_cast<const f16 *>(nullptr));
+    return (TW)fmaf(qq, sn, be);
+}
+// ... and of two channels without projections, whose output goes to the residual stream x; u: their LayerNorm
+template <typename TW>
+__device__ __forceinline__ void few_mix2(float2 &s, float *x, const float *u, float al, float be, float la, bool row_repeat, int half)
+{
+    const float pp = row_repeat ? al : 1.0f, qq = row_repeat ? 1.0f : al;
+    s.x = fmaf(la, s.x, pp * (float)(TW)u[0]);
+    s.y = fmaf(la, s.y, pp * (float)(TW)u[1]);
+    if (half) {
+        s.x = to_state(s.x, static_cast<const f16 *>(nullptr));
+        s.y = to_state(s.y, static_cast<const f16 *>(nullptr));
+    }
+    x[0] += (float)(TW)fmaf(qq, s.x, be);
+    x[1] += (float)(TW)fmaf(qq, s.y, be);
+}
+__device__ __forceinline__ float2 few_state2(const void *state, size_t at, int half)
+{
+    if (half) {
+        const f16 *S = static_cast<const f16 *>(state) + at;
+        return make_float2((float)S[0], (float)S[1]);
+    }
+    return *reinterpret_cast<const float2 *>(static_cast<const float *>(state) + at);
+}
+__device__ __forceinline__ void few_keep2(void *state, size_t at, int half, float2 s)
+{
+    if (half) {
+        f16 *S = static_cast<f16 *>(state) + at;
+        S[0] = (f16)s.x;
+        S[1] = (f16)s.y;
+    } else {
+        *reinterpret_cast<float2 *>(static_cast<float *>(state) + at) = s;
+    }
+}
+// Logits of group n of four columns (w: its vectors), below g1, and the best of a lane's so far
+template <typename TW, int D, int MB>
+__device__ __forceinline__ void few_scores(const FewArgs &p, const u32x4_t (&w)[D * (int)sizeof(TW) / 256], const unsigned char *act, int n, int g1,
+                                           int pos, bool last, int lane, int ln, float (&bv)[(MB + 3) / 4], int (&bi)[(MB + 3) / 4])
+{
+    constexpr int RB = (MB + 3) / 4;
+    float logit[RB];
+    few_products<TW, D * (int)sizeof(TW) / 256, MB>(w, act, D * (int)sizeof(TW) + kFewPad, 0, lane, logit);
+    const int c = 4 * n + few_column(ln);
+    if (n < g1 && c < p.V && (ln & 12) == 0) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int row = 4 * rb + (ln & 3);
+            if (row >= p.B) continue;
+            if (p.logits && last) p.logits[(size_t)row * p.V + c] = logit[rb];
+            const float score = p.temp > 0.0f
+                ? logit[rb] + p.temp * srm_gumbel(srm_rowkey(p.seed, (uint32_t)pos, (uint32_t)row), (uint32_t)c) : logit[rb];
+            if (arg_better(score, c, bv[rb], bi[rb])) { bv[rb] = score; bi[rb] = c; }
+        }
+    }
+}
+// The best of a row's columns that the wavefronts of a work-group have left in `red`
+template <int NWT, int RB>
+__device__ __forceinline__ void few_best(const uint2 *red, int r, int lane, float &bv, int &bi)
+{
+    bv = -INFINITY;
+    bi = 0x7fffffff;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint2 t = red[(min(lane, NWT - 1) * RB + r / 4) * 64 + (r & 3) + 16 * c];
+        if (arg_better(__uint_as_float(t.x), (int)t.y, bv, bi)) { bv = __uint_as_float(t.x); bi = (int)t.y; }
+    }
+    best_of_lanes<16>(bv, bi);
+}
+
 constexpr int few_lds_bytes(int ts, int D, int NWC, int MB)
 {
     return MB * (D * (4 + 6 * ts) + 3 * kFewPad) + MB * NWC * 4 * (4 + 4 + 1) + (kFewGather + NWC) * ((MB + 3) / 4) * 64 * 8 +
            8 * D * 4 + kFewMaxLayers * (int)sizeof(FewLayer) + 256;
+}
+
+// All steps by one work-group, for a launch whose work-groups have not all started (few_arrived): the same products, slices and
+// sums as between them, so the same bits.  Bound by what one CU reads (figures at few_arrive_polls in srm.hip).  LDS as in
+// few_rows_kernel, cleared; the tokens stand in tokb.
+template <typename TW, int D, int NWT, int MB, bool PROJ>
+__device__ __forceinline__ void few_alone(const FewArgs &p, const FewLayer *lay, float *xs, unsigned char *act_a, unsigned char *act_m,
+                                          unsigned char *act_g, uint2 *red, float *lnp, int *tokb, int tid, int lane, int wave)
+{
+    constexpr int TS = (int)sizeof(TW), KD = D * TS / 1024, K4 = 4 * KD, RB = (MB + 3) / 4, XL = D / 64;
+    constexpr int SD = D * TS + kFewPad, SF = 4 * D * TS + kFewPad;
+    const int B = p.B, groups = (p.V + 3) / 4;
+    auto opaque = [](int i) {                        // (as in few_rows_kernel: addresses are formed where they are used)
+        asm volatile("" : "+v"(i));
+        return i;
+    };
+    // (loads of the next piece are not moved in front of it: the kernel's registers are the other path's)
+    auto piece = [] { asm volatile("" : : : "memory"); };
+    auto vectors = [&](const void *W, int first, auto &w) {
+        constexpr int K = sizeof(w) / sizeof(u32x4_t);
+        const unsigned of = opaque(lane);
+        const u32x4_t *base = static_cast<const u32x4_t *>(W) + (size_t)first * 64;
+#pragma unroll
+        for (int j = 0; j < K; ++j) w[j] = few_load(base + j * 64 + of);
+    };
+    // group n of four columns, the inputs in quarters of N vectors each
+    auto quarters = [&](auto n_c, const void *W, int n, const unsigned char *act, int stride, float (&v)[RB]) {
+        constexpr int N = decltype(n_c)::value;
+        float q[4][RB];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            u32x4_t w[N];
+            vectors(W, (n * 4 + k) * N, w);
+            few_products<TW, N, MB>(w, act, stride, k * N, lane, q[k]);
+            if (k & 1) piece();
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) v[rb] = (q[0][rb] + q[1][rb]) + (q[2][rb] + q[3][rb]);
+    };
+    // fn(row, its place in v, column) for what a lane holds of group n
+    auto each = [&](int n, auto &&fn) {
+        const int of = opaque(lane);
+        if ((of & 12) == 0)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                if (4 * rb + (of & 3) < B) fn(4 * rb + (of & 3), rb, 4 * n + few_column(of));
+    };
+    auto parameters = [&](const float *a, const float *b, const float *c, const float *d) {
+        for (int i = tid; i < 4 * D; i += NWT * 64) lnp[i] = few_load((i < 2 * D ? (i < D ? a : b) : (i < 3 * D ? c : d)) + i % D);
+        __syncthreads();
+    };
+    auto normalised = [&](const float *t) {
+        for (int r = wave; r < B; r += NWT) {
+            const int of = opaque(lane);
+            float v[XL], o[XL];
+            few_row(xs + r * D, of, v);
+            few_normalise<D>(v, t, p.eps, of, o);
+            few_leave<TW>(act_a + r * SD, of, o);
+        }
+        __syncthreads();
+    };
+    for (int g = 0; g < p.G; ++g) {
+        const int pos = p.pos0 + g;
+        few_embed<TW, D, MB>(static_cast<const TW *>(p.embed), tokb, xs, tid, NWT * 64);
+        for (int l = 0; l < p.L; ++l) {
+            const FewLayer &y = lay[l];
+            parameters(y.ln[0], y.ln[1], y.ln[2], y.ln[3]);
+            if constexpr (PROJ) {
+                normalised(lnp);
+#pragma unroll 1
+                for (int n = wave; n < D / 4; n += NWT) {
+                    float v[RB];
+                    quarters(std::integral_constant<int, KD>{}, y.w_in, n, act_a, SD, v);
+                    each(n, [&](int r, int rb, int col) {
+                        const int head = col / p.dh;
+                        const size_t at = ((size_t)l * B + r) * D + col;
+                        const float s0 = p.state_half ? (float)static_cast<const f16 *>(p.state)[at] : static_cast<const float *>(p.state)[at];
+                        float sn;
+                        const TW m = few_mix<TW>(v[rb], few_load(y.b_in + col), s0, few_load(y.alpha + (size_t)head * p.n_ctx + pos),
+                                                 few_load(y.beta + (size_t)head * p.n_ctx + pos), few_load(y.lam + head), head < p.hrow,
+                                                 p.state_half, sn);
+                        if (p.state_half) static_cast<f16 *>(p.state)[at] = (f16)sn;
+                        else static_cast<float *>(p.state)[at] = sn;
+                        reinterpret_cast<TW *>(act_m + r * SD)[col] = m;
+                    });
+                }
+                __syncthreads();
+#pragma unroll 1
+                for (int n = wave; n < D / 4; n += NWT) {
+                    float v[RB];
+                    quarters(std::integral_constant<int, KD>{}, y.w_out, n, act_m, SD, v);
+                    each(n, [&](int r, int rb, int col) { xs[r * D + col] += v[rb] + few_load(y.b_out + col); });
+                }
+                __syncthreads();
+                normalised(lnp + 2 * D);
+            } else {
+                for (int r = wave; r < B; r += NWT) {
+                    const int of = opaque(lane);
+                    float x[XL], u[XL];
+                    few_row(xs + r * D, of, x);
+                    few_normalise<D>(x, lnp, p.eps, of, u);
+#pragma unroll
+                    for (int i = 0; i < XL / 2; ++i) {
+                        const int e = few_elem(i, of), h = e / p.dh;
+                        const size_t at = ((size_t)l * B + r) * D + e;
+                        float2 s = few_state2(p.state, at, p.state_half);
+                        few_mix2<TW>(s, x + 2 * i, u + 2 * i, few_load(y.alpha + (size_t)h * p.n_ctx + pos),
+                                     few_load(y.beta + (size_t)h * p.n_ctx + pos), few_load(y.lam + h), h < p.hrow, p.state_half);
+                        few_keep2(p.state, at, p.state_half, s);
+                        *reinterpret_cast<float2 *>(xs + r * D + e) = make_float2(x[2 * i], x[2 * i + 1]);
+                        piece();
+                    }
+                    few_normalise<D>(x, lnp + 2 * D, p.eps, of, u);
+                    few_leave<TW>(act_a + r * SD, of, u);
+                }
+                __syncthreads();
+            }
+#pragma unroll 1
+            for (int n = wave; n < D; n += NWT) {
+                u32x4_t w[K4];
+                float v[RB];
+                vectors(y.w_up, n * K4, w);
+                few_products<TW, K4, MB>(w, act_a, SD, 0, lane, v);
+                const float b = few_load(y.b_up + 4 * n + few_column(opaque(lane)));
+                each(n, [&](int r, int rb, int col) {
+                    reinterpret_cast<TW *>(act_g + r * SF)[col] = (TW)gelu_for(static_cast<const TW *>(nullptr), v[rb] + b);
+                });
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int n = wave; n < D / 4; n += NWT) {
+                float v[RB];
+                quarters(std::integral_constant<int, K4>{}, y.w_down, n, act_g, SF, v);
+                each(n, [&](int r, int rb, int col) { xs[r * D + col] += v[rb] + few_load(y.b_down + col); });
+            }
+            __syncthreads();
+        }
+        parameters(p.lnf_g, p.lnf_b, p.lnf_g, p.lnf_b);
+        normalised(lnp);
+        const bool last = g == p.G - 1;
+        if (p.hidden && last)
+            for (int i = tid; i < B * D; i += NWT * 64) p.hidden[i] = xs[i];
+        float bv[RB];
+        int bi[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            bv[rb] = -INFINITY;
+            bi[rb] = 0x7fffffff;
+        }
+#pragma unroll 1
+        for (int n = wave; n < groups; n += NWT) {
+            u32x4_t w[K4];
+            vectors(p.head, n * K4, w);
+            few_scores<TW, D, MB>(p, w, act_a, n, groups, pos, last, lane, opaque(lane), bv, bi);
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) red[(wave * RB + rb) * 64 + lane] = make_uint2(__float_as_uint(bv[rb]), (unsigned)bi[rb]);
+        __syncthreads();
+        for (int r = wave; r < B; r += NWT) {
+            float v;
+            int t;
+            few_best<NWT, RB>(red, r, lane, v, t);
+            if (t < 0 || t >= p.V) t = 0;            // no ordered value: a valid token all the same
+            if (lane == 0) {
+                tokb[r] = t;
+                if (p.store) p.store[(size_t)g * B + r] = t;
+                if (last) p.tok_out[r] = t;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // MB: rows that the arithmetic is unrolled for (B <= MB); the rows between travel along as finite filler.
@@ -193,7 +547,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     float *const lnp = reinterpret_cast<float *>(red + NWT * RB * 64);                 // [2][4][D] LayerNorm parameters of two layers
     FewLayer *const lay = reinterpret_cast<FewLayer *>(lnp + 8 * D);                   // [L] (a read of memory per phase is a trip of 1 us)
     int *const tokb = reinterpret_cast<int *>(lay + kFewMaxLayers);                    // [MB]
-    int *const dead = tokb + MB;
+    int *const dead = tokb + MB;                                                       // [2]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blk = blockIdx.x, B = p.B;
@@ -201,12 +555,20 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     const int cw = wave - NG;                        // number of a computing wavefront
     const TW *const embed = static_cast<const TW *>(p.embed);
 
+    few_word *const here = p.pw;                     // (arrivals: words of the winners, which nobody writes before all have arrived)
+    if (tid == 0) {
+        few_word found;
+        few_set(here + blk * (MB * 2), kFewHere, found);
+    }
     for (int i = tid; i < (MB * D * 4 + 2 * MB * SD + MB * SF) / 16; i += blockDim.x)
         reinterpret_cast<u32x4_t *>(few_lds)[i] = u32x4_t{0, 0, 0, 0};
     for (int i = tid; i < p.L * (int)(sizeof(FewLayer) / 8); i += blockDim.x)
         reinterpret_cast<few_word *>(lay)[i] = reinterpret_cast<const few_word *>(p.layers)[i];
     if (tid < MB) tokb[tid] = tid < B ? min(max(p.tok_in[tid], 0), p.V - 1) : 0;
-    if (tid == 0) *dead = 0;
+    if (wave == 0) {
+        const bool all = few_arrived<NB>(here, MB * 2, lane, p.arrive_polls);
+        if (lane == 0) *dead = !all;
+    }
     // LDS only: loads and stores of global memory stay in flight across it
     auto barrier = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -214,6 +576,13 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
     barrier();
+    if (__builtin_expect(*dead, 0)) {                // nothing but scratch has been written
+        if (tid == 0)
+            dead[1] = __hip_atomic_fetch_add(p.flag + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == NB - 1;
+        __syncthreads();
+        if (dead[1]) few_alone<TW, D, NWT, MB, PROJ>(p, lay, xs, act_a, act_m, act_g, red, lnp, tokb, tid, lane, wave);
+        return;
+    }
     unsigned tag = 0;                                // of the latest exchange, the same in every wavefront
     // (indexes pass through opaque copies where they are used: what is derived from them would otherwise be formed once, in
     // front of all loops, for every phase, and held in registers that do not exist)
@@ -233,7 +602,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     };
     // w, nx: the wavefront's first two groups; leaves every lane's winners in `red`
     auto head_phase = [&](u32x4_t (&w)[K4], u32x4_t (&nx)[K4], int pos, bool last) {
-        const int ln = opaque(lane), r0 = ln & 3;
+        const int ln = opaque(lane);
         float bv[RB];
         int bi[RB];
 #pragma unroll
@@ -241,22 +610,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
             bv[rb] = -INFINITY;
             bi[rb] = 0x7fffffff;
         }
-        auto group = [&](u32x4_t (&v)[K4], int n) {
-            float logit[RB];
-            few_products<TW, K4, MB>(v, act_a, SD, 0, lane, logit);
-            const int c = 4 * n + few_column(ln);
-            if (n < g1 && c < p.V && (ln & 12) == 0) {
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    const int row = 4 * rb + r0;
-                    if (row >= B) continue;
-                    if (p.logits && last) p.logits[(size_t)row * p.V + c] = logit[rb];
-                    const float score = p.temp > 0.0f
-                        ? logit[rb] + p.temp * srm_gumbel(srm_rowkey(p.seed, (uint32_t)pos, (uint32_t)row), (uint32_t)c) : logit[rb];
-                    if (arg_better(score, c, bv[rb], bi[rb])) { bv[rb] = score; bi[rb] = c; }
-                }
-            }
-        };
+        auto group = [&](u32x4_t (&v)[K4], int n) { few_scores<TW, D, MB>(p, v, act_a, n, g1, pos, last, lane, ln, bv, bi); };
         for (int n = g0 + wave; n < g1; n += 2 * NWT) {
             group(w, n);
             head_load(w, n + 2 * NWT < g1 ? n + 2 * NWT : n);
@@ -282,8 +636,6 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                 for (int i = 0; i < N; ++i) put((i0 + i) * NT + t, (unsigned)v[i]);
             }
         };
-        // element 128 i + 2 lane of a row and the one behind it
-        auto elem = [&](int i, int of) { return 128 * i + 2 * of; };
         auto gather_x = [&] {
             gather(std::integral_constant<int, MB * D>{}, p.xw, [&](int f, unsigned v) {
                 const int b = f / (MB * NWC), r = f / NWC % MB, c = f % NWC;
@@ -311,74 +663,20 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
             gather_g();
             barrier();                               // g is there
         };
-        auto embed_x = [&] {                         // the rows of the tokens into xs
-            constexpr int V = 16 / TS;
-            for (int i = opaque(tid); i < MB * D / V; i += NT) {
-                const int r = i / (D / V), c = i % (D / V) * V;
-                const u32x4_t t = *reinterpret_cast<const u32x4_t *>(embed + (size_t)tokb[r] * D + c);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if constexpr (TS == 2) {
-                        xs[r * D + c + 2 * k] = __uint_as_float(t[k] << 16);
-                        xs[r * D + c + 2 * k + 1] = __uint_as_float(t[k] & 0xffff0000u);
-                    } else {
-                        xs[r * D + c + k] = __uint_as_float(t[k]);
-                    }
-                }
-            }
-        };
-        auto row_x = [&](int r, float (&v)[XL]) {
-            const int of = opaque(lane);
-#pragma unroll
-            for (int i = 0; i < XL / 2; ++i) {
-                const float2 t = *reinterpret_cast<const float2 *>(xs + r * D + elem(i, of));
-                v[2 * i] = t.x;
-                v[2 * i + 1] = t.y;
-            }
-        };
-        // LayerNorm of a row in registers, two-pass statistics; t: gain and bias in LDS
-        auto normalise = [&](const float (&v)[XL], const float *t, float (&o)[XL]) {
-            const int of = opaque(lane);
-            float s = 0.0f, sq = 0.0f;
-#pragma unroll
-            for (int i = 0; i < XL; i += 2) s += v[i] + v[i + 1];
-            const float mean = wave_sum(s) / (float)D;
-#pragma unroll
-            for (int i = 0; i < XL; i += 2) {
-                const float a = v[i] - mean, c = v[i + 1] - mean;
-                sq += a * a + c * c;
-            }
-            const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)D + p.eps);
-#pragma unroll
-            for (int i = 0; i < XL / 2; ++i) {
-                const float2 g = *reinterpret_cast<const float2 *>(t + elem(i, of)), b = *reinterpret_cast<const float2 *>(t + D + elem(i, of));
-                o[2 * i] = (v[2 * i] - mean) * rstd * g.x + b.x;
-                o[2 * i + 1] = (v[2 * i + 1] - mean) * rstd * g.y + b.y;
-            }
-        };
-        auto leave = [&](int r, const float (&o)[XL]) {
-            const int of = opaque(lane);
-#pragma unroll
-            for (int i = 0; i < XL / 2; ++i) {
-                TW *q = reinterpret_cast<TW *>(act_a + r * SD) + elem(i, of);
-                if constexpr (TS == 2) *reinterpret_cast<bf16x2_t *>(q) = __builtin_convertvector(f32x2_t{o[2 * i], o[2 * i + 1]}, bf16x2_t);
-                else *reinterpret_cast<float2 *>(q) = make_float2(o[2 * i], o[2 * i + 1]);
-            }
-        };
         auto leave_normalised = [&](const float *t) {
 #pragma unroll
             for (int q = 0; q < RPW; ++q) {
                 const int r = wave + q * NG;
                 if (r >= MB) break;
                 float v[XL], o[XL];
-                row_x(r, v);
-                normalise(v, t, o);
-                leave(r, o);
+                few_row(xs + r * D, opaque(lane), v);
+                few_normalise<D>(v, t, p.eps, opaque(lane), o);
+                few_leave<TW>(act_a + r * SD, opaque(lane), o);
             }
         };
         for (int g = 0; g < p.G; ++g) {
             const int pos = p.pos0 + g;
-            embed_x();
+            few_embed<TW, D, MB>(embed, tokb, xs, opaque(tid), NT);
             for (int l = 0; l < p.L; ++l) {
                 const float *const t1 = lnp + (l & 1) * 4 * D, *const t2 = t1 + 2 * D;
                 if (l > 0) gather_x();
@@ -405,20 +703,14 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                     const int of = opaque(lane);
 #pragma unroll
                     for (int i = 0; i < XL / 2; ++i) {
-                        const int h = elem(i, of) / p.dh;                  // two consecutive channels lie in one head
+                        const int h = few_elem(i, of) / p.dh;                  // two consecutive channels lie in one head
                         rr[i] = h < p.hrow;
                         al[i] = few_load(alpha + (size_t)h * p.n_ctx + pos);
                         be[i] = few_load(beta + (size_t)h * p.n_ctx + pos);
                         la[i] = few_load(lam + h);
 #pragma unroll
                         for (int q = 0; q < RPW; ++q) {
-                            const size_t at = ((size_t)l * B + min(wave + q * NG, B - 1)) * D + elem(i, of);
-                            if (p.state_half) {
-                                const f16 *S = static_cast<const f16 *>(p.state) + at;
-                                s[q][i] = make_float2((float)S[0], (float)S[1]);
-                            } else {
-                                s[q][i] = *reinterpret_cast<const float2 *>(static_cast<const float *>(p.state) + at);
-                            }
+                            s[q][i] = few_state2(p.state, ((size_t)l * B + min(wave + q * NG, B - 1)) * D + few_elem(i, of), p.state_half);
                         }
                     }
                     barrier();
@@ -427,24 +719,16 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                         const int r = wave + q * NG;
                         if (r >= MB) break;
                         float x[XL], u[XL];
-                        row_x(r, x);
-                        normalise(x, t1, u);
+                        few_row(xs + r * D, opaque(lane), x);
+                        few_normalise<D>(x, t1, p.eps, opaque(lane), u);
 #pragma unroll
                         for (int i = 0; i < XL / 2; ++i) {
-                            const float pp = rr[i] ? al[i] : 1.0f, qq = rr[i] ? 1.0f : al[i];
-                            s[q][i].x = fmaf(la[i], s[q][i].x, pp * (float)(TW)u[2 * i]);
-                            s[q][i].y = fmaf(la[i], s[q][i].y, pp * (float)(TW)u[2 * i + 1]);
-                            if (p.state_half) {
-                                s[q][i].x = to_state(s[q][i].x, static_cast<const f16 *>(nullptr));
-                                s[q][i].y = to_state(s[q][i].y, static_cast<const f16 *>(nullptr));
-                            }
-                            x[2 * i] += (float)(TW)fmaf(qq, s[q][i].x, be[i]);
-                            x[2 * i + 1] += (float)(TW)fmaf(qq, s[q][i].y, be[i]);
-                            const int e = elem(i, of) - blk * NWC;         // (NWC is even: both columns are this work-group's or none)
+                            few_mix2<TW>(s[q][i], x + 2 * i, u + 2 * i, al[i], be[i], la[i], rr[i], p.state_half);
+                            const int e = few_elem(i, of) - blk * NWC;         // (NWC is even: both columns are this work-group's or none)
                             if (e >= 0 && e < NWC) *reinterpret_cast<float2 *>(own + r * NWC + e) = make_float2(x[2 * i], x[2 * i + 1]);
                         }
-                        normalise(x, t2, u);
-                        leave(r, u);
+                        few_normalise<D>(x, t2, p.eps, opaque(lane), u);
+                        few_leave<TW>(act_a + r * SD, opaque(lane), u);
                     }
                     exchange_g();
 #pragma unroll
@@ -453,14 +737,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
 #pragma unroll
                         for (int i = 0; i < XL / 2; ++i) {
                             if (i != blk) continue;                    // (there are at least XL / 2 work-groups)
-                            const size_t at = ((size_t)l * B + wave + q * NG) * D + elem(i, of);
-                            if (p.state_half) {
-                                f16 *S = static_cast<f16 *>(p.state) + at;
-                                S[0] = (f16)s[q][i].x;
-                                S[1] = (f16)s[q][i].y;
-                            } else {
-                                *reinterpret_cast<float2 *>(static_cast<float *>(p.state) + at) = s[q][i];
-                            }
+                            few_keep2(p.state, ((size_t)l * B + wave + q * NG) * D + few_elem(i, of), p.state_half, s[q][i]);
                         }
                     }
                 }
@@ -484,14 +761,9 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
             for (int q = 0; q < RPW; ++q) {
                 const int r = wave + q * NG;
                 if (r >= MB) break;
-                float bv = -INFINITY;
-                int bi = 0x7fffffff;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint2 t = red[(min(lane, NWT - 1) * RB + r / 4) * 64 + (r & 3) + 16 * c];
-                    if (arg_better(__uint_as_float(t.x), (int)t.y, bv, bi)) { bv = __uint_as_float(t.x); bi = (int)t.y; }
-                }
-                best_of_lanes<16>(bv, bi);
+                float bv;
+                int bi;
+                few_best<NWT, RB>(red, r, lane, bv, bi);
                 if (lane < 2) few_put(p.pw + (blk * MB + r) * 2 + lane, lane ? (unsigned)bi : __float_as_uint(bv), tag);
             }
 #pragma unroll
@@ -630,13 +902,9 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                     if (lead) {
                         const int ln = opaque(lane), at = min(ln, MB * NWC - 1), r = at / NWC, col = blk * NWC + at % NWC;
                         if (l == 0) x_own = xs[r * D + col];
-                        const bool row_repeat = col / p.dh < p.hrow;
-                        const float u = (float)(TW)(total(at) + e.b_in);              // u in the activation type
-                        const float pp = row_repeat ? e.al : 1.0f, qq = row_repeat ? 1.0f : e.al;
                         const float s0 = p.state_half ? (float)__builtin_bit_cast(f16, (unsigned short)e.s) : __uint_as_float(e.s);
-                        float sn = fmaf(e.la, s0, pp * u);
-                        if (p.state_half) sn = to_state(sn, static_cast<const f16 *>(nullptr));
-                        const TW m = (TW)fmaf(qq, sn, e.be);
+                        float sn;
+                        const TW m = few_mix<TW>(total(at), e.b_in, s0, e.al, e.be, e.la, col / p.dh < p.hrow, p.state_half, sn);
                         unsigned bits;
                         if constexpr (TS == 2) bits = __builtin_bit_cast(unsigned short, m);
                         else bits = __float_as_uint(m);
@@ -723,12 +991,13 @@ out:
 }
 
 // Words that an earlier call has left in the workspace must not pass for this call's: no tag is zero.  Also the nucleus
-// pass's counter, and the token store of a call whose kernel may give up.
+// pass's counter, and the token store of a call whose kernel may give up.  withdrawn: the vector of an arrival that is withdrawn
+// from the start, or -1.
 __global__ void __launch_bounds__(256)
-few_reset_kernel(u32x4_t *words, int n, int *counter, int32_t *store, int n_store)
+few_reset_kernel(u32x4_t *words, int n, int withdrawn, int *counter, int32_t *store, int n_store)
 {
     const int i0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
-    for (int i = i0; i < n; i += step) words[i] = u32x4_t{0, 0, 0, 0};
+    for (int i = i0; i < n; i += step) words[i] = u32x4_t{i == withdrawn ? (unsigned)kFewWithdrawn : 0, 0, 0, 0};
     for (int i = i0; i < n_store; i += step) store[i] = -1;
     if (i0 == 0) *counter = 0;
 }

@@ -2319,10 +2319,11 @@ static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr
 }
 
 // The launch.  Its work-groups wait for each other, so all of them must become resident: they are at most one per CU (few_ok),
-// other kernels end by themselves (and mega.hpp's few work-groups leave room), and kernels of this kind run one at a time on
-// a device, in the order of their launches, whatever their streams: each launch waits for the event of the one before.  A
-// cooperative launch does as much by a queue of its own, which costs 20 us per launch instead of 5 (a step of 16 layers, d =
-// 1024: 211 | 195 us) and, once used, makes the later launches of the process slower (36 launches, 315 us: by 1 to 2 %).
+// other kernels end by themselves (and mega.hpp's few work-groups leave room), and of this process's own kernels of this kind one
+// runs at a time on a device, in the order of their launches, whatever their streams: each launch waits for the event of the one
+// before.  What this cannot see (other processes' kernels of this kind, cooperative kernels that fill the device) is what their
+// arrival is for.  A cooperative launch costs 20 us instead of 5 (a step of 16 layers, d = 1024: 211 | 195 us) and, once used,
+// makes the later launches of the process slower (36 launches, 315 us: by 1 to 2 %).
 static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st)
 {
     static std::mutex lock;
@@ -2334,6 +2335,12 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
     HIP_TRY(hipExtLaunchKernel(kern, dim3((unsigned)blocks), dim3((unsigned)threads), args, (size_t)lds, st, nullptr, ev, 0));
     return SRM_OK;
 }
+
+// How often an arrival is asked for before it is given up, some 8 ms: longer than any other kernel of this library keeps CUs
+// from it, and about what one work-group alone then takes for a step (us per step, together | alone: d = 1024, 16 layers, 1 row
+// 195 | 7040, 4 rows 290 | 7310, without projections 149 | 5990; d = 512, 8 layers 75 | 960; fp32, d = 256, 8 rows 52 | 410).  The
+// arrival itself costs 0.3 to 0.7 us per launch (195.5 | 196.2; d = 512 74.8 | 75.1).
+constexpr unsigned few_arrive_polls = 1u << 13;
 
 template <typename TW, int D, int NWC, bool PROJ>
 static const void *few_kernel(int mb)
@@ -2374,9 +2381,15 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     a.pw = a.gw + (size_t)mb * (m->wsize == 2 ? m->ff / 2 : m->ff);
     a.flag = reinterpret_cast<unsigned *>(a.pw + (size_t)mb * nb * 2);
     a.max_polls = 1u << 21;                          // a second or two
+    a.arrive_polls = few_arrive_polls;
+    int withdrawn = -1;                              // the last work-group's arrival
+    const char *sw = getenv("SRM_ONE_KERNEL_STEP"), *polls = getenv("SRM_ONE_KERNEL_POLLS");
+    if (sw && sw[0] == '2') withdrawn = (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
+    if (sw && sw[0] == '3') a.arrive_polls = 0;
+    if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
     const int n = (int)(few_bytes(m, mb) / 16), n_store = store ? (int)B * G : 0;
     hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
-                       reinterpret_cast<u32x4_t *>(base), n, w.slow, store, n_store);
+                       reinterpret_cast<u32x4_t *>(base), n, withdrawn, w.slow, store, n_store);
     HIP_TRY(hipGetLastError());
     const int lds = few_lds_bytes((int)m->wsize, D, nwc, mb);
     HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));

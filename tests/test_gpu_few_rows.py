@@ -144,6 +144,88 @@ def test_sampled_and_nucleus_steps_choose_from_their_own_logits(srm, orc_mod):
                 assert got[b] == want
 
 
+@pytest.mark.parametrize("dtype,d,B,variant", CASES)
+def test_one_work_group_alone_gives_the_same_bits(srm, dtype, d, B, variant, monkeypatch):
+    """A launch whose work-groups have not all started is done by one of them.  Forced from the host, first by an arrival that
+    is withdrawn from the start, then by a wait of one look, which ends either way."""
+    kw = dict(vocab=1001, d_model=d, n_layers=6, n_heads=4, n_ctx=12, weight_dtype=dtype, seed=59)
+    kw.update(variant)
+    cfg = srm_synth.tiny_config(**kw)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    toks = srm_synth.make_prompts(cfg, batch=B, length=3)
+    for how in (dict(), dict(temperature=0.8, seed=3)):
+        want, st = _steps(model, cfg, B, 3, toks, **how)
+        for mode in ("2", "3"):
+            monkeypatch.setenv(SWITCH, mode)
+            print(f"one work-group alone {dtype} d={d} B={B} {variant} mode {mode}", flush=True)
+            got, st2 = _steps(model, cfg, B, 3, toks, **how)
+            monkeypatch.delenv(SWITCH)
+            for a, b in zip(want, got):
+                assert all(torch.equal(x, y) for x, y in zip(a, b))
+            assert torch.equal(st, st2)
+    model.close()
+
+
+@pytest.mark.parametrize("dtype,d,B", [("fp32", 256, 5), ("bf16", 512, 3), ("bf16", 1024, 2)])
+def test_generation_by_one_work_group_alone(srm, dtype, d, B, monkeypatch):
+    """All steps of a generate call, their tokens and state carried on, five and seven layers."""
+    for layers in (5, 7):
+        cfg = srm_synth.tiny_config(vocab=333, d_model=d, n_layers=layers, n_heads=4, n_ctx=40, weight_dtype=dtype, seed=61)
+        model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+        G, got = 9, []
+        for mode in (None, "2", "3"):
+            if mode:
+                monkeypatch.setenv(SWITCH, mode)
+            st, ws = model.new_state(B), model.new_workspace(B)
+            tk, out = to_dev(np.arange(B, dtype=np.int32)), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+            print(f"generation by one work-group alone d={d} layers={layers} mode {mode}", flush=True)
+            model.generate(B, 2, G, tk, st, out, workspace=ws, temperature=0.7, seed=11)
+            torch.cuda.synchronize()
+            got.append((st, tk, out))
+        monkeypatch.delenv(SWITCH)
+        assert torch.equal(got[0][1], got[0][2][-1]) and (got[0][2] >= 0).all()
+        for other in got[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+        model.close()
+
+
+def test_a_wait_that_gives_up_leaves_marked_tokens(srm, monkeypatch):
+    """The bound of the waits behind the arrival, set so short from the host that some give up at once: every wavefront ends,
+    the tokens are -1 (behind a nucleus pass too, which takes a negative token for an idle row), and the next call is right."""
+    for dtype, d, B, bare in (("bf16", 512, 3, False), ("bf16", 1024, 4, True), ("fp32", 256, 8, False)):
+        cfg = srm_synth.tiny_config(vocab=1001, d_model=d, n_layers=6, n_heads=4, n_ctx=16, weight_dtype=dtype, seed=67,
+                                    use_projections=not bare)
+        model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+        ws, lg = model.new_workspace(B), torch.zeros((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        tok = to_dev(np.arange(B, dtype=np.int32) * 7)
+
+        def step(**how):
+            st, out = model.new_state(B), torch.full((B,), 5, dtype=torch.int32, device="cuda")
+            model.decode_step(B, 1, tok, st, out, logits=lg, workspace=ws, **how)
+            torch.cuda.synchronize()
+            return out, st, lg.clone()
+
+        def generate():
+            st, tk, out = model.new_state(B), tok.clone(), torch.full((4, B), -7, dtype=torch.int32, device="cuda")
+            model.generate(B, 1, 4, tk, st, out, workspace=ws)
+            torch.cuda.synchronize()
+            return tk, out
+
+        ways = (dict(), dict(temperature=0.7, seed=3), dict(temperature=0.7, top_p=0.6, seed=3))
+        want = [step(**how) for how in ways]
+        monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+        for how in ways:
+            print(f"a wait that gives up {dtype} d={d} B={B} {how}", flush=True)
+            assert (step(**how)[0] == -1).all()
+        if not bare:
+            tk, out = generate()
+            assert (tk == -1).all() and (out == -1).any()
+        monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+        for how, w in zip(ways, want):
+            assert all(torch.equal(a, b) for a, b in zip(step(**how), w))
+        model.close()
+
+
 def test_which_calls_run_as_one_kernel(srm, monkeypatch):
     """By rows, layers and the switch, and never into a graph that is being captured."""
     cfg = srm_synth.tiny_config(vocab=300, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
