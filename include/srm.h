@@ -60,10 +60,13 @@
  *                        srm_generate for those with projections and at least
  *                        six layers times steps (SRM_MEGAKERNEL unset); not on a
  *                        stream that is being captured or whose CU mask leaves
- *                        out some CUs.  Such kernels run one at
- *                        a time per process and device, in the order of the calls,
- *                        whatever their streams.  Their work-groups, half the
- *                        device's CUs or fewer, start their work only once all of
+ *                        out some CUs.  Of such
+ *                        kernels two of d_model 1024 or four others run at a time
+ *                        per process and device; further ones wait for those
+ *                        before them, whatever their streams (an event for each
+ *                        is kept until the process ends).  (Many streams of 3 or 4
+ *                        samples each at d_model 1024 get more done with =0.)
+ *                        Their work-groups start their work only once all of
  *                        them have started.  Where that does not come about within
  *                        some 8 ms (kernels of other processes that wait for each
  *                        other too, cooperative kernels that fill the device), one

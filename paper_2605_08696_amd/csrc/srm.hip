@@ -64,7 +64,8 @@ struct LayerDev {
 
 struct FewLayer;              // (few.hpp)
 typedef unsigned long long few_word;
-constexpr int kFewDevices = 64;                      // devices that few_launch keeps an event for
+constexpr int kFewDevices = 64;                      // devices that few_launch keeps events for
+constexpr int kFewShare = 64, kFewShares = 8;        // CUs of one of its shares of a device; shares at most
 constexpr int kFewMaxLayers = 64;                    // their pointers are kept in LDS
 
 struct srm_model {
@@ -1467,7 +1468,8 @@ static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_by
     if (G * m->L < 6) return false;
     const char *e = getenv("SRM_ONE_KERNEL_STEP");
     if (e && e[0] == '0') return false;
-    if (srm_workspace_bytes(m, B) > workspace_bytes || m->d / few_columns(m) > device_cus()) return false;
+    if (srm_workspace_bytes(m, B) > workspace_bytes ||
+        align_up(m->d / few_columns(m), kFewShare) > (size_t)device_cus()) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
     // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
@@ -2318,21 +2320,51 @@ static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr
     return SRM_OK;
 }
 
-// The launch.  Its work-groups wait for each other, so all of them must become resident: they are at most one per CU (few_ok),
-// other kernels end by themselves (and mega.hpp's few work-groups leave room), and of this process's own kernels of this kind one
-// runs at a time on a device, in the order of their launches, whatever their streams: each launch waits for the event of the one
-// before.  What this cannot see (other processes' kernels of this kind, cooperative kernels that fill the device) is what their
+// The launch.  Its work-groups wait for each other, so all of them must become resident: of this process's kernels of this kind
+// only as many run at a time on a device as have a CU for each work-group (two of d = 1024, four of the others), whatever their
+// streams, and other kernels end by themselves.  The CUs are counted in shares of 64, each with the event of its latest kernel;
+// a launch takes the shares that its stream had before, else unused ones, else those used longest ago, and waits for their
+// events.  What this cannot see (other processes' kernels of this kind, cooperative kernels that fill the device) is what the
 // arrival is for.  A cooperative launch costs 20 us instead of 5 (a step of 16 layers, d = 1024: 211 | 195 us) and, once used,
 // makes the later launches of the process slower (36 launches, 315 us: by 1 to 2 %).
+// us per step of 1 | 2 | 4 | 8 streams at once, a thread each, all streams together: d = 512, 1 row: one kernel at a time 73 | 76 |
+// 76 | 76, this 73 | 41 | 24 | 28, step kernels 134 | 77 | 42 | 41; 4 rows 97 | 99 | 99 | 99, 97 | 51 | 31 | 36, 137 | 75 | 43 | 42;
+// d = 1024, 1 row 198 | 200 | 200 | 199, 198 | 123 | 124 | 128, 348 | 209 | 127 | 164; 4 rows 289 | 291 | 290 | 291, 288 | 168 | 171 |
+// 177, 354 | 213 | 130 | 131: there the step kernels are the better ones from four streams on.
 static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st)
 {
+    struct Share { hipEvent_t ev; hipStream_t st; unsigned long long used; };        // st: only a preference
+    struct Device { Share share[kFewShares]; hipEvent_t own[kFewShares]; };          // events are kept until the process ends
     static std::mutex lock;
-    static hipEvent_t last[kFewDevices];             // kept until the process ends
+    static Device devices[kFewDevices];
+    static unsigned long long launches;
     const std::lock_guard<std::mutex> hold(lock);
-    hipEvent_t &ev = last[device];
+    Device &d = devices[device];
+    const int need = (int)cdiv(blocks, kFewShare), all = std::min(device_cus() / kFewShare, kFewShares) / need * need;
+    if (need < 1 || all < need) return fail(SRM_EINVAL, "few_launch: %d work-groups", blocks);
+    int at = 0;
+    auto rank = [&](int i) {                         // of the shares from i on: smaller is better
+        unsigned long long latest = 0;
+        bool mine = true;
+        for (int k = i; k < i + need; ++k) {
+            latest = std::max(latest, d.share[k].used);
+            mine = mine && d.share[k].used && d.share[k].st == st;
+        }
+        return mine ? 0 : latest + 1;
+    };
+    for (int i = need; i < all; i += need)
+        if (rank(i) < rank(at)) at = i;
+    hipEvent_t &ev = d.own[at];
     if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    else HIP_TRY(hipStreamWaitEvent(st, ev, 0));
+    hipEvent_t waited = nullptr;
+    for (int k = at; k < at + need; ++k) {
+        const hipEvent_t before = d.share[k].ev;
+        if (before && before != waited) HIP_TRY(hipStreamWaitEvent(st, before, 0));
+        waited = before;
+    }
     HIP_TRY(hipExtLaunchKernel(kern, dim3((unsigned)blocks), dim3((unsigned)threads), args, (size_t)lds, st, nullptr, ev, 0));
+    ++launches;
+    for (int k = at; k < at + need; ++k) d.share[k] = Share{ev, st, launches};
     return SRM_OK;
 }
 

@@ -324,6 +324,42 @@ def test_calls_on_several_streams_and_threads(srm):
         assert all(torch.equal(x, y) for x, y in zip(a, b))
 
 
+def test_streams_run_side_by_side_and_more_than_fit_in_turn(srm):
+    """Generate calls of two models on seven streams, more than have a CU for each work-group at once: two of the first ones
+    run at the same time, and all results are those of the same calls alone."""
+    from torch.profiler import profile, ProfilerActivity
+    models = []
+    for dtype, d in (("fp32", 256), ("bf16", 1024)):
+        cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=64, weight_dtype=dtype, seed=29)
+        models.append((cfg, srm.Model(cfg, srm_synth.make_weights(cfg))))
+    jobs, G = 7, 48
+
+    def prepare(k):
+        cfg, model = models[k % 2]
+        B = 1 + k % 4
+        return model, B, model.new_state(B), model.new_workspace(B), to_dev((np.arange(B) * 13 + k).astype(np.int32)), \
+            torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+
+    def run(job, stream=None):
+        model, B, st, ws, tk, out = job
+        model.generate(B, 1, G, tk, st, out, workspace=ws, stream=stream)
+        return tk, st, out
+
+    alone = [run(prepare(k)) for k in range(jobs)]
+    again = [prepare(k) for k in range(jobs)]
+    streams = [torch.cuda.Stream() for _ in range(jobs)]
+    torch.cuda.synchronize()
+    print("one-kernel generation on seven streams", flush=True)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        got = [run(again[k], streams[k]) for k in range(jobs)]
+        torch.cuda.synchronize()
+    for a, b in zip(alone, got):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    spans = sorted((e.time_range.start, e.time_range.end) for e in prof.events() if "few_rows_kernel" in e.name)
+    assert len(spans) == jobs
+    assert any(spans[i + 1][0] < spans[i][1] for i in range(jobs - 1)), spans
+
+
 def test_workspace_size_without_a_model(srm):
     """The size computed from a configuration alone covers the words of the one-kernel steps too."""
     for dtype, d in (("bf16", 1024), ("bf16", 512), ("fp32", 256), ("bf16", 256)):
