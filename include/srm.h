@@ -170,6 +170,11 @@ typedef struct {
  * Copy the weights to the current HIP device (casting matrices to bf16 when
  * configured) and return an opaque model.  ("Method": one parameter set serves
  * both the recurrent and the parallel form.)
+ * A model whose steps can run as one kernel (SRM_ONE_KERNEL_STEP above) keeps
+ * its block matrices and its head a second time, in the order that kernel reads
+ * them, so that the matrices take up to twice their memory; not with
+ * SRM_ONE_KERNEL_STEP=0 at this call, nor where the device's memory has no room
+ * left for the copy: such a model runs by the step kernels.
  * Errors: SRM_EINVAL for a null pointer, non-positive size, odd n_heads with
  * mixed heads, more than 64 coefficient rows per layer, an unknown head_layout,
  * combined heads or mixer_kernel > 1 without projections, mixer_kernel > 1 with

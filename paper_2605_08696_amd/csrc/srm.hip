@@ -192,7 +192,6 @@ static int few_max_rows(const srm_model *m)
     if (m->wsize == 2) return m->d == 512 || m->d == 1024 ? 4 : 0;
     return m->d == 256 && !m->noproj ? 8 : 0;
 }
-static bool few_shape_ok(const srm_model *m) { return few_max_rows(m) > 0; }
 static int few_columns(const srm_model *m) { return m->wsize == 2 ? 8 : 4; }
 static int few_bucket(int64_t B) { return B <= 1 ? 1 : B <= 2 ? 2 : B <= 4 ? 4 : 8; }         // rows the kernel is unrolled for
 // Bytes of its words in the workspace (rows: the rows that the kernel is unrolled for).
@@ -202,6 +201,7 @@ static size_t few_bytes(const srm_model *m, int64_t rows)
     return (size_t)rows * ((size_t)2 * m->d + gw + 2 * (m->d / few_columns(m))) * sizeof(few_word) + 256;
 }
 
+static bool few_packable(const srm_model *m);
 static int few_pack(srm_model *m);
 
 extern "C" int srm_init_weights(const srm_config *cfg, const srm_host_weights *w, srm_model **out)
@@ -347,7 +347,7 @@ extern "C" int srm_init_weights(const srm_config *cfg, const srm_host_weights *w
             return fail(SRM_EHIP, "srm_init_weights: layer table: %s", hipGetErrorString(e));
         }
     }
-    if (few_shape_ok(m)) {
+    if (few_packable(m)) {
         const int rc = few_pack(m);
         if (rc != SRM_OK) { srm_free(m); return rc; }
     }
@@ -1462,14 +1462,15 @@ extern "C" int srm_decode_step_ragged(srm_model *m, int64_t B, int32_t *d_pos, i
 // 117 | 77, 114 | 59; fp32, d = 256: 8 rows 84 | 52, 1 row 80 | 32).  Shallower models have little to gain and keep a step
 // whose sums are, bit for bit, those of the ragged step and of larger batches.
 // SRM_ONE_KERNEL_STEP=0 in the environment keeps the step kernels.
+static bool few_off()
+{
+    const char *e = getenv("SRM_ONE_KERNEL_STEP");
+    return e && e[0] == '0';
+}
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {
-    if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || m->device >= kFewDevices) return false;
-    if (G * m->L < 6) return false;
-    const char *e = getenv("SRM_ONE_KERNEL_STEP");
-    if (e && e[0] == '0') return false;
-    if (srm_workspace_bytes(m, B) > workspace_bytes ||
-        align_up(m->d / few_columns(m), kFewShare) > (size_t)device_cus()) return false;
+    if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
+    if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
     // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
@@ -2263,6 +2264,13 @@ extern "C" int srm_linear(int32_t dtype, int32_t epilogue, const void *d_A, cons
 // of the others were up to 1 % slower, by where their own code then lies: sequence form 4 x 256 of the fp32 model 191.8 | 193.5 us.)
 #include "few.hpp"
 
+// Whether a model gets the packed copies: where some call can use them on this device (current when the model is made).
+static bool few_packable(const srm_model *m)
+{
+    return few_max_rows(m) > 0 && (!m->noproj || m->L >= 6) && !few_off() && m->device < kFewDevices &&
+           align_up(m->d / few_columns(m), kFewShare) <= (size_t)device_cus();
+}
+
 // The packed copies of a model's matrices and, in front of them, its table of layers: one allocation of whole 2 MB pages (a table
 // of its own and the odd size went with decode steps of 65536 samples up to 1 % slower, 27119 against 26849 us before there were
 // copies; 26735 against 26723 this way).
@@ -2272,8 +2280,12 @@ static int few_pack(srm_model *m)
     const size_t head = align_up((size_t)m->V, 4) * d * s, table = align_up(sizeof(FewLayer) * m->L, 256);
     const size_t total = align_up(table + m->L * (2 * proj + 2 * mlp) + head, (size_t)2 << 20);
     hipError_t e = hipMalloc(&m->few_slab, total);
-    if (e != hipSuccess)
-        return fail(e == hipErrorOutOfMemory ? SRM_ENOMEM : SRM_EHIP, "srm_init_weights: hipMalloc(%zu): %s", total, hipGetErrorString(e));
+    if (e == hipErrorOutOfMemory) {                  // the step kernels do all that these are for
+        (void)hipGetLastError();
+        m->few_slab = nullptr;
+        return SRM_OK;
+    }
+    if (e != hipSuccess) return fail(SRM_EHIP, "srm_init_weights: hipMalloc(%zu): %s", total, hipGetErrorString(e));
     m->few_layers = static_cast<FewLayer *>(m->few_slab);
     unsigned char *at = static_cast<unsigned char *>(m->few_slab) + table;
     auto pack = [&](const void *W, size_t N, size_t K) {

@@ -360,6 +360,88 @@ def test_streams_run_side_by_side_and_more_than_fit_in_turn(srm):
     assert any(spans[i + 1][0] < spans[i][1] for i in range(jobs - 1)), spans
 
 
+def test_packed_copies_only_where_a_call_can_use_them(srm, monkeypatch):
+    """A model's second copy of its matrices: not where none of its calls can run as one kernel, and not with the switch off."""
+    def memory_of(**kw):
+        cfg = srm_synth.tiny_config(**{**dict(vocab=40000, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3), **kw})
+        w = srm_synth.make_weights(cfg)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        model = srm.Model(cfg, w)
+        used = before - torch.cuda.mem_get_info()[0]
+        st, tok, lg = model.new_state(2), torch.zeros(2, dtype=torch.int32, device="cuda"), torch.empty((2, cfg.vocab), device="cuda")
+        ws, out = model.new_workspace(2), torch.empty(2, dtype=torch.int32, device="cuda")
+        n = _launches(lambda: model.decode_step(2, 0, tok, st, out, logits=lg, workspace=ws))
+        assert torch.equal(out.long(), lg.argmax(dim=1))
+        model.close()
+        return used, n
+
+    matrices = 2 * (40000 + 6 * 10 * 512) * 512                        # bytes of head and blocks; the embedding is kept once
+    memory_of()
+    with_copies, one = memory_of()
+    monkeypatch.setenv(SWITCH, "0")
+    without, none = memory_of()
+    monkeypatch.delenv(SWITCH)
+    assert one == 1 and none == 0 and with_copies - without >= 0.9 * matrices
+    bare = memory_of(use_projections=False, n_layers=5)
+    monkeypatch.setenv(SWITCH, "0")
+    assert bare[1] == 0 and memory_of(use_projections=False, n_layers=5)[0] == bare[0]
+
+
+def test_model_whose_packed_copies_find_no_room_takes_the_step_kernels(srm, monkeypatch):
+    """Device memory filled up to the model's own allocation and about three quarters of the copies (400 MB): the model is made
+    all the same, and its steps are those of the switch."""
+    import ctypes
+    small = srm_synth.tiny_config(vocab=300, d_model=1024, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
+    srm.Model(small, srm_synth.make_weights(small)).close()            # (kernels loaded)
+    cfg = dataclasses.replace(small, vocab=120000)
+    w = srm_synth.make_weights(small)
+    rng = np.random.default_rng(5)
+    for name in ("embed", "head"):
+        w[name] = (0.02 * rng.standard_normal((cfg.vocab, cfg.d_model), dtype=np.float32))
+    tok, B = to_dev(np.arange(3, dtype=np.int32)), 3
+    lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+    hip = ctypes.CDLL("libamdhip64.so")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    matrices = 2 * (cfg.vocab + 6 * 10 * 1024) * 1024                  # bytes of the copies
+    own = matrices + 2 * cfg.vocab * 1024 + (8 << 20)
+    held = []
+
+    def hold(n):
+        at = ctypes.c_void_p()
+        if hip.hipMalloc(ctypes.byref(at), ctypes.c_size_t(n)) != 0:
+            hip.hipGetLastError()
+            return False
+        held.append(at)
+        return True
+
+    try:
+        assert hold(torch.cuda.mem_get_info()[0] - own - matrices)     # (more can be had than is said to be free)
+        for _ in range(400):                                           # until the model fits and three quarters of the copies do not
+            if not hold(own + matrices * 3 // 4):
+                break
+            assert hip.hipFree(held.pop()) == 0 and hold(32 << 20)
+        print(f"device memory filled, {len(held)} pieces", flush=True)
+        model = srm.Model(cfg, w)
+    finally:
+        for at in held:
+            assert hip.hipFree(at) == 0
+
+    def step():
+        st, out, ws = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda"), model.new_workspace(B)
+        model.decode_step(B, 0, tok, st, out, logits=lg, workspace=ws)
+        torch.cuda.synchronize()
+        return lg.clone(), out, st
+
+    assert _launches(step) == 0
+    got = step()
+    monkeypatch.setenv(SWITCH, "0")
+    assert all(torch.equal(a, b) for a, b in zip(got, step()))
+    assert torch.equal(got[1].long(), got[0].argmax(dim=1))
+    model.close()
+
+
 def test_workspace_size_without_a_model(srm):
     """The size computed from a configuration alone covers the words of the one-kernel steps too."""
     for dtype, d in (("bf16", 1024), ("bf16", 512), ("fp32", 256), ("bf16", 256)):
