@@ -440,11 +440,16 @@ static Workspace carve(const srm_model *m, void *base, int64_t rows)
     return w;
 }
 
+// The arrays of `rows` rows: what every call needs of its workspace, whatever its kernels.
+static size_t row_bytes(const srm_model *m, int64_t rows) { return rows > 0 ? carve(m, nullptr, rows).bytes : 0; }
+
+// What srm_workspace_bytes promises to be enough: behind them the words of few.hpp, without which a step of a few rows takes the
+// step kernels.
 extern "C" size_t srm_workspace_bytes(const srm_model *m, int64_t rows)
 {
     if (!m || rows <= 0) return 0;
-    const int few = few_max_rows(m);                 // the words of few.hpp lie behind the row arrays
-    return carve(m, nullptr, rows).bytes + (few ? few_bytes(m, few_bucket(std::min<int64_t>(rows, few))) : 0);
+    const int few = few_max_rows(m);
+    return row_bytes(m, rows) + (few ? few_bytes(m, few_bucket(std::min<int64_t>(rows, few))) : 0);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1354,15 +1359,15 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
 // Rows per pass of a decode call: the whole batch if the workspace holds it, else as many
 // rows as it holds (the samples are independent, so a step can be taken in slices; this lets
 // a caller keep far more sequences resident than one workspace covers).  0: too small.
-// srm_workspace_bytes(rows) = the row arrays + 256 bytes that srm_generate uses for its step
+// row_bytes(rows) = the row arrays + 256 bytes that srm_generate uses for its step
 // counters at the very end of the caller's buffer, so the row arrays get workspace_bytes - 256.
 static int64_t decode_rows_per_pass(const srm_model *m, int64_t B, size_t workspace_bytes)
 {
-    if (srm_workspace_bytes(m, B) <= workspace_bytes) return B;
+    if (row_bytes(m, B) <= workspace_bytes) return B;
     int64_t lo = 0, hi = B;
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) / 2;
-        if (srm_workspace_bytes(m, mid) <= workspace_bytes) lo = mid; else hi = mid - 1;
+        if (row_bytes(m, mid) <= workspace_bytes) lo = mid; else hi = mid - 1;
     }
     if (lo >= 256) lo = lo / 256 * 256;       // whole GEMM tiles per pass
     return lo < std::min<int64_t>(B, 256) ? 0 : lo;
@@ -1470,7 +1475,7 @@ static bool few_off()
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {
     if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
-    if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
+    if (few_off() || row_bytes(m, B) + few_bytes(m, few_bucket(B)) > workspace_bytes) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
     // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
@@ -1594,7 +1599,7 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
     hipStream_t st = as_stream(hip_stream);
     if (!topp && !d_pos && !eos_plus1 && !getenv("SRM_MEGAKERNEL") && few_ok(m, B, G, ws_bytes, st))
         return few_run(m, B, pos0, G, d_tok, d_tok, d_tokens_out, d_state, temperature, seed, nullptr, nullptr, d_workspace, st);
-    if (!topp && !d_pos && !eos_plus1 && srm_workspace_bytes(m, B) <= ws_bytes) {
+    if (!topp && !d_pos && !eos_plus1 && row_bytes(m, B) <= ws_bytes) {
         const int nblk = mega_blocks(m, B);
         if (nblk > 0)
             return mega_generate(m, (int)B, pos0, G, d_tok, d_state, d_tokens_out, temperature, seed, d_workspace, nblk, st);
@@ -1669,11 +1674,11 @@ extern "C" int srm_generate_ragged(srm_model *m, int64_t B, int32_t G, int32_t *
 // Whole sequences per pass that fit the workspace (0 if not even one does).
 static int64_t seqs_per_pass(const srm_model *m, size_t workspace_bytes, int T, int64_t nseq)
 {
-    if (srm_workspace_bytes(m, T) > workspace_bytes) return 0;
+    if (row_bytes(m, T) > workspace_bytes) return 0;
     int64_t lo = 1, hi = nseq;       // largest n with bytes(n*T) <= workspace_bytes
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) / 2;
-        if (srm_workspace_bytes(m, mid * T) <= workspace_bytes) lo = mid; else hi = mid - 1;
+        if (row_bytes(m, mid * T) <= workspace_bytes) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -1864,7 +1869,7 @@ extern "C" int srm_prefill(srm_model *m, const int32_t *d_prompts, int32_t N, in
     int64_t per_pass = seqs_per_pass(m, workspace_bytes, P, std::min<int64_t>(N, max_seqs));
     if (per_pass < 1)
         return fail(SRM_ENOMEM, "srm_prefill: workspace %zu < %zu bytes (one prompt)", workspace_bytes,
-                    srm_workspace_bytes(m, P));
+                    row_bytes(m, P));
     SRM_TRY(check_device(m));
     hipStream_t st = as_stream(hip_stream);
     return m->wsize == 2 ? prefill_impl<bf16>(m, d_prompts, N, P, fanout_k, d_state, d_next_tok, d_logits,
@@ -1927,11 +1932,11 @@ static int ragged_lengths(const char *who, const srm_model *m, const int32_t *h_
                           int64_t &max_rows, int &pmax)
 {
     if (h_offsets[0] < 0) return fail(SRM_EINVAL, "%s: offsets[0] is negative", who);
-    // rows the workspace holds (largest r with srm_workspace_bytes(r) <= workspace_bytes)
+    // rows the workspace holds (largest r with row_bytes(r) <= workspace_bytes)
     int64_t lo = 0, hi = (1 << 30) - 1;
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) / 2;
-        if (srm_workspace_bytes(m, mid) <= workspace_bytes) lo = mid; else hi = mid - 1;
+        if (row_bytes(m, mid) <= workspace_bytes) lo = mid; else hi = mid - 1;
     }
     max_rows = lo;
     pmax = 0;
@@ -1942,7 +1947,7 @@ static int ragged_lengths(const char *who, const srm_model *m, const int32_t *h_
                         m->cfg.n_ctx);
         if (len > max_rows)
             return fail(SRM_ENOMEM, "%s: workspace %zu < %zu bytes (prompt %d of %lld tokens)", who, workspace_bytes,
-                        srm_workspace_bytes(m, len), n, (long long)len);
+                        row_bytes(m, len), n, (long long)len);
         pmax = std::max(pmax, (int)len);
     }
     return SRM_OK;
@@ -2043,7 +2048,7 @@ extern "C" int srm_parallel_forward(srm_model *m, const int32_t *d_tok, int32_t 
     int64_t per_pass = seqs_per_pass(m, workspace_bytes, T, std::min<int64_t>(B, max_seqs));
     if (per_pass < 1)
         return fail(SRM_ENOMEM, "srm_parallel_forward: workspace %zu < %zu bytes (one sequence)", workspace_bytes,
-                    srm_workspace_bytes(m, T));
+                    row_bytes(m, T));
     SRM_TRY(check_device(m));
     hipStream_t st = as_stream(hip_stream);
     return m->wsize == 2

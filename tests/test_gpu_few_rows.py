@@ -442,6 +442,52 @@ def test_model_whose_packed_copies_find_no_room_takes_the_step_kernels(srm, monk
     model.close()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 512), ("fp32", 256)])
+def test_workspace_without_room_for_the_words(srm, dtype, d, monkeypatch):
+    """The words lie behind the arrays of the rows.  A workspace of those alone holds as many rows as ever: a step of a few by
+    the step kernels, a larger batch in one pass, prompts and sequences of that many positions."""
+    cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=64, weight_dtype=dtype, seed=23)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    most, cols, gw = (4, 8, 2 * d) if dtype == "bf16" else (8, 4, 4 * d)
+
+    def arrays(rows):                                                  # bytes without the words
+        unrolled = next(n for n in (1, 2, 4, 8) if n >= min(rows, most))
+        return model.workspace_bytes(rows) - unrolled * (2 * d + gw + 2 * (d // cols)) * 8 - 256
+
+    def step(B, nbytes):
+        ws = torch.randint(0, 256, (nbytes + 4096,), dtype=torch.uint8, device="cuda")
+        guard, st, out = ws[nbytes:].clone(), model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        tok = to_dev((np.arange(B) % cfg.vocab).astype(np.int32))
+        model.decode_step(B, 2, tok, st, out, workspace=ws[:nbytes])
+        torch.cuda.synchronize()
+        assert torch.equal(ws[nbytes:], guard)
+        return out, st
+
+    for B in (1, most, most + 1, 300):
+        small, whole = step(B, arrays(B)), step(B, model.workspace_bytes(B))
+        assert _launches(lambda: step(B, model.workspace_bytes(B))) == (B <= most)
+        assert _launches(lambda: step(B, arrays(B))) == 0
+        if B <= most:
+            monkeypatch.setenv(SWITCH, "0")
+            whole = step(B, model.workspace_bytes(B))
+            monkeypatch.delenv(SWITCH)
+        assert all(torch.equal(a, b) for a, b in zip(small, whole))
+        with pytest.raises(srm.SrmError):
+            step(min(B, 256), arrays(min(B, 256)) - 256)
+    P = 40
+    toks, st, tk = to_dev(srm_synth.make_prompts(cfg, batch=1, length=P)), model.new_state(1), torch.empty(1, dtype=torch.int32, device="cuda")
+    off, hid = np.array([0, P], dtype=np.int32), torch.empty((1, P, d), dtype=torch.float32, device="cuda")
+    ws = torch.empty(arrays(P), dtype=torch.uint8, device="cuda")
+    model.prefill(toks, 1, st, tk, workspace=ws)
+    keep = model.prefill_ragged(toks.view(-1), off, st, tk, workspace=ws)
+    model.parallel_forward(toks, hid, workspace=ws)
+    assert srm.prefill_ragged_plan(cfg, off, arrays(P))["passes"] == 1
+    torch.cuda.synchronize()
+    del keep
+    with pytest.raises(srm.SrmError):
+        srm.prefill_ragged_plan(cfg, off, arrays(P) - 256)
+
+
 def test_workspace_size_without_a_model(srm):
     """The size computed from a configuration alone covers the words of the one-kernel steps too."""
     for dtype, d in (("bf16", 1024), ("bf16", 512), ("fp32", 256), ("bf16", 256)):
