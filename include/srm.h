@@ -202,8 +202,9 @@ size_t srm_state_bytes(const srm_model *m, int64_t batch);
  * not by the workspace.  Results do not depend on the slicing in fp32 models; in
  * bf16 models a slice takes the kernels of its size, which may sum in another
  * order.
- * It includes what a step as one kernel exchanges (SRM_ONE_KERNEL_STEP above);
- * a workspace short of that alone is accepted and takes the step kernels.
+ * Of a few rows it covers what a step as one kernel exchanges
+ * (SRM_ONE_KERNEL_STEP above), which is more than the arrays of the rows; a
+ * workspace short of that alone is accepted and takes the step kernels.
  */
 size_t srm_workspace_bytes(const srm_model *m, int64_t rows);
 /* The same number from a configuration alone (host only, no GPU call), for sizing buffers before a model

@@ -194,12 +194,15 @@ static int few_max_rows(const srm_model *m)
 }
 static int few_columns(const srm_model *m) { return m->wsize == 2 ? 8 : 4; }
 static int few_bucket(int64_t B) { return B <= 1 ? 1 : B <= 2 ? 2 : B <= 4 ? 4 : 8; }         // rows the kernel is unrolled for
-// Bytes of its words in the workspace (rows: the rows that the kernel is unrolled for).
-static size_t few_bytes(const srm_model *m, int64_t rows)
+// Its memory in the workspace, in the place of the row arrays: the nucleus pass's list (Workspace::slow) of B rows, then the words
+// of the rows that the kernel is unrolled for.
+static size_t few_list_bytes(int64_t B) { return align_up(256 + (size_t)B * 4, 256); }
+static size_t few_words_bytes(const srm_model *m, int64_t B)
 {
     const size_t gw = m->wsize == 2 ? m->ff / 2 : m->ff;
-    return (size_t)rows * ((size_t)2 * m->d + gw + 2 * (m->d / few_columns(m))) * sizeof(few_word) + 256;
+    return (size_t)few_bucket(B) * ((size_t)2 * m->d + gw + 2 * (m->d / few_columns(m))) * sizeof(few_word) + 256;
 }
+static size_t few_bytes(const srm_model *m, int64_t B) { return few_list_bytes(B) + few_words_bytes(m, B); }
 
 static bool few_packable(const srm_model *m);
 static int few_pack(srm_model *m);
@@ -443,13 +446,13 @@ static Workspace carve(const srm_model *m, void *base, int64_t rows)
 // The arrays of `rows` rows: what every call needs of its workspace, whatever its kernels.
 static size_t row_bytes(const srm_model *m, int64_t rows) { return rows > 0 ? carve(m, nullptr, rows).bytes : 0; }
 
-// What srm_workspace_bytes promises to be enough: behind them the words of few.hpp, without which a step of a few rows takes the
-// step kernels.
+// What srm_workspace_bytes promises to be enough: also for the words of few.hpp, which are more than the arrays of a few rows.  A
+// workspace without room for them takes the step kernels.
 extern "C" size_t srm_workspace_bytes(const srm_model *m, int64_t rows)
 {
     if (!m || rows <= 0) return 0;
     const int few = few_max_rows(m);
-    return row_bytes(m, rows) + (few ? few_bytes(m, few_bucket(std::min<int64_t>(rows, few))) : 0);
+    return std::max(row_bytes(m, rows), few ? few_bytes(m, std::min<int64_t>(rows, few)) : 0);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1408,7 +1411,7 @@ static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t 
                         d_workspace, st));
         if (!(temperature > 0.0f && top_p < 1.0f)) return SRM_OK;
         return nucleus(d_logits, B, m->V, Sampling{temperature, seed, pos, nullptr, nullptr, top_p}, d_tok_out, nullptr, nullptr,
-                       0, nullptr, carve(m, d_workspace, B).slow, st);
+                       0, nullptr, static_cast<int *>(d_workspace), st);
     }
     const DecodeArgs a{B, pos, nullptr, nullptr, 0, d_tok_in, d_state, d_tok_out, d_logits, d_hidden, TokenStore(),
                        temperature, seed, top_p};
@@ -1475,7 +1478,7 @@ static bool few_off()
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {
     if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
-    if (few_off() || row_bytes(m, B) + few_bytes(m, few_bucket(B)) > workspace_bytes) return false;
+    if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
     // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
@@ -2407,7 +2410,6 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
                    void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st)
 {
     const int mb = few_bucket(B), D = m->d, nwc = few_columns(m), nb = D / nwc;
-    const Workspace w = carve(m, ws, B);
     const void *kern = m->wsize == 4 ? few_kernel<float, 256, 4, true>(mb)
                        : m->noproj ? (D == 512 ? few_kernel<bf16, 512, 8, false>(mb) : few_kernel<bf16, 1024, 8, false>(mb))
                                    : (D == 512 ? few_kernel<bf16, 512, 8, true>(mb) : few_kernel<bf16, 1024, 8, true>(mb));
@@ -2423,7 +2425,7 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     a.state = state; a.state_half = m->shalf ? 1 : 0;
     a.logits = logits; a.hidden = hidden;
     a.temp = temperature; a.seed = seed;
-    unsigned char *base = static_cast<unsigned char *>(ws) + w.bytes;
+    unsigned char *base = static_cast<unsigned char *>(ws) + few_list_bytes(B);
     a.xw = reinterpret_cast<few_word *>(base);
     a.mw = a.xw + (size_t)mb * D;
     a.gw = a.mw + (size_t)mb * D;
@@ -2436,9 +2438,9 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     if (sw && sw[0] == '2') withdrawn = (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
     if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
-    const int n = (int)(few_bytes(m, mb) / 16), n_store = store ? (int)B * G : 0;
+    const int n = (int)(few_words_bytes(m, B) / 16), n_store = store ? (int)B * G : 0;
     hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
-                       reinterpret_cast<u32x4_t *>(base), n, withdrawn, w.slow, store, n_store);
+                       reinterpret_cast<u32x4_t *>(base), n, withdrawn, static_cast<int *>(ws), store, n_store);
     HIP_TRY(hipGetLastError());
     const int lds = few_lds_bytes((int)m->wsize, D, nwc, mb);
     HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));

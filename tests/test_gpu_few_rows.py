@@ -442,36 +442,48 @@ def test_model_whose_packed_copies_find_no_room_takes_the_step_kernels(srm, monk
     model.close()
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 512), ("fp32", 256)])
-def test_workspace_without_room_for_the_words(srm, dtype, d, monkeypatch):
-    """The words lie behind the arrays of the rows.  A workspace of those alone holds as many rows as ever: a step of a few by
-    the step kernels, a larger batch in one pass, prompts and sequences of that many positions."""
+@pytest.mark.parametrize("dtype,d", [("bf16", 512), ("bf16", 1024), ("fp32", 256)])
+def test_workspace_of_the_row_arrays_alone(srm, dtype, d, monkeypatch):
+    """The words lie where the arrays of the rows would, and only those of a few rows need more room.  A workspace of the arrays
+    alone holds as many rows as ever, and no more: a step of a few by the step kernels where the words find no room, a larger
+    batch in one pass, prompts and sequences of that many positions."""
     cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=64, weight_dtype=dtype, seed=23)
     model = srm.Model(cfg, srm_synth.make_weights(cfg))
     most, cols, gw = (4, 8, 2 * d) if dtype == "bf16" else (8, 4, 4 * d)
+    deep = dataclasses.replace(cfg, n_layers=65)                       # (never one kernel: its workspace is the arrays)
 
-    def arrays(rows):                                                  # bytes without the words
-        unrolled = next(n for n in (1, 2, 4, 8) if n >= min(rows, most))
-        return model.workspace_bytes(rows) - unrolled * (2 * d + gw + 2 * (d // cols)) * 8 - 256
+    def arrays(rows):
+        return srm.workspace_bytes_config(deep, rows)
 
-    def step(B, nbytes):
+    def words(B):
+        unrolled = next(n for n in (1, 2, 4, 8) if n >= B)
+        return 512 + unrolled * (2 * d + gw + 2 * (d // cols)) * 8 + 256
+
+    for rows in (most, 9, 32, 300):
+        assert model.workspace_bytes(rows) == max(arrays(rows), words(min(rows, most)))
+    assert model.workspace_bytes(32) == arrays(32) and model.workspace_bytes(300) == arrays(300)
+
+    def step(B, nbytes, **how):
         ws = torch.randint(0, 256, (nbytes + 4096,), dtype=torch.uint8, device="cuda")
         guard, st, out = ws[nbytes:].clone(), model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
-        tok = to_dev((np.arange(B) % cfg.vocab).astype(np.int32))
-        model.decode_step(B, 2, tok, st, out, workspace=ws[:nbytes])
+        tok, lg = to_dev((np.arange(B) % cfg.vocab).astype(np.int32)), torch.empty((B, cfg.vocab), device="cuda")
+        model.decode_step(B, 2, tok, st, out, logits=lg, workspace=ws[:nbytes], **how)
         torch.cuda.synchronize()
         assert torch.equal(ws[nbytes:], guard)
-        return out, st
+        return out, st, lg
 
-    for B in (1, most, most + 1, 300):
-        small, whole = step(B, arrays(B)), step(B, model.workspace_bytes(B))
-        assert _launches(lambda: step(B, model.workspace_bytes(B))) == (B <= most)
-        assert _launches(lambda: step(B, arrays(B))) == 0
-        if B <= most:
-            monkeypatch.setenv(SWITCH, "0")
-            whole = step(B, model.workspace_bytes(B))
-            monkeypatch.delenv(SWITCH)
-        assert all(torch.equal(a, b) for a, b in zip(small, whole))
+    print(f"workspace of the arrays alone {dtype} d={d}", flush=True)
+    for B in (1, 2, most, most + 1, 300):
+        for how in (dict(), dict(temperature=0.7, top_p=0.9, seed=5)):
+            small, whole = step(B, arrays(B), **how), step(B, model.workspace_bytes(B), **how)
+            assert _launches(lambda: step(B, model.workspace_bytes(B), **how)) == (B <= most)
+            one = B <= most and words(B) <= arrays(B)
+            assert _launches(lambda: step(B, arrays(B), **how)) == one
+            if B <= most and not one:
+                monkeypatch.setenv(SWITCH, "0")
+                whole = step(B, model.workspace_bytes(B), **how)
+                monkeypatch.delenv(SWITCH)
+            assert all(torch.equal(a, b) for a, b in zip(small, whole))
         with pytest.raises(srm.SrmError):
             step(min(B, 256), arrays(min(B, 256)) - 256)
     P = 40
@@ -486,6 +498,9 @@ def test_workspace_without_room_for_the_words(srm, dtype, d, monkeypatch):
     del keep
     with pytest.raises(srm.SrmError):
         srm.prefill_ragged_plan(cfg, off, arrays(P) - 256)
+    with pytest.raises(srm.SrmError):                                  # a workspace of fewer rows
+        model.prefill_ragged(toks.view(-1), off, st, tk, workspace=model.new_workspace(P - 8))
+    model.close()
 
 
 def test_workspace_size_without_a_model(srm):
