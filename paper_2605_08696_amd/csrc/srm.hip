@@ -1475,15 +1475,20 @@ static bool few_off()
     const char *e = getenv("SRM_ONE_KERNEL_STEP");
     return e && e[0] == '0';
 }
+// The default stream by its null name: hipExtStreamGetCUMask reads through the other one, hipStreamLegacy, as through a pointer.
+static hipStream_t few_stream(hipStream_t st) { return st == hipStreamLegacy ? nullptr : st; }
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {
     if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
     if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
+    st = few_stream(st);
+    // (where a question is refused the step kernels do the work, and its error must not be taken for one of theirs)
+    auto refused = [](hipError_t e) { return e != hipSuccess && ((void)hipGetLastError(), true); };
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
+    if (refused(hipStreamIsCapturing(st, &cs)) || cs != hipStreamCaptureStatusNone) return false;
     // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
     uint32_t mask[32] = {};
-    if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) return false;
+    if (refused(hipExtStreamGetCUMask(st, 32, mask))) return false;
     int cus = 0;
     for (const uint32_t bits : mask) cus += __builtin_popcount(bits);
     return cus >= device_cus();
@@ -2410,6 +2415,7 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
                    void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st)
 {
     const int mb = few_bucket(B), D = m->d, nwc = few_columns(m), nb = D / nwc;
+    st = few_stream(st);
     const void *kern = m->wsize == 4 ? few_kernel<float, 256, 4, true>(mb)
                        : m->noproj ? (D == 512 ? few_kernel<bf16, 512, 8, false>(mb) : few_kernel<bf16, 1024, 8, false>(mb))
                                    : (D == 512 ? few_kernel<bf16, 512, 8, true>(mb) : few_kernel<bf16, 1024, 8, true>(mb));

@@ -510,3 +510,35 @@ def test_workspace_size_without_a_model(srm):
         model = srm.Model(cfg, srm_synth.make_weights(cfg))
         for rows in (1, 2, 3, 4, 5, 8, 9, 300):
             assert srm.workspace_bytes_config(cfg, rows) == model.workspace_bytes(rows), (dtype, d, rows)
+
+
+def test_streams_that_are_no_objects_of_their_own(srm):
+    """Steps on the runtime's special stream handles (0: default, 1: legacy, 2: per thread) and on a stream that is destroyed
+    behind them: results as on any other stream, and no error left behind for the next call."""
+    import ctypes
+    import types
+    cfg = srm_synth.tiny_config(vocab=300, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    hip, B = ctypes.CDLL("libamdhip64.so"), 3
+    tok, ws = to_dev(np.arange(B, dtype=np.int32) * 5), model.new_workspace(B)
+
+    def step(handle):
+        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        model.decode_step(B, 0, tok, st, out, logits=lg, workspace=ws, stream=types.SimpleNamespace(cuda_stream=handle))
+        assert hip.hipGetLastError() == 0
+        torch.cuda.synchronize()
+        return lg, out, st
+
+    want = step(torch.cuda.Stream().cuda_stream)
+    for handle in (0, 1, 2):
+        print(f"step on stream handle {handle}", flush=True)
+        assert _launches(lambda: step(handle)) == 1
+        assert all(torch.equal(a, b) for a, b in zip(step(handle), want))
+    for _ in range(6):                                   # (more than the library keeps events for at a time)
+        own = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(own)) == 0
+        assert all(torch.equal(a, b) for a, b in zip(step(own.value), want))
+        assert hip.hipStreamDestroy(own) == 0
+    assert all(torch.equal(a, b) for a, b in zip(step(0), want))
