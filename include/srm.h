@@ -80,6 +80,16 @@
  *                        give up, the tokens of the call are -1 and its state is
  *                        undefined (SRM_ONE_KERNEL_POLLS=n, for tests: that bound
  *                        in polls).
+ *                        The step kernels, with fp32 sums in another order, take
+ *                        such steps in all other calls: on a stream that is being
+ *                        captured, in srm_decode_step_ragged and
+ *                        srm_generate_ragged, in generation with a nucleus, and in
+ *                        generation of models without projections.  So the same
+ *                        step by two of these calls agrees up to that rounding (in
+ *                        bf16 models up to the bf16 rounding of the activations
+ *                        behind it) and chooses the same tokens unless two scores
+ *                        tie within it, but need not have the same bits; with =0
+ *                        it has (see srm_generate for its own one-kernel path).
  */
 #ifndef SRM_H
 #define SRM_H
@@ -218,7 +228,10 @@ size_t srm_workspace_bytes_config(const srm_config *cfg, int64_t rows);
  * place (Eq. 2 / Eq. 3), writes the greedy next token d_tok_out[B].
  * Optional outputs (NULL to skip): d_logits[B][vocab] fp32, d_hidden[B][d]
  * fp32 (residual stream after the last block, before the final LayerNorm).
- * d_tok_out may alias d_tok_in.  Errors: SRM_EINVAL (null pointer, B <= 0,
+ * d_tok_out may alias d_tok_in.  A step of a few samples that runs as one kernel
+ * (SRM_ONE_KERNEL_STEP above) waits within bounds: should a wait ever give up,
+ * the tokens are -1 and the state is undefined, behind a return of SRM_OK.
+ * Errors: SRM_EINVAL (null pointer, B <= 0,
  * pos outside [0, n_ctx)), SRM_ENOMEM (workspace smaller than
  * srm_workspace_bytes(m, min(B, 256))).
  */
@@ -260,12 +273,12 @@ int srm_decode_step_sampled(srm_model *m, int64_t B, int32_t pos, const int32_t 
  * stay the same.  On the legacy default stream (NULL), which cannot be
  * captured, the steps are launched one by one instead.  temperature = 0 is
  * greedy; temperature > 0 samples as srm_decode_step_sampled does.  Results are
- * identical to G srm_decode_step(_sampled) calls, except that a call which
- * qualifies for a one-kernel path (see SRM_ONE_KERNEL_STEP above and
- * srm_generate_one_kernel_blocks) runs
- * all G steps in one launch, with fp32 sums in another order: equal
- * to the step calls up to fp32 rounding, token-exact unless two scores tie
- * within that rounding.  Such a call must not be made under stream capture.
+ * identical to G srm_decode_step(_sampled) calls, except where this call runs
+ * all G steps in one launch or those calls run as one kernel each (see
+ * SRM_ONE_KERNEL_STEP above and srm_generate_one_kernel_blocks), with fp32 sums
+ * in another order: equal up to that rounding, token-exact unless two scores tie
+ * within it.  A call that runs in one launch must not be made under stream
+ * capture.
  * The one-kernel path synchronises its work-groups with bounded waits; should a
  * wait ever give up (a work-group that is not resident: never observed), the
  * kernel ends early, d_tok and the rows of d_tokens_out from that step on hold
@@ -346,7 +359,9 @@ int srm_sample_logits(const float *d_logits, int64_t rows, int32_t vocab, float 
  * host-side update.  temperature = 0 is greedy; temperature > 0 samples as
  * srm_decode_step_topp does (top_p >= 1: no truncation), keyed on the sample's
  * own position.  For active samples the result equals the uniform-position call
- * at that position.  d_logits: [B][vocab], optional unless top_p < 1.
+ * at that position, up to the order of fp32 sums where that call runs as one
+ * kernel (SRM_ONE_KERNEL_STEP above).  d_logits: [B][vocab], optional unless
+ * top_p < 1.
  * Errors: SRM_EINVAL (null pointer, B out of range, negative temperature,
  * top_p <= 0, top_p < 1 without d_logits), SRM_ENOMEM (workspace smaller than
  * srm_workspace_bytes(m, B)), SRM_EHIP.

@@ -542,3 +542,100 @@ def test_streams_that_are_no_objects_of_their_own(srm):
         assert all(torch.equal(a, b) for a, b in zip(step(own.value), want))
         assert hip.hipStreamDestroy(own) == 0
     assert all(torch.equal(a, b) for a, b in zip(step(0), want))
+
+
+@pytest.mark.parametrize("d,B,bare", [(512, 3, False), (1024, 2, False), (1024, 4, True)])
+def test_calls_that_keep_the_step_kernels_agree_with_steps_as_one_kernel(srm, d, B, bare, monkeypatch):
+    """A ragged step with all samples at one position, a captured step, and generation with a nucleus or without projections
+    against eager steps that run as one kernel: equal up to the order of sums and the bf16 roundings behind it, the same
+    tokens unless two scores lie that close, and the same bits with the switch off."""
+    cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=37,
+                                use_projections=not bare)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    ws, P, G, tol = model.new_workspace(B), 3, 5, 4e-2           # each of the two within 2e-2 of exact sums
+    tok0 = to_dev((np.arange(B) * 31 + 2).astype(np.int32))
+
+    def logits():
+        return torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+
+    def step(tok, pos, st, lg, **how):
+        out = torch.empty(B, dtype=torch.int32, device="cuda")
+        model.decode_step(B, pos, tok, st, out, logits=lg, workspace=ws, **how)
+        return out
+
+    def eager():
+        st, lg = model.new_state(B), logits()
+        return lg, step(tok0, P, st, lg), st
+
+    def ragged():
+        st, lg, out = model.new_state(B), logits(), torch.empty(B, dtype=torch.int32, device="cuda")
+        pos = torch.full((B,), P, dtype=torch.int32, device="cuda")
+        model.decode_step_ragged(B, pos, tok0, st, out, advance=False, logits=lg, workspace=ws)
+        return lg, out, st
+
+    def captured():
+        st, lg, out = model.new_state(B), logits(), torch.empty(B, dtype=torch.int32, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            model.decode_step(B, P, tok0, st, out, logits=lg, workspace=ws)
+        for _ in range(3):
+            st.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+        return lg, out, st
+
+    def close(a, b):
+        return (a.float() - b.float()).abs().max() <= tol * b.float().abs().max()
+
+    print(f"calls with the step kernels d={d} B={B} bare={bare}", flush=True)
+    eager(), ragged()
+    seen = {"captured": captured()}
+    assert _launches(lambda: seen.update(one=eager())) == 1
+    assert _launches(lambda: seen.update(ragged=ragged())) == 0
+    lg, out, st = seen["one"]
+    for how in ("ragged", "captured"):
+        lg2, out2, st2 = seen[how]
+        assert rel_err_rows(lg2.cpu().numpy(), lg.cpu().numpy()) <= tol and close(st2, st)
+        assert torch.equal(out2.long(), lg2.argmax(dim=1))
+    monkeypatch.setenv(SWITCH, "0")
+    plain = eager()
+    for how in ("ragged", "captured"):
+        assert all(torch.equal(a, b) for a, b in zip(plain, seen[how]))
+    monkeypatch.delenv(SWITCH)
+
+    ways = [dict(temperature=0.7, top_p=0.9, seed=4)] + ([dict()] if bare else [])
+    for how in ways:
+        def generate():
+            st, tk, out = model.new_state(B), tok0.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+            model.generate(B, P, G, tk, st, out, workspace=ws, **how, **({"logits": logits()} if "top_p" in how else {}))
+            torch.cuda.synchronize()
+            return out, st
+
+        def steps(fed=None):                                     # on their own tokens, or on those of `fed`
+            st, tk, rows, outs = model.new_state(B), tok0, [], []
+            for g in range(G):
+                lg = logits()
+                out = step(tk, P + g, st, lg, **how)
+                rows.append(lg)
+                outs.append(out)
+                tk = out if fed is None else fed[g]
+            torch.cuda.synchronize()
+            return torch.stack(outs), st, rows
+
+        generate()
+        assert _launches(lambda: seen.update(gen=generate())) == 0
+        out, st = seen["gen"]
+        monkeypatch.setenv(SWITCH, "0")
+        same = steps()
+        assert torch.equal(same[0], out) and torch.equal(same[1], st)
+        monkeypatch.delenv(SWITCH)
+        assert _launches(lambda: seen.update(steps=steps(out))) == G
+        outs, st2, rows = seen["steps"]
+        assert close(st2, st)
+        for g in range(G):
+            assert rel_err_rows(rows[g].cpu().numpy(), same[2][g].cpu().numpy()) <= tol
+            if not how:                                          # both tokens are greedy choices from logits this close
+                for b in range(B):
+                    lost = rows[g][b].max() - rows[g][b, out[g, b]]
+                    assert lost <= 2 * tol * rows[g][b].abs().max(), (g, b)
+    model.close()
