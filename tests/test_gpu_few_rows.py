@@ -1,6 +1,7 @@
 """Decode steps of a handful of samples as one kernel (a bf16 model of 512 or 1024 channels, an fp32 one of 256) against the
 oracle and against the step kernels (the library's switch)."""
 import dataclasses
+import time
 
 import numpy as np
 import pytest
@@ -26,12 +27,25 @@ def orc_mod(oracle_mod):
 
 
 def _launches(fn):
-    """How often the kernels of few.hpp run in fn()."""
+    """How often the kernels of few.hpp run in fn().  The profiler drops kernels whose times, converted from the GPU's clock to the
+    host's, lie outside its window, and behind a long wait on the host they may be off by more than a few steps take: so the
+    window has a margin on both sides, whose own kernels show that none of fn's is lost."""
     from torch.profiler import profile, ProfilerActivity
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        fn()
+
+    def mark():
+        torch.zeros(64, device="cuda").erfinv_()
         torch.cuda.synchronize()
-    return sum("few_rows_kernel" in e.name for e in prof.events())
+
+    mark()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        time.sleep(0.05)
+        mark()
+        fn()
+        mark()
+        time.sleep(0.05)
+    names = [e.name for e in prof.events()]
+    assert sum("erfinv" in n for n in names) == 2, "the profiler has lost kernels"
+    return sum("few_rows_kernel" in n for n in names)
 
 
 def _steps(model, cfg, B, T, toks, garbage=None, **how):
@@ -73,10 +87,13 @@ def test_one_kernel_step_matches_oracle_and_step_kernels(srm, orc_mod, dtype, d,
     toks = srm_synth.make_prompts(cfg, batch=B, length=T)
     ref = orc_mod.Oracle(cfg, w, "f64").recurrent_forward(toks)
     print(f"one-kernel step {dtype} d={d} B={B} V={vocab} {variant}", flush=True)
-    one, st = _steps(model, cfg, B, T, toks)
+    runs = {}
+    assert _launches(lambda: runs.update(one=_steps(model, cfg, B, T, toks))) == T
+    one, st = runs["one"]
     again, st2 = _steps(model, cfg, B, T, toks, garbage=0)
     monkeypatch.setenv(SWITCH, "0")
-    many, st3 = _steps(model, cfg, B, T, toks)
+    assert _launches(lambda: runs.update(many=_steps(model, cfg, B, T, toks))) == 0
+    many, st3 = runs["many"]
     half = cfg.state_dtype == "fp16"
     tol = (4e-2 if half else 2e-2) if dtype == "bf16" else (1e-3 if half else 1e-4)
     for t in range(T):
@@ -114,8 +131,7 @@ def test_generation_in_one_kernel_matches_oracle(srm, orc_mod, B, half):
             tk.copy_(dp[:, P - 1])
             out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
             print(f"generation in one kernel B={B} half={half} T={temperature}", flush=True)
-            model.generate(B, P - 1, G, tk, st, out, workspace=ws, **kw)
-            torch.cuda.synchronize()
+            assert _launches(lambda: model.generate(B, P - 1, G, tk, st, out, workspace=ws, **kw)) == 1
             got = out.cpu().numpy().T
             ties = check_tokens(got, ref["tokens"], ref["margin"], np.abs(ref["logits"]).max(axis=2), rtol=1e-3 if half else 1e-4)
             assert (tk.cpu().numpy() == got[:, -1]).all()
@@ -123,6 +139,39 @@ def test_generation_in_one_kernel_matches_oracle(srm, orc_mod, B, half):
                 assert ties == 0
                 s_got = st.view(cfg.n_layers, B, cfg.d_model).permute(1, 0, 2).cpu().numpy()
                 assert np.abs(s_got - ref["state"]).max() <= 1e-4 * np.abs(ref["state"]).max()
+
+
+@pytest.mark.parametrize("temperature", [0.0, 0.8])
+@pytest.mark.parametrize("d,B,layers,half", [(512, 1, 5, False), (512, 3, 7, True), (1024, 2, 7, False), (1024, 4, 6, False), (1024, 4, 5, True)])
+def test_bf16_generation_in_one_kernel_matches_oracle(srm, orc_mod, d, B, layers, half, temperature):
+    """Tokens and state carried from step to step of one launch, the LayerNorm buffers across odd numbers of layers, sampling
+    between steps: every token is the oracle's choice from its logits on the same tokens, or within the bf16 bound of it, and
+    so is the state behind the last."""
+    cfg = srm_synth.tiny_config(vocab=333, d_model=d, n_layers=layers, n_heads=4, n_ctx=40, weight_dtype="bf16", seed=71,
+                                state_dtype="fp16" if half else "fp32")
+    w = srm_synth.make_weights(cfg, stress=True)
+    model, G = srm.Model(cfg, w), 12
+    start = (np.arange(B) * 29 + 5).astype(np.int32)
+    st, ws, tk = model.new_state(B), model.new_workspace(B), to_dev(start)
+    out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+    kw = {"temperature": temperature, "seed": 9} if temperature else {}
+    print(f"bf16 generation in one kernel d={d} B={B} layers={layers} half={half} T={temperature}", flush=True)
+    assert _launches(lambda: model.generate(B, 0, G, tk, st, out, workspace=ws, **kw)) == 1
+    got = out.cpu().numpy().T
+    assert (tk.cpu().numpy() == got[:, -1]).all() and (got >= 0).all() and (got < cfg.vocab).all()
+    fed = np.concatenate([start[:, None], got[:, :-1]], axis=1)
+    orc = orc_mod.Oracle(cfg, w, "f64")
+    logits = orc.recurrent_forward(fed)["logits"]
+    tol = 4e-2 if half else 2e-2                       # the repository's bounds of bf16 logits, of the largest of a row
+    for b in range(B):
+        for g in range(G):
+            row = logits[b, g].astype(np.float64)
+            score = row + temperature * np.array([orc_mod.gumbel(9, g, b, v) if temperature else 0.0 for v in range(cfg.vocab)])
+            assert score.max() - score[got[b, g]] <= 2 * tol * np.abs(row).max(), (b, g)
+    ref = orc.greedy(fed, 1)["state"]
+    s_got = st.float().view(layers, B, d).permute(1, 0, 2).cpu().numpy()
+    assert np.abs(s_got - ref).max() <= tol * np.abs(ref).max()
+    model.close()
 
 
 def test_sampled_and_nucleus_steps_choose_from_their_own_logits(srm, orc_mod):
@@ -179,8 +228,7 @@ def test_generation_by_one_work_group_alone(srm, dtype, d, B, monkeypatch):
             st, ws = model.new_state(B), model.new_workspace(B)
             tk, out = to_dev(np.arange(B, dtype=np.int32)), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
             print(f"generation by one work-group alone d={d} layers={layers} mode {mode}", flush=True)
-            model.generate(B, 2, G, tk, st, out, workspace=ws, temperature=0.7, seed=11)
-            torch.cuda.synchronize()
+            assert _launches(lambda: model.generate(B, 2, G, tk, st, out, workspace=ws, temperature=0.7, seed=11)) == 1
             got.append((st, tk, out))
         monkeypatch.delenv(SWITCH)
         assert torch.equal(got[0][1], got[0][2][-1]) and (got[0][2] >= 0).all()
@@ -512,38 +560,6 @@ def test_workspace_size_without_a_model(srm):
             assert srm.workspace_bytes_config(cfg, rows) == model.workspace_bytes(rows), (dtype, d, rows)
 
 
-def test_streams_that_are_no_objects_of_their_own(srm):
-    """Steps on the runtime's special stream handles (0: default, 1: legacy, 2: per thread) and on a stream that is destroyed
-    behind them: results as on any other stream, and no error left behind for the next call."""
-    import ctypes
-    import types
-    cfg = srm_synth.tiny_config(vocab=300, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
-    model = srm.Model(cfg, srm_synth.make_weights(cfg))
-    hip, B = ctypes.CDLL("libamdhip64.so"), 3
-    tok, ws = to_dev(np.arange(B, dtype=np.int32) * 5), model.new_workspace(B)
-
-    def step(handle):
-        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
-        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
-        torch.cuda.synchronize()
-        model.decode_step(B, 0, tok, st, out, logits=lg, workspace=ws, stream=types.SimpleNamespace(cuda_stream=handle))
-        assert hip.hipGetLastError() == 0
-        torch.cuda.synchronize()
-        return lg, out, st
-
-    want = step(torch.cuda.Stream().cuda_stream)
-    for handle in (0, 1, 2):
-        print(f"step on stream handle {handle}", flush=True)
-        assert _launches(lambda: step(handle)) == 1
-        assert all(torch.equal(a, b) for a, b in zip(step(handle), want))
-    for _ in range(6):                                   # (more than the library keeps events for at a time)
-        own = ctypes.c_void_p()
-        assert hip.hipStreamCreate(ctypes.byref(own)) == 0
-        assert all(torch.equal(a, b) for a, b in zip(step(own.value), want))
-        assert hip.hipStreamDestroy(own) == 0
-    assert all(torch.equal(a, b) for a, b in zip(step(0), want))
-
-
 @pytest.mark.parametrize("d,B,bare", [(512, 3, False), (1024, 2, False), (1024, 4, True)])
 def test_calls_that_keep_the_step_kernels_agree_with_steps_as_one_kernel(srm, d, B, bare, monkeypatch):
     """A ragged step with all samples at one position, a captured step, and generation with a nucleus or without projections
@@ -639,3 +655,35 @@ def test_calls_that_keep_the_step_kernels_agree_with_steps_as_one_kernel(srm, d,
                     lost = rows[g][b].max() - rows[g][b, out[g, b]]
                     assert lost <= 2 * tol * rows[g][b].abs().max(), (g, b)
     model.close()
+
+
+def test_streams_that_are_no_objects_of_their_own(srm):
+    """Steps on the runtime's special stream handles (0: default, 1: legacy, 2: per thread) and on a stream that is destroyed
+    behind them: results as on any other stream, and no error left behind for the next call."""
+    import ctypes
+    import types
+    cfg = srm_synth.tiny_config(vocab=300, d_model=512, n_layers=6, n_heads=4, n_ctx=16, weight_dtype="bf16", seed=3)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    hip, B = ctypes.CDLL("libamdhip64.so"), 3
+    tok, ws = to_dev(np.arange(B, dtype=np.int32) * 5), model.new_workspace(B)
+
+    def step(handle):
+        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        model.decode_step(B, 0, tok, st, out, logits=lg, workspace=ws, stream=types.SimpleNamespace(cuda_stream=handle))
+        assert hip.hipGetLastError() == 0
+        torch.cuda.synchronize()
+        return lg, out, st
+
+    want = step(torch.cuda.Stream().cuda_stream)
+    for handle in (0, 1, 2):
+        print(f"step on stream handle {handle}", flush=True)
+        assert _launches(lambda: step(handle)) == 1
+        assert all(torch.equal(a, b) for a, b in zip(step(handle), want))
+    for _ in range(6):                                   # (more than the library keeps events for at a time)
+        own = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(own)) == 0
+        assert all(torch.equal(a, b) for a, b in zip(step(own.value), want))
+        assert hip.hipStreamDestroy(own) == 0
+    assert all(torch.equal(a, b) for a, b in zip(step(0), want))
