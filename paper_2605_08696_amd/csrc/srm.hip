@@ -186,6 +186,9 @@ static int model_geometry(const char *who, const srm_config *cfg, srm_model *m)
 // 138 | 98, without projections 124 | 54, 4: 131 | 69; fp32, d = 256, 4 layers, 4096 tokens, steps of one launch: 1 row 80 | 32, 8:
 // 84 | 52.  (Eight rows of d = 512 with projections: 141 | 143.)  Eight columns instead of four: d = 1024, 1 row 231 | 213, 4 rows
 // 333 | 323; fp32, 1 row 31 | 29, 8 rows 52 | 55.
+// The bounds are where the measuring ended, not where the step kernels win (but for those eight rows): the widths are those of
+// the benchmark's models, of which the kernel's code exists; it could be made for other multiples of 512 (bf16) and 256 (fp32) up to
+// 2048 and 1024, for eight bf16 rows without projections and for 16 fp32 rows.
 static int few_max_rows(const srm_model *m)
 {
     if (m->dm != m->d || m->ff != 4 * m->d || m->L > kFewMaxLayers || m->V < 4) return 0;
@@ -1465,11 +1468,16 @@ extern "C" int srm_decode_step_ragged(srm_model *m, int64_t B, int32_t *d_pos, i
 
 // ------------------------------------------------------------------ few samples: steps as one kernel (few.hpp)
 // Whether G steps of B samples run as one kernel: the shapes of few_max_rows, a stream that is not being captured and may use
-// every CU, and at least six layers or layers times steps.  That is faster from there on at every size (us, step kernels | one kernel, d = 1024 with
+// every CU, and at least six layers or layers times steps.  That is faster at every size (us, step kernels | one kernel, d = 1024 with
 // projections, 4 rows | 1 row: 6 layers 137 | 118, 134 | 79; 8: 168 | 146, 163 | 98; 24: 521 | 417, 507 | 281; d = 512: 6 layers
-// 117 | 77, 114 | 59; fp32, d = 256: 8 rows 84 | 52, 1 row 80 | 32).  Shallower models have little to gain and keep a step
-// whose sums are, bit for bit, those of the ragged step and of larger batches.
+// 117 | 77, 114 | 59; fp32, d = 256: 8 rows 84 | 52, 1 row 80 | 32), and would be so at every depth (1 layer | 3 layers, 1 row: d = 1024
+// 41 | 33, 76 | 51, d = 512 34 | 26, 63 | 39, fp32 30 | 20, 61 | 34; 4 rows of d = 1024 42 | 41, 77 | 71, 8 fp32 rows 30 | 28, 60 | 52).  The
+// bound on the layers is there for the results, not for speed: steps of shallower models keep, bit for bit, the sums of the ragged
+// step and of larger batches, which their users may compare.
 // SRM_ONE_KERNEL_STEP=0 in the environment keeps the step kernels.
+// Beside other work of the process it holds its gain (a stream of single steps next to one of other calls, large model, us per step and
+// calls per second of the other stream, step kernels | one kernel: prefills of 256 x 128 11060 and 91 | 350 and 60; decode steps of
+// 16384 samples 3340 and 148 | 320 and 93; of 3001 with top-p 1230 and 466 | 270 and 278).
 static bool few_off()
 {
     const char *e = getenv("SRM_ONE_KERNEL_STEP");
