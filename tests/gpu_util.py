@@ -1,4 +1,6 @@
 """Shared helpers of the GPU parity tests (no method arithmetic here)."""
+import time
+
 import numpy as np
 import torch
 
@@ -24,6 +26,28 @@ def check_tokens(got, ref_tokens, ref_margin, ref_logits_absmax, rtol=1e-4):
     tie = ref_margin < rtol * ref_logits_absmax
     assert not (bad & ~tie).any(), f"{int((bad & ~tie).sum())} tokens differ from the oracle"
     return int((bad & tie).sum())
+
+
+def kernel_launches(name, fn):
+    """How often kernels whose names hold `name` run in fn().  The profiler drops kernels whose times, converted from the GPU's clock
+    to the host's, lie outside its window, and behind a long wait on the host they may be off by more than a few steps take: so
+    the window has a margin on both sides, whose own kernels show that none of fn's is lost."""
+    from torch.profiler import profile, ProfilerActivity
+
+    def mark():
+        torch.zeros(64, device="cuda").erfinv_()
+        torch.cuda.synchronize()
+
+    mark()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        time.sleep(0.05)
+        mark()
+        fn()
+        mark()
+        time.sleep(0.05)
+    names = [e.name for e in prof.events()]
+    assert sum("erfinv" in n for n in names) == 2, "the profiler has lost kernels"
+    return sum(name in n for n in names)
 
 
 class Generator:

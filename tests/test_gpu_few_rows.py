@@ -1,14 +1,13 @@
 """Decode steps of a handful of samples as one kernel (a bf16 model of 512 or 1024 channels, an fp32 one of 256) against the
 oracle and against the step kernels (the library's switch)."""
 import dataclasses
-import time
 
 import numpy as np
 import pytest
 import torch
 
 import srm_synth
-from gpu_util import to_dev, rel_err_rows, check_tokens
+from gpu_util import to_dev, rel_err_rows, check_tokens, kernel_launches
 
 pytestmark = pytest.mark.gpu
 SWITCH = "SRM_ONE_KERNEL_STEP"
@@ -27,25 +26,8 @@ def orc_mod(oracle_mod):
 
 
 def _launches(fn):
-    """How often the kernels of few.hpp run in fn().  The profiler drops kernels whose times, converted from the GPU's clock to the
-    host's, lie outside its window, and behind a long wait on the host they may be off by more than a few steps take: so the
-    window has a margin on both sides, whose own kernels show that none of fn's is lost."""
-    from torch.profiler import profile, ProfilerActivity
-
-    def mark():
-        torch.zeros(64, device="cuda").erfinv_()
-        torch.cuda.synchronize()
-
-    mark()
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        time.sleep(0.05)
-        mark()
-        fn()
-        mark()
-        time.sleep(0.05)
-    names = [e.name for e in prof.events()]
-    assert sum("erfinv" in n for n in names) == 2, "the profiler has lost kernels"
-    return sum("few_rows_kernel" in n for n in names)
+    """How often the kernels of few.hpp run in fn()."""
+    return kernel_launches("few_rows_kernel", fn)
 
 
 def _steps(model, cfg, B, T, toks, garbage=None, **how):

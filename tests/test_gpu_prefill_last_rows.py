@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import srm_synth
-from gpu_util import to_dev, rel_err_rows
+from gpu_util import to_dev, rel_err_rows, kernel_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -63,6 +63,46 @@ def test_prefill_of_the_last_rows_matches_oracle(srm, oracle_mod, name, lens):
     for other in got[1:]:
         for x, y in zip(got[0], other):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("lens", [[3, 530, 4], [513], [512], [258] * 3, [2, 560], [1, 580]], ids=str)
+@pytest.mark.parametrize("name,d", [("tiny", 256), ("bare", 256), ("combined", 256), ("narrow mlp", 512)])
+def test_prefill_of_the_last_rows_bf16(srm, oracle_mod, name, d, lens):
+    """The same in bf16, whose rows are half as wide in memory as the residual stream's: packed and uniform prompts against the
+    oracle within the repository's bound for bf16 models, and whether the last rows are gathered."""
+    cfg = srm_synth.tiny_config(vocab=301, d_model=d, n_layers=2, n_heads=4, n_ctx=600, weight_dtype="bf16", seed=31)
+    cfg = dataclasses.replace(cfg, **MODELS[name])
+    N, rows = len(lens), sum(lens)
+    w = srm_synth.make_weights(cfg)
+    model, orc = srm.Model(cfg, w), oracle_mod.Oracle(cfg, w, "f64")
+    prompts = np.random.default_rng(rows).integers(0, cfg.vocab, (N, max(lens))).astype(np.int32)
+    toks = to_dev(np.concatenate([prompts[i, :n] for i, n in enumerate(lens)]))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n, ff = model.workspace_bytes(rows), cfg.mlp_expansion * d
+    gathered = (rows - N) * d >= 1 << 17 and (ff + model.sd) * 2 + 4 * d + 512 <= min(lens) * ff * 2       # enough to save, and room
+    for how in ["packed"] + ["uniform"] * (len(set(lens)) == 1):
+        buf = torch.randint(0, 256, (n + 4096,), dtype=torch.uint8, device="cuda")
+        guard = buf[n:].clone()
+        st, tk = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+        lg = torch.empty((N, cfg.vocab), dtype=torch.float32, device="cuda")
+        print(f"bf16 prefill of last rows {name} d={d} lens={lens} {how}", flush=True)
+        keep = []
+
+        def prefill():
+            if how == "uniform":
+                model.prefill(toks.view(N, -1), 1, st, tk, logits=lg, workspace=buf[:n])
+            else:
+                keep.append(model.prefill_ragged(toks, off, st, tk, logits=lg, workspace=buf[:n]))
+
+        assert kernel_launches("last_rows_kernel", prefill) == gathered
+        assert torch.equal(buf[n:], guard)
+        sv = st.view(cfg.n_layers, N, -1)
+        for b, m in enumerate(lens):
+            ref = orc.greedy(prompts[b:b + 1, :m], 1, want_logits=True)
+            assert rel_err_rows(lg[b:b + 1].cpu().numpy(), ref["logits"][:, 0]) <= 2e-2
+            assert np.abs(sv[:, b].cpu().numpy() - ref["state"][0]).max() <= 2e-2 * np.abs(ref["state"][0]).max()
+        assert torch.equal(tk.long(), lg.argmax(dim=1))
+    model.close()
 
 
 @pytest.mark.parametrize("N,P", [(1, 64), (1, 65), (1, 257), (2, 320), (1, 512), (1, 513), (1, 580), (20, 64), (40, 321)])
