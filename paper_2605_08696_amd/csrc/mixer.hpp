@@ -522,12 +522,14 @@ struct PrefillSeqs {
     const int32_t *slot;             // ragged: destination sample, or null
     int64_t nslots;
 };
-// FEW (at most a block per CU): grid = (tiles of positions, head tiles, B) and the rows of a 512-position prefix in one request.
+// FEW (at most a block per CU): grid = (tiles of positions, head tiles, B); WIDE: and the rows of a 512-position prefix in one request.
 // Otherwise grid = (head tiles, B, tiles of positions), the last positions first: with eight tiles of positions in x each of
 // them went to an XCD of its own, the one with the longest prefixes ended last, and every XCD read all channels (6 x 500
 // positions, 768 blocks: 13.4 -> 10.3 us).  The wider request costs registers that many blocks need (14.5 us there; 64 prompts
-// x 128, 16 layers: 3127 -> 3279 us) and is worth 0.7 us per layer to few (one sequence of 509: 802 -> 793 us).
-template <typename TAct, bool PREFILL, bool FEW>
+// x 128, 16 layers: 3127 -> 3279 us) and is worth 0.7 us per layer to few (one sequence of 509: 802 -> 793 us), but costs those
+// that have no prefix beyond 256 rows 0.5 us (sequence form of 1 x 200, 16 layers: 643 -> 651 us, 4 x 256 1017 -> 1044; one prompt
+// of 200 642 -> 652).
+template <typename TAct, bool PREFILL, bool FEW, bool WIDE>
 __global__ void __launch_bounds__(256)
 mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
                       const float *__restrict__ alpha, const float *__restrict__ beta,
@@ -568,7 +570,7 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
     }
     // rows g, g + 16, ... of the prefix (j0 is a multiple of 64), PRE of them in one request (half of them where that is the whole
     // prefix), the first under the table
-    constexpr int PRE = FEW && sizeof(TAct) == 2 ? 32 : 16;
+    constexpr int PRE = WIDE ? 32 : 16;
     raw_t u[PRE];
     float a[PRE];
     auto request = [&](int i0) {

@@ -1777,12 +1777,15 @@ static int mixer_parallel(const srm_model *m, const LayerDev &y, const Workspace
 {
     const unsigned tiles = (unsigned)cdiv(P, kParSquare), heads = (unsigned)(m->Hs * cdiv(m->dm / m->Hs, 64));
     const size_t lds = (size_t)parallel_table_floats(P) * sizeof(float);
-#define PARALLEL_LAUNCH(FEW, ...)                                                                               \
-    hipLaunchKernelGGL((mixer_parallel_kernel<T, PREFILL, FEW>), dim3(__VA_ARGS__), dim3(256), lds, st,           \
+#define PARALLEL_LAUNCH(FEW, WIDE, ...)                                                                         \
+    hipLaunchKernelGGL((mixer_parallel_kernel<T, PREFILL, FEW, WIDE>), dim3(__VA_ARGS__), dim3(256), lds, st,     \
                        static_cast<const T *>(w.u), static_cast<T *>(w.mx), y.alpha, y.beta, y.lam, m->cfg.n_ctx, m->Hs, \
                        m->hrow, m->dm, P, ps)
-    if ((int64_t)tiles * heads * nseq <= device_cus()) PARALLEL_LAUNCH(true, tiles, heads, (unsigned)nseq);
-    else PARALLEL_LAUNCH(false, heads, (unsigned)nseq, tiles);
+    const bool few = (int64_t)tiles * heads * nseq <= device_cus();
+    constexpr bool wide = sizeof(T) == 2;            // (fp32 rows are twice as wide, and never asked for by more than 16)
+    if (few && P > 256 + kParSquare) PARALLEL_LAUNCH(true, wide, tiles, heads, (unsigned)nseq);
+    else if (few) PARALLEL_LAUNCH(true, false, tiles, heads, (unsigned)nseq);
+    else PARALLEL_LAUNCH(false, false, heads, (unsigned)nseq, tiles);
 #undef PARALLEL_LAUNCH
     HIP_TRY(hipGetLastError());
     return SRM_OK;

@@ -105,7 +105,7 @@ def test_prefill_of_the_last_rows_bf16(srm, oracle_mod, name, d, lens):
     model.close()
 
 
-@pytest.mark.parametrize("N,P", [(1, 64), (1, 65), (1, 257), (2, 320), (1, 512), (1, 513), (1, 580), (20, 64), (40, 321)])
+@pytest.mark.parametrize("N,P", [(1, 64), (1, 65), (1, 257), (2, 320), (1, 321), (1, 512), (1, 513), (1, 580), (20, 64), (40, 321)])
 def test_block_scan_bf16_of_few_and_many_blocks(srm, oracle_mod, N, P):
     """The block form of the mixer on both sides of one block per CU (20 x 64 positions: 80 blocks here, 40 x 321: 960) and at the
     ends of its requests of 256 and 512 rows: prefill and sequence form of a bf16 model against the oracle (the repository's
