@@ -28,10 +28,11 @@ def check_tokens(got, ref_tokens, ref_margin, ref_logits_absmax, rtol=1e-4):
     return int((bad & tie).sum())
 
 
-def kernel_launches(name, fn):
-    """How often kernels whose names hold `name` run in fn().  The profiler drops kernels whose times, converted from the GPU's clock
-    to the host's, lie outside its window, and behind a long wait on the host they may be off by more than a few steps take: so
-    the window has a margin on both sides, whose own kernels show that none of fn's is lost."""
+def kernel_events(name, fn):
+    """The profiler's events of kernels whose names hold `name`, of fn().  The profiler drops kernels whose times,
+    converted from the GPU's clock to the host's, lie outside its window, and behind a long wait on the host they may be
+    off by more than a few steps take: so the window has a margin on both sides, whose own kernels show that none of fn's
+    is lost."""
     from torch.profiler import profile, ProfilerActivity
 
     def mark():
@@ -45,9 +46,13 @@ def kernel_launches(name, fn):
         fn()
         mark()
         time.sleep(0.05)
-    names = [e.name for e in prof.events()]
-    assert sum("erfinv" in n for n in names) == 2, "the profiler has lost kernels"
-    return sum(name in n for n in names)
+    assert sum("erfinv" in e.name for e in prof.events()) == 2, "the profiler has lost kernels"
+    return [e for e in prof.events() if name in e.name]
+
+
+def kernel_launches(name, fn):
+    """How often kernels whose names hold `name` run in fn()."""
+    return len(kernel_events(name, fn))
 
 
 class Generator:

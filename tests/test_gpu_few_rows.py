@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import srm_synth
-from gpu_util import to_dev, rel_err_rows, check_tokens, kernel_launches
+from gpu_util import to_dev, rel_err_rows, check_tokens, kernel_events, kernel_launches
 
 pytestmark = pytest.mark.gpu
 SWITCH = "SRM_ONE_KERNEL_STEP"
@@ -357,7 +357,6 @@ def test_calls_on_several_streams_and_threads(srm):
 def test_streams_run_side_by_side_and_more_than_fit_in_turn(srm):
     """Generate calls of two models on seven streams, more than have a CU for each work-group at once: two of the first ones
     run at the same time, and all results are those of the same calls alone."""
-    from torch.profiler import profile, ProfilerActivity
     models = []
     for dtype, d in (("fp32", 256), ("bf16", 1024)):
         cfg = srm_synth.tiny_config(vocab=700, d_model=d, n_layers=6, n_heads=4, n_ctx=64, weight_dtype=dtype, seed=29)
@@ -380,12 +379,11 @@ def test_streams_run_side_by_side_and_more_than_fit_in_turn(srm):
     streams = [torch.cuda.Stream() for _ in range(jobs)]
     torch.cuda.synchronize()
     print("one-kernel generation on seven streams", flush=True)
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        got = [run(again[k], streams[k]) for k in range(jobs)]
-        torch.cuda.synchronize()
+    got = []
+    events = kernel_events("few_rows_kernel", lambda: got.extend(run(again[k], streams[k]) for k in range(jobs)))
     for a, b in zip(alone, got):
         assert all(torch.equal(x, y) for x, y in zip(a, b))
-    spans = sorted((e.time_range.start, e.time_range.end) for e in prof.events() if "few_rows_kernel" in e.name)
+    spans = sorted((e.time_range.start, e.time_range.end) for e in events)
     assert len(spans) == jobs
     assert any(spans[i + 1][0] < spans[i][1] for i in range(jobs - 1)), spans
 
