@@ -90,6 +90,15 @@
  *                        behind it) and chooses the same tokens unless two scores
  *                        tie within it, but need not have the same bits; with =0
  *                        it has (see srm_generate for its own one-kernel path).
+ *                        Decode steps of 5 to 3072 samples (uniform and ragged,
+ *                        and those of the generate calls) of a bf16 model of
+ *                        d_model 512 with projections, mlp_expansion 4, one
+ *                        matrix per head and at least six layers run their
+ *                        layers as one kernel in the same way: it takes the
+ *                        whole device, one at a time; its wait for the others
+ *                        is some 30 ms, one work-group alone takes 5 to 90 ms
+ *                        per step.  Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
+ *                        SRM_LN_ON_LOAD set, whose kernels it replaces.
  */
 #ifndef SRM_H
 #define SRM_H
@@ -228,7 +237,7 @@ size_t srm_workspace_bytes_config(const srm_config *cfg, int64_t rows);
  * place (Eq. 2 / Eq. 3), writes the greedy next token d_tok_out[B].
  * Optional outputs (NULL to skip): d_logits[B][vocab] fp32, d_hidden[B][d]
  * fp32 (residual stream after the last block, before the final LayerNorm).
- * d_tok_out may alias d_tok_in.  A step of a few samples that runs as one kernel
+ * d_tok_out may alias d_tok_in.  A step that runs as one kernel or whose layers do
  * (SRM_ONE_KERNEL_STEP above) waits within bounds: should a wait ever give up,
  * the tokens are -1 and the state is undefined, behind a return of SRM_OK.
  * Errors: SRM_EINVAL (null pointer, B <= 0,
@@ -271,7 +280,8 @@ int srm_decode_step_sampled(srm_model *m, int64_t B, int32_t pos, const int32_t 
  * captured into a HIP graph on the first call and replayed G - 1 times; the
  * graph is cached in the model and reused while B and the four device pointers
  * stay the same.  On the legacy default stream (NULL), which cannot be
- * captured, the steps are launched one by one instead.  temperature = 0 is
+ * captured, and where the layers of a step run as one kernel (see
+ * SRM_ONE_KERNEL_STEP above), the steps are launched one by one instead.  temperature = 0 is
  * greedy; temperature > 0 samples as srm_decode_step_sampled does.  Results are
  * identical to G srm_decode_step(_sampled) calls, except where this call runs
  * all G steps in one launch or those calls run as one kernel each (see

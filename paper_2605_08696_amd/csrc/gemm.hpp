@@ -1088,6 +1088,7 @@ struct FinalizeRagged {
     int32_t *pos_set;         // prefill: pos_set[destination] = length of the sequence
     int32_t *zero_counter;    // set to 0 (the row list of the nucleus pass that follows)
     int32_t eos_plus1;        // decode with advance: eos token + 1 (0: none); a row that emits it goes idle (position -1)
+    const unsigned *dead;     // decode: not zero where the kernel of the layers has given up -> tokens -1
 };
 
 // Reduce the per-tile partials [nparts][rows] of each row to one token; writes `rep`
@@ -1135,7 +1136,9 @@ argmax_finalize_kernel(const float *__restrict__ part_val, const int32_t *__rest
         for (int k = 1; k < NQ; ++k)
             if (arg_better(sv[k][r], si[k][r], bv, bi)) { bv = sv[k][r]; bi = si[k][r]; }
         if (bi < 0 || bi >= vocab) bi = 0;
-        if (rg.pos_rows) {
+        if (rg.dead && *rg.dead) {
+            bi = -1;
+        } else if (rg.pos_rows) {
             const int p = rg.pos_rows[row0 + row];
             const bool active = p >= 0 && p < rg.n_ctx;
             if (!active) bi = -1;

@@ -1297,7 +1297,10 @@ struct DecodeArgs {
     float top_p;
     int eos_plus1 = 0;
     int *advance_ctr = nullptr;     // step counters of srm_generate, advanced by the first kernel of the step
+    size_t ws_bytes = 0;
 };
+static bool stack_ok(const srm_model *m, int64_t rows, size_t ws_bytes, hipStream_t st);
+static int stack_layers(srm_model *m, const DecodeArgs &a, const Workspace &w, int64_t b0, int64_t nb, hipStream_t st, const unsigned **dead);
 
 template <typename T>
 static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb, void *ws, hipStream_t st)
@@ -1309,9 +1312,12 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
         return static_cast<void *>(static_cast<unsigned char *>(layer_state(m, a.state, l, a.B)) +
                                    (size_t)b0 * dm * m->ssize);
     };
-    SRM_TRY((layernorm<T, true>(m, nullptr, 0, a.tok_in + b0, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a, nb,
-                                st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr,
-                                prefetch_of(m, -1, 0))));
+    const bool stacked = sizeof(T) == 2 && stack_ok(m, nb, a.ws_bytes, st);
+    const unsigned *dead = nullptr;
+    if (stacked) SRM_TRY(stack_layers(m, a, w, b0, nb, st, &dead));
+    else SRM_TRY((layernorm<T, true>(m, nullptr, 0, a.tok_in + b0, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a, nb,
+                                     st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr,
+                                     prefetch_of(m, -1, 0))));
     auto mix = [&](int l) {
         if (!pos_rows) return state_update<T>(m, l, a.pos, nb, w.u, slab(l), w.mx, st, a.pos_dev);
         const LayerDev &y = m->layers[l];
@@ -1338,10 +1344,10 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
     const bool ln1f = !lnf && !tm && in_projection_normalises(m, call_rows);
     // ... and the LM head the last one, where it is the fp32 GEMV (bf16: one launch of many, for 64 rows of a tile)
     const bool head_norm = lnf && sizeof(T) == 4;
-    for (int l = 0; l < m->L; ++l)
+    for (int l = 0; l < m->L && !stacked; ++l)
         SRM_TRY((block<T>(m, l, w, nb, call_rows, st, mix, !head_norm, fuse ? slab(l) : nullptr, where, slab(l), lnf, tm,
                           ln1f)));
-    if (a.hidden)
+    if (a.hidden && !stacked)
         HIP_TRY(hipMemcpyAsync(a.hidden + (size_t)b0 * d, w.x, (size_t)nb * d * 4, hipMemcpyDeviceToDevice, st));
     const Sampling sm{a.temperature, a.seed, a.pos, a.pos_dev, pos_rows, a.top_p, (uint32_t)b0, a.eos_plus1};
     const bool topp = a.temperature > 0.0f && a.top_p < 1.0f;
@@ -1353,6 +1359,7 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
         rg.eos_plus1 = a.eos_plus1;
     }
     if (topp) rg.zero_counter = w.slow;
+    rg.dead = dead;
     float *lg = a.logits ? a.logits + (size_t)b0 * m->V : nullptr;
     SRM_TRY((head_argmax<T>(m, w, w.a, nb, call_rows, lg, a.tok_out, b0, 1, st, a.ts, sm, rg,
                             head_norm ? LnArgs{w.x, m->lnf_g, m->lnf_b, m->cfg.ln_eps} : LnArgs())));
@@ -1379,8 +1386,9 @@ static int64_t decode_rows_per_pass(const srm_model *m, int64_t B, size_t worksp
     return lo < std::min<int64_t>(B, 256) ? 0 : lo;
 }
 
-static int decode_batch(srm_model *m, const DecodeArgs &a, void *ws, size_t workspace_bytes, hipStream_t st)
+static int decode_batch(srm_model *m, DecodeArgs a, void *ws, size_t workspace_bytes, hipStream_t st)
 {
+    a.ws_bytes = workspace_bytes;
     const int64_t rpp = decode_rows_per_pass(m, a.B, workspace_bytes);
     if (rpp <= 0) return fail(SRM_ENOMEM, "workspace %zu bytes holds fewer than %lld rows", workspace_bytes,
                               (long long)std::min<int64_t>(a.B, 256));
@@ -1485,11 +1493,8 @@ static bool few_off()
 }
 // The default stream by its null name: hipExtStreamGetCUMask reads through the other one, hipStreamLegacy, as through a pointer.
 static hipStream_t few_stream(hipStream_t st) { return st == hipStreamLegacy ? nullptr : st; }
-static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
+static bool one_kernel_stream(hipStream_t st)
 {
-    if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
-    if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
-    st = few_stream(st);
     // (where a question is refused the step kernels do the work, and its error must not be taken for one of theirs)
     auto refused = [](hipError_t e) { return e != hipSuccess && ((void)hipGetLastError(), true); };
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -1500,6 +1505,12 @@ static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_by
     int cus = 0;
     for (const uint32_t bits : mask) cus += __builtin_popcount(bits);
     return cus >= device_cus();
+}
+static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
+{
+    if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
+    if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
+    return one_kernel_stream(few_stream(st));
 }
 
 // ------------------------------------------------------------------ generate, few samples: one persistent kernel
@@ -1628,8 +1639,8 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
     SRM_TRY(generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p, d_logits,
                           d_pos, eos_plus1, false));
     if (G == 1) return SRM_OK;
-    // The legacy default stream cannot be captured: loop eagerly there.
-    if (st == nullptr) {
+    // The legacy default stream cannot be captured: loop eagerly there; and so the steps whose layers are one kernel.
+    if (st == nullptr || (decode_rows_per_pass(m, B, ws_bytes) == B && stack_ok(m, B, ws_bytes, st))) {
         for (int g = 1; g < G; ++g)
             SRM_TRY(generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p,
                                   d_logits, d_pos, eos_plus1, true));
@@ -2463,4 +2474,119 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     void *args[] = {&a};
     return few_launch(m->device, kern, nb, (kFewGather + nwc) * 64, lds, args, st);
+}
+
+// ------------------------------------------------------------------ some dozens of samples and more: all layers as one kernel
+#include "stack.hpp"
+
+// How the rows of a step are cut: groups of at least 16.  Up to 64 rows of a group all its members share one tile of rows, 16
+// columns each; above, they are 16 pairs that share 32 columns and take the tiles of up to 64 rows in turn.
+struct StackPlan {
+    int per, cw, rb, tiles;  // rows of a group; columns of a member; 16-row blocks of a tile; tiles of a group
+};
+static StackPlan stack_plan(int64_t rows)
+{
+    StackPlan s;
+    s.per = (int)std::max<int64_t>(16, cdiv(rows, kStackGroups));
+    s.cw = s.per <= 64 ? 16 : 32;
+    s.tiles = s.per <= 64 ? 1 : 2 * (int)cdiv(s.per, 128);
+    s.rb = (int)cdiv(cdiv(s.per, s.tiles), 16);
+    return s;
+}
+// Its memory in the workspace: x and a where they always are, the rest from the array of u on, over what only the step kernels
+// or the head behind it use.
+struct StackMem {
+    unsigned char *words;
+    float2 *stats;
+    bf16 *m, *g;
+    size_t bytes;            // from u on
+};
+static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackPlan &s, int64_t rows)
+{
+    StackMem r;
+    unsigned char *p = static_cast<unsigned char *>(w.u);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        unsigned char *q = p + off;
+        off += align_up(bytes, 256);
+        return q;
+    };
+    const size_t used = (size_t)cdiv(rows, s.per) * s.tiles * s.rb * 16;
+    r.words = take(kStackWordBytes);
+    r.stats = reinterpret_cast<float2 *>(take((size_t)rows * (m->d / s.cw) * sizeof(float2)));
+    r.m = reinterpret_cast<bf16 *>(take(used * m->d * 2));
+    r.g = reinterpret_cast<bf16 *>(take(used * m->ff * 2));
+    r.bytes = off;
+    return r;
+}
+// Which steps.  Measured per decode step with logits (us, step kernels | layers as one kernel), d = 512, 8 layers, 32000 tokens: 5
+// rows 144 | 118, 9: 173 | 119, 37: 184 | 122, 128: 193 | 133, 129: 207 | 152, 300: 243 | 176, 512: 256 | 207, 513: 294 | 217,
+// 1024: 317 | 253, 1025: 374 | 327, 2048: 470 | 418, 3000: 639 | 599, 4096: 745 | 754.  Up to four rows few.hpp's steps are
+// shorter (98).  A width of 512 is what the kernel's registers and LDS were laid out for; at 1024 every XCD would read 21 MB of
+// weights per layer, 22 us at the 0.95 TB/s an XCD gets, where a layer of 37 rows takes 25.  Six layers: as in few_ok, for the
+// results of shallower models.
+constexpr int64_t kStackMinRows = 5, kStackMaxRows = 3072;
+static_assert(kStackMaxRows <= (int64_t)kStackGroups * kStackMaxPer, "their positions are kept in LDS");
+// Polls of the arrival, some 30 ms: about what one work-group alone takes (ms per step: 37 rows 5, 300: 22, 1024: 33, 3000: 87).
+constexpr unsigned stack_arrive_polls = 1u << 15;
+static bool stack_ok(const srm_model *m, int64_t rows, size_t ws_bytes, hipStream_t st)
+{
+    if (!m->few_layers || m->wsize != 2 || m->d != 512 || m->noproj || m->L < 6 || rows < kStackMinRows || rows > kStackMaxRows) return false;
+    if (device_cus() < kStackBlocks || few_off()) return false;
+    if (getenv("SRM_TOKEN_MIX") || getenv("SRM_FUSE_MIXER") || getenv("SRM_LN_ON_LOAD")) return false;
+    // (the last 256 bytes: srm_generate's counters)
+    const Workspace w = carve(m, reinterpret_cast<void *>(256), rows);
+    const size_t at = reinterpret_cast<size_t>(w.u) - 256;
+    if (at + stack_carve(m, w, stack_plan(rows), rows).bytes + 256 > ws_bytes) return false;
+    return one_kernel_stream(few_stream(st));
+}
+
+template <int CW, int RB, bool MULTI>
+static const void *stack_kernel_of()
+{
+    return reinterpret_cast<const void *>(stack_kernel<512, CW, RB, MULTI>);
+}
+static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, int64_t b0, int64_t nb, hipStream_t st, const unsigned **dead)
+{
+    const StackPlan s = stack_plan(nb);
+    const StackMem mem = stack_carve(m, w, s, nb);
+    st = few_stream(st);
+    const void *kern = s.cw == 16 ? (s.rb == 1 ? stack_kernel_of<16, 1, false>() : s.rb == 2 ? stack_kernel_of<16, 2, false>()
+                                     : s.rb == 3 ? stack_kernel_of<16, 3, false>() : stack_kernel_of<16, 4, false>())
+                       : s.tiles == 2 ? (s.rb == 3 ? stack_kernel_of<32, 3, false>() : stack_kernel_of<32, 4, false>())
+                                      : (s.rb == 3 ? stack_kernel_of<32, 3, true>() : stack_kernel_of<32, 4, true>());
+    StackArgs a{};
+    a.layers = m->few_layers;
+    a.lnf_g = m->lnf_g; a.lnf_b = m->lnf_b;
+    a.L = m->L; a.dh = m->dm / m->Hs; a.hrow = m->hrow; a.n_ctx = m->cfg.n_ctx;
+    a.eps = m->cfg.ln_eps;
+    a.rows = (int)nb; a.per = s.per; a.tiles = s.tiles;
+    a.pos = d.pos; a.pos_dev = d.pos_dev; a.pos_rows = d.pos_rows ? d.pos_rows + b0 : nullptr;
+    a.state = static_cast<unsigned char *>(d.state) + (size_t)b0 * m->dm * m->ssize;
+    a.layer_bytes = (size_t)d.B * m->dm * m->ssize;
+    a.state_half = m->shalf ? 1 : 0;
+    a.x = w.x; a.stats = mem.stats; a.m = mem.m; a.g = mem.g;
+    a.a = static_cast<bf16 *>(w.a);
+    a.hidden = d.hidden ? d.hidden + (size_t)b0 * m->d : nullptr;
+    a.here = reinterpret_cast<few_word *>(mem.words);
+    a.count = reinterpret_cast<unsigned *>(mem.words + kStackBlocks * 8);
+    a.dead = reinterpret_cast<unsigned *>(mem.words + kStackBlocks * 8 + kStackGroups * 128);
+    a.max_polls = 1u << 21;                          // a second or two
+    a.arrive_polls = stack_arrive_polls;
+    int withdrawn = -1;                              // the arrival of one of the last work-groups
+    const char *sw = getenv("SRM_ONE_KERNEL_STEP"), *polls = getenv("SRM_ONE_KERNEL_POLLS");
+    if (sw && sw[0] == '2') withdrawn = kStackBlocks * 8 / 16 - 1;
+    if (sw && sw[0] == '3') a.arrive_polls = 0;
+    if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
+    *dead = a.dead;
+    auto begin = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(nb, 4)), dim3(256), 0, st, d.tok_in + b0, static_cast<const bf16 *>(m->embed),
+                           m->V, w.x, mem.stats, (int)nb, reinterpret_cast<u32x4_t *>(mem.words), withdrawn, b0 == 0 ? d.advance_ctr : nullptr);
+        return hipGetLastError();
+    };
+    HIP_TRY(s.cw == 16 ? begin(stack_begin_kernel<512, 16>) : begin(stack_begin_kernel<512, 32>));
+    const int lds = stack_lds_bytes(512, s.cw, s.rb);
+    HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    void *args[] = {&a};
+    return few_launch(m->device, kern, kStackBlocks, kStackThreads, lds, args, st);
 }

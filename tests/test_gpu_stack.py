@@ -1,0 +1,191 @@
+"""Decode steps of some dozens of samples and more whose layers run as one kernel (a bf16 model of 512 channels), against the
+oracle and against the step kernels (the library's switch)."""
+import numpy as np
+import pytest
+import torch
+
+import srm_synth
+from gpu_util import to_dev, rel_err_rows, kernel_launches
+
+pytestmark = pytest.mark.gpu
+SWITCH = "SRM_ONE_KERNEL_STEP"
+
+
+@pytest.fixture(scope="module")
+def srm():
+    import paper_2605_08696_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+@pytest.fixture(scope="module")
+def orc_mod(oracle_mod):
+    return oracle_mod
+
+
+def _launches(fn):
+    return kernel_launches("stack_kernel", fn)
+
+
+def _config(**kw):
+    args = dict(vocab=333, d_model=512, n_layers=6, n_heads=4, n_ctx=12, weight_dtype="bf16", seed=53)
+    args.update(kw)
+    return srm_synth.tiny_config(**args)
+
+
+def _steps(model, cfg, toks, positions=None, garbage=None, **how):
+    """Steps on given tokens [B][T] in a workspace full of `garbage`, with a guard behind it; positions: of each sample."""
+    B, T = toks.shape
+    n = model.workspace_bytes(B)
+    buf = torch.empty(n + 4096, dtype=torch.uint8, device="cuda")
+    buf.random_(0, 256) if garbage is None else buf.fill_(garbage)
+    guard = buf[n:].clone()
+    st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+    lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+    hd = torch.empty((B, cfg.d_model), dtype=torch.float32, device="cuda")
+    tc = to_dev(toks).t().contiguous()
+    res = []
+    for t in range(T):
+        if positions is None:
+            model.decode_step(B, t, tc[t], st, out, logits=lg, hidden=hd, workspace=buf[:n], **how)
+        else:
+            pos = to_dev((positions + t).astype(np.int32))
+            model.decode_step_ragged(B, pos, tc[t], st, out, advance=False, logits=lg, workspace=buf[:n], **how)
+        res.append((lg.clone(), hd.clone(), out.clone()))
+    torch.cuda.synchronize()
+    assert torch.equal(buf[n:], guard)
+    return res, st
+
+
+# rows at the borders of the plan: whole and part groups of 16, a group's tile of one to four blocks of 16, two members on 32
+# columns with tiles of three and four blocks, several tiles to a member
+ROWS = [9, 16, 33, 128, 129, 300, 512, 513, 1024, 1025, 2048, 2100]
+
+
+@pytest.mark.parametrize("B", ROWS)
+@pytest.mark.parametrize("variant", [{}, dict(state_dtype="fp16", head_layout="column")])
+def test_layers_in_one_kernel_match_oracle_and_step_kernels(srm, orc_mod, B, variant, monkeypatch):
+    cfg = _config(**variant)
+    w = srm_synth.make_weights(cfg, stress=True)
+    model, T = srm.Model(cfg, w), 2
+    toks = srm_synth.make_prompts(cfg, batch=B, length=T)
+    some = sorted({0, 15, 16, B // 8, B // 2, B - 17, B - 1} & set(range(B)))
+    ref = orc_mod.Oracle(cfg, w, "f64").recurrent_forward(toks[some])
+    print(f"layers in one kernel B={B} {variant}", flush=True)
+    runs = {}
+    assert _launches(lambda: runs.update(one=_steps(model, cfg, toks))) == T
+    one, st = runs["one"]
+    again, st2 = _steps(model, cfg, toks, garbage=0)
+    monkeypatch.setenv(SWITCH, "0")
+    assert _launches(lambda: runs.update(many=_steps(model, cfg, toks))) == 0
+    many, st3 = runs["many"]
+    tol = 4e-2 if cfg.state_dtype == "fp16" else 2e-2                  # the repository's bounds of bf16 logits
+    for t in range(T):
+        assert all(torch.equal(a, b) for a, b in zip(one[t], again[t]))         # a fixed order of sums: the same bits
+        assert rel_err_rows(one[t][0][some].cpu().numpy(), ref["logits"][:, t]) <= tol
+        assert rel_err_rows(one[t][1][some].cpu().numpy(), ref["hidden"][:, t]) <= tol
+        assert rel_err_rows(one[t][0].cpu().numpy(), many[t][0].cpu().numpy()) <= tol
+        assert torch.equal(one[t][2].long(), one[t][0].argmax(dim=1))
+    assert torch.equal(st, st2)
+    assert (st.float() - st3.float()).abs().max() <= tol * st3.float().abs().max()
+    model.close()
+
+
+@pytest.mark.parametrize("B", [9, 130, 513, 1100])
+def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
+    """A launch whose work-groups have not all started is done by one of them: forced from the host, by an arrival that is
+    withdrawn from the start, then by a wait of one look, which ends either way."""
+    cfg = _config(vocab=200)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    toks = srm_synth.make_prompts(cfg, batch=B, length=2)
+    want, st = _steps(model, cfg, toks)
+    for mode in ("2", "3"):
+        monkeypatch.setenv(SWITCH, mode)
+        print(f"one work-group alone B={B} mode {mode}", flush=True)
+        got, st2 = _steps(model, cfg, toks)
+        monkeypatch.delenv(SWITCH)
+        for a, b in zip(want, got):
+            assert all(torch.equal(x, y) for x, y in zip(a, b))
+        assert torch.equal(st, st2)
+    model.close()
+
+
+def test_ragged_step_in_one_kernel(srm, monkeypatch):
+    """One position per sample, some outside the context: those keep their state and get -1; at one position for all the same
+    bits as the plain step; otherwise the step kernels' results within the bf16 bound."""
+    cfg = _config()
+    model, B, T = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 200, 2
+    toks = srm_synth.make_prompts(cfg, batch=B, length=T)
+    plain, st = _steps(model, cfg, toks)
+    same, st2 = _steps(model, cfg, toks, positions=np.zeros(B))
+    for a, b in zip(plain, same):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[2], b[2])
+    assert torch.equal(st, st2)
+    positions = np.arange(B) % (cfg.n_ctx + 3) - 2
+    print("ragged step in one kernel", flush=True)
+    runs = {}
+    assert _launches(lambda: runs.update(one=_steps(model, cfg, toks, positions=positions))) == T
+    monkeypatch.setenv(SWITCH, "0")
+    many, st4 = _steps(model, cfg, toks, positions=positions)
+    one, st3 = runs["one"]
+    for t in range(T):
+        idle = torch.from_numpy(((positions + t < 0) | (positions + t >= cfg.n_ctx))).cuda()
+        assert (one[t][2][idle] == -1).all() and (one[t][2][~idle] >= 0).all()
+        assert rel_err_rows(one[t][0][~idle].cpu().numpy(), many[t][0][~idle].cpu().numpy()) <= 2e-2
+    assert (st3 - st4).abs().max() <= 2e-2 * st4.abs().max()
+    model.close()
+
+
+def test_generation_and_slices(srm):
+    """srm_generate gives the tokens and states of single steps, and a workspace of fewer rows takes the step in slices."""
+    cfg = _config(vocab=400, n_ctx=40)
+    model, B, G = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 600, 5
+    start = to_dev((np.arange(B) * 7 % cfg.vocab).astype(np.int32))
+    ws, small = model.new_workspace(B), model.new_workspace(256)
+    results = []
+    for stream in (None, torch.cuda.Stream()):
+        st, tk, out = model.new_state(B), start.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        print(f"generation of {B} samples", flush=True)
+        assert _launches(lambda: model.generate(B, 3, G, tk, st, out, workspace=ws, temperature=0.7, seed=9, stream=stream)) == G
+        results.append((out, st))
+    st, tk = model.new_state(B), start.clone()
+    steps = []
+    for g in range(G):
+        model.decode_step(B, 3 + g, tk, st, tk, workspace=ws, temperature=0.7, seed=9)
+        steps.append(tk.clone())
+    results.append((torch.stack(steps), st))
+    for out, st in results[1:]:
+        assert torch.equal(out, results[0][0]) and torch.equal(st, results[0][1])
+    st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+    lg, lg2 = (torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda") for _ in range(2))
+    model.decode_step(B, 3, start, model.new_state(B), out, logits=lg, workspace=ws)
+    assert _launches(lambda: model.decode_step(B, 3, start, st, out, logits=lg2, workspace=small)) == 3
+    assert rel_err_rows(lg2.cpu().numpy(), lg.cpu().numpy()) <= 2e-2
+    model.close()
+
+
+def test_a_wait_that_gives_up_leaves_marked_tokens(srm, monkeypatch):
+    """The bound of the waits behind the arrival, set so short from the host that some give up at once: every wavefront ends,
+    the tokens are -1 (behind a nucleus pass too), and the next call is right."""
+    cfg = _config(vocab=1001, n_ctx=16)
+    model, B = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 150
+    ws, lg = model.new_workspace(B), torch.zeros((B, cfg.vocab), dtype=torch.float32, device="cuda")
+    tok = to_dev(np.arange(B, dtype=np.int32))
+
+    def step(**how):
+        st, out = model.new_state(B), torch.full((B,), 5, dtype=torch.int32, device="cuda")
+        model.decode_step(B, 1, tok, st, out, logits=lg, workspace=ws, **how)
+        torch.cuda.synchronize()
+        return out, st, lg.clone()
+
+    ways = (dict(), dict(temperature=0.7, top_p=0.6, seed=3))
+    want = [step(**how) for how in ways]
+    monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+    for how in ways:
+        print(f"a wait that gives up {how}", flush=True)
+        assert (step(**how)[0] == -1).all()
+    monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+    for how, w in zip(ways, want):
+        assert all(torch.equal(a, b) for a, b in zip(step(**how), w))
+    model.close()
