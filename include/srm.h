@@ -58,11 +58,13 @@
  *                        fp32 one of 256, mlp_expansion 4, one matrix per head,
  *                        at least six layers, and so do all steps of
  *                        srm_generate for those with projections and at least
- *                        six layers times steps (SRM_MEGAKERNEL unset); not on a
+ *                        six layers times steps (up to 32 samples of that fp32
+ *                        model; SRM_MEGAKERNEL unset); not on a
  *                        stream that is being captured or whose CU mask leaves
  *                        out some CUs.  Of such
  *                        kernels two of d_model 1024 or four others run at a time
- *                        per process and device; further ones wait for those
+ *                        per process and device (an fp32 one takes all of it
+ *                        where one stream alone launches them: same bits); further ones wait for those
  *                        before them, whatever their streams (an event for each
  *                        is kept until the process ends).  (Many streams of 3 or 4
  *                        samples each at d_model 1024 get more done with =0.)
@@ -95,7 +97,8 @@
  *                        d_model 512 with projections, mlp_expansion 4, one
  *                        matrix per head and at least six layers run their
  *                        layers as one kernel in the same way: it takes the
- *                        whole device, one at a time; its wait for the others
+ *                        whole device, or half or a quarter of it where streams
+ *                        launch such steps in turn; its wait for the others
  *                        is some 30 ms, one work-group alone takes 5 to 90 ms
  *                        per step.  Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
  *                        SRM_LN_ON_LOAD set, whose kernels it replaces.

@@ -53,10 +53,11 @@ struct FewArgs {
     int V, L, dh, hrow, n_ctx;                       // dh: channels per head
     float eps;
     int B, pos0, G;
+    int Bs, row0;                                    // in groups (XCD): rows of the call, the group's first; else B and 0
     const int32_t *tok_in;                           // [B] tokens at pos0
     int32_t *tok_out;                                // [B] the last tokens
-    int32_t *store;                                  // [G][B] or null
-    void *state;                                     // [L][B][D]
+    int32_t *store;                                  // [G][Bs] or null
+    void *state;                                     // [L][Bs][D]
     int state_half;
     float *logits, *hidden;                          // [B][V], [B][D] of the last step, or null
     float temp;                                      // > 0: Gumbel-max sampling
@@ -66,9 +67,12 @@ struct FewArgs {
     unsigned max_polls, arrive_polls;                // bounds of the waits
 };
 
-__device__ __forceinline__ void few_put(few_word *p, unsigned payload, unsigned tag)
+// near: who polls for the word shares this XCD's L2, and it need not be written through
+__device__ __forceinline__ void few_put(few_word *p, unsigned payload, unsigned tag, bool near = false)
 {
-    __hip_atomic_store(p, ((few_word)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const few_word w = ((few_word)tag << 32) | payload;
+    if (near) __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Polls the words at(0) .. at(N - 1) of every lane until all of the wavefront carry `tag`; false: given up.
 template <int N, typename AT>
@@ -128,6 +132,60 @@ __device__ __forceinline__ bool few_arrived(few_word *words, int stride, int lan
     for (int i = 0; i < N; ++i) few_set(words + (i * 64 + lane) * stride, kFewWithdrawn, v[i]);
     look();
     return __all(here);
+}
+
+// An arrival of `blocks` work-groups, at most NB, whose words say on which XCD one runs (kFewXcd0 plus its number): the work-groups
+// in order of their XCD, an eighth of them to a group.  `me`: this work-group's word.
+constexpr int kFewXcd0 = 4;
+__device__ __forceinline__ int few_xcd() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15; }          // HW_REG_XCC_ID
+struct FewPlace {
+    bool all;                // have arrived
+    int at;                  // this work-group's number in that order
+    bool near;               // its group lies on one XCD
+};
+constexpr int kFewGroups = 8;
+template <int NB>
+__device__ __forceinline__ FewPlace few_place(few_word *words, int blocks, int blk, int me, int lane, unsigned max_polls)
+{
+    static_assert(NB % 64 == 0, "as many words for each lane");
+    constexpr int N = NB / 64;
+    const int per = blocks / kFewGroups;
+    few_word v[N];
+    bool here = false, withdrawn = false;
+    auto look = [&] {
+        here = true;
+        withdrawn = false;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            here = here && v[i] >= kFewXcd0;
+            withdrawn = withdrawn || v[i] == kFewWithdrawn;
+        }
+        here = __all(here);
+        withdrawn = __any(withdrawn);
+    };
+    for (unsigned polls = 0;; ++polls) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            v[i] = i * 64 + lane < blocks ? __hip_atomic_load(words + i * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull >> 33;
+        look();
+        if (here || withdrawn || polls >= max_polls) break;
+    }
+    if (!here && !withdrawn) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (i * 64 + lane < blocks) few_set(words + i * 64 + lane, kFewWithdrawn, v[i]);
+        look();
+    }
+    int below = 0, same = 0, at = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        below += __popcll(__ballot((int)v[i] < me));
+        same += __popcll(__ballot((int)v[i] == me));
+        at += __popcll(__ballot((int)v[i] == me && i * 64 + lane < blk));
+    }
+    at += below;
+    const int first = at / per * per;
+    return FewPlace{here, at, below <= first && first + per <= below + same};
 }
 
 // A load through a pointer that came from LDS: global memory, which the compiler cannot know (a flat load would count as an
@@ -329,7 +387,7 @@ __device__ __forceinline__ void few_scores(const FewArgs &p, const u32x4_t (&w)[
             if (row >= p.B) continue;
             if (p.logits && last) p.logits[(size_t)row * p.V + c] = logit[rb];
             const float score = p.temp > 0.0f
-                ? logit[rb] + p.temp * srm_gumbel(srm_rowkey(p.seed, (uint32_t)pos, (uint32_t)row), (uint32_t)c) : logit[rb];
+                ? logit[rb] + p.temp * srm_gumbel(srm_rowkey(p.seed, (uint32_t)pos, (uint32_t)(row + p.row0)), (uint32_t)c) : logit[rb];
             if (arg_better(score, c, bv[rb], bi[rb])) { bv[rb] = score; bi[rb] = c; }
         }
     }
@@ -346,6 +404,20 @@ __device__ __forceinline__ void few_best(const uint2 *red, int r, int lane, floa
         if (arg_better(__uint_as_float(t.x), (int)t.y, bv, bi)) { bv = __uint_as_float(t.x); bi = (int)t.y; }
     }
     best_of_lanes<16>(bv, bi);
+}
+
+// What group c of `rows` rows each sees of a call
+__device__ __forceinline__ void few_group(FewArgs &p, int c, int rows, int D)
+{
+    const int r0 = c * rows;
+    p.row0 = r0;
+    p.B = min(rows, p.Bs - r0);
+    p.tok_in += r0;
+    p.tok_out += r0;
+    if (p.store) p.store += r0;
+    p.state = static_cast<unsigned char *>(p.state) + (size_t)r0 * D * (p.state_half ? 2 : 4);
+    if (p.logits) p.logits += (size_t)r0 * p.V;
+    if (p.hidden) p.hidden += (size_t)r0 * D;
 }
 
 constexpr int few_lds_bytes(int ts, int D, int NWC, int MB)
@@ -427,7 +499,7 @@ __device__ __forceinline__ void few_alone(const FewArgs &p, const FewLayer *lay,
                     quarters(std::integral_constant<int, KD>{}, y.w_in, n, act_a, SD, v);
                     each(n, [&](int r, int rb, int col) {
                         const int head = col / p.dh;
-                        const size_t at = ((size_t)l * B + r) * D + col;
+                        const size_t at = ((size_t)l * p.Bs + r) * D + col;
                         const float s0 = p.state_half ? (float)static_cast<const f16 *>(p.state)[at] : static_cast<const float *>(p.state)[at];
                         float sn;
                         const TW m = few_mix<TW>(v[rb], few_load(y.b_in + col), s0, few_load(y.alpha + (size_t)head * p.n_ctx + pos),
@@ -456,7 +528,7 @@ __device__ __forceinline__ void few_alone(const FewArgs &p, const FewLayer *lay,
 #pragma unroll
                     for (int i = 0; i < XL / 2; ++i) {
                         const int e = few_elem(i, of), h = e / p.dh;
-                        const size_t at = ((size_t)l * B + r) * D + e;
+                        const size_t at = ((size_t)l * p.Bs + r) * D + e;
                         float2 s = few_state2(p.state, at, p.state_half);
                         few_mix2<TW>(s, x + 2 * i, u + 2 * i, few_load(y.alpha + (size_t)h * p.n_ctx + pos),
                                      few_load(y.beta + (size_t)h * p.n_ctx + pos), few_load(y.lam + h), h < p.hrow, p.state_half);
@@ -517,7 +589,7 @@ __device__ __forceinline__ void few_alone(const FewArgs &p, const FewLayer *lay,
             if (t < 0 || t >= p.V) t = 0;            // no ordered value: a valid token all the same
             if (lane == 0) {
                 tokb[r] = t;
-                if (p.store) p.store[(size_t)g * B + r] = t;
+                if (p.store) p.store[(size_t)g * p.Bs + r] = t;
                 if (last) p.tok_out[r] = t;
             }
         }
@@ -526,10 +598,11 @@ __device__ __forceinline__ void few_alone(const FewArgs &p, const FewLayer *lay,
 }
 
 // MB: rows that the arithmetic is unrolled for (B <= MB); the rows between travel along as finite filler.
-template <typename TW, int D, int NWC, int MB, bool PROJ>
+// XCD: MB rows to a group of work-groups, a group for each XCD (see few_group_rows in srm.hip), the groups on their own.
+template <typename TW, int D, int NWC, int MB, bool PROJ, bool XCD = false>
 __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewArgs p)
 {
-    constexpr int NG = kFewGather, NT = NG * 64, NWT = NG + NWC, NB = D / NWC, FF = 4 * D, TS = (int)sizeof(TW);
+    constexpr int NG = kFewGather, NT = NG * 64, NWT = NG + NWC, NB = D / NWC, NALL = XCD ? kFewGroups * NB : NB, FF = 4 * D, TS = (int)sizeof(TW);
     // 1 KB vectors of four columns: of a slice (a quarter) of d inputs; of d inputs, or a slice of FF inputs
     constexpr int KD = D * TS / 1024, K4 = 4 * KD, RB = (MB + 3) / 4;
     constexpr int GC = TS == 2 ? 2 * NWC : 4 * NWC;                    // words of g per row and work-group
@@ -547,27 +620,44 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     float *const lnp = reinterpret_cast<float *>(red + NWT * RB * 64);                 // [2][4][D] LayerNorm parameters of two layers
     FewLayer *const lay = reinterpret_cast<FewLayer *>(lnp + 8 * D);                   // [L] (a read of memory per phase is a trip of 1 us)
     int *const tokb = reinterpret_cast<int *>(lay + kFewMaxLayers);                    // [MB]
-    int *const dead = tokb + MB;                                                       // [2]
+    int *const dead = tokb + MB;                                                       // [2], then the place in the groups [2]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int blk = blockIdx.x, B = p.B;
+    int blk = blockIdx.x, B = p.B;
+    bool near = false;
     const bool gatherer = wave < NG;
     const int cw = wave - NG;                        // number of a computing wavefront
     const TW *const embed = static_cast<const TW *>(p.embed);
 
-    few_word *const here = p.pw;                     // (arrivals: words of the winners, which nobody writes before all have arrived)
+    // (arrivals: words of the winners, which nobody writes before all have arrived; groups do not wait for each other, and have
+    // theirs behind the winners)
+    few_word *const here = XCD ? p.pw + (size_t)kFewGroups * MB * NB * 2 : p.pw;
+    int me = 0;
     if (tid == 0) {
         few_word found;
-        few_set(here + blk * (MB * 2), kFewHere, found);
+        few_set(here + blk * (XCD ? 1 : MB * 2), XCD ? kFewXcd0 + few_xcd() : kFewHere, found);
+        me = (int)found;
     }
     for (int i = tid; i < (MB * D * 4 + 2 * MB * SD + MB * SF) / 16; i += blockDim.x)
         reinterpret_cast<u32x4_t *>(few_lds)[i] = u32x4_t{0, 0, 0, 0};
     for (int i = tid; i < p.L * (int)(sizeof(FewLayer) / 8); i += blockDim.x)
         reinterpret_cast<few_word *>(lay)[i] = reinterpret_cast<const few_word *>(p.layers)[i];
-    if (tid < MB) tokb[tid] = tid < B ? min(max(p.tok_in[tid], 0), p.V - 1) : 0;
+    auto tokens = [&] {
+        if (tid < MB) tokb[tid] = tid < B ? min(max(p.tok_in[tid], 0), p.V - 1) : 0;
+    };
+    if constexpr (!XCD) tokens();
     if (wave == 0) {
-        const bool all = few_arrived<NB>(here, MB * 2, lane, p.arrive_polls);
-        if (lane == 0) *dead = !all;
+        if constexpr (XCD) {
+            const FewPlace at = few_place<NALL>(here, NALL, blk, __builtin_amdgcn_readfirstlane(me), lane, p.arrive_polls);
+            if (lane == 0) {
+                *dead = !at.all;
+                dead[2] = at.at;
+                dead[3] = at.near;
+            }
+        } else {
+            const bool all = few_arrived<NB>(here, MB * 2, lane, p.arrive_polls);
+            if (lane == 0) *dead = !all;
+        }
     }
     // LDS only: loads and stores of global memory stay in flight across it
     auto barrier = [] {
@@ -578,10 +668,38 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     barrier();
     if (__builtin_expect(*dead, 0)) {                // nothing but scratch has been written
         if (tid == 0)
-            dead[1] = __hip_atomic_fetch_add(p.flag + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == NB - 1;
+            dead[1] = __hip_atomic_fetch_add(p.flag + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == NALL - 1;
         __syncthreads();
-        if (dead[1]) few_alone<TW, D, NWT, MB, PROJ>(p, lay, xs, act_a, act_m, act_g, red, lnp, tokb, tid, lane, wave);
+        if (!dead[1]) return;
+        if constexpr (XCD) {
+#pragma unroll 1
+            for (int c = 0; c < kFewGroups && c * MB < p.Bs; ++c) {
+                FewArgs q = p;
+                few_group(q, c, MB, D);
+                B = q.B;
+                if (tid < MB) tokb[tid] = tid < B ? min(max(q.tok_in[tid], 0), q.V - 1) : 0;
+                __syncthreads();
+                few_alone<TW, D, NWT, MB, PROJ>(q, lay, xs, act_a, act_m, act_g, red, lnp, tokb, tid, lane, wave);
+                __syncthreads();
+            }
+        } else {
+            few_alone<TW, D, NWT, MB, PROJ>(p, lay, xs, act_a, act_m, act_g, red, lnp, tokb, tid, lane, wave);
+        }
         return;
+    }
+    if constexpr (XCD) {
+        const int at = __builtin_amdgcn_readfirstlane(dead[2]), c = at / NB;
+        near = __builtin_amdgcn_readfirstlane(dead[3]);
+        blk = at % NB;
+        if (c * MB >= p.Bs) return;                  // (the whole group: there are no rows for it)
+        few_group(p, c, MB, D);
+        p.xw += (size_t)c * MB * D;
+        p.mw += (size_t)c * MB * D;
+        p.gw += (size_t)c * MB * GC * NB;
+        p.pw += (size_t)c * MB * NB * 2;
+        B = p.B;
+        tokens();
+        barrier();
     }
     unsigned tag = 0;                                // of the latest exchange, the same in every wavefront
     // (indexes pass through opaque copies where they are used: what is derived from them would otherwise be formed once, in
@@ -659,7 +777,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
             barrier();                               // a is there
             barrier();                               // the words of g are staged
             ++tag;
-            if (tid < MB * GC) few_put(p.gw + blk * (MB * GC) + tid, stage[tid], tag);
+            if (tid < MB * GC) few_put(p.gw + blk * (MB * GC) + tid, stage[tid], tag, near);
             gather_g();
             barrier();                               // g is there
         };
@@ -710,7 +828,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                         la[i] = few_load(lam + h);
 #pragma unroll
                         for (int q = 0; q < RPW; ++q) {
-                            s[q][i] = few_state2(p.state, ((size_t)l * B + min(wave + q * NG, B - 1)) * D + few_elem(i, of), p.state_half);
+                            s[q][i] = few_state2(p.state, ((size_t)l * p.Bs + min(wave + q * NG, B - 1)) * D + few_elem(i, of), p.state_half);
                         }
                     }
                     barrier();
@@ -737,7 +855,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
 #pragma unroll
                         for (int i = 0; i < XL / 2; ++i) {
                             if (i != blk) continue;                    // (there are at least XL / 2 work-groups)
-                            few_keep2(p.state, ((size_t)l * B + wave + q * NG) * D + few_elem(i, of), p.state_half, s[q][i]);
+                            few_keep2(p.state, ((size_t)l * p.Bs + wave + q * NG) * D + few_elem(i, of), p.state_half, s[q][i]);
                         }
                     }
                 }
@@ -764,7 +882,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                 float bv;
                 int bi;
                 few_best<NWT, RB>(red, r, lane, bv, bi);
-                if (lane < 2) few_put(p.pw + (blk * MB + r) * 2 + lane, lane ? (unsigned)bi : __float_as_uint(bv), tag);
+                if (lane < 2) few_put(p.pw + (blk * MB + r) * 2 + lane, lane ? (unsigned)bi : __float_as_uint(bv), tag, near);
             }
 #pragma unroll
             for (int q = 0; q < RPW; ++q) {
@@ -789,7 +907,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                 if (lane == 0) {
                     tokb[r] = bi;
                     if (blk == 0 && r < B) {
-                        if (p.store) p.store[(size_t)g * B + r] = bi;
+                        if (p.store) p.store[(size_t)g * p.Bs + r] = bi;
                         if (g == p.G - 1) p.tok_out[r] = bi;
                     }
                 }
@@ -854,7 +972,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
             Epi e{};
             e.b_down = few_load(y.b_down + col);
             if constexpr (PROJ) {
-                const size_t at = ((size_t)l * B + r) * D + col;
+                const size_t at = ((size_t)l * p.Bs + r) * D + col;
                 const int head = col / p.dh;
                 e.b_in = few_load(y.b_in + col);
                 e.b_out = few_load(y.b_out + col);
@@ -909,9 +1027,9 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                         if constexpr (TS == 2) bits = __builtin_bit_cast(unsigned short, m);
                         else bits = __float_as_uint(m);
                         if (ln < MB * NWC) {
-                            few_put(p.mw + blk * (MB * NWC) + ln, bits, tag);
+                            few_put(p.mw + blk * (MB * NWC) + ln, bits, tag, near);
                             if (r < B) {
-                                const size_t sat = ((size_t)l * B + r) * D + col;
+                                const size_t sat = ((size_t)l * p.Bs + r) * D + col;
                                 if (p.state_half) static_cast<f16 *>(p.state)[sat] = (f16)sn;
                                 else static_cast<float *>(p.state)[sat] = sn;
                             }
@@ -925,7 +1043,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                     if (lead) {
                         const int ln = opaque(lane);
                         x_own += total(min(ln, MB * NWC - 1)) + e.b_out;
-                        if (ln < MB * NWC) few_put(p.xw + blk * (MB * NWC) + ln, __float_as_uint(x_own), tag);
+                        if (ln < MB * NWC) few_put(p.xw + blk * (MB * NWC) + ln, __float_as_uint(x_own), tag, near);
                     }
                 }
                 barrier();                           // x is there
@@ -965,7 +1083,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
                 if (lead) {
                     const int ln = opaque(lane);
                     x_own += total(min(ln, MB * NWC - 1)) + e.b_down;
-                    if (ln < MB * NWC) few_put(p.xw + blk * (MB * NWC) + ln, __float_as_uint(x_own), tag);
+                    if (ln < MB * NWC) few_put(p.xw + blk * (MB * NWC) + ln, __float_as_uint(x_own), tag, near);
                 }
                 e = en;
                 b_up = b_up_n;

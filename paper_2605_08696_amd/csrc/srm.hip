@@ -184,7 +184,7 @@ static int model_geometry(const char *who, const srm_config *cfg, srm_model *m)
 // of a work-group.  Measured per step (us, step kernels | one kernel): d = 1024, 16 layers, 32000 tokens: 1 row 349 | 196, 2:
 // 355 | 234, 4: 360 | 288; without projections 299 | 148, 302 | 170, 305 | 202; d = 512, 8 layers: 1 row 136 | 73, 2: 137 | 82, 4:
 // 138 | 98, without projections 124 | 54, 4: 131 | 69; fp32, d = 256, 4 layers, 4096 tokens, steps of one launch: 1 row 80 | 32, 8:
-// 84 | 52.  (Eight rows of d = 512 with projections: 141 | 143.)  Eight columns instead of four: d = 1024, 1 row 231 | 213, 4 rows
+// 84 | 52 (few_group_rows has shorter ones).  (Eight rows of d = 512 with projections: 141 | 143.)  Eight columns instead of four: d = 1024, 1 row 231 | 213, 4 rows
 // 333 | 323; fp32, 1 row 31 | 29, 8 rows 52 | 55.
 // The bounds are where the measuring ended, not where the step kernels win (but for those eight rows): the widths are those of
 // the benchmark's models, of which the kernel's code exists; it could be made for other multiples of 512 (bf16) and 256 (fp32) up to
@@ -1401,7 +1401,8 @@ static int decode_batch(srm_model *m, DecodeArgs a, void *ws, size_t workspace_b
 
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st);
 static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
-                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st);
+                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, size_t ws_bytes, hipStream_t st);
+static int few_group_rows(const srm_model *m, int64_t B, int64_t G, size_t ws_bytes);
 
 static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t pos, const int32_t *d_tok_in,
                               void *d_state, int32_t *d_tok_out, float *d_logits, float *d_hidden,
@@ -1419,7 +1420,7 @@ static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t 
     hipStream_t st = as_stream(hip_stream);
     if (few_ok(m, B, 1, workspace_bytes, st)) {
         SRM_TRY(few_run(m, B, pos, 1, d_tok_in, d_tok_out, nullptr, d_state, temperature, seed, d_logits, d_hidden,
-                        d_workspace, st));
+                        d_workspace, workspace_bytes, st));
         if (!(temperature > 0.0f && top_p < 1.0f)) return SRM_OK;
         return nucleus(d_logits, B, m->V, Sampling{temperature, seed, pos, nullptr, nullptr, top_p}, d_tok_out, nullptr, nullptr,
                        0, nullptr, static_cast<int *>(d_workspace), st);
@@ -1508,8 +1509,8 @@ static bool one_kernel_stream(hipStream_t st)
 }
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {
-    if (!m->few_layers || B > few_max_rows(m) || (G > 1 && m->noproj) || G * m->L < 6) return false;
-    if (few_off() || srm_workspace_bytes(m, B) > workspace_bytes) return false;
+    if (!m->few_layers || (G > 1 && m->noproj) || G * m->L < 6 || few_off()) return false;
+    if (B > few_max_rows(m) ? !few_group_rows(m, B, G, workspace_bytes) : srm_workspace_bytes(m, B) > workspace_bytes) return false;
     return one_kernel_stream(few_stream(st));
 }
 
@@ -1625,7 +1626,8 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
     SRM_TRY(check_device(m));
     hipStream_t st = as_stream(hip_stream);
     if (!topp && !d_pos && !eos_plus1 && !getenv("SRM_MEGAKERNEL") && few_ok(m, B, G, ws_bytes, st))
-        return few_run(m, B, pos0, G, d_tok, d_tok, d_tokens_out, d_state, temperature, seed, nullptr, nullptr, d_workspace, st);
+        return few_run(m, B, pos0, G, d_tok, d_tok, d_tokens_out, d_state, temperature, seed, nullptr, nullptr, d_workspace,
+                       ws_bytes, st);
     if (!topp && !d_pos && !eos_plus1 && row_bytes(m, B) <= ws_bytes) {
         const int nblk = mega_blocks(m, B);
         if (nblk > 0)
@@ -2378,15 +2380,28 @@ static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr
 // 76 | 76, this 73 | 41 | 24 | 28, step kernels 134 | 77 | 42 | 41; 4 rows 97 | 99 | 99 | 99, 97 | 51 | 31 | 36, 137 | 75 | 43 | 42;
 // d = 1024, 1 row 198 | 200 | 200 | 199, 198 | 123 | 124 | 128, 348 | 209 | 127 | 164; 4 rows 289 | 291 | 290 | 291, 288 | 168 | 171 |
 // 177, 354 | 213 | 130 | 131: there the step kernels are the better ones from four streams on.
+struct FewShare { hipEvent_t ev; hipStream_t st; unsigned long long used; };         // st: only a preference
+struct FewDevice { FewShare share[kFewShares]; hipEvent_t own[kFewShares]; };        // events are kept until the process ends
+static std::mutex few_lock;
+static FewDevice few_devices[kFewDevices];
+static unsigned long long few_launches;
+// How many other streams have been launching kernels of this kind in turn with this one: in the latest few launches.
+static int few_others(int device, hipStream_t st)
+{
+    const std::lock_guard<std::mutex> hold(few_lock);
+    const FewShare *const s = few_devices[device].share;
+    int n = 0;
+    for (int i = 0; i < kFewShares; ++i) {
+        bool counts = s[i].used && s[i].st != st && few_launches - s[i].used < kFewShares;
+        for (int k = 0; k < i; ++k) counts = counts && s[k].st != s[i].st;
+        n += counts;
+    }
+    return n;
+}
 static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st)
 {
-    struct Share { hipEvent_t ev; hipStream_t st; unsigned long long used; };        // st: only a preference
-    struct Device { Share share[kFewShares]; hipEvent_t own[kFewShares]; };          // events are kept until the process ends
-    static std::mutex lock;
-    static Device devices[kFewDevices];
-    static unsigned long long launches;
-    const std::lock_guard<std::mutex> hold(lock);
-    Device &d = devices[device];
+    const std::lock_guard<std::mutex> hold(few_lock);
+    FewDevice &d = few_devices[device];
     const int need = (int)cdiv(blocks, kFewShare), all = std::min(device_cus() / kFewShare, kFewShares) / need * need;
     if (need < 1 || all < need) return fail(SRM_EINVAL, "few_launch: %d work-groups", blocks);
     int at = 0;
@@ -2410,8 +2425,8 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
         waited = before;
     }
     HIP_TRY(hipExtLaunchKernel(kern, dim3((unsigned)blocks), dim3((unsigned)threads), args, (size_t)lds, st, nullptr, ev, 0));
-    ++launches;
-    for (int k = at; k < at + need; ++k) d.share[k] = Share{ev, st, launches};
+    ++few_launches;
+    for (int k = at; k < at + need; ++k) d.share[k] = FewShare{ev, st, few_launches};
     return SRM_OK;
 }
 
@@ -2421,6 +2436,17 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
 // arrival itself costs 0.3 to 0.7 us per launch (195.5 | 196.2; d = 512 74.8 | 75.1).
 constexpr unsigned few_arrive_polls = 1u << 13;
 
+constexpr int kFewGroupColumns = 8, kFewGroupBlocks = kFewGroups * 256 / kFewGroupColumns, kFewCuLds = 84 * 1024;
+static size_t few_group_words_bytes(const srm_model *m, int64_t B, int mb)
+{
+    return (align_up((size_t)B, mb) * ((size_t)2 * m->d + m->ff) + (size_t)kFewGroupBlocks * (2 * mb + 1)) * sizeof(few_word) + 256;
+}
+static const void *few_group_kernel(int mb)
+{
+    return mb == 1 ? reinterpret_cast<const void *>(few_rows_kernel<float, 256, kFewGroupColumns, 1, true, true>)
+           : mb == 2 ? reinterpret_cast<const void *>(few_rows_kernel<float, 256, kFewGroupColumns, 2, true, true>)
+                     : reinterpret_cast<const void *>(few_rows_kernel<float, 256, kFewGroupColumns, 4, true, true>);
+}
 template <typename TW, int D, int NWC, bool PROJ>
 static const void *few_kernel(int mb)
 {
@@ -2433,12 +2459,29 @@ static const void *few_kernel(int mb)
     else return nullptr;
 }
 
-static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
-                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st)
+// fp32 steps in groups of rows, each by the work-groups of one XCD, whose exchanges stay in its L2: the rows of a group (0: not
+// that way).  Every XCD reads all weights, at 0.95 TB/s; what is left beside that is the exchanges, some 1 us each.  Generation with the
+// toy model (d = 256, 4 layers, 4096 tokens), us per token, 64 work-groups over all XCDs (from 9 rows on step kernels) | groups: 1 row
+// 31.5 | 26.2, 2: 32.9 | 26.2, 4: 38.1 | 29.4, 8: 52.7 | 30.3, 9: 84 | 33, 16: 86 | 34, 17: 92 | 37, 32: 97 | 38.  Up to 8 rows both have the
+// same bits, and where other streams launch such steps in turn the small grids, of which four fit the device, get more done
+// (8 rows, us per token of 1 | 2 | 4 streams: groups 30 | 30 | 30, small grids 52 | 27 | 14).  Single steps of more than 8 rows
+// keep the sums of the step kernels.
+static int few_group_rows(const srm_model *m, int64_t B, int64_t G, size_t ws_bytes)
 {
-    const int mb = few_bucket(B), D = m->d, nwc = few_columns(m), nb = D / nwc;
+    if (m->wsize != 4 || B > kFewGroups * 4 || (G == 1 && B > few_max_rows(m)) || device_cus() < kFewGroupBlocks) return 0;
+    const int mb = B <= kFewGroups ? 1 : B <= 2 * kFewGroups ? 2 : 4;
+    return few_list_bytes(B) + few_group_words_bytes(m, B, mb) + 256 <= ws_bytes ? mb : 0;
+}
+static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
+                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    const int D = m->d;
     st = few_stream(st);
-    const void *kern = m->wsize == 4 ? few_kernel<float, 256, 4, true>(mb)
+    int gmb = few_group_rows(m, B, G, ws_bytes);
+    if (gmb && B <= few_max_rows(m) && few_others(m->device, st)) gmb = 0;
+    const int mb = gmb ? gmb : few_bucket(B), nwc = gmb ? kFewGroupColumns : few_columns(m), nb = gmb ? kFewGroupBlocks : D / nwc;
+    const void *kern = gmb ? few_group_kernel(gmb)
+                       : m->wsize == 4 ? few_kernel<float, 256, 4, true>(mb)
                        : m->noproj ? (D == 512 ? few_kernel<bf16, 512, 8, false>(mb) : few_kernel<bf16, 1024, 8, false>(mb))
                                    : (D == 512 ? few_kernel<bf16, 512, 8, true>(mb) : few_kernel<bf16, 1024, 8, true>(mb));
     if (!kern) return fail(SRM_EINVAL, "few_run: no kernel for %lld rows", (long long)B);
@@ -2448,29 +2491,34 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     a.lnf_g = m->lnf_g; a.lnf_b = m->lnf_b;
     a.V = m->V; a.L = m->L; a.dh = m->dm / m->Hs; a.hrow = m->hrow; a.n_ctx = m->cfg.n_ctx;
     a.eps = m->cfg.ln_eps;
-    a.B = (int)B; a.pos0 = pos0; a.G = G;
+    a.B = a.Bs = (int)B; a.row0 = 0; a.pos0 = pos0; a.G = G;
     a.tok_in = tok_in; a.tok_out = tok_out; a.store = store;
     a.state = state; a.state_half = m->shalf ? 1 : 0;
     a.logits = logits; a.hidden = hidden;
     a.temp = temperature; a.seed = seed;
     unsigned char *base = static_cast<unsigned char *>(ws) + few_list_bytes(B);
     a.xw = reinterpret_cast<few_word *>(base);
-    a.mw = a.xw + (size_t)mb * D;
-    a.gw = a.mw + (size_t)mb * D;
-    a.pw = a.gw + (size_t)mb * (m->wsize == 2 ? m->ff / 2 : m->ff);
-    a.flag = reinterpret_cast<unsigned *>(a.pw + (size_t)mb * nb * 2);
+    const size_t rows = gmb ? align_up(B, mb) : mb;
+    a.mw = a.xw + rows * D;
+    a.gw = a.mw + rows * D;
+    a.pw = a.gw + rows * (m->wsize == 2 ? m->ff / 2 : m->ff);
+    few_word *const here = a.pw + (size_t)mb * nb * 2;           // (of groups, see few_rows_kernel)
+    a.flag = reinterpret_cast<unsigned *>(here + (gmb ? nb : 0));
     a.max_polls = 1u << 21;                          // a second or two
     a.arrive_polls = few_arrive_polls;
     int withdrawn = -1;                              // the last work-group's arrival
     const char *sw = getenv("SRM_ONE_KERNEL_STEP"), *polls = getenv("SRM_ONE_KERNEL_POLLS");
-    if (sw && sw[0] == '2') withdrawn = (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
+    if (sw && sw[0] == '2')
+        withdrawn = gmb ? (int)((reinterpret_cast<unsigned char *>(here) - base) / 16) + nb / 2 - 1
+                        : (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
     if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
-    const int n = (int)(few_words_bytes(m, B) / 16), n_store = store ? (int)B * G : 0;
+    const int n = (int)((gmb ? few_group_words_bytes(m, B, mb) : few_words_bytes(m, B)) / 16), n_store = store ? (int)B * G : 0;
     hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
                        reinterpret_cast<u32x4_t *>(base), n, withdrawn, static_cast<int *>(ws), store, n_store);
     HIP_TRY(hipGetLastError());
-    const int lds = few_lds_bytes((int)m->wsize, D, nwc, mb);
+    // (groups: a CU for each work-group)
+    const int lds = std::max(few_lds_bytes((int)m->wsize, D, nwc, mb), gmb ? kFewCuLds : 0);
     HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     void *args[] = {&a};
     return few_launch(m->device, kern, nb, (kFewGather + nwc) * 64, lds, args, st);
@@ -2525,6 +2573,9 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
 // shorter (98).  A width of 512 is what the kernel's registers and LDS were laid out for; at 1024 every XCD would read 21 MB of
 // weights per layer, 22 us at the 0.95 TB/s an XCD gets, where a layer of 37 rows takes 25.  Six layers: as in few_ok, for the
 // results of shallower models.
+// Streams that launch such steps in turn take half or a quarter of the work-groups each (few_others), same bits.  us per step, no
+// logits, of 1 | 2 | 4 streams, all streams together: 37 rows 124 | 90 | 72, step kernels 178 | 94 | 60; 300: 171 | 142 | 137, 230 | 132 |
+// 135; 1024: 242 | 217 | 200, 307 | 219 | 210 (always the whole device: 37 rows 118 | 149 | 156).
 constexpr int64_t kStackMinRows = 5, kStackMaxRows = 3072;
 static_assert(kStackMaxRows <= (int64_t)kStackGroups * kStackMaxPer, "their positions are kept in LDS");
 // Polls of the arrival, some 30 ms: about what one work-group alone takes (ms per step: 37 rows 5, 300: 22, 1024: 33, 3000: 87).
@@ -2573,9 +2624,10 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     a.dead = reinterpret_cast<unsigned *>(mem.words + kStackBlocks * 8 + kStackGroups * 128);
     a.max_polls = 1u << 21;                          // a second or two
     a.arrive_polls = stack_arrive_polls;
+    const int others = few_others(m->device, st), blocks = kStackBlocks / (others == 0 ? 1 : others == 1 ? 2 : 4);
     int withdrawn = -1;                              // the arrival of one of the last work-groups
     const char *sw = getenv("SRM_ONE_KERNEL_STEP"), *polls = getenv("SRM_ONE_KERNEL_POLLS");
-    if (sw && sw[0] == '2') withdrawn = kStackBlocks * 8 / 16 - 1;
+    if (sw && sw[0] == '2') withdrawn = blocks * 8 / 16 - 1;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
     if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
     *dead = a.dead;
@@ -2586,7 +2638,7 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     };
     HIP_TRY(s.cw == 16 ? begin(stack_begin_kernel<512, 16>) : begin(stack_begin_kernel<512, 32>));
     const int lds = stack_lds_bytes(512, s.cw, s.rb);
-    HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, std::max(lds, kFewCuLds)));
     void *args[] = {&a};
-    return few_launch(m->device, kern, kStackBlocks, kStackThreads, lds, args, st);
+    return few_launch(m->device, kern, blocks, kStackThreads, std::max(lds, kFewCuLds), args, st);
 }

@@ -32,8 +32,9 @@
 // through (sc1); loads of it are sc1 in both cases (measured: plain stores between XCDs are not seen, within one always).
 //
 // All work-groups must be resident at once: the arrival and its way out are those of few.hpp.  The words of the arrival carry the XCD,
-// from which the groups are formed; a work-group that is left alone does the phases of all groups and members in turn, with the
-// same tiles and sums.
+// from which the groups are formed; a work-group that is left alone does all parts of all groups' phases in turn, with the same
+// tiles and sums.  So does, with four parts to a member, a launch of a quarter of the work-groups, of which four fit the device side
+// by side: for streams that launch such steps in turn (stack_layers in srm.hip).
 #pragma once
 #include "few.hpp"
 
@@ -140,71 +141,37 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blk = blockIdx.x;
 
-    // ---- arrival: as in few.hpp, but that a word is 4 plus the number of the XCD
+    int me = 0;
     if (tid == 0) {
         few_word found;
-        few_set(p.here + blk, 4 + (few_word)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15), found);        // HW_REG_XCC_ID
-        who[4] = (int)found;
+        few_set(p.here + blk, kFewXcd0 + few_xcd(), found);
+        me = (int)found;
     }
     for (int i = tid; i < p.L * (int)(sizeof(FewLayer) / 8); i += kStackThreads)
         reinterpret_cast<few_word *>(lay)[i] = reinterpret_cast<const few_word *>(p.layers)[i];
-    __syncthreads();
     if (wave == 0) {
-        constexpr int N = kStackBlocks / 64;
-        few_word v[N];
-        bool here = false, withdrawn = false;
-        auto look = [&] {
-            here = true;
-            withdrawn = false;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                here = here && v[i] >= 4;
-                withdrawn = withdrawn || v[i] == kFewWithdrawn;
-            }
-            here = __all(here);
-            withdrawn = __any(withdrawn);
-        };
-        for (unsigned polls = 0;; ++polls) {
-#pragma unroll
-            for (int i = 0; i < N; ++i) v[i] = __hip_atomic_load(p.here + i * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            look();
-            if (here || withdrawn || polls >= p.arrive_polls) break;
-        }
-        if (!here && !withdrawn) {
-#pragma unroll
-            for (int i = 0; i < N; ++i) few_set(p.here + i * 64 + lane, kFewWithdrawn, v[i]);
-            look();
-        }
-        // the work-groups in order of their XCD, kStackPer to a group
-        const int me = who[4];
-        int below = 0, same = 0, at = 0;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            below += __popcll(__ballot((int)v[i] < me));
-            same += __popcll(__ballot((int)v[i] == me));
-            at += __popcll(__ballot((int)v[i] == me && i * 64 + lane < blk));
-        }
-        at += below;
-        const int first = at / kStackPer * kStackPer;
+        const FewPlace place = few_place<kStackBlocks>(p.here, gridDim.x, blk, __builtin_amdgcn_readfirstlane(me), lane, p.arrive_polls);
         if (lane == 0) {
-            who[0] = here;
-            who[1] = at;
-            who[2] = below <= first && first + kStackPer <= below + same;          // the group lies on one XCD
-            who[3] = 0;                                                            // a wait of this group has given up
+            who[0] = place.all;
+            who[1] = place.at;
+            who[2] = place.near;
+            who[3] = 0;                              // a wait of this group has given up
         }
     }
     __syncthreads();
     const bool alone = !__builtin_amdgcn_readfirstlane(who[0]);
     if (__builtin_expect(alone, 0)) {
         if (tid == 0)
-            who[5] = __hip_atomic_fetch_add(p.dead + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kStackBlocks - 1;
+            who[5] = __hip_atomic_fetch_add(p.dead + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
         __syncthreads();
         if (!who[5]) return;
     }
     const int at = __builtin_amdgcn_readfirstlane(who[1]);
     const bool pure = __builtin_amdgcn_readfirstlane(who[2]) || alone;
-    const int c0 = alone ? 0 : at / kStackPer, c1 = alone ? kStackGroups : c0 + 1;
-    const int v0 = alone ? 0 : at % kStackPer;
+    // the work-groups of a group, and the parts of a phase that this one does: part v of kStackPer, and every `members`-th behind it
+    const int members = alone ? 1 : (int)gridDim.x / kStackGroups;
+    const int c0 = alone ? 0 : at / members, c1 = alone ? kStackGroups : c0 + 1;
+    const int v0 = alone ? 0 : at % members;
 
     // LDS only: loads and stores of global memory stay in flight across it
     auto barrier = [] {
@@ -271,7 +238,7 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
         if (alone) return;
         if (tid == 0 && !who[3]) {
             unsigned *const n = p.count + c * 32;
-            const unsigned all = phase * kStackPer;
+            const unsigned all = phase * (unsigned)members;
             __hip_atomic_fetch_add(n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             for (unsigned polls = 0; __hip_atomic_load(n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all; ++polls) {
                 if (polls >= p.max_polls) {
@@ -405,8 +372,8 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
         return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, (row * D + ct * CW + e.q) * 4, 0, kSc1));
     };
 
-    // One group by its members; or (ALONE) all groups, all members' parts in turn, the weights of each requested where they are used.
-    auto run = [&](auto ALONE) __attribute__((always_inline)) {
+    // One group, a part to each member; or (MANY) several, their weights requested where they are used, of all groups where alone.
+    auto run = [&](auto MANY) __attribute__((always_inline)) {
     for (int c = c0; c < c1; ++c) {
         const int r0 = c * p.per, r1 = min(p.rows, r0 + p.per);
         if (r0 >= r1) continue;                      // (all members of the group)
@@ -414,14 +381,14 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
         for (int i = tid; i < r1 - r0; i += kStackThreads)
             lpos[i] = p.pos_rows ? p.pos_rows[r0 + i] : p.pos_dev ? *p.pos_dev : p.pos;
         barrier();
-        if constexpr (!ALONE) {
+        if constexpr (!MANY) {
             get_in(0, v0 % COLT * CW);
             get_out(0, v0 % COLT * CW);
         }
-        auto members = [&](auto &&part) __attribute__((always_inline)) {
-            if constexpr (ALONE) {
+        auto parts = [&](auto &&part) __attribute__((always_inline)) {
+            if constexpr (MANY) {
 #pragma unroll 1
-                for (int v = 0; v < kStackPer; ++v) part(v);
+                for (int v = v0; v < kStackPer; v += members) part(v);
             } else {
                 part(v0);
             }
@@ -438,9 +405,9 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
             };
             // ---------------- LayerNorm1, in-projection, state update
             if (l > 0) meet(c);
-            members([&](int v) __attribute__((always_inline)) {
+            parts([&](int v) __attribute__((always_inline)) {
                 const int ct = v % COLT;
-                if constexpr (ALONE) get_in(l, ct * CW);
+                if constexpr (MANY) get_in(l, ct * CW);
                 unsigned char *const S = p.state + (size_t)l * p.layer_bytes;
                 tiles(v, [&](auto first, int t) __attribute__((always_inline)) {
                     const Quad e = my_quad();
@@ -455,7 +422,7 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
                         al = value(y.alpha, head * p.n_ctx + ps);
                         be = value(y.beta, head * p.n_ctx + ps);
                         s0 = p.state_half ? load_state4(reinterpret_cast<const f16 *>(S), at4) : load_state4(reinterpret_cast<const float *>(S), at4);
-                    }, [&] { if constexpr (first && !ALONE) get_up(0, l, ct * CW); });
+                    }, [&] { if constexpr (first && !MANY) get_up(0, l, ct * CW); });
                     barrier();
                     const int ln = opaque(lane);
                     f32x4_t acc[RB][CB];
@@ -497,9 +464,9 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
             meet(c);
             // (the next layer's LayerNorm parameters, 4 x 2 KB, into the L2: the group's rows would wait for them)
             const u32x4_t touched = few_load(reinterpret_cast<const u32x4_t *>(lay[next].ln[tid / (D / 4) & 3]) + tid % (D / 4));
-            members([&](int v) __attribute__((always_inline)) {
+            parts([&](int v) __attribute__((always_inline)) {
                 const int ct = v % COLT;
-                if constexpr (ALONE) get_out(l, ct * CW);
+                if constexpr (MANY) get_out(l, ct * CW);
                 tiles(v, [&](auto first, int t) __attribute__((always_inline)) {
                     const int base = r0 + t * RT, ln = opaque(lane);
                     u32x4_t a[K1][RB];
@@ -519,8 +486,8 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
                         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                             for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = mfma(w_out[cb][j], a[j][rb], acc[rb][cb]);
-                    if (!first || ALONE) barrier();              // (the sums of the tile in front are formed)
-                    if constexpr (first && !ALONE) get_up(1, l, ct * CW);
+                    if (!first || MANY) barrier();              // (the sums of the tile in front are formed)
+                    if constexpr (first && !MANY) get_up(1, l, ct * CW);
                     __builtin_amdgcn_sched_barrier(0);
                     leave(acc);
                     barrier();
@@ -530,17 +497,17 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
             asm volatile("" : : "v"(touched));
             // ---------------- LayerNorm2, MLP up, GELU
             meet(c);
-            members([&](int v) __attribute__((always_inline)) {
+            parts([&](int v) __attribute__((always_inline)) {
                 const int ct = v % COLT;
-                if constexpr (ALONE) { get_up(0, l, ct * CW); get_up(1, l, ct * CW); }
+                if constexpr (MANY) { get_up(0, l, ct * CW); get_up(1, l, ct * CW); }
                 tiles(v, [&](auto first, int t_) __attribute__((always_inline)) {
-                    if (!first || ALONE) barrier();              // (the panel of the tile in front has been read)
+                    if (!first || MANY) barrier();              // (the panel of the tile in front has been read)
                     const int ln = opaque(lane), col = ct * 4 * CW + CW * cg + 4 * (ln >> 4);
                     float4 bias[CB];
                     normalise(r0 + t_ * RT, r1 - 1, y.ln[2], y.ln[3], [&] {
 #pragma unroll
                         for (int cb = 0; cb < CB; ++cb) bias[cb] = vec4(y.b_up, col + 16 * cb);
-                    }, [&] { if constexpr (first && !ALONE) get_down(l, ct * CW); });
+                    }, [&] { if constexpr (first && !MANY) get_down(l, ct * CW); });
                     barrier();
                     f32x4_t acc[RB][CB];
                     clear(acc);
@@ -578,9 +545,9 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
             });
             // ---------------- MLP down
             meet(c);
-            members([&](int v) __attribute__((always_inline)) {
+            parts([&](int v) __attribute__((always_inline)) {
                 const int ct = v % COLT;
-                if constexpr (ALONE) get_down(l, ct * CW);
+                if constexpr (MANY) get_down(l, ct * CW);
                 tiles(v, [&](auto first, int t) __attribute__((always_inline)) {
                     const int base = r0 + t * RT, ln = opaque(lane);
                     constexpr int KC = RB >= 3 ? 2 : RB == 2 ? 4 : K4, NC = K4 / KC;         // blocks of k in a request, requests
@@ -611,18 +578,18 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
                                 for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = mfma(w_down[cb][n * KC + j], a[n & 1][j][rb], acc[rb][cb]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (first && !ALONE) { get_in(next, ct * CW); get_out(next, ct * CW); }
+                    if constexpr (first && !MANY) { get_in(next, ct * CW); get_out(next, ct * CW); }
                     barrier();                 // (the sums of the tile in front are formed)
                     leave(acc);
                     barrier();
                     add_to_x(base, r1, ct, old, bias);
                 });
             });
-            if (!ALONE && who[3]) return;            // given up: the tokens are -1
+            if (who[3]) return;            // given up: the tokens are -1
         }
         meet(c);
         // ---------------- final LayerNorm, a wavefront per row
-        for (int v = v0; v < (ALONE ? kStackPer : v0 + 1); ++v)
+        for (int v = v0; v < kStackPer; v += members)
             for (int i = v * NW + wave; i < r1 - r0; i += kStackPer * NW) {
                 const unsigned row = (unsigned)(r0 + i);
                 float4 o[VL], pg[VL], pb[VL];
@@ -652,6 +619,6 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
             }
     }
     };
-    if (__builtin_expect(alone, 0)) run(std::true_type{});
+    if (members < kStackPer) run(std::true_type{});
     else run(std::false_type{});
 }

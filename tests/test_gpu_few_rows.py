@@ -667,3 +667,72 @@ def test_streams_that_are_no_objects_of_their_own(srm):
         assert all(torch.equal(a, b) for a, b in zip(step(own.value), want))
         assert hip.hipStreamDestroy(own) == 0
     assert all(torch.equal(a, b) for a, b in zip(step(0), want))
+
+
+@pytest.mark.parametrize("B,half", [(9, False), (16, True), (23, False), (32, False)])
+def test_generation_in_groups_matches_oracle(srm, orc_mod, B, half, monkeypatch):
+    """fp32 generation of up to 32 samples, the rows in groups of one, two or four to an XCD: tokens and state of the oracle,
+    sampled tokens keyed on the sample's number in the call, and the same bits by one work-group alone and beside another stream."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], state_dtype="fp16" if half else "fp32", n_layers=3)
+    w = srm_synth.make_weights(cfg)
+    w["head"] = w["head"] * 25.0
+    prompts = srm_synth.make_prompts(cfg, batch=B, length=5)
+    P, G = prompts.shape[1], 12
+    model, orc = srm.Model(cfg, w), orc_mod.Oracle(cfg, w, "f64")
+    ws, dp = model.new_workspace(B * P), to_dev(prompts)
+
+    def generate(temperature, stream=None):
+        st, tk = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        model.prefill(dp[:, :P - 1].contiguous(), 1, st, tk, workspace=ws)
+        tk.copy_(dp[:, P - 1])
+        out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        assert _launches(lambda: model.generate(B, P - 1, G, tk, st, out, workspace=ws, temperature=temperature, seed=7, stream=stream)) == 1
+        return out, tk, st
+
+    for temperature in (0.0, 0.7):
+        kw = {"temperature": temperature, "seed": 7} if temperature else {}
+        ref = orc.greedy(prompts, G, want_logits=True, **kw)
+        print(f"generation in groups B={B} half={half} T={temperature}", flush=True)
+        out, tk, st = generate(temperature)
+        got = out.cpu().numpy().T
+        check_tokens(got, ref["tokens"], ref["margin"], np.abs(ref["logits"]).max(axis=2), rtol=1e-3 if half else 1e-4)
+        assert (tk.cpu().numpy() == got[:, -1]).all()
+        if not half:
+            s_got = st.view(cfg.n_layers, B, cfg.d_model).permute(1, 0, 2).cpu().numpy()
+            assert np.abs(s_got - ref["state"]).max() <= 1e-4 * np.abs(ref["state"]).max()
+        for mode in ("2", "3"):
+            monkeypatch.setenv(SWITCH, mode)
+            assert all(torch.equal(a, b) for a, b in zip(generate(temperature), (out, tk, st)))
+            monkeypatch.delenv(SWITCH)
+        assert all(torch.equal(a, b) for a, b in zip(generate(temperature, torch.cuda.Stream()), (out, tk, st)))
+    monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+    out, tk, st = generate(0.0)
+    assert (tk == -1).any() and (out == -1).any()
+    monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+    model.close()
+
+
+@pytest.mark.parametrize("B", [1, 3, 8])
+def test_fp32_steps_in_groups_and_side_by_side_have_the_same_bits(srm, B):
+    """Up to eight rows run in groups where one stream has the device for itself, and as one small grid among others of its kind
+    where several launch in turn."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model, G = srm.Model(cfg, srm_synth.make_weights(cfg)), 10
+    streams, ws = [torch.cuda.Stream() for _ in range(2)], [model.new_workspace(B) for _ in range(2)]
+    start = to_dev((np.arange(B) * 31).astype(np.int32))
+
+    def generate(i):
+        st, tk, out = model.new_state(B), start.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        model.generate(B, 3, G, tk, st, out, workspace=ws[i], temperature=0.7, seed=5, stream=streams[i])
+        return out, tk, st
+
+    print(f"fp32 generation, groups and side by side B={B}", flush=True)
+    for _ in range(9):
+        want = generate(0)
+    got = [generate(i % 2) for i in range(6)]
+    torch.cuda.synchronize()
+    for one in got:
+        assert all(torch.equal(a, b) for a, b in zip(one, want))
+    model.close()

@@ -189,3 +189,31 @@ def test_a_wait_that_gives_up_leaves_marked_tokens(srm, monkeypatch):
     for how, w in zip(ways, want):
         assert all(torch.equal(a, b) for a, b in zip(step(**how), w))
     model.close()
+
+
+@pytest.mark.parametrize("B", [37, 300, 513, 1100])
+def test_streams_in_turn_give_the_same_bits(srm, B):
+    """Steps launched on two streams in turn take a quarter of the work-groups each, so that several fit the device side by
+    side; eight launches on one stream later it has the device for itself again."""
+    cfg = _config(vocab=200)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    tok = to_dev((np.arange(B) * 3 % cfg.vocab).astype(np.int32))
+    ws = [model.new_workspace(B) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def step(i):
+        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        lg = torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        model.decode_step(B, 2, tok, st, out, logits=lg, workspace=ws[i], stream=streams[i])
+        return st, out, lg
+
+    print(f"streams in turn B={B}", flush=True)
+    for _ in range(9):
+        want = step(0)
+    got = [step(i % 2) for i in range(6)]
+    assert _launches(lambda: got.append(step(1))) == 1
+    torch.cuda.synchronize()
+    for one in got:
+        assert all(torch.equal(a, b) for a, b in zip(one, want))
+    model.close()
