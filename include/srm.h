@@ -43,7 +43,10 @@
  *     SRM_LN_ON_LOAD=0   steps of at most 16 samples (8 where token mixing can
  *                        be one kernel): LayerNorm launches between the GEMMs
  *                        instead of LayerNorm made by the consuming GEMM (same
- *                        bits);
+ *                        bits), and steps and passes of some ten thousand rows
+ *                        of a bf16 model instead of LayerNorm made by the
+ *                        projections in front of it (its sums in another order;
+ *                        SRM_ONE_KERNEL_POLLS=n, for tests, bounds their waits);
  *     SRM_TOKEN_MIX=0    bf16 models of d_model 256 or 512, steps of 9 to about
  *                        1000 samples: the token mixing of a layer as separate
  *                        kernels instead of one (sums in another order); =1 as

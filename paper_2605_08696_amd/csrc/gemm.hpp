@@ -16,7 +16,7 @@
 #include "common.hpp"
 #include <type_traits>
 
-enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_ARGMAX = 3, EPI_F32 = 4, EPI_MIX = 5 };
+enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_ARGMAX = 3, EPI_F32 = 4, EPI_MIX = 5, EPI_RESID_LN = 6 };
 
 struct GemmEpi {
     const float *bias;   // [N] or nullptr
@@ -45,6 +45,13 @@ struct GemmEpi {
     // LNA kernels (A operand = LayerNorm of ln_x rows, computed by the block): ln_x [M][K] fp32, gain, bias, epsilon.
     const float *ln_x, *ln_g, *ln_b;
     float ln_eps;
+    // EPI_RESID_LN (gemm_persist.hpp): EPI_RESID, and the LayerNorm (ln_g, ln_b, ln_eps) of the new rows to ln_out [M][ldo] in the
+    // activation type.  ln_stats [M][column tiles]: mean and squared deviations of a row's columns in a tile; ln_words [row tiles], zero at
+    // the launch: tiles that have left theirs, and from bit 16 on those that have not waited for the others; ln_polls: how often they ask.
+    void *ln_out;
+    float2 *ln_stats;
+    unsigned *ln_words;
+    unsigned ln_polls;
     // Measuring hook (srm_linear_timeline_probe): if not null, every work-group b < clk_blocks of
     // gemm_bf16_kernel writes eight words at clk + 8 b: the 100 MHz wall clock at its start, at the start
     // of its k loop, at the end of the k loop and after its last store has completed; the shader cycle

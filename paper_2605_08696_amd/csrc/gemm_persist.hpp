@@ -23,6 +23,93 @@ constexpr int kPersistLds = 160 * 1024;
 // wave tiles).  Sixteen rows at a time pass through a wave-private stage [16][64] in `stage` (16-byte chunk c of row r at
 // chunk c ^ r: writes and reads free of bank conflicts), so that global accesses are 16-byte vectors over 256 bytes of a
 // row.  Old values (residual stream, recurrent state) are requested for 32 rows at a time, in front of the stage.
+//
+// EPI_RESID_LN also makes the LayerNorm of the new rows, which a launch of its own reads again (16384 rows of 1024: 18.2 us): the new
+// values stay in the accumulators' registers, the tiles of a row exchange the mean and the squared deviations of their 256
+// columns (two-pass within a wavefront's 64, combined by Chan's formula) through memory, and each normalises its own columns.
+// The tiles of a row tile are worked on at the same time, next to each other on an XCD, but nothing promises that: a
+// work-group asks ln_polls times, and if some tile is still missing it leaves its columns to whoever leaves the last one.  Both
+// are one atomic on the row tile's word, so that exactly one of them does it.  (16384 x 1024, both kinds of launch, us, with a
+// LayerNorm launch behind | this: 98.7 | 92.9, of which the sums and the normalising are about 5, the exchange 2, the stores 5.)
+constexpr int kLnTiles = 4;                          // column tiles of a row at most
+template <typename TAct, typename BARRIER>
+__device__ __forceinline__ unsigned persist_ln_exchange(const GemmEpi &ep, const float2 *part, float2 *rows, int M, int m0, int bm, int bn,
+                                                        int nbn, int tid, BARRIER &&lds_barrier)
+{
+    // part [4 wavefronts of 64 columns][256 rows] -> this tile's pair for the others
+    unsigned long long *const stats = reinterpret_cast<unsigned long long *>(ep.ln_stats);
+    auto pair = [](unsigned long long v) {
+        return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+    };
+    if (tid < 256) {
+        float mean = 0.0f, dev = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) mean += part[w * 256 + tid].x;
+        mean *= 0.25f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float2 t = part[w * 256 + tid];
+            dev += t.y + 64.0f * ((t.x - mean) * (t.x - mean));
+        }
+        if (m0 + tid < M)
+            __hip_atomic_store(stats + (size_t)(m0 + tid) * nbn + bn, (unsigned long long)__float_as_uint(dev) << 32 | __float_as_uint(mean),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    lds_barrier();
+    unsigned *const word = ep.ln_words + bm, *const said = reinterpret_cast<unsigned *>(rows + 256);
+    if (tid == 0) {
+        unsigned seen = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+        const bool last = (seen & 0xffff) == (unsigned)nbn;
+        for (unsigned polls = 0; (seen & 0xffff) != (unsigned)nbn && polls < ep.ln_polls; ++polls)
+            seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        said[0] = (seen & 0xffff) == (unsigned)nbn;
+        said[1] = last ? seen >> 16 : 0;             // whose columns this work-group makes besides its own
+    }
+    lds_barrier();
+    if (__builtin_expect(!said[0], 0)) {             // tired of waiting: what is in memory is for whoever comes last
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) {
+            const unsigned seen = __hip_atomic_fetch_or(word, 0x10000u << bn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            said[0] = (seen & 0xffff) == (unsigned)nbn;
+        }
+        __syncthreads();
+        if (!said[0]) return ~0u;
+    }
+    const unsigned others = said[1];
+    if (tid < 256) {
+        const size_t at = (size_t)min(m0 + tid, M - 1) * nbn;
+        float2 t[kLnTiles];
+        float mean = 0.0f, dev = 0.0f;
+#pragma unroll
+        for (int b = 0; b < kLnTiles; ++b)
+            t[b] = pair(__hip_atomic_load(stats + at + min(b, nbn - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma unroll
+        for (int b = 0; b < kLnTiles; ++b) mean += b < nbn ? t[b].x : 0.0f;
+        mean /= (float)nbn;
+#pragma unroll
+        for (int b = 0; b < kLnTiles; ++b) dev += b < nbn ? t[b].y + 256.0f * ((t[b].x - mean) * (t[b].x - mean)) : 0.0f;
+        rows[tid] = make_float2(mean, 1.0f / sqrtf(dev / (float)(nbn * 256) + ep.ln_eps));
+    }
+    lds_barrier();
+    if (__builtin_expect(others != 0, 0)) {
+        __threadfence();
+        for (int b = 0; b < nbn; ++b) {
+            if (!(others >> b & 1)) continue;
+            for (int r = tid >> 6; r < 256 && m0 + r < M; r += 8) {
+                const size_t at = (size_t)(m0 + r) * ep.ldo + b * 256 + (tid & 63) * 4;
+                const float4 x = load4(static_cast<const float *>(ep.out) + at), g = load4(ep.ln_g + b * 256 + (tid & 63) * 4),
+                             c = load4(ep.ln_b + b * 256 + (tid & 63) * 4);
+                const float2 s = rows[r];
+                store4(static_cast<TAct *>(ep.ln_out) + at, make_float4((x.x - s.x) * s.y * g.x + c.x, (x.y - s.x) * s.y * g.y + c.y,
+                                                                        (x.z - s.x) * s.y * g.z + c.z, (x.w - s.x) * s.y * g.w + c.w));
+            }
+        }
+    }
+    return 0;
+}
+
 template <int EPI, typename TAct, bool STORE, typename BARRIER>
 __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned char *stage_base, const GemmEpi &ep, int M, int N,
                                                  int m0, int n0, int bn, const int tid, BARRIER &&lds_barrier)
@@ -68,6 +155,11 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
         const int s_row = lane >> 4, s_chunk = lane & 15;
         const int gcol = wcol0 + s_chunk * 4;
         const unsigned lane_at = (unsigned)s_row * (unsigned)ep.ldo + s_chunk * 4;    // (the rest of an offset is uniform)
+        // (EPI_RESID_LN: the tile's rows that exist, the hardware's range check leaves out the others; fewer registers than addresses)
+        [[maybe_unused]] const auto x_rs = __builtin_amdgcn_make_buffer_rsrc(
+            EPI == EPI_RESID_LN ? static_cast<float *>(ep.out) + (int64_t)m0 * ep.ldo : nullptr, 0, min(256, M - m0) * (int)ep.ldo * 4, 0x00020000);
+        [[maybe_unused]] auto x_row = [&](int t, int it) { return ((wm * WTM + t * 16 + it * 4) * (int)ep.ldo + wcol0) * 4; };
+        [[maybe_unused]] float2 kept[2];             // EPI_RESID_LN: mean and squared deviations of 64 columns of two rows
         auto slices = [&](auto inside_c, auto choice_c) {
             constexpr bool IN = decltype(inside_c)::value;
             auto row_of = [&](int t, int it) { return (int64_t)wrow0 + t * 16 + it * 4 + s_row; };
@@ -80,12 +172,13 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
             static_for<0, TM / 2>([&](auto p_) {
                 constexpr int t0 = 2 * decltype(p_)::value;
                 [[maybe_unused]] float4 old[2][4];
-                if constexpr (EPI == EPI_RESID || EPI == EPI_MIX) {
+                if constexpr (EPI == EPI_RESID || EPI == EPI_RESID_LN || EPI == EPI_MIX) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
                         for (int it = 0; it < 4; ++it) {
                             if constexpr (EPI == EPI_RESID) old[h][it] = load4(static_cast<const float *>(ep.out) + at(t0 + h, it));
+                            else if constexpr (EPI == EPI_RESID_LN) old[h][it] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, (int)lane_at * 4, x_row(t0 + h, it), 0));
                             else if (ep.state_half) old[h][it] = load_state4(static_cast<const f16 *>(ep.state), at(t0 + h, it) >> 2);
                             else old[h][it] = load_state4(static_cast<const float *>(ep.state), at(t0 + h, it) >> 2);
                         }
@@ -118,6 +211,25 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                     f32x4_t v[4];
 #pragma unroll
                     for (int it = 0; it < 4; ++it) v[it] = stage[(it * 4 + s_row) * 16 + (s_chunk ^ (it * 4 + s_row))];
+                    if constexpr (EPI == EPI_RESID_LN) {
+#pragma unroll
+                        for (int it = 0; it < 4; ++it) {               // (the row's first half of acc is in the stage)
+                            const float4 o = old[h][it];
+                            const f32x4_t w = f32x4_t{o.x + v[it][0], o.y + v[it][1], o.z + v[it][2], o.w + v[it][3]};
+                            const float mean = row16_sum((w[0] + w[1]) + (w[2] + w[3])) * (1.0f / 64);
+                            const float a = w[0] - mean, b = w[1] - mean, c = w[2] - mean, d = w[3] - mean;
+                            const float dev = row16_sum((a * a + b * b) + (c * c + d * d));
+                            // row t*16 + it*4 + s_row is kept by lane (4t + it) mod 16 of the sixteen that hold it
+                            if (s_chunk == ((t * 4 + it) & 15)) {
+                                kept[t / 4].x = mean;
+                                kept[t / 4].y = dev;
+                            }
+                            acc[t][it] = w;
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, w), x_rs, (int)lane_at * 4, x_row(t, it), 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        return;
+                    }
 #pragma unroll
                     for (int it = 0; it < 4; ++it) {
                         if (!exists(t, it)) continue;
@@ -143,6 +255,39 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
             with_choice(ep, !inside, [&](auto choice_c) {
                 keys(choice_c);
                 slices(std::integral_constant<bool, !(decltype(choice_c)::value & CHOICE_EDGE)>{}, choice_c);
+            });
+        } else if constexpr (EPI == EPI_RESID_LN) {
+            // (one form for all tiles: of two, whose new values meet behind them, each would have registers of its own for them)
+            slices(std::false_type{}, std::integral_constant<int, CHOICE_EDGE>{});
+            lds_barrier();                           // the stages have been read back
+            float2 *const part = reinterpret_cast<float2 *>(stage_base), *const rows = part + 4 * 256;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {            // row 4t + it = s_chunk + 16 q of this lane's
+                const int k = s_chunk + 16 * q;
+                part[wn * 256 + wm * WTM + (k >> 2) * 16 + (k & 3) * 4 + s_row] = kept[q];
+            }
+            lds_barrier();
+            if (persist_ln_exchange<TAct>(ep, part, rows, M, m0, m0 >> 8, bn, N >> 8, tid, lds_barrier) == ~0u) return;
+            // (addresses formed anew, from an opaque copy: those of the slices' stores would be held in registers until here)
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const int r0 = wm * WTM + (ln >> 4), col = wcol0 + (ln & 15) * 4;
+            const float4 gain = load4(ep.ln_g + col), shift = load4(ep.ln_b + col);            // (whole tiles of columns)
+            const auto out_rs = __builtin_amdgcn_make_buffer_rsrc(static_cast<TAct *>(ep.ln_out) + (int64_t)m0 * ep.ldo, 0,
+                                                                  min(256, M - m0) * (int)ep.ldo * (int)sizeof(TAct), 0x00020000);
+            const int to = (r0 * (int)ep.ldo + col) * (int)sizeof(TAct);
+            static_for<0, TM>([&](auto t_) {
+                constexpr int t = decltype(t_)::value;
+#pragma unroll
+                for (int it = 0; it < 4; ++it) {
+                    const float2 s = rows[r0 + t * 16 + it * 4];
+                    const f32x4_t x = acc[t][it];
+                    const bf16x2_t lo = __builtin_convertvector(f32x2_t{(x[0] - s.x) * s.y * gain.x + shift.x, (x[1] - s.x) * s.y * gain.y + shift.y}, bf16x2_t);
+                    const bf16x2_t hi = __builtin_convertvector(f32x2_t{(x[2] - s.x) * s.y * gain.z + shift.z, (x[3] - s.x) * s.y * gain.w + shift.w}, bf16x2_t);
+                    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)}, out_rs, to,
+                                                          (t * 16 + it * 4) * (int)ep.ldo * (int)sizeof(TAct), 0);
+                }
             });
         } else if (inside) {
             slices(std::true_type{}, std::integral_constant<int, CHOICE_PLAIN>{});
@@ -296,7 +441,7 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
     };
 
     // the epilogues that hold old values leave no registers for the operands that the last k tile has read ahead
-    constexpr bool REREAD = EPI == EPI_RESID || EPI == EPI_MIX;
+    constexpr bool REREAD = EPI == EPI_RESID || EPI == EPI_RESID_LN || EPI == EPI_MIX;
 
     int v = blockIdx.x;                              // gridDim.x <= nblk: every work-group has a first tile
     Tile cur = tile_at(v);
@@ -350,7 +495,7 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
             epilogue(std::true_type{});
             bias_request(nxt.n0);
         } else {
-            if constexpr (EPI != EPI_MIX) bias_request(nxt.n0);
+            if constexpr (EPI != EPI_MIX && EPI != EPI_RESID_LN) bias_request(nxt.n0);
             __builtin_amdgcn_sched_barrier(0);
             epilogue(std::integral_constant<bool, EPI != EPI_ARGMAX>{});
         }
@@ -369,10 +514,17 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         if (vn >= nblk) break;                       // (block-uniform)
         v = vn;
         cur = nxt;
-        if constexpr (EPI == EPI_MIX) bias_request(cur.n0);
+        if constexpr (EPI == EPI_MIX || EPI == EPI_RESID_LN) bias_request(cur.n0);
         lds_barrier();                               // every wave has read its stage back: the unit can be filled
         if constexpr (REREAD) static_for<0, TM + TN>([&](auto r_) { read_one(r_, h0, at(0), at(1)); });
     }
     SRM_WAIT_VM(0);                                  // (the loads behind the last tile, of zero size)
 #undef SRM_WAIT_VM
+}
+
+// The words of a pass's EPI_RESID_LN launches
+__global__ void __launch_bounds__(256) words_clear_kernel(int *words, int n)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) words[i] = 0;
 }

@@ -1164,6 +1164,45 @@ static bool last_rows_ok(const srm_model *m, int64_t N, int64_t rows, int64_t sh
 template <typename T>
 static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr, int64_t rows, hipStream_t st);
 
+// Many rows of a bf16 model: the projections that add to the residual stream also make the LayerNorm behind them
+// (EPI_RESID_LN), where both take the 256x256 persistent tile and a row is whole tiles of it, at most kLnTiles.  us, LayerNorm
+// launches | this: decode step of the large model 13001 rows 5946 | 5763, 16384: 6727 | 6462, prefill 256 x 128 10946 | 10534, d = 512, state in
+// 16 bits, 30001 rows 2976 | 2825; a projection of 16384 x 1024 and its LayerNorm 80.5 + 18.2 | 92.9.  (Smaller launches, in tiles of
+// one round, stay as they are: up to 12 288 rows the LayerNorm launches read the next matrices ahead, worth 3 % at 3001 rows.)
+// SRM_LN_ON_LOAD=0 in the environment keeps the LayerNorm launches.
+static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows)
+{
+    if (m->wsize != 2 || m->noproj || m->d % 256 || m->d / 256 > kLnTiles || rows <= 0 || rows >= (1 << 30)) return false;
+    if ((int64_t)2 * m->L * cdiv(rows, 256) > 64 + rows) return false;           // (the words lie in w.slow)
+    for (const int K : {m->dm, m->ff})
+        if (slices_ok(std::max(rows, call_rows), m->d, K) || choose_one_round_tile(rows, m->d, K, false, false, true) >= 0 ||
+            choose_tile(rows, m->d, K, 64) != 0 || !persist_ok(rows, m->d, K) || K % 64)
+            return false;
+    const char *e = getenv("SRM_LN_ON_LOAD");
+    return !(e && e[0] == '0');
+}
+// x += A W^T + bias, out = LayerNorm(x); launch: its number in the pass
+constexpr unsigned kLnPolls = 1u << 9;               // some 200 us: the tiles of a row come within a few
+static int resid_ln(const srm_model *m, Workspace &w, const void *A, const void *W, const float *bias, int64_t rows, int K, const float *g,
+                    const float *b, int launch, hipStream_t st)
+{
+    const int nbm = (int)cdiv(rows, 256);
+    if (launch == 0) {
+        const int n = 2 * m->L * nbm;
+        hipLaunchKernelGGL(words_clear_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, w.slow, n);
+        HIP_TRY(hipGetLastError());
+    }
+    GemmEpi ep{bias, w.x, (int64_t)m->d};
+    ep.ln_g = g; ep.ln_b = b; ep.ln_eps = m->cfg.ln_eps;
+    ep.ln_out = w.a;
+    ep.ln_stats = static_cast<float2 *>(w.u);        // (nobody reads u behind the mixer)
+    ep.ln_words = reinterpret_cast<unsigned *>(w.slow) + (size_t)launch * nbm;
+    const char *polls = getenv("SRM_ONE_KERNEL_POLLS");
+    ep.ln_polls = polls ? (unsigned)std::max(0, atoi(polls)) : kLnPolls;
+    ep.clk = g_clock_probe; ep.clk_blocks = g_clock_blocks;
+    return launch_bf16_persist<EPI_RESID_LN, bf16>(static_cast<const bf16 *>(A), static_cast<const bf16 *>(W), (int)rows, m->d, K, ep, st);
+}
+
 // One block (token mixing + channel mixing) on `rows` token rows.  On entry
 // w.a holds LayerNorm1(x) of this layer; mix(l) turns w.u into w.mx.  With
 // norm_next, w.a leaves holding the next layer's LayerNorm1(x), or the final
@@ -1245,7 +1284,10 @@ static int block(const srm_model *m, int l, Workspace &w, int64_t rows, int64_t 
         SRM_TRY(mix(l));
         SRM_TRY(keep_last());
     }
-    if (!m->noproj) {
+    const bool fused_ln = resid_ln_ok(m, rows, call_rows);
+    if (fused_ln) {
+        SRM_TRY(resid_ln(m, w, w.mx, y.w_out, y.b_out, rows, dm, y.ln2_g, y.ln2_b, 2 * l, st));
+    } else if (!m->noproj) {
         SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                       MixArgs(), call_rows)));
         if (!lnf) SRM_TRY((layernorm<T, false>(m, w.x, d, nullptr, nullptr, y.ln2_g, y.ln2_b, w.a, rows, st, nullptr, 0, 0,
@@ -1253,6 +1295,9 @@ static int block(const srm_model *m, int l, Workspace &w, int64_t rows, int64_t 
     }
     SRM_TRY((linear<EPI_GELU, T>(w.a, y.w_up, y.b_up, rows, ff, d, w.g, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                  MixArgs(), call_rows, ln2)));
+    if (fused_ln && norm_next)
+        return resid_ln(m, w, w.g, y.w_down, y.b_down, rows, ff, l + 1 < m->L ? m->layers[l + 1].ln1_g : m->lnf_g,
+                        l + 1 < m->L ? m->layers[l + 1].ln1_b : m->lnf_b, 2 * l + 1, st);
     SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                   MixArgs(), call_rows)));
     if ((lnf || ln1f) && l + 1 < m->L) return SRM_OK;              // the next layer's in-projection normalises

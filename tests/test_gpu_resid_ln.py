@@ -1,0 +1,102 @@
+"""LayerNorm made by the projections that add to the residual stream (many rows of a bf16 model, the 256x256 persistent tile) against
+the LayerNorm launches (the library's switch) and the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import srm_synth
+from gpu_util import to_dev, rel_err_rows, kernel_launches
+
+pytestmark = pytest.mark.gpu
+SWITCH = "SRM_LN_ON_LOAD"
+
+
+@pytest.fixture(scope="module")
+def srm():
+    import paper_2605_08696_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+@pytest.fixture(scope="module")
+def orc_mod(oracle_mod):
+    return oracle_mod
+
+
+
+
+# column tiles of a row: four, three, two; a last row tile of one row, of a part, whole; several rounds of the chip
+@pytest.mark.parametrize("d,B,variant", [(1024, 12801, {}), (1024, 32768, dict(state_dtype="fp16")), (768, 17300, {}), (512, 25700, {}),
+                                         (1024, 16384, dict(head_layout="combined"))])
+def test_decode_with_the_layernorm_in_the_residual_epilogue(srm, orc_mod, d, B, variant, monkeypatch):
+    cfg = srm_synth.tiny_config(vocab=260, d_model=d, n_layers=2, n_heads=4, n_ctx=8, weight_dtype="bf16", seed=91, **variant)
+    w = srm_synth.make_weights(cfg, stress=True)
+    for y in w["layers"]:                            # rows far from a mean of zero, and wide ones
+        y["b_out"] = y["b_out"] + np.linspace(-2.0, 6.0, d).astype(np.float32)
+    model = srm.Model(cfg, w)
+    toks = srm_synth.make_prompts(cfg, batch=B, length=2)
+    some = [0, 255, 256, B // 2, B - 2, B - 1]
+    ref = orc_mod.Oracle(cfg, w, "f64").recurrent_forward(toks[some])
+    tc, ws = to_dev(toks).t().contiguous(), model.new_workspace(B)
+
+    def steps():
+        st, out = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")
+        res = []
+        for t in range(2):
+            lg, hd = torch.empty((B, cfg.vocab), device="cuda"), torch.empty((B, d), device="cuda")
+            model.decode_step(B, t, tc[t], st, out, logits=lg, hidden=hd, workspace=ws)
+            res += [lg, hd]
+        torch.cuda.synchronize()
+        return res + [st]
+
+    print(f"LayerNorm in the residual epilogue d={d} B={B} {variant}", flush=True)
+    ws.random_(0, 256)
+    one = steps()
+    assert kernel_launches("gemm_bf16_persist_kernel", steps) > 0
+    again = steps()
+    assert all(torch.equal(a, b) for a, b in zip(one, again))
+    # nobody waits: what each work-group has not made is made by the last of its rows', the same bits
+    monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+    hurried = steps()
+    monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+    assert all(torch.equal(a, b) for a, b in zip(one, hurried))
+    monkeypatch.setenv(SWITCH, "0")
+    many = steps()
+    monkeypatch.delenv(SWITCH)
+    assert not all(torch.equal(a, b) for a, b in zip(one, many))      # (another order of the sums: the epilogue is what ran)
+    tol = 4e-2 if cfg.state_dtype == "fp16" else 2e-2
+    for t in range(2):
+        for k, name in ((0, "logits"), (1, "hidden")):
+            assert rel_err_rows(one[2 * t + k][some].cpu().numpy(), ref[name][:, t]) <= tol
+            assert rel_err_rows(one[2 * t + k].cpu().numpy(), many[2 * t + k].cpu().numpy()) <= tol
+    # no further from 64 bits than the launches: the error of the normalised rows is the rounding to bf16
+    err = [np.sqrt(np.mean((r[3][some].double().cpu().numpy() - ref["hidden"][:, 1]) ** 2)) for r in (one, many)]
+    assert err[0] <= 1.25 * err[1]
+    model.close()
+
+
+def test_prefill_and_sequence_form_with_the_layernorm_in_the_residual_epilogue(srm, monkeypatch):
+    """Prompts in one pass and in several, and the sequence form, against the LayerNorm launches."""
+    cfg = srm_synth.tiny_config(vocab=260, d_model=1024, n_layers=3, n_heads=4, n_ctx=70, weight_dtype="bf16", seed=92)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    N, P = 420, 64
+    toks = to_dev(srm_synth.make_prompts(cfg, batch=N, length=P))
+
+    def run(rows):
+        st, tk = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+        lg, hid = torch.empty((N, cfg.vocab), device="cuda"), torch.empty((N, P, 1024), device="cuda")
+        model.prefill(toks, 1, st, tk, logits=lg, workspace=model.new_workspace(rows))
+        model.parallel_forward(toks, hid, workspace=model.new_workspace(rows))
+        torch.cuda.synchronize()
+        return st, lg, hid.view(N * P, 1024)
+
+    print("prefill and sequence form", flush=True)
+    one, two = run(N * P), run(N * P // 2)
+    monkeypatch.setenv(SWITCH, "0")
+    many = run(N * P)
+    assert not torch.equal(one[2], many[2])
+    for got in (one, two):
+        assert (got[0] - many[0]).abs().max() <= 2e-2 * many[0].abs().max()
+        assert rel_err_rows(got[1].cpu().numpy(), many[1].cpu().numpy()) <= 2e-2
+        assert float((got[2] - many[2]).norm() / many[2].norm()) <= 2e-2
+    model.close()
