@@ -244,6 +244,10 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                             q.old = old[h][it];
                             q.al = al[it]; q.be = be[it]; q.la = la;
                             epi_mix_store<TAct>(ep, row, gcol, q, ps[it] >= 0 && ps[it] < ep.n_ctx, row_repeat, w);
+                        } else if constexpr (EPI == EPI_ARGMAX && IN) {
+                            // (nontemporal, see epi_store4; the uniform part of the offset apart, which saves the registers of the rest)
+                            float *const o = static_cast<float *>(ep.out) + ((wrow0 + t * 16 + it * 4) * ep.ldo + wcol0);
+                            __builtin_nontemporal_store(f32x4_t{w.x, w.y, w.z, w.w}, reinterpret_cast<f32x4_t *>(o + lane_at));
                         } else {
                             epi_store4<EPI, TAct>(ep, row, gcol, w);
                         }
