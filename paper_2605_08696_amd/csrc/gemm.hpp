@@ -258,7 +258,9 @@ __device__ __forceinline__ void epi_store4(const GemmEpi &ep, int64_t row, int c
     } else {
         // Logits: written once, by far more than the L2s hold, and not read by the launch.  Nontemporal, they leave it to the operands (us,
         // ordinary | this, rows x columns x K: 300 x 32000 x 512 30.7 | 29.3, 1024: 54.7 | 53.1, 2000: 96.4 | 88.6, 3001 x 32000 x 1024
-        // 208 | 196; the step of 3001 rows with its nucleus pass behind 2064 | 2044).
+        // 208 | 196; the step of 3001 rows with its nucleus pass behind 2064 | 2044).  It costs where such a pass follows and finds up to
+        // 256 MB of logits in memory instead of the last-level cache (1000 rows 1037.6 | 1040.6, 1500 1370 | 1374), but a choice at each
+        // store costs more (1063 | 1070, 1403 | 1413).
         if (ep.out)
             __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w},
                                         reinterpret_cast<f32x4_t *>(reinterpret_cast<float *>(ep.out) + row * ep.ldo + col));
