@@ -1181,14 +1181,15 @@ static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows)
     const char *e = getenv("SRM_LN_ON_LOAD");
     return !(e && e[0] == '0');
 }
-// x += A W^T + bias, out = LayerNorm(x); launch: its number in the pass
+// x += A W^T + bias, out = LayerNorm(x); launch: its number among the `launches` of so many rows in the pass, of which the first clears
+// the words of all.  (The last rows of a prefill, which the last layer goes on with, count anew: the words lie by the row tiles.)
 constexpr unsigned kLnPolls = 1u << 9;               // some 200 us: the tiles of a row come within a few
 static int resid_ln(const srm_model *m, Workspace &w, const void *A, const void *W, const float *bias, int64_t rows, int K, const float *g,
-                    const float *b, int launch, hipStream_t st)
+                    const float *b, int launch, int launches, hipStream_t st)
 {
     const int nbm = (int)cdiv(rows, 256);
     if (launch == 0) {
-        const int n = 2 * m->L * nbm;
+        const int n = launches * nbm;
         hipLaunchKernelGGL(words_clear_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, w.slow, n);
         HIP_TRY(hipGetLastError());
     }
@@ -1285,8 +1286,9 @@ static int block(const srm_model *m, int l, Workspace &w, int64_t rows, int64_t 
         SRM_TRY(keep_last());
     }
     const bool fused_ln = resid_ln_ok(m, rows, call_rows);
+    const int fused_at = last.n ? 0 : 2 * l, fused_n = last.n ? 2 : 2 * m->L;
     if (fused_ln) {
-        SRM_TRY(resid_ln(m, w, w.mx, y.w_out, y.b_out, rows, dm, y.ln2_g, y.ln2_b, 2 * l, st));
+        SRM_TRY(resid_ln(m, w, w.mx, y.w_out, y.b_out, rows, dm, y.ln2_g, y.ln2_b, fused_at, fused_n, st));
     } else if (!m->noproj) {
         SRM_TRY((linear<EPI_RESID, T>(w.mx, y.w_out, y.b_out, rows, d, dm, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                       MixArgs(), call_rows)));
@@ -1297,7 +1299,7 @@ static int block(const srm_model *m, int l, Workspace &w, int64_t rows, int64_t 
                                  MixArgs(), call_rows, ln2)));
     if (fused_ln && norm_next)
         return resid_ln(m, w, w.g, y.w_down, y.b_down, rows, ff, l + 1 < m->L ? m->layers[l + 1].ln1_g : m->lnf_g,
-                        l + 1 < m->L ? m->layers[l + 1].ln1_b : m->lnf_b, 2 * l + 1, st);
+                        l + 1 < m->L ? m->layers[l + 1].ln1_b : m->lnf_b, fused_at + 1, fused_n, st);
     SRM_TRY((linear<EPI_RESID, T>(w.g, y.w_down, y.b_down, rows, d, ff, w.x, st, nullptr, nullptr, 64, nullptr, Sampling(),
                                   MixArgs(), call_rows)));
     if ((lnf || ln1f) && l + 1 < m->L) return SRM_OK;              // the next layer's in-projection normalises

@@ -100,3 +100,35 @@ def test_prefill_and_sequence_form_with_the_layernorm_in_the_residual_epilogue(s
         assert rel_err_rows(got[1].cpu().numpy(), many[1].cpu().numpy()) <= 2e-2
         assert float((got[2] - many[2]).norm() / many[2].norm()) <= 2e-2
     model.close()
+
+
+@pytest.mark.parametrize("ragged", [False, True])
+def test_prefill_whose_last_rows_are_as_many(srm, ragged, monkeypatch):
+    """The last layer goes on with the prompts' last rows, so many that its projections make the LayerNorm too, in other row tiles than
+    the layers in front of it."""
+    cfg = srm_synth.tiny_config(vocab=260, d_model=1024, n_layers=2, n_heads=4, n_ctx=8, weight_dtype="bf16", seed=93)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    N, P = 16300, 2
+    toks = to_dev(srm_synth.make_prompts(cfg, batch=N, length=P))
+
+    def run():
+        st, tk = model.new_state(N), torch.empty(N, dtype=torch.int32, device="cuda")
+        lg, ws = torch.empty((N, cfg.vocab), device="cuda"), model.new_workspace(N * P)
+        ws.random_(0, 256)
+        if ragged:
+            model.prefill_ragged(toks.reshape(-1), np.arange(0, N * P + 1, P, dtype=np.int32), st, tk, logits=lg, workspace=ws)
+        else:
+            model.prefill(toks, 1, st, tk, logits=lg, workspace=ws)
+        torch.cuda.synchronize()
+        return st, lg
+
+    print(f"last rows, ragged={ragged}", flush=True)
+    one, again = run(), run()
+    assert kernel_launches("last_rows_kernel", run) > 0
+    assert all(torch.equal(a, b) for a, b in zip(one, again))
+    monkeypatch.setenv(SWITCH, "0")
+    many = run()
+    assert not torch.equal(one[1], many[1])
+    assert (one[0] - many[0]).abs().max() <= 2e-2 * many[0].abs().max()
+    assert rel_err_rows(one[1].cpu().numpy(), many[1].cpu().numpy()) <= 2e-2
+    model.close()
