@@ -226,7 +226,10 @@ size_t srm_state_bytes(const srm_model *m, int64_t batch);
  * independent - so the number of resident sequences is bounded by the state,
  * not by the workspace.  Results do not depend on the slicing in fp32 models; in
  * bf16 models a slice takes the kernels of its size, which may sum in another
- * order.
+ * order.  So do passes of prefill and sequence form in bf16 models whose
+ * LayerNorm the projections make (some ten thousand rows of a pass, see
+ * SRM_LN_ON_LOAD) and shorter ones of the same call; all other passes of a call
+ * have the same bits however it is cut.
  * Of a few rows it covers what a step as one kernel exchanges
  * (SRM_ONE_KERNEL_STEP above), which is more than the arrays of the rows; a
  * workspace short of that alone is accepted and takes the step kernels.
