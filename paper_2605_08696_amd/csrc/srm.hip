@@ -1164,13 +1164,30 @@ static bool last_rows_ok(const srm_model *m, int64_t N, int64_t rows, int64_t sh
 template <typename T>
 static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr, int64_t rows, hipStream_t st);
 
+// Streams whose kernels may use every CU: on one that keeps off some, work-groups that wait for others may find no room for those,
+// whatever they wait for (0.5 us to ask).
+// (where a question is refused the kernels without waits do the work, and its error must not be taken for one of theirs)
+static bool refused(hipError_t e) { return e != hipSuccess && ((void)hipGetLastError(), true); }
+// The default stream by its null name: hipExtStreamGetCUMask reads through the other one, hipStreamLegacy, as through a pointer.
+static hipStream_t few_stream(hipStream_t st) { return st == hipStreamLegacy ? nullptr : st; }
+static bool whole_device_stream(hipStream_t st)
+{
+    uint32_t mask[32] = {};
+    if (refused(hipExtStreamGetCUMask(few_stream(st), 32, mask))) return false;
+    int cus = 0;
+    for (const uint32_t bits : mask) cus += __builtin_popcount(bits);
+    return cus >= device_cus();
+}
+
 // Many rows of a bf16 model: the projections that add to the residual stream also make the LayerNorm behind them
 // (EPI_RESID_LN), where both take the 256x256 persistent tile and a row is whole tiles of it, at most kLnTiles.  us, LayerNorm
 // launches | this: decode step of the large model 13001 rows 5946 | 5763, 16384: 6727 | 6462, prefill 256 x 128 10946 | 10534, d = 512, state in
 // 16 bits, 30001 rows 2976 | 2825; a projection of 16384 x 1024 and its LayerNorm 80.5 + 18.2 | 92.9.  (Smaller launches, in tiles of
 // one round, stay as they are: up to 12 288 rows the LayerNorm launches read the next matrices ahead, worth 3 % at 3001 rows.)
-// SRM_LN_ON_LOAD=0 in the environment keeps the LayerNorm launches.
-static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows)
+// SRM_LN_ON_LOAD=0 in the environment keeps the LayerNorm launches, and so does a stream whose CU mask leaves out some CUs: the tiles of a
+// row are not worked on at the same time there, and each waits in vain (16384 rows, us per step of 192 | 128 | 64 CUs: 14485 |
+// 13906 | 26490, with LayerNorm launches 10239 | 10561 | 19267).
+static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows, hipStream_t st)
 {
     if (m->wsize != 2 || m->noproj || m->d % 256 || m->d / 256 > kLnTiles || rows <= 0 || rows >= (1 << 30)) return false;
     if ((int64_t)2 * m->L * cdiv(rows, 256) > 64 + rows) return false;           // (the words lie in w.slow)
@@ -1179,7 +1196,7 @@ static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows)
             choose_tile(rows, m->d, K, 64) != 0 || !persist_ok(rows, m->d, K) || K % 64)
             return false;
     const char *e = getenv("SRM_LN_ON_LOAD");
-    return !(e && e[0] == '0');
+    return !(e && e[0] == '0') && whole_device_stream(st);
 }
 // x += A W^T + bias, out = LayerNorm(x); launch: its number among the `launches` of so many rows in the pass, of which the first clears
 // the words of all.  (The last rows of a prefill, which the last layer goes on with, count anew: the words lie by the row tiles.)
@@ -1285,7 +1302,7 @@ static int block(const srm_model *m, int l, Workspace &w, int64_t rows, int64_t 
         SRM_TRY(mix(l));
         SRM_TRY(keep_last());
     }
-    const bool fused_ln = resid_ln_ok(m, rows, call_rows);
+    const bool fused_ln = resid_ln_ok(m, rows, call_rows, st);
     const int fused_at = last.n ? 0 : 2 * l, fused_n = last.n ? 2 : 2 * m->L;
     if (fused_ln) {
         SRM_TRY(resid_ln(m, w, w.mx, y.w_out, y.b_out, rows, dm, y.ln2_g, y.ln2_b, fused_at, fused_n, st));
@@ -1539,20 +1556,11 @@ static bool few_off()
     const char *e = getenv("SRM_ONE_KERNEL_STEP");
     return e && e[0] == '0';
 }
-// The default stream by its null name: hipExtStreamGetCUMask reads through the other one, hipStreamLegacy, as through a pointer.
-static hipStream_t few_stream(hipStream_t st) { return st == hipStreamLegacy ? nullptr : st; }
 static bool one_kernel_stream(hipStream_t st)
 {
-    // (where a question is refused the step kernels do the work, and its error must not be taken for one of theirs)
-    auto refused = [](hipError_t e) { return e != hipSuccess && ((void)hipGetLastError(), true); };
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (refused(hipStreamIsCapturing(st, &cs)) || cs != hipStreamCaptureStatusNone) return false;
-    // a stream that keeps off some CUs may have no room for all work-groups at once, whatever it waits for (0.5 us to ask)
-    uint32_t mask[32] = {};
-    if (refused(hipExtStreamGetCUMask(st, 32, mask))) return false;
-    int cus = 0;
-    for (const uint32_t bits : mask) cus += __builtin_popcount(bits);
-    return cus >= device_cus();
+    return whole_device_stream(st);
 }
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {

@@ -75,6 +75,49 @@ def test_decode_with_the_layernorm_in_the_residual_epilogue(srm, orc_mod, d, B, 
     model.close()
 
 
+def test_streams_with_a_cu_mask_and_captured_ones(srm, monkeypatch):
+    """On a stream that keeps off some CUs the tiles of a row may not run side by side, so the LayerNorm launches stay; a captured
+    step makes the LayerNorm in the epilogue as an eager one does, in every replay."""
+    import ctypes
+    cfg = srm_synth.tiny_config(vocab=260, d_model=1024, n_layers=2, n_heads=4, n_ctx=8, weight_dtype="bf16", seed=94)
+    model, B = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 13000
+    tok, ws = to_dev((np.arange(B) % cfg.vocab).astype(np.int32)), model.new_workspace(B)
+    state, out, lg = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, cfg.vocab), device="cuda")
+
+    def step(stream=None):
+        state.zero_()
+        torch.cuda.synchronize()
+        model.decode_step(B, 1, tok, state, out, logits=lg, workspace=ws, stream=stream)
+        torch.cuda.synchronize()
+        return out.clone(), state.clone(), lg.clone()
+
+    one = step()
+    monkeypatch.setenv(SWITCH, "0")
+    many = step()
+    monkeypatch.delenv(SWITCH)
+    assert not torch.equal(one[2], many[2])
+    hip = ctypes.CDLL("libamdhip64.so")
+    handle, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(*[0xffffffff] * 4)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+    print("many rows on a stream of 128 CUs", flush=True)
+    got = step(torch.cuda.ExternalStream(handle.value))
+    assert hip.hipStreamDestroy(handle) == 0
+    assert all(torch.equal(a, b) for a, b in zip(got, many))
+
+    print("many rows, captured", flush=True)
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        model.decode_step(B, 1, tok, state, out, logits=lg, workspace=ws, stream=stream)
+    for _ in range(3):
+        for x in (state, out, lg):
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((out, state, lg), one))
+        assert all(torch.equal(a, b) for a, b in zip(step(), one))
+    model.close()
+
+
 def test_prefill_and_sequence_form_with_the_layernorm_in_the_residual_epilogue(srm, monkeypatch):
     """Prompts in one pass and in several, and the sequence form, against the LayerNorm launches."""
     cfg = srm_synth.tiny_config(vocab=260, d_model=1024, n_layers=3, n_heads=4, n_ctx=70, weight_dtype="bf16", seed=92)
