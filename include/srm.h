@@ -289,8 +289,9 @@ int srm_decode_step_sampled(srm_model *m, int64_t B, int32_t pos, const int32_t 
  * captured into a HIP graph on the first call and replayed G - 1 times; the
  * graph is cached in the model and reused while B and the four device pointers
  * stay the same.  On the legacy default stream (NULL), which cannot be
- * captured, and where the layers of a step run as one kernel (see
- * SRM_ONE_KERNEL_STEP above), the steps are launched one by one instead.  temperature = 0 is
+ * captured, and where the layers of a step, or of a slice that the workspace
+ * cuts it into, run as one kernel (see SRM_ONE_KERNEL_STEP above), the steps are
+ * launched one by one instead.  temperature = 0 is
  * greedy; temperature > 0 samples as srm_decode_step_sampled does.  Results are
  * identical to G srm_decode_step(_sampled) calls, except where this call runs
  * all G steps in one launch or those calls run as one kernel each (see

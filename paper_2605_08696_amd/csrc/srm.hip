@@ -1692,12 +1692,15 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
     const TokenStore ts{d_tokens_out, ctr + 1, B};
     hipLaunchKernelGGL(counters_set_kernel, dim3(1), dim3(1), 0, st, ctr, pos0, 0);
     HIP_TRY(hipGetLastError());
+    // Where the layers of a step, or of some slice of it, run as one kernel, all steps are launched one by one: a captured step would
+    // take the step kernels, with their sums.
+    const int64_t rpp = decode_rows_per_pass(m, B, ws_bytes);
+    const bool stacked = stack_ok(m, rpp, ws_bytes, st) || (B % rpp && stack_ok(m, B % rpp, ws_bytes, st));
     // first step eagerly (it also performs every one-time kernel attribute set-up)
     SRM_TRY(generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p, d_logits,
                           d_pos, eos_plus1, false));
     if (G == 1) return SRM_OK;
-    // The legacy default stream cannot be captured: loop eagerly there; and so the steps whose layers are one kernel.
-    if (st == nullptr || (decode_rows_per_pass(m, B, ws_bytes) == B && stack_ok(m, B, ws_bytes, st))) {
+    if (st == nullptr || stacked) {                  // (the legacy default stream cannot be captured either)
         for (int g = 1; g < G; ++g)
             SRM_TRY(generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p,
                                   d_logits, d_pos, eos_plus1, true));

@@ -165,6 +165,29 @@ def test_generation_and_slices(srm):
     model.close()
 
 
+@pytest.mark.parametrize("B,rows", [(600, 256), (258, 256), (3080, 3072), (3075, 256)])
+def test_generation_in_slices(srm, B, rows):
+    """srm_generate through a workspace of fewer rows: every step by the kernels of its slices, the last of which may be too small or
+    the only one small enough for the kernel of all layers, as single steps through that workspace take them, on every stream."""
+    cfg = _config(vocab=400, n_ctx=40)
+    model, G = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 4
+    start = to_dev((np.arange(B) * 7 % cfg.vocab).astype(np.int32))
+    n = model.workspace_bytes(rows) + 256                              # (the step counters)
+    stacks = sum(5 <= min(rows, B - b) <= 3072 for b in range(0, B, rows))
+    st, tk, steps = model.new_state(B), start.clone(), []
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    for g in range(G):
+        model.decode_step(B, 3 + g, tk, st, tk, workspace=ws, temperature=0.7, seed=9)
+        steps.append(tk.clone())
+    for stream in (None, torch.cuda.Stream()):
+        st2, tk, out = model.new_state(B), start.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        print(f"generation of {B} samples through {rows} rows", flush=True)
+        assert _launches(lambda: model.generate(B, 3, G, tk, st2, out, workspace=ws, temperature=0.7, seed=9, stream=stream)) == G * stacks
+        assert torch.equal(out, torch.stack(steps)) and torch.equal(st2, st) and torch.equal(tk, steps[-1])
+    model.close()
+
+
 def test_a_wait_that_gives_up_leaves_marked_tokens(srm, monkeypatch):
     """The bound of the waits behind the arrival, set so short from the host that some give up at once: every wavefront ends,
     the tokens are -1 (behind a nucleus pass too), and the next call is right."""
