@@ -84,7 +84,7 @@
  *                        one-kernel path of srm_generate (see there): should one
  *                        give up, the tokens of the call are -1 and its state is
  *                        undefined (SRM_ONE_KERNEL_POLLS=n, for tests: that bound
- *                        in polls).
+ *                        in polls; =n:g in step g of a generate call alone).
  *                        The step kernels, with fp32 sums in another order, take
  *                        such steps in all other calls: on a stream that is being
  *                        captured, in srm_decode_step_ragged and
@@ -299,10 +299,12 @@ int srm_decode_step_sampled(srm_model *m, int64_t B, int32_t pos, const int32_t 
  * in another order: equal up to that rounding, token-exact unless two scores tie
  * within it.  A call that runs in one launch must not be made under stream
  * capture.
- * The one-kernel path synchronises its work-groups with bounded waits; should a
+ * The one-kernel path synchronises its work-groups with bounded waits, and so do
+ * steps whose layers run as one kernel; should a
  * wait ever give up (a work-group that is not resident: never observed), the
  * kernel ends early, d_tok and the rows of d_tokens_out from that step on hold
- * -1, the state is undefined and the call has already returned SRM_OK (it is
+ * -1 (of a step in slices: from that slice on; srm_generate_ragged leaves the
+ * positions where they are), the state is undefined and the call has already returned SRM_OK (it is
  * asynchronous): a caller that cannot rule this out checks d_tokens_out for -1
  * after synchronising.  Not thread-safe per model.
  * Errors: SRM_EINVAL (null pointer, B or G <= 0, pos0 + G > n_ctx), SRM_ENOMEM

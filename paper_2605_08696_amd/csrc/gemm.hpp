@@ -1102,7 +1102,7 @@ struct FinalizeRagged {
     int32_t *pos_set;         // prefill: pos_set[destination] = length of the sequence
     int32_t *zero_counter;    // set to 0 (the row list of the nucleus pass that follows)
     int32_t eos_plus1;        // decode with advance: eos token + 1 (0: none); a row that emits it goes idle (position -1)
-    const unsigned *dead;     // decode: not zero where the kernel of the layers has given up -> tokens -1
+    const unsigned *dead;     // decode: not zero where a kernel of all layers has given up, in this step or earlier in the call -> tokens -1
 };
 
 // Reduce the per-tile partials [nparts][rows] of each row to one token; writes `rep`

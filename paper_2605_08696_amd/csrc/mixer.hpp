@@ -665,9 +665,9 @@ mixer_parallel_kernel(const TAct *__restrict__ U, TAct *__restrict__ Y,
 }
 
 // Step counters of a multi-step generate call, kept in device memory so that the
-// captured step needs no host-side update: ctr[0] = position, ctr[1] = step.  (Every step after the
+// captured step needs no host-side update: ctr[0] = position, ctr[1] = step; ctr[2]: a wait has given up.  (Every step after the
 // first advances them in its first kernel, the embedding LayerNorm.)
-__global__ void counters_set_kernel(int *ctr, int pos, int step) { ctr[0] = pos; ctr[1] = step; }
+__global__ void counters_set_kernel(int *ctr, int pos, int step) { ctr[0] = pos; ctr[1] = step; ctr[2] = 0; }
 
 // Row b of x' and y': the last row of sequence b, source row seq_end[b + 1] - 1 - base (or (b + 1) len - 1 without seq_end),
 // clamped to [0, src_rows).  d and dm are multiples of 4.  One work-group per row: a trip to memory for the boundary, one for

@@ -1198,6 +1198,12 @@ static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows, hip
     const char *e = getenv("SRM_LN_ON_LOAD");
     return !(e && e[0] == '0') && whole_device_stream(st);
 }
+// SRM_ONE_KERNEL_POLLS in the environment, for tests: a bound of waits, in all launches or ("n:g") in step g of a generate call alone
+static unsigned poll_bound(unsigned otherwise, int step = 0)
+{
+    const char *e = getenv("SRM_ONE_KERNEL_POLLS"), *at = e ? strchr(e, ':') : nullptr;
+    return e && (!at || atoi(at + 1) == step) ? (unsigned)std::max(0, atoi(e)) : otherwise;
+}
 // x += A W^T + bias, out = LayerNorm(x); launch: its number among the `launches` of so many rows in the pass, of which the first clears
 // the words of all.  (The last rows of a prefill, which the last layer goes on with, count anew: the words lie by the row tiles.)
 constexpr unsigned kLnPolls = 1u << 9;               // some 200 us: the tiles of a row come within a few
@@ -1215,8 +1221,7 @@ static int resid_ln(const srm_model *m, Workspace &w, const void *A, const void 
     ep.ln_out = w.a;
     ep.ln_stats = static_cast<float2 *>(w.u);        // (nobody reads u behind the mixer)
     ep.ln_words = reinterpret_cast<unsigned *>(w.slow) + (size_t)launch * nbm;
-    const char *polls = getenv("SRM_ONE_KERNEL_POLLS");
-    ep.ln_polls = polls ? (unsigned)std::max(0, atoi(polls)) : kLnPolls;
+    ep.ln_polls = poll_bound(kLnPolls);
     ep.clk = g_clock_probe; ep.clk_blocks = g_clock_blocks;
     return launch_bf16_persist<EPI_RESID_LN, bf16>(static_cast<const bf16 *>(A), static_cast<const bf16 *>(W), (int)rows, m->d, K, ep, st);
 }
@@ -1362,6 +1367,8 @@ struct DecodeArgs {
     int eos_plus1 = 0;
     int *advance_ctr = nullptr;     // step counters of srm_generate, advanced by the first kernel of the step
     size_t ws_bytes = 0;
+    int step = 0;                   // of a generate call
+    unsigned *gave_up = nullptr;    // ... whose steps may be kernels of all layers: not zero behind a wait that has given up
 };
 static bool stack_ok(const srm_model *m, int64_t rows, size_t ws_bytes, hipStream_t st);
 static int stack_layers(srm_model *m, const DecodeArgs &a, const Workspace &w, int64_t b0, int64_t nb, hipStream_t st, const unsigned **dead);
@@ -1377,7 +1384,7 @@ static int decode_rows(srm_model *m, const DecodeArgs &a, int64_t b0, int64_t nb
                                    (size_t)b0 * dm * m->ssize);
     };
     const bool stacked = sizeof(T) == 2 && stack_ok(m, nb, a.ws_bytes, st);
-    const unsigned *dead = nullptr;
+    const unsigned *dead = a.gave_up;
     if (stacked) SRM_TRY(stack_layers(m, a, w, b0, nb, st, &dead));
     else SRM_TRY((layernorm<T, true>(m, nullptr, 0, a.tok_in + b0, w.x, m->layers[0].ln1_g, m->layers[0].ln1_b, w.a, nb,
                                      st, nullptr, 0, 0, nullptr, 0, nullptr, b0 == 0 ? a.advance_ctr : nullptr,
@@ -1647,12 +1654,14 @@ static int mega_generate(srm_model *m, int B, int pos0, int G, int32_t *tok, voi
 // ------------------------------------------------------------------ generate (G steps in one call)
 static int generate_step(srm_model *m, int64_t B, int32_t *tok, void *state, void *ws, size_t ws_bytes, int *ctr,
                          TokenStore ts, hipStream_t st, float temperature, uint32_t seed, float top_p, float *logits,
-                         int32_t *pos_rows, int eos_plus1, bool advance_first)
+                         int32_t *pos_rows, int eos_plus1, int step, bool stacked)
 {
     // uniform position: read from the device counter; ragged: one position per sample, advanced on the device.
     // Every step but the first of a call advances the counters in its first kernel.
-    const DecodeArgs a{B, 0, pos_rows ? nullptr : ctr, pos_rows, pos_rows ? 1 : 0, tok, state, tok, logits, nullptr, ts,
-                       temperature, seed, top_p, eos_plus1, advance_first ? ctr : nullptr};
+    DecodeArgs a{B, 0, pos_rows ? nullptr : ctr, pos_rows, pos_rows ? 1 : 0, tok, state, tok, logits, nullptr, ts,
+                 temperature, seed, top_p, eos_plus1, step ? ctr : nullptr};
+    a.step = step;
+    if (stacked) a.gave_up = reinterpret_cast<unsigned *>(ctr + 2);
     return decode_batch(m, a, ws, ws_bytes, st);
 }
 
@@ -1698,12 +1707,12 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
     const bool stacked = stack_ok(m, rpp, ws_bytes, st) || (B % rpp && stack_ok(m, B % rpp, ws_bytes, st));
     // first step eagerly (it also performs every one-time kernel attribute set-up)
     SRM_TRY(generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p, d_logits,
-                          d_pos, eos_plus1, false));
+                          d_pos, eos_plus1, 0, stacked));
     if (G == 1) return SRM_OK;
     if (st == nullptr || stacked) {                  // (the legacy default stream cannot be captured either)
         for (int g = 1; g < G; ++g)
             SRM_TRY(generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p,
-                                  d_logits, d_pos, eos_plus1, true));
+                                  d_logits, d_pos, eos_plus1, g, stacked));
         return SRM_OK;
     }
     const bool hit = m->gexec && m->gkey.B == B && m->gkey.tok == d_tok && m->gkey.state == d_state &&
@@ -1715,7 +1724,7 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
         const int rc = generate_step(m, B, d_tok, d_state, d_workspace, ws_bytes, ctr, ts, st, temperature, seed, top_p,
-                                     d_logits, d_pos, eos_plus1, true);
+                                     d_logits, d_pos, eos_plus1, 1, false);
         const hipError_t e = hipStreamEndCapture(st, &graph);
         if (rc != SRM_OK) { if (graph) (void)hipGraphDestroy(graph); return rc; }
         if (e != hipSuccess) return fail(SRM_EHIP, "srm_generate: stream capture failed: %s", hipGetErrorString(e));
@@ -2562,15 +2571,14 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     a.pw = a.gw + rows * (m->wsize == 2 ? m->ff / 2 : m->ff);
     few_word *const here = a.pw + (size_t)mb * nb * 2;           // (of groups, see few_rows_kernel)
     a.flag = reinterpret_cast<unsigned *>(here + (gmb ? nb : 0));
-    a.max_polls = 1u << 21;                          // a second or two
+    a.max_polls = poll_bound(1u << 21);              // a second or two
     a.arrive_polls = few_arrive_polls;
     int withdrawn = -1;                              // the last work-group's arrival
-    const char *sw = getenv("SRM_ONE_KERNEL_STEP"), *polls = getenv("SRM_ONE_KERNEL_POLLS");
+    const char *sw = getenv("SRM_ONE_KERNEL_STEP");
     if (sw && sw[0] == '2')
         withdrawn = gmb ? (int)((reinterpret_cast<unsigned char *>(here) - base) / 16) + nb / 2 - 1
                         : (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
-    if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
     const int n = (int)((gmb ? few_group_words_bytes(m, B, mb) : few_words_bytes(m, B)) / 16), n_store = store ? (int)B * G : 0;
     hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
                        reinterpret_cast<u32x4_t *>(base), n, withdrawn, static_cast<int *>(ws), store, n_store);
@@ -2679,15 +2687,15 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     a.hidden = d.hidden ? d.hidden + (size_t)b0 * m->d : nullptr;
     a.here = reinterpret_cast<few_word *>(mem.words);
     a.count = reinterpret_cast<unsigned *>(mem.words + kStackBlocks * 8);
-    a.dead = reinterpret_cast<unsigned *>(mem.words + kStackBlocks * 8 + kStackGroups * 128);
-    a.max_polls = 1u << 21;                          // a second or two
+    a.left = reinterpret_cast<unsigned *>(mem.words + kStackBlocks * 8 + kStackGroups * 128);
+    a.dead = d.gave_up ? d.gave_up : a.left + 1;     // (that of a call stays set)
+    a.max_polls = poll_bound(1u << 21, d.step);      // a second or two
     a.arrive_polls = stack_arrive_polls;
     const int others = few_others(m->device, st), blocks = kStackBlocks / (others == 0 ? 1 : others == 1 ? 2 : 4);
     int withdrawn = -1;                              // the arrival of one of the last work-groups
-    const char *sw = getenv("SRM_ONE_KERNEL_STEP"), *polls = getenv("SRM_ONE_KERNEL_POLLS");
+    const char *sw = getenv("SRM_ONE_KERNEL_STEP");
     if (sw && sw[0] == '2') withdrawn = blocks * 8 / 16 - 1;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
-    if (polls) a.max_polls = (unsigned)std::max(0, atoi(polls));
     *dead = a.dead;
     auto begin = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(nb, 4)), dim3(256), 0, st, d.tok_in + b0, static_cast<const bf16 *>(m->embed),

@@ -60,7 +60,8 @@ struct StackArgs {
     float *hidden;                                   // [rows][D] or null
     few_word *here;                                  // [kStackBlocks] arrivals
     unsigned *count;                                 // [kStackGroups] 128 bytes apart
-    unsigned *dead;                                  // a wait has given up; [1]: work-groups that have left without arriving all
+    unsigned *dead;                                  // a wait has given up (in this launch, or since the call began)
+    unsigned *left;                                  // work-groups that have left without arriving all
     unsigned max_polls, arrive_polls;
 };
 
@@ -162,7 +163,7 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
     const bool alone = !__builtin_amdgcn_readfirstlane(who[0]);
     if (__builtin_expect(alone, 0)) {
         if (tid == 0)
-            who[5] = __hip_atomic_fetch_add(p.dead + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+            who[5] = __hip_atomic_fetch_add(p.left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
         __syncthreads();
         if (!who[5]) return;
     }

@@ -214,6 +214,52 @@ def test_a_wait_that_gives_up_leaves_marked_tokens(srm, monkeypatch):
     model.close()
 
 
+@pytest.mark.parametrize("how", [dict(), dict(temperature=0.7, seed=3), dict(temperature=0.7, top_p=0.6, seed=3)])
+@pytest.mark.parametrize("rows", [400, 256])
+def test_a_generation_whose_wait_gives_up(srm, rows, how, monkeypatch):
+    """A wait that gives up in one step of a generation only, forced from the host: the tokens from that step on are -1, also where
+    the waits of later steps hold, in every slice behind it; the steps in front are right, and so is the next call."""
+    cfg = _config(vocab=300, n_ctx=30)
+    model, B, G, at = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 400, 5, 2
+    ws = torch.empty(model.workspace_bytes(rows) + 256, dtype=torch.uint8, device="cuda")
+    lg = torch.empty((B, cfg.vocab), device="cuda") if "top_p" in how else None
+    start = to_dev((np.arange(B) * 7 % cfg.vocab).astype(np.int32))
+    idle = torch.arange(B, device="cuda") % 7 == 3
+    pos0 = torch.where(idle, -1, torch.arange(B, device="cuda") % 11).to(torch.int32)
+
+    def plain():
+        st, tk, out = model.new_state(B), start.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        model.generate(B, 3, G, tk, st, out, workspace=ws, logits=lg, **how)
+        torch.cuda.synchronize()
+        return out, tk, st
+
+    def ragged():
+        st, tk, out, pos = model.new_state(B), start.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda"), pos0.clone()
+        model.generate_ragged(B, G, pos, tk, st, out, workspace=ws, logits=lg, **how)
+        torch.cuda.synchronize()
+        return out, tk, st, pos
+
+    for run in (plain, ragged):
+        want = run()
+        active = torch.ones_like(idle) if run is plain else ~idle
+        assert (want[0][:, active] >= 0).all()
+        print(f"generation, a wait gives up in step {at}: {rows} rows {how} {run.__name__}", flush=True)
+        for bound in (f"0:{at}", "0"):
+            monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", bound)
+            got = run()
+            monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+            first = at if ":" in bound else 0
+            assert torch.equal(got[0][:first], want[0][:first])
+            assert (got[0][first + 1:] == -1).all() and (got[1] == -1).all()
+            mid = got[0][first]                      # (a slice in front of the one that gives up has its tokens)
+            assert ((mid == -1) | (mid == want[0][first])).all() and (mid[256 if rows == 256 else 0:] == -1).all()
+            if run is ragged:
+                there = pos0 + first + ((mid != -1) & active).int()
+                assert torch.equal(got[3], torch.where(active, there, pos0))
+        assert all(torch.equal(a, b) for a, b in zip(run(), want))
+    model.close()
+
+
 @pytest.mark.parametrize("B", [37, 300, 513, 1100])
 def test_streams_in_turn_give_the_same_bits(srm, B):
     """Steps launched on two streams in turn take a quarter of the work-groups each, so that several fit the device side by
