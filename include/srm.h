@@ -100,8 +100,10 @@
  *                        d_model 512 with projections, mlp_expansion 4, one
  *                        matrix per head and at least six layers run their
  *                        layers as one kernel in the same way: it takes the
- *                        whole device, or half or a quarter of it where streams
- *                        launch such steps in turn; its wait for the others
+ *                        whole device, or half or a quarter of it where such
+ *                        steps of other streams are running or waiting (several
+ *                        streams of some hundred samples each get more done
+ *                        with =0); its wait for the others
  *                        is some 30 ms, one work-group alone takes 5 to 90 ms
  *                        per step.  Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
  *                        SRM_LN_ON_LOAD set, whose kernels it replaces.

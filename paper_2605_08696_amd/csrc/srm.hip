@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -2448,21 +2449,34 @@ static int gather_last_rows(const srm_model *m, Workspace &w, const LastRows &lr
 // d = 1024, 1 row 198 | 200 | 200 | 199, 198 | 123 | 124 | 128, 348 | 209 | 127 | 164; 4 rows 289 | 291 | 290 | 291, 288 | 168 | 171 |
 // 177, 354 | 213 | 130 | 131: there the step kernels are the better ones from four streams on.
 struct FewShare { hipEvent_t ev; hipStream_t st; unsigned long long used; };         // st: only a preference
-struct FewDevice { FewShare share[kFewShares]; hipEvent_t own[kFewShares]; };        // events are kept until the process ends
+// events are kept until the process ends; met: the latest launch that found one of another stream
+struct FewDevice { FewShare share[kFewShares]; hipEvent_t events[kFewShares]; unsigned long long met; };
 static std::mutex few_lock;
 static FewDevice few_devices[kFewDevices];
 static unsigned long long few_launches;
-// How many other streams have been launching kernels of this kind in turn with this one: in the latest few launches.
+// How many other streams have a kernel of this kind running or waiting (0.3 us for each; none to ask where one stream launches
+// them).  None has at the moment, but one had in the latest few launches: one, which is between two steps.  Streams that launch
+// in turn, each behind a wait for the other, never meet.
 static int few_others(int device, hipStream_t st)
 {
     const std::lock_guard<std::mutex> hold(few_lock);
-    const FewShare *const s = few_devices[device].share;
+    FewDevice &d = few_devices[device];
+    hipStream_t seen[kFewShares];
     int n = 0;
-    for (int i = 0; i < kFewShares; ++i) {
-        bool counts = s[i].used && s[i].st != st && few_launches - s[i].used < kFewShares;
-        for (int k = 0; k < i; ++k) counts = counts && s[k].st != s[i].st;
-        n += counts;
+    bool recent = false;
+    for (const FewShare &s : d.share) {
+        if (!s.used || s.st == st || std::find(seen, seen + n, s.st) != seen + n) continue;
+        recent = recent || few_launches - s.used < kFewShares;
+        // (the question belongs to no capture that this thread has begun)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (refused(hipThreadExchangeStreamCaptureMode(&mode))) continue;
+        const hipError_t e = hipEventQuery(s.ev);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e == hipErrorNotReady) seen[n++] = s.st;
+        else (void)refused(e);
     }
+    if (n) d.met = few_launches + 1;
+    else if (recent && d.met && few_launches + 1 - d.met < kFewShares) return 1;
     return n;
 }
 static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st)
@@ -2483,8 +2497,16 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
     };
     for (int i = need; i < all; i += need)
         if (rank(i) < rank(at)) at = i;
-    hipEvent_t &ev = d.own[at];
-    if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    // an event that no other share's kernel is known by (there are as many events as shares)
+    auto others_have = [&](hipEvent_t e) {
+        for (int k = 0; k < kFewShares; ++k)
+            if ((k < at || k >= at + need) && d.share[k].used && d.share[k].ev == e) return true;
+        return false;
+    };
+    hipEvent_t *own = d.events;
+    while (*own && others_have(*own)) ++own;
+    if (!*own) HIP_TRY(hipEventCreateWithFlags(own, hipEventDisableTiming));
+    const hipEvent_t ev = *own;
     hipEvent_t waited = nullptr;
     for (int k = at; k < at + need; ++k) {
         const hipEvent_t before = d.share[k].ev;
@@ -2530,7 +2552,7 @@ static const void *few_kernel(int mb)
 // that way).  Every XCD reads all weights, at 0.95 TB/s; what is left beside that is the exchanges, some 1 us each.  Generation with the
 // toy model (d = 256, 4 layers, 4096 tokens), us per token, 64 work-groups over all XCDs (from 9 rows on step kernels) | groups: 1 row
 // 31.5 | 26.2, 2: 32.9 | 26.2, 4: 38.1 | 29.4, 8: 52.7 | 30.3, 9: 84 | 33, 16: 86 | 34, 17: 92 | 37, 32: 97 | 38.  Up to 8 rows both have the
-// same bits, and where other streams launch such steps in turn the small grids, of which four fit the device, get more done
+// same bits, and where other streams launch such steps side by side the small grids, of which four fit the device, get more done
 // (8 rows, us per token of 1 | 2 | 4 streams: groups 30 | 30 | 30, small grids 52 | 27 | 14).  Single steps of more than 8 rows
 // keep the sums of the step kernels.
 static int few_group_rows(const srm_model *m, int64_t B, int64_t G, size_t ws_bytes)
@@ -2639,9 +2661,13 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
 // shorter (98).  A width of 512 is what the kernel's registers and LDS were laid out for; at 1024 every XCD would read 21 MB of
 // weights per layer, 22 us at the 0.95 TB/s an XCD gets, where a layer of 37 rows takes 25.  Six layers: as in few_ok, for the
 // results of shallower models.
-// Streams that launch such steps in turn take half or a quarter of the work-groups each (few_others), same bits.  us per step, no
-// logits, of 1 | 2 | 4 streams, all streams together: 37 rows 124 | 90 | 72, step kernels 178 | 94 | 60; 300: 171 | 142 | 137, 230 | 132 |
-// 135; 1024: 242 | 217 | 200, 307 | 219 | 210 (always the whole device: 37 rows 118 | 149 | 156).
+// Streams that launch such steps side by side take half or a quarter of the work-groups each (few_others), same bits.  us per step, no
+// logits, all streams together, of 1 | 2 | 4 streams, a thread each: 37 rows 119 | 91 | 137, step kernels 178 | 99 | 99; 300: 169 | 145 |
+// 119, 231 | 132 | 92; 1024: 235 | 213 | 190, 300 | 215 | 205.  In turn, each behind a wait for the one before: 37 rows 136 | 137 | 136
+// (by half and by a quarter 186 | 284), 300: 186 | 185 | 184 (271 | 438), 1024: 250 | 250 | 250 (370 | 609).
+// Beside other work of the process (300 rows, us per step and calls per second of the other stream, step kernels | this; large model):
+// prefills of 256 x 128 3666 and 93 | 554 and 67; decode steps of 16384 samples 3065 and 149 | 555 and 106; of 3001 with top-p 594
+// and 437 | 235 and 171; no arrival was given up (longest step 1.5 ms).
 constexpr int64_t kStackMinRows = 5, kStackMaxRows = 3072;
 static_assert(kStackMaxRows <= (int64_t)kStackGroups * kStackMaxPer, "their positions are kept in LDS");
 // Polls of the arrival, some 30 ms: about what one work-group alone takes (ms per step: 37 rows 5, 300: 22, 1024: 33, 3000: 87).

@@ -34,7 +34,7 @@
 // All work-groups must be resident at once: the arrival and its way out are those of few.hpp.  The words of the arrival carry the XCD,
 // from which the groups are formed; a work-group that is left alone does all parts of all groups' phases in turn, with the same
 // tiles and sums.  So does, with four parts to a member, a launch of a quarter of the work-groups, of which four fit the device side
-// by side: for streams that launch such steps in turn (stack_layers in srm.hip).
+// by side: for streams that launch such steps side by side (few_others in srm.hip).
 #pragma once
 #include "few.hpp"
 

@@ -1,4 +1,7 @@
 """Shared helpers of the GPU parity tests (no method arithmetic here)."""
+import json
+import os
+import tempfile
 import time
 
 import numpy as np
@@ -28,8 +31,8 @@ def check_tokens(got, ref_tokens, ref_margin, ref_logits_absmax, rtol=1e-4):
     return int((bad & tie).sum())
 
 
-def kernel_events(name, fn):
-    """The profiler's events of kernels whose names hold `name`, of fn().  The profiler drops kernels whose times,
+def _profile(fn):
+    """The profiler over fn().  It drops kernels whose times,
     converted from the GPU's clock to the host's, lie outside its window, and behind a long wait on the host they may be
     off by more than a few steps take: so the window has a margin on both sides, whose own kernels show that none of fn's
     is lost."""
@@ -47,7 +50,24 @@ def kernel_events(name, fn):
         mark()
         time.sleep(0.05)
     assert sum("erfinv" in e.name for e in prof.events()) == 2, "the profiler has lost kernels"
-    return [e for e in prof.events() if name in e.name]
+    return prof
+
+
+def kernel_events(name, fn):
+    """The profiler's events of kernels whose names hold `name`, of fn()."""
+    return [e for e in _profile(fn).events() if name in e.name]
+
+
+def kernel_grids(name, fn):
+    """The work-groups of each launch of such kernels in fn(), in the order in which they started."""
+    prof = _profile(fn)
+    with tempfile.TemporaryDirectory() as tmp:
+        path = os.path.join(tmp, "trace.json")
+        prof.export_chrome_trace(path)
+        with open(path) as f:
+            events = json.load(f)["traceEvents"]
+    found = sorted((e["ts"], e["args"]["grid"][0]) for e in events if e.get("cat") == "kernel" and name in e["name"])
+    return [grid for _, grid in found]
 
 
 def kernel_launches(name, fn):

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import srm_synth
-from gpu_util import to_dev, rel_err_rows, kernel_launches
+from gpu_util import to_dev, rel_err_rows, kernel_launches, kernel_grids
 
 pytestmark = pytest.mark.gpu
 SWITCH = "SRM_ONE_KERNEL_STEP"
@@ -262,8 +262,7 @@ def test_a_generation_whose_wait_gives_up(srm, rows, how, monkeypatch):
 
 @pytest.mark.parametrize("B", [37, 300, 513, 1100])
 def test_streams_in_turn_give_the_same_bits(srm, B):
-    """Steps launched on two streams in turn take a quarter of the work-groups each, so that several fit the device side by
-    side; eight launches on one stream later it has the device for itself again."""
+    """Steps launched on two streams in turn, each behind a synchronisation, have the device for themselves."""
     cfg = _config(vocab=200)
     model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
     tok = to_dev((np.arange(B) * 3 % cfg.vocab).astype(np.int32))
@@ -282,7 +281,87 @@ def test_streams_in_turn_give_the_same_bits(srm, B):
         want = step(0)
     got = [step(i % 2) for i in range(6)]
     assert _launches(lambda: got.append(step(1))) == 1
+    assert kernel_grids("stack_kernel", lambda: got.extend(step(i % 2) for i in range(4))) == [256] * 4
     torch.cuda.synchronize()
     for one in got:
         assert all(torch.equal(a, b) for a, b in zip(one, want))
+    model.close()
+
+
+@pytest.mark.parametrize("n", [2, 4])
+@pytest.mark.parametrize("B", [9, 300, 513, 1100])
+def test_streams_side_by_side_share_the_device(srm, B, n, monkeypatch):
+    """Steps on several streams whose kernels are all still waiting: the first takes the device, a second stream half of the
+    work-groups, further ones a quarter, so that four fit side by side; the same bits, also by one work-group alone, and -1
+    where their waits give up."""
+    cfg = _config(vocab=200)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    tok = to_dev((np.arange(B) * 3 % cfg.vocab).astype(np.int32))
+    ws, streams = [model.new_workspace(B) for _ in range(n)], [torch.cuda.Stream() for _ in range(n)]
+    want = {}
+
+    def steps():
+        got = [(model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda"),
+                torch.empty((B, cfg.vocab), dtype=torch.float32, device="cuda")) for _ in range(n)]
+        torch.cuda.synchronize()
+        for s in streams:
+            with torch.cuda.stream(s):
+                torch.cuda._sleep(40_000_000)                          # some 20 ms: none has begun when the last is launched
+        for (st, out, lg), w, s in zip(got, ws, streams):
+            model.decode_step(B, 2, tok, st, out, logits=lg, workspace=w, stream=s)
+        torch.cuda.synchronize()
+        want["got"] = got
+
+    st, out, lg = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, cfg.vocab), device="cuda")
+    for _ in range(9):                                                 # (streams that have met are reckoned with for eight launches)
+        st.zero_()
+        torch.cuda.synchronize()
+        model.decode_step(B, 2, tok, st, out, logits=lg, workspace=ws[0], stream=streams[0])
+        torch.cuda.synchronize()
+    print(f"{n} streams side by side B={B}", flush=True)
+    assert sorted(kernel_grids("stack_kernel", steps)) == sorted([256, 128, 64, 64][:n])
+    for mode in (None, "2", "3"):
+        if mode:
+            monkeypatch.setenv(SWITCH, mode)
+            print(f"one work-group of each alone, mode {mode}", flush=True)
+            steps()
+            monkeypatch.delenv(SWITCH)
+        for one in want["got"]:
+            assert all(torch.equal(a, b) for a, b in zip(one, (st, out, lg)))
+    monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+    steps()
+    monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+    assert all((one[1] == -1).all() for one in want["got"])
+    steps()
+    for one in want["got"]:
+        assert all(torch.equal(a, b) for a, b in zip(one, (st, out, lg)))
+    model.close()
+
+
+def test_streams_side_by_side_beside_a_capture(srm):
+    """Steps on two streams while the same thread captures a graph on a third: the graph is whole, the steps are right."""
+    cfg, B = _config(vocab=200), 64
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    tok = to_dev((np.arange(B) * 3 % cfg.vocab).astype(np.int32))
+    ws, streams = [model.new_workspace(B) for _ in range(2)], [torch.cuda.Stream() for _ in range(2)]
+    sets = [[model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda")] for _ in range(5)]
+    x, cap, graph = torch.zeros(64, device="cuda"), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+
+    def step(i, k):
+        model.decode_step(B, 2, tok, sets[k][0], sets[k][1], workspace=ws[i], stream=streams[i])
+
+    step(0, 0)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=cap):
+        x.add_(1.0)
+        for k in range(1, 5):
+            step(k % 2, k)
+        x.add_(1.0)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert (x == 6.0).all()
+    for st, out in sets[1:]:
+        assert torch.equal(st, sets[0][0]) and torch.equal(out, sets[0][1])
     model.close()
