@@ -66,10 +66,11 @@
  *                        stream that is being captured or whose CU mask leaves
  *                        out some CUs.  Of such
  *                        kernels two of d_model 1024 or four others run at a time
- *                        per process and device (an fp32 one takes all of it
- *                        where one stream alone launches them: same bits); further ones wait for those
- *                        before them, whatever their streams (an event for each
- *                        is kept until the process ends).  (Many streams of 3 or 4
+ *                        per process and device (an fp32 one takes all of it, of
+ *                        up to 8 samples only where no such kernel of another
+ *                        stream runs or waits: same bits); further ones wait for
+ *                        those before them, whatever their streams (an event for
+ *                        each is kept until the process ends).  (Many streams of 3 or 4
  *                        samples each at d_model 1024 get more done with =0.)
  *                        Their work-groups start their work only once all of
  *                        them have started.  Where that does not come about within

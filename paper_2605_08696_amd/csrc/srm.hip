@@ -89,6 +89,7 @@ struct srm_model {
     MegaLayer *mega_layers;   // device copy of the layers' pointers for the one-kernel small-batch path, or null
     FewLayer *few_layers;     // ... and for the steps of few.hpp, or null,
     void *few_slab;           // which read matrices packed for them
+    unsigned char *few_words; // and, in groups of fp32 rows, exchange words here (see few_group_rows)
     const void *few_head;
     const void *embed, *head;
     const float *lnf_g, *lnf_b;
@@ -175,6 +176,7 @@ static int model_geometry(const char *who, const srm_config *cfg, srm_model *m)
     m->mega_layers = nullptr;
     m->few_layers = nullptr;
     m->few_slab = nullptr;
+    m->few_words = nullptr;
     m->few_head = nullptr;
     m->gexec = nullptr;
     m->gkey = {0, nullptr, nullptr, nullptr, nullptr, 0.0f, 0, 1.0f, nullptr, 0, nullptr, 0};
@@ -1473,8 +1475,8 @@ static int decode_batch(srm_model *m, DecodeArgs a, void *ws, size_t workspace_b
 
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st);
 static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
-                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, size_t ws_bytes, hipStream_t st);
-static int few_group_rows(const srm_model *m, int64_t B, int64_t G, size_t ws_bytes);
+                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st);
+static int few_group_rows(const srm_model *m, int64_t B, int64_t G);
 
 static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t pos, const int32_t *d_tok_in,
                               void *d_state, int32_t *d_tok_out, float *d_logits, float *d_hidden,
@@ -1492,7 +1494,7 @@ static int decode_step_common(const char *who, srm_model *m, int64_t B, int32_t 
     hipStream_t st = as_stream(hip_stream);
     if (few_ok(m, B, 1, workspace_bytes, st)) {
         SRM_TRY(few_run(m, B, pos, 1, d_tok_in, d_tok_out, nullptr, d_state, temperature, seed, d_logits, d_hidden,
-                        d_workspace, workspace_bytes, st));
+                        d_workspace, st));
         if (!(temperature > 0.0f && top_p < 1.0f)) return SRM_OK;
         return nucleus(d_logits, B, m->V, Sampling{temperature, seed, pos, nullptr, nullptr, top_p}, d_tok_out, nullptr, nullptr,
                        0, nullptr, static_cast<int *>(d_workspace), st);
@@ -1573,7 +1575,8 @@ static bool one_kernel_stream(hipStream_t st)
 static bool few_ok(const srm_model *m, int64_t B, int64_t G, size_t workspace_bytes, hipStream_t st)
 {
     if (!m->few_layers || (G > 1 && m->noproj) || G * m->L < 6 || few_off()) return false;
-    if (B > few_max_rows(m) ? !few_group_rows(m, B, G, workspace_bytes) : srm_workspace_bytes(m, B) > workspace_bytes) return false;
+    if (B > few_max_rows(m) ? !few_group_rows(m, B, G) || row_bytes(m, B) > workspace_bytes : srm_workspace_bytes(m, B) > workspace_bytes)
+        return false;
     return one_kernel_stream(few_stream(st));
 }
 
@@ -1691,8 +1694,7 @@ static int generate_common(srm_model *m, int64_t B, int32_t pos0, int32_t G, int
     SRM_TRY(check_device(m));
     hipStream_t st = as_stream(hip_stream);
     if (!topp && !d_pos && !eos_plus1 && !getenv("SRM_MEGAKERNEL") && few_ok(m, B, G, ws_bytes, st))
-        return few_run(m, B, pos0, G, d_tok, d_tok, d_tokens_out, d_state, temperature, seed, nullptr, nullptr, d_workspace,
-                       ws_bytes, st);
+        return few_run(m, B, pos0, G, d_tok, d_tok, d_tokens_out, d_state, temperature, seed, nullptr, nullptr, d_workspace, st);
     if (!topp && !d_pos && !eos_plus1 && row_bytes(m, B) <= ws_bytes) {
         const int nblk = mega_blocks(m, B);
         if (nblk > 0)
@@ -2369,6 +2371,13 @@ extern "C" int srm_linear(int32_t dtype, int32_t epilogue, const void *d_A, cons
 // of the others were up to 1 % slower, by where their own code then lies: sequence form 4 x 256 of the fp32 model 191.8 | 193.5 us.)
 #include "few.hpp"
 
+constexpr int kFewGroupColumns = 8, kFewGroupBlocks = kFewGroups * 256 / kFewGroupColumns, kFewCuLds = 84 * 1024;
+constexpr int64_t kFewGroupRows = kFewGroups * 4;    // samples of a call at most
+static size_t few_group_words_bytes(const srm_model *m, int64_t B, int mb)
+{
+    return (align_up((size_t)B, mb) * ((size_t)2 * m->d + m->ff) + (size_t)kFewGroupBlocks * (2 * mb + 1)) * sizeof(few_word) + 256;
+}
+
 // Whether a model gets the packed copies: where some call can use them on this device (current when the model is made).
 static bool few_packable(const srm_model *m)
 {
@@ -2383,7 +2392,8 @@ static int few_pack(srm_model *m)
 {
     const size_t d = m->d, ff = m->ff, s = m->wsize, proj = m->noproj ? 0 : d * d * s, mlp = d * ff * s;
     const size_t head = align_up((size_t)m->V, 4) * d * s, table = align_up(sizeof(FewLayer) * m->L, 256);
-    const size_t total = align_up(table + m->L * (2 * proj + 2 * mlp) + head, (size_t)2 << 20);
+    const size_t words = m->wsize == 4 ? few_group_words_bytes(m, kFewGroupRows, kFewGroupRows / kFewGroups) : 0;
+    const size_t total = align_up(table + m->L * (2 * proj + 2 * mlp) + head + words, (size_t)2 << 20);
     hipError_t e = hipMalloc(&m->few_slab, total);
     if (e == hipErrorOutOfMemory) {                  // the step kernels do all that these are for
         (void)hipGetLastError();
@@ -2412,6 +2422,7 @@ static int few_pack(srm_model *m)
         }
     }
     m->few_head = pack(m->head, m->V, d);
+    if (words) m->few_words = at;                    // (the copies are whole multiples of 256 bytes)
     e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpy(m->few_layers, fl.data(), sizeof(FewLayer) * m->L, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -2479,7 +2490,9 @@ static int few_others(int device, hipStream_t st)
     else if (recent && d.met && few_launches + 1 - d.met < kFewShares) return 1;
     return n;
 }
-static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st)
+// reset(): what is to stand between the kernels that the launch waits for and its own.
+template <typename F>
+static int few_launch(int device, const void *kern, int blocks, int threads, int lds, void **args, hipStream_t st, F &&reset)
 {
     const std::lock_guard<std::mutex> hold(few_lock);
     FewDevice &d = few_devices[device];
@@ -2513,6 +2526,7 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
         if (before && before != waited) HIP_TRY(hipStreamWaitEvent(st, before, 0));
         waited = before;
     }
+    SRM_TRY(reset());
     HIP_TRY(hipExtLaunchKernel(kern, dim3((unsigned)blocks), dim3((unsigned)threads), args, (size_t)lds, st, nullptr, ev, 0));
     ++few_launches;
     for (int k = at; k < at + need; ++k) d.share[k] = FewShare{ev, st, few_launches};
@@ -2525,11 +2539,6 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
 // arrival itself costs 0.3 to 0.7 us per launch (195.5 | 196.2; d = 512 74.8 | 75.1).
 constexpr unsigned few_arrive_polls = 1u << 13;
 
-constexpr int kFewGroupColumns = 8, kFewGroupBlocks = kFewGroups * 256 / kFewGroupColumns, kFewCuLds = 84 * 1024;
-static size_t few_group_words_bytes(const srm_model *m, int64_t B, int mb)
-{
-    return (align_up((size_t)B, mb) * ((size_t)2 * m->d + m->ff) + (size_t)kFewGroupBlocks * (2 * mb + 1)) * sizeof(few_word) + 256;
-}
 static const void *few_group_kernel(int mb)
 {
     return mb == 1 ? reinterpret_cast<const void *>(few_rows_kernel<float, 256, kFewGroupColumns, 1, true, true>)
@@ -2553,20 +2562,24 @@ static const void *few_kernel(int mb)
 // toy model (d = 256, 4 layers, 4096 tokens), us per token, 64 work-groups over all XCDs (from 9 rows on step kernels) | groups: 1 row
 // 31.5 | 26.2, 2: 32.9 | 26.2, 4: 38.1 | 29.4, 8: 52.7 | 30.3, 9: 84 | 33, 16: 86 | 34, 17: 92 | 37, 32: 97 | 38.  Up to 8 rows both have the
 // same bits, and where other streams launch such steps side by side the small grids, of which four fit the device, get more done
-// (8 rows, us per token of 1 | 2 | 4 streams: groups 30 | 30 | 30, small grids 52 | 27 | 14).  Single steps of more than 8 rows
+// (8 rows, us per token of 1 | 2 | 4 streams: groups 30 | 30 | 30, small grids 52 | 27 | 14); more rows
+// hold the device for their call, whatever their streams, and get more done than the step kernels all the same (16 rows, 2 | 4
+// streams, step kernels 49 | 143, groups 34 | 35; 32 rows 56 | 206, 38 | 39).  Single steps of more than 8 rows
 // keep the sums of the step kernels.
-static int few_group_rows(const srm_model *m, int64_t B, int64_t G, size_t ws_bytes)
+// Their words, more than the arrays of as many rows, are the model's own, so that the way of a call does not depend on its
+// workspace.  Kernels that take the whole device never run side by side, whatever their streams (few_launch).
+static int few_group_rows(const srm_model *m, int64_t B, int64_t G)
 {
-    if (m->wsize != 4 || B > kFewGroups * 4 || (G == 1 && B > few_max_rows(m)) || device_cus() < kFewGroupBlocks) return 0;
-    const int mb = B <= kFewGroups ? 1 : B <= 2 * kFewGroups ? 2 : 4;
-    return few_list_bytes(B) + few_group_words_bytes(m, B, mb) + 256 <= ws_bytes ? mb : 0;
+    if (!m->few_words || B > kFewGroupRows || (G == 1 && B > few_max_rows(m))) return 0;
+    if (device_cus() < kFewGroupBlocks || device_cus() >= 2 * kFewGroupBlocks) return 0;
+    return B <= kFewGroups ? 1 : B <= 2 * kFewGroups ? 2 : 4;
 }
 static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_in, int32_t *tok_out, int32_t *store,
-                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, size_t ws_bytes, hipStream_t st)
+                   void *state, float temperature, uint32_t seed, float *logits, float *hidden, void *ws, hipStream_t st)
 {
     const int D = m->d;
     st = few_stream(st);
-    int gmb = few_group_rows(m, B, G, ws_bytes);
+    int gmb = few_group_rows(m, B, G);
     if (gmb && B <= few_max_rows(m) && few_others(m->device, st)) gmb = 0;
     const int mb = gmb ? gmb : few_bucket(B), nwc = gmb ? kFewGroupColumns : few_columns(m), nb = gmb ? kFewGroupBlocks : D / nwc;
     const void *kern = gmb ? few_group_kernel(gmb)
@@ -2585,7 +2598,7 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     a.state = state; a.state_half = m->shalf ? 1 : 0;
     a.logits = logits; a.hidden = hidden;
     a.temp = temperature; a.seed = seed;
-    unsigned char *base = static_cast<unsigned char *>(ws) + few_list_bytes(B);
+    unsigned char *base = gmb ? m->few_words : static_cast<unsigned char *>(ws) + few_list_bytes(B);
     a.xw = reinterpret_cast<few_word *>(base);
     const size_t rows = gmb ? align_up(B, mb) : mb;
     a.mw = a.xw + rows * D;
@@ -2602,14 +2615,18 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
                         : (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
     const int n = (int)((gmb ? few_group_words_bytes(m, B, mb) : few_words_bytes(m, B)) / 16), n_store = store ? (int)B * G : 0;
-    hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
-                       reinterpret_cast<u32x4_t *>(base), n, withdrawn, static_cast<int *>(ws), store, n_store);
-    HIP_TRY(hipGetLastError());
+    auto reset = [&] {
+        hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
+                           reinterpret_cast<u32x4_t *>(base), n, withdrawn, static_cast<int *>(ws), store, n_store);
+        HIP_TRY(hipGetLastError());
+        return (int)SRM_OK;
+    };
+    if (!gmb) SRM_TRY(reset());
     // (groups: a CU for each work-group)
     const int lds = std::max(few_lds_bytes((int)m->wsize, D, nwc, mb), gmb ? kFewCuLds : 0);
     HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     void *args[] = {&a};
-    return few_launch(m->device, kern, nb, (kFewGather + nwc) * 64, lds, args, st);
+    return few_launch(m->device, kern, nb, (kFewGather + nwc) * 64, lds, args, st, [&] { return gmb ? reset() : (int)SRM_OK; });
 }
 
 // ------------------------------------------------------------------ some dozens of samples and more: all layers as one kernel
@@ -2732,5 +2749,5 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     const int lds = stack_lds_bytes(512, s.cw, s.rb);
     HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, std::max(lds, kFewCuLds)));
     void *args[] = {&a};
-    return few_launch(m->device, kern, blocks, kStackThreads, std::max(lds, kFewCuLds), args, st);
+    return few_launch(m->device, kern, blocks, kStackThreads, std::max(lds, kFewCuLds), args, st, [] { return (int)SRM_OK; });
 }

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import srm_synth
-from gpu_util import to_dev, rel_err_rows, check_tokens, kernel_events, kernel_launches
+from gpu_util import to_dev, rel_err_rows, check_tokens, kernel_events, kernel_launches, kernel_grids
 
 pytestmark = pytest.mark.gpu
 SWITCH = "SRM_ONE_KERNEL_STEP"
@@ -735,4 +735,78 @@ def test_fp32_steps_in_groups_and_side_by_side_have_the_same_bits(srm, B):
     torch.cuda.synchronize()
     for one in got:
         assert all(torch.equal(a, b) for a, b in zip(one, want))
+    model.close()
+
+
+def _alone(model, B=1, G=6):
+    """Launches on one stream, behind which those of other streams in earlier tests no longer count."""
+    st, tk, ws = model.new_state(B), torch.zeros(B, dtype=torch.int32, device="cuda"), model.new_workspace(B)
+    out = torch.empty((G, B), dtype=torch.int32, device="cuda")
+    for _ in range(9):
+        torch.cuda.synchronize()
+        model.generate(B, 3, G, tk, st, out, workspace=ws)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("B", [1, 2, 4, 8, 9, 16, 17, 32])
+def test_groups_whatever_the_workspace(srm, B):
+    """fp32 generation of up to 32 samples runs in groups of the whole device with a workspace of its rows as with a larger one:
+    the same bits.  33 samples do not."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model, G = srm.Model(cfg, srm_synth.make_weights(cfg)), 6
+
+    def generate(B, rows, guard=4096):
+        n = model.workspace_bytes(rows)
+        ws = torch.randint(0, 256, (n + guard,), dtype=torch.uint8, device="cuda")
+        behind = ws[n:].clone()
+        st, tk = model.new_state(B), to_dev((np.arange(B) * 31 % cfg.vocab).astype(np.int32))
+        out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        model.generate(B, 3, G, tk, st, out, workspace=ws[:n], temperature=0.7, seed=5)
+        torch.cuda.synchronize()
+        assert torch.equal(ws[n:], behind)
+        return out, tk, st
+
+    print(f"groups of {B} samples", flush=True)
+    _alone(model)
+    runs = {}
+    for rows in (B, 4 * B + 60):
+        assert kernel_grids("few_rows_kernel", lambda: runs.update({rows: generate(B, rows)})) == [256]
+    assert all(torch.equal(a, b) for a, b in zip(runs[B], runs[4 * B + 60]))
+    if B == 32:
+        assert _launches(lambda: generate(33, 33)) == 0
+    model.close()
+
+
+@pytest.mark.parametrize("B", [1, 8, 16, 32])
+def test_groups_of_several_streams_in_line(srm, B):
+    """Generations in groups that wait on several streams at once: they exchange through words of the model, one after the other,
+    up to eight samples the ones behind the first as small grids; each has the bits of the call alone."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model, G, n = srm.Model(cfg, srm_synth.make_weights(cfg)), 10, 4
+    streams, ws = [torch.cuda.Stream() for _ in range(n)], [model.new_workspace(B) for _ in range(n)]
+    sets = [[model.new_state(B), None, torch.full((G, B), -7, dtype=torch.int32, device="cuda")] for _ in range(2 * n)]
+    for k, one in enumerate(sets):
+        one[1] = to_dev(((np.arange(B) * 31 + 7 * (k % n)) % cfg.vocab).astype(np.int32))
+
+    def generate(k, i):
+        st, tk, out = sets[k]
+        model.generate(B, 3, G, tk, st, out, workspace=ws[i], temperature=0.7, seed=5 + i, stream=streams[i])
+
+    _alone(model)
+    for i in range(n):
+        generate(i, i)
+        torch.cuda.synchronize()
+
+    def side_by_side():
+        for s in streams:
+            with torch.cuda.stream(s):
+                torch.cuda._sleep(40_000_000)
+        for i in range(n):
+            generate(n + i, i)
+
+    print(f"groups of {B} samples on {n} streams", flush=True)
+    grids = kernel_grids("few_rows_kernel", side_by_side)
+    assert sorted(grids) == ([256] * 4 if B > 8 else [64, 64, 64, 256])
+    for i in range(n):
+        assert all(torch.equal(a, b) for a, b in zip(sets[i], sets[n + i]))
     model.close()
