@@ -2647,7 +2647,8 @@ static StackPlan stack_plan(int64_t rows)
     return s;
 }
 // Its memory in the workspace: x and a where they always are, the rest from the array of u on, over what only the step kernels
-// or the head behind it use.
+// or the head behind it use.  Of one group m lies where g does: each is written behind a wait for the last to have read the other.
+// (So five rows find room in the arrays of a small vocabulary too; those of several groups do not wait for each other.)
 struct StackMem {
     unsigned char *words;
     float2 *stats;
@@ -2667,8 +2668,9 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
     const size_t used = (size_t)cdiv(rows, s.per) * s.tiles * s.rb * 16;
     r.words = take(kStackWordBytes);
     r.stats = reinterpret_cast<float2 *>(take((size_t)rows * (m->d / s.cw) * sizeof(float2)));
-    r.m = reinterpret_cast<bf16 *>(take(used * m->d * 2));
+    if (rows > s.per) r.m = reinterpret_cast<bf16 *>(take(used * m->d * 2));
     r.g = reinterpret_cast<bf16 *>(take(used * m->ff * 2));
+    if (rows <= s.per) r.m = r.g;
     r.bytes = off;
     return r;
 }

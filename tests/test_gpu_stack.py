@@ -59,7 +59,8 @@ def _steps(model, cfg, toks, positions=None, garbage=None, **how):
 
 # rows at the borders of the plan: whole and part groups of 16, a group's tile of one to four blocks of 16, two members on 32
 # columns with tiles of three and four blocks, several tiles to a member
-ROWS = [9, 16, 33, 128, 129, 300, 512, 513, 1024, 1025, 2048, 2100]
+# (2049: four tiles become six; 3072: the most rows, whose positions fill their place in LDS); the smallest step, a second group of one row
+ROWS = [5, 9, 16, 17, 33, 128, 129, 300, 512, 513, 1024, 1025, 2048, 2049, 2100, 3072]
 
 
 @pytest.mark.parametrize("B", ROWS)
@@ -91,7 +92,17 @@ def test_layers_in_one_kernel_match_oracle_and_step_kernels(srm, orc_mod, B, var
     model.close()
 
 
-@pytest.mark.parametrize("B", [9, 130, 513, 1100])
+@pytest.mark.parametrize("B,launches", [(4, 0), (5, 1), (3072, 1), (3073, 0)])
+def test_where_the_kernel_ends(srm, B, launches):
+    cfg = _config(vocab=200)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    tok, st, ws = torch.zeros(B, dtype=torch.int32, device="cuda"), model.new_state(B), model.new_workspace(B)
+    print(f"where the kernel ends B={B}", flush=True)
+    assert _launches(lambda: model.decode_step(B, 1, tok, st, tok.clone(), workspace=ws)) == launches
+    model.close()
+
+
+@pytest.mark.parametrize("B", [5, 9, 130, 513, 1100, 3072])
 def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
     """A launch whose work-groups have not all started is done by one of them: forced from the host, by an arrival that is
     withdrawn from the start, then by a wait of one look, which ends either way."""
