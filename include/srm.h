@@ -84,8 +84,10 @@
  *                        The waits behind that are bounded like those of the
  *                        one-kernel path of srm_generate (see there): should one
  *                        give up, the tokens of the call are -1 and its state is
- *                        undefined (SRM_ONE_KERNEL_POLLS=n, for tests: that bound
- *                        in polls; =n:g in step g of a generate call alone).
+ *                        undefined; fp32 generation that takes the whole device
+ *                        may still complete some of its samples
+ *                        (SRM_ONE_KERNEL_POLLS=n, for tests: that bound in polls;
+ *                        =n:g in step g of a generate call alone).
  *                        The step kernels, with fp32 sums in another order, take
  *                        such steps in all other calls: on a stream that is being
  *                        captured, in srm_decode_step_ragged and

@@ -713,31 +713,6 @@ def test_generation_in_groups_matches_oracle(srm, orc_mod, B, half, monkeypatch)
     model.close()
 
 
-@pytest.mark.parametrize("B", [1, 3, 8])
-def test_fp32_steps_in_groups_and_side_by_side_have_the_same_bits(srm, B):
-    """Up to eight rows run in groups where one stream has the device for itself, and as one small grid among others of its kind
-    where several launch in turn."""
-    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
-    model, G = srm.Model(cfg, srm_synth.make_weights(cfg)), 10
-    streams, ws = [torch.cuda.Stream() for _ in range(2)], [model.new_workspace(B) for _ in range(2)]
-    start = to_dev((np.arange(B) * 31).astype(np.int32))
-
-    def generate(i):
-        st, tk, out = model.new_state(B), start.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
-        torch.cuda.synchronize()
-        model.generate(B, 3, G, tk, st, out, workspace=ws[i], temperature=0.7, seed=5, stream=streams[i])
-        return out, tk, st
-
-    print(f"fp32 generation, groups and side by side B={B}", flush=True)
-    for _ in range(9):
-        want = generate(0)
-    got = [generate(i % 2) for i in range(6)]
-    torch.cuda.synchronize()
-    for one in got:
-        assert all(torch.equal(a, b) for a, b in zip(one, want))
-    model.close()
-
-
 def _alone(model, B=1, G=6):
     """Launches on one stream, behind which those of other streams in earlier tests no longer count."""
     st, tk, ws = model.new_state(B), torch.zeros(B, dtype=torch.int32, device="cuda"), model.new_workspace(B)
@@ -777,12 +752,8 @@ def test_groups_whatever_the_workspace(srm, B):
     model.close()
 
 
-@pytest.mark.parametrize("B", [1, 8, 16, 32])
-def test_groups_of_several_streams_in_line(srm, B):
-    """Generations in groups that wait on several streams at once: they exchange through words of the model, one after the other,
-    up to eight samples the ones behind the first as small grids; each has the bits of the call alone."""
-    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
-    model, G, n = srm.Model(cfg, srm_synth.make_weights(cfg)), 10, 4
+def _side_by_side(model, cfg, B, G=10, n=4):
+    """Generations that wait on n streams at once against the same calls alone, one after the other: the grids of their launches."""
     streams, ws = [torch.cuda.Stream() for _ in range(n)], [model.new_workspace(B) for _ in range(n)]
     sets = [[model.new_state(B), None, torch.full((G, B), -7, dtype=torch.int32, device="cuda")] for _ in range(2 * n)]
     for k, one in enumerate(sets):
@@ -792,21 +763,72 @@ def test_groups_of_several_streams_in_line(srm, B):
         st, tk, out = sets[k]
         model.generate(B, 3, G, tk, st, out, workspace=ws[i], temperature=0.7, seed=5 + i, stream=streams[i])
 
-    _alone(model)
-    for i in range(n):
-        generate(i, i)
-        torch.cuda.synchronize()
-
-    def side_by_side():
+    def all_at_once():
         for s in streams:
             with torch.cuda.stream(s):
-                torch.cuda._sleep(40_000_000)
+                torch.cuda._sleep(40_000_000)                          # (none has begun when the last is launched)
         for i in range(n):
             generate(n + i, i)
 
-    print(f"groups of {B} samples on {n} streams", flush=True)
-    grids = kernel_grids("few_rows_kernel", side_by_side)
-    assert sorted(grids) == ([256] * 4 if B > 8 else [64, 64, 64, 256])
+    def one_by_one():
+        for i in range(n):
+            generate(i, i)
+            torch.cuda.synchronize()
+
+    _alone(model)
+    alone = kernel_grids("few_rows_kernel", one_by_one)
+    grids = kernel_grids("few_rows_kernel", all_at_once)
     for i in range(n):
         assert all(torch.equal(a, b) for a, b in zip(sets[i], sets[n + i]))
+    return alone, sorted(grids)
+
+
+@pytest.mark.parametrize("B", [1, 3, 8])
+def test_fp32_steps_in_groups_and_side_by_side_have_the_same_bits(srm, B):
+    """Up to eight rows run in groups where one stream has the device for itself, streams in turn among them, and as one small grid
+    among others of its kind where several run or wait."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    print(f"fp32 generation, groups and side by side B={B}", flush=True)
+    assert _side_by_side(model, cfg, B) == ([256] * 4, [64, 64, 64, 256])
+    model.close()
+
+
+@pytest.mark.parametrize("B", [9, 16, 32])
+def test_groups_of_several_streams_in_line(srm, B):
+    """From nine rows on all run in groups, which exchange through words of the model, one after the other."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg))
+    print(f"groups of {B} samples on four streams", flush=True)
+    assert _side_by_side(model, cfg, B) == ([256] * 4, [256] * 4)
+    model.close()
+
+
+@pytest.mark.parametrize("B", [8, 9, 32])
+def test_groups_whose_waits_give_up(srm, B, monkeypatch):
+    """Groups wait on their own: a sample's tokens are right up to the step in which its group gives up and -1 from there on, the
+    last one too; the next call is right."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model, G = srm.Model(cfg, srm_synth.make_weights(cfg)), 8
+    ws = model.new_workspace(B)
+
+    def generate():
+        st, tk = model.new_state(B), to_dev((np.arange(B) * 31 % cfg.vocab).astype(np.int32))
+        out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        model.generate(B, 3, G, tk, st, out, workspace=ws)
+        torch.cuda.synchronize()
+        return out, tk, st
+
+    _alone(model)
+    want = generate()
+    print(f"groups of {B} samples whose waits give up", flush=True)
+    monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+    assert kernel_grids("few_rows_kernel", generate) == [256]
+    out, tk, _ = generate()
+    monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
+    gone = out == -1
+    assert gone.any() and (gone[1:] | ~gone[:-1]).all()                # once gone, gone
+    assert torch.equal(out[~gone], want[0][~gone])
+    assert torch.equal(tk, torch.where(gone[-1], -1, want[1]))
+    assert all(torch.equal(a, b) for a, b in zip(generate(), want))
     model.close()
