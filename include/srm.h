@@ -80,7 +80,8 @@
  *                        milliseconds per step.  Where several processes share
  *                        a device, =0 is therefore the better setting.  =2 and =3
  *                        (for tests): as if they had not all started, or with that
- *                        wait as short as it can be.
+ *                        wait as short as it can be; =4: where they work in groups,
+ *                        groups that do not share an L2 cache (same bits).
  *                        The waits behind that are bounded like those of the
  *                        one-kernel path of srm_generate (see there): should one
  *                        give up, the tokens of the call are -1 and its state is

@@ -65,6 +65,7 @@ struct FewArgs {
     few_word *xw, *mw, *gw, *pw;                     // words of x [MB][D], m [MB][D], g [MB][FF words], winners [MB][NB][2]
     unsigned *flag;                                  // a wait has given up; [1]: work-groups that have left without arriving all
     unsigned max_polls, arrive_polls;                // bounds of the waits
+    int scattered;                                   // for tests: groups by the work-groups' numbers, which lie on different XCDs
 };
 
 // near: who polls for the word shares this XCD's L2, and it need not be written through
@@ -651,8 +652,8 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
             const FewPlace at = few_place<NALL>(here, NALL, blk, __builtin_amdgcn_readfirstlane(me), lane, p.arrive_polls);
             if (lane == 0) {
                 *dead = !at.all;
-                dead[2] = at.at;
-                dead[3] = at.near;
+                dead[2] = p.scattered ? (int)blockIdx.x : at.at;
+                dead[3] = at.near && !p.scattered;
             }
         } else {
             const bool all = few_arrived<NB>(here, MB * 2, lane, p.arrive_polls);

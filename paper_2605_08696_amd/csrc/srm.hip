@@ -2614,6 +2614,7 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
         withdrawn = gmb ? (int)((reinterpret_cast<unsigned char *>(here) - base) / 16) + nb / 2 - 1
                         : (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
+    a.scattered = sw && sw[0] == '4';
     const int n = (int)((gmb ? few_group_words_bytes(m, B, mb) : few_words_bytes(m, B)) / 16), n_store = store ? (int)B * G : 0;
     auto reset = [&] {
         hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
@@ -2741,6 +2742,7 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     const char *sw = getenv("SRM_ONE_KERNEL_STEP");
     if (sw && sw[0] == '2') withdrawn = blocks * 8 / 16 - 1;
     if (sw && sw[0] == '3') a.arrive_polls = 0;
+    a.scattered = sw && sw[0] == '4';
     *dead = a.dead;
     auto begin = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(nb, 4)), dim3(256), 0, st, d.tok_in + b0, static_cast<const bf16 *>(m->embed),

@@ -63,6 +63,7 @@ struct StackArgs {
     unsigned *dead;                                  // a wait has given up (in this launch, or since the call began)
     unsigned *left;                                  // work-groups that have left without arriving all
     unsigned max_polls, arrive_polls;
+    int scattered;                                   // for tests: groups by the work-groups' numbers, which lie on different XCDs
 };
 
 // mean and squared deviations of the CW columns that CW / 4 neighbouring lanes hold
@@ -154,8 +155,8 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
         const FewPlace place = few_place<kStackBlocks>(p.here, gridDim.x, blk, __builtin_amdgcn_readfirstlane(me), lane, p.arrive_polls);
         if (lane == 0) {
             who[0] = place.all;
-            who[1] = place.at;
-            who[2] = place.near;
+            who[1] = p.scattered ? blk : place.at;
+            who[2] = place.near && !p.scattered;
             who[3] = 0;                              // a wait of this group has given up
         }
     }

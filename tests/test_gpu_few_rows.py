@@ -804,6 +804,30 @@ def test_groups_of_several_streams_in_line(srm, B):
     model.close()
 
 
+@pytest.mark.parametrize("B", [1, 8, 9, 32])
+def test_groups_that_do_not_share_a_cache(srm, B, monkeypatch):
+    """Groups of work-groups on different XCDs: what they exchange is written through the caches, the bits are the same."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=4)
+    model, G = srm.Model(cfg, srm_synth.make_weights(cfg)), 20
+    ws = model.new_workspace(B)
+
+    def generate():
+        st, tk = model.new_state(B), to_dev((np.arange(B) * 31 % cfg.vocab).astype(np.int32))
+        out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        model.generate(B, 3, G, tk, st, out, workspace=ws, temperature=0.7, seed=5)
+        torch.cuda.synchronize()
+        return out, tk, st
+
+    _alone(model)
+    want = generate()
+    monkeypatch.setenv(SWITCH, "4")
+    print(f"groups of {B} samples across the XCDs", flush=True)
+    runs = {}
+    assert kernel_grids("few_rows_kernel", lambda: runs.update(got=generate())) == [256]
+    assert all(torch.equal(a, b) for a, b in zip(runs["got"], want))
+    model.close()
+
+
 @pytest.mark.parametrize("B", [8, 9, 32])
 def test_groups_whose_waits_give_up(srm, B, monkeypatch):
     """Groups wait on their own: a sample's tokens are right up to the step in which its group gives up and -1 from there on, the

@@ -121,6 +121,29 @@ def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
     model.close()
 
 
+@pytest.mark.parametrize("B", [5, 33, 300, 513, 1100, 3072])
+def test_groups_that_do_not_share_a_cache(srm, B, monkeypatch):
+    """Groups of work-groups on different XCDs, as they come about where the XCDs do not get as many work-groups each: what they
+    exchange is written through the caches, the bits are the same, and the tokens -1 where their waits give up."""
+    cfg = _config(vocab=200)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    toks = srm_synth.make_prompts(cfg, batch=B, length=3)
+    want, st = _steps(model, cfg, toks)
+    monkeypatch.setenv(SWITCH, "4")
+    print(f"groups across the XCDs B={B}", flush=True)
+    runs = {}
+    for garbage in (None, 0):
+        assert _launches(lambda: runs.update(got=_steps(model, cfg, toks, garbage=garbage))) == 3
+        got, st2 = runs["got"]
+        for a, b in zip(want, got):
+            assert all(torch.equal(x, y) for x, y in zip(a, b))
+        assert torch.equal(st, st2)
+    monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+    got, _ = _steps(model, cfg, toks)
+    assert all((one[2] == -1).all() for one in got)
+    model.close()
+
+
 def test_ragged_step_in_one_kernel(srm, monkeypatch):
     """One position per sample, some outside the context: those keep their state and get -1; at one position for all the same
     bits as the plain step; otherwise the step kernels' results within the bf16 bound."""
@@ -331,10 +354,10 @@ def test_streams_side_by_side_share_the_device(srm, B, n, monkeypatch):
         torch.cuda.synchronize()
     print(f"{n} streams side by side B={B}", flush=True)
     assert sorted(kernel_grids("stack_kernel", steps)) == sorted([256, 128, 64, 64][:n])
-    for mode in (None, "2", "3"):
+    for mode in (None, "2", "3", "4"):
         if mode:
             monkeypatch.setenv(SWITCH, mode)
-            print(f"one work-group of each alone, mode {mode}", flush=True)
+            print(f"one work-group of each alone, or groups across the XCDs: mode {mode}", flush=True)
             steps()
             monkeypatch.delenv(SWITCH)
         for one in want["got"]:
