@@ -381,7 +381,7 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
         if (r0 >= r1) continue;                      // (all members of the group)
         barrier();
         for (int i = tid; i < r1 - r0; i += kStackThreads)
-            lpos[i] = p.pos_rows ? p.pos_rows[r0 + i] : p.pos_dev ? *p.pos_dev : p.pos;
+            lpos[i] = p.pos_rows ? few_load(p.pos_rows + r0 + i) : p.pos_dev ? few_load(p.pos_dev) : p.pos;
         barrier();
         if constexpr (!MANY) {
             get_in(0, v0 % COLT * CW);

@@ -53,6 +53,11 @@ def test_no_kernel_spills_vector_registers(kernels):
     assert len(kernels) > 200 and not spilled
 
 
+def test_no_kernel_has_scratch_memory(kernels):
+    """Neither for spilled registers nor for an argument whose address is taken; nucleus_slow_kernel apart, as above."""
+    assert not {n: q[".private_segment_fixed_size"] for n, q in kernels.items() if q[".private_segment_fixed_size"] and "nucleus_slow" not in n}
+
+
 def test_bf16_gemms_keep_their_accumulators_in_one_register_file(kernels):
     """Two wavefronts per SIMD leave 256 registers, enough for every tile: with a larger budget the compiler keeps operands
     in accumulation registers and copies them back and forth inside the k loop."""
