@@ -107,9 +107,12 @@
  *                        whole device, or half or a quarter of it where such
  *                        steps of other streams are running or waiting (several
  *                        streams of some hundred samples each get more done
- *                        with =0); its wait for the others
- *                        is some 30 ms, one work-group alone takes 5 to 90 ms
- *                        per step.  Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
+ *                        with =0).  Where some of its
+ *                        work-groups have not started within some 0.1 ms, those
+ *                        that have do the work of the others too (same bits; where
+ *                        three processes step 300 samples each at a time, 0.63 ms
+ *                        per step, 0.33 with =0; =2:n, for tests: as if n had).
+ *                        Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
  *                        SRM_LN_ON_LOAD set, whose kernels it replaces.
  */
 #ifndef SRM_H

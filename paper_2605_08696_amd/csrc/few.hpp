@@ -135,58 +135,64 @@ __device__ __forceinline__ bool few_arrived(few_word *words, int stride, int lan
     return __all(here);
 }
 
-// An arrival of `blocks` work-groups, at most NB, whose words say on which XCD one runs (kFewXcd0 plus its number): the work-groups
-// in order of their XCD, an eighth of them to a group.  `me`: this work-group's word.
+// An arrival of `blocks` work-groups, at most NB, whose words say on which XCD one runs (kFewXcd0 plus its number), and which may go
+// on without those that are missing: whoever is tired of waiting withdraws them, and every work-group comes to the same answer.
+// It is tired after `polls` where at least `least` have arrived, else after `most_polls`.  `me`: this work-group's word.
 constexpr int kFewXcd0 = 4;
 __device__ __forceinline__ int few_xcd() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15; }          // HW_REG_XCC_ID
 struct FewPlace {
-    bool all;                // have arrived
-    int at;                  // this work-group's number in that order
-    bool near;               // its group lies on one XCD
+    int arrived;             // work-groups; in the order of their XCDs:
+    int at, below, same;     // this one's number, how many lie on the XCDs in front of its own and on its own
+    int order;               // its number in the order of the launch
+    __device__ __forceinline__ bool near(int per) const                // its group of `per` lies on one XCD
+    {
+        const int first = at / per * per;
+        return below <= first && first + per <= below + same;
+    }
 };
 constexpr int kFewGroups = 8;
 template <int NB>
-__device__ __forceinline__ FewPlace few_place(few_word *words, int blocks, int blk, int me, int lane, unsigned max_polls)
+__device__ __forceinline__ FewPlace few_place(few_word *words, int blocks, int blk, int me, int lane, int least, unsigned polls,
+                                              unsigned most_polls)
 {
     static_assert(NB % 64 == 0, "as many words for each lane");
     constexpr int N = NB / 64;
-    const int per = blocks / kFewGroups;
     few_word v[N];
-    bool here = false, withdrawn = false;
-    auto look = [&] {
-        here = true;
-        withdrawn = false;
+    auto waits = [&] {                               // for one that has neither arrived nor been withdrawn
+        bool w = false;
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            here = here && v[i] >= kFewXcd0;
-            withdrawn = withdrawn || v[i] == kFewWithdrawn;
-        }
-        here = __all(here);
-        withdrawn = __any(withdrawn);
+        for (int i = 0; i < N; ++i) w = w || (v[i] == 0 && i * 64 + lane < blocks);
+        return __any(w);
     };
-    for (unsigned polls = 0;; ++polls) {
+    auto arrived = [&] {
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) n += __popcll(__ballot(v[i] >= kFewXcd0));
+        return n;
+    };
+    for (unsigned asked = 0;; ++asked) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
-            v[i] = i * 64 + lane < blocks ? __hip_atomic_load(words + i * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull >> 33;
-        look();
-        if (here || withdrawn || polls >= max_polls) break;
-    }
-    if (!here && !withdrawn) {
+            v[i] = i * 64 + lane < blocks ? __hip_atomic_load(words + i * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        if (!waits()) break;
+        if (asked >= most_polls || (asked >= polls && arrived() >= least)) {
 #pragma unroll
-        for (int i = 0; i < N; ++i)
-            if (i * 64 + lane < blocks) few_set(words + i * 64 + lane, kFewWithdrawn, v[i]);
-        look();
+            for (int i = 0; i < N; ++i)
+                if (v[i] == 0 && i * 64 + lane < blocks) few_set(words + i * 64 + lane, kFewWithdrawn, v[i]);
+            break;
+        }
     }
-    int below = 0, same = 0, at = 0;
+    FewPlace p{arrived(), 0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        below += __popcll(__ballot((int)v[i] < me));
-        same += __popcll(__ballot((int)v[i] == me));
-        at += __popcll(__ballot((int)v[i] == me && i * 64 + lane < blk));
+        const int w = (int)v[i], number = i * 64 + lane;
+        p.below += __popcll(__ballot(w >= kFewXcd0 && w < me));
+        p.same += __popcll(__ballot(w == me));
+        p.at += __popcll(__ballot(w == me && number < blk));
+        p.order += __popcll(__ballot(w >= kFewXcd0 && number < blk));
     }
-    at += below;
-    const int first = at / per * per;
-    return FewPlace{here, at, below <= first && first + per <= below + same};
+    p.at += p.below;
+    return p;
 }
 
 // A load through a pointer that came from LDS: global memory, which the compiler cannot know (a flat load would count as an
@@ -649,11 +655,11 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     if constexpr (!XCD) tokens();
     if (wave == 0) {
         if constexpr (XCD) {
-            const FewPlace at = few_place<NALL>(here, NALL, blk, __builtin_amdgcn_readfirstlane(me), lane, p.arrive_polls);
+            const FewPlace place = few_place<NALL>(here, NALL, blk, __builtin_amdgcn_readfirstlane(me), lane, NALL, p.arrive_polls, p.arrive_polls);
             if (lane == 0) {
-                *dead = !at.all;
-                dead[2] = p.scattered ? (int)blockIdx.x : at.at;
-                dead[3] = at.near && !p.scattered;
+                *dead = place.arrived < NALL;
+                dead[2] = p.scattered ? place.order : place.at;
+                dead[3] = place.near(NB) && !p.scattered;
             }
         } else {
             const bool all = few_arrived<NB>(here, MB * 2, lane, p.arrive_polls);

@@ -2690,8 +2690,11 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
 // and 437 | 235 and 171; no arrival was given up (longest step 1.5 ms).
 constexpr int64_t kStackMinRows = 5, kStackMaxRows = 3072;
 static_assert(kStackMaxRows <= (int64_t)kStackGroups * kStackMaxPer, "their positions are kept in LDS");
-// Polls of the arrival, some 30 ms: about what one work-group alone takes (ms per step: 37 rows 5, 300: 22, 1024: 33, 3000: 87).
-constexpr unsigned stack_arrive_polls = 1u << 15;
+// Polls of the arrival, some 0.1 ms: beside other work of the process as good as any longer (300 rows beside prefills, us per step with
+// 7 | 0.8 | 0.2 | 0.1 | 0.04 | 0.01 ms: 564 | 561 | 560 | 560 | 593 | 593, 1024 rows beside 3001 with top-p 279 | 279 | 278 | 278 | 282 | 351).  It
+// counts where other processes run such steps, and each gets some of the CUs (300 rows, three processes: 7216 | 1381 | 787 | 617 | 593 |
+// 593, step kernels 329; two: 340 | - | 336 | - | 336, 280; waiting for all, and one alone otherwise, three took 29242).
+constexpr unsigned stack_arrive_polls = 1u << 9;
 static bool stack_ok(const srm_model *m, int64_t rows, size_t ws_bytes, hipStream_t st)
 {
     if (!m->few_layers || m->wsize != 2 || m->d != 512 || m->noproj || m->L < 6 || rows < kStackMinRows || rows > kStackMaxRows) return false;
@@ -2738,15 +2741,15 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     a.max_polls = poll_bound(1u << 21, d.step);      // a second or two
     a.arrive_polls = stack_arrive_polls;
     const int others = few_others(m->device, st), blocks = kStackBlocks / (others == 0 ? 1 : others == 1 ? 2 : 4);
-    int withdrawn = -1;                              // the arrival of one of the last work-groups
+    int starting = kStackBlocks;                     // work-groups that are not withdrawn from the start
     const char *sw = getenv("SRM_ONE_KERNEL_STEP");
-    if (sw && sw[0] == '2') withdrawn = blocks * 8 / 16 - 1;
-    if (sw && sw[0] == '3') a.arrive_polls = 0;
+    if (sw && sw[0] == '2') starting = sw[1] == ':' ? atoi(sw + 2) : 0;
+    if (sw && sw[0] == '3') a.arrive_polls = sw[1] == ':' ? (unsigned)atoi(sw + 2) : 0;
     a.scattered = sw && sw[0] == '4';
     *dead = a.dead;
     auto begin = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(nb, 4)), dim3(256), 0, st, d.tok_in + b0, static_cast<const bf16 *>(m->embed),
-                           m->V, w.x, mem.stats, (int)nb, reinterpret_cast<u32x4_t *>(mem.words), withdrawn, b0 == 0 ? d.advance_ctr : nullptr);
+                           m->V, w.x, mem.stats, (int)nb, reinterpret_cast<u32x4_t *>(mem.words), starting, b0 == 0 ? d.advance_ctr : nullptr);
         return hipGetLastError();
     };
     HIP_TRY(s.cw == 16 ? begin(stack_begin_kernel<512, 16>) : begin(stack_begin_kernel<512, 32>));

@@ -31,14 +31,17 @@
 // What is written for others is stored plainly where the group lies on one XCD (its L2 is where they read), else written
 // through (sc1); loads of it are sc1 in both cases (measured: plain stores between XCDs are not seen, within one always).
 //
-// All work-groups must be resident at once: the arrival and its way out are those of few.hpp.  The words of the arrival carry the XCD,
-// from which the groups are formed; a work-group that is left alone does all parts of all groups' phases in turn, with the same
-// tiles and sums.  So does, with four parts to a member, a launch of a quarter of the work-groups, of which four fit the device side
-// by side: for streams that launch such steps side by side (few_others in srm.hip).
+// Work-groups that wait for each other must be resident at once: the arrival is that of few.hpp.  Its words carry the XCD, from
+// which the groups are formed.  Where some work-groups have not started within its bound (what other processes run on the device
+// keeps them off their CUs, and may itself wait for these), they are left out: those that have are grouped by the next power of two,
+// and each does two or more parts of a phase, with the same tiles and sums; of fewer than eight, the last to leave does all alone.
+// (They wait longer until there are four for each group: alone, a step takes 5 to 90 ms.)  The same form serves launches of half or a quarter of the work-groups, for streams that launch such steps side by side
+// (few_others in srm.hip).
 #pragma once
 #include "few.hpp"
 
 constexpr int kStackBlocks = 256, kStackGroups = 8, kStackPer = kStackBlocks / kStackGroups, kStackThreads = 512;
+constexpr int kStackLeast = 32;                      // work-groups that go on without the others (four of a group) once tired of waiting
 constexpr int kStackMaxPer = 384;                    // rows of a group: their positions are kept in LDS
 constexpr int kStackWordBytes = kStackBlocks * 8 + kStackGroups * 128 + 256;
 struct StackArgs {
@@ -89,11 +92,11 @@ __device__ __forceinline__ float2 stack_stats(const float4 &v)
 template <int D, int CW>
 __global__ void __launch_bounds__(256)
 stack_begin_kernel(const int32_t *__restrict__ tok, const bf16 *__restrict__ embed, int vocab, float *__restrict__ x,
-                   float2 *__restrict__ stats, int rows, u32x4_t *words, int withdrawn, int *advance_ctr)
+                   float2 *__restrict__ stats, int rows, u32x4_t *words, int starting, int *advance_ctr)
 {
-    if (blockIdx.x == 0) {
-        for (int i = threadIdx.x; i < kStackWordBytes / 16; i += 256)
-            words[i] = u32x4_t{i == withdrawn ? (unsigned)kFewWithdrawn : 0u, 0, 0, 0};
+    if (blockIdx.x == 0) {                           // (starting: for tests, work-groups behind these are withdrawn from the start)
+        auto word = [&](int b) { return b >= starting && b < kStackBlocks ? (unsigned)kFewWithdrawn : 0u; };
+        for (int i = threadIdx.x; i < kStackWordBytes / 16; i += 256) words[i] = u32x4_t{word(2 * i), 0, word(2 * i + 1), 0};
         if (advance_ctr && threadIdx.x == 0) {       // the step counters of a generate call (see ln_kernel)
             advance_ctr[0] += 1;
             advance_ctr[1] += 1;
@@ -152,26 +155,33 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
     for (int i = tid; i < p.L * (int)(sizeof(FewLayer) / 8); i += kStackThreads)
         reinterpret_cast<few_word *>(lay)[i] = reinterpret_cast<const few_word *>(p.layers)[i];
     if (wave == 0) {
-        const FewPlace place = few_place<kStackBlocks>(p.here, gridDim.x, blk, __builtin_amdgcn_readfirstlane(me), lane, p.arrive_polls);
+        const FewPlace place = few_place<kStackBlocks>(p.here, gridDim.x, blk, __builtin_amdgcn_readfirstlane(me), lane, kStackLeast,
+                                                         p.arrive_polls, p.arrive_polls << 6);
+        // as many as there are of a group, or the next power of two below
+        int m = kStackPer;
+        while (m * kStackGroups > place.arrived) m >>= 1;
         if (lane == 0) {
-            who[0] = place.all;
-            who[1] = p.scattered ? blk : place.at;
-            who[2] = place.near && !p.scattered;
+            who[0] = m;
+            who[1] = p.scattered ? place.order : place.at;
+            who[2] = m && place.near(m) && !p.scattered;
             who[3] = 0;                              // a wait of this group has given up
+            who[4] = me < kFewXcd0;                  // withdrawn
         }
     }
     __syncthreads();
     const bool alone = !__builtin_amdgcn_readfirstlane(who[0]);
+    const int at = __builtin_amdgcn_readfirstlane(who[1]);
     if (__builtin_expect(alone, 0)) {
         if (tid == 0)
             who[5] = __hip_atomic_fetch_add(p.left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
         __syncthreads();
         if (!who[5]) return;
+    } else if (__builtin_amdgcn_readfirstlane(who[4]) || at >= __builtin_amdgcn_readfirstlane(who[0]) * kStackGroups) {
+        return;
     }
-    const int at = __builtin_amdgcn_readfirstlane(who[1]);
     const bool pure = __builtin_amdgcn_readfirstlane(who[2]) || alone;
     // the work-groups of a group, and the parts of a phase that this one does: part v of kStackPer, and every `members`-th behind it
-    const int members = alone ? 1 : (int)gridDim.x / kStackGroups;
+    const int members = alone ? 1 : __builtin_amdgcn_readfirstlane(who[0]);
     const int c0 = alone ? 0 : at / members, c1 = alone ? kStackGroups : c0 + 1;
     const int v0 = alone ? 0 : at % members;
 

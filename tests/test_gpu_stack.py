@@ -104,7 +104,7 @@ def test_where_the_kernel_ends(srm, B, launches):
 
 @pytest.mark.parametrize("B", [5, 9, 130, 513, 1100, 3072])
 def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
-    """A launch whose work-groups have not all started is done by one of them: forced from the host, by an arrival that is
+    """A launch of whose work-groups none has started in time is done by one of them: forced from the host, by arrivals that are
     withdrawn from the start, then by a wait of one look, which ends either way."""
     cfg = _config(vocab=200)
     model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
@@ -118,6 +118,24 @@ def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
         for a, b in zip(want, got):
             assert all(torch.equal(x, y) for x, y in zip(a, b))
         assert torch.equal(st, st2)
+    model.close()
+
+
+@pytest.mark.parametrize("B", [5, 300, 513, 3072])
+@pytest.mark.parametrize("started", [7, 8, 17, 35, 100, 129, 255])
+def test_work_groups_that_have_started_do_without_the_others(srm, B, started, monkeypatch):
+    """Some work-groups do not start in time (their arrivals are withdrawn from the start): the others form groups of one to
+    sixteen, some of which lie across XCDs, and of less than eight one is left alone; the same bits."""
+    cfg = _config(vocab=200)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    toks = srm_synth.make_prompts(cfg, batch=B, length=2)
+    want, st = _steps(model, cfg, toks)
+    monkeypatch.setenv(SWITCH, f"2:{started}")
+    print(f"{started} work-groups have started B={B}", flush=True)
+    got, st2 = _steps(model, cfg, toks)
+    for a, b in zip(want, got):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    assert torch.equal(st, st2)
     model.close()
 
 
