@@ -77,11 +77,17 @@
  *                        some 8 ms (kernels of other processes that wait for each
  *                        other too, cooperative kernels that fill the device), one
  *                        of them does the call's work alone: same bits, some
- *                        milliseconds per step.  Where several processes share
+ *                        milliseconds per step.  Those of a kernel that takes the
+ *                        whole device wait 0.1 ms, and those that have started then
+ *                        do the work of the others too (same bits; where three
+ *                        processes generate at a time, 32 samples of the fp32 model
+ *                        0.12 ms per token, the same with =0; 8 samples 0.12, 0.1).
+ *                        Where several processes share
  *                        a device, =0 is therefore the better setting.  =2 and =3
  *                        (for tests): as if they had not all started, or with that
- *                        wait as short as it can be; =4: where they work in groups,
- *                        groups that do not share an L2 cache (same bits).
+ *                        wait as short as it can be; =2:n, of a kernel that takes
+ *                        the whole device: as if n had; =4: where they work in
+ *                        groups, groups that do not share an L2 cache (same bits).
  *                        The waits behind that are bounded like those of the
  *                        one-kernel path of srm_generate (see there): should one
  *                        give up, the tokens of the call are -1 and its state is
@@ -107,11 +113,8 @@
  *                        whole device, or half or a quarter of it where such
  *                        steps of other streams are running or waiting (several
  *                        streams of some hundred samples each get more done
- *                        with =0).  Where some of its
- *                        work-groups have not started within some 0.1 ms, those
- *                        that have do the work of the others too (same bits; where
- *                        three processes step 300 samples each at a time, 0.63 ms
- *                        per step, 0.33 with =0; =2:n, for tests: as if n had).
+ *                        with =0; so do processes: three that step 300 samples
+ *                        each at a time 0.63 ms per step, 0.33 with =0).
  *                        Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
  *                        SRM_LN_ON_LOAD set, whose kernels it replaces.
  */

@@ -33,7 +33,8 @@
 // All work-groups must be resident at once, which an ordinary launch cannot promise: other processes, or kernels that wait for
 // each other themselves, can hold the CUs.  So the first exchange is an arrival, before anything but scratch is written
 // (few_arrived): either every work-group sees that all have started, and then all stay until they end, or every one leaves, and
-// the last to leave does all the work alone (few_alone), slowly and with the same bits.
+// the last to leave does all the work alone (few_alone), slowly and with the same bits.  Kernels in groups that take the whole
+// device (few_place) go on with the work-groups that have started.
 // The waits behind the arrival are bounded all the same: a work-group that gives up raises a flag that ends all other waits, and
 // the tokens are -1.
 #pragma once
@@ -627,7 +628,7 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     float *const lnp = reinterpret_cast<float *>(red + NWT * RB * 64);                 // [2][4][D] LayerNorm parameters of two layers
     FewLayer *const lay = reinterpret_cast<FewLayer *>(lnp + 8 * D);                   // [L] (a read of memory per phase is a trip of 1 us)
     int *const tokb = reinterpret_cast<int *>(lay + kFewMaxLayers);                    // [MB]
-    int *const dead = tokb + MB;                                                       // [2], then the place in the groups [2]
+    int *const dead = tokb + MB;                                                       // [2], then the place in the groups [3]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int blk = blockIdx.x, B = p.B;
@@ -655,11 +656,14 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     if constexpr (!XCD) tokens();
     if (wave == 0) {
         if constexpr (XCD) {
-            const FewPlace place = few_place<NALL>(here, NALL, blk, __builtin_amdgcn_readfirstlane(me), lane, NALL, p.arrive_polls, p.arrive_polls);
+            // (whole groups of those that have started, each of which takes several groups of rows in turn where some are missing)
+            const int own = __builtin_amdgcn_readfirstlane(me);
+            const FewPlace place = few_place<NALL>(here, NALL, blk, own, lane, NB, p.arrive_polls, p.arrive_polls << 6);
             if (lane == 0) {
-                *dead = place.arrived < NALL;
-                dead[2] = p.scattered ? place.order : place.at;
+                *dead = place.arrived < NB;
+                dead[2] = own < kFewXcd0 ? NALL : p.scattered ? place.order : place.at;        // (withdrawn: no group's)
                 dead[3] = place.near(NB) && !p.scattered;
+                dead[4] = place.arrived / NB;
             }
         } else {
             const bool all = few_arrived<NB>(here, MB * 2, lane, p.arrive_polls);
@@ -694,20 +698,8 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
         }
         return;
     }
-    if constexpr (XCD) {
-        const int at = __builtin_amdgcn_readfirstlane(dead[2]), c = at / NB;
-        near = __builtin_amdgcn_readfirstlane(dead[3]);
-        blk = at % NB;
-        if (c * MB >= p.Bs) return;                  // (the whole group: there are no rows for it)
-        few_group(p, c, MB, D);
-        p.xw += (size_t)c * MB * D;
-        p.mw += (size_t)c * MB * D;
-        p.gw += (size_t)c * MB * GC * NB;
-        p.pw += (size_t)c * MB * NB * 2;
-        B = p.B;
-        tokens();
-        barrier();
-    }
+    // All steps of the rows that p sees (*dead: a wait has given up)
+    auto steps = [&]() __attribute__((always_inline)) {
     unsigned tag = 0;                                // of the latest exchange, the same in every wavefront
     // (indexes pass through opaque copies where they are used: what is derived from them would otherwise be formed once, in
     // front of all loops, for every phase, and held in registers that do not exist)
@@ -1113,16 +1105,54 @@ __global__ void __launch_bounds__((kFewGather + NWC) * 64) few_rows_kernel(FewAr
     }
 out:
     if (tid < B) p.tok_out[tid] = -1;
+    };
+    if constexpr (XCD) {
+        const int at = __builtin_amdgcn_readfirstlane(dead[2]), teams = __builtin_amdgcn_readfirstlane(dead[4]);
+        near = __builtin_amdgcn_readfirstlane(dead[3]);
+        blk = at % NB;
+        if (at / NB >= teams) return;                // (the whole group)
+        const FewArgs all = p;
+        auto group = [&](int c) __attribute__((always_inline)) {
+            few_group(p, c, MB, D);
+            p.xw += (size_t)c * MB * D;
+            p.mw += (size_t)c * MB * D;
+            p.gw += (size_t)c * MB * GC * NB;
+            p.pw += (size_t)c * MB * NB * 2;
+            B = p.B;
+            tokens();
+            barrier();
+            steps();
+        };
+        // (the usual case apart: as a loop, what is kept for its next round costs the steps their registers, 38.2 | 38.5 us a token)
+        if (__builtin_expect(teams == kFewGroups, 1)) {
+            if (at / NB * MB < p.Bs) group(at / NB);
+            return;
+        }
+#pragma unroll 1
+        for (int c = at / NB; c * MB < all.Bs; c += teams) {
+            p = all;
+            group(c);
+            if (*dead) {                             // nor will the rest of its rows be right
+                for (c += teams; c * MB < all.Bs; c += teams)
+                    if (tid < min(MB, all.Bs - c * MB)) all.tok_out[c * MB + tid] = -1;
+                return;
+            }
+            barrier();                               // (nobody reads the tokens any more)
+        }
+    } else {
+        steps();
+    }
 }
 
 // Words that an earlier call has left in the workspace must not pass for this call's: no tag is zero.  Also the nucleus
-// pass's counter, and the token store of a call whose kernel may give up.  withdrawn: the vector of an arrival that is withdrawn
-// from the start, or -1.
+// pass's counter, and the token store of a call whose kernel may give up.  n: pairs of words; those from w0 to w1 (of arrivals, for
+// tests) are withdrawn from the start.
 __global__ void __launch_bounds__(256)
-few_reset_kernel(u32x4_t *words, int n, int withdrawn, int *counter, int32_t *store, int n_store)
+few_reset_kernel(u32x4_t *words, int n, int w0, int w1, int *counter, int32_t *store, int n_store)
 {
     const int i0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
-    for (int i = i0; i < n; i += step) words[i] = u32x4_t{i == withdrawn ? (unsigned)kFewWithdrawn : 0, 0, 0, 0};
+    auto word = [&](int w) { return w >= w0 && w < w1 ? (unsigned)kFewWithdrawn : 0u; };
+    for (int i = i0; i < n; i += step) words[i] = u32x4_t{word(2 * i), 0, word(2 * i + 1), 0};
     for (int i = i0; i < n_store; i += step) store[i] = -1;
     if (i0 == 0) *counter = 0;
 }

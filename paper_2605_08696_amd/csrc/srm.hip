@@ -2538,6 +2538,10 @@ static int few_launch(int device, const void *kern, int blocks, int threads, int
 // 195 | 7040, 4 rows 290 | 7310, without projections 149 | 5990; d = 512, 8 layers 75 | 960; fp32, d = 256, 8 rows 52 | 410).  The
 // arrival itself costs 0.3 to 0.7 us per launch (195.5 | 196.2; d = 512 74.8 | 75.1).
 constexpr unsigned few_arrive_polls = 1u << 13;
+// Of the groups of few_group_rows, some 0.1 ms (64 times that until a whole group has started): see stack_arrive_polls.  (Three processes
+// that generate with the toy model at a time, us per token: 8 rows 120, 32 rows 124; step kernels 99 and 124; one work-group alone
+// behind 8 ms 1793 and 1866.)
+constexpr unsigned few_group_polls = 1u << 9;
 
 static const void *few_group_kernel(int mb)
 {
@@ -2607,18 +2611,21 @@ static int few_run(srm_model *m, int64_t B, int pos0, int G, const int32_t *tok_
     few_word *const here = a.pw + (size_t)mb * nb * 2;           // (of groups, see few_rows_kernel)
     a.flag = reinterpret_cast<unsigned *>(here + (gmb ? nb : 0));
     a.max_polls = poll_bound(1u << 21);              // a second or two
-    a.arrive_polls = few_arrive_polls;
-    int withdrawn = -1;                              // the last work-group's arrival
+    a.arrive_polls = gmb ? few_group_polls : few_arrive_polls;
+    // words of the arrivals of work-groups that are withdrawn from the start
+    int w0 = 0, w1 = 0;
     const char *sw = getenv("SRM_ONE_KERNEL_STEP");
-    if (sw && sw[0] == '2')
-        withdrawn = gmb ? (int)((reinterpret_cast<unsigned char *>(here) - base) / 16) + nb / 2 - 1
-                        : (int)((reinterpret_cast<unsigned char *>(a.pw) - base) / 16) + (nb - 1) * mb;
-    if (sw && sw[0] == '3') a.arrive_polls = 0;
+    if (sw && sw[0] == '2') {
+        const few_word *const words = reinterpret_cast<const few_word *>(base);
+        w0 = gmb ? (int)(here - words) + (sw[1] == ':' ? atoi(sw + 2) : 0) : (int)(a.pw - words) + (nb - 1) * mb * 2;
+        w1 = gmb ? (int)(here - words) + nb : w0 + 1;
+    }
+    if (sw && sw[0] == '3') a.arrive_polls = sw[1] == ':' ? (unsigned)atoi(sw + 2) : 0;
     a.scattered = sw && sw[0] == '4';
     const int n = (int)((gmb ? few_group_words_bytes(m, B, mb) : few_words_bytes(m, B)) / 16), n_store = store ? (int)B * G : 0;
     auto reset = [&] {
         hipLaunchKernelGGL(few_reset_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(n, 256))), dim3(256), 0, st,
-                           reinterpret_cast<u32x4_t *>(base), n, withdrawn, static_cast<int *>(ws), store, n_store);
+                           reinterpret_cast<u32x4_t *>(base), n, w0, w1, static_cast<int *>(ws), store, n_store);
         HIP_TRY(hipGetLastError());
         return (int)SRM_OK;
     };

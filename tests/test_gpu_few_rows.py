@@ -828,6 +828,38 @@ def test_groups_that_do_not_share_a_cache(srm, B, monkeypatch):
     model.close()
 
 
+@pytest.mark.parametrize("B", [1, 8, 9, 32])
+@pytest.mark.parametrize("started", [0, 31, 32, 67, 100, 254])
+def test_work_groups_that_have_started_do_without_the_others(srm, B, started, monkeypatch):
+    """Some work-groups do not start in time (their arrivals are withdrawn from the start): the others form as many whole groups as
+    they can, which take the groups of rows in turn, and of less than one group a work-group is left alone; the same bits.  Where
+    waits give up, the rows that a group has not come to are gone as well."""
+    cfg = dataclasses.replace(srm_synth.CONFIGS["C1"], n_layers=2)
+    model, G = srm.Model(cfg, srm_synth.make_weights(cfg)), 5
+    ws = model.new_workspace(B)
+
+    def generate():
+        st, tk = model.new_state(B), to_dev((np.arange(B) * 31 % cfg.vocab).astype(np.int32))
+        out = torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+        model.generate(B, 3, G, tk, st, out, workspace=ws, temperature=0.7, seed=5)
+        torch.cuda.synchronize()
+        return out, tk, st
+
+    _alone(model)
+    want = generate()
+    monkeypatch.setenv(SWITCH, f"2:{started}")
+    print(f"{started} work-groups have started B={B}", flush=True)
+    runs = {}
+    assert kernel_grids("few_rows_kernel", lambda: runs.update(got=generate())) == [256]
+    assert all(torch.equal(a, b) for a, b in zip(runs["got"], want))
+    if started >= 32:
+        monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
+        out, tk, _ = generate()
+        gone = out == -1
+        assert gone.any() and torch.equal(out[~gone], want[0][~gone]) and torch.equal(tk, torch.where(gone[-1], -1, want[1]))
+    model.close()
+
+
 @pytest.mark.parametrize("B", [8, 9, 32])
 def test_groups_whose_waits_give_up(srm, B, monkeypatch):
     """Groups wait on their own: a sample's tokens are right up to the step in which its group gives up and -1 from there on, the

@@ -345,7 +345,7 @@ def test_streams_in_turn_give_the_same_bits(srm, B):
 def test_streams_side_by_side_share_the_device(srm, B, n, monkeypatch):
     """Steps on several streams whose kernels are all still waiting: the first takes the device, a second stream half of the
     work-groups, further ones a quarter, so that four fit side by side; the same bits, also by one work-group alone, and -1
-    where their waits give up."""
+    for all samples of a launch one of whose waits gives up."""
     cfg = _config(vocab=200)
     model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
     tok = to_dev((np.arange(B) * 3 % cfg.vocab).astype(np.int32))
@@ -383,7 +383,9 @@ def test_streams_side_by_side_share_the_device(srm, B, n, monkeypatch):
     monkeypatch.setenv("SRM_ONE_KERNEL_POLLS", "0")
     steps()
     monkeypatch.delenv("SRM_ONE_KERNEL_POLLS")
-    assert all((one[1] == -1).all() for one in want["got"])
+    # (a group of the few work-groups that have started in time may find all of them there at its first look, at every wait)
+    assert any((one[1] == -1).all() for one in want["got"])
+    assert all((one[1] == -1).all() or all(torch.equal(a, b) for a, b in zip(one, (st, out, lg))) for one in want["got"])
     steps()
     for one in want["got"]:
         assert all(torch.equal(a, b) for a, b in zip(one, (st, out, lg)))
