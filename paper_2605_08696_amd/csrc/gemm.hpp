@@ -47,7 +47,8 @@ struct GemmEpi {
     float ln_eps;
     // EPI_RESID_LN (gemm_persist.hpp): EPI_RESID, and the LayerNorm (ln_g, ln_b, ln_eps) of the new rows to ln_out [M][ldo] in the
     // activation type.  ln_stats [M][column tiles]: mean and squared deviations of a row's columns in a tile; ln_words [row tiles], zero at
-    // the launch: tiles that have left theirs, and from bit 16 on those that have not waited for the others; ln_polls: how often they ask.
+    // the launch: tiles that have left theirs, from bit 8 on those that have been begun, and from bit 16 on which ones have not waited
+    // for the others; ln_polls: how often they ask.
     void *ln_out;
     float2 *ln_stats;
     unsigned *ln_words;

@@ -28,11 +28,14 @@ constexpr int kPersistLds = 160 * 1024;
 // values stay in the accumulators' registers, the tiles of a row exchange the mean and the squared deviations of their 256
 // columns (two-pass within a wavefront's 64, combined by Chan's formula) through memory, and each normalises its own columns.
 // The tiles of a row tile are worked on at the same time, next to each other on an XCD, but nothing promises that: a
-// work-group asks ln_polls times, and if some tile is still missing it leaves its columns to whoever leaves the last one.  Both
-// are one atomic on the row tile's word, so that exactly one of them does it.  (16384 x 1024, both kinds of launch, us, with a
+// work-group asks ln_polls times (kLnBegun times while some tile has not even been begun: where several streams or processes have
+// such launches, their work-groups would otherwise hold CUs that each other's wait for: decode steps of 16384 rows on three streams,
+// us per step, 9723 | 6993, LayerNorm launches 6824), and if some tile is still missing it leaves its columns to whoever leaves the
+// last one.  Both are one atomic on the row tile's word, so that exactly one of them does it.  (16384 x 1024, both kinds of launch, us, with a
 // LayerNorm launch behind | this: 98.7 | 92.9, of which the sums and the normalising are about 5, the exchange 2, the stores 5.)
 constexpr int kLnTiles = 4;                          // column tiles of a row at most
-template <typename TAct, typename BARRIER>
+constexpr unsigned kLnBegun = 32;                    // some 12 us
+template <typename BARRIER>
 __device__ __forceinline__ unsigned persist_ln_exchange(const GemmEpi &ep, const float2 *part, float2 *rows, int M, int m0, int bm, int bn,
                                                         int nbn, int tid, BARRIER &&lds_barrier)
 {
@@ -60,21 +63,20 @@ __device__ __forceinline__ unsigned persist_ln_exchange(const GemmEpi &ep, const
     unsigned *const word = ep.ln_words + bm, *const said = reinterpret_cast<unsigned *>(rows + 256);
     if (tid == 0) {
         unsigned seen = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
-        const bool last = (seen & 0xffff) == (unsigned)nbn;
-        for (unsigned polls = 0; (seen & 0xffff) != (unsigned)nbn && polls < ep.ln_polls; ++polls)
+        auto left = [&] { return (seen & 0xff) == (unsigned)nbn; };
+        const bool last = left();
+        for (unsigned polls = 0; !left() && polls < ep.ln_polls && (polls < kLnBegun || (seen >> 8 & 0xff) == (unsigned)nbn); ++polls)
             seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        said[0] = (seen & 0xffff) == (unsigned)nbn;
+        said[0] = left();
         said[1] = last ? seen >> 16 : 0;             // whose columns this work-group makes besides its own
     }
     lds_barrier();
     if (__builtin_expect(!said[0], 0)) {             // tired of waiting: what is in memory is for whoever comes last
-        __threadfence();
-        __syncthreads();
         if (tid == 0) {
-            const unsigned seen = __hip_atomic_fetch_or(word, 0x10000u << bn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            said[0] = (seen & 0xffff) == (unsigned)nbn;
+            const unsigned seen = __hip_atomic_fetch_or(word, 0x10000u << bn, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            said[0] = (seen & 0xff) == (unsigned)nbn;
         }
-        __syncthreads();
+        lds_barrier();
         if (!said[0]) return ~0u;
     }
     const unsigned others = said[1];
@@ -92,22 +94,34 @@ __device__ __forceinline__ unsigned persist_ln_exchange(const GemmEpi &ep, const
         for (int b = 0; b < kLnTiles; ++b) dev += b < nbn ? t[b].y + 256.0f * ((t[b].x - mean) * (t[b].x - mean)) : 0.0f;
         rows[tid] = make_float2(mean, 1.0f / sqrtf(dev / (float)(nbn * 256) + ep.ln_eps));
     }
+    if (others != 0 && tid == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // (of the cache that the wavefronts share)
     lds_barrier();
-    if (__builtin_expect(others != 0, 0)) {
-        __threadfence();
-        for (int b = 0; b < nbn; ++b) {
-            if (!(others >> b & 1)) continue;
-            for (int r = tid >> 6; r < 256 && m0 + r < M; r += 8) {
-                const size_t at = (size_t)(m0 + r) * ep.ldo + b * 256 + (tid & 63) * 4;
-                const float4 x = load4(static_cast<const float *>(ep.out) + at), g = load4(ep.ln_g + b * 256 + (tid & 63) * 4),
-                             c = load4(ep.ln_b + b * 256 + (tid & 63) * 4);
-                const float2 s = rows[r];
-                store4(static_cast<TAct *>(ep.ln_out) + at, make_float4((x.x - s.x) * s.y * g.x + c.x, (x.y - s.x) * s.y * g.y + c.y,
-                                                                        (x.z - s.x) * s.y * g.z + c.z, (x.w - s.x) * s.y * g.w + c.w));
+    return others;
+}
+// The columns of the tiles `others` of these rows, behind its own (whose values are registers until then): eight rows of a wavefront
+// in flight.  (One after the other, in front of its own columns, a tile took some 50 us.)
+template <typename TAct>
+__device__ __forceinline__ void persist_ln_others(const GemmEpi &ep, const float2 *rows, int M, int m0, unsigned others, int tid)
+{
+    constexpr int U = 8;
+    for (; others; others &= others - 1) {
+        const int col = __builtin_ctz(others) * 256 + (tid & 63) * 4;
+        const float4 g = load4(ep.ln_g + col), c = load4(ep.ln_b + col);
+#pragma unroll 1
+        for (int r0 = (tid >> 6) * U; r0 < 256 && m0 + r0 < M; r0 += 8 * U) {
+            float4 x[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) x[i] = load4(static_cast<const float *>(ep.out) + (int64_t)min(m0 + r0 + i, M - 1) * ep.ldo + col);
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const float2 s = rows[r0 + i];
+                if (m0 + r0 + i < M)
+                    store4(static_cast<TAct *>(ep.ln_out) + (int64_t)(m0 + r0 + i) * ep.ldo + col,
+                           make_float4((x[i].x - s.x) * s.y * g.x + c.x, (x[i].y - s.x) * s.y * g.y + c.y,
+                                       (x[i].z - s.x) * s.y * g.z + c.z, (x[i].w - s.x) * s.y * g.w + c.w));
             }
         }
     }
-    return 0;
 }
 
 template <int EPI, typename TAct, bool STORE, typename BARRIER>
@@ -271,7 +285,8 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                 part[wn * 256 + wm * WTM + (k >> 2) * 16 + (k & 3) * 4 + s_row] = kept[q];
             }
             lds_barrier();
-            if (persist_ln_exchange<TAct>(ep, part, rows, M, m0, m0 >> 8, bn, N >> 8, tid, lds_barrier) == ~0u) return;
+            const unsigned others = persist_ln_exchange(ep, part, rows, M, m0, m0 >> 8, bn, N >> 8, tid, lds_barrier);
+            if (others == ~0u) return;
             // (addresses formed anew, from an opaque copy: those of the slices' stores would be held in registers until here)
             int ln = lane;
             asm volatile("" : "+v"(ln));
@@ -293,6 +308,7 @@ __device__ __forceinline__ void persist_epilogue(f32x4_t (&acc)[8][4], unsigned 
                                                           (t * 16 + it * 4) * (int)ep.ldo * (int)sizeof(TAct), 0);
                 }
             });
+            if (__builtin_expect(others != 0, 0)) persist_ln_others<TAct>(ep, rows, M, m0, others, tid);
         } else if (inside) {
             slices(std::true_type{}, std::integral_constant<int, CHOICE_PLAIN>{});
         } else {
@@ -467,6 +483,8 @@ gemm_bf16_persist_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W,
         const bool probe = ep.clk != nullptr && v < ep.clk_blocks;
         const int vn = v + (int)gridDim.x;
         const Tile nxt = tile_at(vn);                // of zero size behind the last tile
+        if constexpr (EPI == EPI_RESID_LN)
+            if (threadIdx.x == 0) __hip_atomic_fetch_add(ep.ln_words + (cur.m0 >> 8), 0x100u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int j = 0; j < TN; ++j)                 // the accumulators start at the bias of their column
 #pragma unroll

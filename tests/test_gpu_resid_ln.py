@@ -118,6 +118,37 @@ def test_streams_with_a_cu_mask_and_captured_ones(srm, monkeypatch):
     model.close()
 
 
+def test_several_streams_at_once(srm):
+    """Steps of as many rows as fill the device on three streams at once: work-groups that find a tile of their rows not even begun
+    leave theirs to the last, with the bits of a step alone."""
+    cfg = srm_synth.tiny_config(vocab=260, d_model=1024, n_layers=4, n_heads=4, n_ctx=8, weight_dtype="bf16", seed=95)
+    model, B, n, T = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 16384, 3, 4
+    tok = to_dev((np.arange(B) % cfg.vocab).astype(np.int32))
+    ws, streams = [model.new_workspace(B) for _ in range(n)], [torch.cuda.Stream() for _ in range(n)]
+
+    def fresh():
+        return model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, 1024), device="cuda")
+
+    def steps(i, st, out, hid):
+        for t in range(T):
+            model.decode_step(B, t, tok, st, out, hidden=hid, workspace=ws[i], stream=streams[i])
+
+    alone, sets = fresh(), [fresh() for _ in range(n)]
+    torch.cuda.synchronize()
+    steps(0, *alone)
+    torch.cuda.synchronize()
+    print("many rows on three streams at once", flush=True)
+    for s in streams:
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(20_000_000)
+    for i in range(n):
+        steps(i, *sets[i])
+    torch.cuda.synchronize()
+    for got in sets:
+        assert all(torch.equal(a, b) for a, b in zip(got, alone))
+    model.close()
+
+
 def test_prefill_and_sequence_form_with_the_layernorm_in_the_residual_epilogue(srm, monkeypatch):
     """Prompts in one pass and in several, and the sequence form, against the LayerNorm launches."""
     cfg = srm_synth.tiny_config(vocab=260, d_model=1024, n_layers=3, n_heads=4, n_ctx=70, weight_dtype="bf16", seed=92)
