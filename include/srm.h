@@ -46,6 +46,7 @@
  *                        bits), and steps and passes of some ten thousand rows
  *                        of a bf16 model instead of LayerNorm made by the
  *                        projections in front of it (its sums in another order;
+ *                        not on a stream whose CU mask leaves out some CUs;
  *                        SRM_ONE_KERNEL_POLLS=n, for tests, bounds their waits);
  *     SRM_TOKEN_MIX=0    bf16 models of d_model 256 or 512, steps of 9 to about
  *                        1000 samples: the token mixing of a layer as separate

@@ -145,9 +145,9 @@ struct FewPlace {
     int arrived;             // work-groups; in the order of their XCDs:
     int at, below, same;     // this one's number, how many lie on the XCDs in front of its own and on its own
     int order;               // its number in the order of the launch
-    __device__ __forceinline__ bool near(int per) const                // its group of `per` lies on one XCD
+    __device__ __forceinline__ bool near(int per) const                // its group of `per`, a power of two, lies on one XCD
     {
-        const int first = at / per * per;
+        const int first = at & -per;
         return below <= first && first + per <= below + same;
     }
 };

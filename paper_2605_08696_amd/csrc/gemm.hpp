@@ -259,9 +259,10 @@ __device__ __forceinline__ void epi_store4(const GemmEpi &ep, int64_t row, int c
     } else {
         // Logits: written once, by far more than the L2s hold, and not read by the launch.  Nontemporal, they leave it to the operands (us,
         // ordinary | this, rows x columns x K: 300 x 32000 x 512 30.7 | 29.3, 1024: 54.7 | 53.1, 2000: 96.4 | 88.6, 3001 x 32000 x 1024
-        // 208 | 196; the step of 3001 rows with its nucleus pass behind 2064 | 2044).  It costs where such a pass follows and finds up to
-        // 256 MB of logits in memory instead of the last-level cache (1000 rows 1037.6 | 1040.6, 1500 1370 | 1374), but a choice at each
-        // store costs more (1063 | 1070, 1403 | 1413).
+        // 208 | 196).  A nucleus pass behind finds up to 256 MB of logits in memory instead of the last-level cache, which costs as much as
+        // the head gains (d = 1024, us per step: 450 rows 768.1 | 770.7, 700: 986.9 | 984.2, 1000: 1038.3 | 1041.6, 1200: 1326.5 | 1327.2, 1500:
+        // 1370.6 | 1374.5, 2000: 1477.4 | 1478.0); behind more it gains (2500: 1835.8 | 1808.2, 3001: 2064 | 2044).  A choice at each store
+        // costs more (1063 | 1070, 1403 | 1413).
         if (ep.out)
             __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w},
                                         reinterpret_cast<f32x4_t *>(reinterpret_cast<float *>(ep.out) + row * ep.ldo + col));

@@ -1209,7 +1209,7 @@ static unsigned poll_bound(unsigned otherwise, int step = 0)
 }
 // x += A W^T + bias, out = LayerNorm(x); launch: its number among the `launches` of so many rows in the pass, of which the first clears
 // the words of all.  (The last rows of a prefill, which the last layer goes on with, count anew: the words lie by the row tiles.)
-constexpr unsigned kLnPolls = 1u << 9;               // some 200 us: the tiles of a row come within a few
+constexpr unsigned kLnPolls = 1u << 9;               // some 200 us: the tiles of a row that have been begun come within a few
 static int resid_ln(const srm_model *m, Workspace &w, const void *A, const void *W, const float *bias, int64_t rows, int K, const float *g,
                     const float *b, int launch, int launches, hipStream_t st)
 {

@@ -182,8 +182,8 @@ __global__ void __launch_bounds__(kStackThreads) stack_kernel(StackArgs p)
     const bool pure = __builtin_amdgcn_readfirstlane(who[2]) || alone;
     // the work-groups of a group, and the parts of a phase that this one does: part v of kStackPer, and every `members`-th behind it
     const int members = alone ? 1 : __builtin_amdgcn_readfirstlane(who[0]);
-    const int c0 = alone ? 0 : at / members, c1 = alone ? kStackGroups : c0 + 1;
-    const int v0 = alone ? 0 : at % members;
+    const int c0 = alone ? 0 : at >> __builtin_ctz(members), c1 = alone ? kStackGroups : c0 + 1;
+    const int v0 = alone ? 0 : at & (members - 1);
 
     // LDS only: loads and stores of global memory stay in flight across it
     auto barrier = [] {
