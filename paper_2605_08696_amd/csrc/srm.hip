@@ -1187,6 +1187,7 @@ static bool whole_device_stream(hipStream_t st)
 // launches | this: decode step of the large model 13001 rows 5946 | 5763, 16384: 6727 | 6462, prefill 256 x 128 10946 | 10534, d = 512, state in
 // 16 bits, 30001 rows 2976 | 2825; a projection of 16384 x 1024 and its LayerNorm 80.5 + 18.2 | 92.9.  (Smaller launches, in tiles of
 // one round, stay as they are: up to 12 288 rows the LayerNorm launches read the next matrices ahead, worth 3 % at 3001 rows.)
+// (Models without projections have the same down-projection in prefill and sequence form; theirs has not been made.)
 // SRM_LN_ON_LOAD=0 in the environment keeps the LayerNorm launches, and so does a stream whose CU mask leaves out some CUs: the tiles of a
 // row are not worked on at the same time there, and each waits in vain (16384 rows, us per step of 192 | 128 | 64 CUs: 14485 |
 // 13906 | 26490, with LayerNorm launches 10239 | 10561 | 19267).
@@ -2687,7 +2688,8 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
 // 1024: 317 | 253, 1025: 374 | 327, 2048: 470 | 418, 3000: 639 | 599, 4096: 745 | 754.  Up to four rows few.hpp's steps are
 // shorter (98).  A width of 512 is what the kernel's registers and LDS were laid out for; at 1024 every XCD would read 21 MB of
 // weights per layer, 22 us at the 0.95 TB/s an XCD gets, where a layer of 37 rows takes 25.  Six layers: as in few_ok, for the
-// results of shallower models.
+// results of shallower models.  (A width of 256, models without projections and combined heads would be forms of its own, which
+// have not been made or measured.)
 // Streams that launch such steps side by side take half or a quarter of the work-groups each (few_others), same bits.  us per step, no
 // logits, all streams together, of 1 | 2 | 4 streams, a thread each: 37 rows 119 | 91 | 137, step kernels 178 | 99 | 99; 300: 169 | 145 |
 // 119, 231 | 132 | 92; 1024: 235 | 213 | 190, 300 | 215 | 205.  In turn, each behind a wait for the one before: 37 rows 136 | 137 | 136

@@ -267,6 +267,31 @@ def test_a_wait_that_gives_up_leaves_marked_tokens(srm, monkeypatch):
 
 
 @pytest.mark.parametrize("how", [dict(), dict(temperature=0.7, seed=3), dict(temperature=0.7, top_p=0.6, seed=3)])
+@pytest.mark.parametrize("rows", [300, 256])
+def test_ragged_generation_with_an_end_token(srm, rows, how):
+    """srm_generate_ragged gives the tokens, positions and states of single ragged steps: samples that are idle, that reach the end of
+    the context and that emit the end token, whole and in slices."""
+    cfg = _config(vocab=40, n_ctx=12)
+    model, B, G, eos = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 300, 6, 7
+    ws = torch.empty(model.workspace_bytes(rows) + 256, dtype=torch.uint8, device="cuda")
+    lg = torch.empty((B, cfg.vocab), device="cuda")
+    start = to_dev((np.arange(B) * 7 % cfg.vocab).astype(np.int32))
+    pos0 = (torch.arange(B, device="cuda") % 14 - 1).to(torch.int32)
+    st, tk, pos, want = model.new_state(B), start.clone(), pos0.clone(), []
+    for g in range(G):
+        model.decode_step_ragged(B, pos, tk, st, tk, advance=True, logits=lg, workspace=ws, **how)
+        pos = torch.where(tk == eos, -1, pos).to(torch.int32)          # (single steps know no end token)
+        want.append(tk.clone())
+    want = torch.stack(want)
+    assert (want == -1).any() and (want == eos).any()
+    st2, tk2, pos2, out = model.new_state(B), start.clone(), pos0.clone(), torch.full((G, B), -7, dtype=torch.int32, device="cuda")
+    print(f"ragged generation through {rows} rows {how}", flush=True)
+    assert _launches(lambda: model.generate_ragged(B, G, pos2, tk2, st2, out, eos_id=eos, logits=lg, workspace=ws, **how)) == G * (-(-B // rows))
+    assert torch.equal(out, want) and torch.equal(pos2, pos) and torch.equal(tk2, want[-1]) and torch.equal(st2, st)
+    model.close()
+
+
+@pytest.mark.parametrize("how", [dict(), dict(temperature=0.7, seed=3), dict(temperature=0.7, top_p=0.6, seed=3)])
 @pytest.mark.parametrize("rows", [400, 256])
 def test_a_generation_whose_wait_gives_up(srm, rows, how, monkeypatch):
     """A wait that gives up in one step of a generation only, forced from the host: the tokens from that step on are -1, also where
