@@ -111,10 +111,10 @@
  *                        d_model 512 with projections, mlp_expansion 4, one
  *                        matrix per head and at least six layers run their
  *                        layers as one kernel in the same way: it takes the
- *                        whole device, or half or a quarter of it where such
- *                        steps of other streams are running or waiting (several
- *                        streams of some hundred samples each get more done
- *                        with =0; so do processes: three that step 300 samples
+ *                        whole device, or up to 1024 samples half or a quarter
+ *                        of it where such steps of other streams are running or
+ *                        waiting (several streams of some hundred samples each
+ *                        get more done with =0; so do processes: three that step 300 samples
  *                        each at a time 0.63 ms per step, 0.33 with =0).
  *                        Not with SRM_TOKEN_MIX, SRM_FUSE_MIXER or
  *                        SRM_LN_ON_LOAD set, whose kernels it replaces.

@@ -2691,12 +2691,15 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
 // results of shallower models.  (A width of 256, models without projections and combined heads would be forms of its own, which
 // have not been made or measured.)
 // Streams that launch such steps side by side take half or a quarter of the work-groups each (few_others), same bits.  us per step, no
-// logits, all streams together, of 1 | 2 | 4 streams, a thread each: 37 rows 119 | 91 | 137, step kernels 178 | 99 | 99; 300: 169 | 145 |
-// 119, 231 | 132 | 92; 1024: 235 | 213 | 190, 300 | 215 | 205.  In turn, each behind a wait for the one before: 37 rows 136 | 137 | 136
-// (by half and by a quarter 186 | 284), 300: 186 | 185 | 184 (271 | 438), 1024: 250 | 250 | 250 (370 | 609).
+// logits, all streams together, of 1 | 2 | 4 streams, a thread each: 37 rows 119 | 91 | 75 to 137, step kernels 178 | 99 | 61 to 99 (how the
+// runtime deals the streams to its queues); 300: 169 | 145 | 119, 231 | 132 | 92; 1024: 235 | 213 | 190, 300 | 215 | 205.  In turn, each
+// behind a wait for the one before: 37 rows 136 | 137 | 136 (by half and by a quarter 186 | 284), 300: 186 | 185 | 184 (271 | 438), 1024:
+// 250 | 250 | 250 (370 | 609).  Larger steps take the whole device one after the other: of 2 | 3 | 4 streams, shared | this, 1100 rows -
+// | 314 | 444, - | 302 | 303; 1536: - | 330 | 261, - | 300 | 299; 2048: 346 | 396 | 319 to 555, 358 | 358 | 359; 3000: - | 574 | 803, - | 504 | 506.
 // Beside other work of the process (300 rows, us per step and calls per second of the other stream, step kernels | this; large model):
 // prefills of 256 x 128 3666 and 93 | 554 and 67; decode steps of 16384 samples 3065 and 149 | 555 and 106; of 3001 with top-p 594
 // and 437 | 235 and 171; no arrival was given up (longest step 1.5 ms).
+constexpr int64_t kStackSharedRows = 1024;
 constexpr int64_t kStackMinRows = 5, kStackMaxRows = 3072;
 static_assert(kStackMaxRows <= (int64_t)kStackGroups * kStackMaxPer, "their positions are kept in LDS");
 // Polls of the arrival, some 0.1 ms: beside other work of the process as good as any longer (300 rows beside prefills, us per step with
@@ -2749,7 +2752,7 @@ static int stack_layers(srm_model *m, const DecodeArgs &d, const Workspace &w, i
     a.dead = d.gave_up ? d.gave_up : a.left + 1;     // (that of a call stays set)
     a.max_polls = poll_bound(1u << 21, d.step);      // a second or two
     a.arrive_polls = stack_arrive_polls;
-    const int others = few_others(m->device, st), blocks = kStackBlocks / (others == 0 ? 1 : others == 1 ? 2 : 4);
+    const int others = nb > kStackSharedRows ? 0 : few_others(m->device, st), blocks = kStackBlocks / (others == 0 ? 1 : others == 1 ? 2 : 4);
     int starting = kStackBlocks;                     // work-groups that are not withdrawn from the start
     const char *sw = getenv("SRM_ONE_KERNEL_STEP");
     if (sw && sw[0] == '2') starting = sw[1] == ':' ? atoi(sw + 2) : 0;
