@@ -106,7 +106,7 @@
  *                        behind it) and chooses the same tokens unless two scores
  *                        tie within it, but need not have the same bits; with =0
  *                        it has (see srm_generate for its own one-kernel path).
- *                        Decode steps of 5 to 3072 samples (uniform and ragged,
+ *                        Decode steps of 5 to 2304 samples (uniform and ragged,
  *                        and those of the generate calls) of a bf16 model of
  *                        d_model 512 with projections, mlp_expansion 4, one
  *                        matrix per head and at least six layers run their

@@ -2684,8 +2684,9 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
     return r;
 }
 // Which steps.  Measured per decode step with logits (us, step kernels | layers as one kernel), d = 512, 8 layers, 32000 tokens: 5
-// rows 144 | 118, 9: 173 | 119, 37: 184 | 122, 128: 193 | 133, 129: 207 | 152, 300: 243 | 176, 512: 256 | 207, 513: 294 | 217,
-// 1024: 317 | 253, 1025: 374 | 327, 2048: 470 | 418, 3000: 639 | 599, 4096: 745 | 754.  Up to four rows few.hpp's steps are
+// rows 139 | 120, 9: 170 | 122, 37: 182 | 122, 128: 190 | 133, 129: 204 | 154, 300: 241 | 178, 512: 256 | 207, 513: 293 | 222, 1024: 316 |
+// 256, 1025: 376 | 334, 1536: 407 | 343, 1537: 416 | 418, 1700: 428 | 416, 2048: 437 | 408, 2304: 525 | 476; then a group's six tiles are of
+// four blocks and not of three: 2305: 532 | 565, 2560: 536 | 579, 3000: 579 | 582, 3072: 574 | 578.  Up to four rows few.hpp's steps are
 // shorter (98).  A width of 512 is what the kernel's registers and LDS were laid out for; at 1024 every XCD would read 21 MB of
 // weights per layer, 22 us at the 0.95 TB/s an XCD gets, where a layer of 37 rows takes 25.  Six layers: as in few_ok, for the
 // results of shallower models.  (A width of 256, models without projections and combined heads would be forms of its own, which
@@ -2700,7 +2701,7 @@ static StackMem stack_carve(const srm_model *m, const Workspace &w, const StackP
 // prefills of 256 x 128 3666 and 93 | 554 and 67; decode steps of 16384 samples 3065 and 149 | 555 and 106; of 3001 with top-p 594
 // and 437 | 235 and 171; no arrival was given up (longest step 1.5 ms).
 constexpr int64_t kStackSharedRows = 1024;
-constexpr int64_t kStackMinRows = 5, kStackMaxRows = 3072;
+constexpr int64_t kStackMinRows = 5, kStackMaxRows = 2304;
 static_assert(kStackMaxRows <= (int64_t)kStackGroups * kStackMaxPer, "their positions are kept in LDS");
 // Polls of the arrival, some 0.1 ms: beside other work of the process as good as any longer (300 rows beside prefills, us per step with
 // 7 | 0.8 | 0.2 | 0.1 | 0.04 | 0.01 ms: 564 | 561 | 560 | 560 | 593 | 593, 1024 rows beside 3001 with top-p 279 | 279 | 278 | 278 | 282 | 351).  It

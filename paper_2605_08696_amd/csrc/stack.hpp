@@ -42,7 +42,7 @@
 
 constexpr int kStackBlocks = 256, kStackGroups = 8, kStackPer = kStackBlocks / kStackGroups, kStackThreads = 512;
 constexpr int kStackLeast = 32;                      // work-groups that go on without the others (four of a group) once tired of waiting
-constexpr int kStackMaxPer = 384;                    // rows of a group: their positions are kept in LDS
+constexpr int kStackMaxPer = 288;                    // rows of a group: their positions are kept in LDS
 constexpr int kStackWordBytes = kStackBlocks * 8 + kStackGroups * 128 + 256;
 struct StackArgs {
     const FewLayer *layers;                          // [L], device

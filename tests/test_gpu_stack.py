@@ -59,8 +59,8 @@ def _steps(model, cfg, toks, positions=None, garbage=None, **how):
 
 # rows at the borders of the plan: whole and part groups of 16, a group's tile of one to four blocks of 16, two members on 32
 # columns with tiles of three and four blocks, several tiles to a member
-# (2049: four tiles become six; 3072: the most rows, whose positions fill their place in LDS); the smallest step, a second group of one row
-ROWS = [5, 9, 16, 17, 33, 128, 129, 300, 512, 513, 1024, 1025, 2048, 2049, 2100, 3072]
+# (2049: four tiles become six; 2304: the most rows, whose positions fill their place in LDS); the smallest step, a second group of one row
+ROWS = [5, 9, 16, 17, 33, 128, 129, 300, 512, 513, 1024, 1025, 2048, 2049, 2100, 2304]
 
 
 @pytest.mark.parametrize("B", ROWS)
@@ -92,7 +92,7 @@ def test_layers_in_one_kernel_match_oracle_and_step_kernels(srm, orc_mod, B, var
     model.close()
 
 
-@pytest.mark.parametrize("B,launches", [(4, 0), (5, 1), (3072, 1), (3073, 0)])
+@pytest.mark.parametrize("B,launches", [(4, 0), (5, 1), (2304, 1), (2305, 0)])
 def test_where_the_kernel_ends(srm, B, launches):
     cfg = _config(vocab=200)
     model = srm.Model(cfg, srm_synth.make_weights(cfg))
@@ -102,7 +102,7 @@ def test_where_the_kernel_ends(srm, B, launches):
     model.close()
 
 
-@pytest.mark.parametrize("B", [5, 9, 130, 513, 1100, 3072])
+@pytest.mark.parametrize("B", [5, 9, 130, 513, 1100, 2304])
 def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
     """A launch of whose work-groups none has started in time is done by one of them: forced from the host, by arrivals that are
     withdrawn from the start, then by a wait of one look, which ends either way."""
@@ -121,7 +121,7 @@ def test_one_work_group_alone_gives_the_same_bits(srm, B, monkeypatch):
     model.close()
 
 
-@pytest.mark.parametrize("B", [5, 300, 513, 3072])
+@pytest.mark.parametrize("B", [5, 300, 513, 2304])
 @pytest.mark.parametrize("started", [7, 8, 17, 35, 100, 129, 255])
 def test_work_groups_that_have_started_do_without_the_others(srm, B, started, monkeypatch):
     """Some work-groups do not start in time (their arrivals are withdrawn from the start): the others form groups of one to
@@ -139,7 +139,7 @@ def test_work_groups_that_have_started_do_without_the_others(srm, B, started, mo
     model.close()
 
 
-@pytest.mark.parametrize("B", [5, 33, 300, 513, 1100, 3072])
+@pytest.mark.parametrize("B", [5, 33, 300, 513, 1100, 2304])
 def test_groups_that_do_not_share_a_cache(srm, B, monkeypatch):
     """Groups of work-groups on different XCDs, as they come about where the XCDs do not get as many work-groups each: what they
     exchange is written through the caches, the bits are the same, and the tokens -1 where their waits give up."""
@@ -217,7 +217,7 @@ def test_generation_and_slices(srm):
     model.close()
 
 
-@pytest.mark.parametrize("B,rows", [(600, 256), (258, 256), (3080, 3072), (3075, 256)])
+@pytest.mark.parametrize("B,rows", [(600, 256), (258, 256), (2310, 2304), (2307, 256)])
 def test_generation_in_slices(srm, B, rows):
     """srm_generate through a workspace of fewer rows: every step by the kernels of its slices, the last of which may be too small or
     the only one small enough for the kernel of all layers, as single steps through that workspace take them, on every stream."""
@@ -225,7 +225,7 @@ def test_generation_in_slices(srm, B, rows):
     model, G = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True)), 4
     start = to_dev((np.arange(B) * 7 % cfg.vocab).astype(np.int32))
     n = model.workspace_bytes(rows) + 256                              # (the step counters)
-    stacks = sum(5 <= min(rows, B - b) <= 3072 for b in range(0, B, rows))
+    stacks = sum(5 <= min(rows, B - b) <= 2304 for b in range(0, B, rows))
     st, tk, steps = model.new_state(B), start.clone(), []
     ws = torch.empty(n, dtype=torch.uint8, device="cuda")
     for g in range(G):
