@@ -1187,14 +1187,24 @@ static bool whole_device_stream(hipStream_t st)
 // launches | this: decode step of the large model 13001 rows 5946 | 5763, 16384: 6727 | 6462, prefill 256 x 128 10946 | 10534, d = 512, state in
 // 16 bits, 30001 rows 2976 | 2825; a projection of 16384 x 1024 and its LayerNorm 80.5 + 18.2 | 92.9.  (Smaller launches, in tiles of
 // one round, stay as they are: up to 12 288 rows the LayerNorm launches read the next matrices ahead, worth 3 % at 3001 rows.)
+// Not where the tiles of a row would lie in two rounds of the chip, and the first of them wait for what is not begun until they have
+// left (27000 rows of 1024, us per step, LayerNorm launches | this: 11670 | 17236, with all that is left to the last ones 13960; 53000 of
+// 512: 5128 | 5840).  Tiles are dealt in groups of eight row tiles, in line or, where that divides them evenly, an eighth to each XCD.
 // (Models without projections have the same down-projection in prefill and sequence form; theirs has not been made.)
 // SRM_LN_ON_LOAD=0 in the environment keeps the LayerNorm launches, and so does a stream whose CU mask leaves out some CUs: the tiles of a
 // row are not worked on at the same time there, and each waits in vain (16384 rows, us per step of 192 | 128 | 64 CUs: 14485 |
 // 13906 | 26490, with LayerNorm launches 10239 | 10561 | 19267).
+static bool resid_ln_rounds_ok(int64_t rows, int d)
+{
+    const int64_t nbn = d / 256, n = cdiv(rows, 256) * nbn, group = 8 * nbn, cus = device_cus();
+    if (nbn == 1 || n <= cus) return true;
+    return n % 8 ? cus % group == 0 : (cus / 8) % group == 0 && n / 8 % group == 0;
+}
 static bool resid_ln_ok(const srm_model *m, int64_t rows, int64_t call_rows, hipStream_t st)
 {
     if (m->wsize != 2 || m->noproj || m->d % 256 || m->d / 256 > kLnTiles || rows <= 0 || rows >= (1 << 30)) return false;
     if ((int64_t)2 * m->L * cdiv(rows, 256) > 64 + rows) return false;           // (the words lie in w.slow)
+    if (!resid_ln_rounds_ok(rows, m->d)) return false;
     for (const int K : {m->dm, m->ff})
         if (slices_ok(std::max(rows, call_rows), m->d, K) || choose_one_round_tile(rows, m->d, K, false, false, true) >= 0 ||
             choose_tile(rows, m->d, K, 64) != 0 || !persist_ok(rows, m->d, K) || K % 64)

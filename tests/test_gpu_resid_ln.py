@@ -118,6 +118,29 @@ def test_streams_with_a_cu_mask_and_captured_ones(srm, monkeypatch):
     model.close()
 
 
+@pytest.mark.parametrize("d,B,fused", [(1024, 16384, True), (1024, 27000, False), (1024, 27300, True), (1024, 32768, True), (768, 17300, True),
+                                       (768, 38000, False), (512, 53000, False), (512, 53300, True)])
+def test_tiles_of_a_row_in_one_round_of_the_chip(srm, d, B, fused, monkeypatch):
+    """More tiles than fit the device at once: where those of a row are not all of one round the LayerNorm launches stay."""
+    cfg = srm_synth.tiny_config(vocab=260, d_model=d, n_layers=1, n_heads=4, n_ctx=4, weight_dtype="bf16", seed=96)
+    model = srm.Model(cfg, srm_synth.make_weights(cfg, stress=True))
+    tok, ws = to_dev((np.arange(B) % cfg.vocab).astype(np.int32)), model.new_workspace(B)
+
+    def step():
+        st, out, hid = model.new_state(B), torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, d), device="cuda")
+        model.decode_step(B, 0, tok, st, out, hidden=hid, workspace=ws)
+        torch.cuda.synchronize()
+        return hid
+
+    print(f"rounds of the chip d={d} B={B}", flush=True)
+    one = step()
+    monkeypatch.setenv(SWITCH, "0")
+    many = step()
+    assert torch.equal(one, many) != fused
+    assert rel_err_rows(one.cpu().numpy(), many.cpu().numpy()) <= 2e-2
+    model.close()
+
+
 def test_several_streams_at_once(srm):
     """Steps of as many rows as fill the device on three streams at once: work-groups that find a tile of their rows not even begun
     leave theirs to the last, with the bits of a step alone."""
